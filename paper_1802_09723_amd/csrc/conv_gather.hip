@@ -117,7 +117,7 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
     static_assert(NT % 8 == 0 && NT <= 32, "NT: two sub-tiles per consumer wavefront, slot index in 5 bits");
     static_assert(LIST_CAP >= 2 * NT, "a ranking round holds at least two work units");
 
-    // LDS: [weights x nbuf_a][windows (TERMS planes) x 2][K-pair table]
+    // LDS: [weights x nbuf_a][windows (TERMS planes) x 2][window offset table]
     extern __shared__ uint4 smem[];
     unsigned char* lds = reinterpret_cast<unsigned char*>(smem);
     const int nbuf_a = g.nslab > 1 ? 2 : 1;  // a single slab of weights is staged once and serves every unit
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
     // depend on the work list.  A dense launch starts their loads at once; a delta launch after the loads
     // of the list phase, which would otherwise queue behind them (loads return in order), and not at all in
     // a workgroup that gets no unit.
-    const int2* utab = reinterpret_cast<const int2*>(offtab) + g.nq * 4;
+    const int2* utab = reinterpret_cast<const int2*>(offtab + conv_tab_words(g));
     int2 ut[MAXU];
     auto early_loads = [&]() {
         if (!producer) return;
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
         }
     };
     if (MODE == MODE_DENSE) early_loads();
-    for (int e = tid; e < g.nq * 4; e += WG_THREADS)  // K-pair table, the same for every slab
+    for (int e = tid; e < conv_tab_words(g) / 2; e += WG_THREADS)  // window offset table, the same for every slab
         tab[e] = reinterpret_cast<const int2*>(offtab)[e];
 
     // ---- how many sub-tiles are active? -------------------------------------------------------------
@@ -361,7 +361,8 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
     const int j = lane & 15, half = (lane >> 4) & 1, khalf = lane >> 5;
     // lane-constant window position of its output position (tap 0,0)
     const int off_lane = (((j >> 2) * g.str_y) * g.ww + (j & 3) * g.str_x) * g.sc * 16;
-    const int rot_lane = g.rot_a * (j >> 2) + g.rot_b * (j & 3);  // this position's share of the chunk rotation
+    // this lane's rows of the window offset table: its position's share of the chunk rotation, its K pairs
+    const int2* tp = tab + (((g.rot_a * (j >> 2) + g.rot_b * (j & 3)) & (g.rot_p - 1)) * 2 + khalf) * g.nq;
     sc_t* y = static_cast<sc_t*>(y_v);
     const sc_t* bias = static_cast<const sc_t*>(bias_v);
     // channel (within the filter group) of register 4*gq of block c; the 4 registers are 4 consecutive channels
@@ -426,7 +427,7 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
         if (r0 == 0) early_loads();
         lds_barrier();  // the list is published
     } else if (r0 == 0) {
-        lds_barrier();  // (the K-pair table is published)
+        lds_barrier();  // (the window offset table is published)
     }
 
 
@@ -585,35 +586,38 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
         // read from LDS into a second register set (the sets swap roles every step, nothing is copied) and
         // the table entries of step q+2 are fetched, so that no address waits for a table read.  The reads
         // are issued one by one between the MFMAs: a wavefront that issues them in a batch leaves the
-        // matrix pipeline idle meanwhile.
-        auto k_loop = [&]<int NPA, int T>(const unsigned char* aw, const unsigned char* bw) {  // T: terms multiplied
-            const unsigned char* ap = aw + lane * 16;
+        // matrix pipeline idle meanwhile.  One consumer per SIMD issues everything, so what is not a matrix
+        // instruction or an operand read is kept off this loop: a pair's window offset comes ready from the table
+        // (one add per operand), the weights' addresses are one base per channel block with immediate offsets (67
+        // instead of 91 instructions per two K steps of 16 matrix instructions; the five-layer stack 687 -> 674 us at
+        // 512 streams, 84.2 -> 80.3 us at one).
+        auto k_loop = [&]<int NPA, int T>(unsigned int aw, unsigned int bw) {  // LDS offsets; T: terms multiplied
+            const unsigned int ap = aw + lane * 16;
             // (slots beyond the allocated ones are never in use; their lanes read slot 0 instead of running
             // off the buffer)
-            const unsigned char* bp = bw + (2 * cw + half < g.nt ? 2 * cw + half : 0) * g.slot_bytes;
-            const int pstride = NPA > 1 ? 8 * g.slot_bytes : 0;
-            const int2* tp = tab + khalf;
+            const unsigned int bp = bw + (2 * cw + half < g.nt ? 2 * cw + half : 0) * g.slot_bytes + off_lane;
+            const unsigned int pstride = NPA > 1 ? 8 * g.slot_bytes : 0;
             constexpr int NB1 = T == 2 ? NPA : 1;
             struct Ops {
                 uint4 a[2][NCB], b0[2][NPA], b1[2][NB1];
             };
             constexpr int N_MFMA = 2 * NCB * NPA * T;
             constexpr int N_READ = 2 * (NCB + NPA * T);
-            auto load_tab = [&](int q, int2(&t)[2]) {
-                t[0] = tp[4 * q];  // tap's byte offset; rotated chunk | mask << 8
-                t[1] = tp[4 * q + 2];
-            };
-            auto fetch = [&](int q, const int2(&t)[2], Ops& o) {
+            auto fetch = [&](int q, const int2& t, Ops& o) {
+#pragma unroll
+                for (int c = 0; c < NCB; ++c) {
+                    unsigned int ao = ap + (unsigned int)(c * nq2 + 2 * q) * 1024u;
+                    asm("" : "+v"(ao));  // (one base register for the step's two fragments)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) o.a[h][c] = *reinterpret_cast<const uint4*>(lds + ao + h * 1024);
+                }
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const int off = off_lane + t[h].x + ((((t[h].y & 0xFF) + rot_lane) & (t[h].y >> 8)) << 4);
-#pragma unroll
-                    for (int c = 0; c < NCB; ++c)
-                        o.a[h][c] = *reinterpret_cast<const uint4*>(ap + (c * nq2 + 2 * q + h) * 1024);
+                    const unsigned int off = bp + (unsigned int)(h ? t.y : t.x);
 #pragma unroll
                     for (int p = 0; p < NPA; ++p) {
-                        o.b0[h][p] = *reinterpret_cast<const uint4*>(bp + off + p * pstride);
-                        if (T == 2) o.b1[h][p] = *reinterpret_cast<const uint4*>(bp + plane_bytes + off + p * pstride);
+                        o.b0[h][p] = *reinterpret_cast<const uint4*>(lds + off + p * pstride);
+                        if (T == 2) o.b1[h][p] = *reinterpret_cast<const uint4*>(lds + plane_bytes + off + p * pstride);
                     }
                 }
             };
@@ -630,8 +634,8 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
             };
             // one K step: multiply `cur`, read step q1 (table entries `t`) into `nxt`, fetch the table entries
             // of step q2 into `tn`; operand sets and table registers swap roles every step, nothing is copied
-            auto step = [&](const Ops& cur, Ops& nxt, const int2(&t)[2], int2(&tn)[2], int q1, int q2) {
-                load_tab(q2, tn);
+            auto step = [&](const Ops& cur, Ops& nxt, const int2& t, int2& tn, int q1, int q2) {
+                tn = tp[q2];
                 fetch(q1, t, nxt);
                 multiply(cur);
                 // issue order: the table read, then MFMAs with the operand reads spread between them
@@ -639,11 +643,10 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
                 sched_interleave<0, N_MFMA, N_READ>();
             };
             Ops o0, o1;
-            int2 ta[2], tb[2];
+            int2 ta, tb = tp[0];
             const int qmax = g.nq - 1;
-            load_tab(0, tb);
             fetch(0, tb, o0);
-            load_tab(min(1, qmax), ta);
+            ta = tp[min(1, qmax)];
             for (int q = 0; q < g.nq; q += 2) {
                 step(o0, o1, ta, tb, min(q + 1, qmax), min(q + 2, qmax));
                 if (q + 1 < g.nq) step(o1, o0, tb, ta, min(q + 2, qmax), min(q + 3, qmax));
@@ -655,8 +658,8 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
             // and this wavefront's own stores and loads of stored projections (previous / this unit) need not
             // have completed -- __syncthreads() would wait for all of them.
             asm volatile("s_barrier" ::: "memory");
-            const unsigned char* aw = lds + (nbuf_a == 2 ? (gs & 1) : 0) * a_bytes;
-            const unsigned char* bw = bbase + (gs & 1) * b_bytes;
+            const unsigned int aw = (unsigned int)((nbuf_a == 2 ? (gs & 1) : 0) * a_bytes);
+            const unsigned int bw = (unsigned int)(nbuf_a * a_bytes + (gs & 1) * b_bytes);
             ++gs;
             if (TERMS == 2 && !full) {
                 if (nact > 1) {
@@ -838,7 +841,7 @@ hipError_t launch_shape(int ncb, int nt, const void* src0, const void* src1, con
 
 size_t conv_lds_bytes(const ConvGeom& g, int ncb, int nt, int terms) {
     return (size_t)(g.nslab > 1 ? 2 : 1) * (size_t)ncb * 2 * g.nq * 1024 + 2 * (size_t)terms * nt * g.slot_bytes +
-           (size_t)g.nq * 4 * sizeof(int2);
+           (size_t)conv_tab_words(g) * sizeof(int);
 }
 
 hipError_t launch_conv(int dtype, int mode, int ncb, int nt, int terms, const void* src0, const void* src1,

@@ -180,31 +180,27 @@ rrm_status pack_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
     const rrm_shape& s = L->shape;
     ConvGeom& g = L->cg;
     const int ntaps = s.kh * g.kw_eff;
-    // K-pair table of a slab (the same for every slab), two words per pair:
-    //   [0] LDS byte offset of the tap's window position (+ the chunk's, for chunks that are not rotated)
-    //   [1] rotated chunks: (chunk + the tap's rotation term) mod rot_p | (rot_p - 1) << 8; others 0
-    // Padded pairs point at offset 0 and carry zero weights.
-    std::vector<int> tab((size_t)g.nq * 4 * 2, 0);
-    for (int e = 0; e < ntaps * g.sc && e < g.nq * 4; ++e) {
-        const int cc = e / ntaps, tap = e % ntaps;
-        const int ky = tap / g.kw_eff, ku = tap % g.kw_eff;
-        const int hp = ky * g.ww + ku;
-        if (cc < g.rot_p) {
-            const int rt = (g.rot_a * (ky / g.str_y) + g.rot_b * (ku / g.str_x)) & (g.rot_p - 1);
-            tab[2 * e] = hp * g.sc * 16;
-            tab[2 * e + 1] = ((cc + rt) & (g.rot_p - 1)) | ((g.rot_p - 1) << 8);
-        } else {
-            tab[2 * e] = hp * g.sc * 16 + cc * 16;
-            tab[2 * e + 1] = 0;
+    // Window offsets of a slab's K pairs (the same for every slab), one table per rotation r of the reading lane's
+    // position: LDS byte offset of the pair's chunk relative to the lane's window position,
+    //   [r][pair & 1][K step] x (pair >> 1 & 1),
+    // so that a lane finds the two pairs of its half of a K step in one 8-byte word and adds nothing but its own
+    // window position.  Padded pairs point at offset 0 and carry zero weights.
+    std::vector<int> tab((size_t)conv_tab_words(g), 0);
+    for (int r = 0; r < g.rot_p; ++r)
+        for (int e = 0; e < ntaps * g.sc && e < g.nq * 4; ++e) {
+            const int cc = e / ntaps, tap = e % ntaps;
+            const int ky = tap / g.kw_eff, ku = tap % g.kw_eff;
+            int slot = cc;  // the chunk's slot within the window position
+            if (cc < g.rot_p) slot = (cc + r + g.rot_a * (ky / g.str_y) + g.rot_b * (ku / g.str_x)) & (g.rot_p - 1);
+            tab[(((size_t)r * 2 + (e & 1)) * g.nq + e / 4) * 2 + (e >> 1 & 1)] = ((ky * g.ww + ku) * g.sc + slot) * 16;
         }
-    }
     // Staging table, appended: what staged unit v = (slot*wpos + hp)*sc + cs of a workgroup holds, two
     // words per unit:
     //   [0] slot | window row << 5 | window column << 13 | (chunk missing in the last slab) << 21
     //   [1] source byte offset relative to the window origin at slab 0: (row*src_w + column)*pos_bytes + chunk*16
     const int n_units = g.nt * g.wpos * g.sc;
     tab.resize(tab.size() + (size_t)n_units * 2, 0);
-    int* ut = tab.data() + (size_t)g.nq * 4 * 2;
+    int* ut = tab.data() + conv_tab_words(g);
     for (int v = 0; v < n_units; ++v) {
         const int r = v / g.sc, cs = v % g.sc;
         const int slot = r / g.wpos, hp = r % g.wpos;
@@ -264,9 +260,7 @@ rrm_status pack_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
 // for the 16 positions of a sub-tile should hit 16 different 16-byte bank groups of the 256-byte bank
 // row.  The rotation coefficients are chosen by exhaustive search over the layer's taps.
 void choose_rotation(ConvGeom& t, int ntaps) {
-    int P = 1;
-    while (P * 2 <= t.sc) P *= 2;
-    t.rot_p = P;
+    const int P = t.rot_p;
     t.rot_a = t.rot_b = 0;
     t.magic_sy = magic_for(t.str_y);
     t.magic_sx = magic_for(t.str_x);
@@ -316,6 +310,8 @@ bool conv_try_shape(ConvGeom& g, int terms, int wg_cb, int nt, int ntaps, long l
         t.pitch = pitch_for(sc);
         t.slot_bytes = t.wpos * t.pitch;
         t.nq = (ntaps * sc + 3) / 4;
+        t.rot_p = 1;  // the largest power of two that the slab's chunks hold
+        while (t.rot_p * 2 <= sc) t.rot_p *= 2;
         if ((long long)conv_lds_bytes(t, wg_cb, nt, terms) > budget) continue;
         if ((long long)nt * t.wpos * sc > max_units) continue;  // staged units per thread are bounded
         t.magic_sc[0] = t.magic_sc[1] = magic_for(sc);

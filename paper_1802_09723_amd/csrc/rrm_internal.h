@@ -106,8 +106,8 @@ struct ConvGeom {
     int slot_bytes;      // wpos*pitch: LDS bytes of one sub-tile's window
     // Bank spreading: within a staged position the first rot_p chunks (a power of two) are rotated by
     // rot_a * (row / str_y) + rot_b * (column / str_x), so that the 16 positions of a sub-tile read
-    // different LDS banks for the same (tap, chunk); the reader splits the rotation into a per-lane and a
-    // per-tap term (the tap's term is folded into the K-pair table).
+    // different LDS banks for the same (tap, chunk).  The window offset table holds the offsets of all K pairs for
+    // every value of a lane's own share of the rotation.
     int rot_p, rot_a, rot_b;
     unsigned int magic_sy, magic_sx;  // reciprocals of str_y, str_x
     int last_sc;         // chunks present in the last slab
@@ -189,6 +189,8 @@ hipError_t launch_scan(int dtype, const void* x_t, void* x_snap, void* d0, void*
 hipError_t launch_scan_fused(const FusedSrc& src, void* x_snap, void* d0, unsigned long long* bitmap, unsigned int* marks,
                              const ScanGeom& g, DevStats* stats, hipStream_t s);
 
+// words of the window offset table: (rotations) x (K pairs of a slab, whole K steps)
+__host__ __device__ inline int conv_tab_words(const ConvGeom& g) { return g.rot_p * g.nq * 4; }
 size_t conv_lds_bytes(const ConvGeom& g, int ncb, int nt, int terms);  // dynamic LDS of the gather kernel
 hipError_t launch_conv(int dtype, int mode, int ncb, int nt, int terms, const void* src0, const void* src1,
                        const void* zero16, unsigned int* subbits, unsigned int* ctrl, const void* wpack, const int* offtab,
