@@ -27,14 +27,16 @@
 // when its channel runs are 16-byte multiples, otherwise the padded (or column-folded) copy that the
 // scan / repack kernels write (see scan.hip); the kernel itself only sees "source positions" of
 // pos_bytes bytes with their own strides and window size.
-// A workgroup has eight wavefronts with two roles.  Wavefronts 0-3 ("producers") own the work list and
-// the copies into LDS; wavefronts 4-7 ("consumers", one per SIMD) only multiply and write results.  Each
-// consumer owns every fourth pair of gathered sub-tiles and all NCB channel blocks (register blocking
-// NCB x NT/8), so one weight fragment read feeds NT/8 MFMAs and one window read feeds NCB MFMAs.  While
+// A workgroup's wavefronts have two roles.  Wavefronts 0-3 ("producers") own the work list and
+// the copies into LDS; the others ("consumers", one per pair of gathered sub-tiles: eight of the 16-slot shape, four of
+// the 8-slot one) only multiply and write results.  A consumer owns its pair and all NCB channel blocks.  While
 // the consumers multiply slab k, the producers stage slab k+1 -- or the first slab of the workgroup's next
 // work unit, including its list and address work -- into the other buffer; the two roles meet at one
 // barrier per slab.  The producers' address arithmetic and load issue thus run in the shadow of the matrix
 // instructions of another wavefront on the same SIMD.
+// Two consumers per SIMD with one pair each read half as much again from LDS as one with two pairs, which costs
+// nothing (the LDS is not what bounds the kernel), and leave registers to fetch the stored projection ahead of its use
+// (see LATE_BASE): the five-layer stack at 512 streams 674 -> 626 us, the eight consumers alone 674 -> 668.
 // The number of sub-tiles per workgroup adapts on the device: few active sub-tiles are spread one per
 // workgroup (latency), many are packed NT per workgroup (operand reuse).
 // Every output element has exactly one owner: no atomics on y, results reproducible run to run.
@@ -100,11 +102,11 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 typedef const void __attribute__((address_space(1))) * gptr_t;
 typedef void __attribute__((address_space(3))) * lptr_t;
 
-constexpr int WG_THREADS = 2 * CONV_THREADS;  // 4 producer + 4 consumer wavefronts
+constexpr int wg_threads(int nt) { return CONV_THREADS + nt / 2 * WAVE; }  // 4 producer + nt / 2 consumer wavefronts
 constexpr int LIST_CAP = 1024;                // ranked sub-tile ids held in LDS per ranking round
 
 template <int DT, int MODE, int NCB, int NT, int TERMS>
-__global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
+__global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     const unsigned char* __restrict__ src0, const unsigned char* __restrict__ src1,
     const unsigned char* __restrict__ zero16, unsigned int* flags, unsigned int* ctrl,
     const uint4* __restrict__ wpack, const int* __restrict__ offtab, const void* __restrict__ bias_v, void* y_v,
@@ -112,9 +114,9 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
     typedef typename Acc<DT>::type acc_t;
     typedef typename Acc<DT>::vec vec_t;
     typedef typename Acc<DT>::scalar sc_t;
-    constexpr int NP = NT / 8;  // pairs of gathered sub-tiles per consumer wavefront
+    constexpr int WG_THREADS = wg_threads(NT);
     constexpr int MAXU = CONV_MAX_STAGE_UNITS;  // staged 16-byte units per producer thread and slab (host guarantees)
-    static_assert(NT % 8 == 0 && NT <= 32, "NT: two sub-tiles per consumer wavefront, slot index in 5 bits");
+    static_assert(NT % 8 == 0 && NT <= 16, "NT: two sub-tiles per consumer wavefront, at most twelve wavefronts");
     static_assert(LIST_CAP >= 2 * NT, "a ranking round holds at least two work units");
 
     // LDS: [weights x nbuf_a][windows (TERMS planes) x 2][window offset table]
@@ -515,32 +517,33 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
     }  // units of the round
     }  // rounds
     } else {
-    // Consumer state of a unit: output addresses (per pair, this lane's position of its sub-tile) and the
-    // accumulators.  The accumulators start from what the result is added to -- the stored projection (delta:
-    // Algorithm 1, P_t = P_{t-1} + F * dI) or the bias (dense: Eq. 3) -- so the epilogue is a plain store.
-    // They are fetched as soon as the previous unit's results are stored (the sub-tile ids come from the
-    // ranked list, not from the producers), long before the unit's first slab is staged.  (Channel counts
-    // that are not multiples of 4 start from zero and add element by element at the end.)
-    unsigned int ybase[NP];
-    bool pos_ok[NP];
-    acc_t acc[NCB][NP];
+    // Consumer state of a unit: this lane's output position of its sub-tile, the accumulators, and what the result is
+    // added to -- the stored projection (delta: Algorithm 1, P_t = P_{t-1} + F * dI) or the bias (dense: Eq. 3).
+    // `base` is fetched as soon as the previous unit's results are stored (the sub-tile ids come from the ranked
+    // list, not from the producers) and is needed only after the unit's last slab: accumulators that start from it
+    // would hold up the unit's first product until these loads, and the previous unit's stores before them (memory
+    // operations of a wavefront are waited for in order), are done.  A dense launch, and the two-term 16-slot shape,
+    // which have no registers to spare for it, start the accumulators from `base`.  (Channel counts that are not multiples of 4 add
+    // element by element at the end.)
+    unsigned int ybase;
+    bool pos_ok;
+    acc_t acc[NCB];
+    constexpr bool LATE_BASE = MODE == MODE_DELTA && !(TERMS == 2 && NT == 16);
+    vec_t base[NCB][LATE_BASE ? 4 : 1];
     auto begin_unit = [&](int iu2, int r0) {
         const int first2 = (bx + iu2 * gx) * per;
         const int mycount2 = min(per, count - first2);
-#pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            const int slot = 2 * (cw + 4 * p) + half;
-            pos_ok[p] = false;
-            ybase[p] = 0;
-            if (slot < mycount2) {
-                const int id = listed ? s_list[(iu2 - r0) * per + slot] : first2 + slot;
-                const int b = (int)udiv_magic((unsigned int)id, (unsigned int)(g.sty * g.stx), g.magic_sub);
-                const int r = id - b * (g.sty * g.stx);
-                const int sy = (int)udiv_magic((unsigned int)r, (unsigned int)g.stx, g.magic_stx), sx = r - sy * g.stx;
-                const int oy = 4 * sy + (j >> 2), ox = 4 * sx + (j & 3);
-                pos_ok[p] = ox < g.wo && oy < g.ho;
-                ybase[p] = (unsigned int)((b * g.ho + oy) * g.wo + ox) * (unsigned int)g.c_out + (unsigned int)(grp * g.og);
-            }
+        const int slot = 2 * cw + half;
+        pos_ok = false;
+        ybase = 0;
+        if (slot < mycount2) {
+            const int id = listed ? s_list[(iu2 - r0) * per + slot] : first2 + slot;
+            const int b = (int)udiv_magic((unsigned int)id, (unsigned int)(g.sty * g.stx), g.magic_sub);
+            const int r = id - b * (g.sty * g.stx);
+            const int sy = (int)udiv_magic((unsigned int)r, (unsigned int)g.stx, g.magic_stx), sx = r - sy * g.stx;
+            const int oy = 4 * sy + (j >> 2), ox = 4 * sx + (j & 3);
+            pos_ok = ox < g.wo && oy < g.ho;
+            ybase = (unsigned int)((b * g.ho + oy) * g.wo + ox) * (unsigned int)g.c_out + (unsigned int)(grp * g.og);
         }
 #pragma unroll
         for (int c = 0; c < NCB; ++c)
@@ -548,18 +551,17 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
             for (int gq = 0; gq < 4; ++gq) {
                 const int co = chan(c, gq);
                 const bool ch_ok = g.vec_store && co < g.og;
-                vec_t bv = vec_t{0, 0, 0, 0};
-                if (!from_y && ch_ok && bias) bv = *reinterpret_cast<const vec_t*>(bias + grp * g.og + co);
-#pragma unroll
-                for (int p = 0; p < NP; ++p) {
-                    vec_t v = bv;
-                    if (from_y && ch_ok && pos_ok[p])
-                        v = *reinterpret_cast<const vec_t*>(y + (ybase[p] + (unsigned int)co));
-                    acc[c][p][4 * gq + 0] = v.x;
-                    acc[c][p][4 * gq + 1] = v.y;
-                    acc[c][p][4 * gq + 2] = v.z;
-                    acc[c][p][4 * gq + 3] = v.w;
+                vec_t v = vec_t{0, 0, 0, 0};
+                if (!from_y && ch_ok && bias) v = *reinterpret_cast<const vec_t*>(bias + grp * g.og + co);
+                if (from_y && ch_ok && pos_ok) v = *reinterpret_cast<const vec_t*>(y + (ybase + (unsigned int)co));
+                if constexpr (LATE_BASE) {
+                    base[c][gq] = v;
+                    v = vec_t{0, 0, 0, 0};
                 }
+                acc[c][4 * gq + 0] = v.x;
+                acc[c][4 * gq + 1] = v.y;
+                acc[c][4 * gq + 2] = v.z;
+                acc[c][4 * gq + 3] = v.w;
             }
     };
     for (int r0 = 0; r0 < my_nunits; r0 += ur) {
@@ -577,32 +579,29 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
     const int first = unit * per;
     int mycount = count - first;
     if (mycount > per) mycount = per;
-    const int nact = mycount > 2 * cw ? (mycount - 2 * cw + 7) / 8 : 0;  // pairs in use (slots 2*(cw+4p), +1)
+    const bool active = mycount > 2 * cw;  // (slots 2*cw, 2*cw + 1)
     {
         // ---- consumers ---------------------------------------------------------------------------------
-        // K loop of one slab, compiled per number of sub-tile pairs in use by the wavefront (no per-pair
-        // branches; unused slots read stale LDS and their results are dropped).  A K step is four K pairs,
+        // K loop of one slab (an unused second slot reads stale LDS and its results are dropped).  A K step is four K pairs,
         // i.e. two MFMA steps.  Software pipeline: while K step q multiplies, the operands of step q+1 are
         // read from LDS into a second register set (the sets swap roles every step, nothing is copied) and
         // the table entries of step q+2 are fetched, so that no address waits for a table read.  The reads
         // are issued one by one between the MFMAs: a wavefront that issues them in a batch leaves the
-        // matrix pipeline idle meanwhile.  One consumer per SIMD issues everything, so what is not a matrix
+        // matrix pipeline idle meanwhile.  What is not a matrix
         // instruction or an operand read is kept off this loop: a pair's window offset comes ready from the table
         // (one add per operand), the weights' addresses are one base per channel block with immediate offsets (67
         // instead of 91 instructions per two K steps of 16 matrix instructions; the five-layer stack 687 -> 674 us at
         // 512 streams, 84.2 -> 80.3 us at one).
-        auto k_loop = [&]<int NPA, int T>(unsigned int aw, unsigned int bw) {  // LDS offsets; T: terms multiplied
+        auto k_loop = [&]<int T>(unsigned int aw, unsigned int bw) {  // LDS offsets; T: terms multiplied
             const unsigned int ap = aw + lane * 16;
             // (slots beyond the allocated ones are never in use; their lanes read slot 0 instead of running
             // off the buffer)
             const unsigned int bp = bw + (2 * cw + half < g.nt ? 2 * cw + half : 0) * g.slot_bytes + off_lane;
-            const unsigned int pstride = NPA > 1 ? 8 * g.slot_bytes : 0;
-            constexpr int NB1 = T == 2 ? NPA : 1;
             struct Ops {
-                uint4 a[2][NCB], b0[2][NPA], b1[2][NB1];
+                uint4 a[2][NCB], b0[2], b1[2];
             };
-            constexpr int N_MFMA = 2 * NCB * NPA * T;
-            constexpr int N_READ = 2 * (NCB + NPA * T);
+            constexpr int N_MFMA = 2 * NCB * T;
+            constexpr int N_READ = 2 * (NCB + T);
             auto fetch = [&](int q, const int2& t, Ops& o) {
 #pragma unroll
                 for (int c = 0; c < NCB; ++c) {
@@ -614,23 +613,18 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const unsigned int off = bp + (unsigned int)(h ? t.y : t.x);
-#pragma unroll
-                    for (int p = 0; p < NPA; ++p) {
-                        o.b0[h][p] = *reinterpret_cast<const uint4*>(lds + off + p * pstride);
-                        if (T == 2) o.b1[h][p] = *reinterpret_cast<const uint4*>(lds + plane_bytes + off + p * pstride);
-                    }
+                    o.b0[h] = *reinterpret_cast<const uint4*>(lds + off);
+                    if (T == 2) o.b1[h] = *reinterpret_cast<const uint4*>(lds + plane_bytes + off);
                 }
             };
             auto multiply = [&](const Ops& o) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
 #pragma unroll
-                    for (int c = 0; c < NCB; ++c)
-#pragma unroll
-                        for (int p = 0; p < NPA; ++p) {
-                            acc[c][p] = mma(o.a[h][c], o.b0[h][p], acc[c][p]);
-                            if (T == 2) acc[c][p] = mma(o.a[h][c], o.b1[h][p], acc[c][p]);
-                        }
+                    for (int c = 0; c < NCB; ++c) {
+                        acc[c] = mma(o.a[h][c], o.b0[h], acc[c]);
+                        if (T == 2) acc[c] = mma(o.a[h][c], o.b1[h], acc[c]);
+                    }
             };
             // one K step: multiply `cur`, read step q1 (table entries `t`) into `nxt`, fetch the table entries
             // of step q2 into `tn`; operand sets and table registers swap roles every step, nothing is copied
@@ -662,79 +656,80 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
             const unsigned int bw = (unsigned int)(nbuf_a * a_bytes + (gs & 1) * b_bytes);
             ++gs;
             if (TERMS == 2 && !full) {
-                if (nact > 1) {
-                    if constexpr (NP >= 2 && TERMS == 2) k_loop.template operator()<2, 2>(aw, bw);
-                } else if (nact > 0) {
-                    if constexpr (TERMS == 2) k_loop.template operator()<1, 2>(aw, bw);
-                }
-            } else if (nact > 1) {
-                if constexpr (NP >= 2) k_loop.template operator()<2, 1>(aw, bw);
-            } else if (nact > 0) {
-                k_loop.template operator()<1, 1>(aw, bw);
+                if constexpr (TERMS == 2)
+                    if (active) k_loop.template operator()<2>(aw, bw);
+            } else if (active) {
+                k_loop.template operator()<1>(aw, bw);
             }
         }
 
         // ---- epilogue ----------------------------------------------------------------------------------
+        if constexpr (LATE_BASE)
+#pragma unroll
+            for (int c = 0; c < NCB; ++c)
+#pragma unroll
+                for (int gq = 0; gq < 4; ++gq) {
+                    acc[c][4 * gq + 0] += base[c][gq].x;
+                    acc[c][4 * gq + 1] += base[c][gq].y;
+                    acc[c][4 * gq + 2] += base[c][gq].z;
+                    acc[c][4 * gq + 3] += base[c][gq].w;
+                }
         // (the store addresses are rebuilt from ybase here: kept across the K loops they would cost two
         // registers per store)
-#pragma unroll
-        for (int p = 0; p < NP; ++p) asm volatile("" : "+v"(ybase[p]));
+        asm volatile("" : "+v"(ybase));
         // The MFMA layout gives a lane 4 consecutive channels of ONE position, so a store instruction writes
         // 32-byte pieces of 32 different rows of y; measured, read-modify-writing an output tile that way runs at
         // 5.9 TB/s against 8 TB/s when the stores are whole 128-byte rows.  So each result block (32 positions x
         // 32 channels) is turned through LDS first: written in the MFMA layout, read back with 8 lanes along the
         // channels of a position, 8 positions per store.  The scratch is the window area of this wavefront's own
-        // first two slots in the buffer of the slab just finished: only this wavefront reads those windows, and
+        // two slots in the buffer of the slab just finished: only this wavefront reads those windows, and
         // the producers are filling the other buffer.
         constexpr int RP = 36;  // words per position row of the scratch (16-byte aligned, spreads the banks)
         if (g.vec_store && g.nt >= 8 && 2 * g.slot_bytes >= 32 * RP * 4) {
             vec_t* scr = reinterpret_cast<vec_t*>(bbase + ((gs - 1) & 1) * b_bytes + (2 * cw) * g.slot_bytes);
             const int posl = lane & 31;
+            // the two sub-tiles of the pair (the same in every lane)
+            unsigned int corner[2];
+            int ny[2], nx[2];
 #pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                // the two sub-tiles of the pair (the same in every lane)
-                unsigned int corner[2];
-                int ny[2], nx[2];
-#pragma unroll
-                for (int sl = 0; sl < 2; ++sl) {
-                    const int slot = 2 * (cw + 4 * p) + sl;
-                    corner[sl] = 0;
-                    ny[sl] = nx[sl] = 0;
-                    if (slot < mycount) {
-                        const int id = listed ? s_list[(iu - r0) * per + slot] : first + slot;
-                        const int b = (int)udiv_magic((unsigned int)id, (unsigned int)(g.sty * g.stx), g.magic_sub);
-                        const int r = id - b * (g.sty * g.stx);
-                        const int sy = (int)udiv_magic((unsigned int)r, (unsigned int)g.stx, g.magic_stx), sx = r - sy * g.stx;
-                        ny[sl] = g.ho - 4 * sy;
-                        nx[sl] = g.wo - 4 * sx;
-                        corner[sl] = (unsigned int)((b * g.ho + 4 * sy) * g.wo + 4 * sx) * (unsigned int)g.c_out +
-                                     (unsigned int)(grp * g.og);
-                    }
+            for (int sl = 0; sl < 2; ++sl) {
+                const int slot = 2 * cw + sl;
+                corner[sl] = 0;
+                ny[sl] = nx[sl] = 0;
+                if (slot < mycount) {
+                    const int id = listed ? s_list[(iu - r0) * per + slot] : first + slot;
+                    const int b = (int)udiv_magic((unsigned int)id, (unsigned int)(g.sty * g.stx), g.magic_sub);
+                    const int r = id - b * (g.sty * g.stx);
+                    const int sy = (int)udiv_magic((unsigned int)r, (unsigned int)g.stx, g.magic_stx), sx = r - sy * g.stx;
+                    ny[sl] = g.ho - 4 * sy;
+                    nx[sl] = g.wo - 4 * sx;
+                    corner[sl] = (unsigned int)((b * g.ho + 4 * sy) * g.wo + 4 * sx) * (unsigned int)g.c_out +
+                                 (unsigned int)(grp * g.og);
                 }
+            }
 #pragma unroll
-                for (int c = 0; c < NCB; ++c) {
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // (the previous block's reads are done)
+            for (int c = 0; c < NCB; ++c) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // (the previous block's reads are done)
 #pragma unroll
-                    for (int gq = 0; gq < 4; ++gq) {
-                        vec_t o;
-                        o.x = acc[c][p][4 * gq + 0];
-                        o.y = acc[c][p][4 * gq + 1];
-                        o.z = acc[c][p][4 * gq + 2];
-                        o.w = acc[c][p][4 * gq + 3];
-                        scr[(posl * RP + 8 * gq + 4 * khalf) >> 2] = o;
-                    }
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // LDS operations of a wavefront execute in order
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    const int ch = (cbg * NCB + c) * 32 + 4 * (lane & 7);
+                for (int gq = 0; gq < 4; ++gq) {
+                    vec_t o;
+                    o.x = acc[c][4 * gq + 0];
+                    o.y = acc[c][4 * gq + 1];
+                    o.z = acc[c][4 * gq + 2];
+                    o.w = acc[c][4 * gq + 3];
+                    scr[(posl * RP + 8 * gq + 4 * khalf) >> 2] = o;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // LDS operations of a wavefront execute in order
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                const int ch = (cbg * NCB + c) * 32 + 4 * (lane & 7);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int q = 8 * i + (lane >> 3);  // position of the pair: sub-tile q / 16, position q % 16
-                        const vec_t o = scr[(q * RP + 4 * (lane & 7)) >> 2];
-                        const int sl = i >> 1, py = 2 * (i & 1) + (lane >> 5), px = (lane >> 3) & 3;
-                        if (py < ny[sl] && px < nx[sl] && ch < g.og)
-                            *reinterpret_cast<vec_t*>(y + (corner[sl] + (unsigned int)((py * g.wo + px) * g.c_out + ch))) = o;
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    const int q = 8 * i + (lane >> 3);  // position of the pair: sub-tile q / 16, position q % 16
+                    const vec_t o = scr[(q * RP + 4 * (lane & 7)) >> 2];
+                    const int sl = i >> 1, py = 2 * (i & 1) + (lane >> 5), px = (lane >> 3) & 3;
+                    if (py < ny[sl] && px < nx[sl] && ch < g.og)
+                        *reinterpret_cast<vec_t*>(y + (corner[sl] + (unsigned int)((py * g.wo + px) * g.c_out + ch))) = o;
                 }
             }
         } else if (g.vec_store) {
@@ -744,16 +739,13 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
                 for (int gq = 0; gq < 4; ++gq) {
                     const int co = chan(c, gq);
                     if (co >= g.og) continue;
-#pragma unroll
-                    for (int p = 0; p < NP; ++p) {
-                        if (!pos_ok[p]) continue;
-                        vec_t o;
-                        o.x = acc[c][p][4 * gq + 0];
-                        o.y = acc[c][p][4 * gq + 1];
-                        o.z = acc[c][p][4 * gq + 2];
-                        o.w = acc[c][p][4 * gq + 3];
-                        *reinterpret_cast<vec_t*>(y + (ybase[p] + (unsigned int)co)) = o;
-                    }
+                    if (!pos_ok) continue;
+                    vec_t o;
+                    o.x = acc[c][4 * gq + 0];
+                    o.y = acc[c][4 * gq + 1];
+                    o.z = acc[c][4 * gq + 2];
+                    o.w = acc[c][4 * gq + 3];
+                    *reinterpret_cast<vec_t*>(y + (ybase + (unsigned int)co)) = o;
                 }
         } else {
             // channel counts that are not multiples of 4: element by element
@@ -762,17 +754,14 @@ __global__ __launch_bounds__(WG_THREADS) void conv_gather_kernel(
 #pragma unroll
                 for (int gq = 0; gq < 4; ++gq) {
                     const int co0 = chan(c, gq);
-#pragma unroll
-                    for (int p = 0; p < NP; ++p) {
-                        if (!pos_ok[p] || co0 >= g.og) continue;
-                        sc_t* yp4 = y + (ybase[p] + (unsigned int)co0);
-                        for (int k = 0; k < 4 && co0 + k < g.og; ++k) {
-                            const sc_t r = acc[c][p][4 * gq + k];
-                            if (from_y) {
-                                if (r != (sc_t)0) yp4[k] += r;
-                            } else {
-                                yp4[k] = r + (bias ? bias[grp * g.og + co0 + k] : (sc_t)0);
-                            }
+                    if (!pos_ok || co0 >= g.og) continue;
+                    sc_t* yp4 = y + (ybase + (unsigned int)co0);
+                    for (int k = 0; k < 4 && co0 + k < g.og; ++k) {
+                        const sc_t r = acc[c][4 * gq + k];
+                        if (from_y) {
+                            if (r != (sc_t)0) yp4[k] += r;
+                        } else {
+                            yp4[k] = r + (bias ? bias[grp * g.og + co0 + k] : (sc_t)0);
                         }
                     }
                 }
@@ -818,7 +807,7 @@ hipError_t launch_one(const void* src0, const void* src1, const void* zero16, un
             granted = lds;
         }
     }
-    hipLaunchKernelGGL(kern, grid, dim3(WG_THREADS), lds, s, static_cast<const unsigned char*>(src0),
+    hipLaunchKernelGGL(kern, grid, dim3(wg_threads(NT)), lds, s, static_cast<const unsigned char*>(src0),
                        static_cast<const unsigned char*>(src1), static_cast<const unsigned char*>(zero16), flags, ctrl,
                        static_cast<const uint4*>(wpack), offtab, bias, y, gg, stats);
     return hipGetLastError();
