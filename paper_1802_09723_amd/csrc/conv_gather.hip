@@ -117,9 +117,13 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     constexpr int WG_THREADS = wg_threads(NT);
     constexpr int MAXU = CONV_MAX_STAGE_UNITS;  // staged 16-byte units per producer thread and slab (host guarantees)
     static_assert(NT % 8 == 0 && NT <= 16, "NT: two sub-tiles per consumer wavefront, at most twelve wavefronts");
+    // Few slots per workgroup (g.ksh > 0): the consumers of a pair split its K steps, and each finishes its share of the
+    // channels from the other parts' sums.  `owner` is the part that finishes (and initialises) a register quad.
+    constexpr bool KSPLIT = NCB == 1 && NT == 8;
+    const int ksh = KSPLIT ? g.ksh : 0;
     static_assert(LIST_CAP >= 2 * NT, "a ranking round holds at least two work units");
 
-    // LDS: [weights x nbuf_a][windows (TERMS planes) x 2][window offset table]
+    // LDS: [weights x nbuf_a][windows (TERMS planes) x 2][window offset table][K parts' sums: g.ksh > 0]
     extern __shared__ uint4 smem[];
     unsigned char* lds = reinterpret_cast<unsigned char*>(smem);
     const int nbuf_a = g.nslab > 1 ? 2 : 1;  // a single slab of weights is staged once and serves every unit
@@ -141,7 +145,9 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool producer = wave < 4;
-    const int cw = wave - 4;  // consumer index
+    const int cw = (wave - 4) & ((NT / 2 >> ksh) - 1);   // consumer: pair of slots
+    const int kpart = KSPLIT ? (wave - 4) >> (2 - ksh) & 3 : 0;  // ... and part of the K steps
+    auto owned = [&](int gq) { return !KSPLIT || (gq >> (2 - ksh)) == kpart; };  // register quad finished by this part
     // Workgroup coordinates: BX of GX unit lanes (a lane takes work units BX, BX + GX, ...), BY of GY channel-block
     // groups.  With g.xcd_gy set the grid is one-dimensional and the coordinates are dealt so that the GY
     // workgroups of a lane, which gather the same input windows, sit on the same XCD (workgroups go to the
@@ -513,6 +519,7 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
                 stage_windows(k + 1, gs & 1);
             }
         }
+        if (KSPLIT && ksh) lds_barrier();  // (the consumers exchange their parts' sums)
     }
     }  // units of the round
     }  // rounds
@@ -550,7 +557,7 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
 #pragma unroll
             for (int gq = 0; gq < 4; ++gq) {
                 const int co = chan(c, gq);
-                const bool ch_ok = g.vec_store && co < g.og;
+                const bool ch_ok = g.vec_store && co < g.og && owned(gq);
                 vec_t v = vec_t{0, 0, 0, 0};
                 if (!from_y && ch_ok && bias) v = *reinterpret_cast<const vec_t*>(bias + grp * g.og + co);
                 if (from_y && ch_ok && pos_ok) v = *reinterpret_cast<const vec_t*>(y + (ybase + (unsigned int)co));
@@ -637,13 +644,16 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
                 sched_interleave<0, N_MFMA, N_READ>();
             };
             Ops o0, o1;
-            int2 ta, tb = tp[0];
-            const int qmax = g.nq - 1;
-            fetch(0, tb, o0);
-            ta = tp[min(1, qmax)];
-            for (int q = 0; q < g.nq; q += 2) {
+            int2 ta, tb;
+            const int q0 = KSPLIT ? (g.nq * kpart) >> ksh : 0, q1 = KSPLIT ? (g.nq * (kpart + 1)) >> ksh : g.nq;
+            if (KSPLIT && q0 >= q1) return;
+            const int qmax = q1 - 1;
+            tb = tp[q0];
+            fetch(q0, tb, o0);
+            ta = tp[min(q0 + 1, qmax)];
+            for (int q = q0; q < q1; q += 2) {
                 step(o0, o1, ta, tb, min(q + 1, qmax), min(q + 2, qmax));
-                if (q + 1 < g.nq) step(o1, o0, tb, ta, min(q + 2, qmax), min(q + 3, qmax));
+                if (q + 1 < q1) step(o1, o0, tb, ta, min(q + 2, qmax), min(q + 3, qmax));
             }
         };
 
@@ -661,6 +671,32 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
             } else if (active) {
                 k_loop.template operator()<1>(aw, bw);
             }
+        }
+
+        if (KSPLIT && ksh) {
+            // the K parts' sums: every part leaves the quads that it does not finish in LDS and adds the others' to its own,
+            // in the order of the parts
+            vec_t* part = reinterpret_cast<vec_t*>(lds + nbuf_a * a_bytes + 2 * b_bytes + conv_tab_words(g) * (int)sizeof(int));
+            const int prow = cw << ksh;  // rows of this pair: [part][quad][lane]
+#pragma unroll
+            for (int gq = 0; gq < 4; ++gq)
+                if (active && !owned(gq))
+                    part[((prow + kpart) * 4 + gq) * WAVE + lane] =
+                        vec_t{acc[0][4 * gq + 0], acc[0][4 * gq + 1], acc[0][4 * gq + 2], acc[0][4 * gq + 3]};
+            lds_barrier();
+            if (active)
+                for (int o = 0; o < (1 << ksh); ++o) {
+                    if (o == kpart) continue;
+#pragma unroll
+                    for (int gq = 0; gq < 4; ++gq)
+                        if (owned(gq)) {
+                            const vec_t v = part[((prow + o) * 4 + gq) * WAVE + lane];
+                            acc[0][4 * gq + 0] += v.x;
+                            acc[0][4 * gq + 1] += v.y;
+                            acc[0][4 * gq + 2] += v.z;
+                            acc[0][4 * gq + 3] += v.w;
+                        }
+                }
         }
 
         // ---- epilogue ----------------------------------------------------------------------------------
@@ -738,8 +774,7 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
 #pragma unroll
                 for (int gq = 0; gq < 4; ++gq) {
                     const int co = chan(c, gq);
-                    if (co >= g.og) continue;
-                    if (!pos_ok) continue;
+                    if (co >= g.og || !pos_ok || !owned(gq)) continue;
                     vec_t o;
                     o.x = acc[c][4 * gq + 0];
                     o.y = acc[c][4 * gq + 1];
@@ -754,7 +789,7 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
 #pragma unroll
                 for (int gq = 0; gq < 4; ++gq) {
                     const int co0 = chan(c, gq);
-                    if (!pos_ok || co0 >= g.og) continue;
+                    if (!pos_ok || co0 >= g.og || !owned(gq)) continue;
                     sc_t* yp4 = y + (ybase + (unsigned int)co0);
                     for (int k = 0; k < 4 && co0 + k < g.og; ++k) {
                         const sc_t r = acc[c][4 * gq + k];
@@ -830,7 +865,7 @@ hipError_t launch_shape(int ncb, int nt, const void* src0, const void* src1, con
 
 size_t conv_lds_bytes(const ConvGeom& g, int ncb, int nt, int terms) {
     return (size_t)(g.nslab > 1 ? 2 : 1) * (size_t)ncb * 2 * g.nq * 1024 + 2 * (size_t)terms * nt * g.slot_bytes +
-           (size_t)conv_tab_words(g) * sizeof(int);
+           (size_t)conv_tab_words(g) * sizeof(int) + (g.ksh ? CONV_PART_BYTES : 0);
 }
 
 hipError_t launch_conv(int dtype, int mode, int ncb, int nt, int terms, const void* src0, const void* src1,

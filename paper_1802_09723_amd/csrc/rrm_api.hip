@@ -265,24 +265,19 @@ void choose_rotation(ConvGeom& t, int ntaps) {
     t.magic_sy = magic_for(t.str_y);
     t.magic_sx = magic_for(t.str_x);
     if (P == 1) return;
+    const int ncc = t.sc == P ? 1 : P;  // (whole positions rotated: another chunk shifts every bank alike)
     long long best = -1;
     for (int a = 0; a < P; ++a)
         for (int b = 0; b < P; ++b) {
             long long cost = 0;
             for (int tap = 0; tap < ntaps; ++tap) {
                 const int ky = tap / t.kw_eff, ku = tap % t.kw_eff;
-                for (int cc = 0; cc < P; ++cc) {
-                    int addr[16], worst = 1;
+                for (int cc = 0; cc < ncc; ++cc) {
+                    int hits[16] = {}, worst = 1;  // positions per 16-byte bank group (all at different addresses)
                     for (int j = 0; j < 16; ++j) {
                         const int hy = (j >> 2) * t.str_y + ky, hx = (j & 3) * t.str_x + ku;
                         const int cs = (cc + a * (hy / t.str_y) + b * (hx / t.str_x)) & (P - 1);
-                        addr[j] = ((hy * t.ww + hx) * t.sc + cs) * 16;
-                    }
-                    for (int j = 0; j < 16; ++j) {
-                        int same = 1;
-                        for (int k = 0; k < j; ++k)
-                            if ((addr[k] & 255) / 16 == (addr[j] & 255) / 16 && addr[k] != addr[j]) ++same;
-                        worst = std::max(worst, same);
+                        worst = std::max(worst, ++hits[((hy * t.ww + hx) * t.sc + cs) & 15]);
                     }
                     cost += worst;
                 }
@@ -295,16 +290,23 @@ void choose_rotation(ConvGeom& t, int ntaps) {
         }
 }
 
+// log2 of the parts that the consumers split a pair's K steps into: one channel block per workgroup and fewer pairs of
+// slots than the four consumers of the eight-slot kernel (with the slot choice in setup_conv, one stream: 13 x 13,
+// 384 -> 384 channels int8 11.6 -> 9.6 us, the five-layer stack 78.3 -> 73.8 us)
+int conv_ksh(int wg_cb, int nt) { return wg_cb != 1 || nt > 4 ? 0 : nt > 2 ? 1 : 2; }
+
 // Fill the slab-dependent fields for (blocks, sub-tiles) per workgroup with the largest slab that fits
 // the LDS budget; false if none does.  Several slabs: a slab is a whole number of K steps (4 pairs
 // each) unless `padded`, which lets every slab end in up to 3 zero-weight pairs.
-bool conv_try_shape(ConvGeom& g, int terms, int wg_cb, int nt, int ntaps, long long budget, bool padded = false) {
+bool conv_try_shape(ConvGeom& g, int terms, int wg_cb, int nt, int ntaps, long long budget, bool padded = false,
+                    bool ksplit = false) {
     const int max_units = CONV_MAX_STAGE_UNITS * CONV_THREADS;
     for (int sc = g.chunks; sc >= 1; --sc) {
         if (!padded && sc < g.chunks && (sc * ntaps) % 4 != 0) continue;
         ConvGeom t = g;
         t.wg_cb = wg_cb;
         t.nt = nt;
+        t.ksh = ksplit ? conv_ksh(wg_cb, nt) : 0;
         t.sc = sc;
         t.nslab = (t.chunks + sc - 1) / sc;
         t.pitch = pitch_for(sc);
@@ -378,21 +380,26 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
     g.vec_store = (s.c_out % 4 == 0) && (g.og % 4 == 0);
     const int ntaps = s.kh * g.kw_eff;
     const int terms = L->dtype == RRM_BF16_F32 ? 2 : 1;
-    // Workgroup shape.  Few sub-tiles in total (one stream of a small map): latency matters, so one
-    // 32-channel block and up to 8 sub-tiles per workgroup, the whole K range in as few slabs as fit.
-    // Many sub-tiles (many streams): operand reuse matters, so 2 channel blocks x 16 sub-tiles.
+    // Workgroup shape.  Few sub-tiles in total (one stream of a small map): latency matters, so one 32-channel block
+    // per workgroup and as few sub-tiles as the chip has workgroups for (one per compute unit); the fewer windows leave
+    // LDS for longer slabs, and the consumers split the K steps.  Many sub-tiles (many streams): operand reuse matters,
+    // so 2 channel blocks x 16 sub-tiles.
     struct Cand { int cb, nt; };
     std::vector<Cand> cands;
     const bool small = (long long)g.n_sub * g.ncb * s.groups <= 1024;
     if (small || g.ncb < 2) {
-        cands = {{1, 8}, {1, 16}, {1, 4}};
-        if (!small) cands = {{1, 16}, {1, 8}, {1, 4}};
+        cands = {{1, 16}, {1, 8}, {1, 4}};
+        if (small) {
+            int nt = 1;
+            while (nt < 8 && (long long)((g.n_sub + nt - 1) / nt) * g.ncb * s.groups > NUM_CU) nt *= 2;
+            cands = {{1, nt}, {1, 8}, {1, 16}, {1, 4}};
+        }
     } else {
         cands = {{2, 16}, {2, 8}, {1, 16}, {1, 8}, {1, 4}};
     }
     bool ok = false;
     // (the kernel's static LDS, about 6 KB, comes on top of the dynamic budget; 160 KB per workgroup in all)
-    long long first_budget = (small ? 96ll : 153ll) * 1024;
+    long long first_budget = 153ll * 1024;
     if (const char* env = std::getenv("RRM_CONV_LDS_KB")) {  // tuning knob: preferred LDS bytes per workgroup
         const long long kb = std::atoll(env);
         if (kb >= 16 && kb <= 153) first_budget = kb * 1024;
@@ -401,7 +408,7 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
         for (const Cand& c : cands) {
             ConvGeom t = g;
             // a slab should hold at least 4 chunks (or all of them) to amortise its barriers
-            if (conv_try_shape(t, terms, c.cb, c.nt, ntaps, budget) && (t.sc >= 4 || t.sc == t.chunks)) {
+            if (conv_try_shape(t, terms, c.cb, c.nt, ntaps, budget, false, small) && (t.sc >= 4 || t.sc == t.chunks)) {
                 g = t;
                 ok = true;
                 break;

@@ -76,6 +76,7 @@ struct FusedSrc {
     const unsigned int* touched_all;
 };
 
+constexpr int CONV_PART_BYTES = 4 * 4 * WAVE * 16;  // LDS of the K parts' sums: four consumers, 16 registers each
 constexpr int CONV_MAX_STAGE_UNITS = 12;  // 16-byte units a thread stages per slab (half for 2 terms)
 
 // Geometry of the gather-tile implicit-GEMM convolution (int8 / bf16 MFMA path).
@@ -120,6 +121,7 @@ struct ConvGeom {
     unsigned int magic_ww;      // d = ww
     unsigned int magic_sub;     // d = sty*stx
     unsigned int magic_stx;     // d = stx
+    int ksh;             // log2 of the parts that a pair's K steps are split into (one channel block, few slots)
     int vec_store;       // 1: y rows allow 16-byte read-modify-write
     unsigned int* fresh;    // see FusedSrc::fresh: cleared at the end of a delta launch
     unsigned int* touched_all;  // see FusedSrc::touched_all: cleared at the end of a delta launch

@@ -1,0 +1,26 @@
+"""GPU parity at the sizes where a kernel's work split changes: edges of tiles, passes and parts, remainders, the smallest
+and largest of a range.  Integer and binary layers bit-exact, bf16 within the bound of the other parity tests."""
+import pytest
+
+import rrm_synth as S
+from gpu_util import run_sequence
+
+pytestmark = pytest.mark.gpu
+
+
+# One channel block and 1, 2, 4 or 8 sub-tiles per workgroup (a layer of few sub-tiles): the consumers split the K steps.
+# (map, c_in, c_out, k, stride, pad, groups, n): K steps fewer than the parts, one slab and several, channel counts off
+# the blocks of 32 and off the fours, groups, several units per workgroup.
+FEW_SUBTILES = [
+    (4, 16, 16, 1, 1, 0, 1, 1), (13, 384, 384, 3, 1, 1, 1, 1), (13, 256, 384, 3, 1, 1, 1, 2), (27, 96, 256, 5, 1, 2, 2, 1),
+    (20, 48, 130, 3, 1, 1, 1, 1), (29, 32, 33, 3, 2, 1, 1, 2), (55, 16, 64, 3, 1, 1, 1, 1), (7, 512, 512, 3, 1, 1, 1, 1),
+    (31, 16, 7, 3, 1, 1, 1, 9), (40, 16, 32, 5, 1, 2, 1, 10),
+]
+
+
+@pytest.mark.parametrize("shp", FEW_SUBTILES)
+@pytest.mark.parametrize("dt", [S.I8, S.BF16])
+def test_window_tile_kernel_with_few_subtiles(shp, dt):
+    m, ci, co, k, st, pad, g, n = shp
+    seq = S.random_layer(9100 + m, S.conv_shape(m, m, ci, co, k, st, pad, g, n=n), dt, T=4, frac=0.2, block=3)
+    run_sequence(seq, check_dense=(0, 3), path=1, conv_kernel=1)
