@@ -721,7 +721,9 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
         // two slots in the buffer of the slab just finished: only this wavefront reads those windows, and
         // the producers are filling the other buffer.
         constexpr int RP = 36;  // words per position row of the scratch (16-byte aligned, spreads the banks)
-        if (g.vec_store && g.nt >= 8 && 2 * g.slot_bytes >= 32 * RP * 4) {
+        if (!active) {
+            // (no pair in this unit, perhaps no slots at all: a 12-slot layer on the 16-slot shape)
+        } else if (g.vec_store && g.nt >= 8 && 2 * g.slot_bytes >= 32 * RP * 4) {
             vec_t* scr = reinterpret_cast<vec_t*>(bbase + ((gs - 1) & 1) * b_bytes + (2 * cw) * g.slot_bytes);
             const int posl = lane & 31;
             // the two sub-tiles of the pair (the same in every lane)
@@ -855,7 +857,7 @@ hipError_t launch_shape(int ncb, int nt, const void* src0, const void* src1, con
 #define RRM_CASE(CBV, NTV)                                                                                          \
     if (ncb == CBV && nt == NTV)                                                                                     \
         return launch_one<DT, MODE, CBV, NTV, TERMS>(src0, src1, zero16, flags, ctrl, wpack, offtab, bias, y, g, stats, s);
-    if (nt < 8) nt = 8;  // fewer slots than the smallest shape: same code, the slot count is in g.nt
+    nt = nt <= 8 ? 8 : 16;  // fewer slots than the shape has: same code, the slot count is in g.nt
     RRM_CASE(2, 16) RRM_CASE(2, 8) RRM_CASE(1, 16) RRM_CASE(1, 8)
 #undef RRM_CASE
     return hipErrorInvalidValue;

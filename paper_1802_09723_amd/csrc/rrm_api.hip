@@ -396,6 +396,8 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
         }
     } else {
         cands = {{2, 16}, {2, 8}, {1, 16}, {1, 8}, {1, 4}};
+        // (12 slots where 16 do not fit: 27 x 27, 5 x 5, 2 x 48 -> 256 channels at 512 streams 92 -> 75 us; two-term layers have too few registers left on the 16-slot code)
+        if (terms == 1) cands.insert(cands.begin() + 1, Cand{2, 12});
     }
     bool ok = false;
     // (the kernel's static LDS, about 6 KB, comes on top of the dynamic budget; 160 KB per workgroup in all)
