@@ -7,7 +7,8 @@
 // The dense layer (Eq. 3) is the same expression with m = "tap inside the image" and factor 1:
 //      P  = b + popc(m) - 2 * popc( m & (w XOR x) ).
 // Per lane and 32 inputs this is one v_bfi_b32 ((w & B) | (~w & A) with A = m & x, B = m & ~x, which
-// equals m & (w XOR x)) and one v_bcnt_u32_b32 with accumulate: plain vector ALU work, no matrix core.
+// equals m & (w XOR x)) and one v_bcnt_u32_b32 with accumulate: plain vector ALU work, no matrix core (the tile
+// kernel).  The band kernel multiplies on the matrix cores instead (see there).
 //
 // Mapping of the tile kernel (the dense layer, and the delta step of layers whose band does not fit LDS): one
 // workgroup = one 8x8 output tile (lane = output position) x 4*CW output channels (wavefront w owns CW of
@@ -15,10 +16,10 @@
 // the tile's input window are staged in LDS once; (slab, tap) pairs in which no lane of the wavefront has a
 // flipped bit are skipped.
 //
-// Mapping of the band kernel (the delta step): one workgroup = a band of output rows of one stream x 4*CW
-// output channels.  It stages the band's input window as above, notes which input positions hold a flip, lists
-// the output positions whose window sees one (ballot compaction into LDS) and deals that list to the lanes 64
-// at a time: a wavefront's lanes are all output positions with work to do, wherever in the band they lie, so
+// Mapping of the band kernel (the delta step): one workgroup = a band of output rows of one stream x 64 output
+// channels.  It stages the band's input window as above, notes which input positions hold a flip, lists
+// the output positions whose window sees one (ballot compaction into LDS) and multiplies that list 64 entries
+// at a time: every column of the product is an output position with work to do, wherever in the band it lies, so
 // the work follows the changed positions instead of the 8x8 tiles they fall into.
 #include <algorithm>
 #include <mutex>
@@ -29,7 +30,10 @@ namespace rrm {
 
 namespace {
 
-constexpr int BAND_THREADS = 512;  // the band kernel's workgroup: eight wavefronts
+constexpr int BAND_THREADS = 64 * BAND_WAVES;  // the band kernel's workgroup
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
 
 // t + popcount(v) in one instruction (v_bcnt_u32_b32 adds its second operand; the compiler otherwise counts
 // into a fresh register and adds pairs of counts with a third instruction)
@@ -171,104 +175,37 @@ __global__ __launch_bounds__(256) void bin_conv_kernel(const unsigned int* __res
     }
 }
 
-// the band kernel's inner part: NP x 64 listed output positions (lane l takes entries first + l, first + 128 + l)
-// against the CW output channels of this wavefront; the filter words of a (slab, tap) are loaded once for all NP
-template <int CW, int NP, bool WL>
-__device__ __forceinline__ void band_items(const unsigned int* A, const unsigned int* B, const unsigned short* list,
-                                           int first, int cnt, const uint4* __restrict__ wpack, const uint4* wl, int* y,
-                                           const BinGeom& g, int b, int oy0, int grp, int co_w, int lane, int wave) {
-    const int ntaps = g.kh * g.kw;
-    const long long ob8 = (long long)grp * g.nob8 + co_w / 8;
-    const bool vec = (g.c_out & 3) == 0 && (g.og & 3) == 0;
-    bool valid[NP];
-    int oyl[NP], ox[NP], lbase[NP], popm[NP];
-    int tot[NP][CW];
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-        const int e = first + p * 128 + lane;
-        valid[p] = e < cnt;
-        const int q = list[valid[p] ? e : 0];
-        oyl[p] = q / g.wo;
-        ox[p] = q - oyl[p] * g.wo;
-        lbase[p] = ((oyl[p] * g.stride) * g.btw_in + ox[p] * g.stride) * g.pitch;
-        popm[p] = 0;
-#pragma unroll
-        for (int o = 0; o < CW; ++o) tot[p][o] = 0;
-    }
-    for (int slab = 0; slab < g.nslab; ++slab) {
-        for (int tap = 0; tap < ntaps; ++tap) {
-            const int ky = tap / g.kw, kx = tap - ky * g.kw;
-            const int toff = (ky * g.btw_in + kx) * g.pitch + slab * 4;
-            uint4 a[NP], bb[NP];
-            unsigned int any = 0;
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                a[p] = *reinterpret_cast<const uint4*>(A + lbase[p] + toff);
-                bb[p] = *reinterpret_cast<const uint4*>(B + lbase[p] + toff);
-                any |= a[p].x | a[p].y | a[p].z | a[p].w | bb[p].x | bb[p].y | bb[p].z | bb[p].w;
-            }
-            if (__ballot(any != 0u) == 0ull) continue;  // wave-uniform: nothing flipped under this tap
-#pragma unroll
-            for (int p = 0; p < NP; ++p)
-                popm[p] = popc_acc(a[p].w | bb[p].w, popc_acc(a[p].z | bb[p].z, popc_acc(a[p].y | bb[p].y, popc_acc(a[p].x | bb[p].x, popm[p]))));
-#pragma unroll
-            for (int o8 = 0; o8 < CW / 8; ++o8) {
-                // filter words of eight output channels: from the workgroup's copy in LDS (every lane reads the same
-                // address: a broadcast, and plain LDS reads pipeline where scalar loads make the wavefront wait), or
-                // through scalar loads
-                const uint4* wp = WL ? wl + ((slab * ntaps + tap) * 4 + wave) * CW + o8 * 8
-                                     : wpack + (((ob8 + o8) * g.nslab + slab) * ntaps + tap) * 8;
-                uint4 wq[8];  // all eight reads in flight before the first is used
-#pragma unroll
-                for (int o = 0; o < 8; ++o) wq[o] = wp[o];
-#pragma unroll
-                for (int o = 0; o < 8; ++o) {
-                    const uint4 w = wq[o];
-#pragma unroll
-                    for (int p = 0; p < NP; ++p) {
-                        int t = tot[p][o8 * 8 + o];
-                        t = popc_acc((w.x & bb[p].x) | (~w.x & a[p].x), t);
-                        t = popc_acc((w.y & bb[p].y) | (~w.y & a[p].y), t);
-                        t = popc_acc((w.z & bb[p].z) | (~w.z & a[p].z), t);
-                        t = popc_acc((w.w & bb[p].w) | (~w.w & a[p].w), t);
-                        tot[p][o8 * 8 + o] = t;
-                    }
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-        if (!valid[p] || popm[p] == 0) continue;
-        const long long ybase = (((long long)b * g.ho + oy0 + oyl[p]) * g.wo + ox[p]) * g.c_out + (long long)grp * g.og + co_w;
-#pragma unroll
-        for (int o4 = 0; o4 < CW / 4; ++o4) {
-            const int co = co_w + o4 * 4;
-            if (co >= g.og) break;
-            int r[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) r[k] = 2 * (popm[p] - 2 * tot[p][o4 * 4 + k]);
-            if (vec && co + 3 < g.og) {
-                int4* yp = reinterpret_cast<int4*>(y + ybase + o4 * 4);
-                int4 o = *yp;
-                o.x += r[0]; o.y += r[1]; o.z += r[2]; o.w += r[3];
-                *yp = o;
-            } else {
-                for (int k = 0; k < 4 && co + k < g.og; ++k) y[ybase + o4 * 4 + k] += r[k];
-            }
-        }
-    }
+// ---- the band kernel's product ------------------------------------------------------------------------------------
+// Half of a difference of two +1/-1 frames is -1, 0 or +1, which the 4-bit float format of the matrix cores (E2M1)
+// holds exactly, like the weights; the products are summed in fp32, exact below 2^24 terms (a band's window in LDS
+// holds far fewer).  v_mfma_f32_32x32x64_f8f6f4 multiplies 32 output channels x 32 listed positions x 64 input
+// channels of one tap in 32 cycles, where the popcount form takes 256 vector cycles, and a lane makes its 32 entries
+// of the difference out of two LDS words with 16 instructions.
+// Measured (28 x 28, 256 -> 256 channels, 64 streams, 5 % of the values flipping): 36.8 -> 23.0 us a step; one stream
+// of 14 x 14, 512 -> 512 channels, 10 %: 16.8 -> 10.3.
+
+// 32 differences as E2M1 nibbles: m = flip mask, q = flips to -1.  Nibble j of register i is bit 4j + i of the word
+// (the weights are packed in the same order): 0x2 = +1, 0xA = -1, 0x0 = unchanged.
+__device__ __forceinline__ v8i expand_e2m1(unsigned int m, unsigned int q) {
+    const unsigned int P = 0x22222222u, N = 0x88888888u;
+    return v8i{(int)(((m << 1) & P) | ((q << 3) & N)), (int)((m & P) | ((q << 2) & N)),
+               (int)(((m >> 1) & P) | ((q << 1) & N)), (int)(((m >> 2) & P) | (q & N)), 0, 0, 0, 0};
+}
+
+__device__ __forceinline__ v16f mma_e2m1(const uint4& a, const v8i& b, v16f c) {
+    const v8i av{(int)a.x, (int)a.y, (int)a.z, (int)a.w, 0, 0, 0, 0};
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, b, c, 4, 4, 0, 0, 0, 0);  // E2M1 x E2M1, unscaled
 }
 
 // FUSED: the whole step in this one launch.  `xsrc` is the new frame x_t and `flip` the stored input: the flip
 // mask is their XOR, formed while the window is staged (no difference kernel, no flip buffer); the change counts
 // are taken over the input rows a band owns; and the workgroup of a stream that finishes staging last (arrival
 // counter) copies the frame into the stored input, when nobody reads the old one any more, and rearms the counter.
-template <int CW, bool FUSED, bool WL>
-__global__ __launch_bounds__(BAND_THREADS) void bin_band_kernel(const unsigned int* __restrict__ xsrc,
+template <bool FUSED>
+__global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigned int* __restrict__ xsrc,
                                                        const unsigned int* flip, unsigned int* snap,
                                                        unsigned int* arrive,
-                                                       const uint4* __restrict__ wpack, int* y, BinGeom g,
+                                                       const uint4* __restrict__ wband, int* y, BinGeom g,
                                                        DevStats* __restrict__ stats) {
     extern __shared__ uint4 smem[];
     const int npos = g.bth_in * g.btw_in;
@@ -276,43 +213,50 @@ __global__ __launch_bounds__(BAND_THREADS) void bin_band_kernel(const unsigned i
     unsigned int* B = A + npos * g.pitch;
     unsigned char* posany = reinterpret_cast<unsigned char*>(B + npos * g.pitch);     // input position holds a flip
     unsigned short* list = reinterpret_cast<unsigned short*>(posany + ((npos + 15) & ~15));  // active output positions
-    // (WL) the workgroup's filter words, [slab][tap][4 * CW channels], behind the list (16-byte aligned)
-    uint4* wl = reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(list) + (((size_t)g.band_rows * g.wo * 2 + 15) & ~(size_t)15));
+    // sums of a pass: 64 positions x 64 channels, rows padded by one word (the lanes of an add are 32 positions)
+    int* red = reinterpret_cast<int*>(reinterpret_cast<unsigned char*>(list) + (((size_t)g.band_rows * g.wo * 2 + 15) & ~(size_t)15));
     __shared__ unsigned int s_wc[BAND_THREADS / 64], s_prev;
 
     // grid: x = list split (fastest, so the workgroups that share a band start together), y = channel block,
     // z = stream x band
     const int sb = (int)blockIdx.z, zsplit = (int)blockIdx.x, nsplit = (int)gridDim.x;
     const int b = sb / g.nbands, band = sb - b * g.nbands;
-    const int nblk = (g.og + 4 * CW - 1) / (4 * CW);
+    const int nblk = (g.og + 63) / 64;
     const int grp = blockIdx.y / nblk;
     const int blk = blockIdx.y - grp * nblk;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // eight wavefronts: four channel sub-blocks (cwave) times two halves of the list (phalf)
-    const int cwave = wave & 3, phalf = wave >> 2;
     const int oy0 = band * g.band_rows;
     const int rows = min(g.band_rows, g.ho - oy0);
     const int iy0 = oy0 * g.stride - g.pad, ix0 = -g.pad;
     const int wg4 = g.nslab * 4;
 
-    for (int i = tid; i < npos; i += BAND_THREADS) posany[i] = 0;
-    if (WL) {
-        const int nit = g.nslab * g.kh * g.kw;
-        for (int i = tid; i < nit * 4 * CW; i += BAND_THREADS) {
-            const int it = i / (4 * CW), c = i - it * (4 * CW);
-            const int co = blk * 4 * CW + c;  // channel within the group
-            uint4 w = make_uint4(0, 0, 0, 0);
-            if (co < g.nob8 * 8) w = wpack[(((long long)grp * g.nob8 + co / 8) * nit + it) * 8 + (co & 7)];
-            wl[i] = w;
+    // A pass is 64 listed positions x 64 channels.  Each half of the wavefronts takes one of its two tiles of 32 positions,
+    // and the four of a half split the K steps (a tap, 64 channels): a wavefront takes steps w, w + 4, ... and adds its
+    // sums in LDS.  Filter fragments go from memory straight into registers, BAND_KU steps in flight; the first ones do
+    // not depend on the list: they are fetched ahead of it (and stay for every pass if they are all).  (Eight parts of both
+    // tiles: twice the adds, and registers for fewer steps in flight.)
+    const int ntaps = g.kh * g.kw, nkt = 2 * g.nslab, nk = ntaps * nkt;  // K steps per tap, in all
+    const int n = lane & 31, khalf = lane >> 5;
+    const uint4* wfrag = wband + ((long long)(grp * 2 * nblk + 2 * blk) * nk) * 64;
+    const int kpart = wave & 3, tile = wave >> 2;
+    uint4 w[BAND_KU][2];
+    auto load_frags = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < BAND_KU; ++i) {
+            const int k = min(k0 + i * 4, nk - 1);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) w[i][c] = (wfrag + (long long)(c * nk + k) * 64)[(unsigned int)lane];
         }
-    }
+    };
+    for (int i = tid; i < npos; i += BAND_THREADS) posany[i] = 0;
+    for (int i = tid; i < 64 * BAND_RP; i += BAND_THREADS) red[i] = 0;
     __syncthreads();
     // (FUSED) input rows whose changes this band counts, by the workgroup of the band's first channel block
     const int own_lo = oy0 * g.stride, own_hi = band == g.nbands - 1 ? g.h : (oy0 + g.band_rows) * g.stride;
     const bool count_here = FUSED && blk == 0 && zsplit == 0;
-    unsigned int nbits = 0, nunits = 0;
-    // ---- stage A = m & x and B = m & ~x of the band's input window ------------------------------
+    unsigned int nbits = 0, nunits = 0, arrived_before = 0;
+    // ---- stage A = m and B = m & ~x of the band's input window ------------------------------
     if (g.vec4) {
         // four words at a time, both loads issued whatever the mask holds (independent loads, several in flight)
         const int units = npos * g.nslab;
@@ -335,7 +279,7 @@ __global__ __launch_bounds__(BAND_THREADS) void bin_band_kernel(const unsigned i
                 }
             }
             if (m.x | m.y | m.z | m.w) posany[hp] = 1;
-            *reinterpret_cast<uint4*>(A + hp * g.pitch + sl * 4) = make_uint4(m.x & xv.x, m.y & xv.y, m.z & xv.z, m.w & xv.w);
+            *reinterpret_cast<uint4*>(A + hp * g.pitch + sl * 4) = m;
             *reinterpret_cast<uint4*>(B + hp * g.pitch + sl * 4) = make_uint4(m.x & ~xv.x, m.y & ~xv.y, m.z & ~xv.z, m.w & ~xv.w);
         }
     } else {
@@ -353,14 +297,16 @@ __global__ __launch_bounds__(BAND_THREADS) void bin_band_kernel(const unsigned i
                     posany[hp] = 1;
                 }
             }
-            A[hp * g.pitch + wd] = m & xv;
+            A[hp * g.pitch + wd] = m;
             B[hp * g.pitch + wd] = m & ~xv;
         }
     }
     __syncthreads();
+    load_frags(kpart);
     if (FUSED) {
         // this workgroup has read the stored input for the last time
-        if (tid == 0) s_prev = atomicAdd(&arrive[b], 1u);
+        // (thread 0 keeps the answer to the end: stored at once, it would hold up the list by a memory round trip)
+        if (tid == 0) arrived_before = atomicAdd(&arrive[b], 1u);
         if (count_here) {
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) {
@@ -407,20 +353,92 @@ __global__ __launch_bounds__(BAND_THREADS) void bin_band_kernel(const unsigned i
     if (cnt > 0 && blockIdx.y == 0 && zsplit == 0 && tid == 0)
         atomicAdd(&stats[sb & (STAT_SLOTS - 1)].active_tiles, (unsigned long long)cnt);
 
-    // The list is dealt in 64-entry chunks: of every four consecutive chunks the first half of the wavefronts takes
-    // the even ones and the second half the odd ones (so a list of up to 128 entries is one chunk each, not two
-    // for one half), two chunks per pass where a half has two (they share the filter words).
-    const int co_w = blk * 4 * CW + cwave * CW;  // first output channel of this wavefront in the group
-    if (co_w < g.og) {
-        for (int first = zsplit * 256 + phalf * 64; first < cnt; first += nsplit * 256) {
-            if (first + 128 < cnt)
-                band_items<CW, 2, WL>(A, B, list, first, cnt, wpack, wl, y, g, b, oy0, grp, co_w, lane, cwave);
-            else
-                band_items<CW, 1, WL>(A, B, list, first, cnt, wpack, wl, y, g, b, oy0, grp, co_w, lane, cwave);
+    // The list in passes of 64 entries, dealt to the workgroups of a list split.
+    const bool vec = (g.c_out & 3) == 0 && (g.og & 3) == 0;
+    for (int first = zsplit * 64; first < cnt; first += nsplit * 64) {
+        // this thread's part of the pass' results: one position, eight channels; fetched now, needed at the end
+        const int e = first + (tid >> 3), c8 = (tid & 7) * 8, co = blk * 64 + c8;
+        const int qe = list[e < cnt ? e : 0], oye = qe / g.wo;
+        int* yp = y + ((((long long)b * g.ho + oy0 + oye) * g.wo + (qe - oye * g.wo)) * g.c_out + (long long)grp * g.og + co);
+        int yv[8];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            int4 t = make_int4(0, 0, 0, 0);
+            if (e < cnt && co + 4 * h < g.og) {
+                if (vec) {
+                    t = reinterpret_cast<const int4*>(yp)[h];
+                } else {
+                    t.x = yp[4 * h];
+                    t.y = co + 4 * h + 1 < g.og ? yp[4 * h + 1] : 0;
+                    t.z = co + 4 * h + 2 < g.og ? yp[4 * h + 2] : 0;
+                    t.w = co + 4 * h + 3 < g.og ? yp[4 * h + 3] : 0;
+                }
+            }
+            yv[4 * h] = t.x;
+            yv[4 * h + 1] = t.y;
+            yv[4 * h + 2] = t.z;
+            yv[4 * h + 3] = t.w;
         }
+        // this lane's column: the window offset of its listed position (an entry beyond the list repeats its first; its
+        // sums are not read)
+        const bool work = first + 32 * tile < cnt && kpart < nk;  // (the same in every lane)
+        const int ent = first + 32 * tile + n;
+        const int q = list[ent < cnt ? ent : 0], oyl = q / g.wo;
+        const int lbase = ((oyl * g.stride) * g.btw_in + (q - oyl * g.wo) * g.stride) * g.pitch + khalf;
+        v16f acc[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
+#pragma unroll 1
+        for (int k0 = kpart; work && k0 < nk; k0 += BAND_KU * 4) {
+            if (k0 != kpart) load_frags(k0);
+#pragma unroll
+            for (int i = 0; i < BAND_KU; ++i) {
+                const int k = k0 + i * 4;
+                if (k >= nk) break;
+                const int tap = (int)udiv_magic((unsigned int)k, (unsigned int)nkt, g.magic_nkt), st = k - tap * nkt;
+                const int ky = (int)udiv_magic((unsigned int)tap, (unsigned int)g.kw, g.magic_kw), kx = tap - ky * g.kw;
+                const int off = (ky * g.btw_in + kx) * g.pitch + 2 * st;
+                const v8i d = expand_e2m1(A[lbase + off], B[lbase + off]);
+#pragma unroll
+                for (int c = 0; c < 2; ++c) acc[c] = mma_e2m1(w[i][c], d, acc[c]);
+            }
+        }
+        if (nk > BAND_KU * 4 && first + nsplit * 64 < cnt) load_frags(kpart);  // (the next pass')
+        if (work) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    atomicAdd(&red[(32 * tile + n) * BAND_RP + 32 * c + 8 * (r >> 2) + 4 * khalf + (r & 3)], (int)acc[c][r]);
+        }
+        __syncthreads();
+        int v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            v[k] = yv[k] + 2 * red[(tid >> 3) * BAND_RP + c8 + k];
+            red[(tid >> 3) * BAND_RP + c8 + k] = 0;
+        }
+        if (e < cnt) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (vec) {
+                    if (co + 4 * h < g.og)
+                        reinterpret_cast<int4*>(yp)[h] = make_int4(v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]);
+                } else {
+#pragma unroll
+                    for (int k = 4 * h; k < 4 * h + 4; ++k)
+                        if (co + k < g.og) yp[k] = v[k];
+                }
+            }
+        }
+        __syncthreads();  // (the sums are cleared for the next pass)
     }
     if (FUSED) {
-        // commit: the stream's last workgroup to finish staging (s_prev was published by the list's barriers)
+        // commit: the stream's last workgroup to finish staging
+        if (tid == 0) s_prev = arrived_before;
+        __syncthreads();
         if (s_prev == (unsigned int)g.nbands * gridDim.y * (unsigned int)nsplit - 1u) {
             const long long words = (long long)g.h * g.w * g.wpp;  // (a multiple of four: whole 16-byte vectors)
             const uint4* src = reinterpret_cast<const uint4*>(xsrc + (long long)b * words);
@@ -459,18 +477,18 @@ hipError_t launch_one(const void* xsrc, const void* flip, unsigned int* tileflag
 
 int bin_consumers(int cw, const BinGeom& g) { return g.groups * ((g.og + 4 * cw - 1) / (4 * cw)); }
 
-template <int CW, bool FUSED, bool WL>
-hipError_t launch_band_k(const void* xsrc, const void* flip, void* snap, unsigned int* arrive, const void* wpack, void* y,
-                         const BinGeom& g, DevStats* stats, hipStream_t s) {
-    const int nblk = (g.og + 4 * CW - 1) / (4 * CW);
+template <bool FUSED>
+hipError_t launch_band(const void* xsrc, const void* flip, void* snap, unsigned int* arrive, const void* wband, void* y,
+                       const BinGeom& g, DevStats* stats, hipStream_t s) {
+    const int nblk = (g.og + 63) / 64;
     // few streams: deal the band's list over several workgroups (each stages the window again: it is small)
     const long long wgs = (long long)g.n * g.nbands * g.groups * nblk;
-    const int chunks = (g.band_rows * g.wo + 255) / 256;  // (a workgroup takes the list 256 entries at a time)
-    int z = (int)((2 * NUM_CU + wgs - 1) / wgs);
+    const int chunks = (g.band_rows * g.wo + 63) / 64;  // (a workgroup takes the list 64 entries at a time)
+    int z = (int)(2 * NUM_CU / wgs);  // (no more than two workgroups per compute unit: what its registers hold)
     z = z < 1 ? 1 : (z > chunks ? chunks : z);
     dim3 grid((unsigned int)z, (unsigned int)(g.groups * nblk), (unsigned int)(g.n * g.nbands));
     const size_t lds = bin_band_lds_bytes(g, g.band_rows);
-    auto kern = bin_band_kernel<CW, FUSED, WL>;
+    auto kern = bin_band_kernel<FUSED>;
     if (lds > 64 * 1024) {
         static std::mutex mu;
         static size_t granted = 0;
@@ -483,32 +501,23 @@ hipError_t launch_band_k(const void* xsrc, const void* flip, void* snap, unsigne
     }
     hipLaunchKernelGGL(kern, grid, dim3(BAND_THREADS), lds, s, static_cast<const unsigned int*>(xsrc),
                        static_cast<const unsigned int*>(flip), static_cast<unsigned int*>(snap), arrive,
-                       static_cast<const uint4*>(wpack), static_cast<int*>(y), g, stats);
+                       static_cast<const uint4*>(wband), static_cast<int*>(y), g, stats);
     return hipGetLastError();
 }
 
-template <int CW, bool FUSED>
-hipError_t launch_band(const void* xsrc, const void* flip, void* snap, unsigned int* arrive, const void* wpack, void* y,
-                       const BinGeom& g, DevStats* stats, hipStream_t s) {
-    if (g.wlds) return launch_band_k<CW, FUSED, true>(xsrc, flip, snap, arrive, wpack, y, g, stats, s);
-    return launch_band_k<CW, FUSED, false>(xsrc, flip, snap, arrive, wpack, y, g, stats, s);
-}
-
 // two launches: xsrc = the stored input after the difference kernel, flip = its flip buffer
-hipError_t launch_bin_band(int cw, const void* xsrc, const void* flip, const void* wpack, void* y, const BinGeom& g,
+hipError_t launch_bin_band(const void* xsrc, const void* flip, const void* wband, void* y, const BinGeom& g,
                            DevStats* stats, hipStream_t s) {
     if (g.band_rows < 1 || g.band_rows * g.wo > 65535) return hipErrorInvalidValue;  // (list entries are 16 bits)
-    if (cw == 16) return launch_band<16, false>(xsrc, flip, nullptr, nullptr, wpack, y, g, stats, s);
-    return launch_band<8, false>(xsrc, flip, nullptr, nullptr, wpack, y, g, stats, s);
+    return launch_band<false>(xsrc, flip, nullptr, nullptr, wband, y, g, stats, s);
 }
 
 // one launch: the whole step (needs g.fused_ok: every input position lies in the window of the band that owns it,
 // and a group's words per position are whole 16-byte vectors)
-hipError_t launch_bin_band_fused(int cw, const void* x_t, void* x_snap, unsigned int* arrive, const void* wpack, void* y,
+hipError_t launch_bin_band_fused(const void* x_t, void* x_snap, unsigned int* arrive, const void* wband, void* y,
                                  const BinGeom& g, DevStats* stats, hipStream_t s) {
     if (g.band_rows < 1 || g.band_rows * g.wo > 65535 || !g.fused_ok || !arrive) return hipErrorInvalidValue;
-    if (cw == 16) return launch_band<16, true>(x_t, x_snap, x_snap, arrive, wpack, y, g, stats, s);
-    return launch_band<8, true>(x_t, x_snap, x_snap, arrive, wpack, y, g, stats, s);
+    return launch_band<true>(x_t, x_snap, x_snap, arrive, wband, y, g, stats, s);
 }
 
 hipError_t launch_bin_conv(int mode, int cw, const void* xsrc, const void* flip, unsigned int* tileflag,

@@ -9,6 +9,9 @@ namespace rrm {
 
 constexpr int BIN_TILE = 8;        // output tile edge of the tile kernel
 constexpr long long BIN_TILE_MAX_LDS = 152 * 1024;  // both window copies of one tile (160 KB per workgroup, less static use)
+constexpr int BAND_WAVES = 8;      // wavefronts of a band-kernel workgroup
+constexpr int BAND_KU = 3;         // K steps whose filter fragments a wavefront has in flight
+constexpr int BAND_RP = 65;        // row pitch (words) of the 64 x 64 sums of a pass
 constexpr int BIN_NUM_CU = 256;    // compute units of the MI355X
 
 struct BinGeom {
@@ -30,19 +33,20 @@ struct BinGeom {
     unsigned int magic_nslab;  // same for d = nslab
     int vec4;                  // 1: a group's words per position are whole 16-byte vectors (wg % 4 == 0, wpp % 4 == 0)
     int fused_ok;              // 1: the band kernel can run the whole step (compare and commit included)
-    int wlds;                  // 1: the band kernel keeps its workgroup's filter words in LDS
+    unsigned int magic_nkt;    // same for d = 2*nslab (K steps per tap)
+    unsigned int magic_kw;     // same for d = kw
+    int wlds;                  // 1: a band-kernel workgroup takes up to 79 KB of LDS (two per compute unit)
 };
 
 
 inline unsigned int bin_magic_for(int d) { return d <= 1 ? 0u : (unsigned int)((1ull << 32) / (unsigned long long)d + 1ull); }
 
 // dynamic LDS of a band-kernel workgroup with bands of band_rows output rows: the A and B words of the band's input
-// window, one flag byte per window position, the list of active output positions (16 bits each), and (wlds) the
-// filter words of 64 output channels
+// window, one flag byte per window position, the list of active output positions (16 bits each), and the sums of
+// a pass
 inline size_t bin_band_lds_bytes(const BinGeom& g, int band_rows) {
     const size_t npos = (size_t)((band_rows - 1) * g.stride + g.kh) * (size_t)((g.wo - 1) * g.stride + g.kw);
-    const size_t wl = g.wlds ? (size_t)g.nslab * g.kh * g.kw * 64 * 16 : 0;
-    return 2 * npos * g.pitch * 4 + ((npos + 15) & ~(size_t)15) + (((size_t)band_rows * g.wo * 2 + 15) & ~(size_t)15) + wl;
+    return 2 * npos * g.pitch * 4 + ((npos + 15) & ~(size_t)15) + (((size_t)band_rows * g.wo * 2 + 15) & ~(size_t)15) + 64 * BAND_RP * 4;
 }
 
 // Fill the geometry of a binary layer.  False: the input window of one 8x8 output tile does not fit LDS (the layer
@@ -69,10 +73,8 @@ inline bool bin_choose_shape(const rrm_shape& s, BinGeom& g) {
     // unit); as tall as fits when the streams alone fill the chip (a tall band wastes least on its halo rows and
     // fills its 64-lane chunks best), shorter -- down to 4 rows -- while there are fewer than two workgroups per
     // compute unit; no band at all = the tile kernel
-    // (the filter words of a workgroup's 64 channels go to LDS too when they take at most 40 KB; the budget is then
-    // 79 KB per workgroup, still two per compute unit)
-    g.wlds = (long long)g.nslab * s.kh * s.kw * 1024 <= 40 * 1024 ? 1 : 0;
-    const long long band_budget = g.wlds ? 79 * 1024 : 64 * 1024 - 64;
+    g.wlds = 1;
+    const long long band_budget = 79 * 1024;
     g.band_rows = 0;
     for (int r = g.ho; r >= 1; --r)
         if ((long long)bin_band_lds_bytes(g, r) <= band_budget && (long long)r * g.wo <= 65535) {
@@ -90,6 +92,8 @@ inline bool bin_choose_shape(const rrm_shape& s, BinGeom& g) {
     if ((long long)g.n * g.nbands > 65535) g.band_rows = 0;  // (stream x band is the grid's z dimension)
     g.vec4 = (g.wg % 4 == 0 && g.wpp % 4 == 0) ? 1 : 0;
     g.magic_nslab = bin_magic_for(g.nslab);
+    g.magic_nkt = bin_magic_for(2 * g.nslab);
+    g.magic_kw = bin_magic_for(g.kw);
     g.bth_in = ((g.band_rows > 1 ? g.band_rows : 1) - 1) * s.stride + s.kh;
     g.btw_in = (g.wo - 1) * s.stride + s.kw;
     g.magic_btw = bin_magic_for(g.btw_in);

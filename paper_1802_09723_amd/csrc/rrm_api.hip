@@ -60,6 +60,7 @@ struct rrm_layer {
     bool scat_auto = false; // ... and does when "path" is automatic
     void* wsc = nullptr;    // weights packed for it
     unsigned int* sc_arrive = nullptr;  // its arrival counters (one per position block)
+    void* wband = nullptr;   // binary: weights packed for the band kernel (matrix cores)
     unsigned int* bin_arrive = nullptr;  // binary single-launch step: arrival counter per stream
     size_t touched_bytes = 0;
     BinGeom bg{};
@@ -101,7 +102,7 @@ struct rrm_layer {
     int opt_path = 0, opt_wm = 0, opt_fc_splits = 0, opt_terms = 2, opt_bin_cw = 0, opt_conv_kernel = 0, opt_bin_fused = 1;
 
     ~rrm_layer() {
-        void* ptrs[] = {wpack, wpos, wsc, sc_arrive, bin_arrive, offtab, bias, x_snap, y_snap, d0, d1, xpad, bitmap, tileflag, touched, ctrl, fresh, zero16, fc_arrive, fc_part, fc_bpart, csc_ptr, csc_row, csc_val, w_rm, stats};
+        void* ptrs[] = {wpack, wpos, wsc, wband, sc_arrive, bin_arrive, offtab, bias, x_snap, y_snap, d0, d1, xpad, bitmap, tileflag, touched, ctrl, fresh, zero16, fc_arrive, fc_part, fc_bpart, csc_ptr, csc_row, csc_val, w_rm, stats};
         for (void* p : ptrs)
             if (p) (void)hipFree(p);
         for (hipEvent_t e : prof_ev) (void)hipEventDestroy(e);
@@ -562,7 +563,24 @@ rrm_status setup_bin(rrm_layer* L, const std::vector<unsigned char>& w) {
                     const size_t dst = (((((size_t)grp * g.nob8 + co / 8) * g.nslab + slab) * ntaps + tap) * 8 + co % 8) * 4 + wd % 4;
                     pack[dst] = ww[(((size_t)(grp * g.og + co)) * ntaps + tap) * g.wg + wd];
                 }
-    return upload(pack.data(), pack.size() * 4, &L->wpack);
+    rrm_status st = upload(pack.data(), pack.size() * 4, &L->wpack);
+    if (st != RRM_OK || g.band_rows == 0) return st;
+    // band kernel: the weights as 4-bit floats (E2M1: 0x2 = +1, 0xA = -1) in per-lane MFMA order
+    // [group][32-channel block, padded to pairs][tap][K step of 2 words][lane] x 16 bytes: lane l -> output channel
+    // l % 32 of the block, word 2 * step + l / 32 of the group's words; nibble j of register i is bit 4j + i of the
+    // word.  Padded channels and words are zero.
+    const int nkt = 2 * g.nslab, ncb = 2 * ((g.og + 63) / 64);
+    std::vector<unsigned int> band((size_t)s.groups * ncb * ntaps * nkt * 64 * 4, 0u);
+    for (int grp = 0; grp < s.groups; ++grp)
+        for (int co = 0; co < g.og; ++co)
+            for (int tap = 0; tap < ntaps; ++tap)
+                for (int wd = 0; wd < g.wg; ++wd) {
+                    const unsigned int v = ww[(((size_t)(grp * g.og + co)) * ntaps + tap) * g.wg + wd];
+                    const int lane = co % 32 + 32 * (wd & 1);
+                    unsigned int* dst = &band[(((((size_t)(grp * ncb + co / 32)) * ntaps + tap) * nkt + wd / 2) * 64 + lane) * 4];
+                    for (int i = 0; i < 4; ++i) dst[i] = 0xAAAAAAAAu ^ ((v >> i & 0x11111111u) << 3);
+                }
+    return upload(band.data(), band.size() * 4, &L->wband);
 }
 
 rrm_status setup_fc(rrm_layer* L, const std::vector<unsigned char>& w) {
@@ -874,14 +892,14 @@ rrm_status rrm_step(rrm_layer* L, const void* x_t, void* y_out, void* hip_stream
             if (L->bg.fused_ok && L->opt_bin_fused) {
                 // one launch: compare, popcount products of the changed positions, commit
                 if ((st = prof_mark(L, 1, s)) != RRM_OK) return st;  // (no separate difference kernel: its time is reported as 0)
-                RRM_HIP(launch_bin_band_fused(cw, x_t, L->x_snap, L->bin_arrive, L->wpack, L->y_snap, L->bg, L->stats, s));
+                RRM_HIP(launch_bin_band_fused(x_t, L->x_snap, L->bin_arrive, L->wband, L->y_snap, L->bg, L->stats, s));
             } else {
             const bool band = L->bg.band_rows > 0;  // (the band kernel reads the flip words itself: no tile stamps)
             RRM_HIP(launch_scan(L->dtype, x_t, L->x_snap, L->d0, L->d1, L->bitmap, L->tileflag,
                                 band ? 0u : (unsigned int)bin_consumers(cw, L->bg), L->sg, L->stats, s));
             if ((st = prof_mark(L, 1, s)) != RRM_OK) return st;
             if (band)
-                RRM_HIP(launch_bin_band(cw, L->x_snap, L->d0, L->wpack, L->y_snap, L->bg, L->stats, s));
+                RRM_HIP(launch_bin_band(L->x_snap, L->d0, L->wband, L->y_snap, L->bg, L->stats, s));
             else
                 RRM_HIP(launch_bin_conv(MODE_DELTA, cw, L->x_snap, L->d0, L->tileflag, L->wpack, nullptr, L->y_snap, L->bg,
                                         L->stats, s));

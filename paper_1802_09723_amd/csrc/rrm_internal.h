@@ -232,9 +232,10 @@ hipError_t launch_bin_conv(int mode, int cw, const void* xsrc, const void* flip,
                            const void* wpack, const void* bias, void* y, const BinGeom& g, DevStats* stats,
                            hipStream_t s);
 int bin_consumers(int cw, const BinGeom& g);     // workgroups per tile of the binary kernel
-hipError_t launch_bin_band(int cw, const void* xsrc, const void* flip, const void* wpack, void* y, const BinGeom& g,
+// wband: weights as E2M1 fragments [group][32-channel block][K step][lane] x 16 bytes (see setup_bin)
+hipError_t launch_bin_band(const void* xsrc, const void* flip, const void* wband, void* y, const BinGeom& g,
                            DevStats* stats, hipStream_t s);
-hipError_t launch_bin_band_fused(int cw, const void* x_t, void* x_snap, unsigned int* arrive, const void* wpack, void* y,
+hipError_t launch_bin_band_fused(const void* x_t, void* x_snap, unsigned int* arrive, const void* wband, void* y,
                                  const BinGeom& g, DevStats* stats, hipStream_t s);
 
 hipError_t launch_fill_bias(int is_float, void* y, const void* bias, long long rows, int c_out, hipStream_t s);

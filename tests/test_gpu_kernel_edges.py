@@ -24,3 +24,15 @@ def test_window_tile_kernel_with_few_subtiles(shp, dt):
     m, ci, co, k, st, pad, g, n = shp
     seq = S.random_layer(9100 + m, S.conv_shape(m, m, ci, co, k, st, pad, g, n=n), dt, T=4, frac=0.2, block=3)
     run_sequence(seq, check_dense=(0, 3), path=1, conv_kernel=1)
+
+
+# The binary band kernel: 64 output channels per workgroup in two blocks of 32, passes of 64 listed positions in two tiles
+# of 32, K steps of two words dealt to eight wavefronts, a few in flight at a time.
+@pytest.mark.parametrize("ci,co,k,m,n,frac", [
+    (32, 1, 1, 5, 1, 0.5), (128, 31, 3, 8, 1, 0.3), (128, 32, 3, 8, 2, 0.6), (128, 33, 3, 9, 1, 0.95), (256, 64, 3, 12, 3, 0.1),
+    (256, 65, 1, 16, 1, 0.95), (512, 130, 3, 7, 2, 0.2), (128, 96, 5, 17, 1, 0.9), (640, 48, 3, 10, 1, 0.4), (96, 20, 3, 11, 2, 0.3),
+])
+def test_binary_band_kernel_edges(ci, co, k, m, n, frac):
+    seq = S.random_layer(9200 + ci + co, S.conv_shape(m, m + 1, ci, co, k, 1, k // 2, 1, n=n), S.BIN, T=4, frac=frac, block=2)
+    run_sequence(seq, check_dense=(0, 3))
+    run_sequence(seq, check_dense=(), bin_single_launch=0)
