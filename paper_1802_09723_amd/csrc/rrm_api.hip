@@ -697,6 +697,10 @@ rrm_status enqueue_dense(rrm_layer* L, const void* x, void* y, hipStream_t st) {
         else
             RRM_HIP(launch_fc_dense(L->dtype, fc_splits(L), L->wpack, x, L->fc_part, L->bias, y, L->fg, st));
     } else if (L->dtype == RRM_BIN_I32) {
+        if (L->bg.band_rows > 0) {
+            RRM_HIP(launch_bin_band_dense(x, L->wband, L->bias, y, L->bg, L->stats, st));
+            return RRM_OK;
+        }
         RRM_HIP(launch_bin_conv(MODE_DENSE, bin_cw(L), x, nullptr, nullptr, L->wpack, L->bias, y, L->bg, L->stats, st));
     } else {
         if (L->use_pos) {
