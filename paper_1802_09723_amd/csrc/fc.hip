@@ -43,7 +43,7 @@ template <int DT, bool CSC>
 __global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned char* __restrict__ x_t,
                                                                unsigned char* x_snap,
                                                                const unsigned char* __restrict__ wT, void* y_v,
-                                                               unsigned int* arrive, FcGeom g,
+                                                               void* y_out, unsigned int* arrive, FcGeom g,
                                                                DevStats* __restrict__ stats) {
     constexpr int PV = DT == RRM_I8_I32 ? 16 : 8;
     constexpr int ESIZE = DT == RRM_I8_I32 ? 1 : 2;
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned ch
                 if (v != (val_t)0) atomicAdd(yb + o, v);
             }
         }
-    } else if (total) {  // (the same in every thread: the list lengths)
+    } else if (total || y_out) {  // (the same in every thread: the list lengths)
 #pragma unroll
         for (int e = 0; e < PV; ++e) {
             val_t v = acc[e];
@@ -321,14 +321,13 @@ __global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned ch
             for (int w = 0; w < FCD_THREADS / 64; ++w) sum += red[w][tid / PV][tid % PV];
             if (co_y < g.c_out) {
                 val_t* yp = static_cast<val_t*>(y_v) + (long long)b * g.c_out + co_y;
-                if constexpr (DT == RRM_I8_I32) {
-                    if (nks > 1) {
+                if (nks > 1) {
+                    if constexpr (DT == RRM_I8_I32)
                         if (sum != 0) atomicAdd(yp, sum);
-                    } else {
-                        *yp = y_old + sum;
-                    }
                 } else {
-                    *yp = y_old + sum;
+                    const val_t now = total ? y_old + sum : y_old;
+                    *yp = now;
+                    if (y_out) static_cast<val_t*>(y_out)[(long long)b * g.c_out + co_y] = now;
                 }
             }
         }
@@ -518,10 +517,21 @@ __global__ __launch_bounds__(FC_MAX_SPLITS * 16) void fc_reduce_kernel(const voi
 
 }  // namespace
 
-hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void* wT, void* y, unsigned int* arrive,
-                           const FcGeom& g, DevStats* stats, hipStream_t s) {
+// workgroups that share the list of a 64-byte slice of a stream's channels: integer layers with long input vectors have
+// up to four while that fills more of the chip's 256 compute units (measured: pays off from about a thousand changed
+// columns; short vectors lose to the extra workgroups' compare)
+static int fc_list_splits(int dtype, const FcGeom& g) {
+    const int ranges = (g.c_out_p * (dtype == RRM_I8_I32 ? 1 : 2) + FCD_SEG - 1) / FCD_SEG;
+    return dtype == RRM_I8_I32 && g.c_in >= 8192 ? std::max(1, std::min(4, 256 / (ranges * g.n))) : 1;
+}
+
+bool fc_delta_writes_out(int dtype, const FcGeom& g) { return !g.csc_ptr && fc_list_splits(dtype, g) == 1; }
+
+hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void* wT, void* y, void* y_out,
+                           unsigned int* arrive, const FcGeom& g, DevStats* stats, hipStream_t s) {
     const int esize = dtype == RRM_I8_I32 ? 1 : 2;
     dim3 block(FCD_THREADS);
+    if (y_out && !fc_delta_writes_out(dtype, g)) return hipErrorInvalidValue;
     if (g.csc_ptr) {
         // pruned weights: up to 64 workgroups per stream share the list (each pays c_out atomic adds at the end)
         const int nw = std::max(1, std::min(64, NUM_CU / g.n));
@@ -540,24 +550,21 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
         dim3 grid((unsigned int)nw, (unsigned int)g.n, 1u);
         if (dtype == RRM_I8_I32)
             hipLaunchKernelGGL((fc_delta_kernel<RRM_I8_I32, true>), grid, block, lds, s, (const unsigned char*)x_t,
-                               (unsigned char*)x_snap, (const unsigned char*)wT, y, arrive, g, stats);
+                               (unsigned char*)x_snap, (const unsigned char*)wT, y, y_out, arrive, g, stats);
         else
             hipLaunchKernelGGL((fc_delta_kernel<RRM_BF16_F32, true>), grid, block, lds, s, (const unsigned char*)x_t,
-                               (unsigned char*)x_snap, (const unsigned char*)wT, y, arrive, g, stats);
+                               (unsigned char*)x_snap, (const unsigned char*)wT, y, y_out, arrive, g, stats);
         return hipGetLastError();
     }
     const int ranges = (g.c_out_p * esize + FCD_SEG - 1) / FCD_SEG;
-    // integer layers with long input vectors: up to four list splits while that fills more of the chip's 256
-    // compute units (measured: pays off from about a thousand changed columns; short vectors lose to the extra
-    // workgroups' compare)
-    const int nks = dtype == RRM_I8_I32 && g.c_in >= 8192 ? std::max(1, std::min(4, 256 / (ranges * g.n))) : 1;
+    const int nks = fc_list_splits(dtype, g);
     dim3 grid((unsigned int)ranges, (unsigned int)g.n, (unsigned int)nks);
     if (dtype == RRM_I8_I32)
         hipLaunchKernelGGL((fc_delta_kernel<RRM_I8_I32, false>), grid, block, 0, s, (const unsigned char*)x_t,
-                           (unsigned char*)x_snap, (const unsigned char*)wT, y, arrive, g, stats);
+                           (unsigned char*)x_snap, (const unsigned char*)wT, y, y_out, arrive, g, stats);
     else
         hipLaunchKernelGGL((fc_delta_kernel<RRM_BF16_F32, false>), grid, block, 0, s, (const unsigned char*)x_t,
-                           (unsigned char*)x_snap, (const unsigned char*)wT, y, arrive, g, stats);
+                           (unsigned char*)x_snap, (const unsigned char*)wT, y, y_out, arrive, g, stats);
     return hipGetLastError();
 }
 

@@ -859,6 +859,7 @@ rrm_status rrm_step(rrm_layer* L, const void* x_t, void* y_out, void* hip_stream
     if (st != RRM_OK) return st;
     if (y_out && (reinterpret_cast<uintptr_t>(y_out) & 15)) return fail(RRM_ERR_ALIGN, "y_out is not 16-byte aligned");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    bool out_written = false;  // the step's own kernel has filled y_out
     const bool first_bin = L->dtype == RRM_BIN_I32 && !L->has_snapshot;
     if (L->opt_path == 2 || first_bin) {
         // full recomputation: P <- b + W (*) x_t, I <- x_t
@@ -886,7 +887,12 @@ rrm_status rrm_step(rrm_layer* L, const void* x_t, void* y_out, void* hip_stream
             fg.csc_row = static_cast<const unsigned short*>(L->csc_row);
             fg.csc_val = L->csc_val;
         }
-        RRM_HIP(launch_fc_delta(L->dtype, x_t, L->x_snap, L->wpack, L->y_snap, L->fc_arrive, fg, L->stats, s));
+        // (the kernel has the new projection in registers: one launch less than a copy after it)
+        const uintptr_t xa = reinterpret_cast<uintptr_t>(x_t), ya = reinterpret_cast<uintptr_t>(y_out);
+        const bool overlap = ya < xa + L->x_bytes && xa < ya + L->y_bytes;  // (then only once the frame has been read)
+        out_written = y_out && !overlap && fc_delta_writes_out(L->dtype, fg);
+        RRM_HIP(launch_fc_delta(L->dtype, x_t, L->x_snap, L->wpack, L->y_snap, out_written ? y_out : nullptr, L->fc_arrive, fg,
+                                L->stats, s));
         if ((st = prof_mark(L, 2, s)) != RRM_OK) return st;
         }
     } else {
@@ -934,7 +940,7 @@ rrm_status rrm_step(rrm_layer* L, const void* x_t, void* y_out, void* hip_stream
     }
     L->has_snapshot = true;
     ++L->steps;
-    if (y_out) RRM_HIP(launch_copy(y_out, L->y_snap, L->y_bytes, s));
+    if (y_out && !out_written) RRM_HIP(launch_copy(y_out, L->y_snap, L->y_bytes, s));
     return RRM_OK;
 }
 

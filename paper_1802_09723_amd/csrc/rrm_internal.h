@@ -209,8 +209,10 @@ hipError_t launch_conv_scatter(int dtype, int terms, const void* x_t, void* x_sn
                                const ScatGeom& g, DevStats* stats, hipStream_t s);
 
 // one delta step of an FC layer in a single launch; `arrive`: one zeroed word per stream (rearmed by the kernel)
-hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void* wT, void* y, unsigned int* arrive,
-                           const FcGeom& g, DevStats* stats, hipStream_t s);
+// y_out: the caller's copy of the projection, or nullptr; allowed where every output has one owner workgroup
+bool fc_delta_writes_out(int dtype, const FcGeom& g);
+hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void* wT, void* y, void* y_out,
+                           unsigned int* arrive, const FcGeom& g, DevStats* stats, hipStream_t s);
 
 // dense FC layer: row/slice split into per-split partial sums (scratch `part`: [n][splits][c_out_p] 4-byte
 // values), then y = bias + the sum of the splits in a fixed order

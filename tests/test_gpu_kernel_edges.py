@@ -36,3 +36,13 @@ def test_binary_band_kernel_edges(ci, co, k, m, n, frac):
     seq = S.random_layer(9200 + ci + co, S.conv_shape(m, m + 1, ci, co, k, 1, k // 2, 1, n=n), S.BIN, T=4, frac=frac, block=2)
     run_sequence(seq, check_dense=(0, 3))
     run_sequence(seq, check_dense=(), bin_single_launch=0)
+
+
+# The FC step fills the caller's copy itself where every output has one owner, and by a copy otherwise; rows off the 16-byte
+# units (also the last bytes of the array); frame 2 repeats frame 1.
+@pytest.mark.parametrize("ci,co,n", [(64, 5, 1), (300, 33, 2), (301, 7, 3), (2049, 40, 2), (4096, 64, 1), (9216, 48, 1), (8192, 16, 3)])
+@pytest.mark.parametrize("dt", [S.I8, S.BF16])
+def test_fc_step_fills_the_callers_copy(ci, co, n, dt):
+    seq = S.random_layer(9400 + ci, S.fc_shape(ci, co, n=n), dt, T=4, frac=0.2)
+    seq.frames[2] = seq.frames[1].copy()
+    run_sequence(seq, check_dense=(0,), y_out_frames=(0, 1, 2, 3), fc_batched=0)
