@@ -74,24 +74,40 @@ __global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned ch
     unsigned int ntrunc = 0, total = 0;
     float tsq = 0.f;
 
-    // the two copies of one 16-byte unit (PV entries from element e0 of the row); rows that are not 16-byte
-    // multiples are gathered element by element (zeros beyond the row's end)
+    // the two copies of one 16-byte unit (PV entries from element e0 of the row).  Rows that are not 16-byte
+    // multiples: the five aligned words around the unit, all in flight together, shifted into place, with zeros beyond
+    // the row's end (element by element the loads waited for each other: 3945 -> 413
+    // bf16, one stream, 11.1 -> 8.5 us)
     auto load_unit = [&](int e0, uint4& a, uint4& s) {
         if (g.vec_ok) {
             a = *reinterpret_cast<const uint4*>(x_t + (row + e0) * ESIZE);
             s = *reinterpret_cast<const uint4*>(x_snap + (row + e0) * ESIZE);
             return;
         }
-        unsigned int aw[4] = {0u, 0u, 0u, 0u}, sw[4] = {0u, 0u, 0u, 0u};
-        for (int e = 0; e < PV; ++e) {
-            if (e0 + e >= g.c_in) break;
-            if (DT == RRM_I8_I32) {
-                aw[e >> 2] |= (unsigned int)x_t[row + e0 + e] << (8 * (e & 3));
-                sw[e >> 2] |= (unsigned int)x_snap[row + e0 + e] << (8 * (e & 3));
-            } else {
-                aw[e >> 1] |= (unsigned int)reinterpret_cast<const unsigned short*>(x_t)[row + e0 + e] << (16 * (e & 1));
-                sw[e >> 1] |= (unsigned int)reinterpret_cast<const unsigned short*>(x_snap)[row + e0 + e] << (16 * (e & 1));
+        const long long off = (row + e0) * ESIZE, total_bytes = (long long)g.n * g.c_in * ESIZE;
+        const unsigned int sh = (unsigned int)off & 3u;
+        unsigned int ra[5], rs[5];
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            const long long d = off - sh + 4 * i;
+            ra[i] = rs[i] = 0u;
+            if (d + 4 <= total_bytes) {
+                ra[i] = *reinterpret_cast<const unsigned int*>(x_t + d);
+                rs[i] = *reinterpret_cast<const unsigned int*>(x_snap + d);
+            } else {  // (the array's last bytes)
+                for (int k = 0; k < 4 && d + k < total_bytes; ++k) {
+                    ra[i] |= (unsigned int)x_t[d + k] << (8 * k);
+                    rs[i] |= (unsigned int)x_snap[d + k] << (8 * k);
+                }
             }
+        }
+        unsigned int aw[4], sw[4];
+        const int valid = (g.c_in - e0) * ESIZE;  // bytes of the row from here on
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const unsigned int keep = valid >= 4 * i + 4 ? 0xFFFFFFFFu : (valid <= 4 * i ? 0u : (1u << (8 * (valid - 4 * i))) - 1u);
+            aw[i] = __builtin_amdgcn_alignbyte(ra[i + 1], ra[i], sh) & keep;
+            sw[i] = __builtin_amdgcn_alignbyte(rs[i + 1], rs[i], sh) & keep;
         }
         a = make_uint4(aw[0], aw[1], aw[2], aw[3]);
         s = make_uint4(sw[0], sw[1], sw[2], sw[3]);
