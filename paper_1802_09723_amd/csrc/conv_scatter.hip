@@ -50,6 +50,9 @@ __device__ __forceinline__ unsigned int f32_to_bf16(float f) {  // round to near
 
 constexpr int ST = 256;  // threads
 
+// Workgroup barrier that publishes LDS contents only (__syncthreads() would also wait for the weights under way)
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 template <int DT, int TERMS>
 __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restrict__ x_t, uint4* x_snap,
                                                           const uint4* __restrict__ wsc, void* y_v, ScatGeom g,
@@ -76,9 +79,34 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
     DevStats* stats = stats_base + (blockIdx.x & (STAT_SLOTS - 1));
     sc_t* y = static_cast<sc_t*>(y_v);
 
+    // The step is a chain of memory round trips, so what does not depend on another is under way together: all of this
+    // thread's units of both frames, then the weights of the wavefront's first work item (an unchanged block fetches
+    // them for nothing).
+    uint4 xa[UPT], xb[UPT];
+#pragma unroll
+    for (int i = 0; i < UPT; ++i) {
+        const int v = tid + ST * i;
+        xa[i] = xb[i] = make_uint4(0, 0, 0, 0);
+        if (v < nunits) {
+            xa[i] = x_t[u0 + v];
+            xb[i] = x_snap[u0 + v];
+        }
+    }
+    const int nitems = g.npair * g.ntaps * g.nkp, istep = (ST / 64) * (int)gridDim.y;
+    int item = (int)blockIdx.y + wave * (int)gridDim.y;
+    uint4 a[8];
+    auto load_weights = [&]() {
+        const int pt = item / g.nkp, k0 = (item - pt * g.nkp) * 8;
+        const uint4* wp = wsc + ((size_t)pt * g.nk + k0) * 64 + lane;
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (k0 + k < g.nk) a[k] = wp[(size_t)k * 64];
+    };
+    if (item < nitems) load_weights();
+
     if (tid < 64) s_flag[tid] = 0u;
     if (tid == 0) *zero_unit = make_uint4(0, 0, 0, 0);
-    __syncthreads();
+    lds_barrier();
 
     // ---- difference with the stored input (Algorithm 1), kept in LDS; new snapshot values in registers -----------
     uint4 keep[UPT];
@@ -89,7 +117,7 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
     for (int i = 0; i < UPT; ++i) {
         const int v = tid + ST * i;
         if (v >= nunits) break;
-        const uint4 a = x_t[u0 + v], b = x_snap[u0 + v];
+        const uint4 a = xa[i], b = xb[i];
         uint4 d0v = make_uint4(0, 0, 0, 0), d1v = d0v;
         bool changed = ((a.x ^ b.x) | (a.y ^ b.y) | (a.z ^ b.z) | (a.w ^ b.w)) != 0u;
         if (changed) {
@@ -151,10 +179,12 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
         dl[v] = d0v;
         if (TERMS == 2) dl[plane + v] = d1v;
     }
-    __syncthreads();
+    lds_barrier();
     // every read of the stored input by this workgroup is done
     const bool shared_block = gridDim.y > 1;
-    if (shared_block && tid == 0) s_prev = atomicAdd(&g.arrive[blockIdx.x], 1u);
+    // (thread 0 keeps the answer to the end: stored at once, it would hold up the list by a memory round trip)
+    unsigned int arrived_before = 0;
+    if (shared_block && tid == 0) arrived_before = atomicAdd(&g.arrive[blockIdx.x], 1u);
 
     // ---- changed positions of the block -> column list (one ballot: a block has at most 64 positions) -----------
     if (wave == 0) {
@@ -163,7 +193,7 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
         if (f) s_list[__popcll(m & ((1ull << lane) - 1ull))] = lane;
         if (lane == 0) s_cnt = (int)__popcll(m);
     }
-    __syncthreads();
+    lds_barrier();
     const int cnt = s_cnt;
 
     // ---- statistics (one workgroup per position block) --------------------------------------------------------------
@@ -217,8 +247,7 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
             ciy[t] = r / g.w;
             cix[t] = r - ciy[t] * g.w;
         }
-        const int nitems = g.npair * g.ntaps * g.nkp;
-        for (int item = (int)blockIdx.y + wave * (int)gridDim.y; item < nitems; item += (ST / 64) * (int)gridDim.y) {
+        for (; item < nitems;) {
             const int pt = item / g.nkp, kp = item - pt * g.nkp;
             const int pair = pt / g.ntaps, tap = pt - pair * g.ntaps;
             const int grp = pair / g.ncb, cb = pair - grp * g.ncb;
@@ -229,12 +258,7 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[t][r] = 0;
             const int k0 = kp * 8;
-            const uint4* wp = wsc + ((size_t)(pair * g.ntaps + tap) * g.nk + k0) * 64 + lane;
             const int ub = grp * g.ug;  // first unit of the group within a position
-            uint4 a[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (k0 + k < g.nk) a[k] = wp[(size_t)k * 64];
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 if (k0 + k >= g.nk) break;
@@ -247,6 +271,8 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
                     if (TERMS == 2) acc[t] = mma(a[k], chunk < g.ug ? bp[plane] : *zero_unit, acc[t]);
                 }
             }
+            item += istep;
+            if (item < nitems) load_weights();  // (ahead of this item's atomic adds)
             // column p of this tap's product belongs to the output position that sees input position p under the tap
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
@@ -268,7 +294,8 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
 
     // ---- commit the stored input (only where a difference was applied) ---------------------------------------------
     if (shared_block) {
-        __syncthreads();  // (s_prev is visible to every thread)
+        if (tid == 0) s_prev = arrived_before;
+        __syncthreads();
         if (s_prev != gridDim.y - 1u) return;
         if (tid == 0) g.arrive[blockIdx.x] = 0u;
     }
