@@ -214,8 +214,8 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
     extern __shared__ uint4 smem[];
     const int npos = g.bth_in * g.btw_in;
     unsigned int* A = reinterpret_cast<unsigned int*>(smem);
-    unsigned int* B = A + npos * g.pitch;
-    unsigned char* posany = reinterpret_cast<unsigned char*>(B + npos * g.pitch);     // input position holds a flip
+    unsigned int* B = A + npos * g.bpitch;
+    unsigned char* posany = reinterpret_cast<unsigned char*>(B + npos * g.bpitch);     // input position holds a flip
     unsigned short* list = reinterpret_cast<unsigned short*>(posany + ((npos + 15) & ~15));  // active output positions
     // sums of a pass: 64 positions x 64 channels, rows padded by one word (the lanes of an add are 32 positions)
     int* red = reinterpret_cast<int*>(reinterpret_cast<unsigned char*>(list) + (((size_t)g.band_rows * g.wo * 2 + 15) & ~(size_t)15));
@@ -284,8 +284,8 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
                 }
             }
             if (m.x | m.y | m.z | m.w) posany[hp] = 1;
-            *reinterpret_cast<uint4*>(A + hp * g.pitch + sl * 4) = m;
-            *reinterpret_cast<uint4*>(B + hp * g.pitch + sl * 4) = make_uint4(m.x & ~xv.x, m.y & ~xv.y, m.z & ~xv.z, m.w & ~xv.w);
+            *reinterpret_cast<uint4*>(A + hp * g.bpitch + sl * 4) = m;
+            *reinterpret_cast<uint4*>(B + hp * g.bpitch + sl * 4) = make_uint4(m.x & ~xv.x, m.y & ~xv.y, m.z & ~xv.z, m.w & ~xv.w);
         }
     } else {
         const int units = npos * wg4;
@@ -302,8 +302,8 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
                     posany[hp] = 1;
                 }
             }
-            A[hp * g.pitch + wd] = m;
-            B[hp * g.pitch + wd] = m & ~xv;
+            A[hp * g.bpitch + wd] = m;
+            B[hp * g.bpitch + wd] = m & ~xv;
         }
     }
     __syncthreads();
@@ -395,7 +395,7 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
         const bool work = first + 32 * tile < cnt && kpart < nk;  // (the same in every lane)
         const int ent = first + 32 * tile + n;
         const int q = list[ent < cnt ? ent : 0], oyl = q / g.wo;
-        const int lbase = ((oyl * g.stride) * g.btw_in + (q - oyl * g.wo) * g.stride) * g.pitch + khalf;
+        const int lbase = ((oyl * g.stride) * g.btw_in + (q - oyl * g.wo) * g.stride) * g.bpitch + khalf;
         v16f acc[2];
 #pragma unroll
         for (int c = 0; c < 2; ++c)
@@ -410,7 +410,7 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
                 if (k >= nk) break;
                 const int tap = (int)udiv_magic((unsigned int)k, (unsigned int)nkt, g.magic_nkt), st = k - tap * nkt;
                 const int ky = (int)udiv_magic((unsigned int)tap, (unsigned int)g.kw, g.magic_kw), kx = tap - ky * g.kw;
-                const int off = (ky * g.btw_in + kx) * g.pitch + 2 * st;
+                const int off = (ky * g.btw_in + kx) * g.bpitch + 2 * st;
                 const v8i d = expand_e2m1(A[lbase + off], B[lbase + off]);
 #pragma unroll
                 for (int c = 0; c < 2; ++c) acc[c] = mma_e2m1(w[i][c], d, acc[c]);
@@ -492,10 +492,11 @@ template <bool FUSED, bool DENSE = false>
 hipError_t launch_band(const void* xsrc, const void* flip, void* snap, unsigned int* arrive, const void* wband, const void* bias, void* y,
                        const BinGeom& g, DevStats* stats, hipStream_t s) {
     const int nblk = (g.og + 63) / 64;
-    // few streams: deal the band's list over several workgroups (each stages the window again: it is small)
+    // few streams: deal the band's list over several workgroups (each stages the window again: it is small, but for a wide
+    // layer, which gets one workgroup per compute unit: 4 x 350, 128 -> 256, 16 streams, 5 %, 15.8 us with two, 10.8 with one)
     const long long wgs = (long long)g.n * g.nbands * g.groups * nblk;
     const int chunks = (g.band_rows * g.wo + 63) / 64;  // (a workgroup takes the list 64 entries at a time)
-    int z = (int)(2 * NUM_CU / wgs);  // (no more than two workgroups per compute unit: what its registers hold)
+    int z = (int)((g.bpitch < g.pitch ? 1 : 2) * NUM_CU / wgs);  // (no more than two workgroups per compute unit: what its registers hold)
     z = z < 1 ? 1 : (z > chunks ? chunks : z);
     dim3 grid((unsigned int)z, (unsigned int)(g.groups * nblk), (unsigned int)(g.n * g.nbands));
     const size_t lds = bin_band_lds_bytes(g, g.band_rows);

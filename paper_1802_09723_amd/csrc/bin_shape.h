@@ -12,6 +12,9 @@ constexpr long long BIN_TILE_MAX_LDS = 152 * 1024;  // both window copies of one
 constexpr int BAND_WAVES = 8;      // wavefronts of a band-kernel workgroup
 constexpr int BAND_KU = 3;         // K steps whose filter fragments a wavefront has in flight
 constexpr int BAND_RP = 65;        // row pitch (words) of the 64 x 64 sums of a pass
+constexpr int BAND_SUMS = 64 * BAND_RP * 4;    // bytes of them
+constexpr long long BAND_LDS = 79 * 1024;      // LDS of a band-kernel workgroup (two per compute unit)
+constexpr long long BAND_WIDE_FRAME = 128 * 1024;  // a stream's frame up to which a wide layer has bands
 constexpr int BIN_NUM_CU = 256;    // compute units of the MI355X
 
 struct BinGeom {
@@ -35,7 +38,7 @@ struct BinGeom {
     int fused_ok;              // 1: the band kernel can run the whole step (compare and commit included)
     unsigned int magic_nkt;    // same for d = 2*nslab (K steps per tap)
     unsigned int magic_kw;     // same for d = kw
-    int wlds;                  // 1: a band-kernel workgroup takes up to 79 KB of LDS (two per compute unit)
+    int bpitch;                // LDS words per staged position of the band kernel: `pitch`, or without its padding
 };
 
 
@@ -46,7 +49,7 @@ inline unsigned int bin_magic_for(int d) { return d <= 1 ? 0u : (unsigned int)((
 // a pass
 inline size_t bin_band_lds_bytes(const BinGeom& g, int band_rows) {
     const size_t npos = (size_t)((band_rows - 1) * g.stride + g.kh) * (size_t)((g.wo - 1) * g.stride + g.kw);
-    return 2 * npos * g.pitch * 4 + ((npos + 15) & ~(size_t)15) + (((size_t)band_rows * g.wo * 2 + 15) & ~(size_t)15) + 64 * BAND_RP * 4;
+    return 2 * npos * g.bpitch * 4 + ((npos + 15) & ~(size_t)15) + (((size_t)band_rows * g.wo * 2 + 15) & ~(size_t)15) + BAND_SUMS;
 }
 
 // Fill the geometry of a binary layer.  False: the input window of one 8x8 output tile does not fit LDS (the layer
@@ -73,19 +76,28 @@ inline bool bin_choose_shape(const rrm_shape& s, BinGeom& g) {
     // unit); as tall as fits when the streams alone fill the chip (a tall band wastes least on its halo rows and
     // fills its 64-lane chunks best), shorter -- down to 4 rows -- while there are fewer than two workgroups per
     // compute unit; no band at all = the tile kernel
-    g.wlds = 1;
-    const long long band_budget = 79 * 1024;
+    // Wide layers, of which one output row fits that budget without the sums of a pass but not with them, stage their
+    // window without the padding: still two workgroups per compute unit.  (3 x 3, 5 % of the values flipping: 2 x 350, 128
+    // -> 128 channels, 64 streams, 37.1 us on the tile kernel and 12.5 on bands; 4 x 350, 128 -> 256, 50.6 and 21.0; 16 x
+    // 350, 128 -> 512, one stream, 17.4 and 11.7.)  Not where a stream's frame is large: its last workgroup copies it
+    // alone (350 x 350, 128 -> 64, one stream: 27 and 80 us; 64 x 350, 128 -> 128, 8 streams, 1 %: 26 and 32).
+    g.bpitch = g.pitch;
     g.band_rows = 0;
-    for (int r = g.ho; r >= 1; --r)
-        if ((long long)bin_band_lds_bytes(g, r) <= band_budget && (long long)r * g.wo <= 65535) {
+    const long long row_lds = (long long)bin_band_lds_bytes(g, 1);
+    const bool wide = row_lds > BAND_LDS;
+    if (wide && row_lds <= BAND_LDS + BAND_SUMS && (long long)g.h * g.w * g.wpp * 4 <= BAND_WIDE_FRAME) g.bpitch = 4 * g.nslab;
+    for (int r = g.ho; r >= 1 && (!wide || g.bpitch < g.pitch); --r)
+        if ((long long)bin_band_lds_bytes(g, r) <= BAND_LDS && (long long)r * g.wo <= 65535) {
             g.band_rows = r;
             break;
         }
+    if (g.band_rows == 0) g.bpitch = g.pitch;
     g.nbands = 1;
     if (g.band_rows > 0) {
         g.nbands = (g.ho + g.band_rows - 1) / g.band_rows;
         const long long per_band = (long long)g.n * g.groups * ((g.og + 63) / 64);
-        while (per_band * g.nbands < 2 * BIN_NUM_CU && (g.ho + g.nbands) / (g.nbands + 1) >= 4) ++g.nbands;
+        // (a row of a wide layer holds several passes of 64 positions: down to one row)
+        while (per_band * g.nbands < 2 * BIN_NUM_CU && g.nbands < g.ho && (wide || (g.ho + g.nbands) / (g.nbands + 1) >= 4)) ++g.nbands;
         g.band_rows = (g.ho + g.nbands - 1) / g.nbands;
         g.nbands = (g.ho + g.band_rows - 1) / g.band_rows;
     }

@@ -697,7 +697,9 @@ rrm_status enqueue_dense(rrm_layer* L, const void* x, void* y, hipStream_t st) {
         else
             RRM_HIP(launch_fc_dense(L->dtype, fc_splits(L), L->wpack, x, L->fc_part, L->bias, y, L->fg, st));
     } else if (L->dtype == RRM_BIN_I32) {
-        if (L->bg.band_rows > 0) {
+        // (the whole map of a wide layer, see bin_shape.h: the tile kernel; 4 x 1100, 128 -> 1024 channels 1 x 1, 11.4 us there and
+        // 15.9 on bands, 24 x 350, 128 -> 512 3 x 3, 19.8 and 18.6, 16 x 350, 128 -> 64, 16 streams, 21.4 and 23.5)
+        if (L->bg.band_rows > 0 && L->bg.bpitch == L->bg.pitch) {
             RRM_HIP(launch_bin_band_dense(x, L->wband, L->bias, y, L->bg, L->stats, st));
             return RRM_OK;
         }

@@ -38,6 +38,21 @@ def test_binary_band_kernel_edges(ci, co, k, m, n, frac):
     run_sequence(seq, check_dense=(), bin_single_launch=0)
 
 
+# Wide binary layers: one output row fits LDS only without the padding of the staged positions.  (h, w, c_in, c_out, k,
+# stride, pad, groups, n): one row and several per band, whole 16-byte vectors and not, columns that no window reads
+# (difference kernel in front), several channel blocks, groups; the dense layer takes the tile kernel.
+@pytest.mark.parametrize("h,w,ci,co,k,st,pad,g,n,frac", [
+    (2, 350, 128, 33, 3, 1, 1, 1, 2, 0.1), (4, 365, 128, 64, 3, 1, 1, 1, 1, 0.6), (3, 345, 64, 70, 3, 1, 1, 1, 1, 0.3),
+    (4, 340, 128, 16, 3, 1, 1, 1, 140, 0.05), (2, 1100, 128, 5, 1, 1, 0, 1, 3, 0.2), (3, 1100, 128, 8, 1, 2, 0, 1, 1, 0.2),
+    (2, 470, 512, 65, 1, 1, 0, 1, 1, 0.9), (2, 350, 256, 24, 3, 1, 1, 2, 2, 0.1),
+])
+def test_binary_wide_layer_on_bands(h, w, ci, co, k, st, pad, g, n, frac):
+    seq = S.random_layer(9300 + w + co, S.conv_shape(h, w, ci, co, k, st, pad, g, n=n), S.BIN, T=4, frac=frac, block=2)
+    stats, _ = run_sequence(seq, check_dense=(0, 3))
+    assert stats["tile_positions"] == 1  # (listed positions: the band kernel)
+    run_sequence(seq, check_dense=(), bin_single_launch=0)
+
+
 # The FC step fills the caller's copy itself where every output has one owner, and by a copy otherwise; rows off the 16-byte
 # units (also the last bytes of the array); frame 2 repeats frame 1.
 @pytest.mark.parametrize("ci,co,n", [(64, 5, 1), (300, 33, 2), (301, 7, 3), (2049, 40, 2), (4096, 64, 1), (9216, 48, 1), (8192, 16, 3)])

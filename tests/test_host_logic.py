@@ -80,8 +80,8 @@ def test_position_kernel_unit_shapes_terminate_and_fit(tmp_path):
 
 def test_binary_band_geometry_terminates_fits_and_covers(tmp_path):
     """The band choice of the binary delta kernel (pure host code), compiled alone and run over the configuration
-    shapes and a sweep: it must end; the bands cover every output row; a band's window, flags, list and filter words
-    fit the LDS budget; and where the single-launch step is allowed every input position lies in the window of the band
+    shapes and a sweep: it must end; the bands cover every output row; a band's window, flags, list and sums fit
+    the LDS budget; and where the single-launch step is allowed every input position lies in the window of the band
     that owns its row (else a change would be missed or counted twice)."""
     import os
     import re
@@ -95,6 +95,10 @@ def test_binary_band_geometry_terminates_fits_and_covers(tmp_path):
              (64, 14, 14, 512, 512, 3, 1, 1, 1), (1, 6, 300, 256, 16, 3, 1, 1, 1), (3, 30, 26, 128, 48, 3, 1, 1, 1),
              (1, 40, 40, 64, 32, 3, 1, 1, 1), (70000, 8, 8, 32, 8, 3, 1, 1, 1), (2, 11, 9, 128, 32, 3, 2, 1, 2),
              (1, 9, 9, 32, 8, 1, 2, 0, 1), (5, 200, 200, 32, 8, 5, 1, 2, 1)]
+    # wide layers whose row fits only without the padding of the staged positions: bands, as long as a frame is small
+    wide = [(1, 16, 350, 128, 128, 3, 1, 1, 1), (64, 4, 365, 128, 256, 3, 1, 1, 1), (3, 5, 335, 64, 130, 3, 1, 1, 1), (2, 4, 990, 128, 8, 1, 1, 0, 1),
+            (1, 4, 1200, 128, 64, 1, 1, 0, 1), (2, 2, 470, 512, 65, 1, 1, 0, 1), (2, 3, 350, 256, 24, 3, 1, 1, 2)]
+    cases += wide
     rng = np.random.default_rng(17)
     for _ in range(80):
         k = int(rng.choice([1, 3, 5, 7]))
@@ -109,13 +113,14 @@ def test_binary_band_geometry_terminates_fits_and_covers(tmp_path):
         f = {k: int(v) for k, v in re.findall(r"(\w+)=(\d+)", out)}
         n, h, w, ci, co, k, stride, pad, grp = cse
         assert f["ho"] == (h + 2 * pad - k) // stride + 1 and f["wo"] == (w + 2 * pad - k) // stride + 1
+        assert cse not in wide or (f["R"] > 0 and f["bpitch"] < f["pitch"]), (cse, f)
         if f["R"] == 0:
             continue
         banded += 1
         R, nb = f["R"], f["nbands"]
         assert nb * R >= f["ho"] and (nb - 1) * R < f["ho"], (cse, f)           # every output row in exactly one band
         assert n * nb <= 65535 and R * f["wo"] <= 65535, (cse, f)               # grid and 16-bit list entries
-        assert f["lds"] <= (79 * 1024 if f["wlds"] else 64 * 1024 - 64), (cse, f)
+        assert f["lds"] <= 79 * 1024 and f["bpitch"] in (f["pitch"], 4 * f["nslab"]), (cse, f)
         assert f["bth"] == (R - 1) * stride + k and f["btw"] == (f["wo"] - 1) * stride + k, (cse, f)
         if f["fused"]:
             fused += 1
