@@ -50,7 +50,7 @@ __device__ __forceinline__ unsigned int f32_to_bf16(float f) {  // round to near
 
 constexpr int ST = 256;  // threads
 
-// Workgroup barrier that publishes LDS contents only (__syncthreads() would also wait for the weights under way)
+// Workgroup barrier that publishes LDS contents only (__syncthreads() would also wait for the answer of the arrival counter)
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <int DT, int TERMS>
@@ -79,31 +79,6 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
     DevStats* stats = stats_base + (blockIdx.x & (STAT_SLOTS - 1));
     sc_t* y = static_cast<sc_t*>(y_v);
 
-    // The step is a chain of memory round trips, so what does not depend on another is under way together: all of this
-    // thread's units of both frames, then the weights of the wavefront's first work item (an unchanged block fetches
-    // them for nothing).
-    uint4 xa[UPT], xb[UPT];
-#pragma unroll
-    for (int i = 0; i < UPT; ++i) {
-        const int v = tid + ST * i;
-        xa[i] = xb[i] = make_uint4(0, 0, 0, 0);
-        if (v < nunits) {
-            xa[i] = x_t[u0 + v];
-            xb[i] = x_snap[u0 + v];
-        }
-    }
-    const int nitems = g.npair * g.ntaps * g.nkp, istep = (ST / 64) * (int)gridDim.y;
-    int item = (int)blockIdx.y + wave * (int)gridDim.y;
-    uint4 a[8];
-    auto load_weights = [&]() {
-        const int pt = item / g.nkp, k0 = (item - pt * g.nkp) * 8;
-        const uint4* wp = wsc + ((size_t)pt * g.nk + k0) * 64 + lane;
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (k0 + k < g.nk) a[k] = wp[(size_t)k * 64];
-    };
-    if (item < nitems) load_weights();
-
     if (tid < 64) s_flag[tid] = 0u;
     if (tid == 0) *zero_unit = make_uint4(0, 0, 0, 0);
     lds_barrier();
@@ -117,7 +92,7 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
     for (int i = 0; i < UPT; ++i) {
         const int v = tid + ST * i;
         if (v >= nunits) break;
-        const uint4 a = xa[i], b = xb[i];
+        const uint4 a = x_t[u0 + v], b = x_snap[u0 + v];
         uint4 d0v = make_uint4(0, 0, 0, 0), d1v = d0v;
         bool changed = ((a.x ^ b.x) | (a.y ^ b.y) | (a.z ^ b.z) | (a.w ^ b.w)) != 0u;
         if (changed) {
@@ -182,7 +157,11 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
     lds_barrier();
     // every read of the stored input by this workgroup is done
     const bool shared_block = gridDim.y > 1;
-    // (thread 0 keeps the answer to the end: stored at once, it would hold up the list by a memory round trip)
+    // (thread 0 keeps the answer to the end: stored at once, it would hold up the list by a memory round trip.  Weights are
+    // fetched after the list, by the blocks with a change only: fetched ahead of the compare, with all of the thread's units of
+    // both frames, they cost more than they hid; one stream, bf16 3 x 3: 20 x 20 x 96, 3 % of the positions changing, 7.95 -> 8.4 us,
+    // 14 x 14 x 256, 5 %, 10.5 -> 11.1, 7 x 7 x 512 with no change 8.2 -> 8.95; only 7 x 7 x 512 at 5 % gained,
+    // 13.5 -> 13.1, and 10 x 10 x 320 over 4 streams at 10 %, 25.4 -> 24.1)
     unsigned int arrived_before = 0;
     if (shared_block && tid == 0) arrived_before = atomicAdd(&g.arrive[blockIdx.x], 1u);
 
@@ -247,7 +226,8 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
             ciy[t] = r / g.w;
             cix[t] = r - ciy[t] * g.w;
         }
-        for (; item < nitems;) {
+        const int nitems = g.npair * g.ntaps * g.nkp;
+        for (int item = (int)blockIdx.y + wave * (int)gridDim.y; item < nitems; item += (ST / 64) * (int)gridDim.y) {
             const int pt = item / g.nkp, kp = item - pt * g.nkp;
             const int pair = pt / g.ntaps, tap = pt - pair * g.ntaps;
             const int grp = pair / g.ncb, cb = pair - grp * g.ncb;
@@ -258,7 +238,12 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[t][r] = 0;
             const int k0 = kp * 8;
+            const uint4* wp = wsc + ((size_t)(pair * g.ntaps + tap) * g.nk + k0) * 64 + lane;
             const int ub = grp * g.ug;  // first unit of the group within a position
+            uint4 a[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (k0 + k < g.nk) a[k] = wp[(size_t)k * 64];
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 if (k0 + k >= g.nk) break;
@@ -271,8 +256,6 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
                     if (TERMS == 2) acc[t] = mma(a[k], chunk < g.ug ? bp[plane] : *zero_unit, acc[t]);
                 }
             }
-            item += istep;
-            if (item < nitems) load_weights();  // (ahead of this item's atomic adds)
             // column p of this tap's product belongs to the output position that sees input position p under the tap
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
