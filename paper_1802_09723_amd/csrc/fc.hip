@@ -39,7 +39,11 @@ __device__ __forceinline__ float bf16_to_f32(unsigned int h) { return __uint_as_
 // column per wavefront with the lanes over its non-zeros, and adds the products into a private copy of the
 // projection's update in LDS (all c_out rows); at the end it adds the rows it touched into the stored projection
 // with atomic adds (exact for integers; fp32 sums then depend on the order within the layer's tolerance).
-template <int DT, bool CSC>
+//
+// ROWS16 = g.vec_ok: rows of whole 16-byte units.  A form of its own, because the code that reads ragged rows costs the
+// others time even where it is not taken (one stream, 9216 -> 4096: int8, 25 % changing, 11.42 -> 11.36 us, bf16, 5 %,
+// 11.92 -> 11.78; the ragged rows themselves, 3945 -> 413 bf16, 7.95 -> 7.84).
+template <int DT, bool CSC, bool ROWS16>
 __global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned char* __restrict__ x_t,
                                                                unsigned char* x_snap,
                                                                const unsigned char* __restrict__ wT, void* y_v,
@@ -79,7 +83,7 @@ __global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned ch
     // the row's end (element by element the loads waited for each other: 3945 -> 413
     // bf16, one stream, 11.1 -> 8.5 us)
     auto load_unit = [&](int e0, uint4& a, uint4& s) {
-        if (g.vec_ok) {
+        if constexpr (ROWS16) {
             a = *reinterpret_cast<const uint4*>(x_t + (row + e0) * ESIZE);
             s = *reinterpret_cast<const uint4*>(x_snap + (row + e0) * ESIZE);
             return;
@@ -147,7 +151,7 @@ __global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned ch
         n_out = make_uint4(nw[0], nw[1], nw[2], nw[3]);
     };
     auto store_unit = [&](int e0, const uint4& nw) {  // commit a unit's new snapshot
-        if (g.vec_ok) {
+        if constexpr (ROWS16) {
             *reinterpret_cast<uint4*>(x_snap + (row + e0) * ESIZE) = nw;
             return;
         }
@@ -548,6 +552,11 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
     const int esize = dtype == RRM_I8_I32 ? 1 : 2;
     dim3 block(FCD_THREADS);
     if (y_out && !fc_delta_writes_out(dtype, g)) return hipErrorInvalidValue;
+    // the kernel's form for this layer
+    auto kern = [&]<bool CSC>() {
+        if (dtype == RRM_I8_I32) return g.vec_ok ? fc_delta_kernel<RRM_I8_I32, CSC, true> : fc_delta_kernel<RRM_I8_I32, CSC, false>;
+        return g.vec_ok ? fc_delta_kernel<RRM_BF16_F32, CSC, true> : fc_delta_kernel<RRM_BF16_F32, CSC, false>;
+    };
     if (g.csc_ptr) {
         // pruned weights: up to 64 workgroups per stream share the list (each pays c_out atomic adds at the end)
         const int nw = std::max(1, std::min(64, NUM_CU / g.n));
@@ -555,32 +564,24 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
         static std::once_flag once;
         static hipError_t attr = hipSuccess;
         std::call_once(once, [] {
-            attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&fc_delta_kernel<RRM_I8_I32, true>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, FC_CSC_MAX_LDS);
-            if (attr == hipSuccess)
-                attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&fc_delta_kernel<RRM_BF16_F32, true>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, FC_CSC_MAX_LDS);
+            for (const void* f : {reinterpret_cast<const void*>(&fc_delta_kernel<RRM_I8_I32, true, true>),
+                                  reinterpret_cast<const void*>(&fc_delta_kernel<RRM_I8_I32, true, false>),
+                                  reinterpret_cast<const void*>(&fc_delta_kernel<RRM_BF16_F32, true, true>),
+                                  reinterpret_cast<const void*>(&fc_delta_kernel<RRM_BF16_F32, true, false>)})
+                if (attr == hipSuccess) attr = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, FC_CSC_MAX_LDS);
         });
         if (attr != hipSuccess) return attr;
         if (lds > (size_t)FC_CSC_MAX_LDS) return hipErrorInvalidValue;
         dim3 grid((unsigned int)nw, (unsigned int)g.n, 1u);
-        if (dtype == RRM_I8_I32)
-            hipLaunchKernelGGL((fc_delta_kernel<RRM_I8_I32, true>), grid, block, lds, s, (const unsigned char*)x_t,
-                               (unsigned char*)x_snap, (const unsigned char*)wT, y, y_out, arrive, g, stats);
-        else
-            hipLaunchKernelGGL((fc_delta_kernel<RRM_BF16_F32, true>), grid, block, lds, s, (const unsigned char*)x_t,
-                               (unsigned char*)x_snap, (const unsigned char*)wT, y, y_out, arrive, g, stats);
+        hipLaunchKernelGGL(kern.template operator()<true>(), grid, block, lds, s, (const unsigned char*)x_t, (unsigned char*)x_snap,
+                           (const unsigned char*)wT, y, y_out, arrive, g, stats);
         return hipGetLastError();
     }
     const int ranges = (g.c_out_p * esize + FCD_SEG - 1) / FCD_SEG;
     const int nks = fc_list_splits(dtype, g);
     dim3 grid((unsigned int)ranges, (unsigned int)g.n, (unsigned int)nks);
-    if (dtype == RRM_I8_I32)
-        hipLaunchKernelGGL((fc_delta_kernel<RRM_I8_I32, false>), grid, block, 0, s, (const unsigned char*)x_t,
-                           (unsigned char*)x_snap, (const unsigned char*)wT, y, y_out, arrive, g, stats);
-    else
-        hipLaunchKernelGGL((fc_delta_kernel<RRM_BF16_F32, false>), grid, block, 0, s, (const unsigned char*)x_t,
-                           (unsigned char*)x_snap, (const unsigned char*)wT, y, y_out, arrive, g, stats);
+    hipLaunchKernelGGL(kern.template operator()<false>(), grid, block, 0, s, (const unsigned char*)x_t, (unsigned char*)x_snap,
+                       (const unsigned char*)wT, y, y_out, arrive, g, stats);
     return hipGetLastError();
 }
 
