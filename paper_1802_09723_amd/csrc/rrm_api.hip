@@ -397,8 +397,13 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
         }
     } else {
         cands = {{2, 16}, {2, 8}, {1, 16}, {1, 8}, {1, 4}};
-        // (12 slots where 16 do not fit: 27 x 27, 5 x 5, 2 x 48 -> 256 channels at 512 streams 92 -> 75 us; two-term layers have too few registers left on the 16-slot code)
-        if (terms == 1) cands.insert(cands.begin() + 1, Cand{2, 12});
+        // 12 slots (on the 16-slot code) where 16 do not fit and 12 save a pass over the grid: 27 x 27, 5 x 5, 2 x 48 -> 256
+        // channels dense at 256 streams, 17 passes for 25, 98 -> 91 us; 2 x 2 at stride 2, 256 -> 256, 64 x 64, 12 streams, one
+        // pass for two, 15.8 -> 14.0.  With equal passes the larger workgroup only costs (the same 8 streams 11.9 -> 15.6).  Of the even
+        // counts between 8 and 16 only this one is tried.  Two-term layers have too few registers left on the 16-slot code.
+        const int lanes = std::max(1, NUM_CU / (s.groups * ((g.ncb + 1) / 2)));
+        auto passes = [&](int nt) { return (g.n_sub + nt * lanes - 1) / (nt * lanes); };
+        if (terms == 1 && passes(12) < passes(8)) cands.insert(cands.begin() + 1, Cand{2, 12});
     }
     bool ok = false;
     // (the kernel's static LDS, about 6 KB, comes on top of the dynamic budget; 160 KB per workgroup in all)
@@ -419,9 +424,9 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
         }
         if (ok) break;
     }
-    if (!ok)
+    if (!ok)  // slabs below 4 chunks (not for 12 slots: 4 x 4 at stride 4, 96 -> 128, 8 slots in 3 slabs 18.2 us, 12 in 6 33.3)
         for (const Cand& c : cands)
-            if (!ok) ok = conv_try_shape(g, terms, c.cb, c.nt, ntaps, 153 * 1024);
+            if (!ok && c.nt != 12) ok = conv_try_shape(g, terms, c.cb, c.nt, ntaps, 153 * 1024);
     if (!ok)  // large filter windows: slabs of any chunk count, down to one sub-tile per workgroup
         for (const Cand& c : {Cand{1, 8}, Cand{1, 4}, Cand{1, 2}, Cand{1, 1}})
             if (!ok) ok = conv_try_shape(g, terms, c.cb, c.nt, ntaps, 153 * 1024, true);

@@ -26,6 +26,25 @@ def test_window_tile_kernel_with_few_subtiles(shp, dt):
     run_sequence(seq, check_dense=(0, 3), path=1, conv_kernel=1)
 
 
+# int8 layers whose windows leave room for 12 slots and not for 16, with sub-tiles enough for 12 to save a pass over the grid:
+# six of the eight consumers have a pair.  (map, c_in, c_out, k, stride, pad, groups, n): one slab of K and several (the last
+# one short), channel runs off 16 bytes, channel counts off the blocks of 32 and off the fours, groups, units of an odd
+# number of sub-tiles, one unit per workgroup and several.
+TWELVE_SLOTS = [
+    (27, 96, 256, 5, 1, 2, 2, 13), (27, 96, 256, 5, 1, 2, 2, 22), (32, 128, 70, 2, 2, 0, 1, 66), (33, 80, 96, 2, 2, 0, 1, 66),
+    (56, 16, 128, 4, 4, 0, 1, 66), (33, 48, 66, 3, 2, 1, 1, 42), (33, 40, 130, 5, 1, 2, 1, 9), (33, 32, 96, 6, 1, 2, 1, 17),
+    (30, 16, 96, 9, 1, 4, 1, 17),
+]
+
+
+@pytest.mark.parametrize("shp", TWELVE_SLOTS)
+def test_window_tile_kernel_with_twelve_slots(shp):
+    m, ci, co, k, st, pad, g, n = shp
+    seq = S.random_layer(9500 + m + n, S.conv_shape(m, m, ci, co, k, st, pad, g, n=n), S.I8, T=4, frac=0.2, block=3)
+    run_sequence(seq, check_dense=(0, 3), path=1, conv_kernel=1)
+    run_sequence(seq, check_dense=(), check_frames=(3,), dense_switch_pct=1, conv_kernel=1)
+
+
 # The binary band kernel: 64 output channels per workgroup in two blocks of 32, passes of 64 listed positions in two tiles
 # of 32, K steps of two words dealt to eight wavefronts, a few in flight at a time.
 @pytest.mark.parametrize("ci,co,k,m,n,frac", [
