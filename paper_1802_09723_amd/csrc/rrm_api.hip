@@ -50,6 +50,7 @@ struct rrm_layer {
     size_t d_bytes = 0;     // bytes of one difference buffer
     ScanGeom sg{};
     ConvGeom cg{};
+    int dense_nt = 0, dense_ksh = 0;  // sub-tiles per workgroup and K parts of a dense launch (delta: cg.nt, cg.ksh)
     PosGeom pg{};           // position-gather kernel (stride-1 layers with 16-byte channel runs)
     bool pos_ok = false;    // the layer can run on the position-gather kernel
     bool use_pos = false;   // ... and does
@@ -385,16 +386,22 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
     // per workgroup and as few sub-tiles as the chip has workgroups for (one per compute unit); the fewer windows leave
     // LDS for longer slabs, and the consumers split the K steps.  Many sub-tiles (many streams): operand reuse matters,
     // so 2 channel blocks x 16 sub-tiles.
+    // A delta launch of few sub-tiles keeps eight of them per workgroup where a unit has few K steps to put against what every
+    // workgroup pays (its share of the work list, the arrival count, the joining of the parts); the dense launch, which has
+    // neither list nor count, does not.  Kernel us of the delta launch at 1 .. 4 and at 8, int8, 30 % of the positions changing:
+    // 64 x 64, 16 -> 32, 5 x 5 at stride 2 (7 K steps), 8 streams 10.3 and 8.9; 28 x 28, 128 -> 96, 1 x 1 (2), 3 streams 8.8 and
+    // 8.2; 64 -> 64, 3 x 3 (9), 10 streams 11.3 and 11.0; 96 -> 128 (14), 3 streams 9.0 and 9.8; 128 -> 64 (18), 10 streams equal.
     struct Cand { int cb, nt; };
     std::vector<Cand> cands;
-    const bool small = (long long)g.n_sub * g.ncb * s.groups <= 1024;
+    const long long blocks = (long long)g.n_sub * g.ncb * s.groups;
+    const bool small = blocks <= 1024;
+    const int ksteps = (ntaps * g.chunks + 3) / 4 * terms;
+    const bool deep = ksteps >= 9 && blocks <= 50 * ksteps;
+    int few = 1;
+    while (few < 8 && (long long)((g.n_sub + few - 1) / few) * g.ncb * s.groups > NUM_CU) few *= 2;
     if (small || g.ncb < 2) {
         cands = {{1, 16}, {1, 8}, {1, 4}};
-        if (small) {
-            int nt = 1;
-            while (nt < 8 && (long long)((g.n_sub + nt - 1) / nt) * g.ncb * s.groups > NUM_CU) nt *= 2;
-            cands = {{1, nt}, {1, 8}, {1, 16}, {1, 4}};
-        }
+        if (small) cands = {{1, deep ? few : 8}, {1, 8}, {1, 16}, {1, 4}};
     } else {
         cands = {{2, 16}, {2, 8}, {1, 16}, {1, 8}, {1, 4}};
         // 12 slots (on the 16-slot code) where 16 do not fit and 12 save a pass over the grid: 27 x 27, 5 x 5, 2 x 48 -> 256
@@ -416,7 +423,7 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
         for (const Cand& c : cands) {
             ConvGeom t = g;
             // a slab should hold at least 4 chunks (or all of them) to amortise its barriers
-            if (conv_try_shape(t, terms, c.cb, c.nt, ntaps, budget, false, small) && (t.sc >= 4 || t.sc == t.chunks)) {
+            if (conv_try_shape(t, terms, c.cb, c.nt, ntaps, budget, false, small && deep) && (t.sc >= 4 || t.sc == t.chunks)) {
                 g = t;
                 ok = true;
                 break;
@@ -431,6 +438,16 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
         for (const Cand& c : {Cand{1, 8}, Cand{1, 4}, Cand{1, 2}, Cand{1, 1}})
             if (!ok) ok = conv_try_shape(g, terms, c.cb, c.nt, ntaps, 153 * 1024, true);
     if (!ok) return fail(RRM_ERR_SHAPE, "input window of one output sub-tile does not fit LDS");
+    L->dense_nt = g.nt;
+    L->dense_ksh = g.ksh;
+    if (small && !deep && g.nslab == 1 && few < g.nt) {  // (the same slab, so the same packed weights and tables)
+        ConvGeom t = g;
+        t.ksh = conv_ksh(1, few);
+        if ((long long)conv_lds_bytes(t, 1, few, 1) <= 153 * 1024) {
+            L->dense_nt = few;
+            L->dense_ksh = t.ksh;
+        }
+    }
     return pack_conv(L, w);
 }
 
@@ -720,8 +737,11 @@ rrm_status enqueue_dense(rrm_layer* L, const void* x, void* y, hipStream_t st) {
             RRM_HIP(launch_repack(L->esize, x, L->xpad, L->sg, st));
             src = L->xpad;
         }
-        RRM_HIP(launch_conv(L->dtype, MODE_DENSE, L->cg.wg_cb, L->cg.nt, 1, src, nullptr, L->zero16, nullptr, nullptr, L->wpack, L->offtab,
-                            L->bias, y, L->cg, L->stats, st));
+        ConvGeom cg = L->cg;
+        cg.nt = L->dense_nt;
+        cg.ksh = L->dense_ksh;
+        RRM_HIP(launch_conv(L->dtype, MODE_DENSE, cg.wg_cb, cg.nt, 1, src, nullptr, L->zero16, nullptr, nullptr, L->wpack, L->offtab,
+                            L->bias, y, cg, L->stats, st));
     }
     return RRM_OK;
 }

@@ -8,13 +8,14 @@ from gpu_util import run_sequence
 pytestmark = pytest.mark.gpu
 
 
-# One channel block and 1, 2, 4 or 8 sub-tiles per workgroup (a layer of few sub-tiles): the consumers split the K steps.
+# One channel block and 1, 2, 4 or 8 sub-tiles per workgroup (a layer of few sub-tiles): the consumers split the K steps, of
+# layers of few K steps in the dense launch only (the delta launch then has eight).
 # (map, c_in, c_out, k, stride, pad, groups, n): K steps fewer than the parts, one slab and several, channel counts off
 # the blocks of 32 and off the fours, groups, several units per workgroup.
 FEW_SUBTILES = [
     (4, 16, 16, 1, 1, 0, 1, 1), (13, 384, 384, 3, 1, 1, 1, 1), (13, 256, 384, 3, 1, 1, 1, 2), (27, 96, 256, 5, 1, 2, 2, 1),
     (20, 48, 130, 3, 1, 1, 1, 1), (29, 32, 33, 3, 2, 1, 1, 2), (55, 16, 64, 3, 1, 1, 1, 1), (7, 512, 512, 3, 1, 1, 1, 1),
-    (31, 16, 7, 3, 1, 1, 1, 9), (40, 16, 32, 5, 1, 2, 1, 10),
+    (31, 16, 7, 3, 1, 1, 1, 9), (40, 16, 32, 5, 1, 2, 1, 10), (20, 112, 130, 3, 1, 1, 1, 1), (29, 128, 33, 3, 2, 1, 1, 2),
 ]
 
 
