@@ -203,7 +203,7 @@ __device__ __forceinline__ v16f mma_e2m1(const uint4& a, const v8i& b, v16f c) {
 // counter) copies the frame into the stored input, when nobody reads the old one any more, and rearms the counter.
 //
 // DENSE: the layer itself (Eq. 3) with the same product: m = "tap inside the image", every output position is listed, and
-// the result is the bias plus the sums.  (`flip` is not read.)  60 x 13, 448 -> 72 channels, 26 streams: 40.9 us on the tile
+// the result is the bias plus the sums.  (`flip` and `stats` are not touched.)  60 x 13, 448 -> 72 channels, 26 streams: 40.9 us on the tile
 // kernel, 28.6 here.
 template <bool FUSED, bool DENSE>
 __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigned int* __restrict__ xsrc,
@@ -525,10 +525,9 @@ hipError_t launch_bin_band(const void* xsrc, const void* flip, const void* wband
 }
 
 // the dense layer: xsrc = x
-hipError_t launch_bin_band_dense(const void* x, const void* wband, const void* bias, void* y, const BinGeom& g, DevStats* stats,
-                                 hipStream_t s) {
+hipError_t launch_bin_band_dense(const void* x, const void* wband, const void* bias, void* y, const BinGeom& g, hipStream_t s) {
     if (g.band_rows < 1 || g.band_rows * g.wo > 65535) return hipErrorInvalidValue;  // (list entries are 16 bits)
-    return launch_band<false, true>(x, nullptr, nullptr, nullptr, wband, bias, y, g, stats, s);
+    return launch_band<false, true>(x, nullptr, nullptr, nullptr, wband, bias, y, g, nullptr, s);
 }
 
 // one launch: the whole step (needs g.fused_ok: every input position lies in the window of the band that owns it,

@@ -52,6 +52,9 @@ inline size_t bin_band_lds_bytes(const BinGeom& g, int band_rows) {
     return 2 * npos * g.bpitch * 4 + ((npos + 15) & ~(size_t)15) + (((size_t)band_rows * g.wo * 2 + 15) & ~(size_t)15) + BAND_SUMS;
 }
 
+// does the layer run the tile kernel: its steps where it has no bands, its dense layer there and where it is a wide one
+inline bool bin_uses_tiles(const BinGeom& g) { return g.band_rows == 0 || g.bpitch < g.pitch; }
+
 // Fill the geometry of a binary layer.  False: the input window of one 8x8 output tile does not fit LDS (the layer
 // cannot be created).
 inline bool bin_choose_shape(const rrm_shape& s, BinGeom& g) {

@@ -574,19 +574,22 @@ rrm_status setup_bin(rrm_layer* L, const std::vector<unsigned char>& w) {
         if (st2 != RRM_OK) return st2;
     }
     const int ntaps = s.kh * s.kw;
-    // filter words: [group][co/8][slab][tap][co%8][4 words]
-    std::vector<unsigned int> pack((size_t)s.groups * g.nob8 * g.nslab * ntaps * 8 * 4, 0u);
     const unsigned int* ww = reinterpret_cast<const unsigned int*>(w.data());
-    for (int grp = 0; grp < s.groups; ++grp)
-        for (int co = 0; co < g.og; ++co)
-            for (int tap = 0; tap < ntaps; ++tap)
-                for (int wd = 0; wd < g.wg; ++wd) {
-                    const int slab = wd / 4;
-                    const size_t dst = (((((size_t)grp * g.nob8 + co / 8) * g.nslab + slab) * ntaps + tap) * 8 + co % 8) * 4 + wd % 4;
-                    pack[dst] = ww[(((size_t)(grp * g.og + co)) * ntaps + tap) * g.wg + wd];
-                }
-    rrm_status st = upload(pack.data(), pack.size() * 4, &L->wpack);
-    if (st != RRM_OK || g.band_rows == 0) return st;
+    if (bin_uses_tiles(g)) {
+        // filter words: [group][co/8][slab][tap][co%8][4 words]
+        std::vector<unsigned int> pack((size_t)s.groups * g.nob8 * g.nslab * ntaps * 8 * 4, 0u);
+        for (int grp = 0; grp < s.groups; ++grp)
+            for (int co = 0; co < g.og; ++co)
+                for (int tap = 0; tap < ntaps; ++tap)
+                    for (int wd = 0; wd < g.wg; ++wd) {
+                        const int slab = wd / 4;
+                        const size_t dst = (((((size_t)grp * g.nob8 + co / 8) * g.nslab + slab) * ntaps + tap) * 8 + co % 8) * 4 + wd % 4;
+                        pack[dst] = ww[(((size_t)(grp * g.og + co)) * ntaps + tap) * g.wg + wd];
+                    }
+        rrm_status st = upload(pack.data(), pack.size() * 4, &L->wpack);
+        if (st != RRM_OK) return st;
+    }
+    if (g.band_rows == 0) return RRM_OK;
     // band kernel: the weights as 4-bit floats (E2M1: 0x2 = +1, 0xA = -1) in per-lane MFMA order
     // [group][32-channel block, padded to pairs][tap][K step of 2 words][lane] x 16 bytes: lane l -> output channel
     // l % 32 of the block, word 2 * step + l / 32 of the group's words; nibble j of register i is bit 4j + i of the
@@ -719,10 +722,10 @@ rrm_status enqueue_dense(rrm_layer* L, const void* x, void* y, hipStream_t st) {
         else
             RRM_HIP(launch_fc_dense(L->dtype, fc_splits(L), L->wpack, x, L->fc_part, L->bias, y, L->fg, st));
     } else if (L->dtype == RRM_BIN_I32) {
-        // (the whole map of a wide layer, see bin_shape.h: the tile kernel; 4 x 1100, 128 -> 1024 channels 1 x 1, 11.4 us there and
+        // (the whole map of a wide layer, see bin_shape.h, on the tile kernel too; 4 x 1100, 128 -> 1024 channels 1 x 1, 11.4 us there and
         // 15.9 on bands, 24 x 350, 128 -> 512 3 x 3, 19.8 and 18.6, 16 x 350, 128 -> 64, 16 streams, 21.4 and 23.5)
-        if (L->bg.band_rows > 0 && L->bg.bpitch == L->bg.pitch) {
-            RRM_HIP(launch_bin_band_dense(x, L->wband, L->bias, y, L->bg, L->stats, st));
+        if (!bin_uses_tiles(L->bg)) {
+            RRM_HIP(launch_bin_band_dense(x, L->wband, L->bias, y, L->bg, st));
             return RRM_OK;
         }
         RRM_HIP(launch_bin_conv(MODE_DENSE, bin_cw(L), x, nullptr, nullptr, L->wpack, L->bias, y, L->bg, L->stats, st));

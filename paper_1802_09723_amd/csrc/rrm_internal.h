@@ -237,8 +237,7 @@ int bin_consumers(int cw, const BinGeom& g);     // workgroups per tile of the b
 // wband: weights as E2M1 fragments [group][32-channel block][K step][lane] x 16 bytes (see setup_bin)
 hipError_t launch_bin_band(const void* xsrc, const void* flip, const void* wband, void* y, const BinGeom& g,
                            DevStats* stats, hipStream_t s);
-hipError_t launch_bin_band_dense(const void* x, const void* wband, const void* bias, void* y, const BinGeom& g, DevStats* stats,
-                                 hipStream_t s);
+hipError_t launch_bin_band_dense(const void* x, const void* wband, const void* bias, void* y, const BinGeom& g, hipStream_t s);
 hipError_t launch_bin_band_fused(const void* x_t, void* x_snap, unsigned int* arrive, const void* wband, void* y,
                                  const BinGeom& g, DevStats* stats, hipStream_t s);
 
