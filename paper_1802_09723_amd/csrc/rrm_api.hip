@@ -414,7 +414,9 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
     }
     bool ok = false;
     // (the kernel's static LDS, about 6 KB, comes on top of the dynamic budget; 160 KB per workgroup in all)
-    long long first_budget = 153ll * 1024;
+    // (few sub-tiles with few K steps: rather fewer sub-tiles or shorter slabs than more LDS; 28 x 28, 128 -> 128 3 x 3 at stride
+    // 2, 16 streams, 4 sub-tiles dense 8.5 us, 8 in 119 KB 9.3; step 9.5 and 9.8)
+    long long first_budget = (small && !deep ? 96ll : 153ll) * 1024;
     if (const char* env = std::getenv("RRM_CONV_LDS_KB")) {  // tuning knob: preferred LDS bytes per workgroup
         const long long kb = std::atoll(env);
         if (kb >= 16 && kb <= 153) first_budget = kb * 1024;
