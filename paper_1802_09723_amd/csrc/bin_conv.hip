@@ -492,11 +492,13 @@ template <bool FUSED, bool DENSE = false>
 hipError_t launch_band(const void* xsrc, const void* flip, void* snap, unsigned int* arrive, const void* wband, const void* bias, void* y,
                        const BinGeom& g, DevStats* stats, hipStream_t s) {
     const int nblk = (g.og + 63) / 64;
-    // few streams: deal the band's list over several workgroups (each stages the window again: it is small, but for a wide
-    // layer, which gets one workgroup per compute unit: 4 x 350, 128 -> 256, 16 streams, 5 %, 15.8 us with two, 10.8 with one)
+    // few streams: deal the band's list over several workgroups, as long as every one has a compute unit to itself (each stages
+    // the window and makes the list again, which a second one per compute unit does not repay: 28 x 28, 256 -> 256 channels 3 x 3,
+    // 8 streams, 5 % of the values flipping, 13.6 us with two, 10.8 with one, 9.6 and 7.3 with no change; 4 x 350, 128 -> 256, 16
+    // streams, 15.8 and 10.8; only long lists of 1 x 1 filters lose, 64 x 500, 128 -> 128, 20 %, 22.9 and 25.0)
     const long long wgs = (long long)g.n * g.nbands * g.groups * nblk;
     const int chunks = (g.band_rows * g.wo + 63) / 64;  // (a workgroup takes the list 64 entries at a time)
-    int z = (int)((g.bpitch < g.pitch ? 1 : 2) * NUM_CU / wgs);  // (no more than two workgroups per compute unit: what its registers hold)
+    int z = (int)(NUM_CU / wgs);
     z = z < 1 ? 1 : (z > chunks ? chunks : z);
     dim3 grid((unsigned int)z, (unsigned int)(g.groups * nblk), (unsigned int)(g.n * g.nbands));
     const size_t lds = bin_band_lds_bytes(g, g.band_rows);
