@@ -286,13 +286,26 @@ def test_large_windows_with_many_channels(case, dt):
 @pytest.mark.parametrize("case", [(5, 4, 96, 1, 1, 31), (11, 4, 128, 1, 1, 33), (7, 4, 384, 4, 1, 24), (9, 4, 192, 2, 5, 17),
                                   (11, 3, 256, 1, 2, 30)], ids=lambda c: "k%ds%dc%dg%dn%dh%d" % c)
 def test_binary_large_strided_windows(case):
-    """the 8 x 8 tile's window takes more than 64 KB of LDS (both copies): the tile kernel runs with the large
-    allocation, for the dense pass and, where no band fits, for the delta steps"""
+    """large windows on bands of a few rows (the 8 x 8 tile's window would take more than 64 KB of LDS, both copies)"""
     k, stride, c_in, groups, n, h = case
     shp = S.LayerShape(S.CONV, n, h, h + 5, c_in, 13 * groups, k, k, stride, k // 2, groups)
     for frac in (0.02, 0.5):
         seq = S.random_layer(7200 + k + stride, shp, S.BIN, T=3, frac=frac, block=2)
         run_sequence(seq, check_dense=(0, 2))
+
+
+@pytest.mark.parametrize("case", [(11, 4, 128, 1, 1, 33, 130, 64), (11, 3, 256, 1, 2, 30, 130, 64), (9, 4, 192, 2, 2, 17, 130, 1)],
+                         ids=lambda c: "k%ds%dc%dg%dn%dh%dw%d_%d" % c)
+@pytest.mark.parametrize("cw", [8, 16])
+def test_binary_large_strided_windows_on_the_tile_kernel(case, cw):
+    """the 8 x 8 tile's window takes more than 64 KB of LDS (both copies) and the map is too wide for bands, or has bands for its
+    steps only (the last case): the tile kernel runs with the large allocation"""
+    k, stride, c_in, groups, n, h, w, positions = case
+    shp = S.LayerShape(S.CONV, n, h, w, c_in, 13 * groups, k, k, stride, k // 2, groups)
+    for frac in (0.02, 0.5):
+        seq = S.random_layer(7300 + k + stride, shp, S.BIN, T=3, frac=frac, block=2)
+        stats, _ = run_sequence(seq, check_dense=(0, 2), bin_cout_per_wave=cw)
+        assert stats["tile_positions"] == positions
 
 
 def test_window_too_large_for_lds_is_refused_with_a_message():
@@ -360,7 +373,7 @@ def test_random_binary_shapes(idx):
 
 
 def test_binary_band_list_longer_than_one_pass_and_wide_layer_on_the_tile_kernel():
-    """The binary delta step's band kernel with several 128-entry passes over a band's list, dealt over several
+    """The binary delta step's band kernel with several 64-entry passes over a band's list, dealt over several
     workgroups (one stream, half of the positions changing), with three streams, and a layer so wide that no
     band of it fits LDS, which takes the tile kernel."""
     big = S.conv_shape(40, 40, 64, 32, 3, 1, 1, 1)
