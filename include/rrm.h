@@ -84,7 +84,7 @@ typedef struct {
     uint64_t changed_units;   /* 16-byte input units with any difference (FC: = changed_elems) */
     uint64_t active_tiles;    /* int8 / bf16 conv: output blocks recomputed (4x4 positions for the window-tile
                                  kernel, single positions for the position-gather kernel); binary conv: output
-                                 positions updated (8x8 tiles where a layer's bands do not fit LDS); FC: columns
+                                 positions updated (8x8 tiles for layers without bands); FC: columns
                                  streamed */
     uint64_t total_tiles;     /* the same unit, counted as a dense step would, summed over delta steps
                                  (FC: c_in per step) */
@@ -232,7 +232,7 @@ rrm_status rrm_set_threshold(rrm_layer* layer, float epsilon);
 
 /* Kernel times of the rrm_step calls made since "profile" was switched on (or since the last call
  * of this function): sums, in microseconds, of the event-bracketed durations of the scan kernel
- * (delta + change map) and of the compute kernel (tile conv / column scatter / popcount conv), and
+ * (delta + change map) and of the compute kernel (tile conv / column scatter / binary conv), and
  * the number of steps summed.  Synchronises with the recorded events.  At most 1024 steps are kept. */
 rrm_status rrm_get_kernel_times(rrm_layer* layer, double* scan_us, double* compute_us, int* steps);
 

@@ -10,14 +10,16 @@
 // equals m & (w XOR x)) and one v_bcnt_u32_b32 with accumulate: plain vector ALU work, no matrix core (the tile
 // kernel).  The band kernel multiplies on the matrix cores instead (see there).
 //
-// Mapping of the tile kernel (layers whose band does not fit LDS): one
+// Mapping of the tile kernel (layers without bands, and the dense layer of those that stage their bands without padding, see
+// bin_shape.h): one
 // workgroup = one 8x8 output tile (lane = output position) x 4*CW output channels (wavefront w owns CW of
 // them); the filter words of an output channel are wave-uniform and come through scalar loads.  A/B words of
 // the tile's input window are staged in LDS once; (slab, tap) pairs in which no lane of the wavefront has a
 // flipped bit are skipped.
 //
 // Mapping of the band kernel (the delta step, and the dense layer): one workgroup = a band of output rows of one stream x 64 output
-// channels.  It stages the band's input window as above, notes which input positions hold a flip, lists
+// channels.  It stages the band's input window (the flip mask m, and the flips to -1, m & ~x), notes which input positions hold a
+// flip, lists
 // the output positions whose window sees one (ballot compaction into LDS) and multiplies that list 64 entries
 // at a time: every column of the product is an output position with work to do, wherever in the band it lies, so
 // the work follows the changed positions instead of the 8x8 tiles they fall into.

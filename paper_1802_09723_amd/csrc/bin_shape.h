@@ -29,8 +29,8 @@ struct BinGeom {
     int nob8;            // packed 8-channel filter blocks per group (og padded to 16)
     unsigned int magic_wg4;    // floor(2^32/d)+1 for d = 4*nslab
     unsigned int magic_tw;     // same for d = tw_in
-    // band kernel (delta step): bands of band_rows output rows over the full width; 0 rows = the layer's bands
-    // do not fit LDS and the delta step runs the tile kernel
+    // band kernel: bands of band_rows output rows over the full width; 0 rows = the layer has no bands (they do not fit
+    // LDS, or it is a wide layer with large frames) and runs the tile kernel
     int band_rows, nbands, bth_in, btw_in;
     unsigned int magic_btw;    // same for d = btw_in
     unsigned int magic_nslab;  // same for d = nslab

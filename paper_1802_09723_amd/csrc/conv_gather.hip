@@ -118,7 +118,7 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     constexpr int MAXU = CONV_MAX_STAGE_UNITS;  // staged 16-byte units per producer thread and slab (host guarantees)
     static_assert(NT % 8 == 0 && NT <= 16, "NT: two sub-tiles per consumer wavefront, at most twelve wavefronts");
     // Few slots per workgroup (g.ksh > 0): the consumers of a pair split its K steps, and each finishes its share of the
-    // channels from the other parts' sums.  `owner` is the part that finishes (and initialises) a register quad.
+    // channels from the other parts' sums (`owned`: the register quads that this part finishes and initialises).
     constexpr bool KSPLIT = NCB == 1 && NT == 8;
     const int ksh = KSPLIT ? g.ksh : 0;
     static_assert(LIST_CAP >= 2 * NT, "a ranking round holds at least two work units");

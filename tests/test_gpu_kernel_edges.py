@@ -47,7 +47,7 @@ def test_window_tile_kernel_with_twelve_slots(shp):
 
 
 # The binary band kernel: 64 output channels per workgroup in two blocks of 32, passes of 64 listed positions in two tiles
-# of 32, K steps of two words dealt to eight wavefronts, a few in flight at a time.
+# of 32, K steps of two words in four parts for each tile, a few in flight at a time.
 @pytest.mark.parametrize("ci,co,k,m,n,frac", [
     (32, 1, 1, 5, 1, 0.5), (128, 31, 3, 8, 1, 0.3), (128, 32, 3, 8, 2, 0.6), (128, 33, 3, 9, 1, 0.95), (256, 64, 3, 12, 3, 0.1),
     (256, 65, 1, 16, 1, 0.95), (512, 130, 3, 7, 2, 0.2), (128, 96, 5, 17, 1, 0.9), (640, 48, 3, 10, 1, 0.4), (96, 20, 3, 11, 2, 0.3),
