@@ -391,12 +391,15 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
     // neither list nor count, does not.  Kernel us of the delta launch at 1 .. 4 and at 8, int8, 30 % of the positions changing:
     // 64 x 64, 16 -> 32, 5 x 5 at stride 2 (7 K steps), 8 streams 10.3 and 8.9; 28 x 28, 128 -> 96, 1 x 1 (2), 3 streams 8.8 and
     // 8.2; 64 -> 64, 3 x 3 (9), 10 streams 11.3 and 11.0; 96 -> 128 (14), 3 streams 9.0 and 9.8; 128 -> 64 (18), 10 streams equal.
+    // From five K steps on the very smallest layers are spread too (step us, 3 %, spread and at 8: 27 x 40, 48 -> 96, 3 x 3 at stride
+    // 2 (7), one stream, 60 blocks, 10.2 and 11.9; 13 x 13, 32 -> 64 (5), 8 streams, 64, 10.6 and 11.6; 5 x 5, 16 -> 32 (7), 8 streams,
+    // 128, 11.5 and 11.2).
     struct Cand { int cb, nt; };
     std::vector<Cand> cands;
     const long long blocks = (long long)g.n_sub * g.ncb * s.groups;
     const bool small = blocks <= 1024;
     const int ksteps = (ntaps * g.chunks + 3) / 4 * terms;
-    const bool deep = ksteps >= 9 && blocks <= 50 * ksteps;
+    const bool deep = ksteps >= 9 ? blocks <= 50 * ksteps : ksteps >= 5 && blocks <= 120;
     int few = 1;
     while (few < 8 && (long long)((g.n_sub + few - 1) / few) * g.ncb * s.groups > NUM_CU) few *= 2;
     if (small || g.ncb < 2) {
@@ -415,7 +418,8 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
     bool ok = false;
     // (the kernel's static LDS, about 6 KB, comes on top of the dynamic budget; 160 KB per workgroup in all)
     // (few sub-tiles with few K steps: rather fewer sub-tiles or shorter slabs than more LDS; 28 x 28, 128 -> 128 3 x 3 at stride
-    // 2, 16 streams, 4 sub-tiles dense 8.5 us, 8 in 119 KB 9.3; step 9.5 and 9.8)
+    // 2, 16 streams, 4 sub-tiles dense 8.5 us, 8 in 119 KB 9.3; step 9.5 and 9.8.  1 x 1 of 96 or 128 bf16 channels then takes two
+    // slabs: step 11.5 us for 12.0 in 153 KB, dense 6.1 for 5.6)
     long long first_budget = (small && !deep ? 96ll : 153ll) * 1024;
     if (const char* env = std::getenv("RRM_CONV_LDS_KB")) {  // tuning knob: preferred LDS bytes per workgroup
         const long long kb = std::atoll(env);
