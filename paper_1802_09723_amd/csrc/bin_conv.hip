@@ -10,8 +10,7 @@
 // equals m & (w XOR x)) and one v_bcnt_u32_b32 with accumulate: plain vector ALU work, no matrix core (the tile
 // kernel).  The band kernel multiplies on the matrix cores instead (see there).
 //
-// Mapping of the tile kernel (layers without bands, and the dense layer of those that stage their bands without padding, see
-// bin_shape.h): one
+// Mapping of the tile kernel (layers without bands, and the dense layer of some that have them, see bin_shape.h): one
 // workgroup = one 8x8 output tile (lane = output position) x 4*CW output channels (wavefront w owns CW of
 // them); the filter words of an output channel are wave-uniform and come through scalar loads.  A/B words of
 // the tile's input window are staged in LDS once; (slab, tap) pairs in which no lane of the wavefront has a

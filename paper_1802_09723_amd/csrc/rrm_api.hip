@@ -583,7 +583,7 @@ rrm_status setup_bin(rrm_layer* L, const std::vector<unsigned char>& w) {
     }
     const int ntaps = s.kh * s.kw;
     const unsigned int* ww = reinterpret_cast<const unsigned int*>(w.data());
-    if (bin_uses_tiles(g)) {
+    if (bin_dense_on_tiles(g)) {  // (the steps of a layer without bands run on tiles too)
         // filter words: [group][co/8][slab][tap][co%8][4 words]
         std::vector<unsigned int> pack((size_t)s.groups * g.nob8 * g.nslab * ntaps * 8 * 4, 0u);
         for (int grp = 0; grp < s.groups; ++grp)
@@ -730,9 +730,7 @@ rrm_status enqueue_dense(rrm_layer* L, const void* x, void* y, hipStream_t st) {
         else
             RRM_HIP(launch_fc_dense(L->dtype, fc_splits(L), L->wpack, x, L->fc_part, L->bias, y, L->fg, st));
     } else if (L->dtype == RRM_BIN_I32) {
-        // (the whole map of a wide layer, see bin_shape.h, on the tile kernel too; 4 x 1100, 128 -> 1024 channels 1 x 1, 11.4 us there and
-        // 15.9 on bands, 24 x 350, 128 -> 512 3 x 3, 19.8 and 18.6, 16 x 350, 128 -> 64, 16 streams, 21.4 and 23.5)
-        if (!bin_uses_tiles(L->bg)) {
+        if (!bin_dense_on_tiles(L->bg)) {
             RRM_HIP(launch_bin_band_dense(x, L->wband, L->bias, y, L->bg, st));
             return RRM_OK;
         }

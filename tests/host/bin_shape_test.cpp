@@ -16,8 +16,8 @@ int main(int argc, char** argv) {
         printf("no\n");
         return 0;
     }
-    printf("ho=%d wo=%d R=%d nbands=%d bth=%d btw=%d lds=%zu bpitch=%d vec4=%d fused=%d pitch=%d nslab=%d\n", g.ho, g.wo, g.band_rows,
+    printf("ho=%d wo=%d R=%d nbands=%d bth=%d btw=%d lds=%zu bpitch=%d vec4=%d fused=%d pitch=%d nslab=%d dtiles=%d\n", g.ho, g.wo, g.band_rows,
            g.nbands, g.bth_in, g.btw_in, g.band_rows > 0 ? rrm::bin_band_lds_bytes(g, g.band_rows) : (size_t)0, g.bpitch, g.vec4,
-           g.fused_ok, g.pitch, g.nslab);
+           g.fused_ok, g.pitch, g.nslab, rrm::bin_dense_on_tiles(g) ? 1 : 0);
     return 0;
 }

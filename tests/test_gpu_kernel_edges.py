@@ -73,6 +73,17 @@ def test_binary_wide_layer_on_bands(h, w, ci, co, k, st, pad, g, n, frac):
     run_sequence(seq, check_dense=(), bin_single_launch=0)
 
 
+# The dense launch of 1 x 1 binary layers: on tiles up to 256 channels a group, on bands above and where these fill the chip and
+# the map leaves its tiles empty.  (h, w, c_in, c_out, stride, groups, n): words off the 16-byte vectors, maps off the tiles.
+@pytest.mark.parametrize("h,w,ci,co,st,g,n", [
+    (1, 1, 32, 1, 1, 1, 1), (9, 17, 96, 33, 1, 1, 2), (13, 13, 128, 65, 2, 1, 1), (16, 24, 256, 70, 1, 1, 3), (7, 9, 288, 16, 1, 1, 2),
+    (9, 8, 512, 24, 1, 2, 2), (13, 13, 128, 8, 1, 1, 172), (12, 13, 256, 5, 1, 1, 171), (13, 13, 96, 8, 1, 1, 172),
+])
+def test_binary_dense_layer_of_1x1_filters(h, w, ci, co, st, g, n):
+    seq = S.random_layer(9600 + w + co + n, S.conv_shape(h, w, ci, co, 1, st, 0, g, n=n), S.BIN, T=3, frac=0.2, block=2)
+    run_sequence(seq, check_dense=(0, 2), check_frames=(0, 2))
+
+
 # The FC step fills the caller's copy itself where every output has one owner, and by a copy otherwise; rows off the 16-byte
 # units (also the last bytes of the array); frame 2 repeats frame 1.
 @pytest.mark.parametrize("ci,co,n", [(64, 5, 1), (300, 33, 2), (301, 7, 3), (2049, 40, 2), (4096, 64, 1), (9216, 48, 1), (8192, 16, 3)])

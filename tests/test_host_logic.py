@@ -98,7 +98,7 @@ def test_binary_band_geometry_terminates_fits_and_covers(tmp_path):
     # wide layers whose row fits only without the padding of the staged positions: bands, as long as a frame is small
     wide = [(1, 16, 350, 128, 128, 3, 1, 1, 1), (64, 4, 365, 128, 256, 3, 1, 1, 1), (3, 5, 335, 64, 130, 3, 1, 1, 1), (2, 4, 990, 128, 8, 1, 1, 0, 1),
             (1, 4, 1200, 128, 64, 1, 1, 0, 1), (2, 2, 470, 512, 65, 1, 1, 0, 1), (2, 3, 350, 256, 24, 3, 1, 1, 2)]
-    cases += wide
+    cases += wide + [(1, 14, 14, 128, 512, 1, 1, 0, 1), (64, 28, 28, 128, 512, 1, 1, 0, 1), (128, 30, 30, 256, 256, 1, 1, 0, 1), (2, 9, 9, 288, 64, 1, 1, 0, 1)]
     rng = np.random.default_rng(17)
     for _ in range(80):
         k = int(rng.choice([1, 3, 5, 7]))
@@ -114,6 +114,11 @@ def test_binary_band_geometry_terminates_fits_and_covers(tmp_path):
         n, h, w, ci, co, k, stride, pad, grp = cse
         assert f["ho"] == (h + 2 * pad - k) // stride + 1 and f["wo"] == (w + 2 * pad - k) // stride + 1
         assert cse not in wide or (f["R"] > 0 and f["bpitch"] < f["pitch"]), (cse, f)
+        # the dense layer: on tiles without bands, for wide layers and for 1 x 1 filters of up to 256 channels (not on a chip full
+        # of bands over mostly empty tiles)
+        t1 = k == 1 and ci // grp <= 256 and not (f["vec4"] and n * f["nbands"] * grp * -(-co // grp // 64) >= 512
+                                                  and 5 * f["ho"] * f["wo"] < 256 * -(-f["ho"] // 8) * -(-f["wo"] // 8))
+        assert f["dtiles"] == int(f["R"] == 0 or f["bpitch"] < f["pitch"] or t1), (cse, f)
         if f["R"] == 0:
             continue
         banded += 1
