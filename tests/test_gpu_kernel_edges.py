@@ -27,7 +27,7 @@ def test_window_tile_kernel_with_few_subtiles(shp, dt):
     run_sequence(seq, check_dense=(0, 3), path=1, conv_kernel=1)
 
 
-# int8 layers whose windows leave room for 12 slots and not for 16, with sub-tiles enough for 12 to save a pass over the grid:
+# int8 layers whose windows leave room for 12 slots and not for 16, with more sub-tiles than one pass of eight over the grid:
 # six of the eight consumers have a pair.  (map, c_in, c_out, k, stride, pad, groups, n): one slab of K and several (the last
 # one short), channel runs off 16 bytes, channel counts off the blocks of 32 and off the fours, groups, units of an odd
 # number of sub-tiles, one unit per workgroup and several.
