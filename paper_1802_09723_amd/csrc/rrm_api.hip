@@ -407,8 +407,7 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
         if (small) cands = {{1, deep ? few : 8}, {1, 8}, {1, 16}, {1, 4}};
     } else {
         cands = {{2, 16}, {2, 8}, {1, 16}, {1, 8}, {1, 4}};
-        // 12 slots (on the 16-slot code, whose eight consumers take fewer pairs each) where 16 do not fit and eight need more than one
-        // pass over the grid: 27 x 27, 5 x 5, 2 x 48 -> 256 channels dense at 256 streams, 17 passes for 25, 98 -> 91 us; 2 x 2 at
+        // 12 slots (on the 16-slot code) where 16 do not fit and eight need more than one pass over the grid: 27 x 27, 5 x 5, 2 x 48 -> 256 channels dense at 256 streams, 17 passes for 25, 98 -> 91 us; 2 x 2 at
         // stride 2, 256 -> 256, 64 x 64, 12 streams, one pass for two, 15.8 -> 14.0; 128 -> 384, 28 x 28, 32 streams, two passes
         // either way, dense 14.1 -> 12.4, step 22.0 -> 20.9 (behind: 3 x 3 at stride 2, 48 -> 128, 28 x 28, 128 streams, 11.2 -> 11.7,
         // 19.9 -> 21.1).  In one pass the larger workgroup only costs (256 -> 256, 64 x 64, 8 streams, dense 11.9 -> 15.6).  Of
