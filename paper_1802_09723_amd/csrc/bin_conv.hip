@@ -493,13 +493,13 @@ template <bool FUSED, bool DENSE = false>
 hipError_t launch_band(const void* xsrc, const void* flip, void* snap, unsigned int* arrive, const void* wband, const void* bias, void* y,
                        const BinGeom& g, DevStats* stats, hipStream_t s) {
     const int nblk = (g.og + 63) / 64;
-    // few streams: deal the band's list over several workgroups.  In a step as long as every one has a compute unit to itself:
-    // each stages the window and makes the list again, which a second one per compute unit does not repay (us with two and with
-    // one, 5 % of the values flipping: 28 x 28, 256 -> 256 channels 3 x 3, 8 streams, 13.6 and 10.8, no change 9.6 and 7.3; 4 x
-    // 350, 128 -> 256, 16 streams, 15.8 and 10.8).  Long lists of many taps lose (kernel us, 20 % of the positions: 5 x 5, 56 x 56,
-    // 128 -> 128, 8 streams, 23.8 and 26.4; 112 x 112, 64 -> 64, 4 streams, 30.1 and 32.9; no change 10.4 and 7.4, 10.5 and
-    // 8.9), and some of 1 x 1 (64 x 500, 128 -> 128, 22.9 and 25.0).  The dense layer makes no list and has all positions: two per compute unit (5 x 5, 112 x 112, 128 -> 128, 2
-    // streams, 20.0 and 24.1; 3 x 3, 56 x 56, 64 -> 64, 16 streams, 14.8 and 16.4).
+    // few streams: deal the band's list over several workgroups.  In a step as long as every one has a compute unit to itself: each
+    // stages the window and makes the list again, which a second one per compute unit does not repay (us with two and with one, 5 %
+    // of the values flipping: 28 x 28, 256 -> 256 channels 3 x 3, 8 streams, 13.6 and 10.8, no change 9.6 and 7.3; 4 x 350, 128 ->
+    // 256, 16 streams, 15.8 and 10.8).  Long lists of many taps lose (kernel us, 20 % of the positions: 5 x 5, 56 x 56, 128 -> 128,
+    // 8 streams, 23.8 and 26.4; 112 x 112, 64 -> 64, 4 streams, 30.1 and 32.9; no change 10.4 and 7.4, 10.5 and 8.9), and some of 1
+    // x 1 (64 x 500, 128 -> 128, 22.9 and 25.0).  The dense layer makes no list and has all positions: two per compute unit (5 x 5,
+    // 112 x 112, 128 -> 128, 2 streams, 20.0 and 24.1; 3 x 3, 56 x 56, 64 -> 64, 16 streams, 14.8 and 16.4).
     const long long wgs = (long long)g.n * g.nbands * g.groups * nblk;
     const int chunks = (g.band_rows * g.wo + 63) / 64;  // (a workgroup takes the list 64 entries at a time)
     int z = (int)((DENSE ? 2 : 1) * NUM_CU / wgs);

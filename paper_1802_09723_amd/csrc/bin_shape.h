@@ -53,11 +53,12 @@ inline size_t bin_band_lds_bytes(const BinGeom& g, int band_rows) {
 }
 
 // Does the dense layer run the tile kernel: without bands; wide layers (4 x 1100, 128 -> 1024 channels 1 x 1, 11.4 us there and
-// 15.9 on bands, 24 x 350, 128 -> 512 3 x 3, 19.8 and 18.6, 16 x 350, 128 -> 64, 16 streams, 21.4 and 23.5); and 1 x 1 filters of few words, whose products are too
-// short for what a pass of the band kernel costs beside them (us, tile and band: 14 x 14, 128 -> 512 channels, 3.4 and 4.9; 16 x
-// 320, 256 -> 256, 2 streams, 8.4 and 12.1; 112 x 112, 64 -> 64, 64 streams, 66 and 85; 512 channels and 3 x 3 of 32 are level or
-// behind: 7 x 7, 512 -> 512, 5.5 and 4.6).  Not where bands fill the chip and their words are read whole, but the map leaves more
-// than a fifth of its 8 x 8 tiles empty (28 x 28, 128 -> 512, 64 streams, 45.4 and 42.0; 13 x 13, 256 -> 256, 128, 16.5 and 15.0).
+// 15.9 on bands, 24 x 350, 128 -> 512 3 x 3, 19.8 and 18.6, 16 x 350, 128 -> 64, 16 streams, 21.4 and 23.5); and 1 x 1 filters
+// of few words, whose products are too short for what a pass of the band kernel costs beside them (us, tile and band: 14 x 14,
+// 128 -> 512 channels, 3.4 and 4.9; 16 x 320, 256 -> 256, 2 streams, 8.4 and 12.1; 112 x 112, 64 -> 64, 64 streams, 66 and 85;
+// 512 channels and 3 x 3 of 32 are level or behind: 7 x 7, 512 -> 512, 5.5 and 4.6).  Not where bands fill the chip and their
+// words are read whole, but the map leaves more than a fifth of its 8 x 8 tiles empty (28 x 28, 128 -> 512, 64 streams, 45.4
+// and 42.0; 13 x 13, 256 -> 256, 128, 16.5 and 15.0).
 inline bool bin_dense_on_tiles(const BinGeom& g) {
     if (g.band_rows == 0 || g.bpitch < g.pitch) return true;
     if (g.kh * g.kw != 1 || g.wg > 8) return false;

@@ -387,12 +387,12 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
     // LDS for longer slabs, and the consumers split the K steps.  Many sub-tiles (many streams): operand reuse matters,
     // so 2 channel blocks x 16 sub-tiles.
     // A delta launch of few sub-tiles keeps eight of them per workgroup where a unit has few K steps to put against what every
-    // workgroup pays (its share of the work list, the arrival count, the joining of the parts); the dense launch, which has
-    // neither list nor count, does not.  Kernel us of the delta launch at 1 .. 4 and at 8, int8, 30 % of the positions changing:
-    // 64 x 64, 16 -> 32, 5 x 5 at stride 2 (7 K steps), 8 streams 10.3 and 8.9; 28 x 28, 128 -> 96, 1 x 1 (2), 3 streams 8.8 and
-    // 8.2; 64 -> 64, 3 x 3 (9), 10 streams 11.3 and 11.0; 96 -> 128 (14), 3 streams 9.0 and 9.8; 128 -> 64 (18), 10 streams equal.
-    // From five K steps on the very smallest layers are spread too (step us, 3 %, spread and at 8: 27 x 40, 48 -> 96, 3 x 3 at stride
-    // 2 (7), one stream, 60 blocks, 10.2 and 11.9; 13 x 13, 32 -> 64 (5), 8 streams, 64, 10.6 and 11.6; 5 x 5, 16 -> 32 (7), 8 streams,
+    // workgroup pays (its share of the work list, the arrival count, the joining of the parts); the dense launch, which has neither
+    // list nor count, does not.  Kernel us of the delta launch at 1 .. 4 and at 8, int8, 30 % of the positions changing: 64 x 64,
+    // 16 -> 32, 5 x 5 at stride 2 (7 K steps), 8 streams 10.3 and 8.9; 28 x 28, 128 -> 96, 1 x 1 (2), 3 streams 8.8 and 8.2; 64 ->
+    // 64, 3 x 3 (9), 10 streams 11.3 and 11.0; 96 -> 128 (14), 3 streams 9.0 and 9.8; 128 -> 64 (18), 10 streams equal. From five K
+    // steps on the very smallest layers are spread too (step us, 3 %, spread and at 8: 27 x 40, 48 -> 96, 3 x 3 at stride 2 (7),
+    // one stream, 60 blocks, 10.2 and 11.9; 13 x 13, 32 -> 64 (5), 8 streams, 64, 10.6 and 11.6; 5 x 5, 16 -> 32 (7), 8 streams,
     // 128, 11.5 and 11.2).
     struct Cand { int cb, nt; };
     std::vector<Cand> cands;
@@ -407,11 +407,12 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
         if (small) cands = {{1, deep ? few : 8}, {1, 8}, {1, 16}, {1, 4}};
     } else {
         cands = {{2, 16}, {2, 8}, {1, 16}, {1, 8}, {1, 4}};
-        // 12 slots (on the 16-slot code) where 16 do not fit and eight need more than one pass over the grid: 27 x 27, 5 x 5, 2 x 48 -> 256 channels dense at 256 streams, 17 passes for 25, 98 -> 91 us; 2 x 2 at
-        // stride 2, 256 -> 256, 64 x 64, 12 streams, one pass for two, 15.8 -> 14.0; 128 -> 384, 28 x 28, 32 streams, two passes
-        // either way, dense 14.1 -> 12.4, step 22.0 -> 20.9 (behind: 3 x 3 at stride 2, 48 -> 128, 28 x 28, 128 streams, 11.2 -> 11.7,
-        // 19.9 -> 21.1).  In one pass the larger workgroup only costs (256 -> 256, 64 x 64, 8 streams, dense 11.9 -> 15.6).  Of
-        // the even counts between 8 and 16 only this one is tried.  Two-term layers have too few registers left on the 16-slot code.
+        // 12 slots (on the 16-slot code) where 16 do not fit and eight need more than one pass over the grid: 27 x 27, 5 x 5, 2 x
+        // 48 -> 256 channels dense at 256 streams, 17 passes for 25, 98 -> 91 us; 2 x 2 at stride 2, 256 -> 256, 64 x 64, 12
+        // streams, one pass for two, 15.8 -> 14.0; 128 -> 384, 28 x 28, 32 streams, two passes either way, dense 14.1 -> 12.4, step
+        // 22.0 -> 20.9 (behind: 3 x 3 at stride 2, 48 -> 128, 28 x 28, 128 streams, 11.2 -> 11.7, 19.9 -> 21.1).  In one pass the
+        // larger workgroup only costs (256 -> 256, 64 x 64, 8 streams, dense 11.9 -> 15.6).  Of the even counts between 8 and 16
+        // only this one is tried.  Two-term layers have too few registers left on the 16-slot code.
         const int lanes = std::max(1, NUM_CU / (s.groups * ((g.ncb + 1) / 2)));
         auto passes = [&](int nt) { return (g.n_sub + nt * lanes - 1) / (nt * lanes); };
         if (terms == 1 && passes(8) > 1) cands.insert(cands.begin() + 1, Cand{2, 12});
