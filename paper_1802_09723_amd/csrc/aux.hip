@@ -60,11 +60,12 @@ __global__ void relu_requant_pool_kernel(const int* __restrict__ y, signed char*
 
 // The same map, four channels per thread (16-byte loads of y), one workgroup row per output row.  With
 // CHANGED, an output is recomputed only if one of the blocks of y under its window was written by the layer's
-// last step (byte flags `touched`, one per block of (1 << tshift)^2 positions); the rest of `out` keeps its value
-// from the previous call.
+// last step (byte flags `touched` with the bit *epoch, one per block of (1 << tshift)^2 positions); the rest of `out` keeps
+// its value from the previous call.
 template <bool CHANGED>
 __global__ __launch_bounds__(256) void relu_requant_pool4_kernel(const int4* __restrict__ y, unsigned int* __restrict__ out,
                                                                  const unsigned char* __restrict__ touched,
+                                                                 const unsigned int* __restrict__ epoch,
                                                                  const unsigned int* __restrict__ touched_all, int tshift,
                                                                  int h, int w, int c4, int ho, int wo, int shift, int pool,
                                                                  unsigned int magic_c4, unsigned int magic_ho) {
@@ -85,7 +86,7 @@ __global__ __launch_bounds__(256) void relu_requant_pool4_kernel(const int4* __r
         unsigned int any = 0;
         for (int sy = sy0; sy <= sy1; ++sy)
             for (int sx = sx0; sx <= sx1; ++sx) any |= t[sy * stx + sx];
-        if (!any) return;
+        if (!(any & epoch[0])) return;
     }
     int4 best = make_int4(0, 0, 0, 0);
     const int4* yb = y + ((size_t)(b * h + y0) * w + x0) * c4 + cv;
@@ -133,7 +134,7 @@ hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s) 
     return hipGetLastError();
 }
 
-hipError_t launch_relu_requant_pool(const void* y, void* out, const void* touched, const unsigned int* touched_all,
+hipError_t launch_relu_requant_pool(const void* y, void* out, const void* touched, const unsigned int* epoch, const unsigned int* touched_all,
                                     int tshift, int n, int h, int w, int c, int shift, int pool, hipStream_t s) {
     const int ho = pool ? (h - 3) / 2 + 1 : h, wo = pool ? (w - 3) / 2 + 1 : w;
     const long long total = (long long)n * ho * wo * c;
@@ -144,10 +145,10 @@ hipError_t launch_relu_requant_pool(const void* y, void* out, const void* touche
         dim3 grid((unsigned int)(n * ho), (unsigned int)((wo * c4 + 255) / 256));
         if (touched)
             hipLaunchKernelGGL(relu_requant_pool4_kernel<true>, grid, dim3(256), 0, s, (const int4*)y, (unsigned int*)out,
-                               (const unsigned char*)touched, touched_all, tshift, h, w, c4, ho, wo, shift, pool, magic(c4), magic(ho));
+                               (const unsigned char*)touched, epoch, touched_all, tshift, h, w, c4, ho, wo, shift, pool, magic(c4), magic(ho));
         else
             hipLaunchKernelGGL(relu_requant_pool4_kernel<false>, grid, dim3(256), 0, s, (const int4*)y, (unsigned int*)out,
-                               (const unsigned char*)nullptr, (const unsigned int*)nullptr, 0, h, w, c4, ho, wo, shift, pool, magic(c4), magic(ho));
+                               (const unsigned char*)nullptr, (const unsigned int*)nullptr, (const unsigned int*)nullptr, 0, h, w, c4, ho, wo, shift, pool, magic(c4), magic(ho));
         return hipGetLastError();
     }
     if (touched) return hipErrorInvalidValue;  // the incremental form needs channel counts in fours

@@ -42,7 +42,7 @@
 // Every output element has exactly one owner: no atomics on y, results reproducible run to run.
 // The grid holds no more workgroups than the chip runs at once; a workgroup takes work units
 // blockIdx.x, blockIdx.x + gridDim.x, ... of the ranked list.
-// The last workgroup to arrive clears the flag array and the arrival counter, so nothing on the host
+// Every workgroup wipes its share of the flag array of the step before's marks (see StepEpoch), so nothing on the host
 // changes between steps (HIP-graph replay safe).
 #include <algorithm>
 #include <mutex>
@@ -108,7 +108,7 @@ constexpr int LIST_CAP = 1024;                // ranked sub-tile ids held in LDS
 template <int DT, int MODE, int NCB, int NT, int TERMS>
 __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     const unsigned char* __restrict__ src0, const unsigned char* __restrict__ src1,
-    const unsigned char* __restrict__ zero16, unsigned int* flags, unsigned int* ctrl,
+    const unsigned char* __restrict__ zero16, unsigned int* flags,
     const uint4* __restrict__ wpack, const int* __restrict__ offtab, const void* __restrict__ bias_v, void* y_v,
     ConvGeom g, DevStats* __restrict__ stats) {
     typedef typename Acc<DT>::type acc_t;
@@ -139,7 +139,6 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     __shared__ int s_ix0[4][NT];
     __shared__ int s_scan[CONV_THREADS / WAVE];
     __shared__ int s_excl[CONV_THREADS];     // per producer thread: set flags before its share, within its wavefront
-    __shared__ int s_last;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -219,6 +218,9 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     const int n_vec = (g.n_words + 3) >> 2;
     const int n_grp = (n_vec + 3) >> 2;
     const int gpt = (n_grp + CONV_THREADS - 1) / CONV_THREADS;
+    const unsigned int eshift = MODE == MODE_DELTA ? g.epoch[EPOCH_TILE] - 1u : 0u;  // this step's bit of a flag
+    // byte flags of a word -> 4 bits: the product moves byte i's bit to bit 24 + i
+    auto nib = [&](unsigned int w) { return ((w >> eshift & LOW) * 0x01020408u) >> 24; };
     auto load_group = [&](int gi) {
         uint4 v[4];
 #pragma unroll
@@ -226,8 +228,6 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
         unsigned long long m = 0;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            // (byte flags 0/1 of a word -> 4 bits: the product moves byte i's bit to bit 24 + i)
-            auto nib = [](unsigned int w) { return ((w & LOW) * 0x01020408u) >> 24; };
             const unsigned int h = nib(v[u].x) | nib(v[u].y) << 4 | nib(v[u].z) << 8 | nib(v[u].w) << 12;
             m |= (unsigned long long)h << (16 * u);
         }
@@ -236,12 +236,11 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     // Small flag arrays are spread over more threads -- 1, 4 or 16 flags each instead of 64 -- because the
     // ranking walks a thread's set bits one by one.  (Then gpt == 1.)
     const int fpt = g.n_sub <= CONV_THREADS ? 1 : g.n_sub <= 4 * CONV_THREADS ? 4 : g.n_sub <= 16 * CONV_THREADS ? 16 : 64;
-    auto nib = [](unsigned int w) { return ((w & LOW) * 0x01020408u) >> 24; };  // byte flags of a word -> 4 bits
     // The k-th 64-flag mask of (producer) thread t's share of the flag array, and the sub-tile of its bit 0.
     auto thread_mask = [&](int t, int k, int& id0) -> unsigned long long {
         if (fpt == 1) {
             id0 = t;
-            return t < g.n_sub ? (unsigned long long)(reinterpret_cast<const unsigned char*>(flags)[t] & 1u) : 0ull;
+            return t < g.n_sub ? (unsigned long long)(reinterpret_cast<const unsigned char*>(flags)[t] >> eshift & 1u) : 0ull;
         }
         if (fpt == 4) {
             id0 = 4 * t;
@@ -266,7 +265,7 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     if (own_group) {
         if (wave == 0) {
             const int id = BX * g.nt + lane;
-            const bool f = lane < g.nt && id < g.n_sub && (reinterpret_cast<const unsigned char*>(flags)[id] & 1u);
+            const bool f = lane < g.nt && id < g.n_sub && (reinterpret_cast<const unsigned char*>(flags)[id] >> eshift & 1u);
             const unsigned long long m = __ballot(f);
             if (f) s_list[__popcll(m & ((1ull << lane) - 1ull))] = id;
             if (lane < 4) s_scan[lane] = lane == 0 ? (int)__popcll(m) : 0;
@@ -324,40 +323,26 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     if (per > g.nt) per = g.nt;
     const int nunits = (count + per - 1) / per;
 
-    unsigned int arrived_before = 0;  // thread 0: workgroups that signalled before this one
-    // Arrival signal, sent once this workgroup has read the flags for the last time.  Every thread has
-    // consumed its flag loads before a barrier by then and this workgroup's stores do not touch the flags,
-    // so no memory fence is needed (a device-scope fence would write back the whole L2).  The answer is
-    // needed only at the end.  (Dense launches have no flags and no signal.)
-    auto arrive = [&]() {
-        if (MODE == MODE_DELTA && tid == 0) arrived_before = atomicAdd(&ctrl[0], 1u);
-    };
-    // The last workgroup to arrive knows that every workgroup has read the flags: it clears them (and
-    // the arrival counter) for the next step, at its own end, off everybody's critical path.
-    auto retire = [&]() {
-        if (MODE != MODE_DELTA) return;
-        if (tid == 0) s_last = (arrived_before == (unsigned int)(GX * GY) - 1u) ? 1 : 0;
-        __syncthreads();
-        if (s_last) {
-            for (int w = tid; w < g.n_words; w += WG_THREADS) {
-                if (g.touched) g.touched[w] = full ? LOW : flags[w];  // what this step wrote in y, for an incremental nonlinearity
-                flags[w] = 0u;
-            }
-            if (tid == 0) {
-                ctrl[0] = 0u;
-                if (g.fresh) g.fresh[0] = 0u;  // the stored input now holds this step's input
-                if (g.touched_all) g.touched_all[0] = 0u;  // `touched` describes this step
-                if (n_flagged && !own_group) atomicAdd(&stats[0].active_tiles, (unsigned long long)n_flagged);
-            }
+    // What a delta launch leaves for the steps and consumers to come (nothing that a workgroup of this launch reads).
+    if (MODE == MODE_DELTA && !producer) {
+        const int nwg = GX * GY, me = BY * GX + BX, share = (g.n_words + nwg - 1) / nwg;
+        const int w1 = min(g.n_words, (me + 1) * share);
+        for (int w = me * share + tid - CONV_THREADS; w < w1; w += WG_THREADS - CONV_THREADS) {
+            const unsigned int v = flags[w], now = v & LOW << eshift;
+            if (v != now) flags[w] = now;  // the step before's marks
+        }
+        if (me == 0 && tid == CONV_THREADS) {
+            g.epoch[EPOCH_SCAN] = 2u - eshift;
+            g.fresh[0] = 0u;  // the stored input holds this step's input
+            g.touched_all[0] = full ? 1u : 0u;  // the flags describe this step, or it writes everything
+            if (n_flagged && !own_group) atomicAdd(&stats[0].active_tiles, (unsigned long long)n_flagged);
         }
         // (each workgroup counted only its own group's flags)
-        if (own_group && tid == 0 && n_flagged && BY == 0)
+        if (own_group && tid == CONV_THREADS && n_flagged && BY == 0)
             atomicAdd(&stats[(unsigned int)BX & (STAT_SLOTS - 1)].active_tiles, (unsigned long long)n_flagged);
-    };
+    }
     if (bx >= nunits) {
         __builtin_amdgcn_s_waitcnt(0);  // let the early weight copy land before the LDS is released
-        arrive();
-        retire();
         return;
     }
     // this workgroup's units: BX + i*gx, i = 0 .. my_nunits-1, ranked in rounds of `ur` units
@@ -486,9 +471,6 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
                 if (iy >= 0 && iy < g.src_h && ix >= 0 && ix < g.src_w) uoff[i] = s_base[wave][slot] + (unsigned int)u.y;
             }
         }
-        // the flags were read for the last time in the last ranking round (the signal is sent where no load
-        // of the issuing thread is waited for soon: returns are in order, a wait would include the atomic)
-        if (iu == r0 && r1 == my_nunits) arrive();
         auto stage_windows = [&](int slab, int buf) {
             unsigned char* dst = bbase + buf * b_bytes;
             const bool last = slab == g.nslab - 1;
@@ -808,12 +790,11 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     }  // units of the round
     }  // rounds
     }
-    retire();
 }
 
 template <int DT, int MODE, int NCB, int NT, int TERMS>
 hipError_t launch_one(const void* src0, const void* src1, const void* zero16, unsigned int* flags,
-                      unsigned int* ctrl, const void* wpack, const int* offtab, const void* bias, void* y,
+                      const void* wpack, const int* offtab, const void* bias, void* y,
                       const ConvGeom& g, DevStats* stats, hipStream_t s) {
     const int ncbg = (g.ncb + NCB - 1) / NCB;
     const size_t lds = conv_lds_bytes(g, NCB, g.nt, TERMS);
@@ -845,18 +826,18 @@ hipError_t launch_one(const void* src0, const void* src1, const void* zero16, un
         }
     }
     hipLaunchKernelGGL(kern, grid, dim3(wg_threads(NT)), lds, s, static_cast<const unsigned char*>(src0),
-                       static_cast<const unsigned char*>(src1), static_cast<const unsigned char*>(zero16), flags, ctrl,
+                       static_cast<const unsigned char*>(src1), static_cast<const unsigned char*>(zero16), flags,
                        static_cast<const uint4*>(wpack), offtab, bias, y, gg, stats);
     return hipGetLastError();
 }
 
 template <int DT, int MODE, int TERMS>
 hipError_t launch_shape(int ncb, int nt, const void* src0, const void* src1, const void* zero16,
-                        unsigned int* flags, unsigned int* ctrl, const void* wpack, const int* offtab, const void* bias, void* y,
+                        unsigned int* flags, const void* wpack, const int* offtab, const void* bias, void* y,
                         const ConvGeom& g, DevStats* stats, hipStream_t s) {
 #define RRM_CASE(CBV, NTV)                                                                                          \
     if (ncb == CBV && nt == NTV)                                                                                     \
-        return launch_one<DT, MODE, CBV, NTV, TERMS>(src0, src1, zero16, flags, ctrl, wpack, offtab, bias, y, g, stats, s);
+        return launch_one<DT, MODE, CBV, NTV, TERMS>(src0, src1, zero16, flags, wpack, offtab, bias, y, g, stats, s);
     nt = nt <= 8 ? 8 : 16;  // fewer slots than the shape has: same code, the slot count is in g.nt
     RRM_CASE(2, 16) RRM_CASE(2, 8) RRM_CASE(1, 16) RRM_CASE(1, 8)
 #undef RRM_CASE
@@ -871,18 +852,18 @@ size_t conv_lds_bytes(const ConvGeom& g, int ncb, int nt, int terms) {
 }
 
 hipError_t launch_conv(int dtype, int mode, int ncb, int nt, int terms, const void* src0, const void* src1,
-                       const void* zero16, unsigned int* flags, unsigned int* ctrl, const void* wpack, const int* offtab,
+                       const void* zero16, unsigned int* flags, const void* wpack, const int* offtab,
                        const void* bias, void* y, const ConvGeom& g, DevStats* stats, hipStream_t s) {
     if (dtype == RRM_I8_I32) {
         if (mode == MODE_DELTA)
-            return launch_shape<RRM_I8_I32, MODE_DELTA, 1>(ncb, nt, src0, src1, zero16, flags, ctrl, wpack, offtab, bias, y, g, stats, s);
-        return launch_shape<RRM_I8_I32, MODE_DENSE, 1>(ncb, nt, src0, src1, zero16, flags, ctrl, wpack, offtab, bias, y, g, stats, s);
+            return launch_shape<RRM_I8_I32, MODE_DELTA, 1>(ncb, nt, src0, src1, zero16, flags, wpack, offtab, bias, y, g, stats, s);
+        return launch_shape<RRM_I8_I32, MODE_DENSE, 1>(ncb, nt, src0, src1, zero16, flags, wpack, offtab, bias, y, g, stats, s);
     }
     if (mode == MODE_DENSE)
-        return launch_shape<RRM_BF16_F32, MODE_DENSE, 1>(ncb, nt, src0, src1, zero16, flags, ctrl, wpack, offtab, bias, y, g, stats, s);
+        return launch_shape<RRM_BF16_F32, MODE_DENSE, 1>(ncb, nt, src0, src1, zero16, flags, wpack, offtab, bias, y, g, stats, s);
     if (terms == 2)
-        return launch_shape<RRM_BF16_F32, MODE_DELTA, 2>(ncb, nt, src0, src1, zero16, flags, ctrl, wpack, offtab, bias, y, g, stats, s);
-    return launch_shape<RRM_BF16_F32, MODE_DELTA, 1>(ncb, nt, src0, src1, zero16, flags, ctrl, wpack, offtab, bias, y, g, stats, s);
+        return launch_shape<RRM_BF16_F32, MODE_DELTA, 2>(ncb, nt, src0, src1, zero16, flags, wpack, offtab, bias, y, g, stats, s);
+    return launch_shape<RRM_BF16_F32, MODE_DELTA, 1>(ncb, nt, src0, src1, zero16, flags, wpack, offtab, bias, y, g, stats, s);
 }
 
 }  // namespace rrm

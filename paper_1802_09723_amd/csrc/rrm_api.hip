@@ -63,7 +63,6 @@ struct rrm_layer {
     unsigned int* sc_arrive = nullptr;  // its arrival counters (one per position block)
     void* wband = nullptr;   // binary: weights packed for the band kernel (matrix cores)
     unsigned int* bin_arrive = nullptr;  // binary single-launch step: arrival counter per stream
-    size_t touched_bytes = 0;
     BinGeom bg{};
     FcGeom fg{};
     // device memory
@@ -77,9 +76,10 @@ struct rrm_layer {
     void* xpad = nullptr;    // dense path of layers whose channel runs are not 16-byte multiples: repacked x
     unsigned long long* bitmap = nullptr;
     unsigned int* tileflag = nullptr;  // binary: 8x8 tile stamps; int8 / bf16: 4x4 sub-tile byte flags
-    unsigned int* touched = nullptr;   // int8 / bf16 conv: the sub-tile flags of the last step (what it wrote in y_snap)
+    unsigned char* touched = nullptr;  // position-gather kernel: byte flags of the positions that the last step wrote
     size_t marks_bytes = 0;
-    unsigned int* ctrl = nullptr;      // arrival counter of the gather kernel
+    // device words: [0 .. 3] counters of the position-gather kernel, [4] FusedSrc::touched_all, [8 + e] StepEpoch e
+    unsigned int* ctrl = nullptr;
     unsigned int* fresh = nullptr;     // conv: device word, non-zero until the first delta step has run (see FusedSrc)
     void* zero16 = nullptr;            // a block of zeros: source of staged units outside the image
     unsigned int* fc_arrive = nullptr;  // FC delta step: arrival counter per stream
@@ -387,8 +387,7 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
     // LDS for longer slabs, and the consumers split the K steps.  Many sub-tiles (many streams): operand reuse matters,
     // so 2 channel blocks x 16 sub-tiles.
     // A delta launch of few sub-tiles keeps eight of them per workgroup where a unit has few K steps to put against what every
-    // workgroup pays (its share of the work list, the arrival count, the joining of the parts); the dense launch, which has neither
-    // list nor count, does not.  Kernel us of the delta launch at 1 .. 4 and at 8, int8, 30 % of the positions changing: 64 x 64,
+    // workgroup pays (its share of the work list, the joining of the parts); the dense launch, which has no list, does not.  Kernel us of the delta launch at 1 .. 4 and at 8, int8, 30 % of the positions changing: 64 x 64,
     // 16 -> 32, 5 x 5 at stride 2 (7 K steps), 8 streams 10.3 and 8.9; 28 x 28, 128 -> 96, 1 x 1 (2), 3 streams 8.8 and 8.2; 64 ->
     // 64, 3 x 3 (9), 10 streams 11.3 and 11.0; 96 -> 128 (14), 3 streams 9.0 and 9.8; 128 -> 64 (18), 10 streams equal. From five K
     // steps on the very smallest layers are spread too (step us, 3 %, spread and at 8: 27 x 40, 48 -> 96, 3 x 3 at stride 2 (7),
@@ -716,6 +715,12 @@ bool use_scatter(const rrm_layer* L) {
     return L->opt_path == 0 && L->opt_conv_kernel == 0 && L->scat_auto;
 }
 
+// where a consumer of an int8 convolution layer sees what its last step wrote: byte flags, and the bit to look for
+const unsigned char* written_flags(const rrm_layer* L) {
+    return L->use_pos ? L->touched : reinterpret_cast<const unsigned char*>(L->tileflag);
+}
+const unsigned int* written_bit(const rrm_layer* L) { return L->ctrl + 8 + (L->use_pos ? EPOCH_ONE : EPOCH_TILE); }
+
 int fc_splits(const rrm_layer* L) { return L->opt_fc_splits > 0 ? L->opt_fc_splits : L->fc_nsplit; }
 
 rrm_status check_ptr(const void* p, const char* what) {
@@ -751,7 +756,7 @@ rrm_status enqueue_dense(rrm_layer* L, const void* x, void* y, hipStream_t st) {
         ConvGeom cg = L->cg;
         cg.nt = L->dense_nt;
         cg.ksh = L->dense_ksh;
-        RRM_HIP(launch_conv(L->dtype, MODE_DENSE, cg.wg_cb, cg.nt, 1, src, nullptr, L->zero16, nullptr, nullptr, L->wpack, L->offtab,
+        RRM_HIP(launch_conv(L->dtype, MODE_DENSE, cg.wg_cb, cg.nt, 1, src, nullptr, L->zero16, nullptr, L->wpack, L->offtab,
                             L->bias, y, cg, L->stats, st));
     }
     return RRM_OK;
@@ -850,13 +855,9 @@ rrm_status rrm_layer_create(const void* weights, const void* bias, const rrm_sha
                                               : (size_t)((s.n * sg.sty * sg.stx + 3) / 4) * 4;
         if ((st = dalloc(L->marks_bytes, (void**)&L->tileflag)) != RRM_OK) return bail(st);
         if (dtype != RRM_BIN_I32) {
-            // everything counts as written until the first step has run (y_snap = bias everywhere)
-            // (one byte per 4x4 block for the window-tile kernel, per output position for the position-gather kernel)
-            L->touched_bytes = L->pos_ok ? std::max(L->marks_bytes, (size_t)s.n * (size_t)ho * (size_t)wo) : L->marks_bytes;
-            if ((st = dalloc(L->touched_bytes, (void**)&L->touched)) != RRM_OK) return bail(st);
-            if (hipMemset(L->touched, 1, round16(L->touched_bytes)) != hipSuccess) return bail(fail(RRM_ERR_HIP, "hipMemset failed"));
-            L->cg.touched = L->touched;
-            L->pg.touched = reinterpret_cast<unsigned char*>(L->touched);
+            // (the window-tile kernel's consumers read its sub-tile flags, the position-gather kernel keeps one byte per position)
+            if (L->pos_ok && (st = dalloc((size_t)s.n * (size_t)ho * (size_t)wo, (void**)&L->touched)) != RRM_OK) return bail(st);
+            L->pg.touched = L->touched;
             // Above this share of active sub-tiles a delta step recomputes the layer instead (the stored
             // input, equal to x_t after the scan, is the source: only layers whose x layout is the kernel's)
             L->cg.xfull = L->cg.aligned ? static_cast<const unsigned char*>(L->x_snap) : nullptr;
@@ -866,13 +867,16 @@ rrm_status rrm_layer_create(const void* weights, const void* bias, const rrm_sha
             L->pg.full_pct = dtype == RRM_BF16_F32 ? 50 : 90;
             if ((st = select_conv_kernel(L, 0)) != RRM_OK) return bail(st);
         }
-        if ((st = dalloc(16, (void**)&L->ctrl)) != RRM_OK) return bail(st);
         {
+            // (everything counts as written until the first step has run: y_snap = bias everywhere)
+            const unsigned int words[16] = {0u, 0u, 0u, 0u, 1u, 1u, 1u, 1u, 1u, 1u, 1u, 1u, 1u, 1u, 1u, 1u};
+            if ((st = upload(words, sizeof(words), (void**)&L->ctrl)) != RRM_OK) return bail(st);
             const unsigned int ones[4] = {1u, 1u, 1u, 1u};
             if ((st = upload(ones, 16, (void**)&L->fresh)) != RRM_OK) return bail(st);
             L->cg.fresh = L->fresh;
             L->pg.fresh = L->fresh;
-            L->cg.touched_all = L->pg.touched_all = L->sc.touched_all = L->ctrl + 3;
+            L->cg.touched_all = L->pg.touched_all = L->sc.touched_all = L->ctrl + 4;
+            L->cg.epoch = L->sg.epoch = L->ctrl + 8;
         }
         if ((st = dalloc(256, &L->zero16)) != RRM_OK) return bail(st);
     }
@@ -906,8 +910,8 @@ rrm_status rrm_step(rrm_layer* L, const void* x_t, void* y_out, void* hip_stream
         if ((st = prof_mark(L, 1, s)) != RRM_OK) return st;
         if ((st = enqueue_dense(L, x_t, L->y_snap, s)) != RRM_OK) return st;
         // a full recomputation writes every output block (enqueued unconditionally: a captured step must not
-        // depend on what the host believes the flags hold)
-        if (L->touched) RRM_HIP(launch_fill_word(L->touched, round16(L->touched_bytes), 0x01010101u, s));
+        // depend on what the host believes the device words hold)
+        if (L->shape.kind == RRM_CONV && L->dtype != RRM_BIN_I32) RRM_HIP(launch_fill_word(L->ctrl + 4, 16, 1u, s));
         if ((st = prof_mark(L, 2, s)) != RRM_OK) return st;
     } else if (L->shape.kind == RRM_FC) {
         if ((st = prof_mark(L, 0, s)) != RRM_OK) return st;
@@ -970,7 +974,7 @@ rrm_status rrm_step(rrm_layer* L, const void* x_t, void* y_out, void* hip_stream
             ConvGeom cg = L->cg;
             if (L->opt_path == 1) cg.xfull = nullptr;  // the sparse path always: no switch to recomputation
             RRM_HIP(launch_conv(L->dtype, MODE_DELTA, L->cg.wg_cb, L->cg.nt, L->dtype == RRM_BF16_F32 ? L->opt_terms : 1,
-                                L->d0, L->d1, L->zero16, L->tileflag, L->ctrl, L->wpack, L->offtab, L->bias, L->y_snap, cg,
+                                L->d0, L->d1, L->zero16, L->tileflag, L->wpack, L->offtab, L->bias, L->y_snap, cg,
                                 L->stats, s));
             }
         }
@@ -987,7 +991,7 @@ rrm_status rrm_step_from_projection(rrm_layer* L, rrm_layer* P, int shift, int p
     if (L == P) return fail(RRM_ERR_STATE, "a layer cannot be its own producer");
     const rrm_shape& s = L->shape;
     const rrm_shape& ps = P->shape;
-    if (s.kind != RRM_CONV || ps.kind != RRM_CONV || L->dtype != RRM_I8_I32 || P->dtype != RRM_I8_I32 || !P->touched)
+    if (s.kind != RRM_CONV || ps.kind != RRM_CONV || L->dtype != RRM_I8_I32 || P->dtype != RRM_I8_I32)
         return fail(RRM_ERR_DTYPE, "rrm_step_from_projection needs two int8 convolution layers");
     const int hy = P->cg.ho, wy = P->cg.wo;
     const int hx = pool ? (hy - 3) / 2 + 1 : hy, wx = pool ? (wy - 3) / 2 + 1 : wy;
@@ -1000,14 +1004,15 @@ rrm_status rrm_step_from_projection(rrm_layer* L, rrm_layer* P, int shift, int p
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     FusedSrc src{};
     src.y = static_cast<const int*>(P->y_snap);
-    src.touched = reinterpret_cast<const unsigned char*>(P->touched);
+    src.touched = written_flags(P);
+    src.epoch = written_bit(P);
     src.hy = hy; src.wy = wy;
     src.tshift = P->tshift;
     src.sty = P->tshift ? P->cg.sty : hy;
     src.stx = P->tshift ? P->cg.stx : wy;
     src.shift = shift; src.pool = pool ? 1 : 0;
     src.fresh = L->fresh;  // a fresh / reset layer holds no f(P) yet: everything is compared
-    src.touched_all = P->ctrl + 3;
+    src.touched_all = P->ctrl + 4;
     rrm_status rs;
     if ((rs = prof_mark(L, 0, st)) != RRM_OK) return rs;
     RRM_HIP(launch_scan_fused(src, L->x_snap, L->d0, L->bitmap, L->tileflag, L->sg, L->stats, st));
@@ -1016,7 +1021,7 @@ rrm_status rrm_step_from_projection(rrm_layer* L, rrm_layer* P, int shift, int p
         RRM_HIP(launch_conv_pos(L->dtype, MODE_DELTA, 1, L->d0, L->d1, L->zero16, L->bitmap, L->ctrl, L->wpos, L->bias,
                                 L->y_snap, L->pg, L->stats, st));
     else
-        RRM_HIP(launch_conv(L->dtype, MODE_DELTA, L->cg.wg_cb, L->cg.nt, 1, L->d0, L->d1, L->zero16, L->tileflag, L->ctrl,
+        RRM_HIP(launch_conv(L->dtype, MODE_DELTA, L->cg.wg_cb, L->cg.nt, 1, L->d0, L->d1, L->zero16, L->tileflag,
                             L->wpack, L->offtab, L->bias, L->y_snap, L->cg, L->stats, st));
     if ((rs = prof_mark(L, 2, st)) != RRM_OK) return rs;
     L->has_snapshot = true;
@@ -1079,8 +1084,8 @@ rrm_status rrm_reset(rrm_layer* L, void* hip_stream) {
         RRM_HIP(launch_fill_zero(L->bitmap, round16(((round16(L->x_bytes) / 16 + 63) / 64) * 8), s));
         RRM_HIP(launch_fill_zero(L->tileflag, round16(L->marks_bytes), s));
         RRM_HIP(launch_fill_zero(L->ctrl, 16, s));
+        RRM_HIP(launch_fill_word(L->ctrl + 4, 48, 1u, s));
         RRM_HIP(launch_fill_word(L->fresh, 16, 1u, s));
-        if (L->touched) RRM_HIP(launch_fill_word(L->touched, round16(L->touched_bytes), 0x01010101u, s));
     }
     if (L->bin_arrive) RRM_HIP(launch_fill_zero(L->bin_arrive, round16((size_t)L->shape.n * sizeof(unsigned int)), s));
     if (L->sc_arrive)
@@ -1239,7 +1244,7 @@ rrm_status rrm_aux_relu_requant_pool_i8(const void* y, void* out, int n, int h, 
     if (!y || !out) return fail(RRM_ERR_NULL, "y / out is NULL");
     if (n < 1 || h < 1 || w < 1 || c < 1 || shift < 0 || shift > 31 || (pool && (h < 3 || w < 3)))
         return fail(RRM_ERR_SHAPE, "bad shape for relu_requant_pool");
-    RRM_HIP(launch_relu_requant_pool(y, out, nullptr, nullptr, 0, n, h, w, c, shift, pool, static_cast<hipStream_t>(hip_stream)));
+    RRM_HIP(launch_relu_requant_pool(y, out, nullptr, nullptr, nullptr, 0, n, h, w, c, shift, pool, static_cast<hipStream_t>(hip_stream)));
     return RRM_OK;
 }
 
@@ -1263,12 +1268,12 @@ rrm_status rrm_aux_probe_copy(void* dst, const void* src, size_t bytes, void* hi
 rrm_status rrm_aux_relu_requant_pool_changed_i8(rrm_layer* L, void* out, int shift, int pool, void* hip_stream) {
     if (!L || !out) return fail(RRM_ERR_NULL, "layer / out is NULL");
     const rrm_shape& s = L->shape;
-    if (s.kind != RRM_CONV || L->dtype != RRM_I8_I32 || !L->touched || s.c_out % 4 != 0)
+    if (s.kind != RRM_CONV || L->dtype != RRM_I8_I32 || s.c_out % 4 != 0)
         return fail(RRM_ERR_SHAPE, "the incremental nonlinearity needs an int8 conv layer with c_out % 4 == 0");
     const int ho = L->cg.ho, wo = L->cg.wo;
     if (shift < 0 || shift > 31 || (pool && (ho < 3 || wo < 3))) return fail(RRM_ERR_SHAPE, "bad shape for relu_requant_pool");
     if (reinterpret_cast<uintptr_t>(out) & 3) return fail(RRM_ERR_ALIGN, "out must be 4-byte aligned");
-    RRM_HIP(launch_relu_requant_pool(L->y_snap, out, L->touched, L->ctrl + 3, L->tshift, s.n, ho, wo, s.c_out, shift, pool,
+    RRM_HIP(launch_relu_requant_pool(L->y_snap, out, written_flags(L), written_bit(L), L->ctrl + 4, L->tshift, s.n, ho, wo, s.c_out, shift, pool,
                                      static_cast<hipStream_t>(hip_stream)));
     return RRM_OK;
 }

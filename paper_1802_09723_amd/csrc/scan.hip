@@ -13,8 +13,8 @@
 // changed in the previous step but not in this one is written back to zero, so the tile kernel can
 // stage its input window with plain loads.  A stamped 8x8 tile holds the number of workgroups that
 // will consume it; each consumer takes one off, so the stamps are all zero again after the binary
-// kernel; the sub-tile flags are cleared by the gather kernel's last workgroup.  Nothing on the host
-// has to change between steps (graph replay safe).
+// kernel; the sub-tile flags hold the step's own value and are wiped by the next step's tile kernel (see StepEpoch).
+// Nothing on the host has to change between steps (graph replay safe).
 //
 // HBM traffic per step: 2|x| read, plus (difference + snapshot) written only where x changed.
 #include "rrm_internal.h"
@@ -70,7 +70,7 @@ __device__ __forceinline__ void mark_tiles(const ScanGeom& g, int pos, unsigned 
 
 // Mark the 4x4 output sub-tiles that see input position `pos`: one byte flag each, plain stores
 // (every writer stores the same value, so no atomics and no same-address serialisation).
-__device__ __forceinline__ void mark_subtiles(const ScanGeom& g, unsigned int pos, unsigned char* flags) {
+__device__ __forceinline__ void mark_subtiles(const ScanGeom& g, unsigned int pos, unsigned char* flags, unsigned char mark) {
     const unsigned int hw = (unsigned int)(g.h * g.w);
     const int b = (int)udiv_big(pos, g.r_hw);
     const int r = (int)(pos - (unsigned int)b * hw);
@@ -83,7 +83,7 @@ __device__ __forceinline__ void mark_subtiles(const ScanGeom& g, unsigned int po
     if (ox_hi > g.wo - 1) ox_hi = g.wo - 1;
     if (oy_lo > oy_hi || ox_lo > ox_hi) return;
     for (int sy = oy_lo >> 2; sy <= (oy_hi >> 2); ++sy)
-        for (int sx = ox_lo >> 2; sx <= (ox_hi >> 2); ++sx) flags[(b * g.sty + sy) * g.stx + sx] = 1;
+        for (int sx = ox_lo >> 2; sx <= (ox_hi >> 2); ++sx) flags[(b * g.sty + sy) * g.stx + sx] = mark;
 }
 
 // Element index of x element e in the padded / folded difference layout (see ScanGeom).
@@ -206,6 +206,7 @@ __device__ __forceinline__ void scan_body(const unsigned char* __restrict__ x_t,
     const long long v = (long long)blk * blockDim.x + threadIdx.x;
     DevStats* __restrict__ stats = stats_base + (blockIdx.x & (STAT_SLOTS - 1));
     const unsigned long long prev_mask = v < nvec ? bitmap[v >> 6] : 0ull;  // wave-uniform word
+    const unsigned int epoch = DT == RRM_BIN_I32 ? 0u : g.epoch[EPOCH_SCAN];
     bool changed = false;
     int p0 = 0, p1 = -1;  // input positions of this unit, when it changed
     unsigned int nelem = 0, ntrunc = 0;
@@ -228,7 +229,7 @@ __device__ __forceinline__ void scan_body(const unsigned char* __restrict__ x_t,
         unsigned int any = 0;
         for (int sy = sy0; sy <= sy1; ++sy)
             for (int sx = sx0; sx <= sx1; ++sx) any |= t[sy * fs.stx + sx];
-        compare = fs.fresh[0] != 0u || fs.touched_all[0] != 0u || any != 0u;
+        compare = fs.fresh[0] != 0u || fs.touched_all[0] != 0u || (any & fs.epoch[0]) != 0u;
         if (compare) {
             b_early = x_snap[v];  // in flight together with the window's loads
             int best[16];
@@ -362,7 +363,7 @@ __device__ __forceinline__ void scan_body(const unsigned char* __restrict__ x_t,
         if (stamp)  // (stamp 0: the layer's delta kernel reads the flip words itself)
             for (int p = p0; p <= p1; ++p) mark_tiles(g, p, tileflag, stamp);
     } else if (g.sty > 0) {  // (layers on the position-gather kernel read the bitmap instead: no flags)
-        for (int p = p0; p <= p1; ++p) mark_subtiles(g, (unsigned int)p, reinterpret_cast<unsigned char*>(tileflag));
+        for (int p = p0; p <= p1; ++p) mark_subtiles(g, (unsigned int)p, reinterpret_cast<unsigned char*>(tileflag), (unsigned char)epoch);
     }
     const unsigned long long mask = __ballot(changed);
     if ((threadIdx.x & 63) == 0 && v < nvec) bitmap[v >> 6] = mask;
@@ -400,6 +401,7 @@ __device__ __forceinline__ void scan_body(const unsigned char* __restrict__ x_t,
         if (blockIdx.x == 0) {  // one scan launch = one delta step
             atomicAdd(&stats_base->delta_steps, 1ull);
             atomicAdd(&stats_base->total_tiles, g.tiles_per_step);
+            if (DT != RRM_BIN_I32) g.epoch[EPOCH_TILE] = epoch;
         }
     }
 }

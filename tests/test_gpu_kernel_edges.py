@@ -92,3 +92,41 @@ def test_fc_step_fills_the_callers_copy(ci, co, n, dt):
     seq = S.random_layer(9400 + ci, S.fc_shape(ci, co, n=n), dt, T=4, frac=0.2)
     seq.frames[2] = seq.frames[1].copy()
     run_sequence(seq, check_dense=(0,), y_out_frames=(0, 1, 2, 3), fc_batched=0)
+
+
+# The sub-tile flags carry the step's own value and are wiped a step later: what a step counts as active is what its own frame
+# changed, whatever the steps before marked.  (map, streams): 1, 4, 16 and 64 flags per thread in the work list, flag arrays
+# off the words of four, one workgroup per flag group and shared ones; the frames change, stay, change elsewhere.
+@pytest.mark.parametrize("m,n", [(9, 1), (29, 3), (31, 15), (31, 40), (64, 17), (63, 67)])
+def test_active_subtiles_of_consecutive_steps(m, n):
+    import numpy as np
+    import oracle
+    from gpu_util import assert_matches, make_layer, to_device
+    seq = S.random_layer(9700 + m, S.conv_shape(m, m, 16, 40, 3, 1, 1, 1, n=n), S.I8, T=2, frac=0.1, block=3)
+    layer = make_layer(seq, path=1, conv_kernel=1)
+    rng = np.random.default_rng(m)
+    x = np.array(seq.frames[0])
+    layer.step(to_device(x, S.I8))
+    seen = layer.stats()["active_tiles"]
+    sub = (m + 3) // 4
+    for t in range(6):
+        changed = np.zeros((n, m, m), bool)
+        if t % 3:
+            for b in range(0, n, 1 + t):
+                y0, x0 = rng.integers(0, m - 2, 2)
+                changed[b, y0:y0 + 2, x0:x0 + 3] = True
+        x[changed] ^= 1
+        layer.step(to_device(x, S.I8))
+        grown = np.zeros((n, m + 2, m + 2), bool)
+        for dy in range(3):
+            for dx in range(3):
+                grown[:, dy:dy + m, dx:dx + m] |= changed
+        tiles = np.zeros((n, 4 * sub, 4 * sub), bool)
+        tiles[:, :m, :m] = grown[:, 1:-1, 1:-1]
+        want = int(tiles.reshape(n, sub, 4, sub, 4).any(axis=(2, 4)).sum())
+        now = layer.stats()["active_tiles"]
+        assert now - seen == want, f"step {t}: {now - seen} active sub-tiles, not {want}"
+        seen = now
+    want = oracle.dense(seq.shape, S.I8, seq.weights, seq.bias, x)
+    assert_matches(layer.y_snapshot().cpu().numpy(), want, S.I8, "last frame")
+    layer.destroy()
