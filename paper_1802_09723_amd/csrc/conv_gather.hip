@@ -48,6 +48,7 @@
 #include <mutex>
 
 #include "rrm_internal.h"
+#include "subtile_list.h"
 
 namespace rrm {
 
@@ -105,12 +106,42 @@ typedef void __attribute__((address_space(3))) * lptr_t;
 constexpr int wg_threads(int nt) { return CONV_THREADS + nt / 2 * WAVE; }  // 4 producer + nt / 2 consumer wavefronts
 constexpr int LIST_CAP = 1024;                // ranked sub-tile ids held in LDS per ranking round
 
+// The kernel's one argument.  It is read through the kernel argument segment, by a pointer that each role of the kernel hides
+// from the compiler once: a field is then loaded where a role uses it instead of all of them at the kernel's start, where they
+// took two hundred scalar registers, most of them spilled into the lanes of vector registers.  (With the reciprocals in ConvGeom
+// and the list of subtile_list.h, a step: 56 x 56, 64 -> 64 bf16, 64 streams, 10 %, 36.05 -> 34.6 us; 35 x 29, 80 -> 112, 9 streams,
+// 18.4 -> 16.95; the five-layer int8 stack at one stream 74.2 -> 70.1; 27 x 27, 96 -> 256 dense, 16 streams, 12.8 -> 12.3.)
+struct ConvArgs {
+    const unsigned char *src0, *src1, *zero16;
+    unsigned int* flags;
+    const uint4* wpack;
+    const int* offtab;
+    const void* bias;
+    void* y;
+    DevStats* stats;
+    ConvGeom g;
+};
+typedef const ConvArgs __attribute__((address_space(4))) * args_t;
+__device__ __forceinline__ args_t hidden(args_t a) {
+    asm volatile("" : "+s"(a));
+    return a;
+}
+
+// A uniform value that stays in a scalar register from here on (what a role's loops use: loaded anew in a loop, a field is a
+// scalar round trip that the loop waits for, with its LDS reads).  Not for pointers: a hidden one is no longer known to be global.
+template <typename T>
+__device__ __forceinline__ T kept(T v) {
+    asm volatile("" : "+s"(v));
+    return v;
+}
+
 template <int DT, int MODE, int NCB, int NT, int TERMS>
-__global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
-    const unsigned char* __restrict__ src0, const unsigned char* __restrict__ src1,
-    const unsigned char* __restrict__ zero16, unsigned int* flags,
-    const uint4* __restrict__ wpack, const int* __restrict__ offtab, const void* __restrict__ bias_v, void* y_v,
-    ConvGeom g, DevStats* __restrict__ stats) {
+__global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(ConvArgs) {
+    const args_t args = (args_t)__builtin_amdgcn_kernarg_segment_ptr();
+    const auto& g = args->g;
+    unsigned int* const flags = args->flags;
+    const int* const offtab = args->offtab;
+    DevStats* const stats = args->stats;
     typedef typename Acc<DT>::type acc_t;
     typedef typename Acc<DT>::vec vec_t;
     typedef typename Acc<DT>::scalar sc_t;
@@ -138,7 +169,6 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     __shared__ int s_iy0[4][NT];             //   (wraps when the origin is in the padding) and the origin itself
     __shared__ int s_ix0[4][NT];
     __shared__ int s_scan[CONV_THREADS / WAVE];
-    __shared__ int s_excl[CONV_THREADS];     // per producer thread: set flags before its share, within its wavefront
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -148,38 +178,26 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     const int kpart = KSPLIT ? (wave - 4) >> (2 - ksh) & 3 : 0;  // ... and part of the K steps
     auto owned = [&](int gq) { return !KSPLIT || (gq >> (2 - ksh)) == kpart; };  // register quad finished by this part
     // Workgroup coordinates: BX of GX unit lanes (a lane takes work units BX, BX + GX, ...), BY of GY channel-block
-    // groups.  With g.xcd_gy set the grid is one-dimensional and the coordinates are dealt so that the GY
+    // groups.  With g.xcd_deal set the grid is one-dimensional and the coordinates are dealt so that the GY
     // workgroups of a lane, which gather the same input windows, sit on the same XCD (workgroups go to the
     // eight XCDs round-robin by their linear index) and find each other's windows in that XCD's L2.
-    int BX, BY, GX, GY;
-    if (g.xcd_gy) {
-        const int lin = (int)blockIdx.x;
-        GY = g.xcd_gy;
-        GX = (int)gridDim.x / GY;
-        const int dealt = (GX >> 3) * 8 * GY;  // workgroups of the lanes that are dealt XCD by XCD
-        if (lin < dealt) {
-            const int slot = lin >> 3;
-            BY = slot % GY;
-            BX = (slot / GY) * 8 + (lin & 7);
-        } else {  // (the few lanes beyond a multiple of eight: wherever they fall)
-            const int rem = lin - dealt;
-            BY = rem % GY;
-            BX = (GX >> 3) * 8 + rem / GY;
-        }
-    } else {
-        BX = (int)blockIdx.x;
-        BY = (int)blockIdx.y;
-        GX = (int)gridDim.x;
-        GY = (int)gridDim.y;
+    const int GX = g.gx, GY = g.gy;
+    int BX = (int)blockIdx.x, BY = (int)blockIdx.y;
+    if (g.xcd_deal) {
+        const int lin = (int)blockIdx.x, dealt = (GX >> 3) * 8 * GY;  // workgroups of the lanes that are dealt XCD by XCD
+        // (the few lanes beyond a multiple of eight: wherever they fall)
+        const int slot = lin < dealt ? lin >> 3 : lin - dealt, lane0 = (int)udiv_magic((unsigned int)slot, (unsigned int)GY, g.magic_gy);
+        BY = slot - lane0 * GY;
+        BX = lin < dealt ? lane0 * 8 + (lin & 7) : (GX >> 3) * 8 + lane0;
     }
 
-    const int ncbg = (g.ncb + NCB - 1) / NCB;  // channel-block groups per filter group
-    const int grp = BY / ncbg;
+    const int ncbg = g.gyg;  // channel-block groups per filter group
+    const int grp = (int)udiv_magic((unsigned int)BY, (unsigned int)ncbg, g.magic_gyg);
     const int cbg = BY - grp * ncbg;
     // packed weights: [group][32-channel block (padded to ncbg*NCB)][MFMA step][lane]; a slab is MFMA steps
     // slab*nq2 .. slab*nq2 + nq2 - 1 of each of this workgroup's NCB blocks
     const int kall = g.nslab * nq2;
-    const uint4* wbase = wpack + ((size_t)(grp * ncbg + cbg) * NCB) * kall * 64 + lane;
+    const uint4* wbase = args->wpack + ((size_t)(grp * ncbg + cbg) * NCB) * kall * 64 + lane;
     auto stage_weights = [&](int slab, int buf) {  // producers
         unsigned char* dst = lds + buf * a_bytes;
 #pragma unroll
@@ -190,79 +208,37 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
                                                  0, 0);
         }
     };
-    // The first weight slab and this thread's rows of the staging table (which serve every unit) do not
-    // depend on the work list.  A dense launch starts their loads at once; a delta launch after the loads
-    // of the list phase, which would otherwise queue behind them (loads return in order), and not at all in
-    // a workgroup that gets no unit.
+    // This thread's rows of the staging table and the first weight slab, which serve every unit, do not depend on the work
+    // list.  A dense launch starts their loads at once; a delta launch when it knows that it has a unit, ahead of making the list
+    // (behind the loads of the flags: loads return in order).
     const int2* utab = reinterpret_cast<const int2*>(offtab + conv_tab_words(g));
     int2 ut[MAXU];
-    auto early_loads = [&]() {
-        if (!producer) return;
-        stage_weights(0, 0);
+    auto load_rows = [&]() {
 #pragma unroll
         for (int i = 0; i < MAXU; ++i) {
-            const int v = tid + i * CONV_THREADS;
-            ut[i] = v < g.nt * g.wpos * g.sc ? utab[v] : int2{0, 0};
+            if (i * CONV_THREADS >= g.nt * g.wpos * g.sc) break;  // (the same in every thread: the table is padded)
+            ut[i] = utab[tid + i * CONV_THREADS];
         }
     };
-    if (MODE == MODE_DENSE) early_loads();
-    for (int e = tid; e < conv_tab_words(g) / 2; e += WG_THREADS)  // window offset table, the same for every slab
-        tab[e] = reinterpret_cast<const int2*>(offtab)[e];
+    if (MODE == MODE_DENSE && producer) {
+        stage_weights(0, 0);
+        load_rows();
+    }
+    if (!producer)
+        for (int e = tid - CONV_THREADS; e < conv_tab_words(g) / 2; e += WG_THREADS - CONV_THREADS)
+            tab[e] = reinterpret_cast<const int2*>(offtab)[e];  // window offset table, the same for every slab
 
     // ---- how many sub-tiles are active? -------------------------------------------------------------
-    // The flag array (one byte per sub-tile) is split into contiguous runs of 64-flag groups, one run per
-    // producer thread.  A group is loaded as four 16-byte vectors and squeezed into a 64-bit mask; a thread's
-    // first group stays in registers, further ones (more than 16384 sub-tiles per launch) are re-read.
     constexpr unsigned int LOW = 0x01010101u;
-    const uint4* fvp = reinterpret_cast<const uint4*>(flags);
-    const int n_vec = (g.n_words + 3) >> 2;
-    const int n_grp = (n_vec + 3) >> 2;
-    const int gpt = (n_grp + CONV_THREADS - 1) / CONV_THREADS;
-    const unsigned int eshift = MODE == MODE_DELTA ? g.epoch[EPOCH_TILE] - 1u : 0u;  // this step's bit of a flag
-    // byte flags of a word -> 4 bits: the product moves byte i's bit to bit 24 + i
-    auto nib = [&](unsigned int w) { return ((w >> eshift & LOW) * 0x01020408u) >> 24; };
-    auto load_group = [&](int gi) {
-        uint4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = 4 * gi + u < n_vec ? fvp[4 * gi + u] : uint4{0u, 0u, 0u, 0u};
-        unsigned long long m = 0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const unsigned int h = nib(v[u].x) | nib(v[u].y) << 4 | nib(v[u].z) << 8 | nib(v[u].w) << 12;
-            m |= (unsigned long long)h << (16 * u);
-        }
-        return m;
-    };
-    // Small flag arrays are spread over more threads -- 1, 4 or 16 flags each instead of 64 -- because the
-    // ranking walks a thread's set bits one by one.  (Then gpt == 1.)
-    const int fpt = g.n_sub <= CONV_THREADS ? 1 : g.n_sub <= 4 * CONV_THREADS ? 4 : g.n_sub <= 16 * CONV_THREADS ? 16 : 64;
-    // The k-th 64-flag mask of (producer) thread t's share of the flag array, and the sub-tile of its bit 0.
-    auto thread_mask = [&](int t, int k, int& id0) -> unsigned long long {
-        if (fpt == 1) {
-            id0 = t;
-            return t < g.n_sub ? (unsigned long long)(reinterpret_cast<const unsigned char*>(flags)[t] >> eshift & 1u) : 0ull;
-        }
-        if (fpt == 4) {
-            id0 = 4 * t;
-            return t < g.n_words ? (unsigned long long)nib(flags[t]) : 0ull;
-        }
-        if (fpt == 16) {
-            id0 = 16 * t;
-            if (t >= n_vec) return 0ull;
-            const uint4 v = fvp[t];
-            return (unsigned long long)(nib(v.x) | nib(v.y) << 4 | nib(v.z) << 8 | nib(v.w) << 12);
-        }
-        const int gi = t * gpt + k;
-        id0 = 64 * gi;
-        return gi < n_grp ? load_group(gi) : 0ull;
-    };
-    const int masks_per_thread = fpt == 64 ? gpt : 1;
-    int count, mine = 0;
+    unsigned int eshift = 0;  // this step's bit of a flag
+    SubtileList ranks;
+    int count;
     // Few sub-tiles in all (one stream of a small map: at most 256, and every group of nt consecutive sub-tiles
     // has a workgroup of its own in the grid): the launch is latency bound, so there is no global list.  A workgroup reads
     // the flags of its own group only, compacts them with one ballot, and is done after one barrier.
     const bool own_group = MODE == MODE_DELTA && g.n_sub <= GX * g.nt && g.n_sub <= CONV_THREADS;
     if (own_group) {
+        eshift = g.epoch[EPOCH_TILE] - 1u;
         if (wave == 0) {
             const int id = BX * g.nt + lane;
             const bool f = lane < g.nt && id < g.n_sub && (reinterpret_cast<const unsigned char*>(flags)[id] >> eshift & 1u);
@@ -274,26 +250,10 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
         count = s_scan[0];
     } else if (MODE == MODE_DELTA) {
         if (producer) {
-            // (four masks at a time: their loads are in flight together)
-            for (int k0 = 0; k0 < masks_per_thread; k0 += 4) {
-                unsigned long long m[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    int id0;
-                    m[k] = k0 + k < masks_per_thread ? thread_mask(tid, k0 + k, id0) : 0ull;
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k) mine += __popcll(m[k]);
-            }
-            // popcount prefix sum (every workgroup does the same small scan)
-            int incl = mine;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_up(incl, o);
-                if (lane >= o) incl += t;
-            }
-            if (lane == 63) s_scan[wave] = incl;
-            s_excl[tid] = incl - mine;  // set flags before this thread's, within its wavefront
+            const int mine = ranks.count(flags, g.n_words, g.epoch, wave, lane, eshift);
+            if (lane == 0) s_scan[wave] = mine;
+        } else {
+            eshift = g.epoch[EPOCH_TILE] - 1u;
         }
         lds_barrier();
         count = s_scan[0] + s_scan[1] + s_scan[2] + s_scan[3];
@@ -317,11 +277,14 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     const int bx = own_group ? 0 : BX;
     // (several units per workgroup: as many as full-size units would need, but of equal size, so that the
     // last pass over the grid is not a nearly empty one of full-size units)
-    const int passes = max(1, (count + gx * g.nt - 1) / (gx * g.nt));
-    int per = (count + gx * passes - 1) / (gx * passes);
-    if (per < 1) per = 1;
-    if (per > g.nt) per = g.nt;
-    const int nunits = (count + per - 1) / per;
+    const unsigned int mgx = own_group ? 0u : g.magic_gx;
+    const int passes = max(1, (int)udiv_magic(udiv_magic((unsigned int)(count + gx * g.nt - 1), (unsigned int)gx, mgx),
+                                              (unsigned int)g.nt, g.magic_per[g.nt]));
+    int per = (int)udiv_magic((unsigned int)(count + gx * passes - 1), (unsigned int)gx, mgx);
+    if (passes > 1) per = passes <= 16 ? (int)udiv_magic((unsigned int)per, (unsigned int)passes, g.magic_per[passes]) : per / passes;
+    per = min(max(per, 1), g.nt);
+    int my_nunits = passes;  // this workgroup's units: bx + i * gx, i = 0 .. my_nunits - 1, as far as they hold a sub-tile
+    while (my_nunits > 0 && (bx + (my_nunits - 1) * gx) * per >= count) --my_nunits;
 
     // What a delta launch leaves for the steps and consumers to come (nothing that a workgroup of this launch reads).
     if (MODE == MODE_DELTA && !producer) {
@@ -341,13 +304,11 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
         if (own_group && tid == CONV_THREADS && n_flagged && BY == 0)
             atomicAdd(&stats[(unsigned int)BX & (STAT_SLOTS - 1)].active_tiles, (unsigned long long)n_flagged);
     }
-    if (bx >= nunits) {
-        __builtin_amdgcn_s_waitcnt(0);  // let the early weight copy land before the LDS is released
+    if (my_nunits == 0) {
+        __builtin_amdgcn_s_waitcnt(0);  // let a dense launch's early weight copy land before the LDS is released
         return;
     }
-    // this workgroup's units: BX + i*gx, i = 0 .. my_nunits-1, ranked in rounds of `ur` units
-    const int my_nunits = (nunits - bx + gx - 1) / gx;
-    const int ur = LIST_CAP / per;
+    constexpr int ur = LIST_CAP / NT;  // units ranked in one round
 
     // lane roles of a consumer: position j of sub-tile `half` of a pair (MFMA column l%32), K pair `khalf` of
     // an MFMA step; of the result it holds channels 8*gq + 4*khalf + (0..3), gq = 0..3, of each 32-channel block
@@ -356,8 +317,6 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     const int off_lane = (((j >> 2) * g.str_y) * g.ww + (j & 3) * g.str_x) * g.sc * 16;
     // this lane's rows of the window offset table: its position's share of the chunk rotation, its K pairs
     const int2* tp = tab + (((g.rot_a * (j >> 2) + g.rot_b * (j & 3)) & (g.rot_p - 1)) * 2 + khalf) * g.nq;
-    sc_t* y = static_cast<sc_t*>(y_v);
-    const sc_t* bias = static_cast<const sc_t*>(bias_v);
     // channel (within the filter group) of register 4*gq of block c; the 4 registers are 4 consecutive channels
     auto chan = [&](int c, int gq) { return (cbg * NCB + c) * 32 + 8 * gq + 4 * khalf; };
     const unsigned int slab_src_bytes = (unsigned int)(g.sc * 16);  // source bytes between consecutive slabs
@@ -368,6 +327,14 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     // each in its own copy of the loops: what one role keeps in registers across iterations is not live
     // in the other's code.
     if (producer) {
+    const args_t pargs = hidden(args);
+    const auto& g = pargs->g;
+    const unsigned char *const src0 = full ? g.xfull : pargs->src0, *const src1 = pargs->src1, *const zero16 = pargs->zero16;
+    const int nslab = kept(g.nslab), src_h = kept(g.src_h), src_w = kept(g.src_w);
+    if (MODE == MODE_DELTA) {
+        load_rows();
+        stage_weights(0, 0);
+    }
     for (int r0 = 0; r0 < my_nunits; r0 += ur) {
     const int r1 = min(r0 + ur, my_nunits);
     // ---- ranking round: the sub-tile ids of units r0 .. r1-1 of this workgroup go to s_list ------------
@@ -375,49 +342,11 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
         if (r0 > 0) __syncthreads();  // the previous round's list is no longer in use
         if (listed && !own_group) {  // (own_group: the list was made with the count)
             // The rank of a set flag is the number of set flags before it; this workgroup owns the ranks
-            // unit*per .. unit*per + per - 1 of its units BX + i*gx, i = r0 .. r1-1.  Every producer
-            // thread looks its share of those ranks up: which thread's flags hold the rank (binary search in
-            // the prefix counts), then which of that thread's set bits it is.  Nobody walks a long run of bits.
-            const int n_owned = (r1 - r0) * per;
-            for (int jj = tid; jj < n_owned; jj += CONV_THREADS) {
-                const int iu = jj / per, kk = jj - iu * per;
-                const int t = (bx + (r0 + iu) * gx) * per + kk;  // the rank
-                if (t >= count) continue;
-                int w = 0, lt = t;  // wavefront holding the rank, rank within it
-                while (lt >= s_scan[w]) lt -= s_scan[w++];
-                int lo = 0, hi = WAVE - 1;  // last thread of the wavefront with s_excl <= lt
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (s_excl[w * WAVE + mid] <= lt) lo = mid;
-                    else hi = mid - 1;
-                }
-                const int owner = w * WAVE + lo;
-                int lr = lt - s_excl[owner];  // rank among the owner's flags
-                int id = -1;
-                for (int k0 = 0; k0 < masks_per_thread && id < 0; k0 += 4) {
-                    unsigned long long m[4];
-                    int id0[4];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        id0[k] = 0;
-                        m[k] = k0 + k < masks_per_thread ? thread_mask(owner, k0 + k, id0[k]) : 0ull;
-                    }
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const int pc = (int)__popcll(m[k]);
-                        if (id < 0 && lr < pc) {
-                            unsigned long long mm = m[k];
-                            while (lr-- > 0) mm &= mm - 1;  // drop the lr lowest set bits
-                            id = id0[k] + __ffsll((long long)mm) - 1;
-                        } else if (id < 0) {
-                            lr -= pc;
-                        }
-                    }
-                }
-                s_list[jj] = id;
-            }
+            // unit*per .. unit*per + per - 1 of its units.
+            int before = 0;
+            for (int w = 0; w < wave; ++w) before += s_scan[w];
+            ranks.fill(s_list, before, eshift, per, g.magic_per[per], BX, GX, g.magic_gx, r0, r1);
         }
-        if (r0 == 0) early_loads();
         lds_barrier();  // the list is published
     } else if (r0 == 0) {
         lds_barrier();  // (the window offset table is published)
@@ -439,7 +368,7 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
             const int iy0 = 4 * sy * g.str_y - g.pad_y, ix0 = 4 * sx * g.str_x - g.pad_x;
             s_iy0[wave][lane] = iy0;
             s_ix0[wave][lane] = ix0;
-            s_base[wave][lane] = (unsigned int)((b * g.src_h + iy0) * g.src_w + ix0) * (unsigned int)g.pos_bytes +
+            s_base[wave][lane] = (unsigned int)((b * src_h + iy0) * src_w + ix0) * (unsigned int)g.pos_bytes +
                                  (unsigned int)(grp * g.grp_bytes);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // LDS operations of one wavefront execute in order
@@ -468,19 +397,19 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
                 const int slot = u.x & 31, hy = (u.x >> 5) & 255, hx = (u.x >> 13) & 255;
                 const int iy = s_iy0[wave][slot] + hy, ix = s_ix0[wave][slot] + hx;
                 ulast |= (unsigned int)((u.x >> 21) & 1) << i;
-                if (iy >= 0 && iy < g.src_h && ix >= 0 && ix < g.src_w) uoff[i] = s_base[wave][slot] + (unsigned int)u.y;
+                if (iy >= 0 && iy < src_h && ix >= 0 && ix < src_w) uoff[i] = s_base[wave][slot] + (unsigned int)u.y;
             }
         }
         auto stage_windows = [&](int slab, int buf) {
             unsigned char* dst = bbase + buf * b_bytes;
-            const bool last = slab == g.nslab - 1;
+            const bool last = slab == nslab - 1;
 #pragma unroll
             for (int i = 0; i < MAXU; ++i) {
                 if (i >= my_units) break;
                 const bool real = uoff[i] != 0xFFFFFFFFu && !(last && ((ulast >> i) & 1u));
                 const unsigned int o = uoff[i] + (unsigned int)slab * slab_src_bytes;
                 unsigned char* d = dst + (i * CONV_THREADS + wave * 64) * 16;  // wave-uniform; lane adds 16*lane
-                const unsigned char* p0 = real ? (full ? g.xfull : src0) + o : zero16;
+                const unsigned char* p0 = real ? src0 + o : zero16;
                 __builtin_amdgcn_global_load_lds((gptr_t)p0, (lptr_t)d, 16, 0, 0);
                 if (TERMS == 2 && !full) {
                     const unsigned char* p1 = real ? src1 + o : zero16;
@@ -492,11 +421,11 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
         // while the consumers still multiply the previous unit's last slab (other parity).
         if (nbuf_a == 2 && iu > 0) stage_weights(0, gs & 1);  // (the very first slab was started at kernel entry)
         stage_windows(0, gs & 1);
-        for (int k = 0; k < g.nslab; ++k) {
+        for (int k = 0; k < nslab; ++k) {
             __builtin_amdgcn_s_waitcnt(0);  // this wavefront's copies for slab k have landed in LDS
             __syncthreads();                // slab k is published; the consumers are done with slab k-1
             ++gs;
-            if (k + 1 < g.nslab) {
+            if (k + 1 < nslab) {
                 stage_weights(k + 1, gs & 1);
                 stage_windows(k + 1, gs & 1);
             }
@@ -506,6 +435,13 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
     }  // units of the round
     }  // rounds
     } else {
+    const args_t cargs = hidden(args);
+    const auto& g = cargs->g;
+    sc_t* const y = static_cast<sc_t*>(cargs->y);
+    const sc_t* const bias = static_cast<const sc_t*>(cargs->bias);
+    const int nslab = kept(g.nslab), nq = kept(g.nq), nt = kept(g.nt), slot_bytes = kept(g.slot_bytes), tiles = kept(g.sty * g.stx),
+              stx = kept(g.stx), ho = kept(g.ho), wo = kept(g.wo), c_out = kept(g.c_out), og = kept(g.og), vec_store = kept(g.vec_store);
+    const unsigned int magic_sub = kept(g.magic_sub), magic_stx = kept(g.magic_stx);
     // Consumer state of a unit: this lane's output position of its sub-tile, the accumulators, and what the result is
     // added to -- the stored projection (delta: Algorithm 1, P_t = P_{t-1} + F * dI) or the bias (dense: Eq. 3).
     // `base` is fetched as soon as the previous unit's results are stored (the sub-tile ids come from the ranked
@@ -527,21 +463,21 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
         ybase = 0;
         if (slot < mycount2) {
             const int id = listed ? s_list[(iu2 - r0) * per + slot] : first2 + slot;
-            const int b = (int)udiv_magic((unsigned int)id, (unsigned int)(g.sty * g.stx), g.magic_sub);
-            const int r = id - b * (g.sty * g.stx);
-            const int sy = (int)udiv_magic((unsigned int)r, (unsigned int)g.stx, g.magic_stx), sx = r - sy * g.stx;
+            const int b = (int)udiv_magic((unsigned int)id, (unsigned int)tiles, magic_sub);
+            const int r = id - b * tiles;
+            const int sy = (int)udiv_magic((unsigned int)r, (unsigned int)stx, magic_stx), sx = r - sy * stx;
             const int oy = 4 * sy + (j >> 2), ox = 4 * sx + (j & 3);
-            pos_ok = ox < g.wo && oy < g.ho;
-            ybase = (unsigned int)((b * g.ho + oy) * g.wo + ox) * (unsigned int)g.c_out + (unsigned int)(grp * g.og);
+            pos_ok = ox < wo && oy < ho;
+            ybase = (unsigned int)((b * ho + oy) * wo + ox) * (unsigned int)c_out + (unsigned int)(grp * og);
         }
 #pragma unroll
         for (int c = 0; c < NCB; ++c)
 #pragma unroll
             for (int gq = 0; gq < 4; ++gq) {
                 const int co = chan(c, gq);
-                const bool ch_ok = g.vec_store && co < g.og && owned(gq);
+                const bool ch_ok = vec_store && co < og && owned(gq);
                 vec_t v = vec_t{0, 0, 0, 0};
-                if (!from_y && ch_ok && bias) v = *reinterpret_cast<const vec_t*>(bias + grp * g.og + co);
+                if (!from_y && ch_ok && bias) v = *reinterpret_cast<const vec_t*>(bias + grp * og + co);
                 if (from_y && ch_ok && pos_ok) v = *reinterpret_cast<const vec_t*>(y + (ybase + (unsigned int)co));
                 if constexpr (LATE_BASE) {
                     base[c][gq] = v;
@@ -585,7 +521,7 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
             const unsigned int ap = aw + lane * 16;
             // (slots beyond the allocated ones are never in use; their lanes read slot 0 instead of running
             // off the buffer)
-            const unsigned int bp = bw + (2 * cw + half < g.nt ? 2 * cw + half : 0) * g.slot_bytes + off_lane;
+            const unsigned int bp = bw + (2 * cw + half < nt ? 2 * cw + half : 0) * slot_bytes + off_lane;
             struct Ops {
                 uint4 a[2][NCB], b0[2], b1[2];
             };
@@ -627,9 +563,11 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
             };
             Ops o0, o1;
             int2 ta, tb;
-            const int q0 = KSPLIT ? (g.nq * kpart) >> ksh : 0, q1 = KSPLIT ? (g.nq * (kpart + 1)) >> ksh : g.nq;
+            const int q0 = KSPLIT ? (nq * kpart) >> ksh : 0, q1 = KSPLIT ? (nq * (kpart + 1)) >> ksh : nq;
             if (KSPLIT && q0 >= q1) return;
             const int qmax = q1 - 1;
+            // (scalar loads and LDS reads share a counter: with none of the former under way the loop's waits are counted ones)
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
             tb = tp[q0];
             fetch(q0, tb, o0);
             ta = tp[min(q0 + 1, qmax)];
@@ -639,7 +577,7 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
             }
         };
 
-        for (int k = 0; k < g.nslab; ++k) {
+        for (int k = 0; k < nslab; ++k) {
             // slab k is staged.  A bare barrier: the producers waited for their copies before they arrived,
             // and this wavefront's own stores and loads of stored projections (previous / this unit) need not
             // have completed -- __syncthreads() would wait for all of them.
@@ -705,8 +643,8 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
         constexpr int RP = 36;  // words per position row of the scratch (16-byte aligned, spreads the banks)
         if (!active) {
             // (no pair in this unit, perhaps no slots at all: a 12-slot layer on the 16-slot shape)
-        } else if (g.vec_store && g.nt >= 8 && 2 * g.slot_bytes >= 32 * RP * 4) {
-            vec_t* scr = reinterpret_cast<vec_t*>(bbase + ((gs - 1) & 1) * b_bytes + (2 * cw) * g.slot_bytes);
+        } else if (vec_store && nt >= 8 && 2 * slot_bytes >= 32 * RP * 4) {
+            vec_t* scr = reinterpret_cast<vec_t*>(bbase + ((gs - 1) & 1) * b_bytes + (2 * cw) * slot_bytes);
             const int posl = lane & 31;
             // the two sub-tiles of the pair (the same in every lane)
             unsigned int corner[2];
@@ -718,13 +656,13 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
                 ny[sl] = nx[sl] = 0;
                 if (slot < mycount) {
                     const int id = listed ? s_list[(iu - r0) * per + slot] : first + slot;
-                    const int b = (int)udiv_magic((unsigned int)id, (unsigned int)(g.sty * g.stx), g.magic_sub);
-                    const int r = id - b * (g.sty * g.stx);
-                    const int sy = (int)udiv_magic((unsigned int)r, (unsigned int)g.stx, g.magic_stx), sx = r - sy * g.stx;
-                    ny[sl] = g.ho - 4 * sy;
-                    nx[sl] = g.wo - 4 * sx;
-                    corner[sl] = (unsigned int)((b * g.ho + 4 * sy) * g.wo + 4 * sx) * (unsigned int)g.c_out +
-                                 (unsigned int)(grp * g.og);
+                    const int b = (int)udiv_magic((unsigned int)id, (unsigned int)tiles, magic_sub);
+                    const int r = id - b * tiles;
+                    const int sy = (int)udiv_magic((unsigned int)r, (unsigned int)stx, magic_stx), sx = r - sy * stx;
+                    ny[sl] = ho - 4 * sy;
+                    nx[sl] = wo - 4 * sx;
+                    corner[sl] = (unsigned int)((b * ho + 4 * sy) * wo + 4 * sx) * (unsigned int)c_out +
+                                 (unsigned int)(grp * og);
                 }
             }
 #pragma unroll
@@ -748,17 +686,17 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
                     const int q = 8 * i + (lane >> 3);  // position of the pair: sub-tile q / 16, position q % 16
                     const vec_t o = scr[(q * RP + 4 * (lane & 7)) >> 2];
                     const int sl = i >> 1, py = 2 * (i & 1) + (lane >> 5), px = (lane >> 3) & 3;
-                    if (py < ny[sl] && px < nx[sl] && ch < g.og)
-                        *reinterpret_cast<vec_t*>(y + (corner[sl] + (unsigned int)((py * g.wo + px) * g.c_out + ch))) = o;
+                    if (py < ny[sl] && px < nx[sl] && ch < og)
+                        *reinterpret_cast<vec_t*>(y + (corner[sl] + (unsigned int)((py * wo + px) * c_out + ch))) = o;
                 }
             }
-        } else if (g.vec_store) {
+        } else if (vec_store) {
 #pragma unroll
             for (int c = 0; c < NCB; ++c)
 #pragma unroll
                 for (int gq = 0; gq < 4; ++gq) {
                     const int co = chan(c, gq);
-                    if (co >= g.og || !pos_ok || !owned(gq)) continue;
+                    if (co >= og || !pos_ok || !owned(gq)) continue;
                     vec_t o;
                     o.x = acc[c][4 * gq + 0];
                     o.y = acc[c][4 * gq + 1];
@@ -773,14 +711,14 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(
 #pragma unroll
                 for (int gq = 0; gq < 4; ++gq) {
                     const int co0 = chan(c, gq);
-                    if (!pos_ok || co0 >= g.og || !owned(gq)) continue;
+                    if (!pos_ok || co0 >= og || !owned(gq)) continue;
                     sc_t* yp4 = y + (ybase + (unsigned int)co0);
-                    for (int k = 0; k < 4 && co0 + k < g.og; ++k) {
+                    for (int k = 0; k < 4 && co0 + k < og; ++k) {
                         const sc_t r = acc[c][4 * gq + k];
                         if (from_y) {
                             if (r != (sc_t)0) yp4[k] += r;
                         } else {
-                            yp4[k] = r + (bias ? bias[grp * g.og + co0 + k] : (sc_t)0);
+                            yp4[k] = r + (bias ? bias[grp * og + co0 + k] : (sc_t)0);
                         }
                     }
                 }
@@ -806,11 +744,14 @@ hipError_t launch_one(const void* src0, const void* src1, const void* zero16, un
     // A full grid (more units than lanes): one-dimensional, with the channel-block groups of a lane on one XCD
     // (see the kernel).
     ConvGeom gg = g;
-    gg.xcd_gy = 0;
-    if (gx >= 8 && gx == resident / gy) {
-        grid = dim3((unsigned int)(gx * gy), 1u);
-        gg.xcd_gy = gy;
-    }
+    gg.gx = gx;
+    gg.gy = gy;
+    gg.gyg = ncbg;
+    gg.magic_gx = magic_of(gx);
+    gg.magic_gy = magic_of(gy);
+    gg.magic_gyg = magic_of(ncbg);
+    gg.xcd_deal = gx >= 8 && gx == resident / gy;
+    if (gg.xcd_deal) grid = dim3((unsigned int)(gx * gy), 1u);
     auto kern = conv_gather_kernel<DT, MODE, NCB, NT, TERMS>;
     if (lds > 64 * 1024) {
         // one per instantiation, shared by every handle and thread of the process: guarded, so that
@@ -825,9 +766,9 @@ hipError_t launch_one(const void* src0, const void* src1, const void* zero16, un
             granted = lds;
         }
     }
-    hipLaunchKernelGGL(kern, grid, dim3(wg_threads(NT)), lds, s, static_cast<const unsigned char*>(src0),
-                       static_cast<const unsigned char*>(src1), static_cast<const unsigned char*>(zero16), flags,
-                       static_cast<const uint4*>(wpack), offtab, bias, y, gg, stats);
+    const ConvArgs args{static_cast<const unsigned char*>(src0), static_cast<const unsigned char*>(src1),
+                        static_cast<const unsigned char*>(zero16), flags, static_cast<const uint4*>(wpack), offtab, bias, y, stats, gg};
+    hipLaunchKernelGGL(kern, grid, dim3(wg_threads(NT)), lds, s, args);
     return hipGetLastError();
 }
 

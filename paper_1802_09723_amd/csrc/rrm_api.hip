@@ -169,10 +169,6 @@ rrm_status dalloc(size_t bytes, void** dev) {
 
 int pitch_for(int sc) { return sc * 16; }
 
-// reciprocal for the kernels' u / d on small u (0 encodes d == 1)
-unsigned int magic_for(int d) { return d <= 1 ? 0u : (unsigned int)((1ull << 32) / (unsigned long long)d + 1ull); }
-
-
 
 // Pack the LDS offset table and the weights for the workgroup shape chosen in L->cg.
 // K pairs are ordered chunk by chunk: pair e of a slab is (chunk slab*sc + e / ntaps, tap e % ntaps),
@@ -200,8 +196,9 @@ rrm_status pack_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
     // words per unit:
     //   [0] slot | window row << 5 | window column << 13 | (chunk missing in the last slab) << 21
     //   [1] source byte offset relative to the window origin at slab 0: (row*src_w + column)*pos_bytes + chunk*16
+    // (rows of one round of the staging threads, the last one padded)
     const int n_units = g.nt * g.wpos * g.sc;
-    tab.resize(tab.size() + (size_t)n_units * 2, 0);
+    tab.resize(tab.size() + (size_t)((n_units + CONV_THREADS - 1) / CONV_THREADS * CONV_THREADS) * 2, 0);
     int* ut = tab.data() + conv_tab_words(g);
     for (int v = 0; v < n_units; ++v) {
         const int r = v / g.sc, cs = v % g.sc;
@@ -264,8 +261,6 @@ rrm_status pack_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
 void choose_rotation(ConvGeom& t, int ntaps) {
     const int P = t.rot_p;
     t.rot_a = t.rot_b = 0;
-    t.magic_sy = magic_for(t.str_y);
-    t.magic_sx = magic_for(t.str_x);
     if (P == 1) return;
     const int ncc = t.sc == P ? 1 : P;  // (whole positions rotated: another chunk shifts every bank alike)
     long long best = -1;
@@ -318,8 +313,6 @@ bool conv_try_shape(ConvGeom& g, int terms, int wg_cb, int nt, int ntaps, long l
         while (t.rot_p * 2 <= sc) t.rot_p *= 2;
         if ((long long)conv_lds_bytes(t, wg_cb, nt, terms) > budget) continue;
         if ((long long)nt * t.wpos * sc > max_units) continue;  // staged units per thread are bounded
-        t.magic_sc[0] = t.magic_sc[1] = magic_for(sc);
-        t.magic_wsc[0] = t.magic_wsc[1] = magic_for(t.wpos);
         choose_rotation(t, ntaps);
         t.last_sc = t.chunks - (t.nslab - 1) * sc;
         g = t;
@@ -374,11 +367,9 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
     g.ww = 3 * g.str_x + g.kw_eff;
     g.wpos = g.wh * g.ww;
     g.ncb = (g.og + 31) / 32;  // 32-channel MFMA blocks per group
-    g.magic_ww = magic_for(g.ww);
-    g.magic_sub = magic_for(g.sty * g.stx);
-    g.magic_stx = magic_for(g.stx);
-    g.magic_wo = magic_for(g.wo);
-    g.magic_ho = magic_for(g.ho);
+    g.magic_sub = magic_of(g.sty * g.stx);
+    g.magic_stx = magic_of(g.stx);
+    for (int d = 0; d <= 16; ++d) g.magic_per[d] = magic_of(d);
     g.vec_store = (s.c_out % 4 == 0) && (g.og % 4 == 0);
     const int ntaps = s.kh * g.kw_eff;
     const int terms = L->dtype == RRM_BF16_F32 ? 2 : 1;
@@ -828,7 +819,7 @@ rrm_status rrm_layer_create(const void* weights, const void* bias, const rrm_sha
         sg.r_c = 1.0 / (double)sg.c;
         sg.r_hw = 1.0 / ((double)s.h * (double)s.w);
         sg.r_w = 1.0 / (double)s.w;
-        sg.magic_stride = magic_for(s.stride);
+        sg.magic_stride = magic_of(s.stride);
         const size_t nvec = round16(L->x_bytes) / 16;
         // difference buffer: x's own layout, or the padded / folded layout of the gather kernel
         L->d_bytes = L->x_bytes;

@@ -122,16 +122,11 @@ struct ConvGeom {
     // different LDS banks for the same (tap, chunk).  The window offset table holds the offsets of all K pairs for
     // every value of a lane's own share of the rotation.
     int rot_p, rot_a, rot_b;
-    unsigned int magic_sy, magic_sx;  // reciprocals of str_y, str_x
     int last_sc;         // chunks present in the last slab
     int nq;              // K steps (4 K pairs = 2 MFMAs deep) per slab: ceil(kh*kw*sc / 4)
     int ncb;             // 32-wide output-channel blocks per group
     int wg_cb, nt;       // workgroup shape: 32-channel blocks (1 or 2) and gathered sub-tiles (8, 16)
-    unsigned int magic_sc[2];   // reciprocals (floor(2^32/d)+1, 0 for d = 1): [0] d = sc
-    unsigned int magic_wsc[2];  // [0] d = wpos
-    unsigned int magic_wo, magic_ho;  // d = wo, d = ho
-    unsigned int magic_ww;      // d = ww
-    unsigned int magic_sub;     // d = sty*stx
+    unsigned int magic_sub;     // reciprocals (floor(2^32/d)+1, 0 for d = 1): d = sty*stx
     unsigned int magic_stx;     // d = stx
     int ksh;             // log2 of the parts that a pair's K steps are split into (one channel block, few slots)
     int vec_store;       // 1: y rows allow 16-byte read-modify-write
@@ -140,8 +135,11 @@ struct ConvGeom {
     unsigned int* epoch;    // see StepEpoch
     const unsigned char* xfull;  // delta launches: the committed input in source layout (full recomputation above
     int full_pct;                //   full_pct % active sub-tiles), or nullptr: never
-    int xcd_gy;          // set by the launcher: 0 = two-dimensional grid, else the channel-block groups of a
-                         // one-dimensional grid dealt XCD by XCD
+    // Set by the launcher: unit lanes, channel-block groups of a lane and of a filter group, with their reciprocals (an integer
+    // division is some thirty dependent instructions that every workgroup of a launch would wait for).  magic_per: of 1 .. 16, made at create.
+    int gx, gy, gyg;
+    unsigned int magic_gx, magic_gy, magic_gyg, magic_per[17];
+    int xcd_deal;        // 1: one-dimensional grid, dealt XCD by XCD; 0: two-dimensional
 };
 
 // Geometry of the single-launch scatter convolution (conv_scatter.hip).
@@ -180,6 +178,9 @@ constexpr int FC_BATCH_MIN_STREAMS = 16;    // from this many streams on an FC l
 constexpr int FC_BATCH_MAX_STREAMS = 4096;  // (launched in groups of at most 128 streams)
 constexpr int FC_CSC_MAX_LDS = 96 * 1024;   // the pruned-weight kernel's update accumulators: c_out <= 24576
 
+// the reciprocal for udiv_magic
+inline unsigned int magic_of(int d) { return d <= 1 ? 0u : (unsigned int)((1ull << 32) / (unsigned long long)d + 1ull); }
+
 // floor(u / d) through the reciprocal magic = floor(2^32 / d) + 1 (0 encodes d == 1).  The product's high word is
 // the quotient or one more than it for every u < 2^32 - d (the reciprocal is rounded up), so one
 // multiply-and-compare makes the result exact over the whole admitted range; without it the estimate is only
@@ -204,7 +205,8 @@ hipError_t launch_scan_fused(const FusedSrc& src, void* x_snap, void* d0, unsign
                              const ScanGeom& g, DevStats* stats, hipStream_t s);
 
 // words of the window offset table: (rotations) x (K pairs of a slab, whole K steps)
-__host__ __device__ inline int conv_tab_words(const ConvGeom& g) { return g.rot_p * g.nq * 4; }
+template <typename G>  // (ConvGeom, in any address space)
+__host__ __device__ inline int conv_tab_words(const G& g) { return g.rot_p * g.nq * 4; }
 size_t conv_lds_bytes(const ConvGeom& g, int ncb, int nt, int terms);  // dynamic LDS of the gather kernel
 hipError_t launch_conv(int dtype, int mode, int ncb, int nt, int terms, const void* src0, const void* src1,
                        const void* zero16, unsigned int* subbits, const void* wpack, const int* offtab,

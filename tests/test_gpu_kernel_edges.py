@@ -95,9 +95,10 @@ def test_fc_step_fills_the_callers_copy(ci, co, n, dt):
 
 
 # The sub-tile flags carry the step's own value and are wiped a step later: what a step counts as active is what its own frame
-# changed, whatever the steps before marked.  (map, streams): 1, 4, 16 and 64 flags per thread in the work list, flag arrays
-# off the words of four, one workgroup per flag group and shared ones; the frames change, stay, change elsewhere.
-@pytest.mark.parametrize("m,n", [(9, 1), (29, 3), (31, 15), (31, 40), (64, 17), (63, 67)])
+# changed, whatever the steps before marked.  (map, streams): flag arrays off the words of four and the vectors of 16, one
+# workgroup per flag group, one round of vectors in the work list, several, and more than stay in registers; the frames
+# change, stay, change elsewhere.
+@pytest.mark.parametrize("m,n", [(9, 1), (29, 3), (31, 15), (31, 40), (64, 17), (63, 67), (63, 150)])
 def test_active_subtiles_of_consecutive_steps(m, n):
     import numpy as np
     import oracle
