@@ -191,9 +191,9 @@ __global__ void repack_word_kernel(const unsigned char* __restrict__ x, unsigned
     dst[r * (unsigned int)g.wp + ix] = word;
 }
 
-// FUSED: the unit's input is computed from the producer's projection (see FusedSrc); a unit none of whose
+// FUSED: the unit's input is computed from the producer's projection (see FusedSrc; no pooling); a unit none of whose
 // source blocks was written by the producer's last step cannot have changed and is not even loaded.
-template <int DT, bool SCATTER, bool FUSED, bool POOL>
+template <int DT, bool SCATTER, bool FUSED>
 __device__ __forceinline__ void scan_body(const unsigned char* __restrict__ x_t, uint4* __restrict__ x_snap,
                                           uint4* __restrict__ d0, uint4* __restrict__ d1,
                                           unsigned long long* __restrict__ bitmap, unsigned int* __restrict__ tileflag,
@@ -220,44 +220,23 @@ __device__ __forceinline__ void scan_body(const unsigned char* __restrict__ x_t,
         const unsigned int p = udiv_big(e0, g.r_c), c0 = e0 - p * (unsigned int)g.c;
         const unsigned int bb = udiv_big(p, g.r_hw), r = p - bb * (unsigned int)(g.h * g.w);
         const int iy = (int)udiv_big(r, g.r_w), ix = (int)r - iy * g.w;
-        // (POOL is a template parameter: the unpooled form keeps no window in registers and runs at twice the
-        // occupancy)
-        constexpr int span = POOL ? 2 : 0;
-        const int y0 = POOL ? 2 * iy : iy, x0 = POOL ? 2 * ix : ix;
         const unsigned char* t = fs.touched + (size_t)bb * fs.sty * fs.stx;
-        const int sy0 = y0 >> fs.tshift, sy1 = (y0 + span) >> fs.tshift, sx0 = x0 >> fs.tshift, sx1 = (x0 + span) >> fs.tshift;
-        unsigned int any = 0;
-        for (int sy = sy0; sy <= sy1; ++sy)
-            for (int sx = sx0; sx <= sx1; ++sx) any |= t[sy * fs.stx + sx];
+        const unsigned int any = t[(iy >> fs.tshift) * fs.stx + (ix >> fs.tshift)];
         compare = fs.fresh[0] != 0u || fs.touched_all[0] != 0u || (any & fs.epoch[0]) != 0u;
         if (compare) {
-            b_early = x_snap[v];  // in flight together with the window's loads
+            b_early = x_snap[v];  // in flight together with the projection's loads
+            const int4* yb = reinterpret_cast<const int4*>(fs.y + (((size_t)bb * fs.hy + iy) * fs.wy + ix) * g.c + c0);
+            int4 w[4];
             int best[16];
 #pragma unroll
-            for (int k = 0; k < 16; ++k) best[k] = 0;
-            const int4* yb = reinterpret_cast<const int4*>(fs.y + (((size_t)bb * fs.hy + y0) * fs.wy + x0) * g.c + c0);
-            const size_t c4 = (size_t)g.c / 4;
-            // a row of the window at a time: its (up to) 12 loads are in flight together
+            for (int q = 0; q < 4; ++q) w[q] = yb[q];
 #pragma unroll
-            for (int dy = 0; dy < 3; ++dy) {
-                if (dy > span) break;
-                int4 w[3][4];
-#pragma unroll
-                for (int dx = 0; dx < 3; ++dx)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        w[dx][q] = dx <= span ? yb[(size_t)(dy * fs.wy + dx) * c4 + q] : make_int4(0, 0, 0, 0);
-#pragma unroll
-                for (int dx = 0; dx < 3; ++dx)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        best[4 * q + 0] = max(best[4 * q + 0], w[dx][q].x);
-                        best[4 * q + 1] = max(best[4 * q + 1], w[dx][q].y);
-                        best[4 * q + 2] = max(best[4 * q + 2], w[dx][q].z);
-                        best[4 * q + 3] = max(best[4 * q + 3], w[dx][q].w);
-                    }
+            for (int q = 0; q < 4; ++q) {
+                best[4 * q + 0] = max(0, w[q].x);
+                best[4 * q + 1] = max(0, w[q].y);
+                best[4 * q + 2] = max(0, w[q].z);
+                best[4 * q + 3] = max(0, w[q].w);
             }
-            // max commutes with the monotone map v -> min(127, max(0, v) >> shift)
             unsigned int wds[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q)
@@ -406,9 +385,6 @@ __device__ __forceinline__ void scan_body(const unsigned char* __restrict__ x_t,
     }
 }
 
-// The entry points.  The pooled fused form keeps a row of its 3x3 window in flight (12 loads of 16 bytes) and is
-// fastest with about 100 registers at four wavefronts per SIMD (measured on the 27 x 27 and 13 x 13 consumers: 47 us
-// against 53 us at 64 registers); every other form needs 32 to 52 registers and runs at the occupancy that allows.
 template <int DT, bool SCATTER, bool FUSED>
 __global__ __launch_bounds__(256) void scan_kernel(const unsigned char* __restrict__ x_t, uint4* __restrict__ x_snap,
                                                    uint4* __restrict__ d0, uint4* __restrict__ d1,
@@ -416,15 +392,131 @@ __global__ __launch_bounds__(256) void scan_kernel(const unsigned char* __restri
                                                    unsigned int* __restrict__ tileflag, unsigned int stamp,
                                                    ScanGeom g, long long nvec, long long total_bytes,
                                                    DevStats* __restrict__ stats_base, FusedSrc fs) {
-    scan_body<DT, SCATTER, FUSED, false>(x_t, x_snap, d0, d1, bitmap, tileflag, stamp, g, nvec, total_bytes, stats_base, fs);
+    scan_body<DT, SCATTER, FUSED>(x_t, x_snap, d0, d1, bitmap, tileflag, stamp, g, nvec, total_bytes, stats_base, fs);
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void scan_pooled_kernel(
-    uint4* __restrict__ x_snap, uint4* __restrict__ d0, unsigned long long* __restrict__ bitmap,
-    unsigned int* __restrict__ tileflag, ScanGeom g, long long nvec, long long total_bytes,
-    DevStats* __restrict__ stats_base, FusedSrc fs) {
-    scan_body<RRM_I8_I32, false, true, true>(nullptr, x_snap, d0, nullptr, bitmap, tileflag, 0u, g, nvec, total_bytes,
-                                             stats_base, fs);
+// The pooled fused form: every unit is the largest of nine positions of the producer's projection, nine times 64 bytes.  Four
+// lanes share a unit, four channels each, so that a load instruction reads 16 whole units' 1 KiB and all nine loads of a unit
+// are in flight.  (A lane that reads all 64 bytes of its unit touches four times as many cache lines per instruction and had
+// three rows of loads one after the other: 27 x 27 x 96 and 13 x 13 x 256 consumers, 512 streams, 41.4 and 41.2 -> 29.7 and
+// 34.0 us, one stream 6.3 -> 5.1 each.  More rows in flight in that form: 48 us.)  A wavefront takes ITER groups of 16 units;
+// with ITER = 4 the lanes first look after a unit each -- its place, whether it can have changed -- and hand that to the four
+// that compute it, and groups with nothing to do are skipped.  The unpooled form, one 64-byte read per unit, is at the rate of
+// the memory as it is: 25.1 us a launch in scan_body's form, 27.4 in this one (13 x 13 x 384, 512 streams).
+template <int ITER>
+__global__ __launch_bounds__(256) void scan_pooled_kernel(unsigned int* __restrict__ x_snap, unsigned int* __restrict__ d0,
+                                                          unsigned long long* __restrict__ bitmap, unsigned char* __restrict__ flags,
+                                                          ScanGeom g, unsigned int nvec, DevStats* __restrict__ stats_base, FusedSrc fs) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // (contiguous ranges of units per XCD: see scan_body)
+    const unsigned int blk = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const unsigned int v0 = (blk * 4u + (unsigned int)wave) * (16u * ITER);  // the wavefront's first unit
+    const unsigned int epoch = g.epoch[EPOCH_SCAN];
+    const unsigned int prev16 = v0 < nvec ? (unsigned int)(bitmap[v0 >> 6] >> (v0 & 63u)) : 0u;  // (ITER = 1)
+    const unsigned long long prev = ITER == 1 ? prev16 & 0xFFFFu : v0 < nvec ? bitmap[v0 >> 6] : 0ull;
+    // this lane's unit: 16 channels of one position (c_in is a multiple of 16)
+    const unsigned int v = v0 + (unsigned int)(ITER == 1 ? lane >> 2 : lane);
+    unsigned int p = 0, off = 0;
+    bool compare = v < nvec;
+    if (compare) {
+        const unsigned int e0 = v * 16u;
+        p = udiv_big(e0, g.r_c);
+        const unsigned int c0 = e0 - p * (unsigned int)g.c, bb = udiv_big(p, g.r_hw), r = p - bb * (unsigned int)(g.h * g.w);
+        const int iy = (int)udiv_big(r, g.r_w), ix = (int)r - iy * g.w, y0 = 2 * iy, x0 = 2 * ix;
+        off = ((bb * (unsigned int)fs.hy + (unsigned int)y0) * (unsigned int)fs.wy + (unsigned int)x0) * (unsigned int)g.c + c0;
+        const unsigned char* t = fs.touched + (size_t)bb * fs.sty * fs.stx;
+        const int sy0 = y0 >> fs.tshift, sy1 = (y0 + 2) >> fs.tshift, sx0 = x0 >> fs.tshift, sx1 = (x0 + 2) >> fs.tshift;
+        unsigned int any = 0;
+        for (int sy = sy0; sy <= sy1; ++sy)
+            for (int sx = sx0; sx <= sx1; ++sx) any |= t[sy * fs.stx + sx];
+        compare = fs.fresh[0] != 0u || fs.touched_all[0] != 0u || (any & fs.epoch[0]) != 0u;
+    }
+    const unsigned long long todo = __ballot(compare);
+    unsigned long long mask = 0;
+    unsigned int nelem = 0;
+#pragma unroll 1
+    for (int i = 0; i < ITER; ++i) {
+        const unsigned long long here = ITER == 1 ? todo : todo >> 16 * i & 0xFFFFull;
+        const unsigned int was = (unsigned int)(prev >> 16 * i) & 0xFFFFu;
+        if (!here && !was) continue;  // (the same in every lane)
+        const unsigned int dw = 4u * (v0 + 16u * (unsigned int)i) + (unsigned int)lane;  // this lane's word of x
+        unsigned int o = off;
+        bool act = compare;
+        if (ITER > 1) {
+            o = __shfl(off, 16 * i + (lane >> 2));
+            act = here >> (lane >> 2) & 1ull;
+        }
+        unsigned int a = 0, b = 0;
+        if (act) {
+            b = x_snap[dw];
+            const char* yb = reinterpret_cast<const char*>(fs.y);
+            const unsigned int vo = (o + 4u * (unsigned int)(lane & 3)) * 4u;
+            int4 w[3][3];
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+                    w[dy][dx] = *reinterpret_cast<const int4*>(yb + (size_t)(dy * fs.wy + dx) * (unsigned int)g.c * 4u + vo);
+            int best[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) {
+                    best[0] = max(best[0], w[dy][dx].x);
+                    best[1] = max(best[1], w[dy][dx].y);
+                    best[2] = max(best[2], w[dy][dx].z);
+                    best[3] = max(best[3], w[dy][dx].w);
+                }
+            // max commutes with the monotone map v -> min(127, max(0, v) >> shift)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) a |= (unsigned int)min(127, best[k] >> fs.shift) << (8 * k);
+        }
+        const unsigned int z = a ^ b;
+        unsigned int zz = z;  // ... of the unit
+        zz |= (unsigned int)__builtin_amdgcn_mov_dpp((int)zz, 0xB1, 0xF, 0xF, true);  // quad_perm 1, 0, 3, 2
+        zz |= (unsigned int)__builtin_amdgcn_mov_dpp((int)zz, 0x4E, 0xF, 0xF, true);  // quad_perm 2, 3, 0, 1
+        const bool changed = zz != 0u;  // (not compared: a == b)
+        if (changed) {
+            // byte-wise wrapping subtraction and its signed-overflow mask
+            const unsigned int H = 0x80808080u, d = ((a | H) - (b & ~H)) ^ ((a ^ ~b) & H);
+            if (z & (a ^ d) & H) atomicOr(&stats_base[blockIdx.x & (STAT_SLOTS - 1)].range_error, 1u);
+            nelem += __popc((((z & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | z) & H);
+            d0[dw] = d;
+            x_snap[dw] = a;
+        } else if (was >> (lane >> 2) & 1u) {
+            d0[dw] = 0u;  // changed last step, unchanged now: the zero of the difference buffer is restored
+        }
+        // one bit per unit: lanes 0 .. 15 take the word of theirs
+        const unsigned int c16 = (unsigned int)__ballot(__shfl(changed ? 1 : 0, 4 * (lane & 15)) != 0) & 0xFFFFu;
+        mask |= (unsigned long long)c16 << 16 * i;
+    }
+    // mark the sub-tiles that see the changed positions
+    if (ITER == 1 ? (lane & 3) == 0 && (mask >> (lane >> 2) & 1ull) : (mask >> lane & 1ull) != 0ull)
+        if (g.sty > 0) mark_subtiles(g, p, flags, (unsigned char)epoch);  // (the position-gather kernel reads the bitmap)
+    __shared__ unsigned int s_ne[4];
+    __shared__ unsigned long long s_mask[4];
+#pragma unroll
+    for (int k = 32; k > 0; k >>= 1) nelem += __shfl_xor(nelem, k);
+    if (lane == 0) {
+        s_ne[wave] = nelem;
+        s_mask[wave] = mask;
+        if (ITER == 4 && v0 < nvec) bitmap[v0 >> 6] = mask;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        DevStats* stats = stats_base + (blockIdx.x & (STAT_SLOTS - 1));
+        if (ITER == 1 && v0 < nvec) bitmap[v0 >> 6] = s_mask[0] | s_mask[1] << 16 | s_mask[2] << 32 | s_mask[3] << 48;
+        const unsigned int nu = (unsigned int)(__popcll(s_mask[0]) + __popcll(s_mask[1]) + __popcll(s_mask[2]) + __popcll(s_mask[3]));
+        if (nu) {
+            atomicAdd(&stats->changed_elems, (unsigned long long)(s_ne[0] + s_ne[1] + s_ne[2] + s_ne[3]));
+            atomicAdd(&stats->changed_units, (unsigned long long)nu);
+        }
+        if (blockIdx.x == 0) {  // one scan launch = one delta step
+            atomicAdd(&stats_base->delta_steps, 1ull);
+            atomicAdd(&stats_base->total_tiles, g.tiles_per_step);
+            g.epoch[EPOCH_TILE] = epoch;
+        }
+    }
 }
 
 }  // namespace
@@ -477,15 +569,22 @@ hipError_t launch_scan_fused(const FusedSrc& src, void* x_snap, void* d0, unsign
     if (g.scatter || g.c % 16 != 0) return hipErrorInvalidValue;
     const long long total_bytes = g.total_elems;
     const long long nvec = total_bytes / 16;
-    const long long blocks = ((nvec + 255) / 256 + 7) / 8 * 8;  // a multiple of the 8 XCDs (see the kernel)
-    if (blocks <= 0) return hipSuccess;
-    if (src.pool)
-        hipLaunchKernelGGL(scan_pooled_kernel, dim3((unsigned int)blocks), dim3(256), 0, s, (uint4*)x_snap, (uint4*)d0, bitmap,
-                           marks, g, nvec, total_bytes, stats, src);
-    else
+    if (nvec <= 0) return hipSuccess;
+    if (src.pool) {
+        // Small inputs: a group per wavefront, four times the wavefronts.  Stack steps with one and four groups: 66.2 and 69.7 us at
+        // one stream, 101.9 and 104.7 at 16 (70 and 43 thousand units), 136.1 and 135.4 at 64, 635 and 603 at 512.
+        const bool small = nvec <= 131072;
+        const unsigned int units = small ? 64u : 256u;  // of a workgroup
+        const dim3 grid(((unsigned int)nvec + units * 8 - 1) / (units * 8) * 8);
+        auto kern = small ? scan_pooled_kernel<1> : scan_pooled_kernel<4>;
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, (unsigned int*)x_snap, (unsigned int*)d0, bitmap, (unsigned char*)marks, g,
+                           (unsigned int)nvec, stats, src);
+    } else {
+        const long long blocks = ((nvec + 255) / 256 + 7) / 8 * 8;  // a multiple of the 8 XCDs (see the kernel)
         hipLaunchKernelGGL((scan_kernel<RRM_I8_I32, false, true>), dim3((unsigned int)blocks), dim3(256), 0, s,
                            (const unsigned char*)nullptr, (uint4*)x_snap, (uint4*)d0, (uint4*)nullptr, bitmap, marks, 0u, g, nvec,
                            total_bytes, stats, src);
+    }
     return hipGetLastError();
 }
 

@@ -131,3 +131,40 @@ def test_active_subtiles_of_consecutive_steps(m, n):
     want = oracle.dense(seq.shape, S.I8, seq.weights, seq.bias, x)
     assert_matches(layer.y_snapshot().cpu().numpy(), want, S.I8, "last frame")
     layer.destroy()
+
+
+# The pooled scan of a layer fed by the layer before: one group of 16 units per wavefront, and four where the input is large.
+# (producer's map, channels, streams): units off the 16s, the 64s and the workgroups, both sides of the line, one unit in all.
+# The producer's frame changes, stays (the difference buffer is cleared) and changes elsewhere; every count is the frame's own.
+@pytest.mark.parametrize("m,c,n", [(3, 16, 1), (11, 48, 3), (55, 16, 2), (29, 32, 40), (55, 16, 180)])
+def test_pooled_scan_of_a_fused_step(m, c, n):
+    import numpy as np
+    import oracle
+    import paper_1802_09723_amd as rrm
+    from gpu_util import assert_matches, to_device
+    rng = np.random.default_rng(m + n)
+    s1, q = S.conv_shape(m, m, 16, c, 3, 1, 1, 1, n=n), (m - 3) // 2 + 1
+    s2 = S.conv_shape(q, q, c, 24, 3 if q > 1 else 1, 1, 1 if q > 1 else 0, 1, n=n)
+    w1, w2 = (rng.integers(-127, 128, (s.c_out, s.kh, s.kw, s.c_in), dtype=np.int8) for s in (s1, s2))
+    b1, b2 = (rng.integers(-1000, 1001, s.c_out).astype(np.int32) for s in (s1, s2))
+    A, B = rrm.Layer(s1, S.I8, w1, b1), rrm.Layer(s2, S.I8, w2, b2)
+    x = S.draw_i8_relu(rng, s1.x_shape)
+    old, shift, seen = np.zeros(s2.x_shape, np.int8), None, (0, 0)
+    for t in range(4):
+        if t in (1, 3):
+            y0 = int(rng.integers(0, max(1, m - 4)))
+            x[::1 + t, y0:y0 + 4, :1 + m // 2] = S.draw_i8_relu(rng, x[::1 + t, y0:y0 + 4, :1 + m // 2].shape)
+        A.step(to_device(x, S.I8))
+        ya = oracle.dense(s1, S.I8, w1, b1, x) if t != 2 else ya
+        if shift is None:
+            shift = oracle.calibrate_shift(ya)
+        B.step_from_projection(A, shift, True)
+        f = oracle.relu_requant_pool(ya, shift, True)
+        st = B.stats()
+        units = int((f != old).reshape(-1, 16).any(axis=1).sum())
+        assert (st["changed_elems"] - seen[0], st["changed_units"] - seen[1]) == (int((f != old).sum()), units), f"step {t}"
+        assert np.array_equal(B.x_snapshot_bytes().cpu().numpy(), f.view(np.uint8).reshape(-1)), f"step {t}"
+        seen, old = (st["changed_elems"], st["changed_units"]), f
+    assert_matches(B.y_snapshot().cpu().numpy(), oracle.dense(s2, S.I8, w2, b2, old), S.I8, "last frame")
+    A.destroy()
+    B.destroy()
