@@ -68,22 +68,27 @@ __device__ __forceinline__ void mark_tiles(const ScanGeom& g, int pos, unsigned 
             tileflag[(b * g.tiles_y + ty) * g.tiles_x + tx] = stamp;
 }
 
-// Mark the 4x4 output sub-tiles that see input position `pos`: one byte flag each, plain stores
-// (every writer stores the same value, so no atomics and no same-address serialisation).
-__device__ __forceinline__ void mark_subtiles(const ScanGeom& g, unsigned int pos, unsigned char* flags, unsigned char mark) {
+// Mark the 4x4 output sub-tiles that see the input positions pos .. last (of a unit of few channels: several): one byte flag
+// each, plain stores (every writer stores the same value, so no atomics and no same-address serialisation).  A run of
+// positions in a row is marked at once -- its output columns are those between its ends', unless the stride leaves columns
+// that no window reads (227 x 227 x 3, one stream, the scan 9.1 -> 8.0 us).
+__device__ __forceinline__ void mark_subtiles(const ScanGeom& g, unsigned int pos, unsigned int last, unsigned char* flags, unsigned char mark) {
     const unsigned int hw = (unsigned int)(g.h * g.w);
-    const int b = (int)udiv_big(pos, g.r_hw);
-    const int r = (int)(pos - (unsigned int)b * hw);
-    const int iy = (int)udiv_big((unsigned int)r, g.r_w), ix = r - iy * g.w;
-    const int ty0 = iy + g.pad - (g.kh - 1), tx0 = ix + g.pad - (g.kw - 1);
-    const int oy_lo = ty0 <= 0 ? 0 : udiv_small(ty0 + g.stride - 1, g.magic_stride);
-    const int ox_lo = tx0 <= 0 ? 0 : udiv_small(tx0 + g.stride - 1, g.magic_stride);
-    int oy_hi = udiv_small(iy + g.pad, g.magic_stride), ox_hi = udiv_small(ix + g.pad, g.magic_stride);
-    if (oy_hi > g.ho - 1) oy_hi = g.ho - 1;
-    if (ox_hi > g.wo - 1) ox_hi = g.wo - 1;
-    if (oy_lo > oy_hi || ox_lo > ox_hi) return;
-    for (int sy = oy_lo >> 2; sy <= (oy_hi >> 2); ++sy)
-        for (int sx = ox_lo >> 2; sx <= (ox_hi >> 2); ++sx) flags[(b * g.sty + sy) * g.stx + sx] = mark;
+    while (pos <= last) {
+        const int b = (int)udiv_big(pos, g.r_hw);
+        const int r = (int)(pos - (unsigned int)b * hw);
+        const int iy = (int)udiv_big((unsigned int)r, g.r_w), ix = r - iy * g.w;
+        const int more = g.stride <= g.kw ? min((int)(last - pos), g.w - 1 - ix) : 0;
+        pos += (unsigned int)more + 1u;
+        const int ty0 = iy + g.pad - (g.kh - 1), tx0 = ix + g.pad - (g.kw - 1);
+        const int oy_lo = ty0 <= 0 ? 0 : udiv_small(ty0 + g.stride - 1, g.magic_stride);
+        const int ox_lo = tx0 <= 0 ? 0 : udiv_small(tx0 + g.stride - 1, g.magic_stride);
+        const int oy_hi = min(udiv_small(iy + g.pad, g.magic_stride), g.ho - 1);
+        const int ox_hi = min(udiv_small(ix + more + g.pad, g.magic_stride), g.wo - 1);
+        if (oy_lo > oy_hi || ox_lo > ox_hi) continue;
+        for (int sy = oy_lo >> 2; sy <= (oy_hi >> 2); ++sy)
+            for (int sx = ox_lo >> 2; sx <= (ox_hi >> 2); ++sx) flags[(b * g.sty + sy) * g.stx + sx] = mark;
+    }
 }
 
 // Element index of x element e in the padded / folded difference layout (see ScanGeom).
@@ -342,7 +347,7 @@ __device__ __forceinline__ void scan_body(const unsigned char* __restrict__ x_t,
         if (stamp)  // (stamp 0: the layer's delta kernel reads the flip words itself)
             for (int p = p0; p <= p1; ++p) mark_tiles(g, p, tileflag, stamp);
     } else if (g.sty > 0) {  // (layers on the position-gather kernel read the bitmap instead: no flags)
-        for (int p = p0; p <= p1; ++p) mark_subtiles(g, (unsigned int)p, reinterpret_cast<unsigned char*>(tileflag), (unsigned char)epoch);
+        if (p0 <= p1) mark_subtiles(g, (unsigned int)p0, (unsigned int)p1, reinterpret_cast<unsigned char*>(tileflag), (unsigned char)epoch);
     }
     const unsigned long long mask = __ballot(changed);
     if ((threadIdx.x & 63) == 0 && v < nvec) bitmap[v >> 6] = mask;
@@ -492,7 +497,7 @@ __global__ __launch_bounds__(256) void scan_pooled_kernel(unsigned int* __restri
     }
     // mark the sub-tiles that see the changed positions
     if (ITER == 1 ? (lane & 3) == 0 && (mask >> (lane >> 2) & 1ull) : (mask >> lane & 1ull) != 0ull)
-        if (g.sty > 0) mark_subtiles(g, p, flags, (unsigned char)epoch);  // (the position-gather kernel reads the bitmap)
+        if (g.sty > 0) mark_subtiles(g, p, p, flags, (unsigned char)epoch);  // (the position-gather kernel reads the bitmap)
     __shared__ unsigned int s_ne[4];
     __shared__ unsigned long long s_mask[4];
 #pragma unroll

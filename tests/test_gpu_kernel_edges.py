@@ -168,3 +168,40 @@ def test_pooled_scan_of_a_fused_step(m, c, n):
     assert_matches(B.y_snapshot().cpu().numpy(), oracle.dense(s2, S.I8, w2, b2, old), S.I8, "last frame")
     A.destroy()
     B.destroy()
+
+
+# Few channels: a 16-byte unit covers several positions, which are marked a run at a time.  Strides beyond the filter leave
+# columns that no window reads; units cross rows; what counts as active is exact.
+@pytest.mark.parametrize("h,w,c,k,st,pad,n", [(9, 5, 3, 3, 1, 1, 2), (40, 33, 3, 11, 4, 0, 2), (12, 50, 2, 1, 3, 0, 1), (31, 30, 1, 2, 5, 1, 3), (7, 3, 5, 3, 2, 1, 2)])
+def test_active_subtiles_of_few_channels(h, w, c, k, st, pad, n):
+    import numpy as np
+    import oracle
+    from gpu_util import assert_matches, make_layer, to_device
+    seq = S.random_layer(9800 + w, S.conv_shape(h, w, c, 16, k, st, pad, 1, n=n), S.I8, T=2, frac=0.1, block=3)
+    layer = make_layer(seq, path=1, conv_kernel=1)
+    rng = np.random.default_rng(w)
+    x = np.array(seq.frames[0])
+    layer.step(to_device(x, S.I8))
+    seen = layer.stats()["active_tiles"]
+    ho, wo = (h + 2 * pad - k) // st + 1, (w + 2 * pad - k) // st + 1
+    for t in range(5):
+        x[rng.integers(0, n), rng.integers(0, h), rng.integers(0, w), rng.integers(0, c)] ^= 1
+        units = (x.reshape(-1) != np.array(seq.frames[0]).reshape(-1)) if t == 0 else (x.reshape(-1) != last.reshape(-1))
+        flat = np.zeros((units.size + 15) // 16 * 16, bool)
+        flat[:units.size] = units
+        flat = np.repeat(flat.reshape(-1, 16).any(axis=1), 16)[:units.size]  # (a position is marked with its whole unit)
+        pos = flat.reshape(n, h, w, c).any(axis=3)
+        want = np.zeros((n, (ho + 3) // 4, (wo + 3) // 4), bool)
+        for b, iy, ix in zip(*np.nonzero(pos)):
+            ys = [oy for oy in range(ho) if 0 <= iy + pad - oy * st < k]
+            xs = [ox for ox in range(wo) if 0 <= ix + pad - ox * st < k]
+            for oy in ys:
+                for ox in xs:
+                    want[b, oy // 4, ox // 4] = True
+        last = x.copy()
+        layer.step(to_device(x, S.I8))
+        now = layer.stats()["active_tiles"]
+        assert now - seen == int(want.sum()), f"step {t}"
+        seen = now
+    assert_matches(layer.y_snapshot().cpu().numpy(), oracle.dense(seq.shape, S.I8, seq.weights, seq.bias, x), S.I8, "last frame")
+    layer.destroy()
