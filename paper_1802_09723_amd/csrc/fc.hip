@@ -18,9 +18,11 @@ namespace rrm {
 
 namespace {
 
-constexpr int FCD_THREADS = 512;   // 8 wavefronts (up to 256 registers each: nothing spills)
-constexpr int FCD_CH = 8192;        // inputs of one compare round = capacity of the changed-column list in LDS
 constexpr int FCD_UN = 8;           // columns in flight per lane
+// inputs of a compare round: one 16-byte unit per thread, at most 56 KB of list (4 or 8 bytes an entry)
+constexpr int fcd_round(int dtype, int threads) {
+    return dtype == RRM_I8_I32 ? threads * 16 : (threads * 8 < 7168 ? threads * 8 : 7168);
+}
 constexpr int FCD_SEG = 64;         // bytes of a weight column one workgroup owns (4 lanes of 16 bytes)
 
 __device__ __forceinline__ float bf16_to_f32(unsigned int h) { return __uint_as_float(h << 16); }
@@ -43,26 +45,40 @@ __device__ __forceinline__ float bf16_to_f32(unsigned int h) { return __uint_as_
 // ROWS16 = g.vec_ok: rows of whole 16-byte units.  A form of its own, because the code that reads ragged rows costs the
 // others time even where it is not taken (one stream, 9216 -> 4096: int8, 25 % changing, 11.42 -> 11.36 us, bf16, 5 %,
 // 11.92 -> 11.78; the ragged rows themselves, 3945 -> 413 bf16, 7.95 -> 7.84).
-template <int DT, bool CSC, bool ROWS16>
-__global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned char* __restrict__ x_t,
+template <int DT, bool CSC, bool ROWS16, int NTH>
+__global__ __launch_bounds__(NTH) void fc_delta_kernel(const unsigned char* __restrict__ x_t,
                                                                unsigned char* x_snap,
                                                                const unsigned char* __restrict__ wT, void* y_v,
                                                                void* y_out, unsigned int* arrive, FcGeom g,
                                                                DevStats* __restrict__ stats) {
     constexpr int PV = DT == RRM_I8_I32 ? 16 : 8;
     constexpr int ESIZE = DT == RRM_I8_I32 ? 1 : 2;
-    constexpr int NCG = FCD_THREADS / 4;  // column groups: 4 lanes (64 bytes) per column
+    constexpr int NCG = NTH / 4;  // column groups: 4 lanes (64 bytes) per column
     typedef typename std::conditional<DT == RRM_I8_I32, int, float>::type val_t;
-    __shared__ unsigned short l_idx[FCD_CH];
-    __shared__ val_t l_val[FCD_CH];
-    __shared__ val_t red[FCD_THREADS / 64][4][PV];
-    __shared__ int wave_tot[FCD_THREADS / 64];
+    // An entry of the changed-column list, one LDS access: index and difference.  (int8: 9 bits of difference above the index)
+    typedef typename std::conditional<DT == RRM_I8_I32, unsigned int, uint2>::type entry_t;
+    auto entry = [](int idx, val_t d) __attribute__((always_inline)) {
+        if constexpr (DT == RRM_I8_I32) return (unsigned int)idx | (unsigned int)d << 16;
+        else return make_uint2((unsigned int)idx, __float_as_uint(d));
+    };
+    auto entry_idx = [](const entry_t& e) __attribute__((always_inline)) {
+        if constexpr (DT == RRM_I8_I32) return (int)(e & 0xFFFFu);
+        else return (int)e.x;
+    };
+    auto entry_val = [](const entry_t& e) __attribute__((always_inline)) {
+        if constexpr (DT == RRM_I8_I32) return (val_t)((int)e >> 16);
+        else return (val_t)__uint_as_float(e.y);
+    };
+    constexpr int CHU = fcd_round(DT, NTH);  // inputs of one compare round = capacity of the list
+    __shared__ entry_t list[CHU];
+    __shared__ __align__(16) val_t red[NTH / 64][4 * PV];  // the wavefronts' sums of the 4 * PV channels
+    __shared__ int wave_tot[NTH / 64];
     __shared__ unsigned int s_prev;
     extern __shared__ uint4 fc_dyn[];  // CSC: one update accumulator per output row
     val_t* ly = reinterpret_cast<val_t*>(fc_dyn);
     const int r = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (CSC)
-        for (int o = tid; o < g.c_out; o += FCD_THREADS) ly[o] = 0;  // (the first round's barriers order this)
+        for (int o = tid; o < g.c_out; o += NTH) ly[o] = 0;  // (the first round's barriers order this)
     // integer layers split long lists over gridDim.z workgroups, pass by pass (pass p of NCG * FCD_UN columns goes
     // to workgroup p % gridDim.z), and add with integer atomics: exact in any order
     const int ks = blockIdx.z, nks = gridDim.z;
@@ -175,11 +191,9 @@ __global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned ch
         }
     };
 
-    // One compare round covers FCD_CH inputs, at most one 16-byte unit per thread: the loads of round c + 1 are
+    // One compare round covers CHU inputs, at most one 16-byte unit per thread: the loads of round c + 1 are
     // issued before round c's columns are streamed, and the first KEEP rounds' new snapshots stay in registers for
     // the commit.
-    constexpr int CHU = FCD_THREADS * PV < FCD_CH ? FCD_THREADS * PV : FCD_CH;
-    static_assert(CHU / PV <= FCD_THREADS && CHU <= FCD_CH, "one unit per thread and round; the list holds a round");
     constexpr int KEEP = 2;
     const int nchunk = (g.c_in + CHU - 1) / CHU;
     uint4 keep_nw[KEEP];
@@ -214,16 +228,11 @@ __global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned ch
             if (ch + 1 < nchunk && tid * PV < CHU && base + CHU + tid * PV < g.c_in)
                 load_unit(base + CHU + tid * PV, cur_a, cur_s);
             const int cnt = __popc(mask);
-            int incl = cnt;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_up(incl, o);
-                if (lane >= o) incl += t;
-            }
+            const int incl = (int)wave_scan((unsigned int)cnt);
             if (lane == 63) wave_tot[wave] = incl;
             __syncthreads();
             int wbase = 0, btot = 0;
-            for (int w = 0; w < FCD_THREADS / 64; ++w) {
+            for (int w = 0; w < NTH / 64; ++w) {
                 const int t = wave_tot[w];
                 if (w < wave) wbase += t;
                 btot += t;
@@ -233,8 +242,7 @@ __global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned ch
 #pragma unroll
                 for (int e = 0; e < PV; ++e)
                     if (mask & (1u << e)) {
-                        l_idx[pos] = (unsigned short)(u * PV + e);
-                        l_val[pos] = dv[e];
+                        list[pos] = entry(u * PV + e, dv[e]);
                         ++pos;
                     }
             }
@@ -248,7 +256,7 @@ __global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned ch
         if (CSC) {
             // ---- this workgroup's blocks of eight listed columns, one column per wavefront ---------------------
             const unsigned int* cptr = g.csc_ptr;
-            constexpr int NW = FCD_THREADS / 64, PRE = 4;  // (PRE columns' offsets in flight per wavefront)
+            constexpr int NW = NTH / 64, PRE = 4;  // (PRE columns' offsets in flight per wavefront)
             const int kstep = (int)gridDim.x * NW;
             for (int k0 = (int)blockIdx.x * NW + wave; k0 < cnt; k0 += PRE * kstep) {
                 unsigned int p0[PRE], p1[PRE];
@@ -257,8 +265,9 @@ __global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned ch
                 for (int i = 0; i < PRE; ++i) {
                     const int k = k0 + i * kstep;
                     const bool ok = k < cnt;
-                    const int j = ok ? base + l_idx[k] : 0;
-                    d[i] = ok ? l_val[k] : (val_t)0;
+                    const entry_t en = list[ok ? k : 0];
+                    const int j = ok ? base + entry_idx(en) : 0;
+                    d[i] = ok ? entry_val(en) : (val_t)0;
                     p0[i] = ok ? cptr[j] : 0u;
                     p1[i] = ok ? cptr[j + 1] : 0u;
                 }
@@ -286,8 +295,9 @@ __global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned ch
                 if (k0 + FCD_UN * NCG <= cnt) {  // a full pass (the same branch in every thread)
 #pragma unroll
                     for (int u = 0; u < FCD_UN; ++u) {
-                        j[u] = base + l_idx[k + u * NCG];
-                        d[u] = l_val[k + u * NCG];
+                        const entry_t en = list[k + u * NCG];
+                        j[u] = base + entry_idx(en);
+                        d[u] = entry_val(en);
                     }
 #pragma unroll
                     for (int u = 0; u < FCD_UN; ++u) w[u] = *reinterpret_cast<const uint4*>(wcol + j[u] * pitch);
@@ -295,8 +305,9 @@ __global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned ch
 #pragma unroll
                     for (int u = 0; u < FCD_UN; ++u) {
                         const bool ok = k + u * NCG < cnt;
-                        j[u] = ok ? base + l_idx[k + u * NCG] : 0;
-                        d[u] = ok ? l_val[k + u * NCG] : (val_t)0;
+                        const entry_t en = list[ok ? k + u * NCG : 0];
+                        j[u] = ok ? base + entry_idx(en) : 0;
+                        d[u] = ok ? entry_val(en) : (val_t)0;
                     }
 #pragma unroll
                     for (int u = 0; u < FCD_UN; ++u)
@@ -309,36 +320,51 @@ __global__ __launch_bounds__(FCD_THREADS) void fc_delta_kernel(const unsigned ch
         if (ch + 1 < nchunk) __syncthreads();  // the list is rewritten by the next round
     }
 
-    // ---- column groups -> one sum per channel: butterfly inside the wavefront (lanes with the same `sub`), then
-    // the wavefronts in order through LDS.  The order is fixed, so fp32 results repeat from run to run.
+    // ---- column groups -> one sum per channel: inside the wavefront (lanes with the same `sub`), then the wavefronts in order
+    // through LDS.  The order is fixed, so fp32 results repeat from run to run.
     if (CSC) {
         __syncthreads();  // every wavefront's LDS adds are done
         if (total) {
             val_t* yb = static_cast<val_t*>(y_v) + (long long)b * g.c_out;
-            for (int o = tid; o < g.c_out; o += FCD_THREADS) {
+            for (int o = tid; o < g.c_out; o += NTH) {
                 const val_t v = ly[o];
                 if (v != (val_t)0) atomicAdd(yb + o, v);
             }
         }
     } else if (total || y_out) {  // (the same in every thread: the list lengths)
+        // The halves of the wavefront exchange half of their values and add, then the rows of 16 lanes half of the rest: a
+        // lane is left with PV / 4 values of its sub's channels, summed over the rows, and adds those of its row's lanes.  All
+        // in vector registers: with 4 * PV shuffles and adds through LDS here (and a shuffled prefix sum above, and index and
+        // difference in two arrays) a step of one stream, 9216 -> 4096 int8, 5 %, took 10.5 us instead of 8.3.
+        auto both = [](val_t lo, val_t hi, auto swap) __attribute__((always_inline)) {
+            const auto r = swap(__builtin_bit_cast(unsigned int, lo), __builtin_bit_cast(unsigned int, hi));
+            return __builtin_bit_cast(val_t, (unsigned int)r[0]) + __builtin_bit_cast(val_t, (unsigned int)r[1]);
+        };
+        auto swap32 = [](unsigned int a, unsigned int b) __attribute__((always_inline)) { return __builtin_amdgcn_permlane32_swap(a, b, false, false); };
+        auto swap16 = [](unsigned int a, unsigned int b) __attribute__((always_inline)) { return __builtin_amdgcn_permlane16_swap(a, b, false, false); };
+        auto ror = [](val_t v, auto ctrl) __attribute__((always_inline)) {
+            return __builtin_bit_cast(val_t, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), decltype(ctrl)::value, 0xF, 0xF, true));
+        };
+        val_t h[PV / 2], q[PV / 4];
 #pragma unroll
-        for (int e = 0; e < PV; ++e) {
-            val_t v = acc[e];
-            v += __shfl_xor(v, 4);
-            v += __shfl_xor(v, 8);
-            v += __shfl_xor(v, 16);
-            v += __shfl_xor(v, 32);
-            acc[e] = v;
+        for (int e = 0; e < PV / 2; ++e) h[e] = both(acc[e], acc[e + PV / 2], swap32);  // lower half: e, upper half: e + PV / 2
+#pragma unroll
+        for (int e = 0; e < PV / 4; ++e) {
+            val_t v = both(h[e], h[e + PV / 4], swap16);  // even rows: e, odd rows: e + PV / 4
+            v += ror(v, std::integral_constant<int, 0x124>{});  // row_ror 4
+            v += ror(v, std::integral_constant<int, 0x128>{});  // row_ror 8
+            q[e] = v;
         }
-        if (lane < 4) {
+        if ((lane & 12) == 0) {
+            val_t* r = red[wave] + sub * PV + (lane >> 5) * (PV / 2) + (lane >> 4 & 1) * (PV / 4);
 #pragma unroll
-            for (int e = 0; e < PV; ++e) red[wave][lane][e] = acc[e];
+            for (int e = 0; e < PV / 4; ++e) r[e] = q[e];
         }
         __syncthreads();
         if (tid < 4 * PV) {
             val_t sum = 0;
 #pragma unroll
-            for (int w = 0; w < FCD_THREADS / 64; ++w) sum += red[w][tid / PV][tid % PV];
+            for (int w = 0; w < NTH / 64; ++w) sum += red[w][tid];
             if (co_y < g.c_out) {
                 val_t* yp = static_cast<val_t*>(y_v) + (long long)b * g.c_out + co_y;
                 if (nks > 1) {
@@ -537,12 +563,13 @@ __global__ __launch_bounds__(FC_MAX_SPLITS * 16) void fc_reduce_kernel(const voi
 
 }  // namespace
 
-// workgroups that share the list of a 64-byte slice of a stream's channels: integer layers with long input vectors have
-// up to four while that fills more of the chip's 256 compute units (measured: pays off from about a thousand changed
-// columns; short vectors lose to the extra workgroups' compare)
+// Workgroups that share the list of a 64-byte slice of a stream's channels: two for integer layers with long input vectors,
+// where that fits the chip's 256 compute units.  Each compares the whole row, so a short list gains nothing by it: one
+// stream, 9216 -> 4096, changed 5 % / 25 % / all of the inputs: one workgroup 7.3 / 10.8 / 25.1 us, two 7.4 / 9.2 / 19.8,
+// four 8.3 / 9.1 / 18.2.  (4096 inputs, 64 slices: one workgroup is as fast at any list length)
 static int fc_list_splits(int dtype, const FcGeom& g) {
     const int ranges = (g.c_out_p * (dtype == RRM_I8_I32 ? 1 : 2) + FCD_SEG - 1) / FCD_SEG;
-    return dtype == RRM_I8_I32 && g.c_in >= 8192 ? std::max(1, std::min(4, 256 / (ranges * g.n))) : 1;
+    return dtype == RRM_I8_I32 && g.c_in >= 8192 ? std::max(1, std::min(2, NUM_CU / (ranges * g.n))) : 1;
 }
 
 bool fc_delta_writes_out(int dtype, const FcGeom& g) { return !g.csc_ptr && fc_list_splits(dtype, g) == 1; }
@@ -550,13 +577,20 @@ bool fc_delta_writes_out(int dtype, const FcGeom& g) { return !g.csc_ptr && fc_l
 hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void* wT, void* y, void* y_out,
                            unsigned int* arrive, const FcGeom& g, DevStats* stats, hipStream_t s) {
     const int esize = dtype == RRM_I8_I32 ? 1 : 2;
-    dim3 block(FCD_THREADS);
     if (y_out && !fc_delta_writes_out(dtype, g)) return hipErrorInvalidValue;
-    // the kernel's form for this layer
-    auto kern = [&]<bool CSC>() {
-        if (dtype == RRM_I8_I32) return g.vec_ok ? fc_delta_kernel<RRM_I8_I32, CSC, true> : fc_delta_kernel<RRM_I8_I32, CSC, false>;
-        return g.vec_ok ? fc_delta_kernel<RRM_BF16_F32, CSC, true> : fc_delta_kernel<RRM_BF16_F32, CSC, false>;
+    const int ranges = (g.c_out_p * esize + FCD_SEG - 1) / FCD_SEG;
+    // 1024 threads instead of 512 where a bf16 row then takes fewer compare rounds and every workgroup still has a compute
+    // unit of its own: 9216 -> 4096, 5 % changed, one stream 10.0 -> 8.6 us; four streams (512 workgroups, two of the small
+    // ones on a compute unit) 15.2 -> 17.8.  int8 rows of twice the length gained nothing (7.4 -> 7.6).
+    const auto rounds = [&](int threads) { return (g.c_in + fcd_round(dtype, threads) - 1) / fcd_round(dtype, threads); };
+    const bool wide = dtype == RRM_BF16_F32 && !g.csc_ptr && (long long)ranges * g.n <= NUM_CU && rounds(1024) < rounds(512);
+    auto form = [&]<bool CSC>() {
+        if (dtype == RRM_I8_I32) return g.vec_ok ? fc_delta_kernel<RRM_I8_I32, CSC, true, 512> : fc_delta_kernel<RRM_I8_I32, CSC, false, 512>;
+        if constexpr (!CSC)
+            if (wide) return g.vec_ok ? fc_delta_kernel<RRM_BF16_F32, CSC, true, 1024> : fc_delta_kernel<RRM_BF16_F32, CSC, false, 1024>;
+        return g.vec_ok ? fc_delta_kernel<RRM_BF16_F32, CSC, true, 512> : fc_delta_kernel<RRM_BF16_F32, CSC, false, 512>;
     };
+    dim3 block(wide ? 1024 : 512);
     if (g.csc_ptr) {
         // pruned weights: up to 64 workgroups per stream share the list (each pays c_out atomic adds at the end)
         const int nw = std::max(1, std::min(64, NUM_CU / g.n));
@@ -564,23 +598,24 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
         static std::once_flag once;
         static hipError_t attr = hipSuccess;
         std::call_once(once, [] {
-            for (const void* f : {reinterpret_cast<const void*>(&fc_delta_kernel<RRM_I8_I32, true, true>),
-                                  reinterpret_cast<const void*>(&fc_delta_kernel<RRM_I8_I32, true, false>),
-                                  reinterpret_cast<const void*>(&fc_delta_kernel<RRM_BF16_F32, true, true>),
-                                  reinterpret_cast<const void*>(&fc_delta_kernel<RRM_BF16_F32, true, false>)})
+            for (const void* f : {reinterpret_cast<const void*>(&fc_delta_kernel<RRM_I8_I32, true, true, 512>),
+                                  reinterpret_cast<const void*>(&fc_delta_kernel<RRM_I8_I32, true, false, 512>),
+                                  reinterpret_cast<const void*>(&fc_delta_kernel<RRM_BF16_F32, true, true, 512>),
+                                  reinterpret_cast<const void*>(&fc_delta_kernel<RRM_BF16_F32, true, false, 512>)})
                 if (attr == hipSuccess) attr = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, FC_CSC_MAX_LDS);
         });
         if (attr != hipSuccess) return attr;
         if (lds > (size_t)FC_CSC_MAX_LDS) return hipErrorInvalidValue;
         dim3 grid((unsigned int)nw, (unsigned int)g.n, 1u);
-        hipLaunchKernelGGL(kern.template operator()<true>(), grid, block, lds, s, (const unsigned char*)x_t, (unsigned char*)x_snap,
+        const auto kernel = form.template operator()<true>();
+        hipLaunchKernelGGL(kernel, grid, block, lds, s, (const unsigned char*)x_t, (unsigned char*)x_snap,
                            (const unsigned char*)wT, y, y_out, arrive, g, stats);
         return hipGetLastError();
     }
-    const int ranges = (g.c_out_p * esize + FCD_SEG - 1) / FCD_SEG;
     const int nks = fc_list_splits(dtype, g);
     dim3 grid((unsigned int)ranges, (unsigned int)g.n, (unsigned int)nks);
-    hipLaunchKernelGGL(kern.template operator()<false>(), grid, block, 0, s, (const unsigned char*)x_t, (unsigned char*)x_snap,
+    const auto kernel = form.template operator()<false>();
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, (const unsigned char*)x_t, (unsigned char*)x_snap,
                        (const unsigned char*)wT, y, y_out, arrive, g, stats);
     return hipGetLastError();
 }

@@ -191,6 +191,20 @@ __device__ __forceinline__ unsigned int udiv_magic(unsigned int u, unsigned int 
     const unsigned int q = __umulhi(u, magic);
     return q * d > u ? q - 1u : q;
 }
+
+// inclusive sum over the 64 lanes (every lane active)
+__device__ __forceinline__ unsigned int wave_scan(unsigned int v) {
+    auto add = [&]<int CTRL, int ROWS>() __attribute__((always_inline)) {
+        v += (unsigned int)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+    };
+    add.template operator()<0x111, 0xF>();  // row_shr 1, 2, 4, 8: within the rows of 16 lanes
+    add.template operator()<0x112, 0xF>();
+    add.template operator()<0x114, 0xF>();
+    add.template operator()<0x118, 0xF>();
+    add.template operator()<0x142, 0xA>();  // row_bcast 15, 31: the rows before
+    add.template operator()<0x143, 0xC>();
+    return v;
+}
 #endif
 
 // ---- launchers implemented in the kernel translation units ------------------------------------

@@ -14,20 +14,6 @@ namespace rrm {
 
 #ifdef __HIPCC__
 
-// inclusive sum over the 64 lanes (every lane active)
-__device__ __forceinline__ unsigned int wave_scan(unsigned int v) {
-    auto add = [&]<int CTRL, int ROWS>() __attribute__((always_inline)) {
-        v += (unsigned int)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
-    };
-    add.template operator()<0x111, 0xF>();  // row_shr 1, 2, 4, 8: within the rows of 16 lanes
-    add.template operator()<0x112, 0xF>();
-    add.template operator()<0x114, 0xF>();
-    add.template operator()<0x118, 0xF>();
-    add.template operator()<0x142, 0xA>();  // row_bcast 15, 31: the rows before
-    add.template operator()<0x143, 0xC>();
-    return v;
-}
-
 // Four wavefronts (`wave` 0 .. 3), each with a contiguous quarter of the flag array.
 struct SubtileList {
     static constexpr int BATCH = 8;  // rounds read together; the first batch stays in registers (32768 sub-tiles)

@@ -94,6 +94,19 @@ def test_fc_step_fills_the_callers_copy(ci, co, n, dt):
     run_sequence(seq, check_dense=(0,), y_out_frames=(0, 1, 2, 3), fc_batched=0)
 
 
+# Compare rounds of the FC step: int8 rows around 8192 inputs (two workgroups on a list from there), bf16 rows around 4096 and,
+# with 1024 threads, 7168; rows off the 16-byte units; channels off the 64 bytes of a workgroup; int8 differences of nine bits;
+# and more streams than leave a bf16 workgroup a compute unit of its own.
+@pytest.mark.parametrize("ci,co,n", [(4097, 40, 1), (7160, 5, 2), (7169, 72, 1), (8191, 64, 1), (8193, 100, 2), (14337, 33, 1), (16385, 20, 1), (5000, 2100, 5)])
+@pytest.mark.parametrize("dt", [S.I8, S.BF16])
+def test_fc_step_compare_rounds(ci, co, n, dt):
+    seq = S.random_layer(9900 + ci, S.fc_shape(ci, co, n=n), dt, T=3, frac=0.4)
+    if dt == S.I8:  # the last entries: from the lowest value to the highest and back
+        for t, frame in enumerate(seq.frames):
+            frame[..., -40:] = (-128, 127)[t % 2]
+    run_sequence(seq, check_dense=(), fc_batched=0)
+
+
 # The sub-tile flags carry the step's own value and are wiped a step later: what a step counts as active is what its own frame
 # changed, whatever the steps before marked.  (map, streams): flag arrays off the words of four and the vectors of 16, one
 # workgroup per flag group, one round of vectors in the work list, several, and more than stay in registers; the frames
