@@ -5,11 +5,11 @@
 // entries of the difference, and every such entry multiplies the weights that see it and is summed into the
 // outputs it touches.  Here a workgroup owns a block of consecutive input positions (and a share of the output
 // channels).  It compares x_t with the stored input for its positions (first statement of the loop), keeps the
-// difference in LDS, compacts the changed positions with one ballot, and multiplies them, as the columns of a
+// difference in LDS, compacts the changed positions with one ballot, and multiplies them, as the rows of a
 // matrix product per filter tap,
-//     Z_tap [c_out x changed positions] = W_tap [c_out x c_in] * dI [c_in x changed positions]
+//     Z_tap [changed positions x c_out] = dI [changed positions x c_in] * W_tap^T [c_in x c_out]
 // (v_mfma_i32_32x32x32_i8 / v_mfma_f32_32x32x16_bf16; weight fragments straight from memory in per-lane order, each
-// used once per workgroup), and adds column p of Z_tap into the stored projection at the output position that sees
+// used once per workgroup), and adds row p of Z_tap into the stored projection at the output position that sees
 // input position p under that tap, with atomic adds: several input positions meet in one output, and integer adds
 // commute (bit-exact); fp32 adds are applied in arrival order (within the layer's tolerance, not bit-reproducible).
 // The work is exactly proportional to the number of changed input positions (Table 1 / Eq. 6 at position
@@ -53,6 +53,16 @@ constexpr int ST = 256;  // threads
 // Workgroup barrier that publishes LDS contents only (__syncthreads() would also wait for the answer of the arrival counter)
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// A uniform value that stays in a scalar register from here on
+template <typename T>
+__device__ __forceinline__ T kept(T v) {
+    asm volatile("" : "+s"(v));
+    return v;
+}
+
+// difference planes in LDS (bf16 with one term: the second one holds the stored input until the difference is formed)
+constexpr int scat_planes(int dtype) { return dtype == RRM_BF16_F32 ? 2 : 1; }
+
 template <int DT, int TERMS>
 __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restrict__ x_t, uint4* x_snap,
                                                           const uint4* __restrict__ wsc, void* y_v, ScatGeom g,
@@ -60,231 +70,307 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
     typedef typename std::conditional<DT == RRM_I8_I32, v16i, v16f>::type acc_t;
     typedef typename std::conditional<DT == RRM_I8_I32, int, float>::type sc_t;
     constexpr int UPT = SCAT_UPT;  // 16-byte units per thread at most
-    // LDS: difference planes [TERMS][PB][U] x 16 bytes, then one 16-byte block of zeros
+    // LDS: difference planes [scat_planes][PB][U] x 16 bytes, then one 16-byte block of zeros
     extern __shared__ uint4 smem[];
     uint4* dl = smem;
     const int plane = g.PB * g.U;  // units per plane
-    uint4* zero_unit = dl + TERMS * plane;
+    uint4* zero_unit = dl + scat_planes(DT) * plane;
     __shared__ unsigned int s_flag[64];
-    __shared__ int s_list[64];
-    __shared__ int s_cnt;
+    __shared__ int s_list[ST / 64][64];  // (every wavefront makes its own list: nothing to wait for)
+    __shared__ __align__(16) int s_out[ST / 64][2][32];  // output offsets of an item's rows, or -1
     __shared__ unsigned int s_prev;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const long long p0 = (long long)blockIdx.x * g.PB;             // first position of the block
-    const int npos = (int)min((long long)g.PB, g.npos_total - p0);  // positions in it
+    const unsigned int p0 = blockIdx.x * (unsigned int)g.PB;                     // first position of the block
+    const int npos = min(g.PB, (int)((unsigned int)g.npos_total - p0));          // positions in it
     const int nunits = npos * g.U;
-    const long long u0 = p0 * g.U;  // first 16-byte unit of the block (positions are contiguous in x)
+    const size_t u0 = (size_t)p0 * g.U;  // first 16-byte unit of the block (positions are contiguous in x)
     DevStats* stats = stats_base + (blockIdx.x & (STAT_SLOTS - 1));
     sc_t* y = static_cast<sc_t*>(y_v);
 
+    // ---- both frames' units, all in flight together ------------------------------------------------------------------
+    uint4 a[UPT], b[UPT];
+#pragma unroll
+    for (int i = 0; i < UPT; ++i) {
+        if (ST * i >= nunits) break;
+        const int v = min(tid + ST * i, nunits - 1);
+        a[i] = x_t[u0 + v];
+        b[i] = x_snap[u0 + v];
+    }
     if (tid < 64) s_flag[tid] = 0u;
     if (tid == 0) *zero_unit = make_uint4(0, 0, 0, 0);
+    const bool counts = blockIdx.y == 0;  // statistics: one workgroup per position block
+    // what the rest of the kernel needs of its arguments arrives while the units do
+    const int U = kept(g.U), ug = kept(g.ug), nk = kept(g.nk), nkp = kept(g.nkp), ntaps = kept(g.ntaps), ncb = kept(g.ncb), kw = kept(g.kw),
+              og = kept(g.og), c_out = kept(g.c_out), nitems = kept(g.npair * g.ntaps * g.nkp), cs = kept(g.cs), pad = kept(g.pad),
+              stride = kept(g.stride), ho = kept(g.ho), wo = kept(g.wo), w_in = kept(g.w), hw = kept(g.h * g.w);
+    const unsigned int magic_U = kept(g.magic_U), magic_hw = kept(g.magic_hw), magic_w = kept(g.magic_w), magic_nkp = kept(g.magic_nkp),
+                       magic_taps = kept(g.magic_taps), magic_ncb = kept(g.magic_ncb), magic_kw = kept(g.magic_kw),
+                       magic_stride = kept(g.magic_stride);
     lds_barrier();
 
-    // ---- difference with the stored input (Algorithm 1), kept in LDS; new snapshot values in registers -----------
-    uint4 keep[UPT];
-    unsigned int keep_mask = 0;
+    // ---- difference with the stored input (Algorithm 1), into LDS -------------------------------------------------------
+    unsigned int keep_mask = 0;        // units to commit
+    unsigned long long trunc_mask = 0;  // bf16: their entries that keep the stored value, eight bits a unit
     unsigned int nelem = 0, nunit = 0, ntrunc = 0;
     float tsq = 0.f;
 #pragma unroll
     for (int i = 0; i < UPT; ++i) {
+        if (ST * i >= nunits) break;
         const int v = tid + ST * i;
-        if (v >= nunits) break;
-        const uint4 a = x_t[u0 + v], b = x_snap[u0 + v];
-        uint4 d0v = make_uint4(0, 0, 0, 0), d1v = d0v;
-        bool changed = ((a.x ^ b.x) | (a.y ^ b.y) | (a.z ^ b.z) | (a.w ^ b.w)) != 0u;
-        if (changed) {
-            const unsigned int aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
-            unsigned int dw[4], lw[4] = {0u, 0u, 0u, 0u}, sw[4] = {a.x, a.y, a.z, a.w};
-            if (DT == RRM_I8_I32) {
-                const unsigned int H = 0x80808080u;
-                unsigned int ovf = 0;
+        const unsigned int aw[4] = {a[i].x, a[i].y, a[i].z, a[i].w}, bw[4] = {b[i].x, b[i].y, b[i].z, b[i].w};
+        const bool changed = v < nunits && ((aw[0] ^ bw[0]) | (aw[1] ^ bw[1]) | (aw[2] ^ bw[2]) | (aw[3] ^ bw[3])) != 0u;
+        if (DT == RRM_I8_I32) {
+            const unsigned int H = 0x80808080u;
+            unsigned int dw[4], ovf = 0;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    // byte-wise wrapping subtraction and its signed-overflow mask
-                    const unsigned int d = ((aw[k] | H) - (bw[k] & ~H)) ^ ((aw[k] ^ ~bw[k]) & H);
-                    ovf |= (aw[k] ^ bw[k]) & (aw[k] ^ d) & H;
-                    dw[k] = d;
-                    const unsigned int z = aw[k] ^ bw[k];
-                    nelem += __popc((((z & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | z) & H);
-                }
-                if (ovf) atomicOr(&stats->range_error, 1u);
-            } else {
-                // (truncation threshold, Sec. 3.4 "Improving sparsity": an entry whose difference is below g.eps is
-                // neither applied nor committed; eps = 0 is the exact method.)  The difference is formed in fp32 and
-                // carried as a bf16 head and a bf16 tail.
-                bool any_pass = false;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    unsigned int hi2 = 0, lo2 = 0, sn2 = 0;
-#pragma unroll
-                    for (int e = 0; e < 2; ++e) {
-                        const unsigned int xa = (aw[k] >> (16 * e)) & 0xFFFFu, xb = (bw[k] >> (16 * e)) & 0xFFFFu;
-                        const float d = bf16_to_f32(xa) - bf16_to_f32(xb);
-                        const bool differ = xa != xb;
-                        const bool trunc = differ && fabsf(d) < g.eps;
-                        const bool pass = differ && !trunc;
-                        any_pass |= pass;
-                        nelem += pass ? 1u : 0u;
-                        ntrunc += trunc ? 1u : 0u;
-                        tsq += trunc ? d * d : 0.f;
-                        const unsigned int hi = pass ? f32_to_bf16(d) : 0u;
-                        const unsigned int lo = pass && TERMS == 2 ? f32_to_bf16(d - bf16_to_f32(hi)) : 0u;
-                        hi2 |= hi << (16 * e);
-                        lo2 |= lo << (16 * e);
-                        sn2 |= (pass ? xa : xb) << (16 * e);
-                    }
-                    dw[k] = hi2;
-                    lw[k] = lo2;
-                    sw[k] = sn2;
-                }
-                changed = any_pass;
+            for (int k = 0; k < 4; ++k) {
+                // byte-wise wrapping subtraction and its signed-overflow mask
+                const unsigned int d = ((aw[k] | H) - (bw[k] & ~H)) ^ ((aw[k] ^ ~bw[k]) & H);
+                ovf |= (aw[k] ^ bw[k]) & (aw[k] ^ d) & H;
+                dw[k] = d;
             }
+            if (v < nunits) dl[v] = make_uint4(dw[0], dw[1], dw[2], dw[3]);
             if (changed) {
-                d0v = make_uint4(dw[0], dw[1], dw[2], dw[3]);
-                d1v = make_uint4(lw[0], lw[1], lw[2], lw[3]);
-                keep[i] = make_uint4(sw[0], sw[1], sw[2], sw[3]);
-                keep_mask |= 1u << i;
-                ++nunit;
-                s_flag[v / g.U] = 1u;  // (every writer stores the same value)
-            }
-        }
-        dl[v] = d0v;
-        if (TERMS == 2) dl[plane + v] = d1v;
-    }
-    lds_barrier();
-    // every read of the stored input by this workgroup is done
-    const bool shared_block = gridDim.y > 1;
-    // (thread 0 keeps the answer to the end: stored at once, it would hold up the list by a memory round trip.  Weights are
-    // fetched after the list, by the blocks with a change only: fetched ahead of the compare, with all of the thread's units of
-    // both frames, they cost more than they hid; one stream, bf16 3 x 3: 20 x 20 x 96, 3 % of the positions changing, 7.95 -> 8.4 us,
-    // 14 x 14 x 256, 5 %, 10.5 -> 11.1, 7 x 7 x 512 with no change 8.2 -> 8.95; only 7 x 7 x 512 at 5 % gained,
-    // 13.5 -> 13.1, and 10 x 10 x 320 over 4 streams at 10 %, 25.4 -> 24.1)
-    unsigned int arrived_before = 0;
-    if (shared_block && tid == 0) arrived_before = atomicAdd(&g.arrive[blockIdx.x], 1u);
-
-    // ---- changed positions of the block -> column list (one ballot: a block has at most 64 positions) -----------
-    if (wave == 0) {
-        const bool f = lane < npos && s_flag[lane] != 0u;
-        const unsigned long long m = __ballot(f);
-        if (f) s_list[__popcll(m & ((1ull << lane) - 1ull))] = lane;
-        if (lane == 0) s_cnt = (int)__popcll(m);
-    }
-    lds_barrier();
-    const int cnt = s_cnt;
-
-    // ---- statistics (one workgroup per position block) --------------------------------------------------------------
-    if (blockIdx.y == 0) {
+                if (ovf) atomicOr(&stats->range_error, 1u);
+                if (counts)
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            nelem += __shfl_xor(nelem, o);
-            nunit += __shfl_xor(nunit, o);
-            if (DT == RRM_BF16_F32) {
-                ntrunc += __shfl_xor(ntrunc, o);
-                tsq += __shfl_xor(tsq, o);
+                    for (int k = 0; k < 4; ++k) {
+                        const unsigned int z = aw[k] ^ bw[k];
+                        nelem += __popc((((z & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | z) & H);
+                    }
+                s_flag[udiv_magic(v, U, magic_U)] = 1u;  // (every writer stores the same value)
+                keep_mask |= 1u << i;
             }
-        }
-        if (lane == 0) {
-            if (nunit) {
-                atomicAdd(&stats->changed_elems, (unsigned long long)nelem);
-                atomicAdd(&stats->changed_units, (unsigned long long)nunit);
+        } else {
+            // a unit that differs lies in the planes as it is until this thread forms its difference, below
+            if (v < nunits) {
+                dl[v] = changed ? a[i] : make_uint4(0, 0, 0, 0);
+                dl[plane + v] = changed ? b[i] : make_uint4(0, 0, 0, 0);
             }
-            if (DT == RRM_BF16_F32 && ntrunc) {
-                atomicAdd(&stats->truncated_elems, (unsigned long long)ntrunc);
-                atomicAdd(&stats->truncated_sumsq, (double)tsq);
-            }
-        }
-        if (tid == 0) {
-            if (cnt) atomicAdd(&stats->active_tiles, (unsigned long long)cnt);
-            if (blockIdx.x == 0) {  // one launch = one delta step
-                atomicAdd(&stats_base->delta_steps, 1ull);
-                atomicAdd(&stats_base->total_tiles, (unsigned long long)g.npos_total);
-                if (g.touched_all) g.touched_all[0] = 1u;  // this path keeps no flags of what it wrote: "everything"
-            }
+            keep_mask |= changed ? 1u << i : 0u;
         }
     }
+    if (DT == RRM_BF16_F32) {
+        // (truncation threshold, Sec. 3.4 "Improving sparsity": an entry whose difference is below g.eps is neither applied
+        // nor committed; eps = 0 is the exact method.)  The difference is formed in fp32 and carried as a bf16 head and a
+        // bf16 tail.  A loop over the thread's units that differ: unrolled over all of them it was 2400 instructions, most of
+        // them fetched for nothing, and the units' loads waited for each other (7 x 7 x 512, one stream, 5 %: 13.3 us a step,
+        // and 9.6 with this loop, one list per wavefront, no integer division and the commit ahead of the products).
+        for (unsigned int m = keep_mask; m; m &= m - 1) {
+            const int i = __ffs(m) - 1, v = tid + ST * i;
+            const uint4 ua = dl[v], ub = dl[plane + v];
+            const unsigned int aw[4] = {ua.x, ua.y, ua.z, ua.w}, bw[4] = {ub.x, ub.y, ub.z, ub.w};
+            unsigned int dw[4], lw[4], passed = 0, tmask = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                unsigned int hi2 = 0, lo2 = 0;
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const unsigned int xa = (aw[k] >> (16 * e)) & 0xFFFFu, xb = (bw[k] >> (16 * e)) & 0xFFFFu;
+                    const float d = bf16_to_f32(xa) - bf16_to_f32(xb);
+                    const bool differ = xa != xb;
+                    const bool trunc = differ && fabsf(d) < g.eps;
+                    const bool pass = differ && !trunc;
+                    passed += pass ? 1u : 0u;
+                    tmask |= trunc ? 1u << (2 * k + e) : 0u;
+                    tsq += trunc ? d * d : 0.f;
+                    const unsigned int hi = pass ? f32_to_bf16(d) : 0u;
+                    const unsigned int lo = pass && TERMS == 2 ? f32_to_bf16(d - bf16_to_f32(hi)) : 0u;
+                    hi2 |= hi << (16 * e);
+                    lo2 |= lo << (16 * e);
+                }
+                dw[k] = hi2;
+                lw[k] = lo2;
+            }
+            dl[v] = make_uint4(dw[0], dw[1], dw[2], dw[3]);
+            if (TERMS == 2) dl[plane + v] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
+            nelem += passed;
+            ntrunc += __popc(tmask);
+            trunc_mask |= (unsigned long long)tmask << (8 * i);
+            if (passed)
+                s_flag[udiv_magic(v, U, magic_U)] = 1u;
+            else
+                keep_mask &= ~(1u << i);
+        }
+    }
+    nunit = __popc(keep_mask);
+    // the wavefront's first item, decoded while others compare
+    int item = (int)blockIdx.y + wave * cs;
+    int grp = 0, cb = 0, ky = 0, kx = 0, k0 = 0;
+    const uint4* wp = wsc;
+    auto decode = [&]() __attribute__((always_inline)) {
+        const int pt = (int)udiv_magic(item, nkp, magic_nkp), pair = (int)udiv_magic(pt, ntaps, magic_taps), tap = pt - pair * ntaps;
+        k0 = (item - pt * nkp) * 8;
+        grp = (int)udiv_magic(pair, ncb, magic_ncb);
+        cb = pair - grp * ncb;
+        ky = (int)udiv_magic(tap, kw, magic_kw);
+        kx = tap - ky * kw;
+        wp = wsc + ((size_t)pt * nk + k0) * 64 + lane;
+    };
+    decode();
+    lds_barrier();
 
-    // ---- the products: work items (channel block of a group, tap, part of the K range of at most 8 steps).  A
-    // workgroup takes items blockIdx.y, + gridDim.y, ... and deals them to its wavefronts; a wavefront has an item's
-    // (at most 8) weight fragments in flight together, multiplies, and applies its columns.
+    // ---- changed positions of the block (at most 64): the wavefront's list -----------------------------------------
+    const bool flag = lane < npos && s_flag[lane] != 0u;
+    const unsigned long long found = __ballot(flag);
+    const int cnt = (int)__popcll(found);
     if (cnt > 0) {
+        // Every read of the stored input by this workgroup is done.  (The workgroups that share a block see the same list, and
+        // without a changed position there is nothing to commit: they don't count.)
+        const bool shared_block = cs > 1;
+        unsigned int arrived_before = 0;
+        if (shared_block && tid == 0) arrived_before = atomicAdd(&g.arrive[blockIdx.x], 1u);
+        if (flag) s_list[wave][__popcll(found & ((1ull << lane) - 1ull))] = lane;
+
+        // ---- the products: work items (channel block of a group, tap, part of the K range of at most 8 steps).  A
+        // workgroup takes items blockIdx.y, + cs, ... and deals them to its wavefronts; a wavefront has an item's
+        // (at most 8) weight fragments in flight together, multiplies, and adds its rows.
+        uint4 wv[8];
+        auto fetch = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (k0 + k < nk) wv[k] = wp[(size_t)k * 64];
+        };
+        if (item < nitems) fetch();
         const int n = lane & 31, khalf = lane >> 5;
         const int ntile = (cnt + 31) >> 5;  // 1 or 2
-        // this lane's columns: block-local position, stream, image coordinates
+        // this lane's positions: block-local position, stream, image coordinates
         int pl[2], cbs[2], ciy[2], cix[2];
         bool cok[2];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             const int ci = t * 32 + n;
             cok[t] = t < ntile && ci < cnt;
-            pl[t] = cok[t] ? s_list[ci] : 0;
-            const long long P = p0 + pl[t];
-            cbs[t] = (int)(P / ((long long)g.h * g.w));
-            const int r = (int)(P - (long long)cbs[t] * g.h * g.w);
-            ciy[t] = r / g.w;
-            cix[t] = r - ciy[t] * g.w;
+            pl[t] = cok[t] ? s_list[wave][ci] : 0;
+            const unsigned int P = p0 + pl[t];
+            cbs[t] = (int)udiv_magic(P, hw, magic_hw);
+            const unsigned int r = P - (unsigned int)cbs[t] * hw;
+            ciy[t] = (int)udiv_magic(r, w_in, magic_w);
+            cix[t] = (int)r - ciy[t] * w_in;
         }
-        const int nitems = g.npair * g.ntaps * g.nkp;
-        for (int item = (int)blockIdx.y + wave * (int)gridDim.y; item < nitems; item += (ST / 64) * (int)gridDim.y) {
-            const int pt = item / g.nkp, kp = item - pt * g.nkp;
-            const int pair = pt / g.ntaps, tap = pt - pair * g.ntaps;
-            const int grp = pair / g.ncb, cb = pair - grp * g.ncb;
-            const int ky = tap / g.kw, kx = tap - ky * g.kw;
-            acc_t acc[2];
+        // ---- commit the stored input (only where a difference was applied), while the weights arrive: at the end the answer of
+        // the arrival counter would be waited for behind all of the outputs' atomic adds
+        bool last = true;
+        if (shared_block) {
+            if (tid == 0) s_prev = arrived_before;
+            lds_barrier();
+            last = s_prev == (unsigned int)cs - 1u;
+            if (last && tid == 0) g.arrive[blockIdx.x] = 0u;
+        }
+        if (last) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[t][r] = 0;
-            const int k0 = kp * 8;
-            const uint4* wp = wsc + ((size_t)(pair * g.ntaps + tap) * g.nk + k0) * 64 + lane;
-            const int ub = grp * g.ug;  // first unit of the group within a position
-            uint4 a[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if (k0 + k < g.nk) a[k] = wp[(size_t)k * 64];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                if (k0 + k >= g.nk) break;
-                const int chunk = 2 * (k0 + k) + khalf;
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    if (t >= ntile) break;
-                    const uint4* bp = chunk < g.ug ? dl + (pl[t] * g.U + ub + chunk) : zero_unit;
-                    acc[t] = mma(a[k], *bp, acc[t]);
-                    if (TERMS == 2) acc[t] = mma(a[k], chunk < g.ug ? bp[plane] : *zero_unit, acc[t]);
+            for (int i = 0; i < UPT; ++i) {
+                if (ST * i >= nunits) break;
+                if (!(keep_mask & (1u << i))) continue;
+                uint4 nw = a[i];
+                const unsigned int tm = (unsigned int)(trunc_mask >> (8 * i)) & 0xFFu;
+                if (DT == RRM_BF16_F32 && tm) {
+                    auto pick = [&](unsigned int x, unsigned int sn, int k) __attribute__((always_inline)) {
+                        const unsigned int old = (tm >> (2 * k) & 1u ? 0xFFFFu : 0u) | (tm >> (2 * k + 1) & 1u ? 0xFFFF0000u : 0u);
+                        return (x & ~old) | (sn & old);
+                    };
+                    nw = make_uint4(pick(a[i].x, b[i].x, 0), pick(a[i].y, b[i].y, 1), pick(a[i].z, b[i].z, 2), pick(a[i].w, b[i].w, 3));
                 }
+                x_snap[u0 + tid + ST * i] = nw;
             }
-            // column p of this tap's product belongs to the output position that sees input position p under the tap
+        }
+        while (item < nitems) {
+            acc_t acc[2];
+            const int ub = grp * ug;  // first unit of the group within a position
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                if (!cok[t]) continue;
-                const int ty = ciy[t] + g.pad - ky, tx = cix[t] + g.pad - kx;
-                if (ty < 0 || tx < 0) continue;
-                const int oy = ty / g.stride, ox = tx / g.stride;
-                if (oy * g.stride != ty || ox * g.stride != tx || oy >= g.ho || ox >= g.wo) continue;
-                sc_t* yp = y + ((size_t)((cbs[t] * g.ho + oy) * g.wo + ox)) * g.c_out + grp * g.og + cb * 32;
+                if (t >= ntile) break;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int c = 8 * (r >> 2) + 4 * khalf + (r & 3);
-                    const sc_t v = acc[t][r];
-                    if (cb * 32 + c < g.og && v != (sc_t)0) atomicAdd(yp + c, v);
+                for (int r = 0; r < 16; ++r) acc[t][r] = 0;
+                // the tile's operands, in flight together (a read ahead of each product was waited for each time)
+                uint4 op[TERMS][8];
+                const uint4* bp = dl + (pl[t] * U + ub + 2 * k0 + khalf);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const bool ok = 2 * (k0 + k) + khalf < ug;  // (units that are not there: zeros)
+                    op[0][k] = *(ok ? bp + 2 * k : zero_unit);
+                    if (TERMS == 2) op[TERMS - 1][k] = *(ok ? bp + plane + 2 * k : zero_unit);
                 }
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+#pragma unroll
+                    for (int e = 0; e < TERMS; ++e) asm volatile("" : "+v"(op[e][k].x), "+v"(op[e][k].y), "+v"(op[e][k].z), "+v"(op[e][k].w));
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    if (k0 + k >= nk) break;
+                    acc[t] = mma(op[0][k], wv[k], acc[t]);
+                    if (TERMS == 2) acc[t] = mma(op[TERMS - 1][k], wv[k], acc[t]);
+                }
+            }
+            // Row p of this tap's product belongs to the output position that sees input position p under the tap: the lanes work
+            // out one position each, and read the four of a register group together.  The lanes of an add are 32 channels of
+            // two positions, whole cache lines.  (With the operands the other way round, 32 positions and two channels: bf16
+            // 3 x 3, one stream, 14 x 14 x 256, 5 / 25 % changed, 9.2 / 13.7 us instead of 7.4 / 8.4; 10 x 10 x 320, four
+            // streams, 10 %, 23.8 instead of 11.4; int8 5 x 5, 27 x 27, 96 -> 256, 10 %, 15.3 instead of 7.2.)
+            const int c = cb * 32 + n;
+            sc_t* yg = y + grp * og + c;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                if (t >= ntile) break;
+                const int ty = ciy[t] + pad - ky, tx = cix[t] + pad - kx;
+                const int oy = (int)udiv_magic(ty, stride, magic_stride), ox = (int)udiv_magic(tx, stride, magic_stride);
+                const bool hit = cok[t] && ty >= 0 && tx >= 0 && oy * stride == ty && ox * stride == tx && oy < ho && ox < wo;
+                if (khalf == 0) s_out[wave][t][n] = hit ? ((cbs[t] * ho + oy) * wo + ox) * c_out : -1;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                if (t >= ntile) break;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int4 o4 = *reinterpret_cast<const int4*>(&s_out[wave][t][8 * q + 4 * khalf]);
+                    const int o[4] = {o4.x, o4.y, o4.z, o4.w};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const sc_t v = acc[t][4 * q + r];
+                        if (o[r] >= 0 && c < og && v != (sc_t)0) atomicAdd(yg + o[r], v);
+                    }
+                }
+            }
+            item += (ST / 64) * cs;
+            if (item < nitems) {
+                decode();
+                fetch();
             }
         }
     }
 
-    // ---- commit the stored input (only where a difference was applied) ---------------------------------------------
-    if (shared_block) {
-        if (tid == 0) s_prev = arrived_before;
-        __syncthreads();
-        if (s_prev != gridDim.y - 1u) return;
-        if (tid == 0) g.arrive[blockIdx.x] = 0u;
+    // ---- statistics ---------------------------------------------------------------------------------------------------
+    if (!counts) return;
+    if (__any(nunit != 0)) {
+        const unsigned int both = wave_scan(nelem | nunit << 16);  // (at most 8192 and 512 a wavefront)
+        if (lane == 63) {
+            atomicAdd(&stats->changed_elems, (unsigned long long)(both & 0xFFFFu));
+            atomicAdd(&stats->changed_units, (unsigned long long)(both >> 16));
+        }
     }
+    if (DT == RRM_BF16_F32 && __any(ntrunc != 0)) {
 #pragma unroll
-    for (int i = 0; i < UPT; ++i)
-        if (keep_mask & (1u << i)) x_snap[u0 + tid + ST * i] = keep[i];
+        for (int o = 32; o > 0; o >>= 1) {
+            ntrunc += __shfl_xor(ntrunc, o);
+            tsq += __shfl_xor(tsq, o);
+        }
+        if (lane == 0) {
+            atomicAdd(&stats->truncated_elems, (unsigned long long)ntrunc);
+            atomicAdd(&stats->truncated_sumsq, (double)tsq);
+        }
+    }
+    if (tid == 0) {
+        if (cnt) atomicAdd(&stats->active_tiles, (unsigned long long)cnt);
+        if (blockIdx.x == 0) {  // one launch = one delta step
+            atomicAdd(&stats_base->delta_steps, 1ull);
+            atomicAdd(&stats_base->total_tiles, (unsigned long long)g.npos_total);
+            if (g.touched_all) g.touched_all[0] = 1u;  // this path keeps no flags of what it wrote: "everything"
+        }
+    }
 }
 
 }  // namespace
@@ -294,7 +380,7 @@ hipError_t launch_conv_scatter(int dtype, int terms, const void* x_t, void* x_sn
     const long long nblk = (g.npos_total + g.PB - 1) / g.PB;
     dim3 grid((unsigned int)nblk, (unsigned int)g.cs);
     const int t = dtype == RRM_BF16_F32 ? terms : 1;
-    const size_t lds = ((size_t)t * g.PB * g.U + 1) * 16;
+    const size_t lds = ((size_t)scat_planes(dtype) * g.PB * g.U + 1) * 16;
     const uint4* xt = static_cast<const uint4*>(x_t);
     uint4* xs = static_cast<uint4*>(x_snap);
     const uint4* w = static_cast<const uint4*>(wsc);

@@ -509,7 +509,7 @@ rrm_status setup_scatter(rrm_layer* L, const std::vector<unsigned char>& w) {
     // positions per block: the block's units fit the threads' registers (SCAT_UPT each) and, times the terms, 64 KB
     g.PB = 0;
     for (int pb : {64, 32, 16, 8})
-        if (pb * g.U <= 256 * SCAT_UPT && terms * pb * g.U <= 4000) {
+        if ((pb < 64 || terms == 1) && pb * g.U <= 256 * SCAT_UPT && terms * pb * g.U <= 4000) {
             g.PB = pb;
             break;
         }
@@ -521,6 +521,8 @@ rrm_status setup_scatter(rrm_layer* L, const std::vector<unsigned char>& w) {
     g.nkp = (g.nk + 7) / 8;
     const long long items = (long long)g.npair * g.ntaps * g.nkp;
     g.cs = (int)std::max(1ll, std::min((items + 3) / 4, (2ll * NUM_CU + nblk - 1) / nblk));
+    g.magic_U = magic_of(g.U); g.magic_hw = magic_of(g.h * g.w); g.magic_w = magic_of(g.w); g.magic_nkp = magic_of(g.nkp);
+    g.magic_taps = magic_of(g.ntaps); g.magic_ncb = magic_of(g.ncb); g.magic_kw = magic_of(g.kw); g.magic_stride = magic_of(g.stride);
     std::vector<unsigned char> pack((size_t)g.npair * g.ntaps * g.nk * 64 * 16, 0);
     const int per_vec = 16 / es;
     for (int pair = 0; pair < g.npair; ++pair)
@@ -539,12 +541,21 @@ rrm_status setup_scatter(rrm_layer* L, const std::vector<unsigned char>& w) {
     if ((st = dalloc((size_t)nblk * sizeof(unsigned int), (void**)&L->sc_arrive)) != RRM_OK) return st;
     g.arrive = L->sc_arrive;
     L->scat_ok = true;
-    // Automatic: layers with few positions in all (one stream of a small map).  Two dependent launches and the per-workgroup
-    // set-up of the tile kernels then cost more than the step's work, as long as about a tenth of the positions change (kernel us,
-    // bf16 3 x 3, scatter against scan + tile: 28 x 28 x 128 at 5 / 10 / 25 % 11.9 / 13.4 / 17.4 and 14.1 / 14.1 / 14.2; 14 x 14 x 256
-    // 11.5 / 13.0 / 15.4 and 15.2 / 15.3 / 15.5; 7 x 7 x 512 14.2 / 18.5 / 24.5 and 17.7 / 17.6 / 18.2; int8 is ahead up to 25 %).
-    // 56 x 56 x 64, 3136 positions: 11.2 / 14.6 / 22.8 and 13.5 / 13.6 / 13.8.
-    L->scat_auto = g.npos_total <= 1024;
+    // Automatic: layers of few output adds.  Two dependent launches and the per-workgroup set-up of the tile kernels cost more
+    // there than the step's work; what the scatter pays more for is its adds into the projection, one per changed position, tap,
+    // output channel and part of K.  us a step, scatter against scan + tile, at 5 / 10 / 25 / 50 % changed (the millions: the
+    // adds if all changed; calls from the host cannot follow each other in less than 7):
+    //   bf16 3 x 3  28 x 28 x 128         0.9   7.5 /  7.6 /  7.7 /  8.7   11.6 / 11.7 / 11.9 / 12.0
+    //   bf16 3 x 3  14 x 14 x 256         0.9   7.1 /  7.3 /  8.5 /  9.9   12.9 / 12.9 / 13.1 / 13.2
+    //   bf16 3 x 3  32 x 32 x 256         4.7  10.9 / 12.5 / 15.0 / 18.5   13.4 / 13.6 / 13.8 / 14.1
+    //   bf16 3 x 3  32 x 32 x 512        18.9  42.2 / 46.0 / 49.0 / 57.0   21.5 / 22.5 / 23.3 / 24.5
+    //   int8 5 x 5  27 x 27, 96 -> 256    4.7   7.2 /  7.4 /  9.9 / 13.3   10.8 / 10.8 / 10.9 / 11.0
+    //   int8 3 x 3  28 x 28 x 96, n = 8   5.4   7.5 /  7.6 /  9.9 / 13.1   13.1 / 13.4 / 14.4 / 15.7
+    //   int8 5 x 5  27 x 27, n = 4       18.7  10.5 / 11.4 / 19.6 / 29.0   13.2 / 13.2 / 14.2 / 18.0
+    // bf16 layers of more than 1024 positions stay on the tiles whatever they would gain: fp32 adds round once per tap and in
+    // the order of their arrival, sums of the tile kernel once and in a fixed order.
+    const long long adds = g.npos_total * g.ntaps * s.c_out * g.nkp;
+    L->scat_auto = adds <= 6ll << 20 && (L->dtype == RRM_I8_I32 || g.npos_total <= 1024);
     return RRM_OK;
 }
 

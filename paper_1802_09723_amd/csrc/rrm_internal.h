@@ -158,6 +158,7 @@ struct ScatGeom {
     int cs;              // work-item splits: workgroups per position block
     long long npos_total;  // n * h * w
     float eps;           // bf16: truncation threshold of the difference (0 = exact)
+    unsigned int magic_U, magic_hw, magic_w, magic_nkp, magic_taps, magic_ncb, magic_kw, magic_stride;  // reciprocals
     unsigned int* arrive;       // one word per position block (used when cs > 1; rearmed by the kernel)
     unsigned int* touched_all;  // device word set by every step of this path: "treat every output as written"
 };

@@ -107,6 +107,21 @@ def test_fc_step_compare_rounds(ci, co, n, dt):
     run_sequence(seq, check_dense=(), fc_batched=0)
 
 
+# The single-launch scatter path: blocks of 8 .. 64 positions (the last one short), one workgroup per block and several, one
+# tile of 32 listed positions and two, units off the pairs of a K step, several parts of K, channels off the blocks of 32,
+# strides that skip positions, groups; a few positions change, then all of them, then none.
+@pytest.mark.parametrize("h,w,ci,co,k,st,pad,g,n", [
+    (8, 8, 16, 16, 3, 1, 1, 1, 1), (5, 13, 48, 33, 3, 1, 1, 1, 1), (13, 5, 80, 31, 3, 2, 1, 1, 3), (9, 7, 144, 70, 1, 1, 0, 1, 2), (9, 9, 288, 40, 3, 1, 1, 2, 1),
+    (6, 6, 512, 64, 3, 1, 1, 1, 1), (4, 4, 1024, 20, 3, 3, 2, 1, 1), (40, 37, 16, 16, 5, 1, 2, 1, 1), (61, 3, 64, 96, 3, 2, 0, 4, 7),
+])
+@pytest.mark.parametrize("dt", [S.I8, S.BF16])
+def test_scatter_path_edges(h, w, ci, co, k, st, pad, g, n, dt):
+    seq = S.random_layer(9800 + h + ci, S.conv_shape(h, w, ci, co, k, st, pad, g, n=n), dt, T=5, frac=0.1, block=2)
+    seq.frames[2] = S.random_layer(9850 + h + ci, seq.shape, dt, T=1, frac=0.1, block=2).frames[0]
+    seq.frames[3] = seq.frames[2].copy()
+    run_sequence(seq, check_dense=(), path=3)
+
+
 # The sub-tile flags carry the step's own value and are wiped a step later: what a step counts as active is what its own frame
 # changed, whatever the steps before marked.  (map, streams): flag arrays off the words of four and the vectors of 16, one
 # workgroup per flag group, one round of vectors in the work list, several, and more than stay in registers; the frames
