@@ -63,7 +63,10 @@ __device__ __forceinline__ T kept(T v) {
 // difference planes in LDS (bf16 with one term: the second one holds the stored input until the difference is formed)
 constexpr int scat_planes(int dtype) { return dtype == RRM_BF16_F32 ? 2 : 1; }
 
-template <int DT, int TERMS>
+// DIFF (int8): the compare is a scan's (one that computed the input from another layer's projection, in a launch of its own); x_t is
+// the difference it left, zero wherever nothing changed.  The launch keeps the sub-tile flags as the tile kernel does, in a
+// row of workgroups of its own behind the position blocks.
+template <int DT, int TERMS, bool DIFF>
 __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restrict__ x_t, uint4* x_snap,
                                                           const uint4* __restrict__ wsc, void* y_v, ScatGeom g,
                                                           DevStats* __restrict__ stats_base) {
@@ -88,6 +91,26 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
     const size_t u0 = (size_t)p0 * g.U;  // first 16-byte unit of the block (positions are contiguous in x)
     DevStats* stats = stats_base + (blockIdx.x & (STAT_SLOTS - 1));
     sc_t* y = static_cast<sc_t*>(y_v);
+    if (DIFF && p0 >= (unsigned int)g.npos_total) {
+        const unsigned int eshift = g.epoch[EPOCH_TILE] - 1u, bits = 0x01010101u << eshift;
+        const int per = (g.n_words + g.cs - 1) / g.cs, w1 = min(g.n_words, ((int)blockIdx.y + 1) * per);
+        unsigned int active = 0;
+        for (int w = (int)blockIdx.y * per + tid; w < w1; w += ST) {
+            const unsigned int f = g.flags[w], now = f & bits;
+            active += __popc(now);
+            if (f != now) g.flags[w] = now;  // the step before's marks
+        }
+        if (__any(active != 0)) {
+            active = wave_scan(active);
+            if (lane == 63) atomicAdd(&stats->active_tiles, (unsigned long long)active);
+        }
+        if (blockIdx.y == 0 && tid == 0) {
+            g.epoch[EPOCH_SCAN] = 2u - eshift;
+            g.fresh[0] = 0u;        // the stored input holds this step's input
+            g.touched_all[0] = 0u;  // the flags describe this step
+        }
+        return;
+    }
 
     // ---- both frames' units, all in flight together ------------------------------------------------------------------
     uint4 a[UPT], b[UPT];
@@ -96,11 +119,11 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
         if (ST * i >= nunits) break;
         const int v = min(tid + ST * i, nunits - 1);
         a[i] = x_t[u0 + v];
-        b[i] = x_snap[u0 + v];
+        if (!DIFF) b[i] = x_snap[u0 + v];
     }
     if (tid < 64) s_flag[tid] = 0u;
     if (tid == 0) *zero_unit = make_uint4(0, 0, 0, 0);
-    const bool counts = blockIdx.y == 0;  // statistics: one workgroup per position block
+    const bool counts = !DIFF && blockIdx.y == 0;  // statistics: one workgroup per position block
     // what the rest of the kernel needs of its arguments arrives while the units do
     const int U = kept(g.U), ug = kept(g.ug), nk = kept(g.nk), nkp = kept(g.nkp), ntaps = kept(g.ntaps), ncb = kept(g.ncb), kw = kept(g.kw),
               og = kept(g.og), c_out = kept(g.c_out), nitems = kept(g.npair * g.ntaps * g.nkp), cs = kept(g.cs), pad = kept(g.pad),
@@ -119,6 +142,13 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
     for (int i = 0; i < UPT; ++i) {
         if (ST * i >= nunits) break;
         const int v = tid + ST * i;
+        if (DIFF) {
+            if (v < nunits) {
+                dl[v] = a[i];
+                if (a[i].x | a[i].y | a[i].z | a[i].w) s_flag[udiv_magic(v, U, magic_U)] = 1u;
+            }
+            continue;
+        }
         const unsigned int aw[4] = {a[i].x, a[i].y, a[i].z, a[i].w}, bw[4] = {b[i].x, b[i].y, b[i].z, b[i].w};
         const bool changed = v < nunits && ((aw[0] ^ bw[0]) | (aw[1] ^ bw[1]) | (aw[2] ^ bw[2]) | (aw[3] ^ bw[3])) != 0u;
         if (DT == RRM_I8_I32) {
@@ -219,7 +249,7 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
     if (cnt > 0) {
         // Every read of the stored input by this workgroup is done.  (The workgroups that share a block see the same list, and
         // without a changed position there is nothing to commit: they don't count.)
-        const bool shared_block = cs > 1;
+        const bool shared_block = !DIFF && cs > 1;
         unsigned int arrived_before = 0;
         if (shared_block && tid == 0) arrived_before = atomicAdd(&g.arrive[blockIdx.x], 1u);
         if (flag) s_list[wave][__popcll(found & ((1ull << lane) - 1ull))] = lane;
@@ -252,7 +282,7 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
         }
         // ---- commit the stored input (only where a difference was applied), while the weights arrive: at the end the answer of
         // the arrival counter would be waited for behind all of the outputs' atomic adds
-        bool last = true;
+        bool last = !DIFF;
         if (shared_block) {
             if (tid == 0) s_prev = arrived_before;
             lds_barrier();
@@ -375,39 +405,45 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
 
 }  // namespace
 
+// LDS beyond 64 KB: for every form of the kernel, once per process
+static hipError_t scatter_lds(size_t lds) {
+    if (lds <= 64 * 1024) return hipSuccess;
+    static std::once_flag once;
+    static hipError_t attr = hipSuccess;
+    std::call_once(once, [] {
+        for (const void* f : {reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_I8_I32, 1, false>),
+                              reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_I8_I32, 1, true>),
+                              reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_BF16_F32, 1, false>),
+                              reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_BF16_F32, 2, false>)})
+            if (attr == hipSuccess) attr = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+    });
+    return attr;
+}
+
 hipError_t launch_conv_scatter(int dtype, int terms, const void* x_t, void* x_snap, const void* wsc, void* y,
                                const ScatGeom& g, DevStats* stats, hipStream_t s) {
     const long long nblk = (g.npos_total + g.PB - 1) / g.PB;
     dim3 grid((unsigned int)nblk, (unsigned int)g.cs);
-    const int t = dtype == RRM_BF16_F32 ? terms : 1;
     const size_t lds = ((size_t)scat_planes(dtype) * g.PB * g.U + 1) * 16;
-    const uint4* xt = static_cast<const uint4*>(x_t);
-    uint4* xs = static_cast<uint4*>(x_snap);
-    const uint4* w = static_cast<const uint4*>(wsc);
-    if (lds > 64 * 1024) {
-        static std::mutex mu;  // shared by every handle and thread of the process
-        static bool granted = false;
-        std::lock_guard<std::mutex> lock(mu);
-        if (!granted) {
-            const int cap = 96 * 1024;
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_scatter_kernel<RRM_I8_I32, 1>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-            if (e == hipSuccess)
-                e = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_scatter_kernel<RRM_BF16_F32, 1>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-            if (e == hipSuccess)
-                e = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_scatter_kernel<RRM_BF16_F32, 2>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-            if (e != hipSuccess) return e;
-            granted = true;
-        }
-    }
-    if (dtype == RRM_I8_I32)
-        hipLaunchKernelGGL((conv_scatter_kernel<RRM_I8_I32, 1>), grid, dim3(ST), lds, s, xt, xs, w, y, g, stats);
-    else if (t == 2)
-        hipLaunchKernelGGL((conv_scatter_kernel<RRM_BF16_F32, 2>), grid, dim3(ST), lds, s, xt, xs, w, y, g, stats);
-    else
-        hipLaunchKernelGGL((conv_scatter_kernel<RRM_BF16_F32, 1>), grid, dim3(ST), lds, s, xt, xs, w, y, g, stats);
+    const hipError_t e = scatter_lds(lds);
+    if (e != hipSuccess) return e;
+    const auto kernel = dtype == RRM_I8_I32 ? conv_scatter_kernel<RRM_I8_I32, 1, false>
+                        : terms == 2        ? conv_scatter_kernel<RRM_BF16_F32, 2, false>
+                                            : conv_scatter_kernel<RRM_BF16_F32, 1, false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(ST), lds, s, static_cast<const uint4*>(x_t), static_cast<uint4*>(x_snap),
+                       static_cast<const uint4*>(wsc), y, g, stats);
+    return hipGetLastError();
+}
+
+hipError_t launch_conv_scatter_diff(const void* d0, const void* wsc, void* y, const ScatGeom& g, DevStats* stats, hipStream_t s) {
+    const long long nblk = (g.npos_total + g.PB - 1) / g.PB;
+    dim3 grid((unsigned int)nblk + 1u, (unsigned int)g.cs);
+    const size_t lds = ((size_t)g.PB * g.U + 1) * 16;
+    const hipError_t e = scatter_lds(lds);
+    if (e != hipSuccess) return e;
+    const auto kernel = conv_scatter_kernel<RRM_I8_I32, 1, true>;
+    hipLaunchKernelGGL(kernel, grid, dim3(ST), lds, s, static_cast<const uint4*>(d0), static_cast<uint4*>(nullptr),
+                       static_cast<const uint4*>(wsc), y, g, stats);
     return hipGetLastError();
 }
 

@@ -878,7 +878,10 @@ rrm_status rrm_layer_create(const void* weights, const void* bias, const rrm_sha
             L->cg.fresh = L->fresh;
             L->pg.fresh = L->fresh;
             L->cg.touched_all = L->pg.touched_all = L->sc.touched_all = L->ctrl + 4;
-            L->cg.epoch = L->sg.epoch = L->ctrl + 8;
+            L->cg.epoch = L->sg.epoch = L->sc.epoch = L->ctrl + 8;
+            L->sc.flags = L->tileflag;
+            L->sc.n_words = L->cg.n_words;
+            L->sc.fresh = L->fresh;
         }
         if ((st = dalloc(256, &L->zero16)) != RRM_OK) return bail(st);
     }
@@ -1022,6 +1025,13 @@ rrm_status rrm_step_from_projection(rrm_layer* L, rrm_layer* P, int shift, int p
     if (L->use_pos)
         RRM_HIP(launch_conv_pos(L->dtype, MODE_DELTA, 1, L->d0, L->d1, L->zero16, L->bitmap, L->ctrl, L->wpos, L->bias,
                                 L->y_snap, L->pg, L->stats, st));
+    else if (L->opt_path == 0 && use_scatter(L))
+        // layers of few adds (see setup_scatter), here after the scan: the tile kernel's start, a list over all flags, staged
+        // windows, costs more than the adds.  us a launch inside a five-layer stack at one stream, tile against this: 27 x 27,
+        // 96 -> 256 7.0 / 6.0, 13 x 13, 256 -> 384 8.9 / 4.8, 384 -> 384 8.4 / 5.5, 384 -> 256 8.4 / 5.8; the stack's step at
+        // 1 / 2 / 4 / 8 / 16 streams 63.4 / 68.0 / 73.1 / 87.7 / 99.2 without, 54.2 / 61.9 / 71.8 / 88.2 / 98.9 with it (with
+        // twice as many adds admitted 54.1 / 62.2 / 71.9 / 89.3 / 107.4).
+        RRM_HIP(launch_conv_scatter_diff(L->d0, L->wsc, L->y_snap, L->sc, L->stats, st));
     else
         RRM_HIP(launch_conv(L->dtype, MODE_DELTA, L->cg.wg_cb, L->cg.nt, 1, L->d0, L->d1, L->zero16, L->tileflag,
                             L->wpack, L->offtab, L->bias, L->y_snap, L->cg, L->stats, st));

@@ -161,6 +161,11 @@ struct ScatGeom {
     unsigned int magic_U, magic_hw, magic_w, magic_nkp, magic_taps, magic_ncb, magic_kw, magic_stride;  // reciprocals
     unsigned int* arrive;       // one word per position block (used when cs > 1; rearmed by the kernel)
     unsigned int* touched_all;  // device word set by every step of this path: "treat every output as written"
+    // products of a difference that a scan has left (launch_conv_scatter_diff): what that launch leaves as the tile kernel would
+    unsigned int* flags;        // 4x4 sub-tile flags
+    int n_words;                // 32-bit words of them
+    unsigned int* epoch;        // see StepEpoch
+    unsigned int* fresh;        // see FusedSrc::fresh
 };
 
 struct FcGeom {
@@ -236,6 +241,8 @@ hipError_t launch_conv_pos(int dtype, int mode, int terms, const void* src0, con
 // accumulation, commit); wsc: weights in [pair][tap][K step][lane] x 16 bytes order
 hipError_t launch_conv_scatter(int dtype, int terms, const void* x_t, void* x_snap, const void* wsc, void* y,
                                const ScatGeom& g, DevStats* stats, hipStream_t s);
+// int8: the products alone, of the difference d0 (in x's layout) that a scan has formed, committed and flagged
+hipError_t launch_conv_scatter_diff(const void* d0, const void* wsc, void* y, const ScatGeom& g, DevStats* stats, hipStream_t s);
 
 // one delta step of an FC layer in a single launch; `arrive`: one zeroed word per stream (rearmed by the kernel)
 // y_out: the caller's copy of the projection, or nullptr; allowed where every output has one owner workgroup

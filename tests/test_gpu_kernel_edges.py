@@ -122,6 +122,45 @@ def test_scatter_path_edges(h, w, ci, co, k, st, pad, g, n, dt):
     run_sequence(seq, check_dense=(), path=3)
 
 
+# A layer of few adds behind another one: its products are the scatter kernel's, of the difference that the scan has left, and
+# the launch leaves flags, statistics and words as the tile kernel does ("path" = 1), in turn with plain steps of either path;
+# what reads the flags then sees all that was written.  (map, c, c_out, k, stride, pad, groups, streams)
+@pytest.mark.parametrize("m,ci,co,k,st,pad,g,n", [
+    (13, 32, 48, 3, 1, 1, 1, 1), (9, 64, 36, 5, 2, 2, 1, 3), (27, 48, 72, 3, 1, 1, 1, 2), (6, 160, 64, 1, 1, 0, 2, 5), (40, 16, 16, 3, 1, 1, 1, 9),
+])
+def test_scatter_of_a_scans_difference(m, ci, co, k, st, pad, g, n):
+    import numpy as np
+    import oracle
+    import paper_1802_09723_amd as rrm
+    import torch
+    from gpu_util import assert_matches, to_device
+    first = S.random_layer(9950 + m, S.conv_shape(m, m, 16, ci, 3, 1, 1, 1, n=n), S.I8, T=8, frac=0.1, block=3)
+    first.frames[4] = first.frames[3].copy()
+    nxt = S.random_layer(9960 + m, S.conv_shape(m, m, ci, co, k, st, pad, g, n=n), S.I8, T=1, frac=0.1, block=3)
+    A = rrm.Layer(first.shape, S.I8, first.weights, first.bias)
+    B, T = (rrm.Layer(nxt.shape, S.I8, nxt.weights, nxt.bias) for _ in range(2))
+    T.set_option("path", 1)
+    shift = oracle.calibrate_shift(oracle.dense(first.shape, S.I8, first.weights, first.bias, first.frames[0]))
+    out = [torch.full(B.y_shape, -1, dtype=torch.int8, device="cuda") for _ in range(2)]
+    for t, x in enumerate(first.frames):
+        A.step(to_device(x, S.I8))
+        f = oracle.relu_requant_pool(oracle.dense(first.shape, S.I8, first.weights, first.bias, x), shift, False)
+        for layer in (B, T):
+            if t == 5:
+                layer.step(to_device(f, S.I8))
+            else:
+                layer.step_from_projection(A, shift, False)
+        want = oracle.dense(nxt.shape, S.I8, nxt.weights, nxt.bias, f)
+        for layer, o in zip((B, T), out):
+            assert_matches(layer.y_snapshot().cpu().numpy(), want, S.I8, f"frame {t}")
+            layer.relu_requant_pool_changed(o, 4, False)
+            assert np.array_equal(o.cpu().numpy(), oracle.relu_requant_pool(want, 4, False)), f"frame {t}: what was written"
+        if t < 5:  # (a plain scatter step counts positions)
+            assert B.stats() == T.stats(), f"frame {t}"
+    for layer in (A, B, T):
+        layer.destroy()
+
+
 # The sub-tile flags carry the step's own value and are wiped a step later: what a step counts as active is what its own frame
 # changed, whatever the steps before marked.  (map, streams): flag arrays off the words of four and the vectors of 16, one
 # workgroup per flag group, one round of vectors in the work list, several, and more than stay in registers; the frames
