@@ -17,11 +17,10 @@
 // flipped bit are skipped.
 //
 // Mapping of the band kernel (the delta step, and the dense layer): one workgroup = a band of output rows of one stream x 64 output
-// channels.  It stages the band's input window (the flip mask m, and the flips to -1, m & ~x), notes which input positions hold a
-// flip, lists
-// the output positions whose window sees one (ballot compaction into LDS) and multiplies that list 64 entries
-// at a time: every column of the product is an output position with work to do, wherever in the band it lies, so
-// the work follows the changed positions instead of the 8x8 tiles they fall into.
+// channels.  It stages the band's input window (the flip mask m and the flips to -1, m & ~x, see pack_e2m1), notes in bits which
+// input positions hold a flip, lists the output positions whose window sees one (ballot compaction into LDS) and multiplies that
+// list 32 or 64 entries at a time: every column of the product is an output position with work to do, wherever in the band it
+// lies, so the work follows the changed positions instead of the 8x8 tiles they fall into.
 #include <algorithm>
 #include <mutex>
 
@@ -35,6 +34,9 @@ constexpr int BAND_THREADS = 64 * BAND_WAVES;  // the band kernel's workgroup
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+
+// Workgroup barrier that publishes LDS contents only (__syncthreads() would also wait for the filter fragments)
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // t + popcount(v) in one instruction (v_bcnt_u32_b32 adds its second operand; the compiler otherwise counts
 // into a fresh register and adds pairs of counts with a third instruction)
@@ -180,22 +182,30 @@ __global__ __launch_bounds__(256) void bin_conv_kernel(const unsigned int* __res
 // Half of a difference of two +1/-1 frames is -1, 0 or +1, which the 4-bit float format of the matrix cores (E2M1)
 // holds exactly, like the weights; the products are summed in fp32, exact below 2^24 terms (a band's window in LDS
 // holds far fewer).  v_mfma_f32_32x32x64_f8f6f4 multiplies 32 output channels x 32 listed positions x 64 input
-// channels of one tap in 32 cycles, where the popcount form takes 256 vector cycles, and a lane makes its 32 entries
-// of the difference out of two LDS words with 16 instructions.
-// Measured (28 x 28, 256 -> 256 channels, 64 streams, 5 % of the values flipping): 36.8 -> 23.0 us a step; one stream
-// of 14 x 14, 512 -> 512 channels, 10 %: 16.8 -> 10.3.
-
-// 32 differences as E2M1 nibbles: m = flip mask, q = flips to -1.  Nibble j of register i is bit 4j + i of the word
-// (the weights are packed in the same order): 0x2 = +1, 0xA = -1, 0x0 = unchanged.
-__device__ __forceinline__ v8i expand_e2m1(unsigned int m, unsigned int q) {
+// channels of one tap in 32 cycles, where the popcount form takes 256 vector cycles.
+// Measured (28 x 28, 256 -> 256 channels, 64 streams, 5 % of the values flipping): 36.8 us a step with popcounts, 23.0 with weights
+// fetched as nibbles (16 bytes a lane, K step and 32 channels: what the vector cache delivers per clock was the bound), 21.0 so;
+// one stream of 14 x 14, 512 -> 512 channels, 10 %: 16.8, 10.3 and 7.4.
+//
+// 32 values of a word are 4 registers of E2M1 nibbles; nibble j of register i is value 4 j + (1, 0, 3, 2)[i].  Of a difference
+// (0x2 = +1, 0xA = -1, 0x0 = unchanged) only the bits 1 and 3 are ever set, so two registers lie in one word of LDS, the second one
+// a bit lower, as the flip mask m and the flips to -1, q, give them in two instructions each; of a weight (0x2 or 0xA) one bit is
+// kept, and a wavefront holds all of its steps' in registers.
+__device__ __forceinline__ uint2 pack_e2m1(unsigned int m, unsigned int q) {
+    const unsigned int M = 0x33333333u;
+    return make_uint2((m & M) | (q << 2 & ~M), (m >> 2 & M) | (q & ~M));
+}
+__device__ __forceinline__ v8i difference_e2m1(const uint2& p) {
+    const unsigned int K = 0xAAAAAAAAu;
+    return v8i{(int)(p.x & K), (int)(p.x << 1 & K), (int)(p.y & K), (int)(p.y << 1 & K), 0, 0, 0, 0};
+}
+__device__ __forceinline__ v8i weights_e2m1(unsigned int minus) {  // `minus`: a bit per value of -1
     const unsigned int P = 0x22222222u, N = 0x88888888u;
-    return v8i{(int)(((m << 1) & P) | ((q << 3) & N)), (int)((m & P) | ((q << 2) & N)),
-               (int)(((m >> 1) & P) | ((q << 1) & N)), (int)(((m >> 2) & P) | (q & N)), 0, 0, 0, 0};
+    return v8i{(int)((minus << 2 & N) | P), (int)((minus << 3 & N) | P), (int)((minus & N) | P), (int)((minus << 1 & N) | P), 0, 0, 0, 0};
 }
 
-__device__ __forceinline__ v16f mma_e2m1(const uint4& a, const v8i& b, v16f c) {
-    const v8i av{(int)a.x, (int)a.y, (int)a.z, (int)a.w, 0, 0, 0, 0};
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, b, c, 4, 4, 0, 0, 0, 0);  // E2M1 x E2M1, unscaled
+__device__ __forceinline__ v16f mma_e2m1(const v8i& a, const v8i& b, v16f c) {
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 4, 4, 0, 0, 0, 0);  // E2M1 x E2M1, unscaled
 }
 
 // FUSED: the whole step in this one launch.  `xsrc` is the new frame x_t and `flip` the stored input: the flip
@@ -206,28 +216,42 @@ __device__ __forceinline__ v16f mma_e2m1(const uint4& a, const v8i& b, v16f c) {
 // DENSE: the layer itself (Eq. 3) with the same product: m = "tap inside the image", every output position is listed, and
 // the result is the bias plus the sums.  (`flip` and `stats` are not touched.)  60 x 13, 448 -> 72 channels, 26 streams: 40.9 us on the tile
 // kernel, 28.6 here.
-template <bool FUSED, bool DENSE>
+//
+// TILES > 0: a pass is 32 * TILES listed positions x 64 channels.  The wavefronts of a tile of 32 positions split the K steps (a
+// tap, 64 channels): a wavefront takes steps kpart, kpart + KPARTS, ... and adds its sums in LDS.  The weights of KU of its steps
+// are in registers at a time (they do not depend on the list: they are fetched ahead of it) and are replaced one by one as they
+// are used; if that is all of them, they stay for every pass.
+// TILES = 0: no pass and no sums in LDS; a wavefront takes tiles with all of their K steps.  For long lists, where there are
+// tiles for all wavefronts.
+template <bool FUSED, bool DENSE, int TILES, int KU>
 __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigned int* __restrict__ xsrc,
                                                        const unsigned int* flip, unsigned int* snap,
                                                        unsigned int* arrive,
-                                                       const uint4* __restrict__ wband, const int* __restrict__ bias,
+                                                       const uint2* __restrict__ wband, const int* __restrict__ bias,
                                                        int* y, BinGeom g, DevStats* __restrict__ stats) {
+    constexpr int KPARTS = TILES > 0 ? BAND_WAVES / TILES : 1, PASS = 32 * TILES;
+    constexpr int CPT = 4 * TILES;  // channels per thread of a pass' results
     extern __shared__ uint4 smem[];
     const int npos = g.bth_in * g.btw_in;
-    unsigned int* A = reinterpret_cast<unsigned int*>(smem);
-    unsigned int* B = A + npos * g.bpitch;
-    unsigned char* posany = reinterpret_cast<unsigned char*>(B + npos * g.bpitch);     // input position holds a flip
-    unsigned short* list = reinterpret_cast<unsigned short*>(posany + ((npos + 15) & ~15));  // active output positions
-    // sums of a pass: 64 positions x 64 channels, rows padded by one word (the lanes of an add are 32 positions)
+    // The mask m and the flips to -1, m & ~x, of a word lie side by side, and a position's words at an odd pitch of such pairs
+    // (except in wide layers, without padding): the 32 lanes of a read are 32 positions and meet no bank twice.
+    const int ip = g.bpitch < g.pitch ? g.nslab * 4 : g.nslab * 4 + 1;
+    uint2* AB = reinterpret_cast<uint2*>(smem);
+    // a bit per input position that holds a flip, rows of whole words (with the padding saved above they take no more than a
+    // byte per position)
+    const int bw = (g.btw_in + 31) >> 5;
+    unsigned int* bits = reinterpret_cast<unsigned int*>(AB + npos * ip);
+    unsigned short* list = reinterpret_cast<unsigned short*>(reinterpret_cast<unsigned char*>(smem) + bin_band_list_offset(g));  // active output positions
+    // sums of a pass: PASS positions x 64 channels, rows padded by one word
     int* red = reinterpret_cast<int*>(reinterpret_cast<unsigned char*>(list) + (((size_t)g.band_rows * g.wo * 2 + 15) & ~(size_t)15));
-    __shared__ unsigned int s_wc[BAND_THREADS / 64], s_prev;
+    __shared__ unsigned int s_wc[BAND_WAVES], s_prev;
 
     // grid: x = list split (fastest, so the workgroups that share a band start together), y = channel block,
     // z = stream x band
-    const int sb = (int)blockIdx.z, zsplit = (int)blockIdx.x, nsplit = (int)gridDim.x;
-    const int b = sb / g.nbands, band = sb - b * g.nbands;
-    const int nblk = (g.og + 63) / 64;
-    const int grp = blockIdx.y / nblk;
+    const int sb = (int)blockIdx.z, zsplit = (int)blockIdx.x, nsplit = g.nsplit;
+    const int b = (int)udiv_magic((unsigned int)sb, (unsigned int)g.nbands, g.magic_nbands), band = sb - b * g.nbands;
+    const int nblk = (g.og + 63) >> 6;
+    const int grp = (int)udiv_magic(blockIdx.y, (unsigned int)nblk, g.magic_nblk);
     const int blk = blockIdx.y - grp * nblk;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -236,63 +260,80 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
     const int iy0 = oy0 * g.stride - g.pad, ix0 = -g.pad;
     const int wg4 = g.nslab * 4;
 
-    // A pass is 64 listed positions x 64 channels.  Each half of the wavefronts takes one of its two tiles of 32 positions,
-    // and the four of a half split the K steps (a tap, 64 channels): a wavefront takes steps w, w + 4, ... and adds its
-    // sums in LDS.  Filter fragments go from memory straight into registers, BAND_KU steps in flight; the first ones do
-    // not depend on the list: they are fetched ahead of it (and stay for every pass if they are all).  (Eight parts of both
-    // tiles: twice the adds, and registers for fewer steps in flight.)
     const int ntaps = g.kh * g.kw, nkt = 2 * g.nslab, nk = ntaps * nkt;  // K steps per tap, in all
     const int n = lane & 31, khalf = lane >> 5;
-    const uint4* wfrag = wband + ((long long)(grp * 2 * nblk + 2 * blk) * nk) * 64;
-    const int kpart = wave & 3, tile = wave >> 2;
-    uint4 w[BAND_KU][2];
-    auto load_frags = [&](int k0) {
-#pragma unroll
-        for (int i = 0; i < BAND_KU; ++i) {
-            const int k = min(k0 + i * 4, nk - 1);
-#pragma unroll
-            for (int c = 0; c < 2; ++c) w[i][c] = (wfrag + (long long)(c * nk + k) * 64)[(unsigned int)lane];
-        }
-    };
-    for (int i = tid; i < npos; i += BAND_THREADS) posany[i] = 0;
-    for (int i = tid; i < 64 * BAND_RP; i += BAND_THREADS) red[i] = 0;
-    __syncthreads();
+    const uint2* wfrag = wband + (long long)(grp * nblk + blk) * nk * 64 + lane;
+    const int kpart = TILES > 0 ? wave & (KPARTS - 1) : 0, tile = wave / KPARTS;
+    uint2 w[KU];  // of a step: the lane's word of the block's channels 0 .. 31 and 32 .. 63
     // (FUSED) input rows whose changes this band counts, by the workgroup of the band's first channel block
     const int own_lo = oy0 * g.stride, own_hi = band == g.nbands - 1 ? g.h : (oy0 + g.band_rows) * g.stride;
     const bool count_here = FUSED && blk == 0 && zsplit == 0;
     unsigned int nbits = 0, nunits = 0, arrived_before = 0;
-    // ---- stage A = m and B = m & ~x of the band's input window ------------------------------
+    auto clear_lds = [&]() __attribute__((always_inline)) {
+        for (int i = tid; i < g.bth_in * bw; i += BAND_THREADS) bits[i] = 0;
+        for (int i = tid; i < PASS * BAND_RP; i += BAND_THREADS) red[i] = 0;
+    };
+    auto first_frags = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < KU; ++i) w[i] = wfrag[(long long)min(kpart + i * KPARTS, nk - 1) * 64];
+    };
+    // ---- stage m and m & ~x of the band's input window ----------------------------------------
     if (g.vec4) {
-        // four words at a time, both loads issued whatever the mask holds (independent loads, several in flight)
+        // four words at a time, BATCH of them in flight per thread
+        constexpr int BATCH = 4;
         const int units = npos * g.nslab;
-#pragma unroll 4
-        for (int u = tid; u < units; u += BAND_THREADS) {
-            const int hp = (int)(g.magic_nslab ? __umulhi((unsigned int)u, g.magic_nslab) : (unsigned int)u), sl = u - hp * g.nslab;
-            const int hy = (int)(g.magic_btw ? __umulhi((unsigned int)hp, g.magic_btw) : (unsigned int)hp), hx = hp - hy * g.btw_in;
-            const int iy = iy0 + hy, ix = ix0 + hx;
-            uint4 m = make_uint4(0, 0, 0, 0), xv = make_uint4(0, 0, 0, 0);
-            if (iy >= 0 && iy < g.h && ix >= 0 && ix < g.w) {
-                const long long wi = (((long long)b * g.h + iy) * g.w + ix) * g.wpp + (long long)grp * g.wg + sl * 4;
-                m = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
-                if (!DENSE) m = *reinterpret_cast<const uint4*>(flip + wi);  // the flip buffer is zero where nothing changed
-                xv = *reinterpret_cast<const uint4*>(xsrc + wi);
-                if (FUSED) {
-                    m = make_uint4(m.x ^ xv.x, m.y ^ xv.y, m.z ^ xv.z, m.w ^ xv.w);
-                    if (count_here && iy >= own_lo && iy < own_hi && (m.x | m.y | m.z | m.w)) {
-                        nbits += __popc(m.x) + __popc(m.y) + __popc(m.z) + __popc(m.w);
+        for (int u0 = 0; u0 < units; u0 += BATCH * BAND_THREADS) {
+            uint4 m[BATCH], xv[BATCH];
+            int hy[BATCH], hx[BATCH];
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                m[i] = xv[i] = make_uint4(0, 0, 0, 0);
+                if (u0 + i * BAND_THREADS >= units) continue;
+                const int u = u0 + i * BAND_THREADS + tid;
+                const int hp = (int)udiv_magic((unsigned int)u, (unsigned int)g.nslab, g.magic_nslab), sl = u - hp * g.nslab;
+                hy[i] = (int)udiv_magic((unsigned int)hp, (unsigned int)g.btw_in, g.magic_btw);
+                hx[i] = hp - hy[i] * g.btw_in;
+                const int iy = iy0 + hy[i], ix = ix0 + hx[i];
+                if (u < units && iy >= 0 && iy < g.h && ix >= 0 && ix < g.w) {
+                    const long long wi = (((long long)b * g.h + iy) * g.w + ix) * g.wpp + (long long)grp * g.wg + sl * 4;
+                    m[i] = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
+                    if (!DENSE) m[i] = *reinterpret_cast<const uint4*>(flip + wi);  // the flip buffer is zero where nothing changed
+                    xv[i] = *reinterpret_cast<const uint4*>(xsrc + wi);
+                }
+            }
+            if (u0 == 0) {
+                clear_lds();
+                lds_barrier();
+            }
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                const int u = u0 + i * BAND_THREADS + tid;
+                if (u >= units) break;
+                const int hp = hy[i] * g.btw_in + hx[i], sl = u - hp * g.nslab, iy = iy0 + hy[i];
+                uint4 f = m[i];
+                const uint4 x = xv[i];
+                if (FUSED) {  // (outside of the frame both are zero)
+                    f = make_uint4(f.x ^ x.x, f.y ^ x.y, f.z ^ x.z, f.w ^ x.w);
+                    if (count_here && iy >= own_lo && iy < own_hi && (f.x | f.y | f.z | f.w)) {
+                        nbits += __popc(f.x) + __popc(f.y) + __popc(f.z) + __popc(f.w);
                         ++nunits;
                     }
                 }
+                if (!DENSE && (f.x | f.y | f.z | f.w)) atomicOr(&bits[hy[i] * bw + (hx[i] >> 5)], 1u << (hx[i] & 31));
+                uint2* d = AB + hp * ip + sl * 4;
+                d[0] = pack_e2m1(f.x, f.x & ~x.x);
+                d[1] = pack_e2m1(f.y, f.y & ~x.y);
+                d[2] = pack_e2m1(f.z, f.z & ~x.z);
+                d[3] = pack_e2m1(f.w, f.w & ~x.w);
             }
-            if (m.x | m.y | m.z | m.w) posany[hp] = 1;
-            *reinterpret_cast<uint4*>(A + hp * g.bpitch + sl * 4) = m;
-            *reinterpret_cast<uint4*>(B + hp * g.bpitch + sl * 4) = make_uint4(m.x & ~xv.x, m.y & ~xv.y, m.z & ~xv.z, m.w & ~xv.w);
         }
     } else {
+        clear_lds();
+        lds_barrier();
         const int units = npos * wg4;
         for (int u = tid; u < units; u += BAND_THREADS) {
-            const int hp = (int)(g.magic_wg4 ? __umulhi((unsigned int)u, g.magic_wg4) : (unsigned int)u), wd = u - hp * wg4;
-            const int hy = (int)(g.magic_btw ? __umulhi((unsigned int)hp, g.magic_btw) : (unsigned int)hp), hx = hp - hy * g.btw_in;
+            const int hp = (int)udiv_magic((unsigned int)u, (unsigned int)wg4, g.magic_wg4), wd = u - hp * wg4;
+            const int hy = (int)udiv_magic((unsigned int)hp, (unsigned int)g.btw_in, g.magic_btw), hx = hp - hy * g.btw_in;
             const int iy = iy0 + hy, ix = ix0 + hx;
             unsigned int m = 0, xv = 0;
             if (wd < g.wg && iy >= 0 && iy < g.h && ix >= 0 && ix < g.w) {
@@ -300,26 +341,272 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
                 m = DENSE ? 0xFFFFFFFFu : flip[wi];  // the flip buffer is zero where nothing changed
                 if (m) {
                     xv = xsrc[wi];
-                    posany[hp] = 1;
+                    if (!DENSE) atomicOr(&bits[hy * bw + (hx >> 5)], 1u << (hx & 31));
                 }
             }
-            A[hp * g.bpitch + wd] = m;
-            B[hp * g.bpitch + wd] = m & ~xv;
+            AB[hp * ip + wd] = pack_e2m1(m, m & ~xv);
         }
     }
-    __syncthreads();
-    load_frags(kpart);
-    if (FUSED) {
-        // this workgroup has read the stored input for the last time
-        // (thread 0 keeps the answer to the end: stored at once, it would hold up the list by a memory round trip)
-        if (tid == 0) arrived_before = atomicAdd(&arrive[b], 1u);
-        if (count_here) {
+    lds_barrier();
+    if (TILES > 0) first_frags();
+    // this workgroup has read the stored input for the last time
+    // (thread 0 keeps the answer to the end: stored at once, it would hold up the list by a memory round trip)
+    if (FUSED && tid == 0) arrived_before = atomicAdd(&arrive[b], 1u);
+    // ---- list the output positions of the band whose window holds a flip ------------------------
+    const int nout = rows * g.wo;
+    int cnt = 0;
+    if (DENSE) {
+        for (int q = tid; q < nout; q += BAND_THREADS) list[q] = (unsigned short)q;
+        cnt = nout;
+        lds_barrier();
+    }
+    for (int base = 0; !DENSE && base < nout; base += BAND_THREADS) {
+        const int q = base + tid;
+        bool act = false;
+        if (q < nout) {
+            const int oyl = (int)udiv_magic((unsigned int)q, (unsigned int)g.wo, g.magic_wo), x0 = (q - oyl * g.wo) * g.stride;
+            const unsigned int* row = bits + (oyl * g.stride) * bw;
+            if (g.kw <= 32) {
+                // the window's columns lie in one or two words of a row; four rows in flight
+                const int i0 = x0 >> 5, i1 = min(i0 + 1, bw - 1), sh = x0 & 31;
+                unsigned long long any = 0;
+                for (int ky = 0; ky < g.kh; ky += 4) {
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                nbits += __shfl_xor(nbits, o);
-                nunits += __shfl_xor(nunits, o);
+                    for (int k = 0; k < 4; ++k) {
+                        const unsigned int* r = row + min(ky + k, g.kh - 1) * bw;
+                        any |= (unsigned long long)r[i1] << 32 | r[i0];
+                    }
+                }
+                act = ((unsigned int)(any >> sh) << (32 - g.kw)) != 0;
+            } else {
+                for (int ky = 0; ky < g.kh; ++ky)
+                    for (int kx = x0; kx < x0 + g.kw; ++kx) act |= (row[ky * bw + (kx >> 5)] >> (kx & 31) & 1u) != 0;
             }
-            if (lane == 0 && nunits) {
+        }
+        // (the same order in every workgroup of the band: the workgroups of a list split deal its chunks among them)
+        const unsigned long long mask = __ballot(act);
+        if (lane == 0) s_wc[wave] = (unsigned int)__popcll(mask);
+        lds_barrier();
+        unsigned int wbase = (unsigned int)cnt, all = 0;
+#pragma unroll
+        for (int k = 0; k < BAND_WAVES; ++k) {
+            const unsigned int c = s_wc[k];
+            if (k < wave) wbase += c;
+            all += c;
+        }
+        if (act) list[wbase + __popcll(mask & ((1ull << lane) - 1ull))] = (unsigned short)q;
+        cnt += (int)all;
+        lds_barrier();  // (the counts are overwritten in the next round; after the last one: the list is complete)
+    }
+
+    const bool vec = (g.c_out & 3) == 0 && (g.og & 3) == 0;
+    // y[0 .. 3] of a position and four channels that start at channel `ch` of the group
+    auto load4 = [&](const int* yp, int ch) __attribute__((always_inline)) {
+        if (vec) return *reinterpret_cast<const int4*>(yp);
+        return make_int4(yp[0], ch + 1 < g.og ? yp[1] : 0, ch + 2 < g.og ? yp[2] : 0, ch + 3 < g.og ? yp[3] : 0);
+    };
+    auto store4 = [&](int* yp, int ch, const int4& v) __attribute__((always_inline)) {
+        if (vec) {
+            *reinterpret_cast<int4*>(yp) = v;
+            return;
+        }
+        yp[0] = v.x;
+        if (ch + 1 < g.og) yp[1] = v.y;
+        if (ch + 2 < g.og) yp[2] = v.z;
+        if (ch + 3 < g.og) yp[3] = v.w;
+    };
+    const int bch = blk * 64;  // the block's first channel of the group
+    auto y_at = [&](int q) __attribute__((always_inline)) {  // ... at a listed position
+        const int oyl = (int)udiv_magic((unsigned int)q, (unsigned int)g.wo, g.magic_wo);
+        return y + ((((long long)b * g.ho + oy0 + oyl) * g.wo + (q - oyl * g.wo)) * g.c_out + (long long)grp * g.og + bch);
+    };
+    auto window_at = [&](int q) __attribute__((always_inline)) {
+        const int oyl = (int)udiv_magic((unsigned int)q, (unsigned int)g.wo, g.magic_wo);
+        return AB + ((oyl * g.stride) * g.btw_in + (q - oyl * g.wo) * g.stride) * ip + khalf;
+    };
+    if constexpr (TILES > 0) {
+        // The list in passes of PASS entries, dealt to the workgroups of a list split.
+        const int el = tid / (64 / CPT), j4 = (tid & (64 / CPT - 1)) * TILES;
+        for (int first = zsplit * PASS; first < cnt; first += nsplit * PASS) {
+            const bool more = first + nsplit * PASS < cnt;
+            // this thread's part of the pass' results: one position, CPT channels; fetched now, needed at the end
+            const int e = first + el;
+            int* yp = y_at(list[e < cnt ? e : 0]) + 4 * j4;
+            int4 yv[TILES];
+#pragma unroll
+            for (int h = 0; h < TILES; ++h) {
+                const int ch = bch + 4 * (j4 + h);
+                yv[h] = make_int4(0, 0, 0, 0);
+                const int* add = DENSE ? (bias ? bias + grp * g.og + ch : nullptr) : yp + 4 * h;
+                if (add && e < cnt && ch < g.og) yv[h] = load4(add, ch);
+            }
+            // this lane's column: the window of its listed position (an entry beyond the list repeats its first; its sums are
+            // not read)
+            const bool work = first + 32 * tile < cnt && kpart < nk;  // (the same in every lane)
+            const int ent = first + 32 * tile + n;
+            const uint2* lp = window_at(list[ent < cnt ? ent : 0]);
+            v16f acc[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
+#pragma unroll 1
+            for (int k0 = kpart; work && k0 < nk; k0 += KU * KPARTS) {
+                uint2 ab[KU];
+#pragma unroll
+                for (int i = 0; i < KU; ++i) {
+                    const int k = min(k0 + i * KPARTS, nk - 1);
+                    const int tap = (int)udiv_magic((unsigned int)k, (unsigned int)nkt, g.magic_nkt), st = k - tap * nkt;
+                    const int ky = (int)udiv_magic((unsigned int)tap, (unsigned int)g.kw, g.magic_kw), kx = tap - ky * g.kw;
+                    ab[i] = lp[(ky * g.btw_in + kx) * ip + 2 * st];
+                }
+#pragma unroll
+                for (int i = 0; i < KU; ++i) {
+                    const int k = k0 + i * KPARTS;
+                    if (k < nk) {
+                        const v8i d = difference_e2m1(ab[i]);
+                        acc[0] = mma_e2m1(weights_e2m1(w[i].x), d, acc[0]);
+                        acc[1] = mma_e2m1(weights_e2m1(w[i].y), d, acc[1]);
+                    }
+                    if (nk > KU * KPARTS) {  // the step that comes in this place next, or in the next pass
+                        const int kn = k + KU * KPARTS;
+                        if (kn < nk || more) w[i] = wfrag[(long long)(kn < nk ? kn : min(kpart + i * KPARTS, nk - 1)) * 64];
+                    }
+                }
+            }
+            if (work) {
+                // columns of a row: [khalf][c][r / 4][r % 4], so that the halves of the wavefront, 32 rows each, meet no bank twice
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) atomicAdd(&red[(32 * tile + n) * BAND_RP + 32 * khalf + 16 * c + r], (int)acc[c][r]);
+            }
+            lds_barrier();
+#pragma unroll
+            for (int h = 0; h < TILES; ++h) {
+                const int c4 = j4 + h;  // channels 4 c4 .. of the block: 32 * (c4 / 8) + 8 * (c4 / 2 % 4) + 4 * (c4 % 2)
+                int* r = red + el * BAND_RP + 32 * (c4 & 1) + 16 * (c4 >> 3) + 4 * (c4 >> 1 & 3);
+                constexpr int F = DENSE ? 1 : 2;
+                const int4 v = make_int4(yv[h].x + F * r[0], yv[h].y + F * r[1], yv[h].z + F * r[2], yv[h].w + F * r[3]);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) r[k] = 0;
+                if (e < cnt && bch + 4 * c4 < g.og) store4(yp + 4 * h, bch + 4 * c4, v);
+            }
+            if (more) lds_barrier();  // (the sums are cleared)
+        }
+    } else {
+        // Every wavefront for itself: NT tiles of 32 listed positions x NB blocks of 32 channels, all K steps.
+        auto item = [&]<int NT, int NB>(int tile0, int c0) __attribute__((always_inline)) {
+            const unsigned int* wf = reinterpret_cast<const unsigned int*>(wfrag) + c0;
+            unsigned int w[KU][NB];
+            auto fetch_w = [&](unsigned int (&f)[NB], int k) __attribute__((always_inline)) {
+                if constexpr (NB == 2) {
+                    const uint2 v = wfrag[(long long)k * 64];
+                    f[0] = v.x;
+                    f[1] = v.y;
+                } else {
+                    f[0] = wf[(long long)k * 128];
+                }
+            };
+#pragma unroll
+            for (int i = 0; i < KU; ++i) fetch_w(w[i], min(i, nk - 1));
+            int q[NT];
+            const uint2* lp[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const int ent = (tile0 + t) * 32 + n;
+                q[t] = list[ent < cnt ? ent : 0];
+                lp[t] = window_at(q[t]);
+            }
+            v16f acc[NT][NB];
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int c = 0; c < NB; ++c)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[t][c][r] = 0.f;
+            int off = 0, st = 0, kx = 0;  // of the next step to read
+#pragma unroll 1
+            for (int k0 = 0; k0 < nk; k0 += KU) {
+#pragma unroll
+                for (int j = 0; j < KU; j += 3) {
+                    uint2 ab[3][NT];
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) ab[i][t] = lp[t][off];
+                        if (k0 + j + i + 1 < nk) {
+                            off += 2;
+                            if (++st == nkt) {
+                                st = 0;
+                                off += ip - 2 * nkt;
+                                if (++kx == g.kw) {
+                                    kx = 0;
+                                    off += (g.btw_in - g.kw) * ip;
+                                }
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        const int k = k0 + j + i;
+                        if (k >= nk) break;
+                        v8i wc[NB];
+#pragma unroll
+                        for (int c = 0; c < NB; ++c) wc[c] = weights_e2m1(w[j + i][c]);
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) {
+                            const v8i d = difference_e2m1(ab[i][t]);
+#pragma unroll
+                            for (int c = 0; c < NB; ++c) acc[t][c] = mma_e2m1(wc[c], d, acc[t][c]);
+                        }
+                        if (k + KU < nk) fetch_w(w[j + i], k + KU);
+                    }
+                }
+            }
+            // a lane holds channels 8 * (r / 4) + 4 * khalf + r % 4 of each block, at one position of each tile
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                if ((tile0 + t) * 32 + n >= cnt) continue;
+                int* yp = y_at(q[t]);
+                int4 yv[NB][4];
+#pragma unroll
+                for (int c = 0; c < NB; ++c)
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) {
+                        const int ch = 32 * (c0 + c) + 8 * h + 4 * khalf;
+                        yv[c][h] = make_int4(0, 0, 0, 0);
+                        const int* add = DENSE ? (bias ? bias + grp * g.og + bch + ch : nullptr) : yp + ch;
+                        if (add && bch + ch < g.og) yv[c][h] = load4(add, bch + ch);
+                    }
+#pragma unroll
+                for (int c = 0; c < NB; ++c)
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) {
+                        const int ch = 32 * (c0 + c) + 8 * h + 4 * khalf;
+                        constexpr int F = DENSE ? 1 : 2;
+                        const v16f& s = acc[t][c];
+                        if (bch + ch < g.og)
+                            store4(yp + ch, bch + ch, make_int4(yv[c][h].x + F * (int)s[4 * h], yv[c][h].y + F * (int)s[4 * h + 1],
+                                                                yv[c][h].z + F * (int)s[4 * h + 2], yv[c][h].w + F * (int)s[4 * h + 3]));
+                    }
+            }
+        };
+        const int ntile = (cnt + 31) >> 5, nb = g.og - bch > 32 ? 2 : 1;
+        if (nb == 1 || 2 * ntile <= BAND_WAVES) {
+            for (int i = wave; i < nb * ntile; i += BAND_WAVES) item.template operator()<1, 1>(nb == 1 ? i : i >> 1, nb == 1 ? 0 : i & 1);
+        } else if (ntile <= BAND_WAVES) {
+            if (wave < ntile) item.template operator()<1, 2>(wave, 0);
+        } else {
+            for (int i = wave; 2 * i < ntile; i += BAND_WAVES) item.template operator()<2, 2>(2 * i, 0);
+        }
+    }
+    if (FUSED) {
+        if (tid == 0) s_prev = arrived_before;
+        if (count_here && __any(nunits != 0)) {
+            nbits = wave_scan(nbits);
+            nunits = wave_scan(nunits);
+            if (lane == 63) {
                 atomicAdd(&stats[sb & (STAT_SLOTS - 1)].changed_elems, (unsigned long long)nbits);
                 atomicAdd(&stats[sb & (STAT_SLOTS - 1)].changed_units, (unsigned long long)nunits);
             }
@@ -329,129 +616,12 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
             atomicAdd(&stats[0].total_tiles, (unsigned long long)g.n * g.ho * g.wo);
         }
     }
-    // ---- list the output positions of the band whose window holds a flip ------------------------
-    const int nout = rows * g.wo;
-    int cnt = 0;
-    if (DENSE) {
-        for (int q = tid; q < nout; q += BAND_THREADS) list[q] = (unsigned short)q;
-        cnt = nout;
-        __syncthreads();
-    }
-    for (int base = 0; !DENSE && base < nout; base += BAND_THREADS) {
-        const int q = base + tid;
-        bool act = false;
-        if (q < nout) {
-            const int oyl = q / g.wo, ox = q - oyl * g.wo;
-            const unsigned char* pa = posany + (oyl * g.stride) * g.btw_in + ox * g.stride;
-            for (int ky = 0; ky < g.kh; ++ky)
-                for (int kx = 0; kx < g.kw; ++kx) act |= pa[ky * g.btw_in + kx] != 0;
-        }
-        // (the same order in every workgroup of the band: the workgroups of a list split deal its chunks among them)
-        const unsigned long long mask = __ballot(act);
-        if (lane == 0) s_wc[wave] = (unsigned int)__popcll(mask);
-        __syncthreads();
-        unsigned int wbase = (unsigned int)cnt, all = 0;
-#pragma unroll
-        for (int w = 0; w < BAND_THREADS / 64; ++w) {
-            const unsigned int c = s_wc[w];
-            if (w < wave) wbase += c;
-            all += c;
-        }
-        if (act) list[wbase + __popcll(mask & ((1ull << lane) - 1ull))] = (unsigned short)q;
-        cnt += (int)all;
-        __syncthreads();  // (the counts are overwritten in the next round; after the last one: the list is complete)
-    }
     if (!DENSE && cnt > 0 && blockIdx.y == 0 && zsplit == 0 && tid == 0)
         atomicAdd(&stats[sb & (STAT_SLOTS - 1)].active_tiles, (unsigned long long)cnt);
-
-    // The list in passes of 64 entries, dealt to the workgroups of a list split.
-    const bool vec = (g.c_out & 3) == 0 && (g.og & 3) == 0;
-    for (int first = zsplit * 64; first < cnt; first += nsplit * 64) {
-        // this thread's part of the pass' results: one position, eight channels; fetched now, needed at the end
-        const int e = first + (tid >> 3), c8 = (tid & 7) * 8, co = blk * 64 + c8;
-        const int qe = list[e < cnt ? e : 0], oye = qe / g.wo;
-        int* yp = y + ((((long long)b * g.ho + oy0 + oye) * g.wo + (qe - oye * g.wo)) * g.c_out + (long long)grp * g.og + co);
-        int yv[8];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            int4 t = make_int4(0, 0, 0, 0);
-            const int* add = DENSE ? (bias ? bias + grp * g.og + co : nullptr) : yp;
-            if (add && e < cnt && co + 4 * h < g.og) {
-                if (vec) {
-                    t = reinterpret_cast<const int4*>(add)[h];
-                } else {
-                    t.x = add[4 * h];
-                    t.y = co + 4 * h + 1 < g.og ? add[4 * h + 1] : 0;
-                    t.z = co + 4 * h + 2 < g.og ? add[4 * h + 2] : 0;
-                    t.w = co + 4 * h + 3 < g.og ? add[4 * h + 3] : 0;
-                }
-            }
-            yv[4 * h] = t.x;
-            yv[4 * h + 1] = t.y;
-            yv[4 * h + 2] = t.z;
-            yv[4 * h + 3] = t.w;
-        }
-        // this lane's column: the window offset of its listed position (an entry beyond the list repeats its first; its
-        // sums are not read)
-        const bool work = first + 32 * tile < cnt && kpart < nk;  // (the same in every lane)
-        const int ent = first + 32 * tile + n;
-        const int q = list[ent < cnt ? ent : 0], oyl = q / g.wo;
-        const int lbase = ((oyl * g.stride) * g.btw_in + (q - oyl * g.wo) * g.stride) * g.bpitch + khalf;
-        v16f acc[2];
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
-#pragma unroll 1
-        for (int k0 = kpart; work && k0 < nk; k0 += BAND_KU * 4) {
-            if (k0 != kpart) load_frags(k0);
-#pragma unroll
-            for (int i = 0; i < BAND_KU; ++i) {
-                const int k = k0 + i * 4;
-                if (k >= nk) break;
-                const int tap = (int)udiv_magic((unsigned int)k, (unsigned int)nkt, g.magic_nkt), st = k - tap * nkt;
-                const int ky = (int)udiv_magic((unsigned int)tap, (unsigned int)g.kw, g.magic_kw), kx = tap - ky * g.kw;
-                const int off = (ky * g.btw_in + kx) * g.bpitch + 2 * st;
-                const v8i d = expand_e2m1(A[lbase + off], B[lbase + off]);
-#pragma unroll
-                for (int c = 0; c < 2; ++c) acc[c] = mma_e2m1(w[i][c], d, acc[c]);
-            }
-        }
-        if (nk > BAND_KU * 4 && first + nsplit * 64 < cnt) load_frags(kpart);  // (the next pass')
-        if (work) {
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    atomicAdd(&red[(32 * tile + n) * BAND_RP + 32 * c + 8 * (r >> 2) + 4 * khalf + (r & 3)], (int)acc[c][r]);
-        }
-        __syncthreads();
-        int v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            v[k] = yv[k] + (DENSE ? 1 : 2) * red[(tid >> 3) * BAND_RP + c8 + k];
-            red[(tid >> 3) * BAND_RP + c8 + k] = 0;
-        }
-        if (e < cnt) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (vec) {
-                    if (co + 4 * h < g.og)
-                        reinterpret_cast<int4*>(yp)[h] = make_int4(v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]);
-                } else {
-#pragma unroll
-                    for (int k = 4 * h; k < 4 * h + 4; ++k)
-                        if (co + k < g.og) yp[k] = v[k];
-                }
-            }
-        }
-        __syncthreads();  // (the sums are cleared for the next pass)
-    }
     if (FUSED) {
         // commit: the stream's last workgroup to finish staging
-        if (tid == 0) s_prev = arrived_before;
-        __syncthreads();
-        if (s_prev == (unsigned int)g.nbands * gridDim.y * (unsigned int)nsplit - 1u) {
+        lds_barrier();
+        if (s_prev == (unsigned int)(g.nbands * g.groups * nblk * nsplit) - 1u) {
             const long long words = (long long)g.h * g.w * g.wpp;  // (a multiple of four: whole 16-byte vectors)
             const uint4* src = reinterpret_cast<const uint4*>(xsrc + (long long)b * words);
             uint4* dst = reinterpret_cast<uint4*>(snap + (long long)b * words);
@@ -489,24 +659,14 @@ hipError_t launch_one(const void* xsrc, const void* flip, unsigned int* tileflag
 
 int bin_consumers(int cw, const BinGeom& g) { return g.groups * ((g.og + 4 * cw - 1) / (4 * cw)); }
 
-template <bool FUSED, bool DENSE = false>
-hipError_t launch_band(const void* xsrc, const void* flip, void* snap, unsigned int* arrive, const void* wband, const void* bias, void* y,
-                       const BinGeom& g, DevStats* stats, hipStream_t s) {
-    const int nblk = (g.og + 63) / 64;
-    // few streams: deal the band's list over several workgroups.  In a step as long as every one has a compute unit to itself: each
-    // stages the window and makes the list again, which a second one per compute unit does not repay (us with two and with one, 5 %
-    // of the values flipping: 28 x 28, 256 -> 256 channels 3 x 3, 8 streams, 13.6 and 10.8, no change 9.6 and 7.3; 4 x 350, 128 ->
-    // 256, 16 streams, 15.8 and 10.8).  Long lists of many taps lose (kernel us, 20 % of the positions: 5 x 5, 56 x 56, 128 -> 128,
-    // 8 streams, 23.8 and 26.4; 112 x 112, 64 -> 64, 4 streams, 30.1 and 32.9; no change 10.4 and 7.4, 10.5 and 8.9), and some of 1
-    // x 1 (64 x 500, 128 -> 128, 22.9 and 25.0).  The dense layer makes no list and has all positions: two per compute unit (5 x 5,
-    // 112 x 112, 128 -> 128, 2 streams, 20.0 and 24.1; 3 x 3, 56 x 56, 64 -> 64, 16 streams, 14.8 and 16.4).
-    const long long wgs = (long long)g.n * g.nbands * g.groups * nblk;
-    const int chunks = (g.band_rows * g.wo + 63) / 64;  // (a workgroup takes the list 64 entries at a time)
-    int z = (int)((DENSE ? 2 : 1) * NUM_CU / wgs);
-    z = z < 1 ? 1 : (z > chunks ? chunks : z);
-    dim3 grid((unsigned int)z, (unsigned int)(g.groups * nblk), (unsigned int)(g.n * g.nbands));
+template <bool FUSED, bool DENSE, int TILES, int KU>
+hipError_t launch_band_form(int z, const void* xsrc, const void* flip, void* snap, unsigned int* arrive, const void* wband, const void* bias,
+                            void* y, const BinGeom& geom, DevStats* stats, hipStream_t s) {
+    BinGeom g = geom;
+    g.nsplit = z;
+    dim3 grid((unsigned int)z, (unsigned int)(g.groups * ((g.og + 63) / 64)), (unsigned int)(g.n * g.nbands));
     const size_t lds = bin_band_lds_bytes(g, g.band_rows);
-    auto kern = bin_band_kernel<FUSED, DENSE>;
+    auto kern = bin_band_kernel<FUSED, DENSE, TILES, KU>;
     if (lds > 64 * 1024) {
         static std::mutex mu;
         static size_t granted = 0;
@@ -519,8 +679,33 @@ hipError_t launch_band(const void* xsrc, const void* flip, void* snap, unsigned 
     }
     hipLaunchKernelGGL(kern, grid, dim3(BAND_THREADS), lds, s, static_cast<const unsigned int*>(xsrc),
                        static_cast<const unsigned int*>(flip), static_cast<unsigned int*>(snap), arrive,
-                       static_cast<const uint4*>(wband), static_cast<const int*>(bias), static_cast<int*>(y), g, stats);
+                       static_cast<const uint2*>(wband), static_cast<const int*>(bias), static_cast<int*>(y), g, stats);
     return hipGetLastError();
+}
+
+template <bool FUSED, bool DENSE = false>
+hipError_t launch_band(const void* xsrc, const void* flip, void* snap, unsigned int* arrive, const void* wband, const void* bias, void* y,
+                       const BinGeom& g, DevStats* stats, hipStream_t s) {
+    const int nblk = (g.og + 63) / 64;
+    const long long wgs = (long long)g.n * g.nbands * g.groups * nblk;
+    const int nout = g.band_rows * g.wo;
+    // A band of at most 32 outputs (see bin_choose_shape): one tile, its K steps over all eight wavefronts.
+    if (nout <= 32 && wgs <= NUM_CU) return launch_band_form<FUSED, DENSE, 1, 9>(1, xsrc, flip, snap, arrive, wband, bias, y, g, stats, s);
+    // The dense layer lists all positions: a wavefront has tiles of its own (us with the K steps split and so: 28 x 28, 256 -> 256, 3 x
+    // 3, 64 streams, 45.4 and 34.5; 56 x 56, 64 -> 64, 32 streams, 23.3 and 17.8; 112 x 112, 128 -> 128, 5 x 5, 2 streams, 25.1 and
+    // 17.8).  Not in a step, whose lists are short and uneven (the first layer, 5 / 20 % changed, 21.0 / 36.3 split and 22.6 / 39.9 so).
+    if constexpr (DENSE)
+        if (nout > 64) return launch_band_form<FUSED, DENSE, 0, 9>(1, xsrc, flip, snap, arrive, wband, bias, y, g, stats, s);
+    // Few streams: deal the band's list over several workgroups, as long as every one has a compute unit to itself: each stages the
+    // window and makes the list again, which a second one per compute unit does not repay.
+    const int z = std::max(1, (int)std::min((long long)(nout + 63) / 64, NUM_CU / wgs));
+    // Weights of nine steps at a time, or of five where nine would fetch more that is not used (us with nine and with five, 5 % of
+    // the values flipping: 9 steps, the layer above, 21.0 and 22.3; 5 steps, 128 -> 256 channels in two groups, 22.0 and 20.1; 25
+    // steps, 14 x 14, 256 -> 256, 5 x 5, 64 streams, 19.0 and 17.8).
+    const int steps = (g.kh * g.kw * 2 * g.nslab + 3) / 4;  // of a wavefront
+    if ((steps + 8) / 9 * 9 <= (steps + 4) / 5 * 5)
+        return launch_band_form<FUSED, DENSE, 2, 9>(z, xsrc, flip, snap, arrive, wband, bias, y, g, stats, s);
+    return launch_band_form<FUSED, DENSE, 2, 5>(z, xsrc, flip, snap, arrive, wband, bias, y, g, stats, s);
 }
 
 // two launches: xsrc = the stored input after the difference kernel, flip = its flip buffer

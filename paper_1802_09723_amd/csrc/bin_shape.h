@@ -10,8 +10,7 @@ namespace rrm {
 constexpr int BIN_TILE = 8;        // output tile edge of the tile kernel
 constexpr long long BIN_TILE_MAX_LDS = 152 * 1024;  // both window copies of one tile (160 KB per workgroup, less static use)
 constexpr int BAND_WAVES = 8;      // wavefronts of a band-kernel workgroup
-constexpr int BAND_KU = 3;         // K steps whose filter fragments a wavefront has in flight
-constexpr int BAND_RP = 65;        // row pitch (words) of the 64 x 64 sums of a pass
+constexpr int BAND_RP = 65;        // row pitch (words) of the sums of a pass (at most 64 x 64)
 constexpr int BAND_SUMS = 64 * BAND_RP * 4;    // bytes of them
 constexpr long long BAND_LDS = 79 * 1024;      // LDS of a band-kernel workgroup (two per compute unit)
 constexpr long long BAND_WIDE_FRAME = 128 * 1024;  // a stream's frame up to which a wide layer has bands
@@ -39,20 +38,29 @@ struct BinGeom {
     unsigned int magic_nkt;    // same for d = 2*nslab (K steps per tap)
     unsigned int magic_kw;     // same for d = kw
     int bpitch;                // LDS words per staged position of the band kernel: `pitch`, or without its padding
+    unsigned int magic_nbands, magic_nblk, magic_wo;  // same for d = nbands, blocks of 64 channels per group, wo
+    int nsplit;                // (set by the launcher) workgroups that share a band's list
 };
 
 
 inline unsigned int bin_magic_for(int d) { return d <= 1 ? 0u : (unsigned int)((1ull << 32) / (unsigned long long)d + 1ull); }
 
 // dynamic LDS of a band-kernel workgroup with bands of band_rows output rows: the A and B words of the band's input
-// window, one flag byte per window position, the list of active output positions (16 bits each), and the sums of
+// window, its flags (a byte per window position, or less), the list of active output positions (16 bits each), and the sums of
 // a pass
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline size_t bin_band_list_offset(const BinGeom& g) {
+    const size_t npos = (size_t)g.bth_in * (size_t)g.btw_in;
+    return 2 * npos * g.bpitch * 4 + ((npos + 15) & ~(size_t)15);
+}
 inline size_t bin_band_lds_bytes(const BinGeom& g, int band_rows) {
     const size_t npos = (size_t)((band_rows - 1) * g.stride + g.kh) * (size_t)((g.wo - 1) * g.stride + g.kw);
     return 2 * npos * g.bpitch * 4 + ((npos + 15) & ~(size_t)15) + (((size_t)band_rows * g.wo * 2 + 15) & ~(size_t)15) + BAND_SUMS;
 }
 
-// Does the dense layer run the tile kernel: without bands; wide layers (4 x 1100, 128 -> 1024 channels 1 x 1, 11.4 us there and
+// Does the dense layer run the tile kernel (the times are of bands whose wavefronts split the K steps): without bands; wide layers (4 x 1100, 128 -> 1024 channels 1 x 1, 11.4 us there and
 // 15.9 on bands, 24 x 350, 128 -> 512 3 x 3, 19.8 and 18.6, 16 x 350, 128 -> 64, 16 streams, 21.4 and 23.5); and 1 x 1 filters
 // of few words, whose products are too short for what a pass of the band kernel costs beside them (us, tile and band: 14 x 14,
 // 128 -> 512 channels, 3.4 and 4.9; 16 x 320, 256 -> 256, 2 streams, 8.4 and 12.1; 112 x 112, 64 -> 64, 64 streams, 66 and 85;
@@ -107,33 +115,55 @@ inline bool bin_choose_shape(const rrm_shape& s, BinGeom& g) {
             break;
         }
     if (g.band_rows == 0) g.bpitch = g.pitch;
-    g.nbands = 1;
-    if (g.band_rows > 0) {
-        g.nbands = (g.ho + g.band_rows - 1) / g.band_rows;
+    const int tallest = g.band_rows;
+    g.vec4 = (g.wg % 4 == 0 && g.wpp % 4 == 0) ? 1 : 0;
+    // Bands of at most `tallest` rows: more of them while there are fewer than `want` workgroups and the next count's bands
+    // still have `min_rows` rows and `min_out` outputs.
+    auto cut = [&](long long want, int min_rows, int min_out) {
+        g.nbands = (g.ho + tallest - 1) / tallest;
         const long long per_band = (long long)g.n * g.groups * ((g.og + 63) / 64);
-        // (a row of a wide layer holds several passes of 64 positions: down to one row)
-        while (per_band * g.nbands < 2 * BIN_NUM_CU && g.nbands < g.ho && (wide || (g.ho + g.nbands) / (g.nbands + 1) >= 4)) ++g.nbands;
+        for (; per_band * g.nbands < want && g.nbands < g.ho; ++g.nbands) {
+            const int next = (g.ho + g.nbands) / (g.nbands + 1);
+            if (next < min_rows || (long long)next * g.wo < min_out) break;
+        }
         g.band_rows = (g.ho + g.nbands - 1) / g.nbands;
         g.nbands = (g.ho + g.band_rows - 1) / g.band_rows;
+        g.bth_in = (g.band_rows - 1) * s.stride + s.kh;
+        g.btw_in = (g.wo - 1) * s.stride + s.kw;
+        // The band kernel can run the whole step in one launch when every input position lies inside the window of
+        // the band that owns its row (band k owns input rows k*R*stride .. (k+1)*R*stride - 1, the last band the rest):
+        // then each position is compared and counted exactly once, and whole 16-byte vectors are compared.
+        const bool cols = g.btw_in - s.pad >= s.w;
+        const bool rows_mid = g.nbands == 1 || s.stride <= s.kh - s.pad;
+        const bool rows_last = (g.nbands - 1) * g.band_rows * s.stride - s.pad + g.bth_in >= s.h;
+        g.fused_ok = g.vec4 && cols && rows_mid && rows_last ? 1 : 0;
+    };
+    g.nbands = 1;
+    g.fused_ok = 0;
+    if (tallest > 0) {
+        // (a row of a wide layer holds several passes: down to one row)
+        cut(2 * BIN_NUM_CU, wide ? 1 : 4, 0);
+        // Layers that leave compute units empty even so: bands of down to half a tile of 32 positions, as long as that does not
+        // cost the single launch.  (us a step, 10 % of the values flipping, and dense, without and so: one stream, 14 x 14, 512 -> 512,
+        // 9.9 and 7.3, dense 9.1 and 7.4; 56 x 56, 128 -> 256, 9.1 and 8.8, 10.2 and 7.5; two of 14 x 14, 512 -> 512, 10.1 and 7.9, 9.3
+        // and 7.4; two of 28 x 28, 256 -> 256, 8.6 and 8.9, 9.6 and 7.4)
+        if ((long long)g.n * g.nbands * g.groups * ((g.og + 63) / 64) < BIN_NUM_CU) {
+            const BinGeom before = g;
+            cut(BIN_NUM_CU, 1, 16);
+            if (g.fused_ok < before.fused_ok) g = before;
+        }
     }
     if ((long long)g.n * g.nbands > 65535) g.band_rows = 0;  // (stream x band is the grid's z dimension)
-    g.vec4 = (g.wg % 4 == 0 && g.wpp % 4 == 0) ? 1 : 0;
     g.magic_nslab = bin_magic_for(g.nslab);
     g.magic_nkt = bin_magic_for(2 * g.nslab);
     g.magic_kw = bin_magic_for(g.kw);
     g.bth_in = ((g.band_rows > 1 ? g.band_rows : 1) - 1) * s.stride + s.kh;
     g.btw_in = (g.wo - 1) * s.stride + s.kw;
+    if (g.band_rows == 0) g.fused_ok = 0;
     g.magic_btw = bin_magic_for(g.btw_in);
-    // The band kernel can run the whole step in one launch when every input position lies inside the window of
-    // the band that owns its row (band k owns input rows k*R*stride .. (k+1)*R*stride - 1, the last band the rest):
-    // then each position is compared and counted exactly once, and whole 16-byte vectors are compared.
-    g.fused_ok = 0;
-    if (g.band_rows > 0 && g.vec4) {
-        const bool cols = g.btw_in - s.pad >= s.w;
-        const bool rows_mid = g.nbands == 1 || s.stride <= s.kh - s.pad;
-        const bool rows_last = (g.nbands - 1) * g.band_rows * s.stride - s.pad + g.bth_in >= s.h;
-        g.fused_ok = (cols && rows_mid && rows_last) ? 1 : 0;
-    }
+    g.magic_nbands = bin_magic_for(g.nbands);
+    g.magic_nblk = bin_magic_for((g.og + 63) / 64);
+    g.magic_wo = bin_magic_for(g.wo);
     return true;
 }
 

@@ -601,20 +601,18 @@ rrm_status setup_bin(rrm_layer* L, const std::vector<unsigned char>& w) {
         if (st != RRM_OK) return st;
     }
     if (g.band_rows == 0) return RRM_OK;
-    // band kernel: the weights as 4-bit floats (E2M1: 0x2 = +1, 0xA = -1) in per-lane MFMA order
-    // [group][32-channel block, padded to pairs][tap][K step of 2 words][lane] x 16 bytes: lane l -> output channel
-    // l % 32 of the block, word 2 * step + l / 32 of the group's words; nibble j of register i is bit 4j + i of the
-    // word.  Padded channels and words are zero.
-    const int nkt = 2 * g.nslab, ncb = 2 * ((g.og + 63) / 64);
-    std::vector<unsigned int> band((size_t)s.groups * ncb * ntaps * nkt * 64 * 4, 0u);
+    // band kernel: the weights' signs in per-lane MFMA order [group][64-channel block][tap][K step of 2 words][lane] x 2 words: of
+    // lane l, word 2 * step + l / 32 of the group's words, of the block's output channels l % 32 and 32 + l % 32; a bit that is set
+    // is a -1.  Padded channels and words may hold anything (no result is read, no difference is there).
+    const int nkt = 2 * g.nslab, nblk = (g.og + 63) / 64;
+    std::vector<unsigned int> band((size_t)s.groups * nblk * ntaps * nkt * 64 * 2, 0u);
     for (int grp = 0; grp < s.groups; ++grp)
         for (int co = 0; co < g.og; ++co)
             for (int tap = 0; tap < ntaps; ++tap)
                 for (int wd = 0; wd < g.wg; ++wd) {
-                    const unsigned int v = ww[(((size_t)(grp * g.og + co)) * ntaps + tap) * g.wg + wd];
-                    const int lane = co % 32 + 32 * (wd & 1);
-                    unsigned int* dst = &band[(((((size_t)(grp * ncb + co / 32)) * ntaps + tap) * nkt + wd / 2) * 64 + lane) * 4];
-                    for (int i = 0; i < 4; ++i) dst[i] = 0xAAAAAAAAu ^ ((v >> i & 0x11111111u) << 3);
+                    const size_t step = (((size_t)grp * nblk + co / 64) * ntaps + tap) * nkt + wd / 2;
+                    band[(step * 64 + co % 32 + 32 * (wd & 1)) * 2 + co % 64 / 32] =
+                        ~ww[(((size_t)(grp * g.og + co)) * ntaps + tap) * g.wg + wd];
                 }
     return upload(band.data(), band.size() * 4, &L->wband);
 }

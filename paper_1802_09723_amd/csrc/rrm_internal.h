@@ -270,7 +270,7 @@ hipError_t launch_bin_conv(int mode, int cw, const void* xsrc, const void* flip,
                            const void* wpack, const void* bias, void* y, const BinGeom& g, DevStats* stats,
                            hipStream_t s);
 int bin_consumers(int cw, const BinGeom& g);     // workgroups per tile of the binary kernel
-// wband: weights as E2M1 fragments [group][32-channel block][K step][lane] x 16 bytes (see setup_bin)
+// wband: the weights' signs in [group][64-channel block][K step][lane] x 8 bytes order (see setup_bin)
 hipError_t launch_bin_band(const void* xsrc, const void* flip, const void* wband, void* y, const BinGeom& g,
                            DevStats* stats, hipStream_t s);
 hipError_t launch_bin_band_dense(const void* x, const void* wband, const void* bias, void* y, const BinGeom& g, hipStream_t s);
