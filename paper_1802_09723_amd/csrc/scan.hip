@@ -106,9 +106,9 @@ __device__ __forceinline__ unsigned int scatter_index(const ScanGeom& g, unsigne
 // padded / folded layout.  The (row, column, channel) of the first element is divided out once and
 // then stepped.
 template <int DT>
-__device__ __forceinline__ void scatter_unit(const ScanGeom& g, long long v, uint4 w0, uint4 w1, uint4* d0, uint4* d1) {
+__device__ __forceinline__ void scatter_unit(const ScanGeom& g, unsigned int v, uint4 w0, uint4 w1, uint4* d0, uint4* d1) {
     constexpr int PV = DT == RRM_I8_I32 ? 16 : 8;
-    const unsigned int e0 = (unsigned int)v * PV;
+    const unsigned int e0 = v * PV;
     const unsigned int total = (unsigned int)g.total_elems;
     const unsigned int p = udiv_big(e0, g.r_c);
     int c = (int)(e0 - p * (unsigned int)g.c);
@@ -196,65 +196,79 @@ __global__ void repack_word_kernel(const unsigned char* __restrict__ x, unsigned
     dst[r * (unsigned int)g.wp + ix] = word;
 }
 
+// Fused scans of up to this many units read the producer's projection without waiting for the flags that say whether they have to:
+// one round trip less, for reads that are mostly not needed.  (us a step of a five-layer stack with and without, 1 / 2 / 4 streams:
+// 52.1 / 60.3 / 70.4 and 54.0 / 61.8 / 71.7; up to 65536 units, 8 streams: 87.1 and 87.4)
+constexpr long long SCAN_SPEC_UNITS = 16384;
+
+// Workgroup barrier that publishes LDS contents only (__syncthreads() would also wait for the stores)
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // FUSED: the unit's input is computed from the producer's projection (see FusedSrc; no pooling); a unit none of whose
 // source blocks was written by the producer's last step cannot have changed and is not even loaded.
-template <int DT, bool SCATTER, bool FUSED>
+// SPEC (fused, small launches): the projection is read without waiting for the flags that say whether it has to be.
+template <int DT, bool SCATTER, bool FUSED, bool SPEC>
 __device__ __forceinline__ void scan_body(const unsigned char* __restrict__ x_t, uint4* __restrict__ x_snap,
                                           uint4* __restrict__ d0, uint4* __restrict__ d1,
                                           unsigned long long* __restrict__ bitmap, unsigned int* __restrict__ tileflag,
-                                          unsigned int stamp, const ScanGeom& g, long long nvec, long long total_bytes,
+                                          unsigned int stamp, const ScanGeom& g, unsigned int nvec, unsigned int total_bytes,
                                           DevStats* __restrict__ stats_base, const FusedSrc& fs) {
     // FUSED: neighbouring workgroups read overlapping rows of the producer's projection (pooling windows), and
     // consecutive workgroup ids go to different XCDs, each with an L2 of its own: the grid is a multiple of 8
     // and workgroup id i works on block (i % 8) * (grid / 8) + i / 8, so that an XCD gets a contiguous range.
     const unsigned int blk = FUSED ? (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
-    const long long v = (long long)blk * blockDim.x + threadIdx.x;
+    const unsigned int v = blk * 256u + threadIdx.x;
     DevStats* __restrict__ stats = stats_base + (blockIdx.x & (STAT_SLOTS - 1));
-    const unsigned long long prev_mask = v < nvec ? bitmap[v >> 6] : 0ull;  // wave-uniform word
-    const unsigned int epoch = DT == RRM_BIN_I32 ? 0u : g.epoch[EPOCH_SCAN];
+    // Every lane loads, those beyond the end unit 0, so that the first thing a wavefront does is to get its loads under way, and
+    // what they all wait for is one round of the arguments.  The step's value comes through a vector load (of an address that
+    // only looks different per lane): a scalar load would be waited for ahead of the units.
+    const bool in = v < nvec;
+    const unsigned int vc = in ? v : 0u;
+    const unsigned long long prev_mask = bitmap[vc >> 6];  // (used where in)
+    uint4 a = make_uint4(0, 0, 0, 0), b = a;
+    if (!FUSED) {
+        const bool whole = in && v * 16u + 16u <= total_bytes;
+        a = *(whole ? reinterpret_cast<const uint4*>(x_t) + v : static_cast<const uint4*>(x_snap));
+        b = x_snap[vc];
+        if (in && !whole) a = load_x_guarded(x_t, (long long)v * 16, total_bytes);
+    }
+    const unsigned int epoch = DT == RRM_BIN_I32 ? 0u : g.epoch[EPOCH_SCAN + (threadIdx.x >> 8)];
     bool changed = false;
     int p0 = 0, p1 = -1;  // input positions of this unit, when it changed
     unsigned int nelem = 0, ntrunc = 0;
     float tsq = 0.f;  // truncated entries of this unit: count and sum of squares (bf16 with a threshold)
-    uint4 a = make_uint4(0, 0, 0, 0);
-    bool compare = v < nvec;
-    uint4 b_early = make_uint4(0, 0, 0, 0);
-    if (FUSED && compare) {
+    bool compare = in;
+    if (FUSED) {
         // (c_in is a multiple of 16: the unit is 16 channels of one position)
-        const unsigned int e0 = (unsigned int)v * 16u;
+        const unsigned int e0 = vc * 16u;
         const unsigned int p = udiv_big(e0, g.r_c), c0 = e0 - p * (unsigned int)g.c;
         const unsigned int bb = udiv_big(p, g.r_hw), r = p - bb * (unsigned int)(g.h * g.w);
         const int iy = (int)udiv_big(r, g.r_w), ix = (int)r - iy * g.w;
         const unsigned char* t = fs.touched + (size_t)bb * fs.sty * fs.stx;
+        const int4* yb = reinterpret_cast<const int4*>(fs.y + (((size_t)bb * fs.hy + iy) * fs.wy + ix) * g.c + c0);
         const unsigned int any = t[(iy >> fs.tshift) * fs.stx + (ix >> fs.tshift)];
-        compare = fs.fresh[0] != 0u || fs.touched_all[0] != 0u || (any & fs.epoch[0]) != 0u;
-        if (compare) {
-            b_early = x_snap[v];  // in flight together with the projection's loads
-            const int4* yb = reinterpret_cast<const int4*>(fs.y + (((size_t)bb * fs.hy + iy) * fs.wy + ix) * g.c + c0);
-            int4 w[4];
-            int best[16];
+        int4 w[4];
+        if (SPEC) {
+            b = x_snap[vc];
 #pragma unroll
             for (int q = 0; q < 4; ++q) w[q] = yb[q];
+        }
+        compare = in && (fs.fresh[0] != 0u || fs.touched_all[0] != 0u || (any & fs.epoch[0]) != 0u);
+        if (compare) {
+            if (!SPEC) {
+                b = x_snap[v];  // in flight together with the projection's loads
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                best[4 * q + 0] = max(0, w[q].x);
-                best[4 * q + 1] = max(0, w[q].y);
-                best[4 * q + 2] = max(0, w[q].z);
-                best[4 * q + 3] = max(0, w[q].w);
+                for (int q = 0; q < 4; ++q) w[q] = yb[q];
             }
+            auto f = [&](int x) __attribute__((always_inline)) { return (unsigned int)min(127, max(0, x) >> fs.shift); };
             unsigned int wds[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                wds[q] = (unsigned int)min(127, best[4 * q] >> fs.shift) | (unsigned int)min(127, best[4 * q + 1] >> fs.shift) << 8 |
-                         (unsigned int)min(127, best[4 * q + 2] >> fs.shift) << 16 |
-                         (unsigned int)min(127, best[4 * q + 3] >> fs.shift) << 24;
+            for (int q = 0; q < 4; ++q) wds[q] = f(w[q].x) | f(w[q].y) << 8 | f(w[q].z) << 16 | f(w[q].w) << 24;
             a = make_uint4(wds[0], wds[1], wds[2], wds[3]);
         }
     }
-    if (v < nvec) {
+    if (in) {
       if (compare) {
-        if (!FUSED) a = load_x_guarded(x_t, v * 16, total_bytes);
-        const uint4 b = FUSED ? b_early : x_snap[v];
         const unsigned int za = a.x ^ b.x, zb = a.y ^ b.y, zc = a.z ^ b.z, zd = a.w ^ b.w;
         changed = (za | zb | zc | zd) != 0u;
         if (changed) {
@@ -350,14 +364,13 @@ __device__ __forceinline__ void scan_body(const unsigned char* __restrict__ x_t,
         if (p0 <= p1) mark_subtiles(g, (unsigned int)p0, (unsigned int)p1, reinterpret_cast<unsigned char*>(tileflag), (unsigned char)epoch);
     }
     const unsigned long long mask = __ballot(changed);
-    if ((threadIdx.x & 63) == 0 && v < nvec) bitmap[v >> 6] = mask;
+    if ((threadIdx.x & 63) == 0 && in) bitmap[v >> 6] = mask;
     // change counts: summed over the wavefront, then over the workgroup, one pair of atomics per workgroup
     // (atomics on one address serialise: a pair per wavefront was the slowest part of a busy scan)
     __shared__ unsigned int s_ne[4], s_nu[4], s_nt[4];
     __shared__ float s_tq[4];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) nelem += __shfl_xor(nelem, o);
-    if (DT == RRM_BF16_F32) {
+    if (mask) nelem = (unsigned int)__builtin_amdgcn_readlane((int)wave_scan(nelem), 63);
+    if (DT == RRM_BF16_F32 && __any(ntrunc != 0u)) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
             ntrunc += __shfl_xor(ntrunc, o);
@@ -370,7 +383,7 @@ __device__ __forceinline__ void scan_body(const unsigned char* __restrict__ x_t,
         s_nt[threadIdx.x >> 6] = ntrunc;
         s_tq[threadIdx.x >> 6] = tsq;
     }
-    __syncthreads();
+    lds_barrier();
     if (threadIdx.x == 0) {
         const unsigned int ne = s_ne[0] + s_ne[1] + s_ne[2] + s_ne[3], nu = s_nu[0] + s_nu[1] + s_nu[2] + s_nu[3];
         if (nu) {
@@ -390,14 +403,14 @@ __device__ __forceinline__ void scan_body(const unsigned char* __restrict__ x_t,
     }
 }
 
-template <int DT, bool SCATTER, bool FUSED>
+template <int DT, bool SCATTER, bool FUSED, bool SPEC = false>
 __global__ __launch_bounds__(256) void scan_kernel(const unsigned char* __restrict__ x_t, uint4* __restrict__ x_snap,
                                                    uint4* __restrict__ d0, uint4* __restrict__ d1,
                                                    unsigned long long* __restrict__ bitmap,
                                                    unsigned int* __restrict__ tileflag, unsigned int stamp,
-                                                   ScanGeom g, long long nvec, long long total_bytes,
+                                                   ScanGeom g, unsigned int nvec, unsigned int total_bytes,
                                                    DevStats* __restrict__ stats_base, FusedSrc fs) {
-    scan_body<DT, SCATTER, FUSED>(x_t, x_snap, d0, d1, bitmap, tileflag, stamp, g, nvec, total_bytes, stats_base, fs);
+    scan_body<DT, SCATTER, FUSED, SPEC>(x_t, x_snap, d0, d1, bitmap, tileflag, stamp, g, nvec, total_bytes, stats_base, fs);
 }
 
 // The pooled fused form: every unit is the largest of nine positions of the producer's projection, nine times 64 bytes.  Four
@@ -408,7 +421,7 @@ __global__ __launch_bounds__(256) void scan_kernel(const unsigned char* __restri
 // with ITER = 4 the lanes first look after a unit each -- its place, whether it can have changed -- and hand that to the four
 // that compute it, and groups with nothing to do are skipped.  The unpooled form, one 64-byte read per unit, is at the rate of
 // the memory as it is: 25.1 us a launch in scan_body's form, 27.4 in this one (13 x 13 x 384, 512 streams).
-template <int ITER>
+template <int ITER, bool SPEC>
 __global__ __launch_bounds__(256) void scan_pooled_kernel(unsigned int* __restrict__ x_snap, unsigned int* __restrict__ d0,
                                                           unsigned long long* __restrict__ bitmap, unsigned char* __restrict__ flags,
                                                           ScanGeom g, unsigned int nvec, DevStats* __restrict__ stats_base, FusedSrc fs) {
@@ -423,12 +436,20 @@ __global__ __launch_bounds__(256) void scan_pooled_kernel(unsigned int* __restri
     const unsigned int v = v0 + (unsigned int)(ITER == 1 ? lane >> 2 : lane);
     unsigned int p = 0, off = 0;
     bool compare = v < nvec;
+    unsigned int b_early = 0;
+    int4 w_early[3][3];
     if (compare) {
         const unsigned int e0 = v * 16u;
         p = udiv_big(e0, g.r_c);
         const unsigned int c0 = e0 - p * (unsigned int)g.c, bb = udiv_big(p, g.r_hw), r = p - bb * (unsigned int)(g.h * g.w);
         const int iy = (int)udiv_big(r, g.r_w), ix = (int)r - iy * g.w, y0 = 2 * iy, x0 = 2 * ix;
         off = ((bb * (unsigned int)fs.hy + (unsigned int)y0) * (unsigned int)fs.wy + (unsigned int)x0) * (unsigned int)g.c + c0;
+        if (SPEC) {
+            b_early = x_snap[4u * v0 + (unsigned int)lane];
+            const int* yb = fs.y + off + 4u * (unsigned int)(lane & 3);
+#pragma unroll
+            for (int k = 0; k < 9; ++k) w_early[k / 3][k % 3] = *reinterpret_cast<const int4*>(yb + (size_t)(k / 3 * fs.wy + k % 3) * (unsigned int)g.c);
+        }
         const unsigned char* t = fs.touched + (size_t)bb * fs.sty * fs.stx;
         const int sy0 = y0 >> fs.tshift, sy1 = (y0 + 2) >> fs.tshift, sx0 = x0 >> fs.tshift, sx1 = (x0 + 2) >> fs.tshift;
         unsigned int any = 0;
@@ -453,7 +474,7 @@ __global__ __launch_bounds__(256) void scan_pooled_kernel(unsigned int* __restri
         }
         unsigned int a = 0, b = 0;
         if (act) {
-            b = x_snap[dw];
+            if (!SPEC) b = x_snap[dw];
             const char* yb = reinterpret_cast<const char*>(fs.y);
             const unsigned int vo = (o + 4u * (unsigned int)(lane & 3)) * 4u;
             int4 w[3][3];
@@ -461,7 +482,8 @@ __global__ __launch_bounds__(256) void scan_pooled_kernel(unsigned int* __restri
             for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
                 for (int dx = 0; dx < 3; ++dx)
-                    w[dy][dx] = *reinterpret_cast<const int4*>(yb + (size_t)(dy * fs.wy + dx) * (unsigned int)g.c * 4u + vo);
+                    w[dy][dx] = SPEC ? w_early[dy][dx] : *reinterpret_cast<const int4*>(yb + (size_t)(dy * fs.wy + dx) * (unsigned int)g.c * 4u + vo);
+            if (SPEC) b = b_early;
             int best[4] = {0, 0, 0, 0};
 #pragma unroll
             for (int dy = 0; dy < 3; ++dy)
@@ -500,14 +522,13 @@ __global__ __launch_bounds__(256) void scan_pooled_kernel(unsigned int* __restri
         if (g.sty > 0) mark_subtiles(g, p, p, flags, (unsigned char)epoch);  // (the position-gather kernel reads the bitmap)
     __shared__ unsigned int s_ne[4];
     __shared__ unsigned long long s_mask[4];
-#pragma unroll
-    for (int k = 32; k > 0; k >>= 1) nelem += __shfl_xor(nelem, k);
+    if (mask) nelem = (unsigned int)__builtin_amdgcn_readlane((int)wave_scan(nelem), 63);
     if (lane == 0) {
         s_ne[wave] = nelem;
         s_mask[wave] = mask;
         if (ITER == 4 && v0 < nvec) bitmap[v0 >> 6] = mask;
     }
-    __syncthreads();
+    lds_barrier();
     if (threadIdx.x == 0) {
         DevStats* stats = stats_base + (blockIdx.x & (STAT_SLOTS - 1));
         if (ITER == 1 && v0 < nvec) bitmap[v0 >> 6] = s_mask[0] | s_mask[1] << 16 | s_mask[2] << 32 | s_mask[3] << 48;
@@ -557,7 +578,7 @@ hipError_t launch_scan(int dtype, const void* x_t, void* x_snap, void* d0, void*
     const FusedSrc none{};
 #define RRM_SCAN(DTV, SC)                                                                                               \
     hipLaunchKernelGGL((scan_kernel<DTV, SC, false>), grid, block, 0, s, xt, (uint4*)x_snap, (uint4*)d0, (uint4*)d1, bitmap, \
-                       tileflag, stamp, g, nvec, total_bytes, stats, none)
+                       tileflag, stamp, g, (unsigned int)nvec, (unsigned int)total_bytes, stats, none)
     if (dtype == RRM_I8_I32) {
         if (g.scatter) RRM_SCAN(RRM_I8_I32, true); else RRM_SCAN(RRM_I8_I32, false);
     } else if (dtype == RRM_BF16_F32) {
@@ -581,14 +602,14 @@ hipError_t launch_scan_fused(const FusedSrc& src, void* x_snap, void* d0, unsign
         const bool small = nvec <= 131072;
         const unsigned int units = small ? 64u : 256u;  // of a workgroup
         const dim3 grid(((unsigned int)nvec + units * 8 - 1) / (units * 8) * 8);
-        auto kern = small ? scan_pooled_kernel<1> : scan_pooled_kernel<4>;
+        auto kern = nvec <= SCAN_SPEC_UNITS ? scan_pooled_kernel<1, true> : small ? scan_pooled_kernel<1, false> : scan_pooled_kernel<4, false>;
         hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, (unsigned int*)x_snap, (unsigned int*)d0, bitmap, (unsigned char*)marks, g,
                            (unsigned int)nvec, stats, src);
     } else {
         const long long blocks = ((nvec + 255) / 256 + 7) / 8 * 8;  // a multiple of the 8 XCDs (see the kernel)
-        hipLaunchKernelGGL((scan_kernel<RRM_I8_I32, false, true>), dim3((unsigned int)blocks), dim3(256), 0, s,
-                           (const unsigned char*)nullptr, (uint4*)x_snap, (uint4*)d0, (uint4*)nullptr, bitmap, marks, 0u, g, nvec,
-                           total_bytes, stats, src);
+        auto kern = nvec <= SCAN_SPEC_UNITS ? scan_kernel<RRM_I8_I32, false, true, true> : scan_kernel<RRM_I8_I32, false, true, false>;
+        hipLaunchKernelGGL(kern, dim3((unsigned int)blocks), dim3(256), 0, s, (const unsigned char*)nullptr, (uint4*)x_snap, (uint4*)d0,
+                           (uint4*)nullptr, bitmap, marks, 0u, g, (unsigned int)nvec, (unsigned int)total_bytes, stats, src);
     }
     return hipGetLastError();
 }

@@ -213,17 +213,21 @@ def test_active_subtiles_of_consecutive_steps(m, n):
     layer.destroy()
 
 
-# The pooled scan of a layer fed by the layer before: one group of 16 units per wavefront, and four where the input is large.
-# (producer's map, channels, streams): units off the 16s, the 64s and the workgroups, both sides of the line, one unit in all.
+# The scan of a layer fed by the layer before, pooled and not: one group of 16 units per wavefront, and four where the input is
+# large (pooled); loads ahead of the flags where it is small.  (producer's map, channels, streams): units off the 16s, the 64s and
+# the workgroups, both sides of the lines, one unit in all.
 # The producer's frame changes, stays (the difference buffer is cleared) and changes elsewhere; every count is the frame's own.
-@pytest.mark.parametrize("m,c,n", [(3, 16, 1), (11, 48, 3), (55, 16, 2), (29, 32, 40), (55, 16, 180)])
-def test_pooled_scan_of_a_fused_step(m, c, n):
+@pytest.mark.parametrize("m,c,n,pool", [
+    (3, 16, 1, True), (11, 48, 3, True), (55, 16, 2, True), (29, 32, 40, True), (29, 48, 40, True), (55, 16, 180, True),
+    (1, 16, 1, False), (11, 48, 3, False), (29, 32, 9, False), (29, 32, 12, False),
+])
+def test_scan_of_a_fused_step(m, c, n, pool):
     import numpy as np
     import oracle
     import paper_1802_09723_amd as rrm
     from gpu_util import assert_matches, to_device
     rng = np.random.default_rng(m + n)
-    s1, q = S.conv_shape(m, m, 16, c, 3, 1, 1, 1, n=n), (m - 3) // 2 + 1
+    s1, q = S.conv_shape(m, m, 16, c, 3, 1, 1, 1, n=n), (m - 3) // 2 + 1 if pool else m
     s2 = S.conv_shape(q, q, c, 24, 3 if q > 1 else 1, 1, 1 if q > 1 else 0, 1, n=n)
     w1, w2 = (rng.integers(-127, 128, (s.c_out, s.kh, s.kw, s.c_in), dtype=np.int8) for s in (s1, s2))
     b1, b2 = (rng.integers(-1000, 1001, s.c_out).astype(np.int32) for s in (s1, s2))
@@ -238,8 +242,8 @@ def test_pooled_scan_of_a_fused_step(m, c, n):
         ya = oracle.dense(s1, S.I8, w1, b1, x) if t != 2 else ya
         if shift is None:
             shift = oracle.calibrate_shift(ya)
-        B.step_from_projection(A, shift, True)
-        f = oracle.relu_requant_pool(ya, shift, True)
+        B.step_from_projection(A, shift, pool)
+        f = oracle.relu_requant_pool(ya, shift, pool)
         st = B.stats()
         units = int((f != old).reshape(-1, 16).any(axis=1).sum())
         assert (st["changed_elems"] - seen[0], st["changed_units"] - seen[1]) == (int((f != old).sum()), units), f"step {t}"
