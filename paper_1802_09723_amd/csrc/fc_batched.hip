@@ -2,15 +2,12 @@
 // streams' vectors [c_in x n], and it runs on the matrix cores with W read once for all streams.
 //
 // Dense layer (Eq. 3, FC form):      Y = b + W X^T
-// Delta step (Algorithm 1, FC branch), int8: Y += W D^T with D = X_t - X_{t-1} for all streams, in two launches:
-//   fc_diff_kernel     writes D (the byte differences), commits the stored input and counts the changes;
-//   fc_bt_kernel       multiplies.  With tens of streams the union of the changed columns is most of the matrix
-//                      (64 streams at 1 % each already touch half of the columns), so the product runs over all of
-//                      W: its cost is one pass over W whatever the density, a tenth of what n separate column walks
-//                      cost at 64 streams.
-// bf16: the fp32 difference of two bf16 values needs two bf16 terms (hi and lo), so the delta product would be two
-// passes of matrix instructions for the same pass over W that the layer itself takes; the step therefore commits,
-// counts and recomputes Y = b + W X_t^T (which is also free of the step-to-step rounding of an accumulated sum).
+// Delta step (Algorithm 1, FC branch): with tens of streams the union of the changed columns is most of the matrix (64
+// streams at 1 % each already touch half of the columns), so a product of the differences would run over all of W: its
+// cost is one pass over W whatever the density, a tenth of what n separate column walks cost at 64 streams -- and the
+// layer itself takes the same pass (a bf16 difference, which needs two bf16 terms, two).  The step therefore recomputes
+// Y = b + W X_t^T, which for integers is the same sum and for bf16 free of the step-to-step rounding of an accumulated one,
+// and commits and counts the frame.
 // Shapes: v_mfma_i32_16x16x64_i8 / v_mfma_f32_16x16x32_bf16.  Lane l of a wavefront supplies 16 bytes of A (row
 // l % 16 of a 16-row block of W, k-group l / 16: contiguous in W's own row-major layout) and 16 bytes of B (stream
 // l % 16 of a 16-stream tile, same k-group: contiguous in a stream's vector), and receives rows 4 (l / 16) .. + 3
@@ -33,84 +30,55 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 
-// D = x_t - x_snap for every stream, x_snap <- x_t, change counts.  One thread per 16-byte unit.  !WRITE_D: the commit
-// and the counts only (the step recomputes the layer from x_t).
-template <int DT, bool WRITE_D>
-__global__ __launch_bounds__(256) void fc_diff_kernel(const uint4* __restrict__ x_t, uint4* __restrict__ x_snap,
-                                                      uint4* __restrict__ d0, uint4* __restrict__ d1, long long nvec,
-                                                      unsigned long long n_cin, DevStats* __restrict__ stats) {
-    const long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+// x_snap <- x_t for every stream, change counts.  One thread per 16-byte unit.
+struct FcCommit {
+    const uint4* x_t;
+    uint4* x_snap;
+    long long nvec;
+    unsigned long long n_cin;
+    DevStats* stats;
+};
+template <int DT>
+__device__ __forceinline__ void fc_commit(unsigned int block, const FcCommit& c) {
+    const long long v = (long long)block * 256 + threadIdx.x;
     unsigned int nchanged = 0;
-    if (v < nvec) {
-        const uint4 a = x_t[v], s = x_snap[v];
-        uint4 hi = make_uint4(0, 0, 0, 0), lo = hi;
+    if (v < c.nvec) {
+        const uint4 a = c.x_t[v], s = c.x_snap[v];
         if ((a.x ^ s.x) | (a.y ^ s.y) | (a.z ^ s.z) | (a.w ^ s.w)) {
             const unsigned int aw[4] = {a.x, a.y, a.z, a.w}, sw[4] = {s.x, s.y, s.z, s.w};
-            unsigned int hw[4], lw[4] = {0u, 0u, 0u, 0u};
-            if (DT == RRM_I8_I32) {
-                const unsigned int H = 0x80808080u;
-                unsigned int ovf = 0;
+            unsigned int ovf = 0;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    // byte-wise wrapping subtraction and its signed-overflow mask
-                    const unsigned int d = ((aw[i] | H) - (sw[i] & ~H)) ^ ((aw[i] ^ ~sw[i]) & H);
-                    ovf |= (aw[i] ^ sw[i]) & (aw[i] ^ d) & H;
-                    hw[i] = d;
-                    const unsigned int z = aw[i] ^ sw[i];
+            for (int i = 0; i < 4; ++i) {
+                const unsigned int z = aw[i] ^ sw[i];
+                if (DT == RRM_I8_I32) {
+                    // byte-wise wrapping subtraction, for its signed-overflow mask
+                    const unsigned int H = 0x80808080u, d = ((aw[i] | H) - (sw[i] & ~H)) ^ ((aw[i] ^ ~sw[i]) & H);
+                    ovf |= z & (aw[i] ^ d) & H;
                     nchanged += __popc((((z & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | z) & H);
-                }
-                if (ovf) atomicOr(&stats->range_error, 1u);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    unsigned int h2 = 0, l2 = 0;
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        const unsigned int xa = (aw[i] >> (16 * k)) & 0xFFFFu, xb = (sw[i] >> (16 * k)) & 0xFFFFu;
-                        if (xa == xb) continue;
-                        ++nchanged;
-                        if (!WRITE_D) continue;
-                        const float d = __uint_as_float(xa << 16) - __uint_as_float(xb << 16);
-                        // round-to-nearest-even bf16 of d, and of what is left
-                        auto to_bf16 = [](float f) {
-                            const unsigned int u = __float_as_uint(f);
-                            return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-                        };
-                        const unsigned int h = to_bf16(d);
-                        const unsigned int l = to_bf16(d - __uint_as_float(h << 16));
-                        h2 |= (h & 0xFFFFu) << (16 * k);
-                        l2 |= (l & 0xFFFFu) << (16 * k);
-                    }
-                    hw[i] = h2;
-                    lw[i] = l2;
+                } else {
+                    nchanged += ((z & 0xFFFFu) != 0u) + (z > 0xFFFFu);
                 }
             }
-            hi = make_uint4(hw[0], hw[1], hw[2], hw[3]);
-            lo = make_uint4(lw[0], lw[1], lw[2], lw[3]);
-            x_snap[v] = a;
-        }
-        if (WRITE_D) {
-            d0[v] = hi;
-            if (DT == RRM_BF16_F32) d1[v] = lo;
+            if (ovf) atomicOr(&c.stats->range_error, 1u);
+            c.x_snap[v] = a;
         }
     }
     // counts: wavefront, then workgroup, then one set of atomics
     __shared__ unsigned int s_n[4];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) nchanged += __shfl_xor(nchanged, o);
+    if (__any(nchanged != 0u)) nchanged = (unsigned int)__builtin_amdgcn_readlane((int)wave_scan(nchanged), 63);
     if ((threadIdx.x & 63) == 0) s_n[threadIdx.x >> 6] = nchanged;
     __syncthreads();
     if (threadIdx.x == 0) {
         const unsigned int tot = s_n[0] + s_n[1] + s_n[2] + s_n[3];
         if (tot) {
-            DevStats* slot = stats + (blockIdx.x & (STAT_SLOTS - 1));
+            DevStats* slot = c.stats + (block & (STAT_SLOTS - 1));
             atomicAdd(&slot->changed_elems, (unsigned long long)tot);
             atomicAdd(&slot->changed_units, (unsigned long long)tot);
             atomicAdd(&slot->active_tiles, (unsigned long long)tot);
         }
-        if (blockIdx.x == 0) {  // one launch = one delta step
-            atomicAdd(&stats->delta_steps, 1ull);
-            atomicAdd(&stats->total_tiles, n_cin);
+        if (block == 0) {  // one launch = one delta step
+            atomicAdd(&c.stats->delta_steps, 1ull);
+            atomicAdd(&c.stats->total_tiles, c.n_cin);
         }
     }
 }
@@ -266,13 +234,20 @@ __global__ __launch_bounds__(256) void fc_bt_kernel(const unsigned char* __restr
     }
 }
 
-// y = base + the splits' sums, added in the order of the splits (bit-reproducible fp32); base: y itself (delta step)
-// or the bias.  One thread per four consecutive output channels of one stream.
-template <int DT, bool DELTA>
+// y = bias + the splits' sums, added in the order of the splits (bit-reproducible fp32).  One thread per four consecutive output
+// channels of one stream.  y_out: the caller's copy, or nullptr.  COMMIT: the workgroups behind the `blocks` of the reduction commit and count the frame.  (In a launch of
+// its own ahead of the product: a step of 9216 -> 4096 bf16, 64 streams, 24.9 -> 22.5 us; int8, where that launch also wrote the
+// differences and the sums went onto y, 18.7 -> 16.0.)
+template <int DT, bool COMMIT>
 __global__ __launch_bounds__(256) void fc_bt_reduce_kernel(const void* __restrict__ part_v, const void* __restrict__ bias_v,
-                                                           void* y_v, long long nvec, int c_out4, int splits) {
+                                                           void* y_v, void* y_out, long long nvec, int c_out4, int splits,
+                                                           unsigned int blocks, FcCommit cm) {
+    if (COMMIT && blockIdx.x >= blocks) {
+        fc_commit<DT>(blockIdx.x - blocks, cm);
+        return;
+    }
     typedef typename std::conditional<DT == RRM_I8_I32, v4i, v4f>::type acc_t;
-    const long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long v = (long long)blockIdx.x * 256 + threadIdx.x;
     if (v >= nvec) return;
     const acc_t* part = static_cast<const acc_t*>(part_v);
     acc_t sum = part[v];
@@ -283,16 +258,13 @@ __global__ __launch_bounds__(256) void fc_bt_reduce_kernel(const void* __restric
     }
     acc_t* y = static_cast<acc_t*>(y_v);
     acc_t base;
-    if (DELTA) {
-        base = y[v];
-    } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) base[i] = 0;
-        if (bias_v) base = static_cast<const acc_t*>(bias_v)[v % c_out4];
-    }
+    for (int i = 0; i < 4; ++i) base[i] = 0;
+    if (bias_v) base = static_cast<const acc_t*>(bias_v)[v % c_out4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) base[i] += sum[i];
     y[v] = base;
+    if (y_out) static_cast<acc_t*>(y_out)[v] = base;
 }
 
 int bt_chunk(int ntiles) { return ntiles <= 4 ? 4 : 2; }
@@ -306,8 +278,9 @@ int bt_group(int n) {
     return std::min(n, ((n + ngroups - 1) / ngroups + 15) / 16 * 16);
 }
 
-template <int DT, bool DELTA>
-void launch_batched(const void* w_rm, const void* b0, void* part, const void* bias, void* y, const FcGeom& g, hipStream_t s) {
+template <int DT>
+void launch_batched(const void* w_rm, const void* b0, void* part, const void* bias, void* y, void* y_out, const FcGeom& g,
+                    const FcCommit* commit, hipStream_t s) {
     const int esize = DT == RRM_I8_I32 ? 1 : 2;
     const int nsteps = g.c_in * esize / 64;
     const int per = bt_group(g.n);
@@ -324,6 +297,7 @@ void launch_batched(const void* w_rm, const void* b0, void* part, const void* bi
         dim3 grid((unsigned int)((g.c_out + 63) / 64), (unsigned int)splits);
         const unsigned char* p0 = static_cast<const unsigned char*>(b0) + (size_t)s0 * g.c_in * esize;
         unsigned char* yg = static_cast<unsigned char*>(y) + (size_t)s0 * g.c_out * 4;
+        unsigned char* og = y_out ? static_cast<unsigned char*>(y_out) + (size_t)s0 * g.c_out * 4 : nullptr;
 #define RRM_BT(T, C)                                                                                                  \
     if (ntiles <= T) {                                                                                                \
         hipLaunchKernelGGL((fc_bt_kernel<DT, T, C>), grid, dim3(256), 0, s, w, p0, part, gg, cps);                    \
@@ -331,8 +305,13 @@ void launch_batched(const void* w_rm, const void* b0, void* part, const void* bi
         RRM_BT(1, 4) RRM_BT(2, 4) RRM_BT(3, 4) RRM_BT(4, 4) RRM_BT(6, 2) RRM_BT(8, 2) {}
 #undef RRM_BT
         const long long nvec = (long long)gg.n * g.c_out / 4;
-        hipLaunchKernelGGL((fc_bt_reduce_kernel<DT, DELTA>), dim3((unsigned int)((nvec + 255) / 256)), dim3(256), 0, s, part, bias,
-                           yg, nvec, g.c_out / 4, splits);
+        const unsigned int blocks = (unsigned int)((nvec + 255) / 256);
+        if (commit && s0 + per >= g.n)
+            hipLaunchKernelGGL((fc_bt_reduce_kernel<DT, true>), dim3(blocks + (unsigned int)((commit->nvec + 255) / 256)), dim3(256), 0,
+                               s, part, bias, yg, og, nvec, g.c_out / 4, splits, blocks, *commit);
+        else
+            hipLaunchKernelGGL((fc_bt_reduce_kernel<DT, false>), dim3(blocks), dim3(256), 0, s, part, bias, yg, og, nvec, g.c_out / 4,
+                               splits, blocks, FcCommit{});
     }
 }
 
@@ -363,30 +342,23 @@ hipError_t launch_fc_batched_dense(int dtype, const void* w_rm, const void* x, v
                                    const FcGeom& g, hipStream_t s) {
     if (!fc_batched_ok(dtype, g)) return hipErrorInvalidValue;
     if (dtype == RRM_I8_I32)
-        launch_batched<RRM_I8_I32, false>(w_rm, x, part, bias, y, g, s);
+        launch_batched<RRM_I8_I32>(w_rm, x, part, bias, y, nullptr, g, nullptr, s);
     else
-        launch_batched<RRM_BF16_F32, false>(w_rm, x, part, bias, y, g, s);
+        launch_batched<RRM_BF16_F32>(w_rm, x, part, bias, y, nullptr, g, nullptr, s);
     return hipGetLastError();
 }
 
-hipError_t launch_fc_batched_delta(int dtype, const void* w_rm, const void* x_t, void* x_snap, void* d0, void* part,
-                                   const void* bias, void* y, const FcGeom& g, DevStats* stats, hipStream_t s) {
+hipError_t launch_fc_batched_delta(int dtype, const void* w_rm, const void* x_t, void* x_snap, void* part,
+                                   const void* bias, void* y, void* y_out, const FcGeom& g, DevStats* stats, hipStream_t s) {
     if (!fc_batched_ok(dtype, g) || g.eps != 0.0f) return hipErrorInvalidValue;
     const int esize = dtype == RRM_I8_I32 ? 1 : 2;
     const long long nvec = (long long)g.n * g.c_in * esize / 16;
     const unsigned long long n_cin = (unsigned long long)g.n * (unsigned long long)g.c_in;
-    dim3 dgrid((unsigned int)((nvec + 255) / 256)), dblock(256);
-    if (dtype == RRM_I8_I32) {
-        hipLaunchKernelGGL((fc_diff_kernel<RRM_I8_I32, true>), dgrid, dblock, 0, s, (const uint4*)x_t, (uint4*)x_snap, (uint4*)d0,
-                           (uint4*)nullptr, nvec, n_cin, stats);
-        launch_batched<RRM_I8_I32, true>(w_rm, d0, part, nullptr, y, g, s);
-    } else {
-        // bf16: the difference needs two bf16 terms, i.e. two products over all of W, while the layer itself (Eq. 3)
-        // is one -- and it does not accumulate rounding from step to step.  The step commits, counts and recomputes.
-        hipLaunchKernelGGL((fc_diff_kernel<RRM_BF16_F32, false>), dgrid, dblock, 0, s, (const uint4*)x_t, (uint4*)x_snap,
-                           (uint4*)nullptr, (uint4*)nullptr, nvec, n_cin, stats);
-        launch_batched<RRM_BF16_F32, false>(w_rm, x_t, part, bias, y, g, s);
-    }
+    const FcCommit commit{static_cast<const uint4*>(x_t), static_cast<uint4*>(x_snap), nvec, n_cin, stats};
+    if (dtype == RRM_I8_I32)
+        launch_batched<RRM_I8_I32>(w_rm, x_t, part, bias, y, y_out, g, &commit, s);
+    else
+        launch_batched<RRM_BF16_F32>(w_rm, x_t, part, bias, y, y_out, g, &commit, s);
     return hipGetLastError();
 }
 

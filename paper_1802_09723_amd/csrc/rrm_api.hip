@@ -672,11 +672,9 @@ rrm_status setup_fc(rrm_layer* L, const std::vector<unsigned char>& w) {
             L->csc_ok = true;
         }
     }
-    // many streams: the layer runs as one product on the matrix cores, from W in its own layout; int8 steps
-    // multiply the difference of all streams (d0), bf16 steps recompute from x_t
+    // many streams: the layer runs as one product on the matrix cores, from W in its own layout (steps recompute it from x_t)
     if (fc_batched_ok(L->dtype, g)) {
         if ((st = upload(w.data(), (size_t)s.c_in * s.c_out * es, &L->w_rm)) != RRM_OK) return st;
-        if (L->dtype == RRM_I8_I32 && (st = dalloc((size_t)s.n * s.c_in * es, &L->d0)) != RRM_OK) return st;
         if ((st = dalloc((size_t)fc_batched_splits(L->dtype, g) * s.n * s.c_out * 4, &L->fc_bpart)) != RRM_OK) return st;
     }
     // dense path: enough workgroups to keep memory busy (about 256 in total, at most 64 row splits per stream)
@@ -918,11 +916,15 @@ rrm_status rrm_step(rrm_layer* L, const void* x_t, void* y_out, void* hip_stream
         if ((st = prof_mark(L, 2, s)) != RRM_OK) return st;
     } else if (L->shape.kind == RRM_FC) {
         if ((st = prof_mark(L, 0, s)) != RRM_OK) return st;
+        // (the last kernel has the new projection in registers: one launch less than a copy after it)
+        const uintptr_t xa = reinterpret_cast<uintptr_t>(x_t), ya = reinterpret_cast<uintptr_t>(y_out);
+        const bool overlap = ya < xa + L->x_bytes && xa < ya + L->y_bytes;  // (then only once the frame has been read)
         if (L->w_rm && L->opt_fc_batched && !L->use_csc && L->fg.eps == 0.0f) {
-            // many streams: difference (or commit) of all streams, then one product over W (two launches; the events
-            // bracket both)
+            // many streams: one product over W, then the sums, the commit and the counts (two launches; the events bracket both)
             if ((st = prof_mark(L, 1, s)) != RRM_OK) return st;
-            RRM_HIP(launch_fc_batched_delta(L->dtype, L->w_rm, x_t, L->x_snap, L->d0, L->fc_bpart, L->bias, L->y_snap, L->fg, L->stats, s));
+            out_written = y_out && !overlap;
+            RRM_HIP(launch_fc_batched_delta(L->dtype, L->w_rm, x_t, L->x_snap, L->fc_bpart, L->bias, L->y_snap, out_written ? y_out : nullptr,
+                                            L->fg, L->stats, s));
             if ((st = prof_mark(L, 2, s)) != RRM_OK) return st;
         } else {
         if ((st = prof_mark(L, 1, s)) != RRM_OK) return st;  // (no separate scan kernel: its time is reported as 0)
@@ -932,9 +934,6 @@ rrm_status rrm_step(rrm_layer* L, const void* x_t, void* y_out, void* hip_stream
             fg.csc_row = static_cast<const unsigned short*>(L->csc_row);
             fg.csc_val = L->csc_val;
         }
-        // (the kernel has the new projection in registers: one launch less than a copy after it)
-        const uintptr_t xa = reinterpret_cast<uintptr_t>(x_t), ya = reinterpret_cast<uintptr_t>(y_out);
-        const bool overlap = ya < xa + L->x_bytes && xa < ya + L->y_bytes;  // (then only once the frame has been read)
         out_written = y_out && !overlap && fc_delta_writes_out(L->dtype, fg);
         RRM_HIP(launch_fc_delta(L->dtype, x_t, L->x_snap, L->wpack, L->y_snap, out_written ? y_out : nullptr, L->fc_arrive, fg,
                                 L->stats, s));

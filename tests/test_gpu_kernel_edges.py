@@ -174,6 +174,19 @@ def test_scatter_of_a_scans_difference(m, ci, co, k, st, pad, g, n):
         layer.destroy()
 
 
+# Many streams: the launch that sums the splits commits and counts the frame and fills the caller's copy; one group of streams and
+# several, a frame that repeats.
+@pytest.mark.parametrize("ci,co,n", [(64, 16, 16), (192, 48, 33), (1024, 80, 129), (320, 272, 300)])
+@pytest.mark.parametrize("dt", [S.I8, S.BF16])
+def test_fc_step_of_many_streams(ci, co, n, dt):
+    import numpy as np
+    seq = S.random_layer(9930 + n, S.fc_shape(ci, co, n=n), dt, T=4, frac=0.1)
+    seq.frames[2] = seq.frames[1].copy()
+    st, _ = run_sequence(seq, check_dense=(0,), y_out_frames=(0, 1, 2, 3))
+    before = [np.zeros_like(seq.frames[0])] + list(seq.frames[:-1])
+    assert st["changed_elems"] == sum(int((a != b).sum()) for a, b in zip(before, seq.frames)) and st["delta_steps"] == 4
+
+
 # The sub-tile flags carry the step's own value and are wiped a step later: what a step counts as active is what its own frame
 # changed, whatever the steps before marked.  (map, streams): flag arrays off the words of four and the vectors of 16, one
 # workgroup per flag group, one round of vectors in the work list, several, and more than stay in registers; the frames
