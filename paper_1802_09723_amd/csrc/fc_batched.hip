@@ -251,10 +251,16 @@ __global__ __launch_bounds__(256) void fc_bt_reduce_kernel(const void* __restric
     if (v >= nvec) return;
     const acc_t* part = static_cast<const acc_t*>(part_v);
     acc_t sum = part[v];
-    for (int sp = 1; sp < splits; ++sp) {
-        const acc_t o = part[(long long)sp * nvec + v];
+    for (int s0 = 1; s0 < splits; s0 += 5) {  // (five in flight)
+        acc_t o[5];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) sum[i] += o[i];
+        for (int k = 0; k < 5; ++k) o[k] = part[(long long)min(s0 + k, splits - 1) * nvec + v];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            if (s0 + k >= splits) break;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sum[i] += o[k][i];
+        }
     }
     acc_t* y = static_cast<acc_t*>(y_v);
     acc_t base;
@@ -273,9 +279,24 @@ int bt_chunk(int ntiles) { return ntiles <= 4 ? 4 : 2; }
 // k range in single steps with a barrier each and far fewer splits: two launches of 128 take half its time, W is read
 // twice)
 constexpr int BT_MAX_STREAMS = 128;
+constexpr int BT_MAX_SPLITS = 16;
 int bt_group(int n) {
     const int ngroups = (n + BT_MAX_STREAMS - 1) / BT_MAX_STREAMS;
     return std::min(n, ((n + ngroups - 1) / ngroups + 15) / 16 * 16);
+}
+
+// Splits of the k range: about one workgroup per compute unit, at least four chunks per split (what a workgroup has in flight)
+// and at most sixteen, which the sums' launch reads.  The partial sums' bytes are no bound, they stay in the caches.  (us a step,
+// held to half of W's bytes and three chunks, and so: int8 2048 -> 1024, 100 streams, 15.7 and 10.0; 300 streams, 45.8 and 27.8;
+// 4096 -> 4096, 128 streams, 18.7 and 16.6; bf16 1024 -> 512, 128 streams, 15.8 and 10.0.  With eight and with 64 splits at most:
+// bf16 9216 -> 256, 100 streams, 19.8 and 18.9, with sixteen 16.6; 4096 -> 1024 14.0, 15.4 and 15.5.)
+int fc_batched_splits(int dtype, const FcGeom& g) {
+    const int esize = dtype == RRM_I8_I32 ? 1 : 2;
+    const int n = bt_group(g.n);  // (streams of one launch)
+    const int ck = bt_chunk((n + 15) / 16);
+    const int chunks = (g.c_in * esize / 64 + ck - 1) / ck;
+    const int groups = (g.c_out + 63) / 64;
+    return std::max(1, std::min(std::min((NUM_CU + groups - 1) / groups, BT_MAX_SPLITS), (chunks + 3) / 4));
 }
 
 template <int DT>
@@ -317,18 +338,9 @@ void launch_batched(const void* w_rm, const void* b0, void* part, const void* bi
 
 }  // namespace
 
-// Splits of the k range: about one workgroup per compute unit, at least three chunks per split, and partial sums
-// (written and read once per split) of at most half the bytes of W.
-int fc_batched_splits(int dtype, const FcGeom& g) {
-    const int esize = dtype == RRM_I8_I32 ? 1 : 2;
-    const int n = bt_group(g.n);  // (streams of one launch)
-    const int ck = bt_chunk((n + 15) / 16);
-    const int chunks = (g.c_in * esize / 64 + ck - 1) / ck;
-    const int groups = (g.c_out + 63) / 64;
-    int s = (NUM_CU + groups - 1) / groups;
-    s = std::min(s, chunks / 3);
-    s = std::min(s, g.c_in * esize / (16 * n));
-    return std::max(s, 1);
+// bytes of the partial sums (the groups of streams of one call use them one after the other)
+size_t fc_batched_part_bytes(int dtype, const FcGeom& g) {
+    return (size_t)fc_batched_splits(dtype, g) * (size_t)bt_group(g.n) * (size_t)g.c_out * 4;
 }
 
 bool fc_batched_ok(int dtype, const FcGeom& g) {

@@ -675,7 +675,7 @@ rrm_status setup_fc(rrm_layer* L, const std::vector<unsigned char>& w) {
     // many streams: the layer runs as one product on the matrix cores, from W in its own layout (steps recompute it from x_t)
     if (fc_batched_ok(L->dtype, g)) {
         if ((st = upload(w.data(), (size_t)s.c_in * s.c_out * es, &L->w_rm)) != RRM_OK) return st;
-        if ((st = dalloc((size_t)fc_batched_splits(L->dtype, g) * s.n * s.c_out * 4, &L->fc_bpart)) != RRM_OK) return st;
+        if ((st = dalloc(fc_batched_part_bytes(L->dtype, g), &L->fc_bpart)) != RRM_OK) return st;
     }
     // dense path: enough workgroups to keep memory busy (about 256 in total, at most 64 row splits per stream)
     L->fc_nsplit = std::max(1, std::min(64, 256 / (fc_dense_slices(L->dtype, g) * s.n)));

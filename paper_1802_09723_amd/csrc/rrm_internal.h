@@ -253,7 +253,7 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
 // dense FC layer: row/slice split into per-split partial sums (scratch `part`: [n][splits][c_out_p] 4-byte
 // values), then y = bias + the sum of the splits in a fixed order
 bool fc_batched_ok(int dtype, const FcGeom& g);
-int fc_batched_splits(int dtype, const FcGeom& g);  // splits of the k range; part: [splits][n][c_out] 4-byte sums
+size_t fc_batched_part_bytes(int dtype, const FcGeom& g);  // of `part`: the partial sums
 hipError_t launch_fc_batched_dense(int dtype, const void* w_rm, const void* x, void* part, const void* bias, void* y,
                                    const FcGeom& g, hipStream_t s);
 hipError_t launch_fc_batched_delta(int dtype, const void* w_rm, const void* x_t, void* x_snap, void* part,
