@@ -147,15 +147,15 @@ rrm_status rrm_read_snapshot(rrm_layer* layer, void* x_dst, void* y_dst, void* h
  *                 densely every step, 3 INT8 / BF16 conv: the single-launch scatter path always (one kernel compares,
  *                 multiplies the changed input positions and adds the products into the stored projection with
  *                 atomic adds: work proportional to the changed input positions; fp32 results then depend on the
- *                 order of the adds within the layer's tolerance).  Automatic mode takes path 3 for layers with few
- *                 positions in all (one stream of a small map), where two dependent launches cost more than the work.
+ *                 order of the adds within the layer's tolerance).  Automatic mode takes path 3 for layers of few
+ *                 such adds, and there the products alone behind a scan that another layer's projection feeds.
  *   "fc_splits"   FC, dense path: number of row splits of the weight matrix, in [1, the default chosen at
  *                 create] (the partial-sum scratch is sized for the default)
- *   "fc_batched"  FC with 16 to 4096 streams (c_out a multiple of 16, rows of whole 64-byte steps): 1 (default) =
- *                 dense layer and step run as one product on the matrix cores with W read once for all streams:
- *                 an I8 step multiplies the difference of all streams (one pass over W whatever the density), a
- *                 BF16 step commits x_t and recomputes b + W x_t (its difference would need two bf16 terms, two
- *                 products); 0 = one column walk per stream as at batch 1.  Layers with a truncation threshold
+ *   "fc_batched"  FC with 4 to 4096 streams (c_out a multiple of 16, rows of whole 64-byte steps): 1 (default) =
+ *                 the dense layer runs as one product on the matrix cores with W read once for all streams, and
+ *                 so does a step where that is cheaper than the streams' column walks (many streams or output
+ *                 channels): it commits x_t and recomputes b + W x_t, one pass over W whatever the density;
+ *                 0 = one column walk per stream as at batch 1.  Layers with a truncation threshold
  *                 or "fc_sparse_weights" take the walk.
  *   "fc_sparse_weights"  FC, delta step: 1 = walk the non-zero weights of the changed columns only (pruned
  *                 models, Sec. 4.3; the (row, value) lists exist when at most half of W is non-zero at create,

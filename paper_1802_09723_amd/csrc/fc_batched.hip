@@ -350,6 +350,25 @@ bool fc_batched_ok(int dtype, const FcGeom& g) {
            (long long)g.c_in * esize * g.c_out <= 0xFFFFFFFFll;
 }
 
+// Does a step run as one product?  Its cost is a pass over W, the streams' own column walks cost by the number of their workgroups
+// (64 bytes of a stream's channels each), all of which compare their stream's row.  us a step walking, 1 / 5 / 25 % changed, and as
+// a product:
+//   int8  9216 -> 4096   4 streams   256 workgroups    9.4 / 10.2 / 14.6   12.2      8 streams   512   12.4 / 13.4 / 21.2   12.2
+//   int8  4096 -> 4096   4           256               7.2 /  7.4 /  7.7    9.5      8           512   10.1 / 10.7 / 10.9    9.4
+//   int8  2048 -> 1024  24           384               7.6 /  8.3 /  8.6    9.6     32           512    8.8 /  9.0 /  9.7    9.6
+//   int8  1024 ->  512  64           512               7.4 /  7.8 /  8.1    9.6    100           800   10.8 / 11.1 / 11.4    9.6
+//   bf16  9216 -> 4096   4           512              14.3 / 15.6 / 25.3   18.1      6           768   21.2 / 23.7 / 38.5   18.2
+//   bf16  4096 -> 4096   2           256               7.2 /  7.3 /  8.8   10.0      4           512   10.1 / 10.3 / 12.4   10.0
+//   bf16  2048 -> 2048   6           384               8.4 /  8.4 /  8.6    9.2      8           512    9.8 /  9.9 / 10.1    9.3
+// Rows of more than 16 KB: the product is dearer, the line is a quarter later.  bf16 layers of 16 and more streams always: a
+// recomputed sum carries one step's rounding, a walked one all of its steps'.
+bool fc_step_batched(int dtype, const FcGeom& g) {
+    const int esize = dtype == RRM_I8_I32 ? 1 : 2;
+    if (dtype == RRM_BF16_F32 && g.n >= 16) return true;
+    const long long workgroups = (long long)g.n * ((g.c_out_p * esize + 63) / 64);
+    return workgroups >= (g.c_in * esize > 16384 ? 640 : 512);
+}
+
 hipError_t launch_fc_batched_dense(int dtype, const void* w_rm, const void* x, void* part, const void* bias, void* y,
                                    const FcGeom& g, hipStream_t s) {
     if (!fc_batched_ok(dtype, g)) return hipErrorInvalidValue;

@@ -180,7 +180,10 @@ struct FcGeom {
     const unsigned short* csc_row;
     const void* csc_val;
 };
-constexpr int FC_BATCH_MIN_STREAMS = 16;    // from this many streams on an FC layer runs as one product on the matrix cores
+// From this many streams on an FC layer can run as one product on the matrix cores, and the dense layer does (us a stream by
+// itself and so, 4 streams: int8 9216 -> 4096 19.0 and 12.1, bf16 23.9 and 18.1, 4096 -> 4096 12.2 and 9.6, 13.9 and 10.0, smaller
+// layers level; 2 streams: 12.8 and 12.1, 16.2 and 17.9, 9.4 and 9.6, 10.1 and 9.9).  Steps: see fc_step_batched
+constexpr int FC_BATCH_MIN_STREAMS = 4;
 constexpr int FC_BATCH_MAX_STREAMS = 4096;  // (launched in groups of at most 128 streams)
 constexpr int FC_CSC_MAX_LDS = 96 * 1024;   // the pruned-weight kernel's update accumulators: c_out <= 24576
 
@@ -253,6 +256,7 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
 // dense FC layer: row/slice split into per-split partial sums (scratch `part`: [n][splits][c_out_p] 4-byte
 // values), then y = bias + the sum of the splits in a fixed order
 bool fc_batched_ok(int dtype, const FcGeom& g);
+bool fc_step_batched(int dtype, const FcGeom& g);
 size_t fc_batched_part_bytes(int dtype, const FcGeom& g);  // of `part`: the partial sums
 hipError_t launch_fc_batched_dense(int dtype, const void* w_rm, const void* x, void* part, const void* bias, void* y,
                                    const FcGeom& g, hipStream_t s);

@@ -175,8 +175,8 @@ def test_scatter_of_a_scans_difference(m, ci, co, k, st, pad, g, n):
 
 
 # Many streams: the launch that sums the splits commits and counts the frame and fills the caller's copy; one group of streams and
-# several, a frame that repeats.
-@pytest.mark.parametrize("ci,co,n", [(64, 16, 16), (192, 48, 33), (1024, 80, 129), (320, 272, 300)])
+# several, a frame that repeats; few streams of many channels, on both sides of the line.
+@pytest.mark.parametrize("ci,co,n", [(64, 16, 16), (192, 48, 33), (1024, 80, 129), (320, 272, 300), (128, 4096, 4), (64, 4096, 8), (192, 2048, 7), (128, 2064, 15)])
 @pytest.mark.parametrize("dt", [S.I8, S.BF16])
 def test_fc_step_of_many_streams(ci, co, n, dt):
     import numpy as np
