@@ -328,23 +328,38 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
             }
         }
     } else {
-        clear_lds();
-        lds_barrier();
+        // a word at a time, BATCH of them in flight per thread
+        constexpr int BATCH = 4;
         const int units = npos * wg4;
-        for (int u = tid; u < units; u += BAND_THREADS) {
-            const int hp = (int)udiv_magic((unsigned int)u, (unsigned int)wg4, g.magic_wg4), wd = u - hp * wg4;
-            const int hy = (int)udiv_magic((unsigned int)hp, (unsigned int)g.btw_in, g.magic_btw), hx = hp - hy * g.btw_in;
-            const int iy = iy0 + hy, ix = ix0 + hx;
-            unsigned int m = 0, xv = 0;
-            if (wd < g.wg && iy >= 0 && iy < g.h && ix >= 0 && ix < g.w) {
-                const long long wi = (((long long)b * g.h + iy) * g.w + ix) * g.wpp + (long long)grp * g.wg + wd;
-                m = DENSE ? 0xFFFFFFFFu : flip[wi];  // the flip buffer is zero where nothing changed
-                if (m) {
-                    xv = xsrc[wi];
-                    if (!DENSE) atomicOr(&bits[hy * bw + (hx >> 5)], 1u << (hx & 31));
+        for (int u0 = 0; u0 < units; u0 += BATCH * BAND_THREADS) {
+            unsigned int m[BATCH], xv[BATCH], at[BATCH];  // at: input position (row, column) of the word
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                m[i] = xv[i] = at[i] = 0;
+                if (u0 + i * BAND_THREADS >= units) continue;
+                const int u = u0 + i * BAND_THREADS + tid;
+                const int hp = (int)udiv_magic((unsigned int)u, (unsigned int)wg4, g.magic_wg4), wd = u - hp * wg4;
+                const int hy = (int)udiv_magic((unsigned int)hp, (unsigned int)g.btw_in, g.magic_btw), hx = hp - hy * g.btw_in;
+                const int iy = iy0 + hy, ix = ix0 + hx;
+                at[i] = (unsigned int)hy << 16 | (unsigned int)hx;
+                if (u < units && wd < g.wg && iy >= 0 && iy < g.h && ix >= 0 && ix < g.w) {
+                    const long long wi = (((long long)b * g.h + iy) * g.w + ix) * g.wpp + (long long)grp * g.wg + wd;
+                    m[i] = DENSE ? 0xFFFFFFFFu : flip[wi];  // the flip buffer is zero where nothing changed
+                    xv[i] = xsrc[wi];
                 }
             }
-            AB[hp * ip + wd] = pack_e2m1(m, m & ~xv);
+            if (u0 == 0) {
+                clear_lds();
+                lds_barrier();
+            }
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                const int u = u0 + i * BAND_THREADS + tid;
+                if (u >= units) break;
+                const int hy = (int)(at[i] >> 16), hx = (int)(at[i] & 0xFFFFu), hp = hy * g.btw_in + hx;
+                if (!DENSE && m[i]) atomicOr(&bits[hy * bw + (hx >> 5)], 1u << (hx & 31));
+                AB[hp * ip + u - hp * wg4] = pack_e2m1(m[i], m[i] & ~xv[i]);
+            }
         }
     }
     lds_barrier();
@@ -694,17 +709,23 @@ hipError_t launch_band(const void* xsrc, const void* flip, void* snap, unsigned 
     // The dense layer lists all positions: a wavefront has tiles of its own (us with the K steps split and so: 28 x 28, 256 -> 256, 3 x
     // 3, 64 streams, 45.4 and 34.5; 56 x 56, 64 -> 64, 32 streams, 23.3 and 17.8; 112 x 112, 128 -> 128, 5 x 5, 2 streams, 25.1 and
     // 17.8).  Not in a step, whose lists are short and uneven (the first layer, 5 / 20 % changed, 21.0 / 36.3 split and 22.6 / 39.9 so).
+    // Nor where workgroups have compute units to spare and a tile alone is a long chain (8 streams, 28 x 28, 448 -> 256,
+    // 72 steps, 16.4 split and 17.0; two of 55 x 55, 384 -> 480, 54 steps, 22.6 and 18.5).
+    const int nk = g.kh * g.kw * 2 * g.nslab;
     if constexpr (DENSE)
-        if (nout > 64) return launch_band_form<FUSED, DENSE, 0, 9>(1, xsrc, flip, snap, arrive, wband, bias, y, g, stats, s);
+        if (nout > 64 && (wgs > NUM_CU || nk <= 64)) return launch_band_form<FUSED, DENSE, 0, 9>(1, xsrc, flip, snap, arrive, wband, bias, y, g, stats, s);
     // Few streams: deal the band's list over several workgroups, as long as every one has a compute unit to itself: each stages the
     // window and makes the list again, which a second one per compute unit does not repay.
-    const int z = std::max(1, (int)std::min((long long)(nout + 63) / 64, NUM_CU / wgs));
-    // Weights of nine steps at a time, or of five where nine would fetch more that is not used (us with nine and with five, 5 % of
-    // the values flipping: 9 steps, the layer above, 21.0 and 22.3; 5 steps, 128 -> 256 channels in two groups, 22.0 and 20.1; 25
-    // steps, 14 x 14, 256 -> 256, 5 x 5, 64 streams, 19.0 and 17.8).
-    const int steps = (g.kh * g.kw * 2 * g.nslab + 3) / 4;  // of a wavefront
-    if ((steps + 8) / 9 * 9 <= (steps + 4) / 5 * 5)
+    const int z = std::max(1, (int)std::min((long long)(nout + 63) / 64, (DENSE ? 2 : 1) * NUM_CU / wgs));
+    // Weights of five, seven or nine of a wavefront's steps at a time, whichever fetches least that is not used (us with nine and with
+    // five, 5 % of the values flipping: 9 steps, the layer above, 21.0 and 22.3; 5 steps, 128 -> 256 channels in two groups, 22.0 and
+    // 20.1; 25 steps, 14 x 14, 256 -> 256, 5 x 5, 64 streams, 19.0 and 17.8; with five and with seven: 14 steps, 55 x 55, 384 -> 480, two
+    // streams, 18.2 and 17.8.  Eighteen, with a compute unit per workgroup: the last one 20.2).
+    const int steps = (nk + 3) / 4;
+    auto fetched = [&](int ku) { return (steps + ku - 1) / ku * ku; };
+    if (fetched(9) <= std::min(fetched(7), fetched(5)))
         return launch_band_form<FUSED, DENSE, 2, 9>(z, xsrc, flip, snap, arrive, wband, bias, y, g, stats, s);
+    if (fetched(7) <= fetched(5)) return launch_band_form<FUSED, DENSE, 2, 7>(z, xsrc, flip, snap, arrive, wband, bias, y, g, stats, s);
     return launch_band_form<FUSED, DENSE, 2, 5>(z, xsrc, flip, snap, arrive, wband, bias, y, g, stats, s);
 }
 
