@@ -75,9 +75,9 @@ inline bool bin_dense_on_tiles(const BinGeom& g) {
     return !(fills && empty && g.vec4);
 }
 
-// Fill the geometry of a binary layer.  False: the input window of one 8x8 output tile does not fit LDS (the layer
-// cannot be created).
-inline bool bin_choose_shape(const rrm_shape& s, BinGeom& g) {
+// Fill the geometry of a binary layer, for its steps or for its dense launches (only the bands differ).  False: the input
+// window of one 8x8 output tile does not fit LDS (the layer cannot be created).
+inline bool bin_choose_shape(const rrm_shape& s, BinGeom& g, bool dense = false) {
     g.n = s.n; g.h = s.h; g.w = s.w; g.c_out = s.c_out; g.kh = s.kh; g.kw = s.kw;
     g.stride = s.stride; g.pad = s.pad; g.groups = s.groups;
     g.wpp = s.c_in / 32;
@@ -117,16 +117,8 @@ inline bool bin_choose_shape(const rrm_shape& s, BinGeom& g) {
     if (g.band_rows == 0) g.bpitch = g.pitch;
     const int tallest = g.band_rows;
     g.vec4 = (g.wg % 4 == 0 && g.wpp % 4 == 0) ? 1 : 0;
-    // Bands of at most `tallest` rows: more of them while there are fewer than `want` workgroups and the next count's bands
-    // still have `min_rows` rows and `min_out` outputs.
-    auto cut = [&](long long want, int min_rows, int min_out) {
-        g.nbands = (g.ho + tallest - 1) / tallest;
-        const long long per_band = (long long)g.n * g.groups * ((g.og + 63) / 64);
-        for (; per_band * g.nbands < want && g.nbands < g.ho; ++g.nbands) {
-            const int next = (g.ho + g.nbands) / (g.nbands + 1);
-            if (next < min_rows || (long long)next * g.wo < min_out) break;
-        }
-        g.band_rows = (g.ho + g.nbands - 1) / g.nbands;
+    auto set_rows = [&](int rows) {
+        g.band_rows = rows;
         g.nbands = (g.ho + g.band_rows - 1) / g.band_rows;
         g.bth_in = (g.band_rows - 1) * s.stride + s.kh;
         g.btw_in = (g.wo - 1) * s.stride + s.kw;
@@ -138,16 +130,40 @@ inline bool bin_choose_shape(const rrm_shape& s, BinGeom& g) {
         const bool rows_last = (g.nbands - 1) * g.band_rows * s.stride - s.pad + g.bth_in >= s.h;
         g.fused_ok = g.vec4 && cols && rows_mid && rows_last ? 1 : 0;
     };
+    const long long per_band = (long long)g.n * g.groups * ((g.og + 63) / 64);
+    // Bands of at most `tallest` rows: more of them while there are fewer than `want` workgroups and the next count's bands
+    // still have `min_rows` rows and `min_out` outputs.
+    auto cut = [&](long long want, int min_rows, int min_out) {
+        g.nbands = (g.ho + tallest - 1) / tallest;
+        for (; per_band * g.nbands < want && g.nbands < g.ho; ++g.nbands) {
+            const int next = (g.ho + g.nbands) / (g.nbands + 1);
+            if (next < min_rows || (long long)next * g.wo < min_out) break;
+        }
+        set_rows((g.ho + g.nbands - 1) / g.nbands);
+    };
     g.nbands = 1;
     g.fused_ok = 0;
     if (tallest > 0) {
         // (a row of a wide layer holds several passes: down to one row)
         cut(2 * BIN_NUM_CU, wide ? 1 : 4, 0);
+        // A few workgroups over two per compute unit wait for the first ones to end: a band fewer then, as long as two thirds of
+        // those places are taken.  (us without and so, dense: 26 streams of 60 x 13, 448 -> 72, ten bands, 29.3 and 21.5; 54 of 40 x
+        // 40, 128 -> 128, 5 x 5, five, 47.9 and 36.7; 50 of 20 x 20, 256 -> 256, three, 25.0 and 19.8; but 64 of 28 x 28, 128 -> 384,
+        // two, 42.1 and 44.9.  A step, 5 % of the values flipping: 43 streams of 14 x 14, 256 -> 512, two bands, 16.0 and 11.3; the
+        // third dense layer 17.2 and 15.3; but the second 33.7 and 34.5: of many bands some are short and make room early.)  1 x 1
+        // filters keep theirs: bin_dense_on_tiles goes by the count.
+        const int fewer = g.nbands - 1;
+        if (s.kh * s.kw > 1 && per_band * g.nbands > 2 * BIN_NUM_CU && 3 * per_band * fewer >= 4 * BIN_NUM_CU &&
+            (dense ? fewer >= 2 : fewer <= 3) && (g.ho + fewer - 1) / fewer <= tallest) {
+            const BinGeom before = g;
+            set_rows((g.ho + fewer - 1) / fewer);
+            if (g.fused_ok < before.fused_ok) g = before;
+        }
         // Layers that leave compute units empty even so: bands of down to half a tile of 32 positions, as long as that does not
         // cost the single launch.  (us a step, 10 % of the values flipping, and dense, without and so: one stream, 14 x 14, 512 -> 512,
         // 9.9 and 7.3, dense 9.1 and 7.4; 56 x 56, 128 -> 256, 9.1 and 8.8, 10.2 and 7.5; two of 14 x 14, 512 -> 512, 10.1 and 7.9, 9.3
         // and 7.4; two of 28 x 28, 256 -> 256, 8.6 and 8.9, 9.6 and 7.4)
-        if ((long long)g.n * g.nbands * g.groups * ((g.og + 63) / 64) < BIN_NUM_CU) {
+        if (per_band * g.nbands < BIN_NUM_CU) {
             const BinGeom before = g;
             cut(BIN_NUM_CU, 1, 16);
             if (g.fused_ok < before.fused_ok) g = before;

@@ -63,7 +63,7 @@ struct rrm_layer {
     unsigned int* sc_arrive = nullptr;  // its arrival counters (one per position block)
     void* wband = nullptr;   // binary: weights packed for the band kernel (matrix cores)
     unsigned int* bin_arrive = nullptr;  // binary single-launch step: arrival counter per stream
-    BinGeom bg{};
+    BinGeom bg{}, bg_dense{};
     FcGeom fg{};
     // device memory
     void* wpack = nullptr;   // conv: MFMA fragment order; FC: W^T; binary: scalar-load order
@@ -579,7 +579,7 @@ rrm_status select_conv_kernel(rrm_layer* L, int which) {
 rrm_status setup_bin(rrm_layer* L, const std::vector<unsigned char>& w) {
     const rrm_shape& s = L->shape;
     BinGeom& g = L->bg;
-    if (!bin_choose_shape(s, g)) return fail(RRM_ERR_SHAPE, "input window of one output tile does not fit LDS");
+    if (!bin_choose_shape(s, g) || !bin_choose_shape(s, L->bg_dense, true)) return fail(RRM_ERR_SHAPE, "input window of one output tile does not fit LDS");
     if (g.fused_ok) {
         rrm_status st2 = dalloc((size_t)s.n * sizeof(unsigned int), (void**)&L->bin_arrive);
         if (st2 != RRM_OK) return st2;
@@ -736,7 +736,7 @@ rrm_status enqueue_dense(rrm_layer* L, const void* x, void* y, hipStream_t st) {
             RRM_HIP(launch_fc_dense(L->dtype, fc_splits(L), L->wpack, x, L->fc_part, L->bias, y, L->fg, st));
     } else if (L->dtype == RRM_BIN_I32) {
         if (!bin_dense_on_tiles(L->bg)) {
-            RRM_HIP(launch_bin_band_dense(x, L->wband, L->bias, y, L->bg, st));
+            RRM_HIP(launch_bin_band_dense(x, L->wband, L->bias, y, L->bg_dense, st));
             return RRM_OK;
         }
         RRM_HIP(launch_bin_conv(MODE_DENSE, bin_cw(L), x, nullptr, nullptr, L->wpack, L->bias, y, L->bg, L->stats, st));

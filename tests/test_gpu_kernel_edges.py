@@ -71,6 +71,17 @@ def test_binary_band_kernel_forms(h, w, ci, co, k, st, pad, g, n, frac):
     run_sequence(seq, check_dense=(0, 2), check_frames=(0, 2))
 
 
+# A band fewer where bands make a few workgroups over two per compute unit: in the step and the dense launch, in one of them (many
+# bands; one band left), with strides and words off the 16-byte vectors (two launches).
+@pytest.mark.parametrize("h,w,ci,co,k,st,pad,g,n,frac", [
+    (12, 7, 128, 8, 3, 1, 1, 1, 180, 0.1), (20, 5, 32, 8, 3, 1, 1, 1, 110, 0.1), (8, 9, 128, 5, 3, 1, 1, 1, 350, 0.1),
+    (23, 9, 128, 66, 3, 2, 1, 1, 88, 0.2), (13, 6, 96, 8, 5, 1, 2, 1, 176, 0.1), (14, 5, 256, 18, 3, 1, 1, 2, 65, 0.2),
+])
+def test_binary_bands_over_two_workgroups_per_compute_unit(h, w, ci, co, k, st, pad, g, n, frac):
+    seq = S.random_layer(9350 + h + w + n, S.conv_shape(h, w, ci, co, k, st, pad, g, n=n), S.BIN, T=3, frac=frac, block=2)
+    run_sequence(seq, check_dense=(0, 2), check_frames=(0, 2))
+
+
 # Wide binary layers: one output row fits LDS only without the padding of the staged positions.  (h, w, c_in, c_out, k,
 # stride, pad, groups, n): one row and several per band, whole 16-byte vectors and not, columns that no window reads
 # (difference kernel in front), several channel blocks, groups; the dense layer takes the tile kernel.
