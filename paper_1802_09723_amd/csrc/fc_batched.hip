@@ -234,10 +234,10 @@ __global__ __launch_bounds__(256) void fc_bt_kernel(const unsigned char* __restr
     }
 }
 
-// y = bias + the splits' sums, added in the order of the splits (bit-reproducible fp32).  One thread per four consecutive output
-// channels of one stream.  y_out: the caller's copy, or nullptr.  COMMIT: the workgroups behind the `blocks` of the reduction commit and count the frame.  (In a launch of
-// its own ahead of the product: a step of 9216 -> 4096 bf16, 64 streams, 24.9 -> 22.5 us; int8, where that launch also wrote the
-// differences and the sums went onto y, 18.7 -> 16.0.)
+// y = bias + the splits' sums, added in the order of the splits (bit-reproducible fp32).  One thread per four consecutive
+// output channels of one stream.  y_out: the caller's copy, or nullptr.  COMMIT: the workgroups behind the `blocks` of the
+// reduction commit and count the frame.  (In a launch of its own ahead of the product: a step of 9216 -> 4096 bf16, 64 streams,
+// 24.9 -> 22.5 us; int8, where that launch also wrote the differences and the sums went onto y, 18.7 -> 16.0.)
 template <int DT, bool COMMIT>
 __global__ __launch_bounds__(256) void fc_bt_reduce_kernel(const void* __restrict__ part_v, const void* __restrict__ bias_v,
                                                            void* y_v, void* y_out, long long nvec, int c_out4, int splits,
