@@ -19,9 +19,9 @@
  *   Sec. 3.2 last paragraph); each has its own snapshots, weights are shared.
  *
  * Element types (rrm_dtype)
- *   RRM_I8_I32    x, weights int8; bias, y int32.  Exact.  The difference of two inputs must
+ *   RRM_I8_I32    x, weights int8; bias, y int32.  Exact.  A convolution needs differences of two inputs that
  *                 fit int8 (true whenever inputs are post-ReLU values in [0,127]); a violation
- *                 raises the sticky RRM_ERR_RANGE reported by rrm_get_stats.
+ *                 raises the sticky RRM_ERR_RANGE reported by rrm_get_stats.  FC layers take any inputs.
  *   RRM_BF16_F32  x, weights bfloat16 (16-bit patterns); bias, y float32.  Inputs must be
  *                 finite.
  *   RRM_BIN_I32   x, weights are +1/-1 values bit-packed along the channel axis into 32-bit

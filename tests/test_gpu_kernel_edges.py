@@ -198,6 +198,18 @@ def test_fc_step_of_many_streams(ci, co, n, dt):
     assert st["changed_elems"] == sum(int((a != b).sum()) for a, b in zip(before, seq.frames)) and st["delta_steps"] == 4
 
 
+# Any two int8 inputs are in range for an FC layer, whichever way its step runs: frames from the lowest value to the highest and
+# back are exact and raise no range error.  (c_out, streams): the column walk and the product, one group of streams and several.
+@pytest.mark.parametrize("co,n,product", [(48, 1, False), (48, 20, False), (4096, 8, True), (2048, 33, True), (272, 300, True)])
+def test_fc_step_of_full_range_differences(co, n, product):
+    assert (n * ((co + 63) // 64) >= 512) == product
+    seq = S.random_layer(9970 + n, S.fc_shape(192, co, n=n), S.I8, T=4, frac=0.3)
+    for t, frame in enumerate(seq.frames):
+        frame[..., -40:] = (-128, 127)[t % 2]
+    st, _ = run_sequence(seq, check_dense=())
+    assert st["range_error"] == 0
+
+
 # The sub-tile flags carry the step's own value and are wiped a step later: what a step counts as active is what its own frame
 # changed, whatever the steps before marked.  (map, streams): flag arrays off the words of four and the vectors of 16, one
 # workgroup per flag group, one round of vectors in the work list, several, and more than stay in registers; the frames
