@@ -83,13 +83,16 @@ typedef struct {
     uint64_t changed_elems;   /* input elements (binary: bits) that differed from the snapshot */
     uint64_t changed_units;   /* 16-byte input units with any difference (FC: = changed_elems) */
     uint64_t active_tiles;    /* int8 / bf16 conv: output blocks recomputed (4x4 positions for the window-tile
-                                 kernel, single positions for the position-gather kernel); binary conv: output
+                                 kernel, single positions for the position-gather kernel), or input positions
+                                 multiplied (single-launch scatter path); binary conv: output
                                  positions updated (8x8 tiles for layers without bands); FC: columns
                                  streamed */
     uint64_t total_tiles;     /* the same unit, counted as a dense step would, summed over delta steps
-                                 (FC: c_in per step) */
+                                 (FC: c_in per step).  Steps on different paths add different units: rrm_reset
+                                 between them keeps the counters apart */
     int32_t range_error;      /* non-zero once an int8 difference overflowed */
-    int32_t tile_positions;   /* output positions per tile of active_tiles / total_tiles: 16, 1, 64; FC: 0 */
+    int32_t tile_positions;   /* positions per tile of active_tiles / total_tiles, as the last enqueued step counts
+                                 them: 16, 1, 64; FC: 0 */
     uint64_t truncated_elems; /* BF16 with a threshold: differences below it (neither applied nor committed) */
     double truncated_sumsq;   /* and the sum of their squares: sum over steps of l2(u)^2 of Eq. 7's truncated maps */
 } rrm_stats;

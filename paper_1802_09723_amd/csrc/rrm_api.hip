@@ -95,6 +95,7 @@ struct rrm_layer {
     // state
     bool has_snapshot = false;
     unsigned long long steps = 0;  // rrm_step calls enqueued by the host
+    int count_positions = 16;      // int8 / bf16 conv: rrm_stats::tile_positions, by the kernel of the last step enqueued
     // event brackets of the "profile" option: 3 events per step (before scan, between, after)
     std::vector<hipEvent_t> prof_ev;
     int prof_n = 0;
@@ -567,6 +568,7 @@ rrm_status select_conv_kernel(rrm_layer* L, int which) {
     // differ widely (its fixed set-up per (stream, band) unit is paid by the static streams too, and once a
     // third of the positions change the gather saves little over whole windows): it is the caller's choice.
     L->use_pos = which == 2;
+    L->count_positions = L->use_pos ? 1 : 16;
     L->tshift = L->use_pos ? 0 : 2;
     ScanGeom& sg = L->sg;
     sg.sty = L->use_pos ? 0 : L->cg.sty;  // (no sub-tile flags for the position-gather kernel: it reads the bitmap)
@@ -964,9 +966,11 @@ rrm_status rrm_step(rrm_layer* L, const void* x_t, void* y_out, void* hip_stream
             ScatGeom sc = L->sc;
             sc.eps = L->sg.eps;
             RRM_HIP(launch_conv_scatter(L->dtype, L->opt_terms, x_t, L->x_snap, L->wsc, L->y_snap, sc, L->stats, s));
+            L->count_positions = 1;
         } else {
             RRM_HIP(launch_scan(L->dtype, x_t, L->x_snap, L->d0, L->d1, L->bitmap, L->tileflag, 0u, L->sg, L->stats, s));
             if ((st = prof_mark(L, 1, s)) != RRM_OK) return st;
+            L->count_positions = L->use_pos ? 1 : 16;
             if (L->use_pos) {
                 PosGeom pg = L->pg;
                 if (L->opt_path == 1) pg.xfull = nullptr;  // the sparse path always: no switch to recomputation
@@ -1019,6 +1023,7 @@ rrm_status rrm_step_from_projection(rrm_layer* L, rrm_layer* P, int shift, int p
     if ((rs = prof_mark(L, 0, st)) != RRM_OK) return rs;
     RRM_HIP(launch_scan_fused(src, L->x_snap, L->d0, L->bitmap, L->tileflag, L->sg, L->stats, st));
     if ((rs = prof_mark(L, 1, st)) != RRM_OK) return rs;
+    L->count_positions = L->use_pos ? 1 : 16;
     if (L->use_pos)
         RRM_HIP(launch_conv_pos(L->dtype, MODE_DELTA, 1, L->d0, L->d1, L->zero16, L->bitmap, L->ctrl, L->wpos, L->bias,
                                 L->y_snap, L->pg, L->stats, st));
@@ -1203,7 +1208,7 @@ rrm_status rrm_get_stats(rrm_layer* L, rrm_stats* out) {
     out->active_tiles = d.active_tiles;
     out->total_tiles = d.total_tiles;
     out->range_error = (int32_t)d.range_error;
-    out->tile_positions = L->shape.kind == RRM_FC ? 0 : (L->dtype == RRM_BIN_I32 ? (L->bg.band_rows > 0 ? 1 : TILE * TILE) : (L->use_pos ? 1 : 16));
+    out->tile_positions = L->shape.kind == RRM_FC ? 0 : (L->dtype == RRM_BIN_I32 ? (L->bg.band_rows > 0 ? 1 : TILE * TILE) : L->count_positions);
     out->truncated_elems = d.truncated_elems;
     out->truncated_sumsq = d.truncated_sumsq;
     if (d.range_error) return fail(RRM_ERR_RANGE, "an int8 input difference did not fit int8");

@@ -210,6 +210,28 @@ def test_fc_step_of_full_range_differences(co, n, product):
     assert st["range_error"] == 0
 
 
+# What a step counts and the unit that the statistics name go together: input positions on the single-launch scatter path (automatic
+# for layers of few adds, asked for otherwise), 4 x 4 blocks of output positions on the tile kernel.
+@pytest.mark.parametrize("m,ci,co,n,dt,path", [(20, 16, 24, 4, S.I8, 0), (9, 32, 40, 1, S.BF16, 0), (40, 96, 96, 8, S.I8, 3)])
+def test_units_of_the_step_counters(m, ci, co, n, dt, path):
+    from gpu_util import make_layer, to_device
+    seq = S.random_layer(9980 + m, S.conv_shape(m, m, ci, co, 3, 1, 1, 1, n=n), dt, T=3, frac=0.1, block=3)
+    layer = make_layer(seq, path=path)
+    changed, last = 0, 0
+    for x in seq.frames:
+        layer.step(to_device(x, dt))
+        changed += int((x != last).any(axis=3).sum())
+        last = x
+    st = layer.stats()
+    assert (st["tile_positions"], st["active_tiles"], st["total_tiles"]) == (1, changed, 3 * n * m * m)
+    layer.set_option("path", 1)
+    layer.reset()
+    layer.step(to_device(seq.frames[0], dt))
+    st = layer.stats()
+    assert (st["tile_positions"], st["active_tiles"], st["total_tiles"]) == (16,) + 2 * (n * ((m + 3) // 4) ** 2,)
+    layer.destroy()
+
+
 # The sub-tile flags carry the step's own value and are wiped a step later: what a step counts as active is what its own frame
 # changed, whatever the steps before marked.  (map, streams): flag arrays off the words of four and the vectors of 16, one
 # workgroup per flag group, one round of vectors in the work list, several, and more than stay in registers; the frames
