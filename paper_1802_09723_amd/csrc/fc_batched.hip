@@ -27,8 +27,10 @@ namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef double v4d __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
+constexpr int BT_CHAIN_TILES = 2;  // bf16 products of up to so many 16-stream tiles sum short chains (see fc_bt_kernel)
 
 // x_snap <- x_t for every stream, change counts.  One thread per 16-byte unit.  (No difference is formed: any two int8 inputs
 // are in range, as they are for the column walk with its nine-bit differences.)
@@ -124,11 +126,31 @@ __global__ __launch_bounds__(256) void fc_bt_kernel(const unsigned char* __restr
         xp[i] = (unsigned int)min(s, g.n - 1) * (unsigned int)row_bytes + (tid & 3) * 16;  // (streams beyond n: the last one's bytes, unused)
         xoff[i] = (xc * NS + s) * 5 + (tid & 3);
     }
+    // A matrix instruction rounds its fp32 sum more than once, and the error of a chain of them grows as the square root of its
+    // length.  Up to BT_CHAIN_TILES tiles a chain therefore has a chunk's CK instructions, and the chains are summed in 64 bits (relative
+    // error of 9216 -> 4096, 4 .. 15 streams, whose chains are 72 instructions long without: 2.3e-7 and 0.6e-7, the column walk's
+    // 0.9e-7; us dense 18.2 and 18.3).  More tiles' sums would cost more than they are worth (64 streams, 22.2 and 27.6 us): there
+    // the splits bound the chains, see fc_batched_splits.
+    constexpr bool CHAINS = DT == RRM_BF16_F32 && TMAX <= BT_CHAIN_TILES;
     acc_t acc[TMAX];
+    v4d total[CHAINS ? TMAX : 1];
 #pragma unroll
     for (int t = 0; t < TMAX; ++t)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[t][i] = 0;
+        for (int i = 0; i < 4; ++i) {
+            acc[t][i] = 0;
+            if constexpr (CHAINS) total[t][i] = 0;
+        }
+    auto join = [&]() __attribute__((always_inline)) {
+        if constexpr (CHAINS)
+#pragma unroll
+            for (int t = 0; t < TMAX; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    total[t][i] += (double)acc[t][i];
+                    acc[t][i] = 0;
+                }
+    };
     auto mma = [&](const uint4& a, const uint4& bb, acc_t c) {
         if constexpr (DT == RRM_I8_I32)
             return __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(v4i, a), __builtin_bit_cast(v4i, bb), c, 0, 0, 0);
@@ -198,6 +220,7 @@ __global__ __launch_bounds__(256) void fc_bt_kernel(const unsigned char* __restr
     };
     auto phase = [&](int j, int buf, Set& nxt) __attribute__((always_inline)) {
         if (j < nch) compute(acur, buf, j);
+        join();
         stage(nxt, buf ^ 1);
         take(nxt);
         issue(j + 5, nxt);
@@ -224,6 +247,9 @@ __global__ __launch_bounds__(256) void fc_bt_kernel(const unsigned char* __restr
 #pragma unroll
         for (int t = 0; t < TMAX; ++t) {
             const int s = 16 * t + (lane & 15);
+            if constexpr (CHAINS)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[t][i] = (float)total[t][i];
             if (s < g.n) *reinterpret_cast<acc_t*>(part + (long long)s * g.c_out + oc) = acc[t];
         }
     }
@@ -233,7 +259,9 @@ __global__ __launch_bounds__(256) void fc_bt_kernel(const unsigned char* __restr
 // output channels of one stream.  y_out: the caller's copy, or nullptr.  COMMIT: the workgroups behind the `blocks` of the
 // reduction commit and count the frame.  (In a launch of its own ahead of the product: a step of 9216 -> 4096 bf16, 64 streams,
 // 24.9 -> 22.5 us; int8, where that launch also wrote the differences and the sums went onto y, 18.7 -> 16.0.)
-template <int DT, bool COMMIT>
+// WIDE (bf16): the splits are summed in 64 bits, where the product kernel sums its chains so or there are many splits (64 streams of
+// 9216 -> 4096, whose four splits gain nothing by it, would take 0.2 us longer).
+template <int DT, bool COMMIT, bool WIDE>
 __global__ __launch_bounds__(256) void fc_bt_reduce_kernel(const void* __restrict__ part_v, const void* __restrict__ bias_v,
                                                            void* y_v, void* y_out, long long nvec, int c_out4, int splits,
                                                            unsigned int blocks, FcCommit cm) {
@@ -244,8 +272,13 @@ __global__ __launch_bounds__(256) void fc_bt_reduce_kernel(const void* __restric
     typedef typename std::conditional<DT == RRM_I8_I32, v4i, v4f>::type acc_t;
     const long long v = (long long)blockIdx.x * 256 + threadIdx.x;
     if (v >= nvec) return;
+    typedef typename std::conditional<WIDE, v4d, acc_t>::type sum_t;
     const acc_t* part = static_cast<const acc_t*>(part_v);
-    acc_t sum = part[v];
+    sum_t sum = __builtin_convertvector(part[v], sum_t);
+    auto add = [&](const acc_t& a) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[i] += a[i];
+    };
     for (int s0 = 1; s0 < splits; s0 += 5) {  // (five in flight)
         acc_t o[5];
 #pragma unroll
@@ -253,19 +286,14 @@ __global__ __launch_bounds__(256) void fc_bt_reduce_kernel(const void* __restric
 #pragma unroll
         for (int k = 0; k < 5; ++k) {
             if (s0 + k >= splits) break;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) sum[i] += o[k][i];
+            add(o[k]);
         }
     }
+    if (bias_v) add(static_cast<const acc_t*>(bias_v)[v % c_out4]);
+    const acc_t out = __builtin_convertvector(sum, acc_t);
     acc_t* y = static_cast<acc_t*>(y_v);
-    acc_t base;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) base[i] = 0;
-    if (bias_v) base = static_cast<const acc_t*>(bias_v)[v % c_out4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) base[i] += sum[i];
-    y[v] = base;
-    if (y_out) static_cast<acc_t*>(y_out)[v] = base;
+    y[v] = out;
+    if (y_out) static_cast<acc_t*>(y_out)[v] = out;
 }
 
 int bt_chunk(int ntiles) { return ntiles <= 4 ? 4 : 2; }
@@ -280,18 +308,21 @@ int bt_group(int n) {
     return std::min(n, ((n + ngroups - 1) / ngroups + 15) / 16 * 16);
 }
 
-// Splits of the k range: about one workgroup per compute unit, at least four chunks per split (what a workgroup has in flight)
-// and at most sixteen, which the sums' launch reads.  The partial sums' bytes are no bound, they stay in the caches.  (us a step,
-// held to half of W's bytes and three chunks, and so: int8 2048 -> 1024, 100 streams, 15.7 and 10.0; 300 streams, 45.8 and 27.8;
-// 4096 -> 4096, 128 streams, 18.7 and 16.6; bf16 1024 -> 512, 128 streams, 15.8 and 10.0.  With eight and with 64 splits at most:
-// bf16 9216 -> 256, 100 streams, 19.8 and 18.9, with sixteen 16.6; 4096 -> 1024 14.0, 15.4 and 15.5.)
-int fc_batched_splits(int dtype, const FcGeom& g) {
+// Splits of the k range of one launch of n streams: about one workgroup per compute unit, about four chunks per split (what a
+// workgroup has in flight) and at most sixteen, which the sums' launch reads.  The partial sums' bytes are no bound, they stay in
+// the caches.  (us a step, held to half of W's bytes and three chunks, and so: int8 2048 -> 1024, 100 streams, 15.7 and 10.0; 300
+// streams, 45.8 and 27.8; 4096 -> 4096, 128 streams, 18.7 and 16.6; bf16 1024 -> 512, 128 streams, 15.8 and 10.0.  With eight and
+// with 64 splits at most: bf16 9216 -> 256, 100 streams, 19.8 and 18.9, with sixteen 16.6; 4096 -> 1024 14.0, 15.4 and 15.5.)
+// More where a bf16 split's chain of matrix instructions would be longer than 16, or, with more than 64 streams, 32: the
+// rounding error of long rows is then no larger than that of short ones (see fc_bt_kernel).
+int bt_splits(int dtype, const FcGeom& g, int n) {
     const int esize = dtype == RRM_I8_I32 ? 1 : 2;
-    const int n = bt_group(g.n);  // (streams of one launch)
-    const int ck = bt_chunk((n + 15) / 16);
+    const int ntiles = (n + 15) / 16, ck = bt_chunk(ntiles);
     const int chunks = (g.c_in * esize / 64 + ck - 1) / ck;
     const int groups = (g.c_out + 63) / 64;
-    return std::max(1, std::min(std::min((NUM_CU + groups - 1) / groups, BT_MAX_SPLITS), (chunks + 3) / 4));
+    int most = BT_MAX_SPLITS;
+    if (dtype == RRM_BF16_F32 && ntiles > BT_CHAIN_TILES) most = std::max(most, ck == 4 ? (chunks + 3) / 4 : (chunks + 15) / 16);
+    return std::max(1, std::min(std::min((NUM_CU + groups - 1) / groups, most), (chunks + 3) / 4));
 }
 
 template <int DT>
@@ -307,7 +338,7 @@ void launch_batched(const void* w_rm, const void* b0, void* part, const void* bi
         const int ntiles = (gg.n + 15) / 16;
         const int ck = bt_chunk(ntiles);
         const int chunks = (nsteps + ck - 1) / ck;
-        const int want = fc_batched_splits(DT, gg);
+        const int want = bt_splits(DT, g, gg.n);
         const int cps = (chunks + want - 1) / want;
         const int splits = (chunks + cps - 1) / cps;  // (no empty split)
         dim3 grid((unsigned int)((g.c_out + 63) / 64), (unsigned int)splits);
@@ -322,20 +353,25 @@ void launch_batched(const void* w_rm, const void* b0, void* part, const void* bi
 #undef RRM_BT
         const long long nvec = (long long)gg.n * g.c_out / 4;
         const unsigned int blocks = (unsigned int)((nvec + 255) / 256);
-        if (commit && s0 + per >= g.n)
-            hipLaunchKernelGGL((fc_bt_reduce_kernel<DT, true>), dim3(blocks + (unsigned int)((commit->nvec + 255) / 256)), dim3(256), 0,
-                               s, part, bias, yg, og, nvec, g.c_out / 4, splits, blocks, *commit);
-        else
-            hipLaunchKernelGGL((fc_bt_reduce_kernel<DT, false>), dim3(blocks), dim3(256), 0, s, part, bias, yg, og, nvec, g.c_out / 4,
-                               splits, blocks, FcCommit{});
+        const bool last = commit && s0 + per >= g.n;
+        constexpr bool BF = DT == RRM_BF16_F32;
+        const bool wide = BF && (ntiles <= BT_CHAIN_TILES || splits > BT_MAX_SPLITS);
+        const auto reduce = last ? (wide ? fc_bt_reduce_kernel<DT, true, BF> : fc_bt_reduce_kernel<DT, true, false>)
+                                 : (wide ? fc_bt_reduce_kernel<DT, false, BF> : fc_bt_reduce_kernel<DT, false, false>);
+        const FcCommit cm = last ? *commit : FcCommit{};
+        hipLaunchKernelGGL(reduce, dim3(blocks + (last ? (unsigned int)((cm.nvec + 255) / 256) : 0u)), dim3(256), 0, s, part, bias, yg, og,
+                           nvec, g.c_out / 4, splits, blocks, cm);
     }
 }
 
 }  // namespace
 
-// bytes of the partial sums (the groups of streams of one call use them one after the other)
+// bytes of the partial sums (the groups of streams of one call use them one after the other; the last group can be smaller and
+// have more splits)
 size_t fc_batched_part_bytes(int dtype, const FcGeom& g) {
-    return (size_t)fc_batched_splits(dtype, g) * (size_t)bt_group(g.n) * (size_t)g.c_out * 4;
+    const int per = bt_group(g.n), last = g.n - (g.n - 1) / per * per;
+    const auto sums = [&](int n) { return (size_t)bt_splits(dtype, g, n) * (size_t)n; };
+    return std::max(sums(per), sums(last)) * (size_t)g.c_out * 4;
 }
 
 bool fc_batched_ok(int dtype, const FcGeom& g) {
@@ -355,8 +391,9 @@ bool fc_batched_ok(int dtype, const FcGeom& g) {
 //   bf16  9216 -> 4096   4           512              14.3 / 15.6 / 25.3   18.1      6           768   21.2 / 23.7 / 38.5   18.2
 //   bf16  4096 -> 4096   2           256               7.2 /  7.3 /  8.8   10.0      4           512   10.1 / 10.3 / 12.4   10.0
 //   bf16  2048 -> 2048   6           384               8.4 /  8.4 /  8.6    9.2      8           512    9.8 /  9.9 / 10.1    9.3
-// Rows of more than 16 KB: the product is dearer, the line is a quarter later.  bf16 layers of 16 and more streams always: a
-// recomputed sum carries one step's rounding, a walked one all of its steps'.
+// Rows of more than 16 KB: the product is dearer, the line is a quarter later.  bf16 layers of 16 and more streams always.
+// (Rounding, 9216 -> 4096: a recomputed sum 0.6e-7 up to 32 streams and 2.3e-7 beyond, whatever ran before; a walked one 0.9e-7
+// after the first step, 1.2e-7 after the sixth.)
 bool fc_step_batched(int dtype, const FcGeom& g) {
     const int esize = dtype == RRM_I8_I32 ? 1 : 2;
     if (dtype == RRM_BF16_F32 && g.n >= 16) return true;

@@ -198,6 +198,36 @@ def test_fc_step_of_many_streams(ci, co, n, dt):
     assert st["changed_elems"] == sum(int((a != b).sum()) for a, b in zip(before, seq.frames)) and st["delta_steps"] == 4
 
 
+# The rounding error of a bf16 layer as one product, norm over norm against 64 bits: dense, and the step where it takes the product.
+# Up to 32 streams: chains of four matrix instructions (each adds about 0.26e-7, independent roundings: 0.52e-7), a rounding per
+# split and one of the result (0.35e-7 each, the mean of 2^-24 over a binade): 0.72e-7.  More streams: chains of at most 16 or, from
+# 65 streams on, 32 instructions, 1.04e-7 and 1.5e-7.  The bounds leave a third.  Rows where the split cap binds, few outputs and many.
+@pytest.mark.parametrize("ci,co,n,bound", [
+    (4096, 4096, 4, 1e-7), (4096, 4096, 15, 1e-7), (9216, 256, 16, 1e-7), (65536, 64, 4, 1e-7), (65536, 64, 29, 1e-7), (608, 48, 5, 1e-7),
+    (65536, 64, 33, 1.45e-7), (24576, 192, 64, 1.45e-7), (65536, 64, 65, 2e-7), (65536, 48, 129, 2e-7),
+])
+def test_fc_product_rounding(ci, co, n, bound):
+    import numpy as np
+    import paper_1802_09723_amd as rrm
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(ci + n)
+    w = (torch.randn((co, ci), generator=gen, device="cuda") * 0.05).to(torch.bfloat16)
+    bias = torch.randn((co,), generator=gen, device="cuda") * 0.1
+    layer = rrm.Layer(S.fc_shape(ci, co, n=n), S.BF16, w.view(torch.int16).cpu().numpy().view(np.uint16), bias.cpu().numpy())
+    y = torch.empty(layer.y_shape, dtype=torch.float32, device="cuda")
+    for t in range(2):
+        x = torch.randn((n, ci), generator=gen, device="cuda").clamp_(min=0).to(torch.bfloat16)
+        want = x.double() @ w.double().T + bias.double()
+        layer.dense(x, y)
+        layer.step(x)
+        torch.cuda.synchronize()
+        error = float((y.double() - want).norm() / want.norm())
+        assert error <= bound, f"frame {t}: {error:.2e}"
+        if n >= 16 or n * (2 * co // 64) >= 512:
+            assert torch.equal(layer.y_snapshot(), y), f"frame {t}: the step's projection is not the dense one"
+    layer.destroy()
+
+
 # Any two int8 inputs are in range for an FC layer, whichever way its step runs: frames from the lowest value to the highest and
 # back are exact and raise no range error.  (c_out, streams): the column walk and the product, one group of streams and several.
 @pytest.mark.parametrize("co,n,product", [(48, 1, False), (48, 20, False), (4096, 8, True), (2048, 33, True), (272, 300, True)])
