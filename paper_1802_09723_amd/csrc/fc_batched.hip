@@ -311,8 +311,11 @@ int bt_group(int n) {
 // Splits of the k range of one launch of n streams: about one workgroup per compute unit, about four chunks per split (what a
 // workgroup has in flight) and at most sixteen, which the sums' launch reads.  The partial sums' bytes are no bound, they stay in
 // the caches.  (us a step, held to half of W's bytes and three chunks, and so: int8 2048 -> 1024, 100 streams, 15.7 and 10.0; 300
-// streams, 45.8 and 27.8; 4096 -> 4096, 128 streams, 18.7 and 16.6; bf16 1024 -> 512, 128 streams, 15.8 and 10.0.  With eight and
-// with 64 splits at most: bf16 9216 -> 256, 100 streams, 19.8 and 18.9, with sixteen 16.6; 4096 -> 1024 14.0, 15.4 and 15.5.)
+// streams, 45.8 and 27.8; 4096 -> 4096, 128 streams, 18.7 and 16.6; bf16 1024 -> 512, 128 streams, 15.8 and 10.0.  Dense with at
+// most 8 / 12 / 16 splits: bf16 9216 -> 256, 100 streams, 18.3 / 16.5 / 16.8; 9216 -> 1024, 100, 19.7 / 18.3 / 18.9; 4096 -> 256, 100,
+// 12.8 / 13.0 / 12.6; 65536 -> 64, 16, 28.2 with twelve, 23.9 with sixteen; int8 9216 -> 1024, 100, 15.2 / 14.9 / 16.2.  Twelve are
+// often a little faster, and eight for 4096 -> 1024, 100, 14.1 / 14.8 / 15.3, but longer chains cost bf16 precision: relative error of
+// 9216 -> 256, 100 streams, 1.39e-7 with twelve and 1.31e-7 with sixteen.)
 // More where a bf16 split's chain of matrix instructions would be longer than 16, or, with more than 64 streams, 32: the
 // rounding error of long rows is then no larger than that of short ones (see fc_bt_kernel).
 int bt_splits(int dtype, const FcGeom& g, int n) {
