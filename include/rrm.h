@@ -157,7 +157,7 @@ rrm_status rrm_read_snapshot(rrm_layer* layer, void* x_dst, void* y_dst, void* h
  *   "fc_batched"  FC with 4 to 4096 streams (c_out a multiple of 16, rows of whole 64-byte steps): 1 (default) =
  *                 the dense layer runs as one product on the matrix cores with W read once for all streams, and
  *                 so does a step where that is cheaper than the streams' column walks (many streams or output
- *                 channels): it commits x_t and recomputes b + W x_t, one pass over W whatever the density;
+ *                 channels, long rows): it commits x_t and recomputes b + W x_t, one pass over W whatever the density;
  *                 0 = one column walk per stream as at batch 1.  Layers with a truncation threshold
  *                 or "fc_sparse_weights" take the walk.
  *   "fc_sparse_weights"  FC, delta step: 1 = walk the non-zero weights of the changed columns only (pruned

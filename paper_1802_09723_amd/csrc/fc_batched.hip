@@ -394,14 +394,24 @@ bool fc_batched_ok(int dtype, const FcGeom& g) {
 //   bf16  9216 -> 4096   4           512              14.3 / 15.6 / 25.3   18.1      6           768   21.2 / 23.7 / 38.5   18.2
 //   bf16  4096 -> 4096   2           256               7.2 /  7.3 /  8.8   10.0      4           512   10.1 / 10.3 / 12.4   10.0
 //   bf16  2048 -> 2048   6           384               8.4 /  8.4 /  8.6    9.2      8           512    9.8 /  9.9 / 10.1    9.3
-// Rows of more than 16 KB: the product is dearer, the line is a quarter later.  bf16 layers of 16 and more streams always.
+// Rows of more than 16 KB: the product is dearer, the line is a quarter later.
+// int8 layers below that line whose walks would read more than 200 MiB of W if everything changed, of a W that the caches hold: level
+// while next to nothing changes, and dear soon.  us a step walking, 1 / 5 / 25 / 50 / 100 % changed, and as a product:
+//   9216 -> 1024  24 streams  216 MiB   10.1 / 10.2 / 15.1 / 18.9 / 25.6   10.8      9216 -> 4096   7   252   11.5 / 11.9 / 19.9 / 30.0 / 40.4   12.4
+//   9216 -> 2048  15          270       11.9 / 12.3 / 16.1 / 21.9 / 30.5   10.3      9216 ->  512  63   284   10.4 / 10.7 / 15.0 / 19.3 / 26.5   11.1
+// and on the other side of it, where a walk is ahead up to a quarter and the product from half on:
+//   9216 -> 1024  16          144        9.6 /  9.8 / 11.3 / 13.5 / 17.9   10.3      4096 -> 1024  31   124    8.7 /  9.3 / 11.2 / 13.4 / 16.5   10.3
+//   4096 -> 4096   7          112        9.4 / 10.0 / 11.9 / 13.5 / 17.0   10.2      9216 ->  256  64   144    9.2 /  9.6 / 10.9 / 13.1 / 17.4   11.4
+//   2048 -> 1024  31           62        8.7 /  9.1 /  9.4 / 11.2 / 12.2    9.8      1024 ->  512  63    32    7.7 /  7.7 /  8.0 /  8.2 /  8.9   10.0
+// (more than 64 streams, whose product is dearer: 9216 -> 256, 127, 286 MiB, 11.6 / 11.8 / 14.8 / 19.6 / 26.8 and 14.4).  bf16 layers of 16 and more streams always.
 // (Rounding, 9216 -> 4096: a recomputed sum 0.6e-7 up to 32 streams and 2.3e-7 beyond, whatever ran before; a walked one 0.9e-7
 // after the first step, 1.2e-7 after the sixth.)
 bool fc_step_batched(int dtype, const FcGeom& g) {
     const int esize = dtype == RRM_I8_I32 ? 1 : 2;
     if (dtype == RRM_BF16_F32 && g.n >= 16) return true;
     const long long workgroups = (long long)g.n * ((g.c_out_p * esize + 63) / 64);
-    return workgroups >= (g.c_in * esize > 16384 ? 640 : 512);
+    if (workgroups >= (g.c_in * esize > 16384 ? 640 : 512)) return true;
+    return dtype == RRM_I8_I32 && g.n <= 64 && (long long)g.c_in * g.c_out <= 40ll << 20 && workgroups * 64 * g.c_in >= 200ll << 20;
 }
 
 hipError_t launch_fc_batched_dense(int dtype, const void* w_rm, const void* x, void* part, const void* bias, void* y,

@@ -185,6 +185,29 @@ def test_scatter_of_a_scans_difference(m, ci, co, k, st, pad, g, n):
         layer.destroy()
 
 
+def fc_step_is_product(dt, ci, co, n):
+    """Which way a step of an FC layer runs where both are possible: one product for all streams, or a column walk per stream."""
+    if dt == S.BF16 and n >= 16:
+        return True
+    es = 1 if dt == S.I8 else 2
+    walks = n * ((co * es + 63) // 64)
+    if walks >= (640 if ci * es > 16384 else 512):
+        return True
+    return dt == S.I8 and n <= 64 and ci * co <= 40 << 20 and walks * 64 * ci >= 200 << 20
+
+
+# int8 layers whose walks would read more than 200 MiB: on both sides of that line, of the 64 streams and of a W of 40 MiB.
+@pytest.mark.parametrize("ci,co,n,product", [
+    (9216, 1040, 22, True), (9216, 1040, 20, False), (16384, 192, 50, False), (16384, 208, 50, True), (8192, 368, 64, False), (8192, 400, 64, True),
+    (8256, 400, 65, False), (16384, 2576, 5, False), (16384, 2560, 5, True),
+])
+def test_fc_step_of_long_rows(ci, co, n, product):
+    assert fc_step_is_product(S.I8, ci, co, n) == product
+    seq = S.random_layer(9940 + n, S.fc_shape(ci, co, n=n), S.I8, T=3, frac=0.1)
+    st, _ = run_sequence(seq, check_frames=(1, 2), y_out_frames=(1, 2), check_dense=())
+    assert st["delta_steps"] == 3
+
+
 # Many streams: the launch that sums the splits commits and counts the frame and fills the caller's copy; one group of streams and
 # several, a frame that repeats; few streams of many channels, on both sides of the line.
 @pytest.mark.parametrize("ci,co,n", [(64, 16, 16), (192, 48, 33), (1024, 80, 129), (320, 272, 300), (128, 4096, 4), (64, 4096, 8), (192, 2048, 7), (128, 2064, 15)])
@@ -223,7 +246,7 @@ def test_fc_product_rounding(ci, co, n, bound):
         torch.cuda.synchronize()
         error = float((y.double() - want).norm() / want.norm())
         assert error <= bound, f"frame {t}: {error:.2e}"
-        if n >= 16 or n * (2 * co // 64) >= 512:
+        if fc_step_is_product(S.BF16, ci, co, n):
             assert torch.equal(layer.y_snapshot(), y), f"frame {t}: the step's projection is not the dense one"
     layer.destroy()
 
@@ -232,7 +255,7 @@ def test_fc_product_rounding(ci, co, n, bound):
 # back are exact and raise no range error.  (c_out, streams): the column walk and the product, one group of streams and several.
 @pytest.mark.parametrize("co,n,product", [(48, 1, False), (48, 20, False), (4096, 8, True), (2048, 33, True), (272, 300, True)])
 def test_fc_step_of_full_range_differences(co, n, product):
-    assert (n * ((co + 63) // 64) >= 512) == product
+    assert fc_step_is_product(S.I8, 192, co, n) == product
     seq = S.random_layer(9970 + n, S.fc_shape(192, co, n=n), S.I8, T=4, frac=0.3)
     for t, frame in enumerate(seq.frames):
         frame[..., -40:] = (-128, 127)[t % 2]
