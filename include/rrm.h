@@ -126,7 +126,8 @@ rrm_status rrm_dense(rrm_layer* layer, const void* x, void* y, void* hip_stream)
 /* rrm_dense for callers that cannot allocate device memory while they run (code under HIP-graph capture, tight
  * serving loops, harnesses that forbid it): FC layers only; the partial sums of the row splits, which rrm_dense
  * keeps in a buffer the handle allocated at create, live in a static device array of 4 MiB that exists once per
- * GPU.  The call allocates and frees nothing.  Same arguments and result as rrm_dense.  A layer whose partial
+ * GPU.  The call allocates and frees nothing.  Same arguments and result as rrm_dense (of a BF16 layer that rrm_dense
+ * runs as one product, see "fc_batched", up to the order of the fp32 sums).  A layer whose partial
  * sums (n x row splits x c_out x 4 bytes) exceed the array gives RRM_ERR_SHAPE.  Every call on a GPU shares that
  * GPU's array: calls that overlap in time on one GPU (different streams, different handles) race.
  * Errors: RRM_ERR_NULL, RRM_ERR_ALIGN, RRM_ERR_SHAPE (not an FC layer, or too large), RRM_ERR_HIP. */
@@ -151,15 +152,18 @@ rrm_status rrm_read_snapshot(rrm_layer* layer, void* x_dst, void* y_dst, void* h
  *                 multiplies the changed input positions and adds the products into the stored projection with
  *                 atomic adds: work proportional to the changed input positions; fp32 results then depend on the
  *                 order of the adds within the layer's tolerance).  Automatic mode takes path 3 for layers of few
- *                 such adds, and there the products alone behind a scan that another layer's projection feeds.
+ *                 such adds, and there the products alone behind a scan that another layer's projection feeds: ahead
+ *                 while up to about half of the positions change; a sequence in which most of them do, frame after
+ *                 frame, is better served by "path" 2, or by "conv_kernel" 1, which keeps the switch to recomputation.
  *   "fc_splits"   FC, dense path: number of row splits of the weight matrix, in [1, the default chosen at
- *                 create] (the partial-sum scratch is sized for the default)
+ *                 create] (the partial-sum scratch is sized for the default).  Without effect where the dense layer
+ *                 runs as one product (see "fc_batched"); rrm_dense_noalloc always splits so
  *   "fc_batched"  FC with 4 to 4096 streams (c_out a multiple of 16, rows of whole 64-byte steps): 1 (default) =
  *                 the dense layer runs as one product on the matrix cores with W read once for all streams, and
  *                 so does a step where that is cheaper than the streams' column walks (many streams or output
  *                 channels, long rows): it commits x_t and recomputes b + W x_t, one pass over W whatever the density;
  *                 0 = one column walk per stream as at batch 1.  Layers with a truncation threshold
- *                 or "fc_sparse_weights" take the walk.
+ *                 or "fc_sparse_weights" take the walk.  Such a layer keeps W twice, as the walk and as the product read it
  *   "fc_sparse_weights"  FC, delta step: 1 = walk the non-zero weights of the changed columns only (pruned
  *                 models, Sec. 4.3; the (row, value) lists exist when at most half of W is non-zero at create,
  *                 else RRM_ERR_OPTION), 0 = walk whole columns (default).  fp32 sums of the sparse walk
@@ -169,7 +173,7 @@ rrm_status rrm_read_snapshot(rrm_layer* layer, void* x_dst, void* y_dst, void* h
  *                 4x4 output blocks recomputes the whole projection (same result; cheaper than reading and
  *                 re-writing most of it); 1..100, 100 = never; defaults 75 (int8) / 40 (bf16) for the window-tile
  *                 kernel, which decides per launch, and 90 / 50 for the position-gather kernel, which decides per
- *                 work unit
+ *                 work unit.  Without effect on steps that take path 3
  *   "conv_kernel" INT8 / BF16 conv: 0 = automatic (the window-tile kernel), 1 = window-tile kernel (4x4 output
  *                 blocks with their input windows gathered into LDS; any stride), 2 = position-gather kernel
  *                 (single active output positions as columns of the product; stride 1 and channel runs of

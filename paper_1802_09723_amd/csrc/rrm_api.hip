@@ -544,15 +544,23 @@ rrm_status setup_scatter(rrm_layer* L, const std::vector<unsigned char>& w) {
     L->scat_ok = true;
     // Automatic: layers of few output adds.  Two dependent launches and the per-workgroup set-up of the tile kernels cost more
     // there than the step's work; what the scatter pays more for is its adds into the projection, one per changed position, tap,
-    // output channel and part of K.  us a step, scatter against scan + tile, at 5 / 10 / 25 / 50 % changed (the millions: the
-    // adds if all changed; calls from the host cannot follow each other in less than 7):
-    //   bf16 3 x 3  28 x 28 x 128         0.9   7.5 /  7.6 /  7.7 /  8.7   11.6 / 11.7 / 11.9 / 12.0
-    //   bf16 3 x 3  14 x 14 x 256         0.9   7.1 /  7.3 /  8.5 /  9.9   12.9 / 12.9 / 13.1 / 13.2
-    //   bf16 3 x 3  32 x 32 x 256         4.7  10.9 / 12.5 / 15.0 / 18.5   13.4 / 13.6 / 13.8 / 14.1
-    //   bf16 3 x 3  32 x 32 x 512        18.9  42.2 / 46.0 / 49.0 / 57.0   21.5 / 22.5 / 23.3 / 24.5
-    //   int8 5 x 5  27 x 27, 96 -> 256    4.7   7.2 /  7.4 /  9.9 / 13.3   10.8 / 10.8 / 10.9 / 11.0
-    //   int8 3 x 3  28 x 28 x 96, n = 8   5.4   7.5 /  7.6 /  9.9 / 13.1   13.1 / 13.4 / 14.4 / 15.7
-    //   int8 5 x 5  27 x 27, n = 4       18.7  10.5 / 11.4 / 19.6 / 29.0   13.2 / 13.2 / 14.2 / 18.0
+    // output channel and part of K.  us a step, scatter against scan + tile, at 5 / 10 / 25 / 50 / 100 % changed, in squares (the
+    // millions, of 2^20: the adds if all changed; calls from the host cannot follow each other in less than 7):
+    //   int8 3 x 3  56 x 56 x 64, n = 2          3.4   7.4 /  7.7 /  7.8 /  9.5 / 14.3   10.9 / 11.3 / 11.9 / 11.9 / 11.2
+    //   int8 1 x 1  64 x 64, 512 -> 64, n = 8    4.0   8.6 /  9.5 / 11.7 / 14.4 / 20.9   17.1 / 18.3 / 20.2 / 24.1 / 26.7
+    //   int8 5 x 5  27 x 27, 96 -> 256           4.5   7.8 /  7.9 / 11.0 / 12.8 / 18.8   10.5 / 11.0 / 10.8 / 11.2 / 10.6
+    //   int8 3 x 3  28 x 28 x 96, n = 8          5.2   7.4 /  7.5 / 10.0 / 13.1 / 18.1   12.9 / 13.4 / 14.3 / 15.4 / 15.4
+    //   int8 3 x 3  14 x 14, 512 -> 256, n = 6   5.2  10.1 / 10.3 / 14.0 / 17.0 / 21.9   12.5 / 12.9 / 13.3 / 13.3 / 13.6
+    //   int8 5 x 5  61 x 61, 16 -> 32, n = 2     5.7   7.7 /  7.8 / 10.3 / 13.7 / 22.6   10.9 / 10.7 / 11.1 / 11.0 / 10.6
+    //   int8 5 x 5  27 x 27, n = 4              17.8  10.5 / 11.4 / 19.6 / 29.0          13.2 / 13.2 / 14.2 / 18.0
+    //   bf16 3 x 3  28 x 28 x 128                0.9   7.5 /  7.6 /  7.7 /  8.7 / 10.3   11.6 / 11.7 / 11.9 / 12.0 / 11.6
+    //   bf16 3 x 3  14 x 14 x 256                0.9   7.1 /  7.3 /  8.5 /  9.9 / 11.9   12.9 / 12.9 / 13.1 / 13.2 / 12.7
+    //   bf16 5 x 5  28 x 28 x 128                2.4   8.3 /  9.2 / 11.7 / 11.7 / 16.5   13.6 / 13.6 / 14.1 / 14.0 / 14.0
+    //   bf16 3 x 3  32 x 32 x 256                4.5  10.8 / 11.9 / 14.4 / 17.7 / 24.8   13.2 / 13.4 / 13.7 / 14.2 / 14.3
+    //   bf16 3 x 3  14 x 14 x 512, n = 2         6.9  17.6 / 19.2 / 22.1 / 24.4 / 37.6   17.2 / 17.8 / 17.8 / 18.1 / 18.4
+    // So the line goes by what video does, a tenth of the positions or so: far ahead there, mostly ahead at a quarter and level
+    // at a half.  A frame in which everything changes costs the layers near it up to twice what the tiles take, which recompute
+    // above dense_switch_pct: one in a while repays itself.
     // bf16 layers of more than 1024 positions stay on the tiles whatever they would gain: fp32 adds round once per tap and in
     // the order of their arrival, sums of the tile kernel once and in a fixed order.
     const long long adds = g.npos_total * g.ntaps * s.c_out * g.nkp;
@@ -708,7 +716,7 @@ int bin_cw(const rrm_layer* L) {
 }
 
 // does this step of a convolution layer take the single-launch scatter path?  ("path" = 3: always where the layer
-// is eligible; automatic, with the kernel choice left automatic too: layers with few positions, see setup_scatter)
+// is eligible; automatic, with the kernel choice left automatic too: layers of few adds, see setup_scatter)
 bool use_scatter(const rrm_layer* L) {
     if (!L->scat_ok || L->dtype == RRM_BIN_I32) return false;
     if (L->opt_path == 3) return true;
