@@ -405,9 +405,9 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
 
 }  // namespace
 
-// LDS beyond 64 KB: for every form of the kernel, once per process
+// A workgroup's LDS beyond 64 KB, dynamic and static (the lists and flags, 2.3 KB): for every form of the kernel, once per process
 static hipError_t scatter_lds(size_t lds) {
-    if (lds <= 64 * 1024) return hipSuccess;
+    if (lds + 4 * 1024 <= 64 * 1024) return hipSuccess;
     static std::once_flag once;
     static hipError_t attr = hipSuccess;
     std::call_once(once, [] {

@@ -146,6 +146,13 @@ def test_scatter_path_edges(h, w, ci, co, k, st, pad, g, n, dt):
     run_sequence(seq, check_dense=(), path=3)
 
 
+# ... and the bf16 blocks whose planes and lists together are beyond 64 KB of LDS.
+@pytest.mark.parametrize("ci", [496, 1000])
+def test_scatter_path_with_the_largest_blocks(ci):
+    seq = S.random_layer(9870 + ci, S.conv_shape(6, 7, ci, 24, 3, 1, 1, 1, n=2), S.BF16, T=3, frac=0.2, block=2)
+    run_sequence(seq, check_dense=(), path=3)
+
+
 # A layer of few adds behind another one: its products are the scatter kernel's, of the difference that the scan has left, and
 # the launch leaves flags, statistics and words as the tile kernel does ("path" = 1), in turn with plain steps of either path;
 # what reads the flags then sees all that was written.  (map, c, c_out, k, stride, pad, groups, streams)
