@@ -203,6 +203,27 @@ def fc_step_is_product(dt, ci, co, n):
     return dt == S.I8 and n <= 64 and ci * co <= 40 << 20 and walks * 64 * ci >= 200 << 20
 
 
+# int8 steps as one product: every stream-tile count and group count, on the shortest layer of whole 64-row groups and off them that
+# takes the product; k ranges with a ragged last chunk, one split and several.
+@pytest.mark.parametrize("n", [4, 9, 15, 16, 17, 32, 33, 48, 64, 65, 90, 100, 128, 129, 190, 300, 520])
+def test_fc_int8_product_step_at_every_stream_count(n):
+    co, ci = 64 * ((511 + n) // n) - 48 * (n % 2), 64 * (1, 2, 5, 7, 13, 24)[n % 6]
+    assert fc_step_is_product(S.I8, ci, co, n) and not fc_step_is_product(S.I8, ci, 64 * (511 // n), n)
+    seq = S.random_layer(9950 + n, S.fc_shape(ci, co, n=n), S.I8, T=3, frac=0.2)
+    st, _ = run_sequence(seq, check_dense=(0, 2), y_out_frames=(1, 2))
+    walk, _ = run_sequence(seq, check_dense=(2,), fc_batched=0)
+    assert st["delta_steps"] == 3 and st["changed_elems"] == walk["changed_elems"]
+
+
+# Sixteen splits and around: the sums' launch reads five at a time behind the first.  (c_in, c_out, streams), int8 in bytes: 16, 12, 11
+# and 6 splits of four-step chunks, 16 and 9 of two-step ones; the dense layer, and the step of bf16 layers.
+@pytest.mark.parametrize("ci,co,n", [(16384, 64, 16), (12288, 48, 20), (11264, 112, 33), (6144, 64, 16), (8192, 80, 70), (4608, 64, 128)])
+@pytest.mark.parametrize("dt", [S.I8, S.BF16])
+def test_fc_product_of_many_splits(ci, co, n, dt):
+    seq = S.random_layer(9960 + n, S.fc_shape(ci // (1 if dt == S.I8 else 2), co, n=n), dt, T=2, frac=0.2)
+    run_sequence(seq, check_dense=(0, 1), rel=1e-4)
+
+
 # int8 layers whose walks would read more than 200 MiB: on both sides of that line, of the 64 streams and of a W of 40 MiB.
 @pytest.mark.parametrize("ci,co,n,product", [
     (9216, 1040, 22, True), (9216, 1040, 20, False), (16384, 192, 50, False), (16384, 208, 50, True), (8192, 368, 64, False), (8192, 400, 64, True),

@@ -551,9 +551,9 @@ def test_fc_pruned_weights_walk_nonzeros_only(dtype):
 
 @pytest.mark.parametrize("dtype", [S.I8, S.BF16])
 def test_fc_many_streams_as_one_product(dtype):
-    """FC layers with 16 or more streams run as one product on the matrix cores (dense layer and delta step): a
-    ragged stream count, one tile exactly, several tiles, the full-size fc7 at 64 streams; and the same handles on
-    the per-stream column walk."""
+    """FC layers with 16 or more streams run as one product on the matrix cores (the dense layer; the step of the bf16
+    ones and of the full-size int8 one, int8 layers of few channels walk): a ragged stream count, one tile exactly,
+    several tiles, the full-size fc7 at 64 streams; and the same handles on the per-stream column walk."""
     cases = [(S.fc_shape(192, 48, n=16), 0.3), (S.fc_shape(640, 272, n=37), 0.1), (S.fc_shape(4096, 4096, n=64), 0.05),
              (S.fc_shape(128, 16, n=200), 0.5)]
     for i, (shp, frac) in enumerate(cases):
@@ -565,9 +565,9 @@ def test_fc_many_streams_as_one_product(dtype):
 
 
 def _batched_fc_shapes():
-    """every stream-tile count the product kernel is built for (1, 2, 3, 4, 6, 8, 12, 16 tiles of 16 streams, and
-    ragged counts between them), row counts that are not multiples of the 64-row group, k ranges that leave a ragged
-    last chunk, one split and several"""
+    """every stream-tile count the product kernel is built for (1, 2, 3, 4, 6, 8 tiles of 16 streams, and ragged counts
+    between them and beyond), row counts that are not multiples of the 64-row group, k ranges that leave a ragged last
+    chunk, one split and several; in the dense layer, the bf16 steps and the int8 steps of 256 and more streams"""
     rng = S.rng_for(9100)
     out = []
     for n in (16, 17, 32, 33, 48, 64, 65, 90, 96, 100, 128, 129, 190, 200, 256, 300, 512):
