@@ -70,15 +70,15 @@ __device__ __forceinline__ void mark_tiles(const ScanGeom& g, int pos, unsigned 
 
 // Mark the 4x4 output sub-tiles that see the input positions pos .. last (of a unit of few channels: several): one byte flag
 // each, plain stores (every writer stores the same value, so no atomics and no same-address serialisation).  A run of
-// positions in a row is marked at once -- its output columns are those between its ends', unless the stride leaves columns
-// that no window reads (227 x 227 x 3, one stream, the scan 9.1 -> 8.0 us).
+// positions in a row is marked at once -- the outputs whose windows meet it are those between its ends', at any stride (227 x 227
+// x 3, one stream, the scan 9.1 -> 8.0 us).
 __device__ __forceinline__ void mark_subtiles(const ScanGeom& g, unsigned int pos, unsigned int last, unsigned char* flags, unsigned char mark) {
     const unsigned int hw = (unsigned int)(g.h * g.w);
     while (pos <= last) {
         const int b = (int)udiv_big(pos, g.r_hw);
         const int r = (int)(pos - (unsigned int)b * hw);
         const int iy = (int)udiv_big((unsigned int)r, g.r_w), ix = r - iy * g.w;
-        const int more = g.stride <= g.kw ? min((int)(last - pos), g.w - 1 - ix) : 0;
+        const int more = min((int)(last - pos), g.w - 1 - ix);
         pos += (unsigned int)more + 1u;
         const int ty0 = iy + g.pad - (g.kh - 1), tx0 = ix + g.pad - (g.kw - 1);
         const int oy_lo = ty0 <= 0 ? 0 : udiv_small(ty0 + g.stride - 1, g.magic_stride);
