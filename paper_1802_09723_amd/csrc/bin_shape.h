@@ -60,13 +60,14 @@ inline size_t bin_band_lds_bytes(const BinGeom& g, int band_rows) {
     return 2 * npos * g.bpitch * 4 + ((npos + 15) & ~(size_t)15) + (((size_t)band_rows * g.wo * 2 + 15) & ~(size_t)15) + BAND_SUMS;
 }
 
-// Does the dense layer run the tile kernel (the times are of bands whose wavefronts split the K steps): without bands; wide layers (4 x 1100, 128 -> 1024 channels 1 x 1, 11.4 us there and
-// 15.9 on bands, 24 x 350, 128 -> 512 3 x 3, 19.8 and 18.6, 16 x 350, 128 -> 64, 16 streams, 21.4 and 23.5); and 1 x 1 filters
-// of few words, whose products are too short for what a pass of the band kernel costs beside them (us, tile and band: 14 x 14,
-// 128 -> 512 channels, 3.4 and 4.9; 16 x 320, 256 -> 256, 2 streams, 8.4 and 12.1; 112 x 112, 64 -> 64, 64 streams, 66 and 85;
-// 512 channels and 3 x 3 of 32 are level or behind: 7 x 7, 512 -> 512, 5.5 and 4.6).  Not where bands fill the chip and their
-// words are read whole, but the map leaves more than a fifth of its 8 x 8 tiles empty (28 x 28, 128 -> 512, 64 streams, 45.4
-// and 42.0; 13 x 13, 256 -> 256, 128, 16.5 and 15.0).
+// Does the dense layer run the tile kernel: without bands; wide layers (us, tile and band: 4 x 1100, 128 -> 1024 channels 1 x 1, 11.8
+// and 31.0; 3 x 3, one stream, 4 x 350, 128 -> 64, 7.5 and 14.5; 24 x 350, 128 -> 512, 20.8 and 19.9; four streams of 8 x 350, 128 -> 256,
+// 14.8 and 17.1; but many streams gain on bands: 16 of 16 x 350, 128 -> 64, 21.8 and 18.5, 64 of 2 x 350, 128 -> 128, 58.8 and 18.4); and 1 x 1
+// filters of few words, whose products are too short for what a band costs beside them (16 x 320, 256 -> 256, 2 streams, 8.7
+// and 13.0; 112 x 112, 64 -> 64, 64 streams, 65.5 and 85.5; 20 x 33, 224 -> 112, 30 streams, 8.4 and 10.1; 14 x 14, 256 -> 512, 8
+// streams, 7.2 and 7.5; but 28 x 28, 256 -> 256, 16 streams, 10.3 and 9.3; 512 channels are level or behind: 7 x 7, 512 -> 512, 64
+// streams, 9.0 and 7.8).  Not where bands fill the chip and their words are read whole, but the map leaves more than a fifth of its
+// 8 x 8 tiles empty (28 x 28, 128 -> 512, 64 streams, 45.2 and 41.3; 13 x 13, 256 -> 256, 128, 18.3 and 13.0).
 inline bool bin_dense_on_tiles(const BinGeom& g) {
     if (g.band_rows == 0 || g.bpitch < g.pitch) return true;
     if (g.kh * g.kw != 1 || g.wg > 8) return false;

@@ -379,12 +379,12 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
     // LDS for longer slabs, and the consumers split the K steps.  Many sub-tiles (many streams): operand reuse matters,
     // so 2 channel blocks x 16 sub-tiles.
     // A delta launch of few sub-tiles keeps eight of them per workgroup where a unit has few K steps to put against what every
-    // workgroup pays (its share of the work list, the joining of the parts); the dense launch, which has no list, does not.  Kernel us of the delta launch at 1 .. 4 and at 8, int8, 30 % of the positions changing: 64 x 64,
-    // 16 -> 32, 5 x 5 at stride 2 (7 K steps), 8 streams 10.3 and 8.9; 28 x 28, 128 -> 96, 1 x 1 (2), 3 streams 8.8 and 8.2; 64 ->
-    // 64, 3 x 3 (9), 10 streams 11.3 and 11.0; 96 -> 128 (14), 3 streams 9.0 and 9.8; 128 -> 64 (18), 10 streams equal. From five K
-    // steps on the very smallest layers are spread too (step us, 3 %, spread and at 8: 27 x 40, 48 -> 96, 3 x 3 at stride 2 (7),
-    // one stream, 60 blocks, 10.2 and 11.9; 13 x 13, 32 -> 64 (5), 8 streams, 64, 10.6 and 11.6; 5 x 5, 16 -> 32 (7), 8 streams,
-    // 128, 11.5 and 11.2).
+    // workgroup pays (its share of the work list, the joining of the parts); the dense launch, which has no list, does not.
+    // Kernel us of the delta launch at 1 .. 4 and at 8, int8, 30 % of the positions changing: 64 x 64, 16 -> 32, 5 x 5 at stride 2 (7
+    // K steps), 8 streams 10.3 and 8.9; 28 x 28, 128 -> 96, 1 x 1 (2), 3 streams 8.8 and 8.2; 64 -> 64, 3 x 3 (9), 10 streams 11.3
+    // and 11.0; 96 -> 128 (14), 3 streams 9.0 and 9.8; 128 -> 64 (18), 10 streams equal. From five K steps on the very smallest
+    // layers are spread too (step us, 3 %, spread and at 8: 27 x 40, 48 -> 96, 3 x 3 at stride 2 (7), one stream, 60 blocks, 10.2 and
+    // 11.9; 13 x 13, 32 -> 64 (5), 8 streams, 64, 10.6 and 11.6; 5 x 5, 16 -> 32 (7), 8 streams, 128, 11.5 and 11.2).
     struct Cand { int cb, nt; };
     std::vector<Cand> cands;
     const long long blocks = (long long)g.n_sub * g.ncb * s.groups;
