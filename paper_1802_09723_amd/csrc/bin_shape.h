@@ -161,10 +161,12 @@ inline bool bin_choose_shape(const rrm_shape& s, BinGeom& g, bool dense = false)
             if (g.fused_ok < before.fused_ok) g = before;
         }
         // Layers that leave compute units empty even so: bands of down to half a tile of 32 positions, as long as that does not
-        // cost the single launch.  (us a step, 10 % of the values flipping, and dense, without and so: one stream, 14 x 14, 512 -> 512,
-        // 9.9 and 7.3, dense 9.1 and 7.4; 56 x 56, 128 -> 256, 9.1 and 8.8, 10.2 and 7.5; two of 14 x 14, 512 -> 512, 10.1 and 7.9, 9.3
-        // and 7.4; two of 28 x 28, 256 -> 256, 8.6 and 8.9, 9.6 and 7.4)
-        if (per_band * g.nbands < BIN_NUM_CU) {
+        // cost the single launch.  A step stages and lists as much again for it, which few K steps do not repay.  (us a step, 2 / 5 / 10
+        // % of the values flipping, without and so: 72 K steps, one stream of 14 x 14, 512 -> 512, 8.9 / 8.8 / 10.2 and 7.4 / 7.3 / 7.6; two
+        // of 28 x 28, 512 -> 256, 10.4 / 10.7 / 11.2 and 9.8 / 9.9 / 10.1; 36, one of 28 x 28, 256 -> 256, 7.1 / 7.8 / 8.1 and 7.1 / 7.3 / 7.4,
+        // but two 7.9 / 8.2 / 8.3 and 8.5 / 8.7 / 8.8; 18, two of 28 x 28, 128 -> 256, 7.3 / 7.4 / 7.6 and 8.1 / 8.3 / 8.3; 4, 256 -> 256 1 x
+        // 1, 7.3 / 7.3 / 7.4 and 8.0 / 8.1 / 8.2.  Dense: 14 x 14, 512 -> 512, 9.1 and 7.4; 56 x 56, 128 -> 256, 10.2 and 7.5)
+        if (per_band * g.nbands < BIN_NUM_CU && (dense || s.kh * s.kw * 2 * g.nslab >= 32)) {
             const BinGeom before = g;
             cut(BIN_NUM_CU, 1, 16);
             if (g.fused_ok < before.fused_ok) g = before;

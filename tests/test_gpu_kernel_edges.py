@@ -60,11 +60,13 @@ def test_binary_band_kernel_edges(ci, co, k, m, n, frac):
 
 # Forms of the band kernel: bands of a tile or less and of several, one workgroup per compute unit and more; K steps of a wavefront
 # fewer than, equal to and beyond the weights in its registers, one block of 32 channels and two; the dense layer with a tile per
-# wavefront, with one per wavefront and block, with two tiles per wavefront; filters wider than a word of flags.
+# wavefront, with one per wavefront and block, with two tiles per wavefront; filters wider than a word of flags; a step with taller
+# bands than the dense launch (fewer than 32 K steps) and not.
 @pytest.mark.parametrize("h,w,ci,co,k,st,pad,g,n,frac", [
     (14, 14, 512, 130, 3, 1, 1, 1, 1, 0.3), (5, 7, 128, 40, 3, 1, 1, 1, 1, 0.9), (11, 40, 32, 20, 3, 1, 1, 1, 1, 0.2), (12, 12, 128, 96, 3, 1, 1, 1, 130, 0.2),
     (9, 9, 256, 65, 3, 2, 1, 1, 150, 0.5), (20, 20, 64, 34, 5, 1, 2, 2, 12, 0.3), (24, 30, 128, 30, 3, 1, 1, 1, 90, 0.1), (40, 13, 640, 64, 1, 1, 0, 1, 5, 0.4),
     (36, 39, 32, 8, 33, 1, 2, 1, 1, 0.02), (16, 16, 384, 70, 3, 1, 1, 1, 140, 0.05),
+    (20, 9, 128, 70, 4, 1, 1, 1, 2, 0.1), (20, 9, 96, 70, 5, 1, 2, 1, 2, 0.1), (28, 28, 256, 80, 1, 1, 0, 1, 2, 0.1),
 ])
 def test_binary_band_kernel_forms(h, w, ci, co, k, st, pad, g, n, frac):
     seq = S.random_layer(9250 + h + ci + co, S.conv_shape(h, w, ci, co, k, st, pad, g, n=n), S.BIN, T=3, frac=frac, block=2)
