@@ -30,7 +30,7 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
-constexpr int BT_CHAIN_TILES = 2;  // bf16 products of up to so many 16-stream tiles sum short chains (see fc_bt_kernel)
+constexpr int BT_CHAIN_TILES = 1;  // bf16 products of up to so many 16-stream tiles sum short chains (see fc_bt_kernel)
 
 // x_snap <- x_t for every stream, change counts.  One thread per 16-byte unit.  (No difference is formed: any two int8 inputs
 // are in range, as they are for the column walk with its nine-bit differences.)
@@ -127,10 +127,10 @@ __global__ __launch_bounds__(256) void fc_bt_kernel(const unsigned char* __restr
         xoff[i] = (xc * NS + s) * 5 + (tid & 3);
     }
     // A matrix instruction rounds its fp32 sum more than once, and the error of a chain of them grows as the square root of its
-    // length.  Up to BT_CHAIN_TILES tiles a chain therefore has a chunk's CK instructions, and the chains are summed in 64 bits (relative
-    // error of 9216 -> 4096, 4 .. 15 streams, whose chains are 72 instructions long without: 2.3e-7 and 0.6e-7, the column walk's
-    // 0.9e-7; us dense 18.2 and 18.3).  More tiles' sums would cost more than they are worth (64 streams, 22.2 and 27.6 us): there
-    // the splits bound the chains, see fc_batched_splits.
+    // length.  Up to BT_CHAIN_TILES tiles a chain therefore has a chunk's CK instructions, and the chains are summed in 64 bits, behind
+    // the loads of a chunk to come (relative error of 9216 -> 4096, 4 .. 15 streams, whose chains are 72 instructions long without:
+    // 2.3e-7 and 0.6e-7, the column walk's 0.9e-7; us dense, 8 streams, 18.3 and 18.9).  More tiles' sums would cost more than they are
+    // worth (32 streams of 9216 -> 256, 12.9 and 13.9, 64 of 9216 -> 4096 22.2 and 27.6): there the splits bound the chains, see bt_splits.
     constexpr bool CHAINS = DT == RRM_BF16_F32 && TMAX <= BT_CHAIN_TILES;
     acc_t acc[TMAX];
     v4d total[CHAINS ? TMAX : 1];
@@ -220,10 +220,10 @@ __global__ __launch_bounds__(256) void fc_bt_kernel(const unsigned char* __restr
     };
     auto phase = [&](int j, int buf, Set& nxt) __attribute__((always_inline)) {
         if (j < nch) compute(acur, buf, j);
-        join();
         stage(nxt, buf ^ 1);
         take(nxt);
         issue(j + 5, nxt);
+        join();
         __syncthreads();
     };
     issue(0, s0);
@@ -316,7 +316,7 @@ int bt_group(int n) {
 // 12.8 / 13.0 / 12.6; 65536 -> 64, 16, 28.2 with twelve, 23.9 with sixteen; int8 9216 -> 1024, 100, 15.2 / 14.9 / 16.2.  Twelve are
 // often a little faster, and eight for 4096 -> 1024, 100, 14.1 / 14.8 / 15.3, but longer chains cost bf16 precision: relative error of
 // 9216 -> 256, 100 streams, 1.39e-7 with twelve and 1.31e-7 with sixteen.)
-// More where a bf16 split's chain of matrix instructions would be longer than 16, or, with more than 64 streams, 32: the
+// More where a bf16 split's chain of matrix instructions would be longer than 20, or, with more than 64 streams, 32: the
 // rounding error of long rows is then no larger than that of short ones (see fc_bt_kernel).
 int bt_splits(int dtype, const FcGeom& g, int n) {
     const int esize = dtype == RRM_I8_I32 ? 1 : 2;
@@ -324,7 +324,7 @@ int bt_splits(int dtype, const FcGeom& g, int n) {
     const int chunks = (g.c_in * esize / 64 + ck - 1) / ck;
     const int groups = (g.c_out + 63) / 64;
     int most = BT_MAX_SPLITS;
-    if (dtype == RRM_BF16_F32 && ntiles > BT_CHAIN_TILES) most = std::max(most, ck == 4 ? (chunks + 3) / 4 : (chunks + 15) / 16);
+    if (dtype == RRM_BF16_F32 && ntiles > BT_CHAIN_TILES) most = std::max(most, ck == 4 ? (chunks + 4) / 5 : (chunks + 15) / 16);
     return std::max(1, std::min(std::min((NUM_CU + groups - 1) / groups, most), (chunks + 3) / 4));
 }
 
@@ -404,7 +404,7 @@ bool fc_batched_ok(int dtype, const FcGeom& g) {
 //   4096 -> 4096   7          112        9.4 / 10.0 / 11.9 / 13.5 / 17.0   10.2      9216 ->  256  64   144    9.2 /  9.6 / 10.9 / 13.1 / 17.4   11.4
 //   2048 -> 1024  31           62        8.7 /  9.1 /  9.4 / 11.2 / 12.2    9.8      1024 ->  512  63    32    7.7 /  7.7 /  8.0 /  8.2 /  8.9   10.0
 // (more than 64 streams, whose product is dearer: 9216 -> 256, 127, 286 MiB, 11.6 / 11.8 / 14.8 / 19.6 / 26.8 and 14.4).  bf16 layers of 16 and more streams always.
-// (Rounding, 9216 -> 4096: a recomputed sum 0.6e-7 up to 32 streams and 2.3e-7 beyond, whatever ran before; a walked one 0.9e-7
+// (Rounding, 9216 -> 4096: a recomputed sum 0.6e-7 up to 16 streams and 2.3e-7 beyond, whatever ran before; a walked one 0.9e-7
 // after the first step, 1.2e-7 after the sixth.)
 bool fc_step_batched(int dtype, const FcGeom& g) {
     const int esize = dtype == RRM_I8_I32 ? 1 : 2;
