@@ -403,7 +403,8 @@ bool fc_batched_ok(int dtype, const FcGeom& g) {
 //   9216 -> 1024  16          144        9.6 /  9.8 / 11.3 / 13.5 / 17.9   10.3      4096 -> 1024  31   124    8.7 /  9.3 / 11.2 / 13.4 / 16.5   10.3
 //   4096 -> 4096   7          112        9.4 / 10.0 / 11.9 / 13.5 / 17.0   10.2      9216 ->  256  64   144    9.2 /  9.6 / 10.9 / 13.1 / 17.4   11.4
 //   2048 -> 1024  31           62        8.7 /  9.1 /  9.4 / 11.2 / 12.2    9.8      1024 ->  512  63    32    7.7 /  7.7 /  8.0 /  8.2 /  8.9   10.0
-// (more than 64 streams, whose product is dearer: 9216 -> 256, 127, 286 MiB, 11.6 / 11.8 / 14.8 / 19.6 / 26.8 and 14.4).  bf16 layers of 16 and more streams always.
+// (more than 64 streams, whose product is dearer: 9216 -> 256, 127, 286 MiB, 11.6 / 11.8 / 14.8 / 19.6 / 26.8 and 14.4).
+// bf16 layers of 16 and more streams always.
 // (Rounding, 9216 -> 4096: a recomputed sum 0.6e-7 up to 16 streams and 2.3e-7 beyond, whatever ran before; a walked one 0.9e-7
 // after the first step, 1.2e-7 after the sixth.)
 bool fc_step_batched(int dtype, const FcGeom& g) {
