@@ -430,3 +430,13 @@ def test_active_subtiles_of_few_channels(h, w, c, k, st, pad, n):
         seen = now
     assert_matches(layer.y_snapshot().cpu().numpy(), oracle.dense(seq.shape, S.I8, seq.weights, seq.bias, x), S.I8, "last frame")
     layer.destroy()
+
+
+def test_default_stream_is_the_current_one():
+    """A call without a stream goes to torch's current stream, inside and outside of a stream context."""
+    from paper_1802_09723_amd import binding
+    assert (binding._stream_ptr(None) or 0) == torch.cuda.current_stream().cuda_stream
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        assert binding._stream_ptr(None) == s.cuda_stream == binding._stream_ptr(s)
+    assert (binding._stream_ptr(None) or 0) == torch.cuda.current_stream().cuda_stream
