@@ -19,10 +19,16 @@ namespace rrm {
 namespace {
 
 constexpr int FCD_UN = 8;           // columns in flight per lane
-// inputs of a compare round: one 16-byte unit per thread, at most 56 KB of list (4 or 8 bytes an entry)
-constexpr int fcd_round(int dtype, int threads) {
-    return dtype == RRM_I8_I32 ? threads * 16 : (threads * 8 < 7168 ? threads * 8 : 7168);
+// Inputs of a compare round, and so entries of the list (4 or 8 bytes each): one or two 16-byte units per thread.  A round is a
+// chain of loads, two barriers and column reads that nothing overlaps, 1.7 us of it, so that whole-unit rows of up to 12288 int8
+// entries are one round, and bf16 rows of up to 11264 where the larger form has a compute unit to itself.  One stream, 9216 -> 4096,
+// two rounds and one: int8, 5 / 25 % changed, 7.4 / 9.5 -> 6.1 / 8.1 us, bf16 8.8 / 13.0 -> 6.75 / 11.8.
+constexpr int fcd_round(int dtype, int threads, bool two) {
+    return !two ? threads * (dtype == RRM_I8_I32 ? 16 : 8) : dtype == RRM_I8_I32 ? 12288 : threads > 512 ? threads * 16 : threads * 8;
 }
+constexpr int FCD_BOOKS = 64;       // threads of the wavefront that announces the workgroup
+// Workgroup barrier that publishes LDS contents only (__syncthreads() would also wait for loads and answers on their way)
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 constexpr int FCD_SEG = 64;         // bytes of a weight column one workgroup owns (4 lanes of 16 bytes)
 
 __device__ __forceinline__ float bf16_to_f32(unsigned int h) { return __uint_as_float(h << 16); }
@@ -46,7 +52,7 @@ __device__ __forceinline__ float bf16_to_f32(unsigned int h) { return __uint_as_
 // others time even where it is not taken (one stream, 9216 -> 4096: int8, 25 % changing, 11.42 -> 11.36 us, bf16, 5 %,
 // 11.92 -> 11.78; the ragged rows themselves, 3945 -> 413 bf16, 7.95 -> 7.84).
 template <int DT, bool CSC, bool ROWS16, int NTH>
-__global__ __launch_bounds__(NTH) void fc_delta_kernel(const unsigned char* __restrict__ x_t,
+__global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigned char* __restrict__ x_t,
                                                                unsigned char* x_snap,
                                                                const unsigned char* __restrict__ wT, void* y_v,
                                                                void* y_out, unsigned int* arrive, FcGeom g,
@@ -69,7 +75,8 @@ __global__ __launch_bounds__(NTH) void fc_delta_kernel(const unsigned char* __re
         if constexpr (DT == RRM_I8_I32) return (val_t)((int)e >> 16);
         else return (val_t)__uint_as_float(e.y);
     };
-    constexpr int CHU = fcd_round(DT, NTH);  // inputs of one compare round = capacity of the list
+    constexpr int CHU = fcd_round(DT, NTH, ROWS16 && !CSC);  // inputs of one compare round = capacity of the list
+    constexpr int UPT = (CHU / PV + NTH - 1) / NTH;  // units of a round per thread
     __shared__ entry_t list[CHU];
     __shared__ __align__(16) val_t red[NTH / 64][4 * PV];  // the wavefronts' sums of the 4 * PV channels
     __shared__ int wave_tot[NTH / 64];
@@ -77,6 +84,31 @@ __global__ __launch_bounds__(NTH) void fc_delta_kernel(const unsigned char* __re
     extern __shared__ uint4 fc_dyn[];  // CSC: one update accumulator per output row
     val_t* ly = reinterpret_cast<val_t*>(fc_dyn);
     const int r = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int nchunk = (g.c_in + CHU - 1) / CHU;
+    // The stream's workgroups count up one word, and the answer, up to 2 us among 128 of them, must not be waited for by a
+    // wavefront that streams columns (loads and answers return in order).  A launch of at most a workgroup per compute unit has one
+    // wavefront more for that; where two share one there is no room for it (four streams of 9216 -> 4096 bf16, 15.9 us, would take
+    // 19.8).  One stream, 4096 -> 4096 int8, 5.4 -> 5.05 us.
+    const bool books = blockDim.x > NTH;
+    if (wave == NTH / 64) {
+        unsigned int total = 0;
+        for (int ch = 0; ch < nchunk; ++ch) {
+            lds_barrier();
+            for (int w = 0; w < NTH / 64; ++w) total += (unsigned int)wave_tot[w];
+            // every read of the stored input by this workgroup is done: tell the stream's other workgroups
+            unsigned int before = 0;
+            if (ch == nchunk - 1 && lane == 0) before = atomicAdd(&arrive[b], 1u);
+            lds_barrier();
+            if (ch + 1 < nchunk)
+                lds_barrier();
+            else {
+                if (CSC || total || y_out) lds_barrier();
+                if (lane == 0) s_prev = before;
+            }
+        }
+        lds_barrier();
+        return;
+    }
     if (CSC)
         for (int o = tid; o < g.c_out; o += NTH) ly[o] = 0;  // (the first round's barriers order this)
     // integer layers split long lists over gridDim.z workgroups, pass by pass (pass p of NCG * FCD_UN columns goes
@@ -132,8 +164,8 @@ __global__ __launch_bounds__(NTH) void fc_delta_kernel(const unsigned char* __re
         a = make_uint4(aw[0], aw[1], aw[2], aw[3]);
         s = make_uint4(sw[0], sw[1], sw[2], sw[3]);
     };
-    // difference of a unit: mask of the entries to apply, their values, and the unit's new snapshot
-    auto diff_unit = [&](const uint4& a, const uint4& s, val_t (&dv)[PV], unsigned int& mask, uint4& n_out) {
+    // difference of a unit: mask of the entries to apply, and the unit's new snapshot
+    auto diff_unit = [&](const uint4& a, const uint4& s, unsigned int& mask, uint4& n_out) {
         mask = 0;
         n_out = a;
         if (!((a.x ^ s.x) | (a.y ^ s.y) | (a.z ^ s.z) | (a.w ^ s.w))) return;
@@ -144,7 +176,6 @@ __global__ __launch_bounds__(NTH) void fc_delta_kernel(const unsigned char* __re
             if (DT == RRM_I8_I32) {
                 const int xa = (int)(signed char)(aw[e >> 2] >> (8 * (e & 3)));
                 const int xb = (int)(signed char)(sw[e >> 2] >> (8 * (e & 3)));
-                dv[e] = (val_t)(xa - xb);
                 if (xa != xb) mask |= 1u << e;
             } else {
                 // (truncation threshold, Sec. 3.4 "Improving sparsity": a difference below g.eps is neither
@@ -152,7 +183,6 @@ __global__ __launch_bounds__(NTH) void fc_delta_kernel(const unsigned char* __re
                 const unsigned int xa = (aw[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
                 const unsigned int xb = (sw[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
                 const float d = bf16_to_f32(xa) - bf16_to_f32(xb);
-                dv[e] = (val_t)d;
                 if (xa != xb) {
                     if (fabsf(d) < g.eps) {
                         ++ntrunc;
@@ -165,6 +195,13 @@ __global__ __launch_bounds__(NTH) void fc_delta_kernel(const unsigned char* __re
             }
         }
         n_out = make_uint4(nw[0], nw[1], nw[2], nw[3]);
+    };
+    auto value = [&](const uint4& a, const uint4& s, int e) {  // ... and an entry's value
+        const unsigned int aw[4] = {a.x, a.y, a.z, a.w}, sw[4] = {s.x, s.y, s.z, s.w};
+        if constexpr (DT == RRM_I8_I32)
+            return (val_t)((int)(signed char)(aw[e >> 2] >> (8 * (e & 3))) - (int)(signed char)(sw[e >> 2] >> (8 * (e & 3))));
+        else
+            return (val_t)(bf16_to_f32((aw[e >> 1] >> (16 * (e & 1))) & 0xFFFFu) - bf16_to_f32((sw[e >> 1] >> (16 * (e & 1))) & 0xFFFFu));
     };
     auto store_unit = [&](int e0, const uint4& nw) {  // commit a unit's new snapshot
         if constexpr (ROWS16) {
@@ -191,46 +228,59 @@ __global__ __launch_bounds__(NTH) void fc_delta_kernel(const unsigned char* __re
         }
     };
 
-    // One compare round covers CHU inputs, at most one 16-byte unit per thread: the loads of round c + 1 are
-    // issued before round c's columns are streamed, and the first KEEP rounds' new snapshots stay in registers for
-    // the commit.
-    constexpr int KEEP = 2;
-    const int nchunk = (g.c_in + CHU - 1) / CHU;
-    uint4 keep_nw[KEEP];
-    unsigned int keep_mask[KEEP];
+    // One compare round covers CHU inputs: the loads of round c + 1 are issued before round c's columns are streamed, and
+    // the first KEEP rounds' new snapshots stay in registers for the commit.
+    constexpr int KEEP = UPT == 1 ? 2 : 1;
+    uint4 keep_nw[KEEP][UPT];
+    unsigned int keep_mask[KEEP][UPT];
 #pragma unroll
-    for (int i = 0; i < KEEP; ++i) keep_mask[i] = 0;
-    // this workgroup's channels of the stored projection, fetched now and needed at the end
+    for (int i = 0; i < KEEP; ++i)
+#pragma unroll
+        for (int k = 0; k < UPT; ++k) keep_mask[i][k] = 0;
+    uint4 cur_a[UPT], cur_s[UPT];
+    auto load_round = [&](int base) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < UPT; ++k) {
+            const int e0 = (tid + k * NTH) * PV;
+            cur_a[k] = cur_s[k] = make_uint4(0, 0, 0, 0);
+            if (e0 < CHU && base + e0 < g.c_in) load_unit(base + e0, cur_a[k], cur_s[k]);
+        }
+    };
+    load_round(0);
+    // this workgroup's channels of the stored projection, fetched now (behind the units: loads return in order) and needed at the end
     const int co_y = r * (FCD_SEG / ESIZE) + tid;
     val_t y_old = 0;
     if (!CSC && nks == 1 && tid < 4 * PV && co_y < g.c_out) y_old = static_cast<const val_t*>(y_v)[(long long)b * g.c_out + co_y];
-    uint4 cur_a = make_uint4(0, 0, 0, 0), cur_s = cur_a;
-    if (tid * PV < min(CHU, g.c_in)) load_unit(tid * PV, cur_a, cur_s);
     for (int ch = 0; ch < nchunk; ++ch) {
         const int base = ch * CHU;
-        const int n_in = min(CHU, g.c_in - base);
-        const int nunits = (n_in + PV - 1) / PV;
         // ---- compare + ordered compaction of this round's inputs ------------------------------------------
         int running = 0;
         {
-            const int u = tid;
-            val_t dv[PV];
-            unsigned int mask = 0;
-            uint4 nw = cur_a;
-            if (u < nunits) diff_unit(cur_a, cur_s, dv, mask, nw);
+            unsigned int mask[UPT];
+            uint4 a[UPT], s[UPT];
+            int cnt = 0;
+            const bool all = g.c_in - base > NTH * PV;  // (a shorter round: one unit per thread)
 #pragma unroll
-            for (int i = 0; i < KEEP; ++i)
-                if (ch == i) {
-                    keep_nw[i] = nw;
-                    keep_mask[i] = mask;
-                }
+            for (int k = 0; k < UPT; ++k) {
+                mask[k] = 0;
+                if (k && !all) break;
+                a[k] = cur_a[k];
+                s[k] = cur_s[k];
+                uint4 nw;
+                diff_unit(a[k], s[k], mask[k], nw);  // (units that are not there are zeros in both)
+                cnt += __popc(mask[k]);
+#pragma unroll
+                for (int i = 0; i < KEEP; ++i)
+                    if (ch == i) {
+                        keep_nw[i][k] = nw;
+                        keep_mask[i][k] = mask[k];
+                    }
+            }
             // the next round's units are on their way while this round's columns are streamed
-            if (ch + 1 < nchunk && tid * PV < CHU && base + CHU + tid * PV < g.c_in)
-                load_unit(base + CHU + tid * PV, cur_a, cur_s);
-            const int cnt = __popc(mask);
+            if (ch + 1 < nchunk) load_round(base + CHU);
             const int incl = (int)wave_scan((unsigned int)cnt);
             if (lane == 63) wave_tot[wave] = incl;
-            __syncthreads();
+            lds_barrier();
             int wbase = 0, btot = 0;
             for (int w = 0; w < NTH / 64; ++w) {
                 const int t = wave_tot[w];
@@ -238,21 +288,24 @@ __global__ __launch_bounds__(NTH) void fc_delta_kernel(const unsigned char* __re
                 btot += t;
             }
             int pos = wbase + incl - cnt;
-            if (mask) {
 #pragma unroll
-                for (int e = 0; e < PV; ++e)
-                    if (mask & (1u << e)) {
-                        list[pos] = entry(u * PV + e, dv[e]);
-                        ++pos;
-                    }
+            for (int k = 0; k < UPT; ++k) {
+                if (k && !all) break;
+                if (mask[k]) {
+#pragma unroll
+                    for (int e = 0; e < PV; ++e)
+                        if (mask[k] & (1u << e)) {
+                            list[pos] = entry((tid + k * NTH) * PV + e, value(a[k], s[k], e));
+                            ++pos;
+                        }
+                }
             }
             running = btot;
-            __syncthreads();  // the list is published (and wave_tot may be rewritten)
+            lds_barrier();  // the list is published (and wave_tot may be rewritten)
         }
         const int cnt = running;
         total += (unsigned int)cnt;
-        // every read of the stored input by this workgroup is done: tell the stream's other workgroups
-        if (ch == nchunk - 1 && tid == 0) s_prev = atomicAdd(&arrive[b], 1u);
+        if (!books && ch == nchunk - 1 && tid == 0) s_prev = atomicAdd(&arrive[b], 1u);
         if (CSC) {
             // ---- this workgroup's blocks of eight listed columns, one column per wavefront ---------------------
             const unsigned int* cptr = g.csc_ptr;
@@ -317,13 +370,13 @@ __global__ __launch_bounds__(NTH) void fc_delta_kernel(const unsigned char* __re
                 for (int u = 0; u < FCD_UN; ++u) fma16(w[u], d[u]);
             }
         }
-        if (ch + 1 < nchunk) __syncthreads();  // the list is rewritten by the next round
+        if (ch + 1 < nchunk) lds_barrier();  // the list is rewritten by the next round
     }
 
     // ---- column groups -> one sum per channel: inside the wavefront (lanes with the same `sub`), then the wavefronts in order
     // through LDS.  The order is fixed, so fp32 results repeat from run to run.
     if (CSC) {
-        __syncthreads();  // every wavefront's LDS adds are done
+        lds_barrier();  // every wavefront's LDS adds are done
         if (total) {
             val_t* yb = static_cast<val_t*>(y_v) + (long long)b * g.c_out;
             for (int o = tid; o < g.c_out; o += NTH) {
@@ -360,7 +413,7 @@ __global__ __launch_bounds__(NTH) void fc_delta_kernel(const unsigned char* __re
 #pragma unroll
             for (int e = 0; e < PV / 4; ++e) r[e] = q[e];
         }
-        __syncthreads();
+        lds_barrier();
         if (tid < 4 * PV) {
             val_t sum = 0;
 #pragma unroll
@@ -404,24 +457,27 @@ __global__ __launch_bounds__(NTH) void fc_delta_kernel(const unsigned char* __re
         }
     }
     // ---- commit: the workgroup that finished comparing last snapshots the input (applied entries only) -------
-    __syncthreads();  // (s_prev was written by thread 0 after the last round's barrier)
+    lds_barrier();  // (s_prev was written by thread 0 after the last round's barrier)
     if (s_prev == gridDim.x * gridDim.z - 1u) {
 #pragma unroll
         for (int i = 0; i < KEEP; ++i)
-            if (i < nchunk && keep_mask[i]) store_unit(i * CHU + tid * PV, keep_nw[i]);
+#pragma unroll
+            for (int k = 0; k < UPT; ++k)
+                if (i < nchunk && keep_mask[i][k]) store_unit(i * CHU + (tid + k * NTH) * PV, keep_nw[i][k]);
         for (int ch = KEEP; ch < nchunk; ++ch) {  // (long rows: compare again)
-            const int e0 = ch * CHU + tid * PV;
-            if (tid * PV >= CHU || e0 >= g.c_in) continue;
-            uint4 a, s, nw;
-            val_t dv[PV];
-            unsigned int mask = 0;
-            load_unit(e0, a, s);
-            const unsigned int nt0 = ntrunc;
-            const float tq0 = tsq;
-            diff_unit(a, s, dv, mask, nw);
-            ntrunc = nt0;  // (already counted)
-            tsq = tq0;
-            if (mask) store_unit(e0, nw);
+            for (int k = 0; k < UPT; ++k) {
+                const int u0 = (tid + k * NTH) * PV, e0 = ch * CHU + u0;
+                if (u0 >= CHU || e0 >= g.c_in) continue;
+                uint4 a, s, nw;
+                unsigned int mask = 0;
+                load_unit(e0, a, s);
+                const unsigned int nt0 = ntrunc;
+                const float tq0 = tsq;
+                diff_unit(a, s, mask, nw);
+                ntrunc = nt0;  // (already counted)
+                tsq = tq0;
+                if (mask) store_unit(e0, nw);
+            }
         }
         if (tid == 0) arrive[b] = 0u;
     }
@@ -579,18 +635,19 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
     const int esize = dtype == RRM_I8_I32 ? 1 : 2;
     if (y_out && !fc_delta_writes_out(dtype, g)) return hipErrorInvalidValue;
     const int ranges = (g.c_out_p * esize + FCD_SEG - 1) / FCD_SEG;
-    // 1024 threads instead of 512 where a bf16 row then takes fewer compare rounds and every workgroup still has a compute
-    // unit of its own: 9216 -> 4096, 5 % changed, one stream 10.0 -> 8.6 us; four streams (512 workgroups, two of the small
-    // ones on a compute unit) 15.2 -> 17.8.  int8 rows of twice the length gained nothing (7.4 -> 7.6).
-    const auto rounds = [&](int threads) { return (g.c_in + fcd_round(dtype, threads) - 1) / fcd_round(dtype, threads); };
-    const bool wide = dtype == RRM_BF16_F32 && !g.csc_ptr && (long long)ranges * g.n <= NUM_CU && rounds(1024) < rounds(512);
+    // 704 threads (and the announcing wavefront: three a SIMD, and so the registers for two units per thread; 960 threads spilled,
+    // 10.3 us) instead of 512 where a bf16 row then takes fewer compare rounds and every workgroup still has a compute unit of its
+    // own: 9216 -> 4096, 5 % changed, one stream 8.8 -> 6.75 us; a row that is one round either way loses (4096 -> 4096, 25 %,
+    // 6.7 -> 7.25).
+    const auto rounds = [&](int threads) { return (g.c_in + fcd_round(dtype, threads, g.vec_ok != 0) - 1) / fcd_round(dtype, threads, g.vec_ok != 0); };
+    const bool wide = dtype == RRM_BF16_F32 && !g.csc_ptr && (long long)ranges * g.n <= NUM_CU && rounds(704) < rounds(512);
     auto form = [&]<bool CSC>() {
         if (dtype == RRM_I8_I32) return g.vec_ok ? fc_delta_kernel<RRM_I8_I32, CSC, true, 512> : fc_delta_kernel<RRM_I8_I32, CSC, false, 512>;
         if constexpr (!CSC)
-            if (wide) return g.vec_ok ? fc_delta_kernel<RRM_BF16_F32, CSC, true, 1024> : fc_delta_kernel<RRM_BF16_F32, CSC, false, 1024>;
+            if (wide) return g.vec_ok ? fc_delta_kernel<RRM_BF16_F32, CSC, true, 704> : fc_delta_kernel<RRM_BF16_F32, CSC, false, 704>;
         return g.vec_ok ? fc_delta_kernel<RRM_BF16_F32, CSC, true, 512> : fc_delta_kernel<RRM_BF16_F32, CSC, false, 512>;
     };
-    dim3 block(wide ? 1024 : 512);
+    dim3 block(wide ? 704 : 512);
     if (g.csc_ptr) {
         // pruned weights: up to 64 workgroups per stream share the list (each pays c_out atomic adds at the end)
         const int nw = std::max(1, std::min(64, NUM_CU / g.n));
@@ -613,6 +670,7 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
         return hipGetLastError();
     }
     const int nks = fc_list_splits(dtype, g);
+    if ((long long)ranges * g.n * nks <= NUM_CU) block.x += FCD_BOOKS;
     dim3 grid((unsigned int)ranges, (unsigned int)g.n, (unsigned int)nks);
     const auto kernel = form.template operator()<false>();
     hipLaunchKernelGGL(kernel, grid, block, 0, s, (const unsigned char*)x_t, (unsigned char*)x_snap,

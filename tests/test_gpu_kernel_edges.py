@@ -1,6 +1,7 @@
 """GPU parity at the sizes where a kernel's work split changes: edges of tiles, passes and parts, remainders, the smallest
 and largest of a range.  Integer and binary layers bit-exact, bf16 within the bound of the other parity tests."""
 import pytest
+import torch
 
 import rrm_synth as S
 from gpu_util import run_sequence
@@ -121,7 +122,7 @@ def test_fc_step_fills_the_callers_copy(ci, co, n, dt):
 
 
 # Compare rounds of the FC step: int8 rows around 8192 inputs (two workgroups on a list from there), bf16 rows around 4096 and,
-# with 1024 threads, 7168; rows off the 16-byte units; channels off the 64 bytes of a workgroup; int8 differences of nine bits;
+# of the larger form, 5632 and 11264; rows off the 16-byte units; channels off the 64 bytes of a workgroup; int8 differences of nine bits;
 # and more streams than leave a bf16 workgroup a compute unit of its own.
 @pytest.mark.parametrize("ci,co,n", [(4097, 40, 1), (7160, 5, 2), (7169, 72, 1), (8191, 64, 1), (8193, 100, 2), (14337, 33, 1), (16385, 20, 1), (5000, 2100, 5)])
 @pytest.mark.parametrize("dt", [S.I8, S.BF16])
@@ -131,6 +132,22 @@ def test_fc_step_compare_rounds(ci, co, n, dt):
         for t, frame in enumerate(seq.frames):
             frame[..., -40:] = (-128, 127)[t % 2]
     run_sequence(seq, check_dense=(), fc_batched=0)
+
+
+# Rounds of two units per thread (int8 up to 12288 entries, bf16 of the larger form up to 11264) and their neighbours: the second
+# unit's first and last thread, a second round of one unit, two full rounds, ragged rows, which keep one unit.  One workgroup per
+# compute unit (the wavefront that announces it) and more (many channels and streams: thread 0 does).
+@pytest.mark.parametrize("ci,co,n", [
+    (8192, 64, 1), (8208, 48, 1), (12288, 64, 2), (12304, 32, 1), (24576, 32, 1), (4096, 64, 1), (4104, 32, 2), (5632, 32, 1), (5640, 64, 1),
+    (11264, 32, 1), (11272, 32, 1), (9217, 32, 1), (12289, 16, 2), (9216, 8256, 3),
+])
+@pytest.mark.parametrize("dt", [S.I8, S.BF16])
+def test_fc_step_rounds_of_two_units(ci, co, n, dt):
+    seq = S.random_layer(9990 + ci, S.fc_shape(ci, co, n=n), dt, T=3, frac=0.3)
+    st, _ = run_sequence(seq, check_dense=(), y_out_frames=(1, 2), fc_batched=0)
+    import numpy as np
+    before = [np.zeros_like(seq.frames[0])] + list(seq.frames[:-1])
+    assert st["changed_elems"] == sum(int((a != b).sum()) for a, b in zip(before, seq.frames)) and st["delta_steps"] == 3
 
 
 # The single-launch scatter path: blocks of 8 .. 64 positions (the last one short), one workgroup per block and several, one
