@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256) void bin_conv_kernel(const unsigned int* __res
 // channels of one tap in 32 cycles, where the popcount form takes 256 vector cycles.
 // Measured (28 x 28, 256 -> 256 channels, 64 streams, 5 % of the values flipping): 36.8 us a step with popcounts, 23.0 with weights
 // fetched as nibbles (16 bytes a lane, K step and 32 channels: what the vector cache delivers per clock was the bound), 21.0 so;
-// one stream of 14 x 14, 512 -> 512 channels, 10 %: 16.8, 10.3 and 7.4.
+// one stream of 14 x 14, 512 -> 512 channels, 10 %: 16.8, 10.3 and 7.4 (6.3 with shorter lists and the steps' table).
 //
 // 32 values of a word are 4 registers of E2M1 nibbles; nibble j of register i is value 4 j + (1, 0, 3, 2)[i].  Of a difference
 // (0x2 = +1, 0xA = -1, 0x0 = unchanged) only the bits 1 and 3 are ever set, so two registers lie in one word of LDS, the second one
@@ -223,19 +223,19 @@ __device__ __forceinline__ v16f mma_e2m1(const v8i& a, const v8i& b, v16f c) {
 // are used; if that is all of them, they stay for every pass.
 // TILES = 0: no pass and no sums in LDS; a wavefront takes tiles with all of their K steps.  For long lists, where there are
 // tiles for all wavefronts.
-template <bool FUSED, bool DENSE, int TILES, int KU>
+template <bool FUSED, bool DENSE, int TILES, int KU, int CB>
 __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigned int* __restrict__ xsrc,
                                                        const unsigned int* flip, unsigned int* snap,
                                                        unsigned int* arrive,
                                                        const uint2* __restrict__ wband, const int* __restrict__ bias,
                                                        int* y, BinGeom g, DevStats* __restrict__ stats) {
     constexpr int KPARTS = TILES > 0 ? BAND_WAVES / TILES : 1, PASS = 32 * TILES;
-    constexpr int CPT = 4 * TILES;  // channels per thread of a pass' results
+    constexpr int CPT = 4 * TILES;  // channels per thread of a pass' results (CB = 1: half of the threads have none)
     extern __shared__ uint4 smem[];
     const int npos = g.bth_in * g.btw_in;
     // The mask m and the flips to -1, m & ~x, of a word lie side by side, and a position's words at an odd pitch of such pairs
     // (except in wide layers, without padding): the 32 lanes of a read are 32 positions and meet no bank twice.
-    const int ip = g.bpitch < g.pitch ? g.nslab * 4 : g.nslab * 4 + 1;
+    const int ip = bin_pair_pitch(g);
     uint2* AB = reinterpret_cast<uint2*>(smem);
     // a bit per input position that holds a flip, rows of whole words (with the padding saved above they take no more than a
     // byte per position)
@@ -250,8 +250,8 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
     // z = stream x band
     const int sb = (int)blockIdx.z, zsplit = (int)blockIdx.x, nsplit = g.nsplit;
     const int b = (int)udiv_magic((unsigned int)sb, (unsigned int)g.nbands, g.magic_nbands), band = sb - b * g.nbands;
-    const int nblk = (g.og + 63) >> 6;
-    const int grp = (int)udiv_magic(blockIdx.y, (unsigned int)nblk, g.magic_nblk);
+    const int nblk = (g.og + 32 * CB - 1) / (32 * CB);
+    const int grp = (int)udiv_magic(blockIdx.y, (unsigned int)nblk, CB == 2 ? g.magic_nblk : g.magic_nblk32);
     const int blk = blockIdx.y - grp * nblk;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -262,9 +262,19 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
 
     const int ntaps = g.kh * g.kw, nkt = 2 * g.nslab, nk = ntaps * nkt;  // K steps per tap, in all
     const int n = lane & 31, khalf = lane >> 5;
-    const uint2* wfrag = wband + (long long)(grp * nblk + blk) * nk * 64 + lane;
+    // (the weights are packed for blocks of 64)
+    const uint2* wfrag = wband + (long long)(CB == 2 ? grp * nblk + blk : grp * ((g.og + 63) >> 6) + (blk >> 1)) * nk * 64 + lane;
     const int kpart = TILES > 0 ? wave & (KPARTS - 1) : 0, tile = wave / KPARTS;
-    uint2 w[KU];  // of a step: the lane's word of the block's channels 0 .. 31 and 32 .. 63
+    unsigned int w[KU][CB];  // of a step: the lane's word of the block's channels 0 .. 31 and 32 .. 63
+    auto fetch_w = [&](unsigned int (&f)[CB], int k) __attribute__((always_inline)) {
+        if constexpr (CB == 2) {
+            const uint2 v = wfrag[(long long)k * 64];
+            f[0] = v.x;
+            f[1] = v.y;
+        } else {
+            f[0] = reinterpret_cast<const unsigned int*>(wfrag + (long long)k * 64)[blk & 1];
+        }
+    };
     // (FUSED) input rows whose changes this band counts, by the workgroup of the band's first channel block
     const int own_lo = oy0 * g.stride, own_hi = band == g.nbands - 1 ? g.h : (oy0 + g.band_rows) * g.stride;
     const bool count_here = FUSED && blk == 0 && zsplit == 0;
@@ -273,9 +283,23 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
         for (int i = tid; i < g.bth_in * bw; i += BAND_THREADS) bits[i] = 0;
         for (int i = tid; i < PASS * BAND_RP; i += BAND_THREADS) red[i] = 0;
     };
+    // Where the wavefront's K steps lie in a window, from a table, a lane each (up to 64 of them).  Worked out, it was a chain of some
+    // twenty scalar instructions a step that every pass waited for (a dependent instruction takes 8 cycles): with the table, 14 x 14, 512 ->
+    // 512, 10 %, 64 streams, 26.0 -> 24.0 us a step, one stream 7.5 -> 6.9; 28 x 28, 448 -> 256 dense, 8 streams, 16.6 -> 14.5.
+    int at0 = 0;
     auto first_frags = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < KU; ++i) w[i] = wfrag[(long long)min(kpart + i * KPARTS, nk - 1) * 64];
+        for (int i = 0; i < KU; ++i) fetch_w(w[i], min(kpart + i * KPARTS, nk - 1));
+    };
+    // What does not depend on the staged window, while its loads are on their way.  (The weights too where a compute unit has one
+    // workgroup; where two share it their addresses only hold up the window: 28 x 28, 256 -> 256, 8 streams, 10.1 us and 10.9 so.)
+    auto ahead = [&]() __attribute__((always_inline)) {
+        clear_lds();
+        if (TILES > 0) {
+            at0 = g.steps[min(kpart + lane * KPARTS, nk - 1)];
+            if (TILES == 1) first_frags();
+        }
+        lds_barrier();
     };
     // ---- stage m and m & ~x of the band's input window ----------------------------------------
     if (g.vec4) {
@@ -301,10 +325,7 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
                     xv[i] = *reinterpret_cast<const uint4*>(xsrc + wi);
                 }
             }
-            if (u0 == 0) {
-                clear_lds();
-                lds_barrier();
-            }
+            if (u0 == 0) ahead();
 #pragma unroll
             for (int i = 0; i < BATCH; ++i) {
                 const int u = u0 + i * BAND_THREADS + tid;
@@ -348,10 +369,7 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
                     xv[i] = xsrc[wi];
                 }
             }
-            if (u0 == 0) {
-                clear_lds();
-                lds_barrier();
-            }
+            if (u0 == 0) ahead();
 #pragma unroll
             for (int i = 0; i < BATCH; ++i) {
                 const int u = u0 + i * BAND_THREADS + tid;
@@ -363,7 +381,7 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
         }
     }
     lds_barrier();
-    if (TILES > 0) first_frags();
+    if (TILES > 1) first_frags();
     // this workgroup has read the stored input for the last time
     // (thread 0 keeps the answer to the end: stored at once, it would hold up the list by a memory round trip)
     if (FUSED && tid == 0) arrived_before = atomicAdd(&arrive[b], 1u);
@@ -375,8 +393,11 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
         cnt = nout;
         lds_barrier();
     }
+    // (up to 64 outputs: every wavefront makes the list for itself, and all of them the same one, so that none waits for another: 14 x
+    // 14, 512 -> 512, one stream, 1.0 -> 0.55 us from the staged window to the list)
+    const bool short_list = nout <= 64;
     for (int base = 0; !DENSE && base < nout; base += BAND_THREADS) {
-        const int q = base + tid;
+        const int q = short_list ? lane : base + tid;
         bool act = false;
         if (q < nout) {
             const int oyl = (int)udiv_magic((unsigned int)q, (unsigned int)g.wo, g.magic_wo), x0 = (q - oyl * g.wo) * g.stride;
@@ -400,6 +421,14 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
         }
         // (the same order in every workgroup of the band: the workgroups of a list split deal its chunks among them)
         const unsigned long long mask = __ballot(act);
+        if (short_list) {
+            if (act) list[__popcll(mask & ((1ull << lane) - 1ull))] = (unsigned short)q;
+            cnt = (int)__popcll(mask);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // LDS operations of one wavefront execute in order
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            break;
+        }
         if (lane == 0) s_wc[wave] = (unsigned int)__popcll(mask);
         lds_barrier();
         unsigned int wbase = (unsigned int)cnt, all = 0;
@@ -430,7 +459,7 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
         if (ch + 2 < g.og) yp[2] = v.z;
         if (ch + 3 < g.og) yp[3] = v.w;
     };
-    const int bch = blk * 64;  // the block's first channel of the group
+    const int bch = blk * 32 * CB;  // the block's first channel of the group
     auto y_at = [&](int q) __attribute__((always_inline)) {  // ... at a listed position
         const int oyl = (int)udiv_magic((unsigned int)q, (unsigned int)g.wo, g.magic_wo);
         return y + ((((long long)b * g.ho + oy0 + oyl) * g.wo + (q - oyl * g.wo)) * g.c_out + (long long)grp * g.og + bch);
@@ -441,71 +470,75 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
     };
     if constexpr (TILES > 0) {
         // The list in passes of PASS entries, dealt to the workgroups of a list split.
-        const int el = tid / (64 / CPT), j4 = (tid & (64 / CPT - 1)) * TILES;
+        constexpr int PT = 32 * CB / CPT;  // threads per position of the results
+        const int el = tid / PT, j4 = (tid & (PT - 1)) * TILES;
+        const bool mine = CB == 2 || el < PASS;
         for (int first = zsplit * PASS; first < cnt; first += nsplit * PASS) {
             const bool more = first + nsplit * PASS < cnt;
             // this thread's part of the pass' results: one position, CPT channels; fetched now, needed at the end
             const int e = first + el;
-            int* yp = y_at(list[e < cnt ? e : 0]) + 4 * j4;
+            const bool out = mine && e < cnt;
+            int* yp = y_at(list[out ? e : 0]) + 4 * j4;
             int4 yv[TILES];
 #pragma unroll
             for (int h = 0; h < TILES; ++h) {
                 const int ch = bch + 4 * (j4 + h);
                 yv[h] = make_int4(0, 0, 0, 0);
                 const int* add = DENSE ? (bias ? bias + grp * g.og + ch : nullptr) : yp + 4 * h;
-                if (add && e < cnt && ch < g.og) yv[h] = load4(add, ch);
+                if (add && out && ch < g.og) yv[h] = load4(add, ch);
             }
             // this lane's column: the window of its listed position (an entry beyond the list repeats its first; its sums are
             // not read)
             const bool work = first + 32 * tile < cnt && kpart < nk;  // (the same in every lane)
             const int ent = first + 32 * tile + n;
             const uint2* lp = window_at(list[ent < cnt ? ent : 0]);
-            v16f acc[2];
+            v16f acc[CB];
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
+            for (int c = 0; c < CB; ++c)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
+            int first_of = 0, at = at0;  // the K step whose place lane 0 holds, past kpart
 #pragma unroll 1
             for (int k0 = kpart; work && k0 < nk; k0 += KU * KPARTS) {
+                const int i0 = (k0 - kpart) / KPARTS;  // (a power of two)
+                if (i0 - first_of + KU > 64) {  // (more than 64 steps a wavefront)
+                    first_of = i0;
+                    at = g.steps[min(k0 + lane * KPARTS, nk - 1)];
+                }
                 uint2 ab[KU];
 #pragma unroll
-                for (int i = 0; i < KU; ++i) {
-                    const int k = min(k0 + i * KPARTS, nk - 1);
-                    const int tap = (int)udiv_magic((unsigned int)k, (unsigned int)nkt, g.magic_nkt), st = k - tap * nkt;
-                    const int ky = (int)udiv_magic((unsigned int)tap, (unsigned int)g.kw, g.magic_kw), kx = tap - ky * g.kw;
-                    ab[i] = lp[(ky * g.btw_in + kx) * ip + 2 * st];
-                }
+                for (int i = 0; i < KU; ++i) ab[i] = lp[__builtin_amdgcn_readlane(at, i0 - first_of + i)];
 #pragma unroll
                 for (int i = 0; i < KU; ++i) {
                     const int k = k0 + i * KPARTS;
                     if (k < nk) {
                         const v8i d = difference_e2m1(ab[i]);
-                        acc[0] = mma_e2m1(weights_e2m1(w[i].x), d, acc[0]);
-                        acc[1] = mma_e2m1(weights_e2m1(w[i].y), d, acc[1]);
+#pragma unroll
+                        for (int c = 0; c < CB; ++c) acc[c] = mma_e2m1(weights_e2m1(w[i][c]), d, acc[c]);
                     }
                     if (nk > KU * KPARTS) {  // the step that comes in this place next, or in the next pass
                         const int kn = k + KU * KPARTS;
-                        if (kn < nk || more) w[i] = wfrag[(long long)(kn < nk ? kn : min(kpart + i * KPARTS, nk - 1)) * 64];
+                        if (kn < nk || more) fetch_w(w[i], kn < nk ? kn : min(kpart + i * KPARTS, nk - 1));
                     }
                 }
             }
             if (work) {
                 // columns of a row: [khalf][c][r / 4][r % 4], so that the halves of the wavefront, 32 rows each, meet no bank twice
 #pragma unroll
-                for (int c = 0; c < 2; ++c)
+                for (int c = 0; c < CB; ++c)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) atomicAdd(&red[(32 * tile + n) * BAND_RP + 32 * khalf + 16 * c + r], (int)acc[c][r]);
             }
             lds_barrier();
 #pragma unroll
-            for (int h = 0; h < TILES; ++h) {
+            for (int h = 0; h < TILES && mine; ++h) {
                 const int c4 = j4 + h;  // channels 4 c4 .. of the block: 32 * (c4 / 8) + 8 * (c4 / 2 % 4) + 4 * (c4 % 2)
                 int* r = red + el * BAND_RP + 32 * (c4 & 1) + 16 * (c4 >> 3) + 4 * (c4 >> 1 & 3);
                 constexpr int F = DENSE ? 1 : 2;
                 const int4 v = make_int4(yv[h].x + F * r[0], yv[h].y + F * r[1], yv[h].z + F * r[2], yv[h].w + F * r[3]);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) r[k] = 0;
-                if (e < cnt && bch + 4 * c4 < g.og) store4(yp + 4 * h, bch + 4 * c4, v);
+                if (out && bch + 4 * c4 < g.og) store4(yp + 4 * h, bch + 4 * c4, v);
             }
             if (more) lds_barrier();  // (the sums are cleared)
         }
@@ -674,14 +707,14 @@ hipError_t launch_one(const void* xsrc, const void* flip, unsigned int* tileflag
 
 int bin_consumers(int cw, const BinGeom& g) { return g.groups * ((g.og + 4 * cw - 1) / (4 * cw)); }
 
-template <bool FUSED, bool DENSE, int TILES, int KU>
+template <bool FUSED, bool DENSE, int TILES, int KU, int CB = 2>
 hipError_t launch_band_form(int z, const void* xsrc, const void* flip, void* snap, unsigned int* arrive, const void* wband, const void* bias,
                             void* y, const BinGeom& geom, DevStats* stats, hipStream_t s) {
     BinGeom g = geom;
     g.nsplit = z;
-    dim3 grid((unsigned int)z, (unsigned int)(g.groups * ((g.og + 63) / 64)), (unsigned int)(g.n * g.nbands));
+    dim3 grid((unsigned int)z, (unsigned int)(g.groups * ((g.og + 32 * CB - 1) / (32 * CB))), (unsigned int)(g.n * g.nbands));
     const size_t lds = bin_band_lds_bytes(g, g.band_rows);
-    auto kern = bin_band_kernel<FUSED, DENSE, TILES, KU>;
+    auto kern = bin_band_kernel<FUSED, DENSE, TILES, KU, CB>;
     if (lds > 64 * 1024) {
         static std::mutex mu;
         static size_t granted = 0;
@@ -705,6 +738,11 @@ hipError_t launch_band(const void* xsrc, const void* flip, void* snap, unsigned 
     const long long wgs = (long long)g.n * g.nbands * g.groups * nblk;
     const int nout = g.band_rows * g.wo;
     // A band of at most 32 outputs (see bin_choose_shape): one tile, its K steps over all eight wavefronts.
+    // Where such bands leave compute units empty, blocks of 32 channels: half of the products' and the sums' instructions per wavefront,
+    // twice the workgroups that stage, list and count up the stream's arrival word (us a step with 64 and with 32 channels: 14 x 14, one
+    // stream, 512 -> 512, 56 workgroups of 64, 6.8 and 6.3; two, 256 -> 256, 56, 6.25 and 6.05; but 28 x 28, 256 -> 256, 112, 7.1 and 7.5; 24 x
+    // 24, 256 -> 128, two streams, 96, 7.0 and 7.3.  Dense, no list and no count: 28 x 28 5.35 and 5.05).
+    if (nout <= 32 && (DENSE ? 2 : 4) * wgs <= NUM_CU) return launch_band_form<FUSED, DENSE, 1, 9, 1>(1, xsrc, flip, snap, arrive, wband, bias, y, g, stats, s);
     if (nout <= 32 && wgs <= NUM_CU) return launch_band_form<FUSED, DENSE, 1, 9>(1, xsrc, flip, snap, arrive, wband, bias, y, g, stats, s);
     // The dense layer lists all positions: a wavefront has tiles of its own (us with the K steps split and so: 28 x 28, 256 -> 256, 3 x
     // 3, 64 streams, 45.4 and 34.5; 56 x 56, 64 -> 64, 32 streams, 23.3 and 17.8; 112 x 112, 128 -> 128, 5 x 5, 2 streams, 25.1 and

@@ -38,7 +38,8 @@ struct BinGeom {
     unsigned int magic_nkt;    // same for d = 2*nslab (K steps per tap)
     unsigned int magic_kw;     // same for d = kw
     int bpitch;                // LDS words per staged position of the band kernel: `pitch`, or without its padding
-    unsigned int magic_nbands, magic_nblk, magic_wo;  // same for d = nbands, blocks of 64 channels per group, wo
+    unsigned int magic_nbands, magic_nblk, magic_nblk32, magic_wo;  // same for d = nbands, blocks of 64 and of 32 channels per group, wo
+    const int* steps;          // (device memory) a K step's place in a position's window, in pairs of words: see bin_step_at
     int nsplit;                // (set by the launcher) workgroups that share a band's list
 };
 
@@ -58,6 +59,17 @@ inline size_t bin_band_list_offset(const BinGeom& g) {
 inline size_t bin_band_lds_bytes(const BinGeom& g, int band_rows) {
     const size_t npos = (size_t)((band_rows - 1) * g.stride + g.kh) * (size_t)((g.wo - 1) * g.stride + g.kw);
     return 2 * npos * g.bpitch * 4 + ((npos + 15) & ~(size_t)15) + (((size_t)band_rows * g.wo * 2 + 15) & ~(size_t)15) + BAND_SUMS;
+}
+
+// Pairs of staged words per input position, at an odd pitch except in wide layers; where a K step (a tap, two words of its channels)
+// starts in the window of an output position
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline int bin_pair_pitch(const BinGeom& g) { return g.bpitch < g.pitch ? g.nslab * 4 : g.nslab * 4 + 1; }
+inline int bin_step_at(const BinGeom& g, int k) {
+    const int nkt = 2 * g.nslab, tap = k / nkt;
+    return (tap / g.kw * g.btw_in + tap % g.kw) * bin_pair_pitch(g) + 2 * (k - tap * nkt);
 }
 
 // Does the dense layer run the tile kernel: without bands; wide layers (us, tile and band: 4 x 1100, 128 -> 1024 channels 1 x 1, 11.8
@@ -182,6 +194,7 @@ inline bool bin_choose_shape(const rrm_shape& s, BinGeom& g, bool dense = false)
     g.magic_btw = bin_magic_for(g.btw_in);
     g.magic_nbands = bin_magic_for(g.nbands);
     g.magic_nblk = bin_magic_for((g.og + 63) / 64);
+    g.magic_nblk32 = bin_magic_for((g.og + 31) / 32);
     g.magic_wo = bin_magic_for(g.wo);
     return true;
 }

@@ -64,6 +64,7 @@ struct rrm_layer {
     void* wband = nullptr;   // binary: weights packed for the band kernel (matrix cores)
     unsigned int* bin_arrive = nullptr;  // binary single-launch step: arrival counter per stream
     BinGeom bg{}, bg_dense{};
+    int* bsteps = nullptr;   // binary: BinGeom::steps
     FcGeom fg{};
     // device memory
     void* wpack = nullptr;   // conv: MFMA fragment order; FC: W^T; binary: scalar-load order
@@ -104,7 +105,7 @@ struct rrm_layer {
     int opt_path = 0, opt_wm = 0, opt_fc_splits = 0, opt_terms = 2, opt_bin_cw = 0, opt_conv_kernel = 0, opt_bin_fused = 1;
 
     ~rrm_layer() {
-        void* ptrs[] = {wpack, wpos, wsc, wband, sc_arrive, bin_arrive, offtab, bias, x_snap, y_snap, d0, d1, xpad, bitmap, tileflag, touched, ctrl, fresh, zero16, fc_arrive, fc_part, fc_bpart, csc_ptr, csc_row, csc_val, w_rm, stats};
+        void* ptrs[] = {wpack, wpos, wsc, wband, sc_arrive, bin_arrive, bsteps, offtab, bias, x_snap, y_snap, d0, d1, xpad, bitmap, tileflag, touched, ctrl, fresh, zero16, fc_arrive, fc_part, fc_bpart, csc_ptr, csc_row, csc_val, w_rm, stats};
         for (void* p : ptrs)
             if (p) (void)hipFree(p);
         for (hipEvent_t e : prof_ev) (void)hipEventDestroy(e);
@@ -611,6 +612,11 @@ rrm_status setup_bin(rrm_layer* L, const std::vector<unsigned char>& w) {
         if (st != RRM_OK) return st;
     }
     if (g.band_rows == 0) return RRM_OK;
+    std::vector<int> steps((size_t)ntaps * 2 * g.nslab);
+    for (size_t k = 0; k < steps.size(); ++k) steps[k] = bin_step_at(g, (int)k);
+    rrm_status st3 = upload(steps.data(), steps.size() * sizeof(int), (void**)&L->bsteps);
+    if (st3 != RRM_OK) return st3;
+    g.steps = L->bg_dense.steps = L->bsteps;  // (the window of a position does not depend on the bands)
     // band kernel: the weights' signs in per-lane MFMA order [group][64-channel block][tap][K step of 2 words][lane] x 2 words: of
     // lane l, word 2 * step + l / 32 of the group's words, of the block's output channels l % 32 and 32 + l % 32; a bit that is set
     // is a -1.  Padded channels and words may hold anything (no result is read, no difference is there).

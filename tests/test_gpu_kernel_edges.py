@@ -74,6 +74,20 @@ def test_binary_band_kernel_forms(h, w, ci, co, k, st, pad, g, n, frac):
     run_sequence(seq, check_dense=(0, 2), check_frames=(0, 2))
 
 
+# Lists that every wavefront makes for itself (bands of up to 64 outputs: one, a tile, a tile and more, 64) and not (65); blocks of 32
+# channels (few workgroups: channels below, at, off and beyond them, an odd count of them, groups), in the step and the dense launch;
+# wavefronts of more than 64 K steps, whose places come in turns (words of 2048 and of 4096 channels).
+@pytest.mark.parametrize("h,w,ci,co,k,st,pad,g,n,frac", [
+    (1, 1, 128, 7, 1, 1, 0, 1, 1, 1.0), (4, 8, 256, 32, 3, 1, 1, 1, 1, 0.5), (6, 16, 128, 33, 3, 1, 1, 1, 2, 0.5), (4, 64, 128, 64, 3, 1, 1, 1, 1, 0.3),
+    (4, 65, 128, 65, 3, 1, 1, 1, 1, 0.3), (14, 14, 256, 96, 3, 1, 1, 2, 1, 0.3), (14, 13, 512, 160, 3, 1, 1, 1, 1, 0.4), (9, 9, 256, 31, 3, 2, 1, 1, 3, 0.5),
+    (4, 7, 2048, 40, 3, 1, 1, 1, 1, 0.5), (2, 4, 4096, 33, 3, 1, 1, 1, 1, 0.6), (6, 40, 2048, 70, 3, 1, 1, 1, 2, 0.3),
+])
+def test_binary_bands_of_short_lists_and_narrow_blocks(h, w, ci, co, k, st, pad, g, n, frac):
+    seq = S.random_layer(9450 + h + w + co, S.conv_shape(h, w, ci, co, k, st, pad, g, n=n), S.BIN, T=3, frac=frac, block=2)
+    run_sequence(seq, check_dense=(0, 2))
+    run_sequence(seq, check_dense=(), check_frames=(2,), bin_single_launch=0)
+
+
 # A band fewer where bands make a few workgroups over two per compute unit: in the step and the dense launch, in one of them (many
 # bands; one band left), with strides and words off the 16-byte vectors (two launches).
 @pytest.mark.parametrize("h,w,ci,co,k,st,pad,g,n,frac", [
