@@ -229,6 +229,7 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
                                                        unsigned int* arrive,
                                                        const uint2* __restrict__ wband, const int* __restrict__ bias,
                                                        int* y, BinGeom g, DevStats* __restrict__ stats) {
+    fetch_args<7 * sizeof(void*) + sizeof(BinGeom) + sizeof(void*)>();
     constexpr int KPARTS = TILES > 0 ? BAND_WAVES / TILES : 1, PASS = 32 * TILES;
     constexpr int CPT = 4 * TILES;  // channels per thread of a pass' results (CB = 1: half of the threads have none)
     extern __shared__ uint4 smem[];

@@ -138,6 +138,7 @@ __device__ __forceinline__ T kept(T v) {
 template <int DT, int MODE, int NCB, int NT, int TERMS>
 __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(ConvArgs) {
     const args_t args = (args_t)__builtin_amdgcn_kernarg_segment_ptr();
+    fetch_args<sizeof(ConvArgs)>();
     const auto& g = args->g;
     unsigned int* const flags = args->flags;
     const int* const offtab = args->offtab;

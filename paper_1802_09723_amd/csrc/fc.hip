@@ -57,6 +57,7 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
                                                                const unsigned char* __restrict__ wT, void* y_v,
                                                                void* y_out, unsigned int* arrive, FcGeom g,
                                                                DevStats* __restrict__ stats) {
+    fetch_args<6 * sizeof(void*) + sizeof(FcGeom) + sizeof(void*)>();
     constexpr int PV = DT == RRM_I8_I32 ? 16 : 8;
     constexpr int ESIZE = DT == RRM_I8_I32 ? 1 : 2;
     constexpr int NCG = NTH / 4;  // column groups: 4 lanes (64 bytes) per column
@@ -89,7 +90,7 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
     // wavefront that streams columns (loads and answers return in order).  A launch of at most a workgroup per compute unit has one
     // wavefront more for that; where two share one there is no room for it (four streams of 9216 -> 4096 bf16, 15.9 us, would take
     // 19.8).  One stream, 4096 -> 4096 int8, 5.4 -> 5.05 us.
-    const bool books = blockDim.x > NTH;
+    const bool books = g.books != 0;
     if (wave == NTH / 64) {
         unsigned int total = 0;
         for (int ch = 0; ch < nchunk; ++ch) {
@@ -670,11 +671,13 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
         return hipGetLastError();
     }
     const int nks = fc_list_splits(dtype, g);
-    if ((long long)ranges * g.n * nks <= NUM_CU) block.x += FCD_BOOKS;
+    FcGeom gb = g;
+    gb.books = (long long)ranges * g.n * nks <= NUM_CU;
+    if (gb.books) block.x += FCD_BOOKS;
     dim3 grid((unsigned int)ranges, (unsigned int)g.n, (unsigned int)nks);
     const auto kernel = form.template operator()<false>();
     hipLaunchKernelGGL(kernel, grid, block, 0, s, (const unsigned char*)x_t, (unsigned char*)x_snap,
-                       (const unsigned char*)wT, y, y_out, arrive, g, stats);
+                       (const unsigned char*)wT, y, y_out, arrive, gb, stats);
     return hipGetLastError();
 }
 

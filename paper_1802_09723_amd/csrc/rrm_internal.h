@@ -173,6 +173,7 @@ struct FcGeom {
     int c_out_p;         // row pitch of the transposed weights (elements), multiple of per_vec
     int per_vec;         // output channels per lane per 16-byte load: 16 / 8
     int vec_ok;          // 1: x rows are 16-byte aligned multiples
+    int books;           // (set by the launcher) 1: the wavefront that announces the workgroup is there
     float eps;           // bf16: truncation threshold of the difference (0 = exact)
     // pruned weights (delta step only): column j of W holds the non-zeros csc_ptr[j] .. csc_ptr[j + 1] - 1, each a
     // row index and a value (int8 / bf16 bits); csc_ptr == nullptr = the dense columns are walked
@@ -199,6 +200,20 @@ __device__ __forceinline__ unsigned int udiv_magic(unsigned int u, unsigned int 
     if (!magic) return u;
     const unsigned int q = __umulhi(u, magic);
     return q * d > u ? q - 1u : q;
+}
+
+// Reads a word of each 64-byte line of a kernel's first BYTES of arguments (at most 512), all in flight together.  The lines come from
+// host memory, 0.25 us each, and the compiler reads them one after the other as fields are needed; after this they are in
+// the scalar cache (us a call without and so: 56 x 56, 64 -> 64 bf16, 64 streams, 34.0 and 33.6; 35 x 29, 80 -> 112, nine
+// streams, 16.85 and 16.6; a first frame of 27 x 27, 96 -> 256, 5 x 5 int8, 16 streams, 12.6 and 12.4).
+template <int BYTES>
+__device__ __forceinline__ void fetch_args() {
+    typedef const unsigned int __attribute__((address_space(4))) * words_t;
+    const words_t p = (words_t)__builtin_amdgcn_kernarg_segment_ptr();
+    constexpr int L = (BYTES + 63) / 64;
+    static_assert(L <= 8, "eight lines");
+    auto at = [&](int i) __attribute__((always_inline)) { return p[16 * (i < L ? i : L - 1)]; };
+    asm volatile("" ::"s"(at(0)), "s"(at(1)), "s"(at(2)), "s"(at(3)), "s"(at(4)), "s"(at(5)), "s"(at(6)), "s"(at(7)));
 }
 
 // inclusive sum over the 64 lanes (every lane active)

@@ -213,6 +213,7 @@ __device__ __forceinline__ void scan_body(const unsigned char* __restrict__ x_t,
                                           unsigned long long* __restrict__ bitmap, unsigned int* __restrict__ tileflag,
                                           unsigned int stamp, const ScanGeom& g, unsigned int nvec, unsigned int total_bytes,
                                           DevStats* __restrict__ stats_base, const FusedSrc& fs) {
+    fetch_args<6 * sizeof(void*) + 8 + sizeof(ScanGeom) + 16 + (FUSED ? sizeof(FusedSrc) : 0)>();
     // FUSED: neighbouring workgroups read overlapping rows of the producer's projection (pooling windows), and
     // consecutive workgroup ids go to different XCDs, each with an L2 of its own: the grid is a multiple of 8
     // and workgroup id i works on block (i % 8) * (grid / 8) + i / 8, so that an XCD gets a contiguous range.
@@ -425,6 +426,7 @@ template <int ITER, bool SPEC>
 __global__ __launch_bounds__(256) void scan_pooled_kernel(unsigned int* __restrict__ x_snap, unsigned int* __restrict__ d0,
                                                           unsigned long long* __restrict__ bitmap, unsigned char* __restrict__ flags,
                                                           ScanGeom g, unsigned int nvec, DevStats* __restrict__ stats_base, FusedSrc fs) {
+    fetch_args<4 * sizeof(void*) + sizeof(ScanGeom) + 16 + sizeof(FusedSrc)>();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // (contiguous ranges of units per XCD: see scan_body)
     const unsigned int blk = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
