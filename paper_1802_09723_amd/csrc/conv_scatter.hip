@@ -18,6 +18,14 @@
 // The stored input is committed by the workgroup's own threads from registers; when several workgroups share a
 // position block (output-channel splits) the one that finishes its compare last does it (arrival counter per block,
 // rearmed by that workgroup), because the others still read the old values until then.
+//
+// A step of few changes is bound by its serial chain, not by bytes or matrix rate: arguments (0.25 us a line), the units, the
+// compare, a list, weights, products, adds, commit, each waiting for the one before.  So the arguments are fetched together,
+// the arrival and the commit have a wavefront of their own beside the products, blocks of 1, 2, 4 and 8 units a thread have
+// forms of their own (UPT; one form of 8 with its loops cut short in the others cost 0.3 us: it is the registers and the code to
+// step over), and the compiler is held to registers for 2 wavefronts a SIMD, which is what a chip of two workgroups a compute
+// unit needs, instead of spilling for more (waves_per_eu).  32 x 32, 16 -> 16 int8, 5 %, 4.4 us a step before and 4.2 now; 28 x 28, 512
+// -> 128 1 x 1 int8 6.8 and 5.3; 14 x 14 x 256 bf16 7.1 and 5.9.
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -48,7 +56,20 @@ __device__ __forceinline__ unsigned int f32_to_bf16(float f) {  // round to near
     return u >> 16;
 }
 
-constexpr int ST = 256;  // threads
+constexpr int ST = 256;          // threads that compare and multiply
+constexpr int SCAT_BOOKS = 64;   // ... and of the wavefront that announces the workgroup to the others of its block
+
+// The differences of two entries each (fp32), as bf16 heads and tails, rounded to nearest even
+__device__ __forceinline__ unsigned int pack_bf16(float a, float b) {
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned int, __builtin_convertvector(v2f{a, b}, v2bf));
+}
+__device__ __forceinline__ void split_pair(unsigned int a, unsigned int b, unsigned int& hi, unsigned int& lo) {
+    const float d0 = __uint_as_float(a << 16) - __uint_as_float(b << 16), d1 = __uint_as_float(a & 0xFFFF0000u) - __uint_as_float(b & 0xFFFF0000u);
+    hi = pack_bf16(d0, d1);
+    lo = pack_bf16(d0 - __uint_as_float(hi << 16), d1 - __uint_as_float(hi & 0xFFFF0000u));
+}
 
 // Workgroup barrier that publishes LDS contents only (__syncthreads() would also wait for the answer of the arrival counter)
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -66,22 +87,23 @@ constexpr int scat_planes(int dtype) { return dtype == RRM_BF16_F32 ? 2 : 1; }
 // DIFF (int8): the compare is a scan's (one that computed the input from another layer's projection, in a launch of its own); x_t is
 // the difference it left, zero wherever nothing changed.  The launch keeps the sub-tile flags as the tile kernel does, in a
 // row of workgroups of its own behind the position blocks.
-template <int DT, int TERMS, bool DIFF>
-__global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restrict__ x_t, uint4* x_snap,
+template <int DT, int TERMS, bool DIFF, int UPT>
+__global__ __launch_bounds__(ST + SCAT_BOOKS) __attribute__((amdgpu_waves_per_eu(2, 3))) void conv_scatter_kernel(const uint4* __restrict__ x_t, uint4* x_snap,
                                                           const uint4* __restrict__ wsc, void* y_v, ScatGeom g,
                                                           DevStats* __restrict__ stats_base) {
     typedef typename std::conditional<DT == RRM_I8_I32, v16i, v16f>::type acc_t;
     typedef typename std::conditional<DT == RRM_I8_I32, int, float>::type sc_t;
-    constexpr int UPT = SCAT_UPT;  // 16-byte units per thread at most
+    // (14 x 14, 512 -> 512 int8, six streams, eight units a thread, 14.65 us a step without and 14.75 so)
+    if (DIFF || UPT < SCAT_UPT) fetch_args<4 * sizeof(void*) + sizeof(ScatGeom) + sizeof(void*)>();
     // LDS: difference planes [scat_planes][PB][U] x 16 bytes, then one 16-byte block of zeros
     extern __shared__ uint4 smem[];
     uint4* dl = smem;
     const int plane = g.PB * g.U;  // units per plane
     uint4* zero_unit = dl + scat_planes(DT) * plane;
     __shared__ unsigned int s_flag[64];
-    __shared__ int s_list[ST / 64][64];  // (every wavefront makes its own list: nothing to wait for)
-    __shared__ __align__(16) int s_out[ST / 64][2][32];  // output offsets of an item's rows, or -1
+    __shared__ int s_list[ST / 64 + 1][64];  // (every wavefront makes its own list: nothing to wait for)
     __shared__ unsigned int s_prev;
+    __shared__ __align__(16) int s_out[ST / 64][2][32];  // output offsets of an item's rows, or -1
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -109,6 +131,61 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
             g.fresh[0] = 0u;        // the stored input holds this step's input
             g.touched_all[0] = 0u;  // the flags describe this step
         }
+        return;
+    }
+
+    // A block's workgroups count up one word, and the answer (0.7 us on an idle chip, 1.7 among the 36 of 14 x 14 x 256 bf16) must
+    // not be waited for by a wavefront that has products to make: one more wavefront asks for it, and commits the stored input
+    // if its workgroup was the last of the block to compare.
+    const bool books = !DIFF && UPT * ST <= SCAT_BOOKS_UNITS && g.books != 0;
+    if (books && wave == ST / 64) {
+        const int U = kept(g.U);
+        const unsigned int magic_U = kept(g.magic_U);
+        lds_barrier();
+        lds_barrier();
+        const bool flag = lane < npos && s_flag[lane] != 0u;
+        const unsigned long long found = __ballot(flag);
+        // (the workgroups that share a block see the same list, and without a changed position there is nothing to commit: they
+        // don't count)
+        if (!found) return;
+        unsigned int before = 0;
+        if (lane == 0) before = atomicAdd(&g.arrive[blockIdx.x], 1u);
+        int* const mine = s_list[ST / 64];
+        if (flag) mine[__popcll(found & ((1ull << lane) - 1ull))] = lane * U;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // LDS operations of one wavefront execute in order
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // The units of the changed positions, all in flight, and on their way before it is known whether they are needed: this
+        // commit is what a launch ends with (32 x 32, 16 -> 16 int8, 4.7 us without and 4.2 so; 14 x 14 x 256 bf16, 5 %, 6.65 and
+        // 6.2).
+        constexpr int BATCH = SCAT_BOOKS_UNITS / 64;
+        const int total = (int)__popcll(found) * U;
+        uint4 x[BATCH];
+        auto place = [&](int v) __attribute__((always_inline)) {
+            const unsigned int c = (unsigned int)min(v + lane, total - 1), i = udiv_magic(c, (unsigned int)U, magic_U);
+            return (unsigned int)(mine[i] + (int)(c - i * (unsigned int)U));
+        };
+        auto keep = [&](unsigned int x, unsigned int o) __attribute__((always_inline)) {  // entries whose difference was truncated keep the stored value
+            const float d0 = __uint_as_float(x << 16) - __uint_as_float(o << 16), d1 = __uint_as_float(x & 0xFFFF0000u) - __uint_as_float(o & 0xFFFF0000u);
+            const unsigned int old = (fabsf(d0) < g.eps ? 0xFFFFu : 0u) | (fabsf(d1) < g.eps ? 0xFFFF0000u : 0u);
+            return (x & ~old) | (o & old);
+        };
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k)
+            if (64 * k < total) x[k] = x_t[u0 + place(64 * k)];
+        if (__builtin_amdgcn_readfirstlane((int)before) != g.cs - 1) return;
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k)
+            if (64 * k < total) {
+                uint4* const p = x_snap + u0 + place(64 * k);
+                uint4 n = x[k];
+                if (DT == RRM_BF16_F32 && g.eps != 0.f) {
+                    const uint4 o = *p;
+                    n = make_uint4(keep(n.x, o.x), keep(n.y, o.y), keep(n.z, o.z), keep(n.w, o.w));
+                }
+                if (64 * k + lane < total) *p = n;
+            }
+        if (lane == 0) g.arrive[blockIdx.x] = 0u;
         return;
     }
 
@@ -188,7 +265,29 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
         // bf16 tail.  A loop over the thread's units that differ: unrolled over all of them it was 2400 instructions, most of
         // them fetched for nothing, and the units' loads waited for each other (7 x 7 x 512, one stream, 5 %: 13.3 us a step,
         // and 9.6 with this loop, one list per wavefront, no integer division and the commit ahead of the products).
-        for (unsigned int m = keep_mask; m; m &= m - 1) {
+        if (g.eps == 0.f) {
+            // (nothing is truncated.  Two entries at a time, a third of the instructions; the planes of an entry that is equal are
+            // cleared, because an infinity less itself is not 0)
+            for (unsigned int m = keep_mask; m; m &= m - 1) {
+                const int i = __ffs(m) - 1, v = tid + ST * i;
+                const uint4 ua = dl[v], ub = dl[plane + v];
+                const unsigned int aw[4] = {ua.x, ua.y, ua.z, ua.w}, bw[4] = {ub.x, ub.y, ub.z, ub.w};
+                unsigned int hw[4], lw[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const unsigned int z = aw[k] ^ bw[k], d = (((z & 0x7FFF7FFFu) + 0x7FFF7FFFu) | z) & 0x80008000u;
+                    const unsigned int differ = d | (d - (d >> 15));
+                    split_pair(aw[k], bw[k], hw[k], lw[k]);
+                    hw[k] &= differ;
+                    lw[k] &= differ;
+                    nelem += __popc(d);
+                }
+                dl[v] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+                if (TERMS == 2) dl[plane + v] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
+                s_flag[udiv_magic(v, U, magic_U)] = 1u;
+            }
+        }
+        for (unsigned int m = g.eps == 0.f ? 0u : keep_mask; m; m &= m - 1) {
             const int i = __ffs(m) - 1, v = tid + ST * i;
             const uint4 ua = dl[v], ub = dl[plane + v];
             const unsigned int aw[4] = {ua.x, ua.y, ua.z, ua.w}, bw[4] = {ub.x, ub.y, ub.z, ub.w};
@@ -225,6 +324,18 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
                 keep_mask &= ~(1u << i);
         }
     }
+    if (DT == RRM_BF16_F32 && g.eps != 0.f) {  // what will be stored: truncated entries keep their value
+#pragma unroll
+        for (int i = 0; i < UPT; ++i) {
+            if (ST * i >= nunits) break;
+            const unsigned int tm = (unsigned int)(trunc_mask >> (8 * i)) & 0xFFu;
+            auto pick = [&](unsigned int x, unsigned int sn, int k) __attribute__((always_inline)) {
+                const unsigned int old = (tm >> (2 * k) & 1u ? 0xFFFFu : 0u) | (tm >> (2 * k + 1) & 1u ? 0xFFFF0000u : 0u);
+                return (x & ~old) | (sn & old);
+            };
+            if (tm) a[i] = make_uint4(pick(a[i].x, b[i].x, 0), pick(a[i].y, b[i].y, 1), pick(a[i].z, b[i].z, 2), pick(a[i].w, b[i].w, 3));
+        }
+    }
     nunit = __popc(keep_mask);
     // the wavefront's first item, decoded while others compare
     int item = (int)blockIdx.y + wave * cs;
@@ -247,11 +358,10 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
     const unsigned long long found = __ballot(flag);
     const int cnt = (int)__popcll(found);
     if (cnt > 0) {
-        // Every read of the stored input by this workgroup is done.  (The workgroups that share a block see the same list, and
-        // without a changed position there is nothing to commit: they don't count.)
-        const bool shared_block = !DIFF && cs > 1;
+        // (blocks of more units than the books' wavefront commits at once: every read of the stored input by this workgroup is done)
+        const bool count_here = !DIFF && !books && cs > 1;
         unsigned int arrived_before = 0;
-        if (shared_block && tid == 0) arrived_before = atomicAdd(&g.arrive[blockIdx.x], 1u);
+        if (count_here && tid == 0) arrived_before = atomicAdd(&g.arrive[blockIdx.x], 1u);
         if (flag) s_list[wave][__popcll(found & ((1ull << lane) - 1ull))] = lane;
 
         // ---- the products: work items (channel block of a group, tap, part of the K range of at most 8 steps).  A
@@ -282,8 +392,8 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
         }
         // ---- commit the stored input (only where a difference was applied), while the weights arrive: at the end the answer of
         // the arrival counter would be waited for behind all of the outputs' atomic adds
-        bool last = !DIFF;
-        if (shared_block) {
+        bool last = !DIFF && !books;
+        if (count_here) {
             if (tid == 0) s_prev = arrived_before;
             lds_barrier();
             last = s_prev == (unsigned int)cs - 1u;
@@ -293,17 +403,7 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
 #pragma unroll
             for (int i = 0; i < UPT; ++i) {
                 if (ST * i >= nunits) break;
-                if (!(keep_mask & (1u << i))) continue;
-                uint4 nw = a[i];
-                const unsigned int tm = (unsigned int)(trunc_mask >> (8 * i)) & 0xFFu;
-                if (DT == RRM_BF16_F32 && tm) {
-                    auto pick = [&](unsigned int x, unsigned int sn, int k) __attribute__((always_inline)) {
-                        const unsigned int old = (tm >> (2 * k) & 1u ? 0xFFFFu : 0u) | (tm >> (2 * k + 1) & 1u ? 0xFFFF0000u : 0u);
-                        return (x & ~old) | (sn & old);
-                    };
-                    nw = make_uint4(pick(a[i].x, b[i].x, 0), pick(a[i].y, b[i].y, 1), pick(a[i].z, b[i].z, 2), pick(a[i].w, b[i].w, 3));
-                }
-                x_snap[u0 + tid + ST * i] = nw;
+                if (keep_mask & (1u << i)) x_snap[u0 + tid + ST * i] = a[i];
             }
         }
         while (item < nitems) {
@@ -340,7 +440,14 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
             // 3 x 3, one stream, 14 x 14 x 256, 5 / 25 % changed, 9.2 / 13.7 us instead of 7.4 / 8.4; 10 x 10 x 320, four
             // streams, 10 %, 23.8 instead of 11.4; int8 5 x 5, 27 x 27, 96 -> 256, 10 %, 15.3 instead of 7.2.)
             const int c = cb * 32 + n;
-            sc_t* yg = y + grp * og + c;
+            // An address from a scalar base and a 32-bit offset (an output has at most 2^30 entries) takes half of the instructions, where there are scalar registers for the
+            // base: next to the books they are short, and it would be fetched back from a vector register's lane at every add (us a
+            // step with it and without: 14 x 14, 512 -> 256 int8, half changed, 9.15 and 8.3; 28 x 28, 256 -> 64 bf16, 8.3 and 7.75;
+            // without books 64 x 64, 512 -> 64 1 x 1, 8 streams, 10.05 and 10.3; the five-layer stack 50.3 -> 48.5).
+            constexpr bool SADDR = DIFF || UPT * ST > SCAT_BOOKS_UNITS;
+            const int least = c < og ? 0 : 0x7FFFFFFF;  // (no row is that large: a channel that is not there adds nothing)
+            char* const yb = reinterpret_cast<char*>(y);
+            const unsigned int ch = (unsigned int)(grp * og + c);
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
                 if (t >= ntile) break;
@@ -360,8 +467,12 @@ __global__ __launch_bounds__(ST) void conv_scatter_kernel(const uint4* __restric
                     const int o[4] = {o4.x, o4.y, o4.z, o4.w};
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const sc_t v = acc[t][4 * q + r];
-                        if (o[r] >= 0 && c < og && v != (sc_t)0) atomicAdd(yg + o[r], v);
+                        if constexpr (SADDR) {
+                            if (o[r] >= least) atomicAdd(reinterpret_cast<sc_t*>(yb + ((unsigned int)o[r] + ch) * 4u), acc[t][4 * q + r]);
+                        } else {
+                            const sc_t v = acc[t][4 * q + r];
+                            if (o[r] >= 0 && c < og && v != (sc_t)0) atomicAdd(y + grp * og + c + o[r], v);
+                        }
                     }
                 }
             }
@@ -411,26 +522,42 @@ static hipError_t scatter_lds(size_t lds) {
     static std::once_flag once;
     static hipError_t attr = hipSuccess;
     std::call_once(once, [] {
-        for (const void* f : {reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_I8_I32, 1, false>),
-                              reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_I8_I32, 1, true>),
-                              reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_BF16_F32, 1, false>),
-                              reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_BF16_F32, 2, false>)})
-            if (attr == hipSuccess) attr = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+        auto all = [&]<int UPT>() {
+            for (const void* f : {reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_I8_I32, 1, false, UPT>),
+                                  reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_I8_I32, 1, true, UPT>),
+                                  reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_BF16_F32, 1, false, UPT>),
+                                  reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_BF16_F32, 2, false, UPT>)})
+                if (attr == hipSuccess) attr = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+        };
+        all.template operator()<1>();
+        all.template operator()<2>();
+        all.template operator()<4>();
+        all.template operator()<8>();
     });
     return attr;
 }
 
+// the form of the kernel for blocks of PB * U units: see UPT there
+template <int DT, int TERMS, bool DIFF>
+static auto scatter_form(const ScatGeom& g) {
+    const int upt = (g.PB * g.U + ST - 1) / ST;
+    return upt <= 1 ? conv_scatter_kernel<DT, TERMS, DIFF, 1> : upt <= 2 ? conv_scatter_kernel<DT, TERMS, DIFF, 2>
+           : upt <= 4 ? conv_scatter_kernel<DT, TERMS, DIFF, 4> : conv_scatter_kernel<DT, TERMS, DIFF, 8>;
+}
+
 hipError_t launch_conv_scatter(int dtype, int terms, const void* x_t, void* x_snap, const void* wsc, void* y,
-                               const ScatGeom& g, DevStats* stats, hipStream_t s) {
+                               const ScatGeom& g0, DevStats* stats, hipStream_t s) {
+    ScatGeom g = g0;
     const long long nblk = (g.npos_total + g.PB - 1) / g.PB;
     dim3 grid((unsigned int)nblk, (unsigned int)g.cs);
     const size_t lds = ((size_t)scat_planes(dtype) * g.PB * g.U + 1) * 16;
     const hipError_t e = scatter_lds(lds);
     if (e != hipSuccess) return e;
-    const auto kernel = dtype == RRM_I8_I32 ? conv_scatter_kernel<RRM_I8_I32, 1, false>
-                        : terms == 2        ? conv_scatter_kernel<RRM_BF16_F32, 2, false>
-                                            : conv_scatter_kernel<RRM_BF16_F32, 1, false>;
-    hipLaunchKernelGGL(kernel, grid, dim3(ST), lds, s, static_cast<const uint4*>(x_t), static_cast<uint4*>(x_snap),
+    g.books = g.cs > 1 && g.PB * g.U <= SCAT_BOOKS_UNITS && (dtype == RRM_I8_I32 || nblk * g.cs <= NUM_CU);
+    const auto kernel = dtype == RRM_I8_I32 ? scatter_form<RRM_I8_I32, 1, false>(g)
+                        : terms == 2        ? scatter_form<RRM_BF16_F32, 2, false>(g)
+                                            : scatter_form<RRM_BF16_F32, 1, false>(g);
+    hipLaunchKernelGGL(kernel, grid, dim3(ST + (g.books ? SCAT_BOOKS : 0)), lds, s, static_cast<const uint4*>(x_t), static_cast<uint4*>(x_snap),
                        static_cast<const uint4*>(wsc), y, g, stats);
     return hipGetLastError();
 }
@@ -441,7 +568,7 @@ hipError_t launch_conv_scatter_diff(const void* d0, const void* wsc, void* y, co
     const size_t lds = ((size_t)g.PB * g.U + 1) * 16;
     const hipError_t e = scatter_lds(lds);
     if (e != hipSuccess) return e;
-    const auto kernel = conv_scatter_kernel<RRM_I8_I32, 1, true>;
+    const auto kernel = scatter_form<RRM_I8_I32, 1, true>(g);
     hipLaunchKernelGGL(kernel, grid, dim3(ST), lds, s, static_cast<const uint4*>(d0), static_cast<uint4*>(nullptr),
                        static_cast<const uint4*>(wsc), y, g, stats);
     return hipGetLastError();

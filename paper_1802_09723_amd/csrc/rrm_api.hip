@@ -56,7 +56,7 @@ struct rrm_layer {
     bool use_pos = false;   // ... and does
     int tshift = 2;         // log2 of the side of the output blocks that `touched` flags: 2 (4x4) or 0 (positions)
     void* wpos = nullptr;   // weights packed for the position-gather kernel
-    ScatGeom sc{};          // single-launch scatter path
+    ScatGeom sc{}, sc_diff{};  // single-launch scatter path; its products alone, behind a scan
     bool scat_ok = false;   // the layer can run on it
     bool scat_auto = false; // ... and does when "path" is automatic
     void* wsc = nullptr;    // weights packed for it
@@ -516,13 +516,23 @@ rrm_status setup_scatter(rrm_layer* L, const std::vector<unsigned char>& w) {
             break;
         }
     if (g.PB == 0) return RRM_OK;
-    const long long nblk = (g.npos_total + g.PB - 1) / g.PB;
     // Work items of a position block: (channel block, tap, part of the K range of at most 8 steps); a workgroup's four
     // wavefronts take one item each per round.  Few position blocks: the items of a block are split over more
     // workgroups (one round each at most), up to about two workgroups per compute unit in all.
     g.nkp = (g.nk + 7) / 8;
     const long long items = (long long)g.npair * g.ntaps * g.nkp;
-    g.cs = (int)std::max(1ll, std::min((items + 3) / 4, (2ll * NUM_CU + nblk - 1) / nblk));
+    // Where that leaves few blocks, they are of at most the units that one wavefront commits (see the kernel; us a step: 28 x 28, 512 -> 128 1 x
+    // 1, 25 blocks, 6.85 -> 5.35; 14 x 14, 512 -> 256, half changed, 7 blocks, 8.95 -> 8.2; two streams, 10 %, 13 blocks, 7.45 and 7.55; but 20 x
+    // 20, 384 -> 128, three streams, 38 blocks, 6.9 and 8.3: every block reads all weights).  Behind a scan, where the scan commits,
+    // only a few (a five-layer stack, one stream, 6 blocks, 50.3 and 49.0 us; two and four, 11 and 22 blocks, 58.7 and 59.5, 69.2 and 70.3).
+    const int pb_most = g.PB;
+    auto cut = [&](ScatGeom& t, long long most_blocks) {
+        for (t.PB = pb_most; t.PB > 8 && t.PB * t.U > SCAT_BOOKS_UNITS && t.npos_total <= most_blocks * (t.PB / 2);) t.PB /= 2;
+        const long long nblk = (t.npos_total + t.PB - 1) / t.PB;
+        t.cs = (int)std::max(1ll, std::min((items + 3) / 4, (2ll * NUM_CU + nblk - 1) / nblk));
+        return nblk;
+    };
+    const long long nblk = cut(g, 32);
     g.magic_U = magic_of(g.U); g.magic_hw = magic_of(g.h * g.w); g.magic_w = magic_of(g.w); g.magic_nkp = magic_of(g.nkp);
     g.magic_taps = magic_of(g.ntaps); g.magic_ncb = magic_of(g.ncb); g.magic_kw = magic_of(g.kw); g.magic_stride = magic_of(g.stride);
     std::vector<unsigned char> pack((size_t)g.npair * g.ntaps * g.nk * 64 * 16, 0);
@@ -542,6 +552,8 @@ rrm_status setup_scatter(rrm_layer* L, const std::vector<unsigned char>& w) {
     if (st != RRM_OK) return st;
     if ((st = dalloc((size_t)nblk * sizeof(unsigned int), (void**)&L->sc_arrive)) != RRM_OK) return st;
     g.arrive = L->sc_arrive;
+    L->sc_diff = g;
+    cut(L->sc_diff, 8);
     L->scat_ok = true;
     // Automatic: layers of few output adds.  Two dependent launches and the per-workgroup set-up of the tile kernels cost more
     // there than the step's work; what the scatter pays more for is its adds into the projection, one per changed position, tap,
@@ -889,11 +901,11 @@ rrm_status rrm_layer_create(const void* weights, const void* bias, const rrm_sha
             if ((st = upload(ones, 16, (void**)&L->fresh)) != RRM_OK) return bail(st);
             L->cg.fresh = L->fresh;
             L->pg.fresh = L->fresh;
-            L->cg.touched_all = L->pg.touched_all = L->sc.touched_all = L->ctrl + 4;
-            L->cg.epoch = L->sg.epoch = L->sc.epoch = L->ctrl + 8;
-            L->sc.flags = L->tileflag;
-            L->sc.n_words = L->cg.n_words;
-            L->sc.fresh = L->fresh;
+            L->cg.touched_all = L->pg.touched_all = L->sc.touched_all = L->sc_diff.touched_all = L->ctrl + 4;
+            L->cg.epoch = L->sg.epoch = L->sc_diff.epoch = L->ctrl + 8;
+            L->sc_diff.flags = L->tileflag;
+            L->sc_diff.n_words = L->cg.n_words;
+            L->sc_diff.fresh = L->fresh;
         }
         if ((st = dalloc(256, &L->zero16)) != RRM_OK) return bail(st);
     }
@@ -1047,7 +1059,7 @@ rrm_status rrm_step_from_projection(rrm_layer* L, rrm_layer* P, int shift, int p
         // 96 -> 256 7.0 / 6.0, 13 x 13, 256 -> 384 8.9 / 4.8, 384 -> 384 8.4 / 5.5, 384 -> 256 8.4 / 5.8; the stack's step at
         // 1 / 2 / 4 / 8 / 16 streams 63.4 / 68.0 / 73.1 / 87.7 / 99.2 without, 54.2 / 61.9 / 71.8 / 88.2 / 98.9 with it (with
         // twice as many adds admitted 54.1 / 62.2 / 71.9 / 89.3 / 107.4).
-        RRM_HIP(launch_conv_scatter_diff(L->d0, L->wsc, L->y_snap, L->sc, L->stats, st));
+        RRM_HIP(launch_conv_scatter_diff(L->d0, L->wsc, L->y_snap, L->sc_diff, L->stats, st));
     else
         RRM_HIP(launch_conv(L->dtype, MODE_DELTA, L->cg.wg_cb, L->cg.nt, 1, L->d0, L->d1, L->zero16, L->tileflag,
                             L->wpack, L->offtab, L->bias, L->y_snap, L->cg, L->stats, st));

@@ -143,6 +143,7 @@ struct ConvGeom {
 };
 
 // Geometry of the single-launch scatter convolution (conv_scatter.hip).
+constexpr int SCAT_BOOKS_UNITS = 1024;  // units of a position block that one wavefront commits at once
 constexpr int SCAT_UPT = 8;  // 16-byte units of x per thread of a position block at most
 struct ScatGeom {
     int n, h, w, c_out, kh, kw, stride, pad, groups;
@@ -157,6 +158,7 @@ struct ScatGeom {
     int PB;              // input positions per block (at most 64)
     int cs;              // work-item splits: workgroups per position block
     long long npos_total;  // n * h * w
+    int books;           // (set by the launcher) 1: the wavefront that announces the workgroup is there
     float eps;           // bf16: truncation threshold of the difference (0 = exact)
     unsigned int magic_U, magic_hw, magic_w, magic_nkp, magic_taps, magic_ncb, magic_kw, magic_stride;  // reciprocals
     unsigned int* arrive;       // one word per position block (used when cs > 1; rearmed by the kernel)

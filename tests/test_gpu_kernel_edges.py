@@ -179,6 +179,75 @@ def test_scatter_path_edges(h, w, ci, co, k, st, pad, g, n, dt):
     run_sequence(seq, check_dense=(), path=3)
 
 
+# Forms of the scatter kernel: one, two, four and eight units per thread, and one beyond a whole number of them; the commit by the
+# wavefront that announces the workgroup (few workgroups; 1024 units, the most that it takes), by all threads (more units, many
+# bf16 workgroups, one workgroup per block); blocks halved to those 1024 units and not (few blocks, and many).  With and without a threshold
+# (bf16): the stored input holds the entries that differ by it or more, the projection is that input's.
+@pytest.mark.parametrize("h,w,ci,co,k,n", [
+    (9, 7, 16, 16, 3, 1), (16, 16, 64, 32, 3, 1), (12, 11, 144, 40, 3, 1), (14, 14, 256, 64, 3, 1), (14, 14, 512, 32, 1, 1), (8, 8, 1024, 33, 1, 1),
+    (40, 40, 512, 16, 1, 2), (31, 33, 256, 96, 3, 1), (24, 24, 16, 8, 1, 9),
+])
+@pytest.mark.parametrize("dt,eps", [(S.I8, 0.0), (S.BF16, 0.0), (S.BF16, 0.25)])
+def test_scatter_kernel_forms(h, w, ci, co, k, n, dt, eps):
+    import numpy as np
+    import oracle
+    from gpu_util import assert_matches, make_layer, to_device, x_bytes
+    seq = S.random_layer(9880 + h + ci, S.conv_shape(h, w, ci, co, k, 1, k // 2, 1, n=n), dt, T=5, frac=0.15, block=3)
+    seq.frames[3] = seq.frames[2].copy()
+    layer = make_layer(seq, path=3)
+    if eps:
+        layer.set_threshold(eps)
+    stored = np.zeros_like(seq.frames[0])
+    for t, x in enumerate(seq.frames):
+        layer.step(to_device(x, dt))
+        if dt == S.BF16:
+            f32 = lambda a: (a.astype(np.uint32) << 16).view(np.float32)
+            keep = np.abs(f32(x) - f32(stored)) < np.float32(eps)
+            stored = np.where(keep, stored, x)
+        else:
+            stored = x
+        assert np.array_equal(layer.x_snapshot_bytes().cpu().numpy(), x_bytes(stored, dt)), f"stored input after frame {t}"
+        want = oracle.dense(seq.shape, dt, seq.weights, seq.bias, stored)
+        assert_matches(layer.y_snapshot().cpu().numpy(), want, dt, f"frame {t}")
+    layer.destroy()
+
+
+# The differences without a threshold are made by another loop than with one.  Denormal, huge and infinite entries that change, and
+# infinite ones that stay beside entries that change: with a threshold that truncates nothing the projections are the same bits
+# (1 x 1 and one part of the channels: one add an output), and an infinity that stays adds nothing.
+def test_scatter_differences_of_special_values():
+    import numpy as np
+    import torch
+    from gpu_util import make_layer, to_device
+    seq = S.random_layer(9891, S.conv_shape(9, 11, 128, 40, 1, 1, 0, 1), S.BF16, T=4, frac=0.3, block=2)
+    for t, x in enumerate(seq.frames):
+        x[..., 3, 4, 5] = 0x7F80
+        x[..., 7, 2, 0] = 0xFF80
+        x[..., 5, 5, :] = [(0x0001, 0x8003, 0x7F7F, 0x0080)[(c + t) % 4] for c in range(128)]
+        x[..., 6, 6, :] = 0x7F7F if t % 2 else 0xFF7F
+        x[..., 8, 8, 17:19] = (0x7F80, 0x4000) if t == 2 else (0x4000, 0x7F80)
+        x[..., 3, 4, 6] = x[..., 7, 2, 9] = 0x3F80 + t
+    exact, other = make_layer(seq, path=3), make_layer(seq, path=3)
+    other.set_threshold(2.0 ** -149)
+    for t, x in enumerate(seq.frames):
+        got = []
+        for layer in (exact, other):
+            layer.step(to_device(x, S.BF16))
+            got.append(layer.y_snapshot().cpu().numpy())
+        assert np.array_equal(got[0], got[1], equal_nan=True), f"frame {t}"
+        if t == 0:  # (an infinity's tail is not a number: the projections that the first frame left start again from zero)
+            for layer in (exact, other):
+                state = type("State", (), {"__cuda_array_interface__": {
+                    "shape": (9 * 11 * 40,), "typestr": "<f4", "data": (layer.snapshot_ptrs()[1], False), "version": 2}})()
+                torch.as_tensor(state, device="cuda").zero_()
+            torch.cuda.synchronize()
+        else:
+            y = got[0].reshape(9, 11, 40)
+            assert np.isfinite(y[3, 4]).all() and np.isfinite(y[7, 2]).all() and y[3, 4].any() and y[7, 2].any(), f"frame {t}"
+    exact.destroy()
+    other.destroy()
+
+
 # ... and the bf16 blocks whose planes and lists together are beyond 64 KB of LDS.
 @pytest.mark.parametrize("ci", [496, 1000])
 def test_scatter_path_with_the_largest_blocks(ci):
