@@ -20,11 +20,12 @@ namespace {
 
 constexpr int FCD_UN = 8;           // columns in flight per lane
 // Inputs of a compare round, and so entries of the list (4 or 8 bytes each): one or two 16-byte units per thread.  A round is a
-// chain of loads, two barriers and column reads that nothing overlaps, 1.7 us of it, so that whole-unit rows of up to 12288 int8
-// entries are one round, and bf16 rows of up to 11264 where the larger form has a compute unit to itself.  One stream, 9216 -> 4096,
+// chain of loads, two barriers and column reads that nothing overlaps, 1.7 us of it, so that rows of up to 12288 int8
+// entries (of whole columns) are one round, and bf16 rows of up to 11264 where the larger form has a compute unit to itself.  One stream, 9216 -> 4096,
 // two rounds and one: int8, 5 / 25 % changed, 7.4 / 9.5 -> 6.1 / 8.1 us, bf16 8.8 / 13.0 -> 6.75 / 11.8.
-constexpr int fcd_round(int dtype, int threads, bool two) {
-    return !two ? threads * (dtype == RRM_I8_I32 ? 16 : 8) : dtype == RRM_I8_I32 ? 12288 : threads > 512 ? threads * 16 : threads * 8;
+constexpr int fcd_round(int dtype, int threads, bool csc) {
+    if (dtype == RRM_I8_I32) return csc ? threads * 16 : 12288;
+    return threads * (threads > 512 ? 16 : 8);
 }
 constexpr int FCD_BOOKS = 64;       // threads of the wavefront that announces the workgroup
 // Workgroup barrier that publishes LDS contents only (__syncthreads() would also wait for loads and answers on their way)
@@ -50,7 +51,7 @@ __device__ __forceinline__ float bf16_to_f32(unsigned int h) { return __uint_as_
 //
 // ROWS16 = g.vec_ok: rows of whole 16-byte units.  A form of its own, because the code that reads ragged rows costs the
 // others time even where it is not taken (one stream, 9216 -> 4096: int8, 25 % changing, 11.42 -> 11.36 us, bf16, 5 %,
-// 11.92 -> 11.78; the ragged rows themselves, 3945 -> 413 bf16, 7.95 -> 7.84).
+// 11.92 -> 11.78).
 template <int DT, bool CSC, bool ROWS16, int NTH>
 __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigned char* __restrict__ x_t,
                                                                unsigned char* x_snap,
@@ -76,7 +77,7 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
         if constexpr (DT == RRM_I8_I32) return (val_t)((int)e >> 16);
         else return (val_t)__uint_as_float(e.y);
     };
-    constexpr int CHU = fcd_round(DT, NTH, ROWS16 && !CSC);  // inputs of one compare round = capacity of the list
+    constexpr int CHU = fcd_round(DT, NTH, CSC);  // inputs of one compare round = capacity of the list
     constexpr int UPT = (CHU / PV + NTH - 1) / NTH;  // units of a round per thread
     __shared__ entry_t list[CHU];
     __shared__ __align__(16) val_t red[NTH / 64][4 * PV];  // the wavefronts' sums of the 4 * PV channels
@@ -127,10 +128,11 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
     unsigned int ntrunc = 0, total = 0;
     float tsq = 0.f;
 
-    // the two copies of one 16-byte unit (PV entries from element e0 of the row).  Rows that are not 16-byte
-    // multiples: the five aligned words around the unit, all in flight together, shifted into place, with zeros beyond
-    // the row's end (element by element the loads waited for each other: 3945 -> 413
-    // bf16, one stream, 11.1 -> 8.5 us)
+    // the two copies of one 16-byte unit (PV entries from element e0 of the row).  Rows that are not 16-byte multiples: one
+    // load each at whatever alignment the entries have (vector memory takes any), the array's last unit from its last sixteen bytes
+    // and shifted into place, with zeros beyond the row's end.  (As five aligned words each,
+    // shifted into place, they took 20 registers a unit and a chain of 1.5 us: one stream, 5 % changed, 9001 -> 4001 bf16 10.3 -> 7.2 us, 8301
+    // -> 1001 int8, in one round since, 9.6 -> 6.3; six streams of 5886 -> 269 bf16 8.2 -> 6.6.)
     auto load_unit = [&](int e0, uint4& a, uint4& s) {
         if constexpr (ROWS16) {
             a = *reinterpret_cast<const uint4*>(x_t + (row + e0) * ESIZE);
@@ -138,32 +140,33 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
             return;
         }
         const long long off = (row + e0) * ESIZE, total_bytes = (long long)g.n * g.c_in * ESIZE;
-        const unsigned int sh = (unsigned int)off & 3u;
-        unsigned int ra[5], rs[5];
-#pragma unroll
-        for (int i = 0; i < 5; ++i) {
-            const long long d = off - sh + 4 * i;
-            ra[i] = rs[i] = 0u;
-            if (d + 4 <= total_bytes) {
-                ra[i] = *reinterpret_cast<const unsigned int*>(x_t + d);
-                rs[i] = *reinterpret_cast<const unsigned int*>(x_snap + d);
-            } else {  // (the array's last bytes)
-                for (int k = 0; k < 4 && d + k < total_bytes; ++k) {
-                    ra[i] |= (unsigned int)x_t[d + k] << (8 * k);
-                    rs[i] |= (unsigned int)x_snap[d + k] << (8 * k);
-                }
+        typedef unsigned __int128 u128;
+        u128 ua = 0, us = 0;
+        if (total_bytes >= 16) {
+            const long long at = off + 16 <= total_bytes ? off : total_bytes - 16;
+            __builtin_memcpy(&ua, x_t + at, 16);
+            __builtin_memcpy(&us, x_snap + at, 16);
+            if (at != off) {
+                ua >>= 8 * (int)(off - at);
+                us >>= 8 * (int)(off - at);
             }
-        }
-        unsigned int aw[4], sw[4];
-        const int valid = (g.c_in - e0) * ESIZE;  // bytes of the row from here on
+        } else {
+            typedef typename std::conditional<DT == RRM_I8_I32, unsigned char, unsigned short>::type elem_t;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const unsigned int keep = valid >= 4 * i + 4 ? 0xFFFFFFFFu : (valid <= 4 * i ? 0u : (1u << (8 * (valid - 4 * i))) - 1u);
-            aw[i] = __builtin_amdgcn_alignbyte(ra[i + 1], ra[i], sh) & keep;
-            sw[i] = __builtin_amdgcn_alignbyte(rs[i + 1], rs[i], sh) & keep;
+            for (int e = 0; e < PV; ++e)
+                if (off + e * ESIZE < total_bytes) {
+                    ua |= (u128)reinterpret_cast<const elem_t*>(x_t + off)[e] << (8 * ESIZE * e);
+                    us |= (u128)reinterpret_cast<const elem_t*>(x_snap + off)[e] << (8 * ESIZE * e);
+                }
         }
-        a = make_uint4(aw[0], aw[1], aw[2], aw[3]);
-        s = make_uint4(sw[0], sw[1], sw[2], sw[3]);
+        const int valid = (g.c_in - e0) * ESIZE;  // bytes of the row from here on
+        if (valid < 16) {
+            const u128 keep = ((u128)1 << (8 * valid)) - 1;
+            ua &= keep;
+            us &= keep;
+        }
+        a = __builtin_bit_cast(uint4, ua);
+        s = __builtin_bit_cast(uint4, us);
     };
     // difference of a unit: mask of the entries to apply, and the unit's new snapshot
     auto diff_unit = [&](const uint4& a, const uint4& s, unsigned int& mask, uint4& n_out) {
@@ -207,6 +210,10 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
     auto store_unit = [&](int e0, const uint4& nw) {  // commit a unit's new snapshot
         if constexpr (ROWS16) {
             *reinterpret_cast<uint4*>(x_snap + (row + e0) * ESIZE) = nw;
+            return;
+        }
+        if (e0 + PV <= g.c_in) {
+            __builtin_memcpy(x_snap + (row + e0) * ESIZE, &nw, 16);
             return;
         }
         const unsigned int w[4] = {nw.x, nw.y, nw.z, nw.w};
@@ -640,7 +647,7 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
     // 10.3 us) instead of 512 where a bf16 row then takes fewer compare rounds and every workgroup still has a compute unit of its
     // own: 9216 -> 4096, 5 % changed, one stream 8.8 -> 6.75 us; a row that is one round either way loses (4096 -> 4096, 25 %,
     // 6.7 -> 7.25).
-    const auto rounds = [&](int threads) { return (g.c_in + fcd_round(dtype, threads, g.vec_ok != 0) - 1) / fcd_round(dtype, threads, g.vec_ok != 0); };
+    const auto rounds = [&](int threads) { return (g.c_in + fcd_round(dtype, threads, false) - 1) / fcd_round(dtype, threads, false); };
     const bool wide = dtype == RRM_BF16_F32 && !g.csc_ptr && (long long)ranges * g.n <= NUM_CU && rounds(704) < rounds(512);
     auto form = [&]<bool CSC>() {
         if (dtype == RRM_I8_I32) return g.vec_ok ? fc_delta_kernel<RRM_I8_I32, CSC, true, 512> : fc_delta_kernel<RRM_I8_I32, CSC, false, 512>;

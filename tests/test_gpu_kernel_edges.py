@@ -149,7 +149,7 @@ def test_fc_step_compare_rounds(ci, co, n, dt):
 
 
 # Rounds of two units per thread (int8 up to 12288 entries, bf16 of the larger form up to 11264) and their neighbours: the second
-# unit's first and last thread, a second round of one unit, two full rounds, ragged rows, which keep one unit.  One workgroup per
+# unit's first and last thread, a second round of one unit, two full rounds, ragged rows.  One workgroup per
 # compute unit (the wavefront that announces it) and more (many channels and streams: thread 0 does).
 @pytest.mark.parametrize("ci,co,n", [
     (8192, 64, 1), (8208, 48, 1), (12288, 64, 2), (12304, 32, 1), (24576, 32, 1), (4096, 64, 1), (4104, 32, 2), (5632, 32, 1), (5640, 64, 1),
@@ -162,6 +162,26 @@ def test_fc_step_rounds_of_two_units(ci, co, n, dt):
     import numpy as np
     before = [np.zeros_like(seq.frames[0])] + list(seq.frames[:-1])
     assert st["changed_elems"] == sum(int((a != b).sum()) for a, b in zip(before, seq.frames)) and st["delta_steps"] == 3
+
+
+# Ragged rows, read and committed 16 bytes at a time at any alignment: arrays of fewer than 16 bytes, of 16 and just over (the
+# array's last unit is read from its last 16 bytes), rows one entry off whole units, many streams (a row's last unit beside the next
+# row's first), second units of a thread that end with the row.
+@pytest.mark.parametrize("ci,co,n", [
+    (1, 3, 1), (3, 5, 2), (7, 16, 1), (5, 4, 3), (9, 8, 1), (15, 20, 1), (17, 20, 1), (25, 9, 7), (127, 33, 15), (4103, 20, 3), (8195, 24, 2), (5633, 40, 2),
+    (11263, 16, 1), (12287, 33, 2),
+])
+@pytest.mark.parametrize("dt", [S.I8, S.BF16])
+def test_fc_step_of_ragged_rows(ci, co, n, dt):
+    import numpy as np
+    from gpu_util import make_layer, to_device, x_bytes
+    seq = S.random_layer(9940 + ci, S.fc_shape(ci, co, n=n), dt, T=4, frac=0.5)
+    run_sequence(seq, check_dense=(), fc_batched=0)
+    layer = make_layer(seq, fc_batched=0)
+    for t, x in enumerate(seq.frames):
+        layer.step(to_device(x, dt))
+        assert np.array_equal(layer.x_snapshot_bytes().cpu().numpy(), x_bytes(x, dt)), f"stored input after frame {t}"
+    layer.destroy()
 
 
 # The single-launch scatter path: blocks of 8 .. 64 positions (the last one short), one workgroup per block and several, one
