@@ -129,7 +129,8 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
     float tsq = 0.f;
 
     // the two copies of one 16-byte unit (PV entries from element e0 of the row).  Rows that are not 16-byte multiples: one
-    // load each at whatever alignment the entries have (vector memory takes any), the array's last unit from its last sixteen bytes
+    // load each at whatever alignment the entries have (vector memory takes any), both under way before either is looked at (with
+    // load_unit_at, one after the other, 0.5 us more), the array's last unit from its last sixteen bytes
     // and shifted into place, with zeros beyond the row's end.  (As five aligned words each,
     // shifted into place, they took 20 registers a unit and a chain of 1.5 us: one stream, 5 % changed, 9001 -> 4001 bf16 10.3 -> 7.2 us, 8301
     // -> 1001 int8, in one round since, 9.6 -> 6.3; six streams of 5886 -> 269 bf16 8.2 -> 6.6.)

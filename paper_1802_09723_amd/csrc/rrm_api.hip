@@ -864,6 +864,7 @@ rrm_status rrm_layer_create(const void* weights, const void* bias, const rrm_sha
             sg.wp = L->cg.wp;
             sg.cp = L->cg.cp;
             sg.cg = L->cg.cg;
+            sg.r_cg = 1.0 / (double)sg.cg;
             sg.groups = s.groups;
             L->d_bytes = (size_t)s.n * s.h * sg.wp * s.groups * sg.cp * L->esize;
             if ((st = dalloc(L->d_bytes, &L->xpad)) != RRM_OK) return bail(st);  // dense path's repacked x

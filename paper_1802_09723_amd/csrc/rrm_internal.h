@@ -51,7 +51,7 @@ struct ScanGeom {
     int scatter, wp, cp, cg, groups;
     // reciprocals for the scan's index arithmetic: doubles for dividends up to 2^30 (see udiv_big), a
     // 32-bit one for the small dividends of the receptive-field bounds (floor(2^32/stride)+1, 0 for 1)
-    double r_c, r_hw, r_w;
+    double r_c, r_hw, r_w, r_cg;
     unsigned int magic_stride;
     float eps;  // bf16: truncation threshold of the difference (0 = exact)
     unsigned long long tiles_per_step;  // what a dense step would count as "tiles" (added to the device counters)
@@ -202,6 +202,25 @@ __device__ __forceinline__ unsigned int udiv_magic(unsigned int u, unsigned int 
     if (!magic) return u;
     const unsigned int q = __umulhi(u, magic);
     return q * d > u ? q - 1u : q;
+}
+
+// The 16 bytes at byte `off` of an array, at any alignment (vector memory takes any), with zeros from `valid` bytes on: one load,
+// and the array's last ones from its last sixteen bytes, shifted into place.  off < total, valid > 0, off a multiple of ESIZE.
+template <int ESIZE>
+__device__ __forceinline__ uint4 load_unit_at(const unsigned char* p, long long off, long long total, int valid) {
+    typedef unsigned __int128 u128;
+    u128 u = 0;
+    if (total >= 16) {
+        const long long at = off + 16 <= total ? off : total - 16;
+        __builtin_memcpy(&u, p + at, 16);
+        if (at != off) u >>= 8 * (int)(off - at);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 16; e += ESIZE)
+            if (off + e < total) u |= (u128)(ESIZE == 1 ? p[off + e] : *reinterpret_cast<const unsigned short*>(p + off + e)) << (8 * e);
+    }
+    if (valid < 16) u &= ((u128)1 << (8 * valid)) - 1;
+    return __builtin_bit_cast(uint4, u);
 }
 
 // Reads a word of each 64-byte line of a kernel's first BYTES of arguments (at most 512), all in flight together.  The lines come from

@@ -184,6 +184,33 @@ def test_fc_step_of_ragged_rows(ci, co, n, dt):
     layer.destroy()
 
 
+# Channel runs that are not whole units: a unit of x within one run, across two (of a position's groups, of two positions), a run
+# of just over a unit and of a unit less than two, runs shorter than a unit, arrays of fewer than 16 bytes, the array's last unit cut
+# short.  Changes come and go, so that the padded differences are written and wiped; the dense launch re-lays the whole frame.
+@pytest.mark.parametrize("h,w,ci,co,k,g,n", [
+    (1, 1, 5, 4, 1, 1, 1), (1, 2, 3, 8, 1, 1, 1), (5, 7, 17, 8, 3, 1, 1), (9, 6, 31, 16, 3, 1, 2), (4, 5, 100, 33, 3, 1, 3), (7, 5, 154, 20, 5, 2, 2),
+    (3, 3, 66, 12, 3, 3, 1), (6, 6, 40, 16, 3, 1, 2), (8, 9, 505, 24, 1, 1, 1), (6, 5, 36, 8, 3, 4, 2), (11, 13, 23, 9, 3, 1, 5),
+])
+@pytest.mark.parametrize("dt,eps", [(S.I8, 0.0), (S.BF16, 0.0), (S.BF16, 0.25)])
+def test_ragged_channel_runs(h, w, ci, co, k, g, n, dt, eps):
+    import numpy as np
+    import oracle
+    from gpu_util import assert_matches, make_layer, to_device
+    seq = S.random_layer(9860 + h + ci, S.conv_shape(h, w, ci, co, k, 1, k // 2, g, n=n), dt, T=5, frac=0.3, block=2)
+    seq.frames[3] = seq.frames[2].copy()
+    run_sequence(seq, check_dense=(0, 1, 4), dense_switch_pct=100)
+    if eps:
+        layer = make_layer(seq, dense_switch_pct=100)
+        layer.set_threshold(eps)
+        stored = np.zeros_like(seq.frames[0])
+        f32 = lambda a: (a.astype(np.uint32) << 16).view(np.float32)
+        for t, x in enumerate(seq.frames):
+            layer.step(to_device(x, dt))
+            stored = np.where(np.abs(f32(x) - f32(stored)) < np.float32(eps), stored, x)
+            assert_matches(layer.y_snapshot().cpu().numpy(), oracle.dense(seq.shape, dt, seq.weights, seq.bias, stored), dt, f"frame {t}")
+        layer.destroy()
+
+
 # The single-launch scatter path: blocks of 8 .. 64 positions (the last one short), one workgroup per block and several, one
 # tile of 32 listed positions and two, units off the pairs of a K step, several parts of K, channels off the blocks of 32,
 # strides that skip positions, groups; a few positions change, then all of them, then none.
