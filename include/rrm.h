@@ -158,7 +158,7 @@ rrm_status rrm_read_snapshot(rrm_layer* layer, void* x_dst, void* y_dst, void* h
  *   "fc_splits"   FC, dense path: number of row splits of the weight matrix, in [1, the default chosen at
  *                 create] (the partial-sum scratch is sized for the default).  Without effect where the dense layer
  *                 runs as one product (see "fc_batched"); rrm_dense_noalloc always splits so
- *   "fc_batched"  FC with 4 to 4096 streams (c_out a multiple of 16, rows of whole 64-byte steps): 1 (default) =
+ *   "fc_batched"  FC with 4 to 4096 streams (c_out off 16 or rows off 64 bytes: where it pays): 1 (default) =
  *                 the dense layer runs as one product on the matrix cores with W read once for all streams, and
  *                 so does a step where that is cheaper than the streams' column walks (many streams or output
  *                 channels, long rows): it commits x_t and recomputes b + W x_t, one pass over W whatever the density;

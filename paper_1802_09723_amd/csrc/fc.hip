@@ -21,10 +21,10 @@ namespace {
 constexpr int FCD_UN = 8;           // columns in flight per lane
 // Inputs of a compare round, and so entries of the list (4 or 8 bytes each): one or two 16-byte units per thread.  A round is a
 // chain of loads, two barriers and column reads that nothing overlaps, 1.7 us of it, so that rows of up to 12288 int8
-// entries (of whole columns) are one round, and bf16 rows of up to 11264 where the larger form has a compute unit to itself.  One stream, 9216 -> 4096,
+// entries (`two`) are one round, and bf16 rows of up to 11264 where the larger form has a compute unit to itself.  One stream, 9216 -> 4096,
 // two rounds and one: int8, 5 / 25 % changed, 7.4 / 9.5 -> 6.1 / 8.1 us, bf16 8.8 / 13.0 -> 6.75 / 11.8.
-constexpr int fcd_round(int dtype, int threads, bool csc) {
-    if (dtype == RRM_I8_I32) return csc ? threads * 16 : 12288;
+constexpr int fcd_round(int dtype, int threads, bool two) {
+    if (dtype == RRM_I8_I32) return two ? 12288 : threads * 16;
     return threads * (threads > 512 ? 16 : 8);
 }
 constexpr int FCD_BOOKS = 64;       // threads of the wavefront that announces the workgroup
@@ -52,7 +52,7 @@ __device__ __forceinline__ float bf16_to_f32(unsigned int h) { return __uint_as_
 // ROWS16 = g.vec_ok: rows of whole 16-byte units.  A form of its own, because the code that reads ragged rows costs the
 // others time even where it is not taken (one stream, 9216 -> 4096: int8, 25 % changing, 11.42 -> 11.36 us, bf16, 5 %,
 // 11.92 -> 11.78).
-template <int DT, bool CSC, bool ROWS16, int NTH>
+template <int DT, bool CSC, bool ROWS16, int NTH, bool TWO>
 __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigned char* __restrict__ x_t,
                                                                unsigned char* x_snap,
                                                                const unsigned char* __restrict__ wT, void* y_v,
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
         if constexpr (DT == RRM_I8_I32) return (val_t)((int)e >> 16);
         else return (val_t)__uint_as_float(e.y);
     };
-    constexpr int CHU = fcd_round(DT, NTH, CSC);  // inputs of one compare round = capacity of the list
+    constexpr int CHU = fcd_round(DT, NTH, TWO);  // inputs of one compare round = capacity of the list
     constexpr int UPT = (CHU / PV + NTH - 1) / NTH;  // units of a round per thread
     __shared__ entry_t list[CHU];
     __shared__ __align__(16) val_t red[NTH / 64][4 * PV];  // the wavefronts' sums of the 4 * PV channels
@@ -128,12 +128,10 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
     unsigned int ntrunc = 0, total = 0;
     float tsq = 0.f;
 
-    // the two copies of one 16-byte unit (PV entries from element e0 of the row).  Rows that are not 16-byte multiples: one
-    // load each at whatever alignment the entries have (vector memory takes any), both under way before either is looked at (with
-    // load_unit_at, one after the other, 0.5 us more), the array's last unit from its last sixteen bytes
-    // and shifted into place, with zeros beyond the row's end.  (As five aligned words each,
-    // shifted into place, they took 20 registers a unit and a chain of 1.5 us: one stream, 5 % changed, 9001 -> 4001 bf16 10.3 -> 7.2 us, 8301
-    // -> 1001 int8, in one round since, 9.6 -> 6.3; six streams of 5886 -> 269 bf16 8.2 -> 6.6.)
+    // the two copies of one 16-byte unit (PV entries from element e0 of the row).  Rows that are not 16-byte multiples: one load
+    // each at the entries' own alignment.  (As five aligned words each, shifted into place, they took 20 registers a unit and a
+    // chain of 1.5 us: one stream, 5 % changed, 9001 -> 4001 bf16 10.3 -> 7.2 us, 8301 -> 1001 int8, in one round since, 9.6 -> 6.3;
+    // six streams of 5886 -> 269 bf16 8.2 -> 6.6.)
     auto load_unit = [&](int e0, uint4& a, uint4& s) {
         if constexpr (ROWS16) {
             a = *reinterpret_cast<const uint4*>(x_t + (row + e0) * ESIZE);
@@ -141,33 +139,7 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
             return;
         }
         const long long off = (row + e0) * ESIZE, total_bytes = (long long)g.n * g.c_in * ESIZE;
-        typedef unsigned __int128 u128;
-        u128 ua = 0, us = 0;
-        if (total_bytes >= 16) {
-            const long long at = off + 16 <= total_bytes ? off : total_bytes - 16;
-            __builtin_memcpy(&ua, x_t + at, 16);
-            __builtin_memcpy(&us, x_snap + at, 16);
-            if (at != off) {
-                ua >>= 8 * (int)(off - at);
-                us >>= 8 * (int)(off - at);
-            }
-        } else {
-            typedef typename std::conditional<DT == RRM_I8_I32, unsigned char, unsigned short>::type elem_t;
-#pragma unroll
-            for (int e = 0; e < PV; ++e)
-                if (off + e * ESIZE < total_bytes) {
-                    ua |= (u128)reinterpret_cast<const elem_t*>(x_t + off)[e] << (8 * ESIZE * e);
-                    us |= (u128)reinterpret_cast<const elem_t*>(x_snap + off)[e] << (8 * ESIZE * e);
-                }
-        }
-        const int valid = (g.c_in - e0) * ESIZE;  // bytes of the row from here on
-        if (valid < 16) {
-            const u128 keep = ((u128)1 << (8 * valid)) - 1;
-            ua &= keep;
-            us &= keep;
-        }
-        a = __builtin_bit_cast(uint4, ua);
-        s = __builtin_bit_cast(uint4, us);
+        load_units_at<ESIZE>(x_t, x_snap, off, total_bytes, (g.c_in - e0) * ESIZE, a, s);
     };
     // difference of a unit: mask of the entries to apply, and the unit's new snapshot
     auto diff_unit = [&](const uint4& a, const uint4& s, unsigned int& mask, uint4& n_out) {
@@ -650,11 +622,18 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
     // 6.7 -> 7.25).
     const auto rounds = [&](int threads) { return (g.c_in + fcd_round(dtype, threads, false) - 1) / fcd_round(dtype, threads, false); };
     const bool wide = dtype == RRM_BF16_F32 && !g.csc_ptr && (long long)ranges * g.n <= NUM_CU && rounds(704) < rounds(512);
+    const int nks = fc_list_splits(dtype, g);
+    const bool few = (long long)ranges * g.n * nks <= NUM_CU;  // a compute unit for every workgroup
     auto form = [&]<bool CSC>() {
-        if (dtype == RRM_I8_I32) return g.vec_ok ? fc_delta_kernel<RRM_I8_I32, CSC, true, 512> : fc_delta_kernel<RRM_I8_I32, CSC, false, 512>;
+        if (dtype == RRM_I8_I32) {
+            if (g.vec_ok) return fc_delta_kernel<RRM_I8_I32, CSC, true, 512, !CSC>;
+            // (a form of two ragged units a thread has no registers for a second workgroup on its compute unit: 22 streams of 599 -> 990,
+            // 352 workgroups, 10.8 us and 8.6 with one)
+            return !CSC && few ? fc_delta_kernel<RRM_I8_I32, CSC, false, 512, !CSC> : fc_delta_kernel<RRM_I8_I32, CSC, false, 512, false>;
+        }
         if constexpr (!CSC)
-            if (wide) return g.vec_ok ? fc_delta_kernel<RRM_BF16_F32, CSC, true, 704> : fc_delta_kernel<RRM_BF16_F32, CSC, false, 704>;
-        return g.vec_ok ? fc_delta_kernel<RRM_BF16_F32, CSC, true, 512> : fc_delta_kernel<RRM_BF16_F32, CSC, false, 512>;
+            if (wide) return g.vec_ok ? fc_delta_kernel<RRM_BF16_F32, CSC, true, 704, true> : fc_delta_kernel<RRM_BF16_F32, CSC, false, 704, true>;
+        return g.vec_ok ? fc_delta_kernel<RRM_BF16_F32, CSC, true, 512, false> : fc_delta_kernel<RRM_BF16_F32, CSC, false, 512, false>;
     };
     dim3 block(wide ? 704 : 512);
     if (g.csc_ptr) {
@@ -664,10 +643,10 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
         static std::once_flag once;
         static hipError_t attr = hipSuccess;
         std::call_once(once, [] {
-            for (const void* f : {reinterpret_cast<const void*>(&fc_delta_kernel<RRM_I8_I32, true, true, 512>),
-                                  reinterpret_cast<const void*>(&fc_delta_kernel<RRM_I8_I32, true, false, 512>),
-                                  reinterpret_cast<const void*>(&fc_delta_kernel<RRM_BF16_F32, true, true, 512>),
-                                  reinterpret_cast<const void*>(&fc_delta_kernel<RRM_BF16_F32, true, false, 512>)})
+            for (const void* f : {reinterpret_cast<const void*>(&fc_delta_kernel<RRM_I8_I32, true, true, 512, false>),
+                                  reinterpret_cast<const void*>(&fc_delta_kernel<RRM_I8_I32, true, false, 512, false>),
+                                  reinterpret_cast<const void*>(&fc_delta_kernel<RRM_BF16_F32, true, true, 512, false>),
+                                  reinterpret_cast<const void*>(&fc_delta_kernel<RRM_BF16_F32, true, false, 512, false>)})
                 if (attr == hipSuccess) attr = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, FC_CSC_MAX_LDS);
         });
         if (attr != hipSuccess) return attr;
@@ -678,9 +657,8 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
                            (const unsigned char*)wT, y, y_out, arrive, g, stats);
         return hipGetLastError();
     }
-    const int nks = fc_list_splits(dtype, g);
     FcGeom gb = g;
-    gb.books = (long long)ranges * g.n * nks <= NUM_CU;
+    gb.books = few;
     if (gb.books) block.x += FCD_BOOKS;
     dim3 grid((unsigned int)ranges, (unsigned int)g.n, (unsigned int)nks);
     const auto kernel = form.template operator()<false>();

@@ -41,25 +41,7 @@ struct FcCommit {
     unsigned long long n_cin;
     DevStats* stats;
 };
-template <int DT>
-__device__ __forceinline__ void fc_commit(unsigned int block, const FcCommit& c) {
-    const long long v = (long long)block * 256 + threadIdx.x;
-    unsigned int nchanged = 0;
-    if (v < c.nvec) {
-        const uint4 a = c.x_t[v], s = c.x_snap[v];
-        if ((a.x ^ s.x) | (a.y ^ s.y) | (a.z ^ s.z) | (a.w ^ s.w)) {
-            const unsigned int aw[4] = {a.x, a.y, a.z, a.w}, sw[4] = {s.x, s.y, s.z, s.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const unsigned int z = aw[i] ^ sw[i];
-                if (DT == RRM_I8_I32)
-                    nchanged += __popc((((z & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | z) & 0x80808080u);
-                else
-                    nchanged += ((z & 0xFFFFu) != 0u) + (z > 0xFFFFu);
-            }
-            c.x_snap[v] = a;
-        }
-    }
+__device__ __forceinline__ void fc_count(unsigned int block, unsigned int nchanged, const FcCommit& c) {
     // counts: wavefront, then workgroup, then one set of atomics
     __shared__ unsigned int s_n[4];
     if (__any(nchanged != 0u)) nchanged = (unsigned int)__builtin_amdgcn_readlane((int)wave_scan(nchanged), 63);
@@ -79,6 +61,68 @@ __device__ __forceinline__ void fc_commit(unsigned int block, const FcCommit& c)
         }
     }
 }
+template <int DT>
+__device__ __forceinline__ unsigned int fc_changes(const uint4& a, const uint4& s) {  // entries of a unit that differ
+    unsigned int nchanged = 0;
+    const unsigned int zw[4] = {a.x ^ s.x, a.y ^ s.y, a.z ^ s.z, a.w ^ s.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const unsigned int z = zw[i];
+        if (DT == RRM_I8_I32)
+            nchanged += __popc((((z & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | z) & 0x80808080u);
+        else
+            nchanged += ((z & 0xFFFFu) != 0u) + (z > 0xFFFFu);
+    }
+    return nchanged;
+}
+template <int DT>
+__device__ __forceinline__ void fc_commit(unsigned int block, const FcCommit& c) {
+    const long long v = (long long)block * 256 + threadIdx.x;
+    unsigned int nchanged = 0;
+    if (v < c.nvec) {
+        const uint4 a = c.x_t[v], s = c.x_snap[v];
+        if ((a.x ^ s.x) | (a.y ^ s.y) | (a.z ^ s.z) | (a.w ^ s.w)) {
+            nchanged = fc_changes<DT>(a, s);
+            c.x_snap[v] = a;
+        }
+    }
+    fc_count(block, nchanged, c);
+}
+// Vectors whose entries do not fill whole 64-byte steps, ahead of the product: their copy with every row padded by zeros to whole
+// steps, a thread per 16 bytes of it, and (COMMIT) x_snap <- x_t with the change counts on the way.  It costs a launch, 2.5 us;
+// without it such layers walk (steps) and read W once a stream (dense): 8999 -> 4000 bf16, 64 streams, a step of 2 % 144 us and 40.5, dense
+// 200 and 39.5 (see fc_step_batched and fc_dense_batched).
+template <int DT, bool COMMIT>
+__global__ __launch_bounds__(256) void fc_pad_kernel(const unsigned char* __restrict__ x, uint4* __restrict__ padded, int row_bytes,
+                                                     unsigned int per_row, unsigned int magic_per_row, unsigned int n_units,
+                                                     long long total, FcCommit c) {
+    constexpr int ESIZE = DT == RRM_I8_I32 ? 1 : 2;
+    const unsigned int v = blockIdx.x * 256u + threadIdx.x;
+    unsigned int nchanged = 0;
+    if (v < n_units) {
+        const unsigned int row = udiv_magic(v, per_row, magic_per_row), u = v - row * per_row;
+        const int valid = row_bytes - 16 * (int)u;
+        uint4 a = make_uint4(0, 0, 0, 0), s = a;
+        if (valid > 0) {
+            const long long off = (long long)row * row_bytes + 16 * u;
+            if (COMMIT) {
+                unsigned char* const snap = reinterpret_cast<unsigned char*>(c.x_snap);
+                load_units_at<ESIZE>(x, snap, off, total, valid, a, s);
+                if ((a.x ^ s.x) | (a.y ^ s.y) | (a.z ^ s.z) | (a.w ^ s.w)) {
+                    nchanged = fc_changes<DT>(a, s);
+                    if (valid >= 16)
+                        __builtin_memcpy(snap + off, &a, 16);
+                    else
+                        store_piece(snap + off, __builtin_bit_cast(unsigned __int128, a), (unsigned int)valid);
+                }
+            } else {
+                a = load_unit_at<ESIZE>(x, off, total, valid);
+            }
+        }
+        padded[v] = a;
+    }
+    if (COMMIT) fc_count(blockIdx.x, nchanged, c);
+}
 
 // Partial products P[split] = W[:, k range of the split] B[:, k range]^T.  w: [c_out][c_in] row-major; b: [n][c_in]
 // (the streams' vectors, or their differences); part: [splits][n][c_out] 4-byte sums.
@@ -90,7 +134,7 @@ __device__ __forceinline__ void fc_commit(unsigned int block, const FcCommit& c)
 // double-buffered, one barrier per chunk.
 // LDS layout: (step of the chunk, stream) -> 80 bytes (64 used): the 16 streams that a group of 16 lanes reads for
 // one k-group start 20 banks apart and fall on 16 different 4-bank groups.
-template <int DT, int TMAX, int CK>
+template <int DT, int TMAX, int CK, bool CHAINS>
 __global__ __launch_bounds__(256) void fc_bt_kernel(const unsigned char* __restrict__ w, const unsigned char* __restrict__ b,
                                                     void* __restrict__ part_v, FcGeom g, int cps) {
     constexpr int ESIZE = DT == RRM_I8_I32 ? 1 : 2;
@@ -131,7 +175,6 @@ __global__ __launch_bounds__(256) void fc_bt_kernel(const unsigned char* __restr
     // the loads of a chunk to come (relative error of 9216 -> 4096, 4 .. 15 streams, whose chains are 72 instructions long without:
     // 2.3e-7 and 0.6e-7, the column walk's 0.9e-7; us dense, 8 streams, 18.3 and 18.9).  More tiles' sums would cost more than they are
     // worth (32 streams of 9216 -> 256, 12.9 and 13.9, 64 of 9216 -> 4096 22.2 and 27.6): there the splits bound the chains, see bt_splits.
-    constexpr bool CHAINS = DT == RRM_BF16_F32 && TMAX <= BT_CHAIN_TILES;
     acc_t acc[TMAX];
     v4d total[CHAINS ? TMAX : 1];
 #pragma unroll
@@ -261,9 +304,9 @@ __global__ __launch_bounds__(256) void fc_bt_kernel(const unsigned char* __restr
 // 24.9 -> 22.5 us; int8, where that launch also wrote the differences and the sums went onto y, 18.7 -> 16.0.)
 // WIDE (bf16): the splits are summed in 64 bits, where the product kernel sums its chains so or there are many splits (64 streams of
 // 9216 -> 4096, whose four splits gain nothing by it, would take 0.2 us longer).
-template <int DT, bool COMMIT, bool WIDE>
+template <int DT, bool COMMIT, bool WIDE, bool RAGGED>
 __global__ __launch_bounds__(256) void fc_bt_reduce_kernel(const void* __restrict__ part_v, const void* __restrict__ bias_v,
-                                                           void* y_v, void* y_out, long long nvec, int c_out4, int splits,
+                                                           void* y_v, void* y_out, long long nvec, int c_out4, int c_out, int splits,
                                                            unsigned int blocks, FcCommit cm) {
     if (COMMIT && blockIdx.x >= blocks) {
         fc_commit<DT>(blockIdx.x - blocks, cm);
@@ -288,6 +331,21 @@ __global__ __launch_bounds__(256) void fc_bt_reduce_kernel(const void* __restric
             if (s0 + k >= splits) break;
             add(o[k]);
         }
+    }
+    if constexpr (RAGGED) {  // c_out is not whole 16-row blocks: the sums' rows are c_out4 vectors, y's c_out entries
+        typedef typename std::conditional<DT == RRM_I8_I32, int, float>::type val_t;
+        const long long row = v / c_out4;
+        const int o0 = 4 * (int)(v - row * c_out4);
+        const val_t* const bias = static_cast<const val_t*>(bias_v);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (o0 + i >= c_out) break;
+            if (bias) sum[i] += bias[o0 + i];
+            const val_t r = (val_t)sum[i];
+            static_cast<val_t*>(y_v)[row * c_out + o0 + i] = r;
+            if (y_out) static_cast<val_t*>(y_out)[row * c_out + o0 + i] = r;
+        }
+        return;
     }
     if (bias_v) add(static_cast<const acc_t*>(bias_v)[v % c_out4]);
     const acc_t out = __builtin_convertvector(sum, acc_t);
@@ -329,9 +387,22 @@ int bt_splits(int dtype, const FcGeom& g, int n) {
 }
 
 template <int DT>
-void launch_batched(const void* w_rm, const void* b0, void* part, const void* bias, void* y, void* y_out, const FcGeom& g,
+void launch_batched(const void* w_rm, const void* x_t, void* padded, void* part, const void* bias, void* y, void* y_out, const FcGeom& real,
                     const FcCommit* commit, hipStream_t s) {
-    const int esize = DT == RRM_I8_I32 ? 1 : 2;
+    constexpr int esize = DT == RRM_I8_I32 ? 1 : 2;
+    constexpr bool BF = DT == RRM_BF16_F32;
+    const FcGeom g = fc_product_geom(DT, real);
+    const bool ragged = g.c_out != real.c_out;
+    const void* b0 = x_t;
+    if (g.c_in != real.c_in) {
+        const unsigned int per_row = (unsigned int)(g.c_in * esize / 16), units = (unsigned int)g.n * per_row;
+        const auto pad = commit ? fc_pad_kernel<DT, true> : fc_pad_kernel<DT, false>;
+        hipLaunchKernelGGL(pad, dim3((units + 255u) / 256u), dim3(256), 0, s, static_cast<const unsigned char*>(x_t), static_cast<uint4*>(padded),
+                           real.c_in * esize, per_row, magic_of((int)per_row), units, (long long)real.n * real.c_in * esize,
+                           commit ? *commit : FcCommit{});
+        b0 = padded;
+        commit = nullptr;
+    }
     const int nsteps = g.c_in * esize / 64;
     const int per = bt_group(g.n);
     const unsigned char* w = static_cast<const unsigned char*>(w_rm);
@@ -346,42 +417,77 @@ void launch_batched(const void* w_rm, const void* b0, void* part, const void* bi
         const int splits = (chunks + cps - 1) / cps;  // (no empty split)
         dim3 grid((unsigned int)((g.c_out + 63) / 64), (unsigned int)splits);
         const unsigned char* p0 = static_cast<const unsigned char*>(b0) + (size_t)s0 * g.c_in * esize;
-        unsigned char* yg = static_cast<unsigned char*>(y) + (size_t)s0 * g.c_out * 4;
-        unsigned char* og = y_out ? static_cast<unsigned char*>(y_out) + (size_t)s0 * g.c_out * 4 : nullptr;
+        unsigned char* yg = static_cast<unsigned char*>(y) + (size_t)s0 * real.c_out * 4;
+        unsigned char* og = y_out ? static_cast<unsigned char*>(y_out) + (size_t)s0 * real.c_out * 4 : nullptr;
+        // (padded layers took a walk, or sums of a few rows each, whose error is that of short chains)
+        const bool chains = BF && (ntiles <= BT_CHAIN_TILES || ragged || g.c_in != real.c_in);
 #define RRM_BT(T, C)                                                                                                  \
     if (ntiles <= T) {                                                                                                \
-        hipLaunchKernelGGL((fc_bt_kernel<DT, T, C>), grid, dim3(256), 0, s, w, p0, part, gg, cps);                    \
+        const auto product = chains ? fc_bt_kernel<DT, T, C, BF> : fc_bt_kernel<DT, T, C, BF && T <= BT_CHAIN_TILES>; \
+        hipLaunchKernelGGL(product, grid, dim3(256), 0, s, w, p0, part, gg, cps);                                     \
     } else
         RRM_BT(1, 4) RRM_BT(2, 4) RRM_BT(3, 4) RRM_BT(4, 4) RRM_BT(6, 2) RRM_BT(8, 2) {}
 #undef RRM_BT
         const long long nvec = (long long)gg.n * g.c_out / 4;
         const unsigned int blocks = (unsigned int)((nvec + 255) / 256);
-        const bool last = commit && s0 + per >= g.n;
-        constexpr bool BF = DT == RRM_BF16_F32;
-        const bool wide = BF && (ntiles <= BT_CHAIN_TILES || splits > BT_MAX_SPLITS);
-        const auto reduce = last ? (wide ? fc_bt_reduce_kernel<DT, true, BF> : fc_bt_reduce_kernel<DT, true, false>)
-                                 : (wide ? fc_bt_reduce_kernel<DT, false, BF> : fc_bt_reduce_kernel<DT, false, false>);
+        const bool last = commit && s0 + per >= g.n, wide = BF && (chains || splits > BT_MAX_SPLITS);
+        auto form = [&]<bool RAGGED>() {
+            return last ? (wide ? fc_bt_reduce_kernel<DT, true, BF, RAGGED> : fc_bt_reduce_kernel<DT, true, false, RAGGED>)
+                        : (wide ? fc_bt_reduce_kernel<DT, false, BF, RAGGED> : fc_bt_reduce_kernel<DT, false, false, RAGGED>);
+        };
+        const auto reduce = ragged ? form.template operator()<true>() : form.template operator()<false>();
         const FcCommit cm = last ? *commit : FcCommit{};
         hipLaunchKernelGGL(reduce, dim3(blocks + (last ? (unsigned int)((cm.nvec + 255) / 256) : 0u)), dim3(256), 0, s, part, bias, yg, og,
-                           nvec, g.c_out / 4, splits, blocks, cm);
+                           nvec, g.c_out / 4, real.c_out, splits, blocks, cm);
     }
 }
 
 }  // namespace
 
+FcGeom fc_product_geom(int dtype, const FcGeom& g) {
+    const int step = dtype == RRM_I8_I32 ? 64 : 32;
+    FcGeom p = g;
+    p.c_in = (g.c_in + step - 1) / step * step;
+    p.c_out = (g.c_out + 15) / 16 * 16;
+    return p;
+}
+
 // bytes of the partial sums (the groups of streams of one call use them one after the other; the last group can be smaller and
 // have more splits)
-size_t fc_batched_part_bytes(int dtype, const FcGeom& g) {
+size_t fc_batched_part_bytes(int dtype, const FcGeom& real) {
+    const FcGeom g = fc_product_geom(dtype, real);
     const int per = bt_group(g.n), last = g.n - (g.n - 1) / per * per;
     const auto sums = [&](int n) { return (size_t)bt_splits(dtype, g, n) * (size_t)n; };
     return std::max(sums(per), sums(last)) * (size_t)g.c_out * 4;
 }
 
+// padded for the product: rows off the 64-byte steps (its vectors, in a launch of their own) or outputs off the blocks of 16
+static bool fc_rows_padded(int dtype, const FcGeom& g) { return fc_product_geom(dtype, g).c_in != g.c_in; }
+static bool fc_padded(int dtype, const FcGeom& g) { return fc_rows_padded(dtype, g) || fc_product_geom(dtype, g).c_out != g.c_out; }
+
 bool fc_batched_ok(int dtype, const FcGeom& g) {
     const int esize = dtype == RRM_I8_I32 ? 1 : 2;
-    // (whole 16-row blocks and 64-byte steps; byte offsets into W in 32 bits)
-    return g.n >= FC_BATCH_MIN_STREAMS && g.n <= FC_BATCH_MAX_STREAMS && g.c_out % 16 == 0 && (g.c_in * esize) % 64 == 0 &&
-           (long long)g.c_in * esize * g.c_out <= 0xFFFFFFFFll;
+    // (byte offsets into W and the vectors in 32 bits)
+    const FcGeom p = fc_product_geom(dtype, g);
+    if (g.n < FC_BATCH_MIN_STREAMS || g.n > FC_BATCH_MAX_STREAMS || (long long)p.c_in * esize * std::max(p.c_out, p.n) > 0xFFFFFFFFll) return false;
+    return !fc_padded(dtype, g) || fc_dense_batched(dtype, g) || fc_step_batched(dtype, g);  // (no copy of W for what never runs so)
+}
+
+// Does the dense layer run as one product?  Otherwise it reads W once a stream, from the caches.  Padded layers: us a call without
+// and with it (with the launch that pads the vectors, but for the last row of a type):
+//   int8  8999 -> 4000   4 streams  17.5 / 13.7   64 streams 163 / 21.6      8999 -> 1001   4  10.0 / 11.0    8  12.1 / 11.4   64  48.3 / 14.1
+//   int8  4100 -> 1001   8           9.6 / 10.4   16          11.8 / 10.0    4099 ->  270  16  10.9 / 10.1   32  15.5 / 10.7   64  24.2 / 11.7
+//   int8  1001 ->  500  64          10.8 / 10.9  128          15.4 / 11.3     523 ->  270 128  11.1 / 10.5
+//   int8  4096 -> 1001   4           8.6 /  7.6   16          11.8 /  7.6
+//   bf16  8999 -> 4000   4          21.6 / 23.2    8          34.5 / 23.4    8999 -> 1001   8  13.2 / 15.0   16  19.3 / 15.0   64  58.4 / 21.0
+//   bf16  4100 -> 1001  16          12.0 / 11.8   32          17.6 / 12.9    4099 ->  270  32  11.6 / 12.4   64  17.0 / 14.8
+//   bf16  1001 ->  500 128          13.0 / 13.8                              2050 -> 1001  32  12.1 / 11.4   64  18.9 / 13.6
+//   bf16  4096 -> 1001   4           7.7 /  9.2   16          12.1 /  9.2
+bool fc_dense_batched(int dtype, const FcGeom& g) {
+    if (!fc_padded(dtype, g)) return true;
+    const long long w = (long long)g.c_in * g.c_out * (dtype == RRM_I8_I32 ? 1 : 2), rows = fc_rows_padded(dtype, g) ? 1 : 0;
+    if (dtype == RRM_I8_I32) return g.n * w >= (rows ? 56ll : 16ll) * 1000000 || (g.n >= 16 && (long long)g.n * g.c_in >= 100000);
+    return (2ll * g.n - 5) * w >= (rows ? 256ll : 192ll) << 20;
 }
 
 // Does a step run as one product?  Its cost is a pass over W, the streams' own column walks cost by the number of their workgroups
@@ -405,27 +511,45 @@ bool fc_batched_ok(int dtype, const FcGeom& g) {
 //   2048 -> 1024  31           62        8.7 /  9.1 /  9.4 / 11.2 / 12.2    9.8      1024 ->  512  63    32    7.7 /  7.7 /  8.0 /  8.2 /  8.9   10.0
 // (more than 64 streams, whose product is dearer: 9216 -> 256, 127, 286 MiB, 11.6 / 11.8 / 14.8 / 19.6 / 26.8 and 14.4).
 // bf16 layers of 16 and more streams always.
+// Padded layers, whose product is a launch dearer and whose bf16 sums are all of short chains, as exact as the walk's: us a step
+// walking, 2 / 25 % changed, and as a product:
+//   int8  8999 -> 4000   8 streams   504 workgroups   13.3 / 28.6   14.4     64 streams  4032   79.8 / 178   22.5
+//   int8  4099 -> 4000   8           504              10.7 / 16.4   11.3     16          1008   19.5 / 27.9  11.6
+//   int8  4100 -> 1001  32           512               9.6 / 12.4   11.6     48           768   13.8 / 16.6  12.0
+//   int8  1001 ->  500  64           512               7.8 /  8.7   11.6     96           768   11.8 / 12.3  11.5
+//   int8  4099 ->  270 128           640              10.7 / 13.8   14.2    523 -> 270  128  640  11.2 / 11.3  11.2
+//   bf16  8999 -> 4000   4           500              15.3 / 27.8   23.7      8          1000   25.2 / 48.1  24.0
+//   bf16  4100 -> 1001  16           512              11.4 / 13.4   12.3     32          1024   18.6 / 22.7  13.4
+//   bf16  2050 -> 1001  16           512              10.1 / 10.4   11.0     64          2048   24.2 / 28.0  14.2
+//   bf16  1001 ->  500  64          1024              13.2 / 13.3   13.2    128          2048   20.8 / 21.3  14.3
+//   bf16  4099 ->  270  64           576              11.5 / 14.4   15.4    128          1152   17.2 / 21.3  20.2
+//   rows of whole 64 bytes: int8 4096 -> 1001, 16, 256, 7.0 / 7.5 and 7.7, 64, 1024, 13.8 / 15.6 and 9.8; bf16 16, 512, 10.3 / 11.0 and 9.4
 // (Rounding, 9216 -> 4096: a recomputed sum 0.6e-7 up to 16 streams and 2.3e-7 beyond, whatever ran before; a walked one 0.9e-7
 // after the first step, 1.2e-7 after the sixth.)
 bool fc_step_batched(int dtype, const FcGeom& g) {
     const int esize = dtype == RRM_I8_I32 ? 1 : 2;
-    if (dtype == RRM_BF16_F32 && g.n >= 16) return true;
     const long long workgroups = (long long)g.n * ((g.c_out_p * esize + 63) / 64);
+    if (fc_padded(dtype, g)) {
+        const bool rows = fc_rows_padded(dtype, g);
+        if (dtype == RRM_I8_I32) return workgroups >= (rows ? 704 : 512);
+        return workgroups >= (g.n > 64 ? 1280 : !rows ? 512 : g.c_in * esize > 16384 ? 1000 : 896);
+    }
+    if (dtype == RRM_BF16_F32 && g.n >= 16) return true;
     if (workgroups >= (g.c_in * esize > 16384 ? 640 : 512)) return true;
     return dtype == RRM_I8_I32 && g.n <= 64 && (long long)g.c_in * g.c_out <= 40ll << 20 && workgroups * 64 * g.c_in >= 200ll << 20;
 }
 
-hipError_t launch_fc_batched_dense(int dtype, const void* w_rm, const void* x, void* part, const void* bias, void* y,
+hipError_t launch_fc_batched_dense(int dtype, const void* w_rm, const void* x, void* padded, void* part, const void* bias, void* y,
                                    const FcGeom& g, hipStream_t s) {
     if (!fc_batched_ok(dtype, g)) return hipErrorInvalidValue;
     if (dtype == RRM_I8_I32)
-        launch_batched<RRM_I8_I32>(w_rm, x, part, bias, y, nullptr, g, nullptr, s);
+        launch_batched<RRM_I8_I32>(w_rm, x, padded, part, bias, y, nullptr, g, nullptr, s);
     else
-        launch_batched<RRM_BF16_F32>(w_rm, x, part, bias, y, nullptr, g, nullptr, s);
+        launch_batched<RRM_BF16_F32>(w_rm, x, padded, part, bias, y, nullptr, g, nullptr, s);
     return hipGetLastError();
 }
 
-hipError_t launch_fc_batched_delta(int dtype, const void* w_rm, const void* x_t, void* x_snap, void* part,
+hipError_t launch_fc_batched_delta(int dtype, const void* w_rm, const void* x_t, void* x_snap, void* padded, void* part,
                                    const void* bias, void* y, void* y_out, const FcGeom& g, DevStats* stats, hipStream_t s) {
     if (!fc_batched_ok(dtype, g) || g.eps != 0.0f) return hipErrorInvalidValue;
     const int esize = dtype == RRM_I8_I32 ? 1 : 2;
@@ -433,9 +557,9 @@ hipError_t launch_fc_batched_delta(int dtype, const void* w_rm, const void* x_t,
     const unsigned long long n_cin = (unsigned long long)g.n * (unsigned long long)g.c_in;
     const FcCommit commit{static_cast<const uint4*>(x_t), static_cast<uint4*>(x_snap), nvec, n_cin, stats};
     if (dtype == RRM_I8_I32)
-        launch_batched<RRM_I8_I32>(w_rm, x_t, part, bias, y, y_out, g, &commit, s);
+        launch_batched<RRM_I8_I32>(w_rm, x_t, padded, part, bias, y, y_out, g, &commit, s);
     else
-        launch_batched<RRM_BF16_F32>(w_rm, x_t, part, bias, y, y_out, g, &commit, s);
+        launch_batched<RRM_BF16_F32>(w_rm, x_t, padded, part, bias, y, y_out, g, &commit, s);
     return hipGetLastError();
 }
 

@@ -702,7 +702,16 @@ rrm_status setup_fc(rrm_layer* L, const std::vector<unsigned char>& w) {
     }
     // many streams: the layer runs as one product on the matrix cores, from W in its own layout (steps recompute it from x_t)
     if (fc_batched_ok(L->dtype, g)) {
-        if ((st = upload(w.data(), (size_t)s.c_in * s.c_out * es, &L->w_rm)) != RRM_OK) return st;
+        const FcGeom p = fc_product_geom(L->dtype, g);
+        if (p.c_in == g.c_in && p.c_out == g.c_out) {
+            if ((st = upload(w.data(), (size_t)s.c_in * s.c_out * es, &L->w_rm)) != RRM_OK) return st;
+        } else {  // (rows of whole 64-byte steps, blocks of whole 16 rows: zeros)
+            std::fill(t.begin(), t.end(), 0);
+            t.resize((size_t)p.c_in * p.c_out * es, 0);
+            for (int o = 0; o < s.c_out; ++o) std::memcpy(t.data() + (size_t)o * p.c_in * es, w.data() + (size_t)o * s.c_in * es, (size_t)s.c_in * es);
+            if ((st = upload(t.data(), (size_t)p.c_in * p.c_out * es, &L->w_rm)) != RRM_OK) return st;
+            if (p.c_in != g.c_in && (st = dalloc((size_t)s.n * p.c_in * es, &L->xpad)) != RRM_OK) return st;
+        }
         if ((st = dalloc(fc_batched_part_bytes(L->dtype, g), &L->fc_bpart)) != RRM_OK) return st;
     }
     // dense path: enough workgroups to keep memory busy (about 256 in total, at most 64 row splits per stream)
@@ -758,8 +767,8 @@ rrm_status check_ptr(const void* p, const char* what) {
 // dense layer of Eq. 3 from x into y
 rrm_status enqueue_dense(rrm_layer* L, const void* x, void* y, hipStream_t st) {
     if (L->shape.kind == RRM_FC) {
-        if (L->w_rm && L->opt_fc_batched)
-            RRM_HIP(launch_fc_batched_dense(L->dtype, L->w_rm, x, L->fc_bpart, L->bias, y, L->fg, st));
+        if (L->w_rm && L->opt_fc_batched && fc_dense_batched(L->dtype, L->fg))
+            RRM_HIP(launch_fc_batched_dense(L->dtype, L->w_rm, x, L->xpad, L->fc_bpart, L->bias, y, L->fg, st));
         else
             RRM_HIP(launch_fc_dense(L->dtype, fc_splits(L), L->wpack, x, L->fc_part, L->bias, y, L->fg, st));
     } else if (L->dtype == RRM_BIN_I32) {
@@ -952,7 +961,7 @@ rrm_status rrm_step(rrm_layer* L, const void* x_t, void* y_out, void* hip_stream
             // many streams: one product over W, then the sums, the commit and the counts (two launches; the events bracket both)
             if ((st = prof_mark(L, 1, s)) != RRM_OK) return st;
             out_written = y_out && !overlap;
-            RRM_HIP(launch_fc_batched_delta(L->dtype, L->w_rm, x_t, L->x_snap, L->fc_bpart, L->bias, L->y_snap, out_written ? y_out : nullptr,
+            RRM_HIP(launch_fc_batched_delta(L->dtype, L->w_rm, x_t, L->x_snap, L->xpad, L->fc_bpart, L->bias, L->y_snap, out_written ? y_out : nullptr,
                                             L->fg, L->stats, s));
             if ((st = prof_mark(L, 2, s)) != RRM_OK) return st;
         } else {

@@ -185,7 +185,8 @@ struct FcGeom {
 };
 // From this many streams on an FC layer can run as one product on the matrix cores, and the dense layer does (us a stream by
 // itself and so, 4 streams: int8 9216 -> 4096 19.0 and 12.1, bf16 23.9 and 18.1, 4096 -> 4096 12.2 and 9.6, 13.9 and 10.0, smaller
-// layers level; 2 streams: 12.8 and 12.1, 16.2 and 17.9, 9.4 and 9.6, 10.1 and 9.9).  Steps: see fc_step_batched
+// layers level; 2 streams: 12.8 and 12.1, 16.2 and 17.9, 9.4 and 9.6, 10.1 and 9.9).  Steps: see fc_step_batched; layers whose
+// vectors or weights are padded for it: fc_dense_batched
 constexpr int FC_BATCH_MIN_STREAMS = 4;
 constexpr int FC_BATCH_MAX_STREAMS = 4096;  // (launched in groups of at most 128 streams)
 constexpr int FC_CSC_MAX_LDS = 96 * 1024;   // the pruned-weight kernel's update accumulators: c_out <= 24576
@@ -221,6 +222,61 @@ __device__ __forceinline__ uint4 load_unit_at(const unsigned char* p, long long 
     }
     if (valid < 16) u &= ((u128)1 << (8 * valid)) - 1;
     return __builtin_bit_cast(uint4, u);
+}
+
+// The same of two arrays, both loads under way before either is looked at (one after the other they are two round trips)
+template <int ESIZE>
+__device__ __forceinline__ void load_units_at(const unsigned char* p, const unsigned char* q, long long off, long long total, int valid,
+                                              uint4& a, uint4& b) {
+    typedef unsigned __int128 u128;
+    typedef std::conditional_t<ESIZE == 1, unsigned char, unsigned short> elem_t;
+    u128 ua = 0, ub = 0;
+    if (total >= 16) {
+        const long long at = off + 16 <= total ? off : total - 16;
+        __builtin_memcpy(&ua, p + at, 16);
+        __builtin_memcpy(&ub, q + at, 16);
+        if (at != off) {
+            ua >>= 8 * (int)(off - at);
+            ub >>= 8 * (int)(off - at);
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 16 / ESIZE; ++e)
+            if (off + e * ESIZE < total) {
+                ua |= (u128)reinterpret_cast<const elem_t*>(p + off)[e] << (8 * ESIZE * e);
+                ub |= (u128)reinterpret_cast<const elem_t*>(q + off)[e] << (8 * ESIZE * e);
+            }
+    }
+    if (valid < 16) {
+        const u128 keep = ((u128)1 << (8 * valid)) - 1;
+        ua &= keep;
+        ub &= keep;
+    }
+    a = __builtin_bit_cast(uint4, ua);
+    b = __builtin_bit_cast(uint4, ub);
+}
+
+// the lowest `bytes` (below 16) bytes of u, at any alignment
+__device__ __forceinline__ void store_piece(unsigned char* p, unsigned __int128 u, unsigned int bytes) {
+    if (bytes & 8u) {
+        const unsigned long long v = (unsigned long long)u;
+        __builtin_memcpy(p, &v, 8);
+        p += 8;
+        u >>= 64;
+    }
+    if (bytes & 4u) {
+        const unsigned int v = (unsigned int)u;
+        __builtin_memcpy(p, &v, 4);
+        p += 4;
+        u >>= 32;
+    }
+    if (bytes & 2u) {
+        const unsigned short v = (unsigned short)u;
+        __builtin_memcpy(p, &v, 2);
+        p += 2;
+        u >>= 16;
+    }
+    if (bytes & 1u) *p = (unsigned char)u;
 }
 
 // Reads a word of each 64-byte line of a kernel's first BYTES of arguments (at most 512), all in flight together.  The lines come from
@@ -293,10 +349,12 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
 // values), then y = bias + the sum of the splits in a fixed order
 bool fc_batched_ok(int dtype, const FcGeom& g);
 bool fc_step_batched(int dtype, const FcGeom& g);
+bool fc_dense_batched(int dtype, const FcGeom& g);
+FcGeom fc_product_geom(int dtype, const FcGeom& g);  // c_in and c_out as the product has them: whole 64-byte steps and 16-row blocks
 size_t fc_batched_part_bytes(int dtype, const FcGeom& g);  // of `part`: the partial sums
-hipError_t launch_fc_batched_dense(int dtype, const void* w_rm, const void* x, void* part, const void* bias, void* y,
+hipError_t launch_fc_batched_dense(int dtype, const void* w_rm, const void* x, void* padded, void* part, const void* bias, void* y,
                                    const FcGeom& g, hipStream_t s);
-hipError_t launch_fc_batched_delta(int dtype, const void* w_rm, const void* x_t, void* x_snap, void* part,
+hipError_t launch_fc_batched_delta(int dtype, const void* w_rm, const void* x_t, void* x_snap, void* padded, void* part,
                                    const void* bias, void* y, void* y_out, const FcGeom& g, DevStats* stats, hipStream_t s);
 int fc_dense_slices(int dtype, const FcGeom& g);
 hipError_t launch_fc_dense(int dtype, int splits, const void* wT, const void* x, void* part, const void* bias, void* y,

@@ -102,29 +102,6 @@ __device__ __forceinline__ unsigned int scatter_index(const ScanGeom& g, unsigne
     return ((r * g.wp + ix) * g.groups + grp) * g.cp + (c - grp * g.cg);
 }
 
-// the lowest `bytes` (below 16) bytes of u, at any alignment
-__device__ __forceinline__ void store_piece(unsigned char* p, unsigned __int128 u, unsigned int bytes) {
-    if (bytes & 8u) {
-        const unsigned long long v = (unsigned long long)u;
-        __builtin_memcpy(p, &v, 8);
-        p += 8;
-        u >>= 64;
-    }
-    if (bytes & 4u) {
-        const unsigned int v = (unsigned int)u;
-        __builtin_memcpy(p, &v, 4);
-        p += 4;
-        u >>= 32;
-    }
-    if (bytes & 2u) {
-        const unsigned short v = (unsigned short)u;
-        __builtin_memcpy(p, &v, 2);
-        p += 2;
-        u >>= 16;
-    }
-    if (bytes & 1u) *p = (unsigned char)u;
-}
-
 // Write the 16 bytes of unit v (already computed difference words) into the padded / folded layout; where runs are shorter than
 // a unit element by element, the (row, column, channel) of the first one divided out once and then stepped.
 template <int DT>

@@ -188,7 +188,7 @@ def _replay_case(seq, **opts):
 
 
 @pytest.mark.parametrize("case", ["scatter_bf16", "scatter_i8", "binary_one_launch", "binary_two_launches", "fc_walk",
-                                  "fc_pruned", "fc_batched_i8", "fc_batched_bf16"])
+                                  "fc_pruned", "fc_batched_i8", "fc_batched_bf16", "fc_padded_i8", "fc_padded_bf16"])
 def test_single_layer_graphs_of_the_newer_paths_replay_correctly(case):
     """The paths whose step keeps state on the device between launches (arrival counters that the last workgroup
     rearms, stored inputs committed by whoever finishes last, difference buffers): captured once, replayed several
@@ -207,5 +207,9 @@ def test_single_layer_graphs_of_the_newer_paths_replay_correctly(case):
         _replay_case(S.pruned(S.config3("fc7", S.BF16, 0.10, T=5), 0.1, 4242), fc_sparse_weights=1)
     elif case == "fc_batched_i8":
         _replay_case(S.random_layer(9101, S.fc_shape(1024, 512, n=40), S.I8, T=5, frac=0.1))
+    elif case == "fc_padded_i8":
+        _replay_case(S.random_layer(9103, S.fc_shape(1030, 501, n=90), S.I8, T=5, frac=0.1))
+    elif case == "fc_padded_bf16":
+        _replay_case(S.random_layer(9104, S.fc_shape(515, 1001, n=33), S.BF16, T=5, frac=0.1))
     else:
         _replay_case(S.random_layer(9102, S.fc_shape(512, 256, n=24), S.BF16, T=5, frac=0.1))

@@ -211,6 +211,37 @@ def test_ragged_channel_runs(h, w, ci, co, k, g, n, dt, eps):
         layer.destroy()
 
 
+# The product of layers that are padded for it, steps and dense: rows of one entry over a step and one short of it, of whole 16-byte
+# units, with whole units of padding; outputs one over a block of 16, off the fours that a thread sums, one short of a block, and
+# outputs alone padded (rows of whole steps); every count of 16-stream tiles, groups of streams; the stored input, the counts and
+# the caller's copy; rounding as the walk's (sums of short chains).
+@pytest.mark.parametrize("ci,co,n", [
+    (65, 33, 704), (63, 64, 704), (2049, 1001, 44), (4095, 1007, 64), (2048, 1001, 33), (100, 130, 300), (999, 2002, 23), (2064, 1601, 28),
+    (3001, 1030, 90), (4100, 4001, 16), (2999, 513, 128), (2300, 7000, 9),
+])
+@pytest.mark.parametrize("dt", [S.I8, S.BF16])
+def test_fc_padded_product(ci, co, n, dt):
+    import numpy as np
+    from gpu_util import make_layer, to_device, x_bytes
+    seq = S.random_layer(9930 + ci, S.fc_shape(ci, co, n=n), dt, T=3, frac=0.3)
+    st, _ = run_sequence(seq, check_dense=(0, 2), y_out_frames=(1, 2), rel=1e-5)
+    before = [np.zeros_like(seq.frames[0])] + list(seq.frames[:-1])
+    assert st["changed_elems"] == sum(int((a != b).sum()) for a, b in zip(before, seq.frames)) and st["delta_steps"] == 3
+    layer, walk = make_layer(seq), make_layer(seq, fc_batched=0)
+    for x in seq.frames:
+        xd = to_device(x, dt)
+        layer.step(xd)
+        walk.step(xd)
+        assert np.array_equal(layer.x_snapshot_bytes().cpu().numpy(), x_bytes(x, dt))
+    if dt == S.BF16:  # against 64 bits; the walk's own sums too
+        f64 = lambda a: (a.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+        want = f64(seq.frames[-1]).reshape(n, ci) @ f64(seq.weights).reshape(co, ci).T + (0 if seq.bias is None else seq.bias.astype(np.float64))
+        err = [np.linalg.norm(l.y_snapshot().cpu().numpy().reshape(n, co) - want) / np.linalg.norm(want) for l in (layer, walk)]
+        assert err[0] <= max(err[1], 1.0e-7), err
+    layer.destroy()
+    walk.destroy()
+
+
 # The single-launch scatter path: blocks of 8 .. 64 positions (the last one short), one workgroup per block and several, one
 # tile of 32 listed positions and two, units off the pairs of a K step, several parts of K, channels off the blocks of 32,
 # strides that skip positions, groups; a few positions change, then all of them, then none.
