@@ -135,7 +135,9 @@ __device__ __forceinline__ T kept(T v) {
     return v;
 }
 
-template <int DT, int MODE, int NCB, int NT, int TERMS>
+// CUT: a group's channels are not a multiple of four.  A form of its own: the scalar registers that the cut quads' conditions take cost
+// the others 4 to 10 % (the five-layer stack, 512 streams, 571 -> 604 us).
+template <int DT, int MODE, int NCB, int NT, int TERMS, bool CUT>
 __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(ConvArgs) {
     const args_t args = (args_t)__builtin_amdgcn_kernarg_segment_ptr();
     fetch_args<sizeof(ConvArgs)>();
@@ -441,7 +443,7 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(ConvArgs) {
     sc_t* const y = static_cast<sc_t*>(cargs->y);
     const sc_t* const bias = static_cast<const sc_t*>(cargs->bias);
     const int nslab = kept(g.nslab), nq = kept(g.nq), nt = kept(g.nt), slot_bytes = kept(g.slot_bytes), tiles = kept(g.sty * g.stx),
-              stx = kept(g.stx), ho = kept(g.ho), wo = kept(g.wo), c_out = kept(g.c_out), og = kept(g.og), vec_store = kept(g.vec_store);
+              stx = kept(g.stx), ho = kept(g.ho), wo = kept(g.wo), c_out = kept(g.c_out), og = kept(g.og);
     const unsigned int magic_sub = kept(g.magic_sub), magic_stx = kept(g.magic_stx);
     // Consumer state of a unit: this lane's output position of its sub-tile, the accumulators, and what the result is
     // added to -- the stored projection (delta: Algorithm 1, P_t = P_{t-1} + F * dI) or the bias (dense: Eq. 3).
@@ -449,8 +451,24 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(ConvArgs) {
     // list, not from the producers) and is needed only after the unit's last slab: accumulators that start from it
     // would hold up the unit's first product until these loads, and the previous unit's stores before them (memory
     // operations of a wavefront are waited for in order), are done.  A dense launch, and the two-term 16-slot shape,
-    // which have no registers to spare for it, start the accumulators from `base`.  (Channel counts that are not multiples of 4 add
-    // element by element at the end.)
+    // which have no registers to spare for it, start the accumulators from `base`.
+    // Four outputs at the alignment of one (a position's channels need not be multiples of 4), fewer at the end of a group's channels.
+    // (All of
+    // such a layer's outputs entry by entry, added to the stored ones at the end: 28 x 28, 128 -> 101, 16 streams, int8 step 25.8 us and 14.6 so,
+    // bf16 26.5 and 19.3, bf16 dense 17.5 and 11.6; 59 x 59, 64 -> 469 1 x 1, nine streams, int8 dense 61.9 and 33.0.)
+    struct __attribute__((packed, aligned(CUT ? 4 : 16))) quad {
+        vec_t v;
+    };
+    auto load4 = [](const sc_t* p) __attribute__((always_inline)) { return reinterpret_cast<const quad*>(p)->v; };
+    auto store4 = [&](sc_t* p, const vec_t& v, int n) __attribute__((always_inline)) {
+        if (!CUT || n >= 4) {
+            reinterpret_cast<quad*>(p)->v = v;
+        } else {
+            p[0] = v.x;
+            if (n > 1) p[1] = v.y;
+            if (n > 2) p[2] = v.z;
+        }
+    };
     unsigned int ybase;
     bool pos_ok;
     acc_t acc[NCB];
@@ -476,10 +494,16 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(ConvArgs) {
 #pragma unroll
             for (int gq = 0; gq < 4; ++gq) {
                 const int co = chan(c, gq);
-                const bool ch_ok = vec_store && co < og && owned(gq);
+                const bool ch_ok = (CUT ? co + 3 : co) < og && owned(gq);
                 vec_t v = vec_t{0, 0, 0, 0};
-                if (!from_y && ch_ok && bias) v = *reinterpret_cast<const vec_t*>(bias + grp * og + co);
-                if (from_y && ch_ok && pos_ok) v = *reinterpret_cast<const vec_t*>(y + (ybase + (unsigned int)co));
+                if (!from_y && ch_ok && bias) v = load4(bias + grp * og + co);
+                if (from_y && ch_ok && pos_ok) v = load4(y + (ybase + (unsigned int)co));
+                if (CUT && co < og && co + 3 >= og && owned(gq) && (from_y ? pos_ok : bias != nullptr)) {
+                    const sc_t* const p = from_y ? y + (ybase + (unsigned int)co) : bias + grp * og + co;
+                    v.x = p[0];
+                    if (co + 1 < og) v.y = p[1];
+                    if (co + 2 < og) v.z = p[2];
+                }
                 if constexpr (LATE_BASE) {
                     base[c][gq] = v;
                     v = vec_t{0, 0, 0, 0};
@@ -644,7 +668,7 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(ConvArgs) {
         constexpr int RP = 36;  // words per position row of the scratch (16-byte aligned, spreads the banks)
         if (!active) {
             // (no pair in this unit, perhaps no slots at all: a 12-slot layer on the 16-slot shape)
-        } else if (vec_store && nt >= 8 && 2 * slot_bytes >= 32 * RP * 4) {
+        } else if (nt >= 8 && 2 * slot_bytes >= 32 * RP * 4) {
             vec_t* scr = reinterpret_cast<vec_t*>(bbase + ((gs - 1) & 1) * b_bytes + (2 * cw) * slot_bytes);
             const int posl = lane & 31;
             // the two sub-tiles of the pair (the same in every lane)
@@ -687,11 +711,10 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(ConvArgs) {
                     const int q = 8 * i + (lane >> 3);  // position of the pair: sub-tile q / 16, position q % 16
                     const vec_t o = scr[(q * RP + 4 * (lane & 7)) >> 2];
                     const int sl = i >> 1, py = 2 * (i & 1) + (lane >> 5), px = (lane >> 3) & 3;
-                    if (py < ny[sl] && px < nx[sl] && ch < og)
-                        *reinterpret_cast<vec_t*>(y + (corner[sl] + (unsigned int)((py * wo + px) * c_out + ch))) = o;
+                    if (py < ny[sl] && px < nx[sl] && ch < og) store4(y + (corner[sl] + (unsigned int)((py * wo + px) * c_out + ch)), o, og - ch);
                 }
             }
-        } else if (vec_store) {
+        } else {
 #pragma unroll
             for (int c = 0; c < NCB; ++c)
 #pragma unroll
@@ -703,25 +726,7 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(ConvArgs) {
                     o.y = acc[c][4 * gq + 1];
                     o.z = acc[c][4 * gq + 2];
                     o.w = acc[c][4 * gq + 3];
-                    *reinterpret_cast<vec_t*>(y + (ybase + (unsigned int)co)) = o;
-                }
-        } else {
-            // channel counts that are not multiples of 4: element by element
-#pragma unroll
-            for (int c = 0; c < NCB; ++c)
-#pragma unroll
-                for (int gq = 0; gq < 4; ++gq) {
-                    const int co0 = chan(c, gq);
-                    if (!pos_ok || co0 >= og || !owned(gq)) continue;
-                    sc_t* yp4 = y + (ybase + (unsigned int)co0);
-                    for (int k = 0; k < 4 && co0 + k < og; ++k) {
-                        const sc_t r = acc[c][4 * gq + k];
-                        if (from_y) {
-                            if (r != (sc_t)0) yp4[k] += r;
-                        } else {
-                            yp4[k] = r + (bias ? bias[grp * og + co0 + k] : (sc_t)0);
-                        }
-                    }
+                    store4(y + (ybase + (unsigned int)co), o, og - co);
                 }
         }
         if (iu + 1 < r1) begin_unit(iu + 1, r0);  // (a new round's first unit waits for its ranking)
@@ -731,7 +736,7 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(ConvArgs) {
     }
 }
 
-template <int DT, int MODE, int NCB, int NT, int TERMS>
+template <int DT, int MODE, int NCB, int NT, int TERMS, bool CUT>
 hipError_t launch_one(const void* src0, const void* src1, const void* zero16, unsigned int* flags,
                       const void* wpack, const int* offtab, const void* bias, void* y,
                       const ConvGeom& g, DevStats* stats, hipStream_t s) {
@@ -753,7 +758,7 @@ hipError_t launch_one(const void* src0, const void* src1, const void* zero16, un
     gg.magic_gyg = magic_of(ncbg);
     gg.xcd_deal = gx >= 8 && gx == resident / gy;
     if (gg.xcd_deal) grid = dim3((unsigned int)(gx * gy), 1u);
-    auto kern = conv_gather_kernel<DT, MODE, NCB, NT, TERMS>;
+    auto kern = conv_gather_kernel<DT, MODE, NCB, NT, TERMS, CUT>;
     if (lds > 64 * 1024) {
         // one per instantiation, shared by every handle and thread of the process: guarded, so that
         // distinct handles stay independent
@@ -779,7 +784,8 @@ hipError_t launch_shape(int ncb, int nt, const void* src0, const void* src1, con
                         const ConvGeom& g, DevStats* stats, hipStream_t s) {
 #define RRM_CASE(CBV, NTV)                                                                                          \
     if (ncb == CBV && nt == NTV)                                                                                     \
-        return launch_one<DT, MODE, CBV, NTV, TERMS>(src0, src1, zero16, flags, wpack, offtab, bias, y, g, stats, s);
+        return g.og % 4 ? launch_one<DT, MODE, CBV, NTV, TERMS, true>(src0, src1, zero16, flags, wpack, offtab, bias, y, g, stats, s) \
+                        : launch_one<DT, MODE, CBV, NTV, TERMS, false>(src0, src1, zero16, flags, wpack, offtab, bias, y, g, stats, s);
     nt = nt <= 8 ? 8 : 16;  // fewer slots than the shape has: same code, the slot count is in g.nt
     RRM_CASE(2, 16) RRM_CASE(2, 8) RRM_CASE(1, 16) RRM_CASE(1, 8)
 #undef RRM_CASE

@@ -372,7 +372,6 @@ rrm_status setup_conv(rrm_layer* L, const std::vector<unsigned char>& w) {
     g.magic_sub = magic_of(g.sty * g.stx);
     g.magic_stx = magic_of(g.stx);
     for (int d = 0; d <= 16; ++d) g.magic_per[d] = magic_of(d);
-    g.vec_store = (s.c_out % 4 == 0) && (g.og % 4 == 0);
     const int ntaps = s.kh * g.kw_eff;
     const int terms = L->dtype == RRM_BF16_F32 ? 2 : 1;
     // Workgroup shape.  Few sub-tiles in total (one stream of a small map): latency matters, so one 32-channel block

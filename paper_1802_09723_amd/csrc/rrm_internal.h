@@ -129,7 +129,6 @@ struct ConvGeom {
     unsigned int magic_sub;     // reciprocals (floor(2^32/d)+1, 0 for d = 1): d = sty*stx
     unsigned int magic_stx;     // d = stx
     int ksh;             // log2 of the parts that a pair's K steps are split into (one channel block, few slots)
-    int vec_store;       // 1: y rows allow 16-byte read-modify-write
     unsigned int* fresh;    // see FusedSrc::fresh: cleared at the end of a delta launch
     unsigned int* touched_all;  // see FusedSrc::touched_all: written by every delta launch
     unsigned int* epoch;    // see StepEpoch

@@ -242,6 +242,19 @@ def test_fc_padded_product(ci, co, n, dt):
     walk.destroy()
 
 
+# Output channels off the fours that a lane holds: one, two and three of a last four, fewer than four in all, whole blocks of 32 and one
+# more, two blocks, groups whose channels start at any offset; maps off the 4 x 4 sub-tiles; few sub-tiles (K in parts) and
+# many; changed sub-tiles alone, and everything recomputed.
+@pytest.mark.parametrize("h,w,ci,co,k,st,g,n", [
+    (5, 6, 16, 1, 3, 1, 1, 1), (9, 7, 32, 3, 3, 1, 1, 2), (8, 8, 64, 33, 3, 1, 1, 1), (13, 13, 128, 66, 3, 1, 2, 3), (14, 10, 48, 101, 1, 1, 1, 9),
+    (20, 20, 32, 62, 5, 2, 1, 8), (28, 28, 64, 67, 3, 1, 1, 24), (30, 29, 32, 130, 3, 1, 1, 40), (40, 40, 48, 18, 3, 1, 3, 20), (17, 17, 256, 5, 3, 1, 1, 40),
+])
+@pytest.mark.parametrize("dt,opts", [(S.I8, {}), (S.BF16, {}), (S.BF16, {"bf16_terms": 1}), (S.I8, {"dense_switch_pct": 1}), (S.BF16, {"dense_switch_pct": 1})])
+def test_output_channels_off_the_fours(h, w, ci, co, k, st, g, n, dt, opts):
+    seq = S.random_layer(9840 + h + co, S.conv_shape(h, w, ci, co, k, st, k // 2, g, n=n), dt, T=3, frac=0.1, block=2)
+    run_sequence(seq, check_dense=(0, 2), rel=5e-3 if opts.get("bf16_terms") else 1e-4, path=1, **opts)
+
+
 # The single-launch scatter path: blocks of 8 .. 64 positions (the last one short), one workgroup per block and several, one
 # tile of 32 listed positions and two, units off the pairs of a K step, several parts of K, channels off the blocks of 32,
 # strides that skip positions, groups; a few positions change, then all of them, then none.
