@@ -472,8 +472,27 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(ConvArgs) {
     unsigned int ybase;
     bool pos_ok;
     acc_t acc[NCB];
-    constexpr bool LATE_BASE = MODE == MODE_DELTA && !(TERMS == 2 && NT == 16);
+    // fp32 sums of CUT layers always meet it at the end, in the two-term shape of 16 slots and two blocks fetched only then (END_BASE):
+    // accumulators that start from it round every product at its magnitude (relative error of 40 x 40, 48 -> 18 1 x 1, 40 streams,
+    // 3.75e-8 so and 3.57e-8, of 56 x 56, 24 -> 101, 20 streams, 5 % changed, 6.67e-8 and 6.53e-8, whose step takes 17.5 and 18.6 us).
+    constexpr bool CUT_SUMS = CUT && DT == RRM_BF16_F32;
+    constexpr bool LATE_BASE = TERMS == 2 && NT == 16 ? CUT_SUMS && NCB == 1 : MODE == MODE_DELTA || CUT_SUMS;
+    constexpr bool END_BASE = CUT_SUMS && !LATE_BASE;
     vec_t base[NCB][LATE_BASE ? 4 : 1];
+    auto base_quad = [&](int c, int gq) __attribute__((always_inline)) {
+        const int co = chan(c, gq);
+        const bool ch_ok = (CUT ? co + 3 : co) < og && owned(gq);
+        vec_t v = vec_t{0, 0, 0, 0};
+        if (!from_y && ch_ok && bias) v = load4(bias + grp * og + co);
+        if (from_y && ch_ok && pos_ok) v = load4(y + (ybase + (unsigned int)co));
+        if (CUT && co < og && co + 3 >= og && owned(gq) && (from_y ? pos_ok : bias != nullptr)) {
+            const sc_t* const p = from_y ? y + (ybase + (unsigned int)co) : bias + grp * og + co;
+            v.x = p[0];
+            if (co + 1 < og) v.y = p[1];
+            if (co + 2 < og) v.z = p[2];
+        }
+        return v;
+    };
     auto begin_unit = [&](int iu2, int r0) {
         const int first2 = (bx + iu2 * gx) * per;
         const int mycount2 = min(per, count - first2);
@@ -493,21 +512,11 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(ConvArgs) {
         for (int c = 0; c < NCB; ++c)
 #pragma unroll
             for (int gq = 0; gq < 4; ++gq) {
-                const int co = chan(c, gq);
-                const bool ch_ok = (CUT ? co + 3 : co) < og && owned(gq);
                 vec_t v = vec_t{0, 0, 0, 0};
-                if (!from_y && ch_ok && bias) v = load4(bias + grp * og + co);
-                if (from_y && ch_ok && pos_ok) v = load4(y + (ybase + (unsigned int)co));
-                if (CUT && co < og && co + 3 >= og && owned(gq) && (from_y ? pos_ok : bias != nullptr)) {
-                    const sc_t* const p = from_y ? y + (ybase + (unsigned int)co) : bias + grp * og + co;
-                    v.x = p[0];
-                    if (co + 1 < og) v.y = p[1];
-                    if (co + 2 < og) v.z = p[2];
-                }
-                if constexpr (LATE_BASE) {
-                    base[c][gq] = v;
-                    v = vec_t{0, 0, 0, 0};
-                }
+                if constexpr (LATE_BASE)
+                    base[c][gq] = base_quad(c, gq);
+                else if constexpr (!END_BASE)
+                    v = base_quad(c, gq);
                 acc[c][4 * gq + 0] = v.x;
                 acc[c][4 * gq + 1] = v.y;
                 acc[c][4 * gq + 2] = v.z;
@@ -645,15 +654,20 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(ConvArgs) {
         }
 
         // ---- epilogue ----------------------------------------------------------------------------------
-        if constexpr (LATE_BASE)
+        if constexpr (LATE_BASE || END_BASE)
 #pragma unroll
             for (int c = 0; c < NCB; ++c)
 #pragma unroll
                 for (int gq = 0; gq < 4; ++gq) {
-                    acc[c][4 * gq + 0] += base[c][gq].x;
-                    acc[c][4 * gq + 1] += base[c][gq].y;
-                    acc[c][4 * gq + 2] += base[c][gq].z;
-                    acc[c][4 * gq + 3] += base[c][gq].w;
+                    vec_t v;
+                    if constexpr (LATE_BASE)
+                        v = base[c][gq];
+                    else
+                        v = base_quad(c, gq);
+                    acc[c][4 * gq + 0] += v.x;
+                    acc[c][4 * gq + 1] += v.y;
+                    acc[c][4 * gq + 2] += v.z;
+                    acc[c][4 * gq + 3] += v.w;
                 }
         // (the store addresses are rebuilt from ybase here: kept across the K loops they would cost two
         // registers per store)

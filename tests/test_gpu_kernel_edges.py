@@ -255,6 +255,38 @@ def test_output_channels_off_the_fours(h, w, ci, co, k, st, g, n, dt, opts):
     run_sequence(seq, check_dense=(0, 2), rel=5e-3 if opts.get("bf16_terms") else 1e-4, path=1, **opts)
 
 
+# ... and their fp32 sums round once, when they meet the projection or the bias.  Inputs and weights are multiples of 1/64 and of 1/256 and
+# the sums below 2^7, so that sums of products among themselves are exact in fp32 in any order; projections of 4096 and more are
+# multiples of 2^-11, which every addition rounds to.  Sixteen slots of two terms (one channel block, two, groups, 1 x 1) and eight.
+@pytest.mark.parametrize("h,w,ci,co,k,g,n", [(40, 40, 16, 18, 3, 1, 11), (40, 40, 16, 66, 3, 1, 11), (40, 40, 48, 18, 3, 3, 11), (40, 40, 48, 18, 1, 1, 11), (28, 28, 128, 101, 3, 1, 8)])
+def test_output_channels_off_the_fours_round_once(h, w, ci, co, k, g, n):
+    import numpy as np
+    import oracle
+    from gpu_util import make_layer, to_device
+    seq = S.random_layer(9830 + co + k, S.conv_shape(h, w, ci, co, k, 1, k // 2, g, n=n), S.BF16, T=2, frac=0.1, block=2)
+    rng = np.random.default_rng(9831 + co + k)
+    bf16 = lambda a: (a.astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    seq.weights = bf16(rng.integers(-16, 17, seq.weights.shape) / 256.0)
+    seq.bias = rng.uniform(4200.0, 8000.0, co).astype(np.float32)
+    changed = (seq.frames[1] != seq.frames[0]).any(axis=-1, keepdims=True)
+    seq.frames[0] = bf16(rng.integers(0, 65, seq.frames[0].shape) / 64.0)
+    seq.frames[1] = np.where(changed, bf16(rng.integers(0, 65, seq.frames[1].shape) / 64.0), seq.frames[0])
+    sums = [oracle.dense(seq.shape, S.BF16, seq.weights, None, x) for x in seq.frames]
+    assert max(abs(s).max() for s in sums) < 128.0
+    full = [(seq.bias.astype(np.float64) + s).astype(np.float32) for s in sums]
+    stepped = (full[0].astype(np.float64) + (sums[1] - sums[0])).astype(np.float32)
+    frames = [to_device(x, S.BF16) for x in seq.frames]
+    for opts, want in (({"path": 1}, stepped), ({"dense_switch_pct": 1}, full[1])):
+        layer = make_layer(seq, conv_kernel=1, **opts)
+        for x, y in zip(frames, (full[0], want)):
+            layer.step(x)
+            assert np.array_equal(layer.y_snapshot().cpu().numpy(), y), opts
+        y = torch.empty(layer.y_shape, dtype=torch.float32, device="cuda")
+        layer.dense(frames[1], y)
+        assert np.array_equal(y.cpu().numpy(), full[1])
+        layer.destroy()
+
+
 # The single-launch scatter path: blocks of 8 .. 64 positions (the last one short), one workgroup per block and several, one
 # tile of 32 listed positions and two, units off the pairs of a K step, several parts of K, channels off the blocks of 32,
 # strides that skip positions, groups; a few positions change, then all of them, then none.
