@@ -605,6 +605,11 @@ __global__ __launch_bounds__(wg_threads(NT)) void conv_gather_kernel(ConvArgs) {
             tb = tp[q0];
             fetch(q0, tb, o0);
             ta = tp[min(q0 + 1, qmax)];
+            // Two matrix instructions a step do not hide where the loop lies in the 32-byte lines that instructions are fetched in: it
+            // begins eight bytes into one, the fastest of the eight places.  (us a call over them, long windows that leave short
+            // slabs, five streams of 46 x 25, 456 -> 144, 5 x 5 bf16: half changed, recomputed, 71.4 .. 74.9, dense 57.2 .. 60.9; 448 ->
+            // 144 int8 dense 38.3 .. 41.2.  The other shapes' times are within 1 % of each other.)
+            if constexpr (KSPLIT && T == 1) asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0");
             for (int q = q0; q < q1; q += 2) {
                 step(o0, o1, ta, tb, min(q + 1, qmax), min(q + 2, qmax));
                 if (q + 1 < q1) step(o1, o0, tb, ta, min(q + 2, qmax), min(q + 3, qmax));

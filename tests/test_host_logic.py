@@ -1,5 +1,11 @@
 """Host-side logic that needs no GPU: the index arithmetic the kernels rely on."""
+import os
+import re
+import struct
+import subprocess
+
 import numpy as np
+import pytest
 
 
 def _magic(d):
@@ -138,3 +144,48 @@ def test_binary_band_geometry_terminates_fits_and_covers(tmp_path):
                 hi = h if b == nb - 1 else (b + 1) * R * stride
                 assert lo >= b * R * stride - pad and hi <= b * R * stride - pad + f["bth"], (cse, f, b)
     assert banded >= 40 and fused >= 10
+
+
+def _gfx950_functions(path, tmp_path, name):
+    """{kernel: [(address, instruction)]} of the library's gfx950 functions whose mangled name holds `name`."""
+    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+    if not os.path.exists(objdump):
+        pytest.skip("no llvm-objdump")
+    blob, found = open(path, "rb").read(), {}
+    for at in (m.start() for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", blob)):
+        pos = at + 32
+        for _ in range(struct.unpack_from("<Q", blob, at + 24)[0]):
+            off, size, n = struct.unpack_from("<QQQ", blob, pos)
+            if b"gfx950" in blob[pos + 24:pos + 24 + n] and name.encode() in blob[at + off:at + off + size]:
+                obj = tmp_path / f"{at}.o"
+                obj.write_bytes(blob[at + off:at + off + size])
+                fn = None
+                for line in subprocess.run([objdump, "-d", str(obj)], capture_output=True, text=True, check=True).stdout.splitlines():
+                    if m := re.match(r"^[0-9a-f]+ <(.*)>:", line):
+                        fn = m.group(1) if name in m.group(1) else None
+                        if fn:
+                            found[fn] = []
+                    elif fn and (m := re.match(r"^\s+(\S.*?)\s*// ([0-9A-F]+): ", line)):
+                        found[fn].append((int(m.group(2), 16), m.group(1)))
+            pos += 24 + n
+    return found
+
+
+def test_short_k_loops_begin_where_they_are_fastest(tmp_path):
+    """The one-term K loop of the window-tile kernel's shape of one channel block and eight slots begins eight bytes into a 32-byte
+    line of instructions, in every form of the kernel (wherever else it lies it is up to 6 % slower)."""
+    from paper_1802_09723_amd.binding import lib_path
+    if not os.path.exists(lib_path()):
+        pytest.skip("the library is not built")
+    kernels = {k: v for k, v in _gfx950_functions(lib_path(), tmp_path, "conv_gather_kernel").items()
+               if re.search(r"conv_gather_kernelILi\dELi\dELi1ELi8E", k)}
+    assert len(kernels) >= 10
+    for fn, code in kernels.items():
+        loops = []  # (length, begin) of the loops around this kernel's four one-term products
+        for at, text in code:
+            m = re.match(r"s_c?branch\S* (\d+)", text)
+            if m and int(m.group(1)) > 32767:
+                begin = at + 4 + 4 * (int(m.group(1)) - 65536)
+                if sum("v_mfma" in t for a, t in code if begin <= a <= at) == 4:
+                    loops.append((at - begin, begin))
+        assert loops and min(loops)[1] % 32 == 8, fn
