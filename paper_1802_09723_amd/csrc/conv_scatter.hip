@@ -87,8 +87,8 @@ constexpr int scat_planes(int dtype) { return dtype == RRM_BF16_F32 ? 2 : 1; }
 // DIFF (int8): the compare is a scan's (one that computed the input from another layer's projection, in a launch of its own); x_t is
 // the difference it left, zero wherever nothing changed.  The launch keeps the sub-tile flags as the tile kernel does, in a
 // row of workgroups of its own behind the position blocks.
-template <int DT, int TERMS, bool DIFF, int UPT>
-__global__ __launch_bounds__(ST + SCAT_BOOKS) __attribute__((amdgpu_waves_per_eu(2, 3))) void conv_scatter_kernel(const uint4* __restrict__ x_t, uint4* x_snap,
+template <int DT, int TERMS, bool DIFF, int UPT, bool BOOKS>
+__global__ __launch_bounds__(ST + (BOOKS ? SCAT_BOOKS : 0)) __attribute__((amdgpu_waves_per_eu(2, 3))) void conv_scatter_kernel(const uint4* __restrict__ x_t, uint4* x_snap,
                                                           const uint4* __restrict__ wsc, void* y_v, ScatGeom g,
                                                           DevStats* __restrict__ stats_base) {
     typedef typename std::conditional<DT == RRM_I8_I32, v16i, v16f>::type acc_t;
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(ST + SCAT_BOOKS) __attribute__((amdgpu_waves_per_eu
     const int plane = g.PB * g.U;  // units per plane
     uint4* zero_unit = dl + scat_planes(DT) * plane;
     __shared__ unsigned int s_flag[64];
-    __shared__ int s_list[ST / 64 + 1][64];  // (every wavefront makes its own list: nothing to wait for)
+    __shared__ int s_list[ST / 64 + (BOOKS ? 1 : 0)][64];  // (every wavefront makes its own list: nothing to wait for)
     __shared__ unsigned int s_prev;
     __shared__ __align__(16) int s_out[ST / 64][2][32];  // output offsets of an item's rows, or -1
 
@@ -136,8 +136,10 @@ __global__ __launch_bounds__(ST + SCAT_BOOKS) __attribute__((amdgpu_waves_per_eu
 
     // A block's workgroups count up one word, and the answer (0.7 us on an idle chip, 1.7 among the 36 of 14 x 14 x 256 bf16) must
     // not be waited for by a wavefront that has products to make: one more wavefront asks for it, and commits the stored input
-    // if its workgroup was the last of the block to compare.
-    const bool books = !DIFF && UPT * ST <= SCAT_BOOKS_UNITS && g.books != 0;
+    // if its workgroup was the last of the block to compare.  (BOOKS: see launch_conv_scatter.  Always set then, but read from the
+    // arguments: known to the compiler, it waits for the weights ahead of the list, 28 x 28, 512 -> 128 1 x 1, 5.2 -> 5.4 us.)
+    static_assert(!BOOKS || (!DIFF && UPT * ST <= SCAT_BOOKS_UNITS), "one wavefront commits a block's units");
+    const bool books = BOOKS && g.books != 0;
     if (books && wave == ST / 64) {
         const int U = kept(g.U);
         const unsigned int magic_U = kept(g.magic_U);
@@ -440,11 +442,12 @@ __global__ __launch_bounds__(ST + SCAT_BOOKS) __attribute__((amdgpu_waves_per_eu
             // 3 x 3, one stream, 14 x 14 x 256, 5 / 25 % changed, 9.2 / 13.7 us instead of 7.4 / 8.4; 10 x 10 x 320, four
             // streams, 10 %, 23.8 instead of 11.4; int8 5 x 5, 27 x 27, 96 -> 256, 10 %, 15.3 instead of 7.2.)
             const int c = cb * 32 + n;
-            // An address from a scalar base and a 32-bit offset (an output has at most 2^30 entries) takes half of the instructions, where there are scalar registers for the
-            // base: next to the books they are short, and it would be fetched back from a vector register's lane at every add (us a
-            // step with it and without: 14 x 14, 512 -> 256 int8, half changed, 9.15 and 8.3; 28 x 28, 256 -> 64 bf16, 8.3 and 7.75;
-            // without books 64 x 64, 512 -> 64 1 x 1, 8 streams, 10.05 and 10.3; the five-layer stack 50.3 -> 48.5).
-            constexpr bool SADDR = DIFF || UPT * ST > SCAT_BOOKS_UNITS;
+            // An address from a scalar base and a 32-bit offset (an output has at most 2^30 entries) takes half of the instructions,
+            // where there are scalar registers for the base: next to the books they are short, and it would be fetched back from a
+            // vector register's lane at every add (us a step with it and without: 14 x 14, 512 -> 256 int8, half changed, 9.15 and 8.3;
+            // 28 x 28, 256 -> 64 bf16, 8.3 and 7.75; without books 24 x 27, 32 -> 48, ten streams, 4.6 and 5.0, 64 x 64, 512 -> 64
+            // 1 x 1, 8 streams, 10.05 and 10.3; the five-layer stack 50.3 -> 48.5).
+            constexpr bool SADDR = !BOOKS;
             const int least = c < og ? 0 : 0x7FFFFFFF;  // (no row is that large: a channel that is not there adds nothing)
             char* const yb = reinterpret_cast<char*>(y);
             const unsigned int ch = (unsigned int)(grp * og + c);
@@ -516,33 +519,38 @@ __global__ __launch_bounds__(ST + SCAT_BOOKS) __attribute__((amdgpu_waves_per_eu
 
 }  // namespace
 
-// A workgroup's LDS beyond 64 KB, dynamic and static (the lists and flags, 2.3 KB): for every form of the kernel, once per process
+// A workgroup's LDS beyond 64 KB, dynamic and static (the lists and flags, 2.6 KB at most): for every form of the kernel, once per process
 static hipError_t scatter_lds(size_t lds) {
     if (lds + 4 * 1024 <= 64 * 1024) return hipSuccess;
     static std::once_flag once;
     static hipError_t attr = hipSuccess;
     std::call_once(once, [] {
-        auto all = [&]<int UPT>() {
-            for (const void* f : {reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_I8_I32, 1, false, UPT>),
-                                  reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_I8_I32, 1, true, UPT>),
-                                  reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_BF16_F32, 1, false, UPT>),
-                                  reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_BF16_F32, 2, false, UPT>)})
+        auto all = [&]<int UPT, bool BOOKS>() {
+            for (const void* f : {reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_I8_I32, 1, false, UPT, BOOKS>),
+                                  reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_I8_I32, 1, !BOOKS, UPT, BOOKS>),
+                                  reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_BF16_F32, 1, false, UPT, BOOKS>),
+                                  reinterpret_cast<const void*>(&conv_scatter_kernel<RRM_BF16_F32, 2, false, UPT, BOOKS>)})
                 if (attr == hipSuccess) attr = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
         };
-        all.template operator()<1>();
-        all.template operator()<2>();
-        all.template operator()<4>();
-        all.template operator()<8>();
+        all.template operator()<1, false>();
+        all.template operator()<2, false>();
+        all.template operator()<4, false>();
+        all.template operator()<8, false>();
+        all.template operator()<1, true>();
+        all.template operator()<2, true>();
+        all.template operator()<4, true>();
     });
     return attr;
 }
 
 // the form of the kernel for blocks of PB * U units: see UPT there
-template <int DT, int TERMS, bool DIFF>
+template <int DT, int TERMS, bool DIFF, bool BOOKS>
 static auto scatter_form(const ScatGeom& g) {
     const int upt = (g.PB * g.U + ST - 1) / ST;
-    return upt <= 1 ? conv_scatter_kernel<DT, TERMS, DIFF, 1> : upt <= 2 ? conv_scatter_kernel<DT, TERMS, DIFF, 2>
-           : upt <= 4 ? conv_scatter_kernel<DT, TERMS, DIFF, 4> : conv_scatter_kernel<DT, TERMS, DIFF, 8>;
+    if constexpr (!BOOKS)
+        if (upt > 4) return conv_scatter_kernel<DT, TERMS, DIFF, 8, false>;
+    return upt <= 1 ? conv_scatter_kernel<DT, TERMS, DIFF, 1, BOOKS> : upt <= 2 ? conv_scatter_kernel<DT, TERMS, DIFF, 2, BOOKS>
+                                                                                : conv_scatter_kernel<DT, TERMS, DIFF, 4, BOOKS>;
 }
 
 hipError_t launch_conv_scatter(int dtype, int terms, const void* x_t, void* x_snap, const void* wsc, void* y,
@@ -553,11 +561,18 @@ hipError_t launch_conv_scatter(int dtype, int terms, const void* x_t, void* x_sn
     const size_t lds = ((size_t)scat_planes(dtype) * g.PB * g.U + 1) * 16;
     const hipError_t e = scatter_lds(lds);
     if (e != hipSuccess) return e;
-    g.books = g.cs > 1 && g.PB * g.U <= SCAT_BOOKS_UNITS && (dtype == RRM_I8_I32 || nblk * g.cs <= NUM_CU);
-    const auto kernel = dtype == RRM_I8_I32 ? scatter_form<RRM_I8_I32, 1, false>(g)
-                        : terms == 2        ? scatter_form<RRM_BF16_F32, 2, false>(g)
-                                            : scatter_form<RRM_BF16_F32, 1, false>(g);
-    hipLaunchKernelGGL(kernel, grid, dim3(ST + (g.books ? SCAT_BOOKS : 0)), lds, s, static_cast<const uint4*>(x_t), static_cast<uint4*>(x_snap),
+    // The wavefront of the books costs a compute unit that holds two workgroups more than it saves the one that is last: int8 up to a
+    // few workgroups more than there are compute units, bf16, with more registers, up to that.  (us a step with and without, int8,
+    // 5 / 25 % changed: 280 workgroups, 11 x 19, 368 -> 96, three streams, 5.55 / 6.7 and 5.85 / 7.15; 294, 18 x 18, 352 -> 96, two, 5.5
+    // / 6.95 and 5.4 / 7.0; 343, 28 x 28 x 96, four, 4.95 / 7.25 and 4.85 / 6.85; 510, 24 x 27, 32 -> 48, ten, 5.2 / 6.85 and 4.6 / 6.65)
+    const bool books = g.books = g.cs > 1 && g.PB * g.U <= SCAT_BOOKS_UNITS && nblk * g.cs <= (dtype == RRM_I8_I32 ? 9 * NUM_CU / 8 : NUM_CU);
+    auto form = [&]<bool BOOKS>() {
+        return dtype == RRM_I8_I32 ? scatter_form<RRM_I8_I32, 1, false, BOOKS>(g)
+               : terms == 2        ? scatter_form<RRM_BF16_F32, 2, false, BOOKS>(g)
+                                   : scatter_form<RRM_BF16_F32, 1, false, BOOKS>(g);
+    };
+    const auto kernel = books ? form.template operator()<true>() : form.template operator()<false>();
+    hipLaunchKernelGGL(kernel, grid, dim3(ST + (books ? SCAT_BOOKS : 0)), lds, s, static_cast<const uint4*>(x_t), static_cast<uint4*>(x_snap),
                        static_cast<const uint4*>(wsc), y, g, stats);
     return hipGetLastError();
 }
@@ -568,7 +583,7 @@ hipError_t launch_conv_scatter_diff(const void* d0, const void* wsc, void* y, co
     const size_t lds = ((size_t)g.PB * g.U + 1) * 16;
     const hipError_t e = scatter_lds(lds);
     if (e != hipSuccess) return e;
-    const auto kernel = scatter_form<RRM_I8_I32, 1, true>(g);
+    const auto kernel = scatter_form<RRM_I8_I32, 1, true, false>(g);
     hipLaunchKernelGGL(kernel, grid, dim3(ST), lds, s, static_cast<const uint4*>(d0), static_cast<uint4*>(nullptr),
                        static_cast<const uint4*>(wsc), y, g, stats);
     return hipGetLastError();

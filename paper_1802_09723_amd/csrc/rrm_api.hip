@@ -520,18 +520,28 @@ rrm_status setup_scatter(rrm_layer* L, const std::vector<unsigned char>& w) {
     // workgroups (one round each at most), up to about two workgroups per compute unit in all.
     g.nkp = (g.nk + 7) / 8;
     const long long items = (long long)g.npair * g.ntaps * g.nkp;
-    // Where that leaves few blocks, they are of at most the units that one wavefront commits (see the kernel; us a step: 28 x 28, 512 -> 128 1 x
-    // 1, 25 blocks, 6.85 -> 5.35; 14 x 14, 512 -> 256, half changed, 7 blocks, 8.95 -> 8.2; two streams, 10 %, 13 blocks, 7.45 and 7.55; but 20 x
-    // 20, 384 -> 128, three streams, 38 blocks, 6.9 and 8.3: every block reads all weights).  Behind a scan, where the scan commits,
+    // Where that leaves few blocks, they are of at most the units that one wavefront commits (see the kernel): the chain of a step is
+    // shorter, but every block reads all weights, and int8 blocks that many workgroups share lose by it where not every one of those
+    // has a compute unit.  us a step, 4 / 10 / 25 / 50 % changed, without and so (blocks x workgroups of each, so):
+    //   int8  11 x 11, 352 -> 384 3 x 3            4 x 54   5.9 / 6.1 / 6.6 / 7.4     5.0 / 5.0 / 6.2 / 6.7
+    //   int8  12 x 21, 352 -> 64, two streams     16 x  9   5.9 / 6.1 / 6.6 / 7.2     4.8 / 5.2 / 5.4 / 5.9
+    //   int8  24 x 7, 400 -> 112, five            27 x 18   7.1 / 7.0 / 8.0 / 9.2     6.0 / 6.1 / 7.2 / 8.2
+    //   int8  20 x 20, 384 -> 64 5 x 5, two       25 x 21   6.4 / 7.8 / 9.5 / 10.4    6.6 / 8.1 / 9.3 / 10.9   (and so left as they are)
+    //   int8  8 x 24, 352 -> 432                   6 x 63   6.5 / 6.7 / 7.5 / 8.4     6.4 / 6.9 / 8.1 / 9.1    (and so left)
+    //   int8  14 x 14, 512 -> 256, two            13 x 36   6.5 /     / 8.5 / 10.0    6.4 /     / 8.9 / 10.5   (and so left)
+    //   bf16  15 x 15, 288 -> 192 at stride 2, two 29 x 18  8.3 / 8.7 / 11.7 / 12.6   8.5 / 8.6 / 10.5 / 11.0
+    // (20 x 20, 384 -> 128 int8, three streams, 38 blocks, 6.9 and 8.3.)  Behind a scan, where the scan commits,
     // only a few (a five-layer stack, one stream, 6 blocks, 50.3 and 49.0 us; two and four, 11 and 22 blocks, 58.7 and 59.5, 69.2 and 70.3).
     const int pb_most = g.PB;
-    auto cut = [&](ScatGeom& t, long long most_blocks) {
-        for (t.PB = pb_most; t.PB > 8 && t.PB * t.U > SCAT_BOOKS_UNITS && t.npos_total <= most_blocks * (t.PB / 2);) t.PB /= 2;
-        const long long nblk = (t.npos_total + t.PB - 1) / t.PB;
-        t.cs = (int)std::max(1ll, std::min((items + 3) / 4, (2ll * NUM_CU + nblk - 1) / nblk));
-        return nblk;
+    auto cut = [&](ScatGeom& t, long long most_blocks, bool commits) {
+        auto blocks = [&](int pb) { return (t.npos_total + pb - 1) / pb; };
+        auto splits = [&](int pb) { return std::max(1ll, std::min((items + 3) / 4, (2ll * NUM_CU + blocks(pb) - 1) / blocks(pb))); };
+        auto fits = [&](int pb) { return !commits || terms == 2 || splits(pb) <= 20 || blocks(pb) * splits(pb) <= 9 * NUM_CU / 8; };
+        for (t.PB = pb_most; t.PB > 8 && t.PB * t.U > SCAT_BOOKS_UNITS && t.npos_total <= most_blocks * (t.PB / 2) && fits(t.PB / 2);) t.PB /= 2;
+        t.cs = (int)splits(t.PB);
+        return blocks(t.PB);
     };
-    const long long nblk = cut(g, 32);
+    const long long nblk = cut(g, 32, true);
     g.magic_U = magic_of(g.U); g.magic_hw = magic_of(g.h * g.w); g.magic_w = magic_of(g.w); g.magic_nkp = magic_of(g.nkp);
     g.magic_taps = magic_of(g.ntaps); g.magic_ncb = magic_of(g.ncb); g.magic_kw = magic_of(g.kw); g.magic_stride = magic_of(g.stride);
     std::vector<unsigned char> pack((size_t)g.npair * g.ntaps * g.nk * 64 * 16, 0);
@@ -552,7 +562,7 @@ rrm_status setup_scatter(rrm_layer* L, const std::vector<unsigned char>& w) {
     if ((st = dalloc((size_t)nblk * sizeof(unsigned int), (void**)&L->sc_arrive)) != RRM_OK) return st;
     g.arrive = L->sc_arrive;
     L->sc_diff = g;
-    cut(L->sc_diff, 8);
+    cut(L->sc_diff, 8, false);
     L->scat_ok = true;
     // Automatic: layers of few output adds.  Two dependent launches and the per-workgroup set-up of the tile kernels cost more
     // there than the step's work; what the scatter pays more for is its adds into the projection, one per changed position, tap,

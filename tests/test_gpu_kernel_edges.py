@@ -304,11 +304,13 @@ def test_scatter_path_edges(h, w, ci, co, k, st, pad, g, n, dt):
 
 # Forms of the scatter kernel: one, two, four and eight units per thread, and one beyond a whole number of them; the commit by the
 # wavefront that announces the workgroup (few workgroups; 1024 units, the most that it takes), by all threads (more units, many
-# bf16 workgroups, one workgroup per block); blocks halved to those 1024 units and not (few blocks, and many).  With and without a threshold
+# workgroups that share blocks of one, two and four units a thread, one workgroup per block); blocks halved to those 1024 units and not (few
+# blocks, and many; shared by few workgroups, and by many).  With and without a threshold
 # (bf16): the stored input holds the entries that differ by it or more, the projection is that input's.
 @pytest.mark.parametrize("h,w,ci,co,k,n", [
     (9, 7, 16, 16, 3, 1), (16, 16, 64, 32, 3, 1), (12, 11, 144, 40, 3, 1), (14, 14, 256, 64, 3, 1), (14, 14, 512, 32, 1, 1), (8, 8, 1024, 33, 1, 1),
-    (40, 40, 512, 16, 1, 2), (31, 33, 256, 96, 3, 1), (24, 24, 16, 8, 1, 9),
+    (40, 40, 512, 16, 1, 2), (31, 33, 256, 96, 3, 1), (24, 24, 16, 8, 1, 9), (24, 27, 32, 48, 3, 10), (28, 28, 96, 96, 3, 4), (20, 20, 256, 96, 3, 8),
+    (13, 13, 384, 256, 3, 2), (24, 7, 400, 112, 3, 5),
 ])
 @pytest.mark.parametrize("dt,eps", [(S.I8, 0.0), (S.BF16, 0.0), (S.BF16, 0.25)])
 def test_scatter_kernel_forms(h, w, ci, co, k, n, dt, eps):
