@@ -124,7 +124,10 @@ def _stream_ptr(stream) -> Optional[int]:
         # torch.cuda.current_stream() builds a Stream object, 2.8 us of a step whose C call takes 2.9 (one int8 16 -> 16 layer of
         # 32 x 32, one live video: 6.6 us a step with it, 4.5 without)
         if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+            try:
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+            except AttributeError:  # (torch's own names, which another version need not have)
+                pass
         return torch.cuda.current_stream().cuda_stream or None
     if isinstance(stream, int):
         return stream or None

@@ -146,6 +146,23 @@ def test_binary_band_geometry_terminates_fits_and_covers(tmp_path):
     assert banded >= 40 and fused >= 10
 
 
+@pytest.mark.parametrize("gone", [(), ("_cuda_getCurrentRawStream",), ("_cuda_getDevice",)])
+def test_the_current_stream_whatever_torch_names_it(monkeypatch, gone):
+    """The raw stream comes from functions that are torch's own; without them from the stream object."""
+    import types
+
+    import torch
+    from paper_1802_09723_amd.binding import _stream_ptr
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    for handle in (0x1230, 0):
+        monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 1, raising=False)
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: handle if device == 1 else -1, raising=False)
+        monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=handle))
+        for name in gone:
+            monkeypatch.delattr(torch._C, name)
+        assert _stream_ptr(None) == (handle or None)
+
+
 def _gfx950_functions(path, tmp_path, name):
     """{kernel: [(address, instruction)]} of the library's gfx950 functions whose mangled name holds `name`."""
     objdump = "/opt/rocm/llvm/bin/llvm-objdump"
