@@ -35,8 +35,6 @@ struct BinGeom {
     unsigned int magic_nslab;  // same for d = nslab
     int vec4;                  // 1: a group's words per position are whole 16-byte vectors (wg % 4 == 0, wpp % 4 == 0)
     int fused_ok;              // 1: the band kernel can run the whole step (compare and commit included)
-    unsigned int magic_nkt;    // same for d = 2*nslab (K steps per tap)
-    unsigned int magic_kw;     // same for d = kw
     int bpitch;                // LDS words per staged position of the band kernel: `pitch`, or without its padding
     unsigned int magic_nbands, magic_nblk, magic_nblk32, magic_wo;  // same for d = nbands, blocks of 64 and of 32 channels per group, wo
     const int* steps;          // (device memory) a K step's place in a position's window, in pairs of words: see bin_step_at
@@ -186,8 +184,6 @@ inline bool bin_choose_shape(const rrm_shape& s, BinGeom& g, bool dense = false)
     }
     if ((long long)g.n * g.nbands > 65535) g.band_rows = 0;  // (stream x band is the grid's z dimension)
     g.magic_nslab = bin_magic_for(g.nslab);
-    g.magic_nkt = bin_magic_for(2 * g.nslab);
-    g.magic_kw = bin_magic_for(g.kw);
     g.bth_in = ((g.band_rows > 1 ? g.band_rows : 1) - 1) * s.stride + s.kh;
     g.btw_in = (g.wo - 1) * s.stride + s.kw;
     if (g.band_rows == 0) g.fused_ok = 0;
