@@ -58,6 +58,7 @@ __device__ __forceinline__ unsigned int f32_to_bf16(float f) {  // round to near
 
 constexpr int ST = 256;          // threads that compare and multiply
 constexpr int SCAT_BOOKS = 64;   // ... and of the wavefront that announces the workgroup to the others of its block
+constexpr size_t SCAT_STATIC_LDS = 4 * 1024;  // room for the static arrays of a workgroup
 
 // The differences of two entries each (fp32), as bf16 heads and tails, rounded to nearest even
 __device__ __forceinline__ unsigned int pack_bf16(float a, float b) {
@@ -104,6 +105,7 @@ __global__ __launch_bounds__(ST + (BOOKS ? SCAT_BOOKS : 0)) __attribute__((amdgp
     __shared__ int s_list[ST / 64 + (BOOKS ? 1 : 0)][64];  // (every wavefront makes its own list: nothing to wait for)
     __shared__ unsigned int s_prev;
     __shared__ __align__(16) int s_out[ST / 64][2][32];  // output offsets of an item's rows, or -1
+    static_assert(sizeof(s_flag) + sizeof(s_list) + sizeof(s_prev) + sizeof(s_out) + 64 <= SCAT_STATIC_LDS, "see scatter_lds");
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -521,7 +523,7 @@ __global__ __launch_bounds__(ST + (BOOKS ? SCAT_BOOKS : 0)) __attribute__((amdgp
 
 // A workgroup's LDS beyond 64 KB, dynamic and static (the lists and flags, 2.6 KB at most): for every form of the kernel, once per process
 static hipError_t scatter_lds(size_t lds) {
-    if (lds + 4 * 1024 <= 64 * 1024) return hipSuccess;
+    if (lds + SCAT_STATIC_LDS <= 64 * 1024) return hipSuccess;
     static std::once_flag once;
     static hipError_t attr = hipSuccess;
     std::call_once(once, [] {
