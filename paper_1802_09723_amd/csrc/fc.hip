@@ -37,7 +37,7 @@ __device__ __forceinline__ float bf16_to_f32(unsigned int h) { return __uint_as_
 // One launch per step (Algorithm 1, FC branch; the column walk of Sec. 3.5): workgroup (r, b) owns FCD_SEG bytes
 // worth of output channels of stream b.  Every workgroup compares x_t with the stored input itself (the vector is
 // a few KB: redoing the compare costs less than a second launch), compacts the changed entries (index, difference)
-// in index order into LDS, streams its 64-byte piece of every listed column of W (rows of W^T), and adds the
+// into LDS in a fixed order (thread by thread, a thread's first unit and then its second), streams its 64-byte piece of every listed column of W (rows of W^T), and adds the
 // column sum into its own channels of the stored projection: one owner per output, no partial sums in memory, no
 // atomics on y, the same summation order in every run.  The stored input is committed by whichever workgroup of
 // the stream finishes its compare last (an arrival counter tells it that nobody reads the old values any more);
@@ -91,6 +91,7 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
     // wavefront that streams columns (loads and answers return in order).  A launch of at most a workgroup per compute unit has one
     // wavefront more for that; where two share one there is no room for it (four streams of 9216 -> 4096 bf16, 15.9 us, would take
     // 19.8).  One stream, 4096 -> 4096 int8, 5.4 -> 5.05 us.
+    // It passes the barriers that the others pass, one for one: a barrier added there has to be added here.
     const bool books = g.books != 0;
     if (wave == NTH / 64) {
         unsigned int total = 0;
@@ -438,7 +439,7 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
         }
     }
     // ---- commit: the workgroup that finished comparing last snapshots the input (applied entries only) -------
-    lds_barrier();  // (s_prev was written by thread 0 after the last round's barrier)
+    lds_barrier();  // (s_prev was written after the last round's barrier: by thread 0, or by the announcing wavefront)
     if (s_prev == gridDim.x * gridDim.z - 1u) {
 #pragma unroll
         for (int i = 0; i < KEEP; ++i)
@@ -619,7 +620,10 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
     // 704 threads (and the announcing wavefront: three a SIMD, and so the registers for two units per thread; 960 threads spilled,
     // 10.3 us) instead of 512 where a bf16 row then takes fewer compare rounds and every workgroup still has a compute unit of its
     // own: 9216 -> 4096, 5 % changed, one stream 8.8 -> 6.75 us; a row that is one round either way loses (4096 -> 4096, 25 %,
-    // 6.7 -> 7.25).
+    // 6.7 -> 7.25).  Its lanes sum more products each than those of 1024 threads did, of whose rows two rounds left some lanes fewer, and
+    // fewer wavefronts are added up in order at the end: relative error against 64 bits, 9216 -> 4096, 5 / 25 / 100 % changed, 8.6 / 9.4
+    // / 10.2e-8 and 7.3 / 8.6 / 9.5e-8 so, 7168 -> 2048 8.2 / 8.9 / 9.7 and 6.7 / 8.4 / 9.4, 25088 -> 4096 8.8 / 10.0 / 11.7 and 8.1 / 9.3 /
+    // 11.5, two streams of 16384 -> 2048 8.5 / 9.6 / 10.5 and 7.5 / 9.0 / 10.6.
     const auto rounds = [&](int threads) { return (g.c_in + fcd_round(dtype, threads, false) - 1) / fcd_round(dtype, threads, false); };
     const bool wide = dtype == RRM_BF16_F32 && !g.csc_ptr && (long long)ranges * g.n <= NUM_CU && rounds(704) < rounds(512);
     const int nks = fc_list_splits(dtype, g);

@@ -483,6 +483,9 @@ bool fc_batched_ok(int dtype, const FcGeom& g) {
 //   bf16  4100 -> 1001  16          12.0 / 11.8   32          17.6 / 12.9    4099 ->  270  32  11.6 / 12.4   64  17.0 / 14.8
 //   bf16  1001 ->  500 128          13.0 / 13.8                              2050 -> 1001  32  12.1 / 11.4   64  18.9 / 13.6
 //   bf16  4096 -> 1001   4           7.7 /  9.2   16          12.1 /  9.2
+// (bf16: a stream's own read of W adds 0.045 us a MB of it; the product takes what about two and a half of them add, and 5 us beyond
+// that path's fixed part, 4 without the launch that pads: level at (n - 2.5) w of 128 and 96 MiB, a fit to the rows above.  int8 products
+// are level from a smaller n w on, and with many streams from the bytes of the vectors.)
 bool fc_dense_batched(int dtype, const FcGeom& g) {
     if (!fc_padded(dtype, g)) return true;
     const long long w = (long long)g.c_in * g.c_out * (dtype == RRM_I8_I32 ? 1 : 2), rows = fc_rows_padded(dtype, g) ? 1 : 0;

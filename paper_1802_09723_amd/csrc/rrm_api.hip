@@ -967,7 +967,8 @@ rrm_status rrm_step(rrm_layer* L, const void* x_t, void* y_out, void* hip_stream
         const uintptr_t xa = reinterpret_cast<uintptr_t>(x_t), ya = reinterpret_cast<uintptr_t>(y_out);
         const bool overlap = ya < xa + L->x_bytes && xa < ya + L->y_bytes;  // (then only once the frame has been read)
         if (L->w_rm && L->opt_fc_batched && fc_step_batched(L->dtype, L->fg) && !L->use_csc && L->fg.eps == 0.0f) {
-            // many streams: one product over W, then the sums, the commit and the counts (two launches; the events bracket both)
+            // many streams: one product over W, then the sums, the commit and the counts (two launches, or three: rows off the 64 bytes are
+            // padded, committed and counted ahead of the product; the events bracket all)
             if ((st = prof_mark(L, 1, s)) != RRM_OK) return st;
             out_written = y_out && !overlap;
             RRM_HIP(launch_fc_batched_delta(L->dtype, L->w_rm, x_t, L->x_snap, L->xpad, L->fc_bpart, L->bias, L->y_snap, out_written ? y_out : nullptr,

@@ -377,7 +377,8 @@ hipError_t launch_bin_band_fused(const void* x_t, void* x_snap, unsigned int* ar
 hipError_t launch_fill_bias(int is_float, void* y, const void* bias, long long rows, int c_out, hipStream_t s);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
-// x (caller layout) -> the padded / folded source layout described by g (pad elements are left untouched)
+// x (caller layout) -> the padded / folded source layout described by g (pad elements: zeros or left
+// untouched, zeros from the allocation)
 hipError_t launch_repack(int esize, const void* x, void* dst, const ScanGeom& g, hipStream_t s);
 hipError_t launch_fill_word(void* p, size_t bytes, unsigned int word, hipStream_t s);
 hipError_t launch_probe_mfma(int is_bf16, void* sink, int iters, int workgroups, hipStream_t s);
