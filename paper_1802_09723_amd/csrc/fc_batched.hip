@@ -495,24 +495,26 @@ bool fc_dense_batched(int dtype, const FcGeom& g) {
 
 // Does a step run as one product?  Its cost is a pass over W, the streams' own column walks cost by the number of their workgroups
 // (64 bytes of a stream's channels each), all of which compare their stream's row.  us a step walking, 1 / 5 / 25 % changed, and as
-// a product:
-//   int8  9216 -> 4096   4 streams   256 workgroups    9.4 / 10.2 / 14.6   12.2      8 streams   512   12.4 / 13.4 / 21.2   12.2
-//   int8  4096 -> 4096   4           256               7.2 /  7.4 /  7.7    9.5      8           512   10.1 / 10.7 / 10.9    9.4
-//   int8  2048 -> 1024  24           384               7.6 /  8.3 /  8.6    9.6     32           512    8.8 /  9.0 /  9.7    9.6
-//   int8  1024 ->  512  64           512               7.4 /  7.8 /  8.1    9.6    100           800   10.8 / 11.1 / 11.4    9.6
-//   bf16  9216 -> 4096   4           512              14.3 / 15.6 / 25.3   18.1      6           768   21.2 / 23.7 / 38.5   18.2
-//   bf16  4096 -> 4096   2           256               7.2 /  7.3 /  8.8   10.0      4           512   10.1 / 10.3 / 12.4   10.0
-//   bf16  2048 -> 2048   6           384               8.4 /  8.4 /  8.6    9.2      8           512    9.8 /  9.9 / 10.1    9.3
+// a product (its step where it runs so, its dense layer, 0.1 .. 0.4 us less, elsewhere):
+//   int8  9216 -> 4096   4 streams   256 workgroups    7.1 /  7.7 / 13.7   11.8      8 streams   512   11.0 / 12.3 / 21.6   12.1
+//   int8  4096 -> 4096   4           256               6.3 /  6.8 /  7.1    7.4      8           512   10.0 / 10.7 / 10.9    7.2
+//   int8  2048 -> 1024  24           384               7.5 /  8.3 /  8.6    7.5     32           512    8.6 /  9.1 /  9.6    7.9
+//   int8  1024 ->  512  64           512               7.3 /  7.7 /  8.0    8.5    100           800   10.7 / 11.2 / 11.3    8.4
+//   bf16  9216 -> 4096   4           512              14.0 / 15.4 / 25.2   18.2      6           768   20.9 / 23.7 / 38.3   18.5
+//   bf16  4096 -> 4096   2           256               6.5 /  6.7 /  8.5    9.6      4           512    9.9 / 10.3 / 12.4   10.4
+//   bf16  2048 -> 2048   6           384               8.5 /  8.5 /  8.7    7.5      8           512    9.8 /  9.9 / 10.2    7.6
 // Rows of more than 16 KB: the product is dearer, the line is a quarter later.
 // int8 layers below that line whose walks would read more than 200 MiB of W if everything changed, of a W that the caches hold: level
 // while next to nothing changes, and dear soon.  us a step walking, 1 / 5 / 25 / 50 / 100 % changed, and as a product:
-//   9216 -> 1024  24 streams  216 MiB   10.1 / 10.2 / 15.1 / 18.9 / 25.6   10.8      9216 -> 4096   7   252   11.5 / 11.9 / 19.9 / 30.0 / 40.4   12.4
-//   9216 -> 2048  15          270       11.9 / 12.3 / 16.1 / 21.9 / 30.5   10.3      9216 ->  512  63   284   10.4 / 10.7 / 15.0 / 19.3 / 26.5   11.1
-// and on the other side of it, where a walk is ahead up to a quarter and the product from half on:
-//   9216 -> 1024  16          144        9.6 /  9.8 / 11.3 / 13.5 / 17.9   10.3      4096 -> 1024  31   124    8.7 /  9.3 / 11.2 / 13.4 / 16.5   10.3
-//   4096 -> 4096   7          112        9.4 / 10.0 / 11.9 / 13.5 / 17.0   10.2      9216 ->  256  64   144    9.2 /  9.6 / 10.9 / 13.1 / 17.4   11.4
-//   2048 -> 1024  31           62        8.7 /  9.1 /  9.4 / 11.2 / 12.2    9.8      1024 ->  512  63    32    7.7 /  7.7 /  8.0 /  8.2 /  8.9   10.0
-// (more than 64 streams, whose product is dearer: 9216 -> 256, 127, 286 MiB, 11.6 / 11.8 / 14.8 / 19.6 / 26.8 and 14.4).
+//   9216 -> 1024  24 streams  216 MiB    8.9 /  9.4 / 14.1 / 18.2 / 26.9   10.0      9216 -> 4096   7   252   10.3 / 11.5 / 20.6 / 30.2 / 39.5   12.1
+//   9216 -> 2048  15          270       10.7 / 11.7 / 16.9 / 22.5 / 31.8    9.5      9216 ->  512  63   284    8.6 /  9.4 / 13.9 / 18.6 / 28.0   10.6
+// and on the other side of it, where a walk is ahead, or level, up to a quarter and the product from half on:
+//   9216 -> 1024  16          144        7.2 /  7.5 /  9.9 / 12.3 / 16.7    8.8      4096 -> 1024  31   124    8.6 /  9.2 /  9.6 / 12.0 / 16.5    8.0
+//   4096 -> 4096   7          112        9.3 / 10.0 / 10.1 / 12.7 / 17.2    7.2      9216 ->  256  64   144    7.5 /  8.1 / 10.2 / 12.5 / 17.4   10.5
+//   2048 -> 1024  31           62        8.6 /  8.9 /  9.4 /  9.5 / 11.8    7.6      1024 ->  512  63    32    7.2 /  7.6 /  7.9 /  8.1 /  8.0    8.1
+// (more than 64 streams, whose product is dearer: 9216 -> 256, 127, 286 MiB, 10.0 / 10.6 / 13.6 / 17.9 / 26.7 and 14.0).
+// Both sides have become faster since the line was laid, the product of short rows by more: rows of up to 4096 with a few hundred workgroups
+// are level or ahead as products now, at any change.
 // bf16 layers of 16 and more streams always.
 // Padded layers, whose product is a launch dearer and whose bf16 sums are all of short chains, as exact as the walk's: us a step
 // walking, 2 / 25 % changed, and as a product:

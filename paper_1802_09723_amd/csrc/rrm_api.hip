@@ -567,21 +567,21 @@ rrm_status setup_scatter(rrm_layer* L, const std::vector<unsigned char>& w) {
     // Automatic: layers of few output adds.  Two dependent launches and the per-workgroup set-up of the tile kernels cost more
     // there than the step's work; what the scatter pays more for is its adds into the projection, one per changed position, tap,
     // output channel and part of K.  us a step, scatter against scan + tile, at 5 / 10 / 25 / 50 / 100 % changed, in squares (the
-    // millions, of 2^20: the adds if all changed; calls from the host cannot follow each other in less than 7):
-    //   int8 3 x 3  56 x 56 x 64, n = 2          3.4   7.4 /  7.7 /  7.8 /  9.5 / 14.3   10.9 / 11.3 / 11.9 / 11.9 / 11.2
-    //   int8 1 x 1  64 x 64, 512 -> 64, n = 8    4.0   8.6 /  9.5 / 11.7 / 14.4 / 20.9   17.1 / 18.3 / 20.2 / 24.1 / 26.7
-    //   int8 5 x 5  27 x 27, 96 -> 256           4.5   7.8 /  7.9 / 11.0 / 12.8 / 18.8   10.5 / 11.0 / 10.8 / 11.2 / 10.6
-    //   int8 3 x 3  28 x 28 x 96, n = 8          5.2   7.4 /  7.5 / 10.0 / 13.1 / 18.1   12.9 / 13.4 / 14.3 / 15.4 / 15.4
-    //   int8 3 x 3  14 x 14, 512 -> 256, n = 6   5.2  10.1 / 10.3 / 14.0 / 17.0 / 21.9   12.5 / 12.9 / 13.3 / 13.3 / 13.6
-    //   int8 5 x 5  61 x 61, 16 -> 32, n = 2     5.7   7.7 /  7.8 / 10.3 / 13.7 / 22.6   10.9 / 10.7 / 11.1 / 11.0 / 10.6
-    //   int8 5 x 5  27 x 27, n = 4              17.8  10.5 / 11.4 / 19.6 / 29.0          13.2 / 13.2 / 14.2 / 18.0
-    //   bf16 3 x 3  28 x 28 x 128                0.9   7.5 /  7.6 /  7.7 /  8.7 / 10.3   11.6 / 11.7 / 11.9 / 12.0 / 11.6
-    //   bf16 3 x 3  14 x 14 x 256                0.9   7.1 /  7.3 /  8.5 /  9.9 / 11.9   12.9 / 12.9 / 13.1 / 13.2 / 12.7
-    //   bf16 5 x 5  28 x 28 x 128                2.4   8.3 /  9.2 / 11.7 / 11.7 / 16.5   13.6 / 13.6 / 14.1 / 14.0 / 14.0
-    //   bf16 3 x 3  32 x 32 x 256                4.5  10.8 / 11.9 / 14.4 / 17.7 / 24.8   13.2 / 13.4 / 13.7 / 14.2 / 14.3
-    //   bf16 3 x 3  14 x 14 x 512, n = 2         6.9  17.6 / 19.2 / 22.1 / 24.4 / 37.6   17.2 / 17.8 / 17.8 / 18.1 / 18.4
-    // So the line goes by what video does, a tenth of the positions or so: far ahead there, mostly ahead at a quarter and level
-    // at a half.  A frame in which everything changes costs the layers near it up to twice what the tiles take, which recompute
+    // millions, of 2^20: the adds if all changed; calls from the host cannot follow each other in less than 4.5):
+    //   int8 3 x 3  56 x 56 x 64, n = 2          3.4   4.8 /  5.3 /  6.7 /  9.1 / 14.7   10.3 / 10.7 / 10.9 / 11.2 / 11.1
+    //   int8 1 x 1  64 x 64, 512 -> 64, n = 8    4.0   8.9 /  9.4 / 11.3 / 14.1 / 20.3   16.7 / 17.8 / 20.8 / 24.2 / 26.5
+    //   int8 5 x 5  27 x 27, 96 -> 256           4.5   7.2 /  8.8 / 10.6 / 13.8 / 18.7   10.0 / 10.1 / 10.2 / 10.2 / 10.2
+    //   int8 3 x 3  28 x 28 x 96, n = 8          5.2   6.0 /  7.0 /  9.7 / 13.2 / 17.9   12.1 / 12.7 / 14.4 / 15.0 / 14.9
+    //   int8 3 x 3  14 x 14, 512 -> 256, n = 6   5.2   9.2 / 10.0 / 13.8 / 17.7 / 22.2   11.5 / 11.8 / 12.1 / 12.5 / 12.6
+    //   int8 5 x 5  61 x 61, 16 -> 32, n = 2     5.7   6.0 /  6.7 /  9.4 / 13.2 / 22.4    9.8 / 10.0 / 10.2 / 10.4 / 10.0
+    //   int8 5 x 5  27 x 27, 96 -> 256, n = 4   17.8   9.6 / 11.9 / 19.9 / 29.6 / 47.2   12.3 / 13.0 / 16.6 / 16.6 / 16.3
+    //   bf16 3 x 3  28 x 28 x 128                0.9   5.6 /  6.1 /  7.0 /  7.6 /  9.2   11.0 / 11.1 / 11.3 / 11.3 / 11.4
+    //   bf16 3 x 3  14 x 14 x 256                0.9   5.9 /  6.1 /  7.3 /  8.4 /  9.6   11.9 / 11.9 / 12.0 / 12.1 / 12.1
+    //   bf16 5 x 5  28 x 28 x 128                2.4   7.3 /  8.9 / 10.9 / 12.9 / 16.7   12.6 / 12.8 / 12.8 / 13.0 / 13.3
+    //   bf16 3 x 3  32 x 32 x 256                4.5  10.0 / 12.3 / 14.4 / 18.6 / 23.5   12.5 / 12.6 / 12.8 / 13.1 / 13.3
+    //   bf16 3 x 3  14 x 14 x 512, n = 2         6.9  16.5 / 17.1 / 21.3 / 27.7 / 35.9   16.7 / 16.9 / 17.2 / 17.5 / 17.8
+    // So the line goes by what video does, a tenth of the positions or so: ahead there, about level at a quarter, behind from a
+    // half on.  A frame in which everything changes costs the layers near it up to twice what the tiles take, which recompute
     // above dense_switch_pct: one in a while repays itself.
     // bf16 layers of more than 1024 positions stay on the tiles whatever they would gain: fp32 adds round once per tap and in
     // the order of their arrival, sums of the tile kernel once and in a fixed order.
