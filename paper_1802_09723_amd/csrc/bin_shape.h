@@ -35,6 +35,9 @@ struct BinGeom {
     unsigned int magic_nslab;  // same for d = nslab
     int vec4;                  // 1: a group's words per position are whole 16-byte vectors (wg % 4 == 0, wpp % 4 == 0)
     int fused_ok;              // 1: the band kernel can run the whole step (compare and commit included)
+    // (Nothing.  The same instructions take 6.10 us a step with the fields after it here and 6.23 eight bytes lower: 14 x 14, 512 -> 512, one
+    // stream, 10 %; 256 -> 256, two, 5.90 and 6.00.  Only their places among the kernel's arguments differ; the cause is not known.)
+    int gap[2];
     int bpitch;                // LDS words per staged position of the band kernel: `pitch`, or without its padding
     unsigned int magic_nbands, magic_nblk, magic_nblk32, magic_wo;  // same for d = nbands, blocks of 64 and of 32 channels per group, wo
     const int* steps;          // (device memory) a K step's place in a position's window, in pairs of words: see bin_step_at
