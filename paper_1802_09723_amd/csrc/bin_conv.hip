@@ -292,14 +292,17 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
 #pragma unroll
         for (int i = 0; i < KU; ++i) fetch_w(w[i], min(kpart + i * KPARTS, nk - 1));
     };
-    // What does not depend on the staged window, while its loads are on their way.  (The weights too where a compute unit has one
-    // workgroup; where two share it their addresses only hold up the window: 28 x 28, 256 -> 256, 8 streams, 10.1 us and 10.9 so.)
+    // What does not depend on the staged window, while its loads are on their way.  The weights and the table too where a compute unit
+    // has one workgroup.  Where two share it they are fetched after the window, which they would hold up: the weights 28 x 28, 256 -> 256, 8
+    // streams, 10.1 us and 10.9 so; the table, a load on its way through the loop that stages, 36 x 36, 256 -> 184 1 x 1, 59 streams, 16.9 and
+    // 18.0 (17.0 before there was a table), 28 x 28, 128 -> 109, 30 streams, 14.2 and 15.1, 28 x 28, 256 -> 256, 64 streams, 19.3 and 20.5.
+    auto fetch_first = [&]() __attribute__((always_inline)) {
+        at0 = g.steps[min(kpart + lane * KPARTS, nk - 1)];
+        first_frags();
+    };
     auto ahead = [&]() __attribute__((always_inline)) {
         clear_lds();
-        if (TILES > 0) {
-            at0 = g.steps[min(kpart + lane * KPARTS, nk - 1)];
-            if (TILES == 1) first_frags();
-        }
+        if (TILES == 1) fetch_first();
         lds_barrier();
     };
     // ---- stage m and m & ~x of the band's input window ----------------------------------------
@@ -382,7 +385,7 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
         }
     }
     lds_barrier();
-    if (TILES > 1) first_frags();
+    if (TILES > 1) fetch_first();
     // this workgroup has read the stored input for the last time
     // (thread 0 keeps the answer to the end: stored at once, it would hold up the list by a memory round trip)
     if (FUSED && tid == 0) arrived_before = atomicAdd(&arrive[b], 1u);
