@@ -229,7 +229,9 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
                                                        unsigned int* arrive,
                                                        const uint2* __restrict__ wband, const int* __restrict__ bias,
                                                        int* y, BinGeom g, DevStats* __restrict__ stats) {
-    fetch_args<7 * sizeof(void*) + sizeof(BinGeom) + sizeof(void*)>();
+    // (Not where two workgroups share a compute unit: 12 x 43, 256 -> 480, 13 streams, 10.9 us a step without and 11.1 so, 8 x 22, 64 -> 164, 56
+    // streams, 10.65 and 10.8; 35 x 35, 384 -> 144 5 x 5 dense, two streams, 11.65 and 11.8)
+    if (TILES == 1) fetch_args<7 * sizeof(void*) + sizeof(BinGeom) + sizeof(void*)>();
     constexpr int KPARTS = TILES > 0 ? BAND_WAVES / TILES : 1, PASS = 32 * TILES;
     constexpr int CPT = 4 * TILES;  // channels per thread of a pass' results (CB = 1: half of the threads have none)
     extern __shared__ uint4 smem[];
