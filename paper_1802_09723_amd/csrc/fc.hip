@@ -142,10 +142,12 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
         const long long off = (row + e0) * ESIZE, total_bytes = (long long)g.n * g.c_in * ESIZE;
         load_units_at<ESIZE>(x_t, x_snap, off, total_bytes, (g.c_in - e0) * ESIZE, a, s);
     };
-    // difference of a unit: mask of the entries to apply, and the unit's new snapshot.  CSC: their values too, every entry's at once; the
-    // other forms work them out entry by entry, which saves registers (pruned 9216 -> 4096, 5 / 25 % changed, so and like those: int8 7.95 /
-    // 11.25 us a step and 8.25 / 11.6, bf16 20.65 / 31.65 and 20.9 / 31.9)
-    auto diff_unit = [&](const uint4& a, const uint4& s, val_t (&dv)[CSC ? PV : 1], unsigned int& mask, uint4& n_out) {
+    // difference of a unit: mask of the entries to apply, and the unit's new snapshot.  VALUES: their values too, every entry's at once (us
+    // a step so and entry by entry, as the list is made: 1024 -> 4096 int8, 7 streams, 9.25 and 9.4, 2048 -> 2048, nine, 7.95 and 8.2, 4096 ->
+    // 1024 bf16, twelve, 8.9 and 9.05; pruned 9216 -> 4096, 5 / 25 % changed, int8 7.95 / 11.25 and 8.25 / 11.6).  Not the forms of two units a
+    // thread and of ragged bf16 rows, which have no registers for them (5001 -> 1501 bf16, 7 streams, 13.9 and 10.5).
+    constexpr bool VALUES = CSC || (UPT == 1 && (ROWS16 || DT == RRM_I8_I32));
+    auto diff_unit = [&](const uint4& a, const uint4& s, val_t (&dv)[VALUES ? PV : 1], unsigned int& mask, uint4& n_out) {
         mask = 0;
         n_out = a;
         if (!((a.x ^ s.x) | (a.y ^ s.y) | (a.z ^ s.z) | (a.w ^ s.w))) return;
@@ -156,7 +158,7 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
             if (DT == RRM_I8_I32) {
                 const int xa = (int)(signed char)(aw[e >> 2] >> (8 * (e & 3)));
                 const int xb = (int)(signed char)(sw[e >> 2] >> (8 * (e & 3)));
-                if constexpr (CSC) dv[e] = (val_t)(xa - xb);
+                if constexpr (VALUES) dv[e] = (val_t)(xa - xb);
                 if (xa != xb) mask |= 1u << e;
             } else {
                 // (truncation threshold, Sec. 3.4 "Improving sparsity": a difference below g.eps is neither
@@ -164,7 +166,7 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
                 const unsigned int xa = (aw[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
                 const unsigned int xb = (sw[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
                 const float d = bf16_to_f32(xa) - bf16_to_f32(xb);
-                if constexpr (CSC) dv[e] = (val_t)d;
+                if constexpr (VALUES) dv[e] = (val_t)d;
                 if (xa != xb) {
                     if (fabsf(d) < g.eps) {
                         ++ntrunc;
@@ -243,8 +245,8 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
         int running = 0;
         {
             unsigned int mask[UPT];
-            static_assert(!CSC || UPT == 1, "one unit's values");
-            val_t dv[CSC ? PV : 1];
+            static_assert(!VALUES || UPT == 1, "one unit's values");
+            val_t dv[VALUES ? PV : 1];
             uint4 a[UPT], s[UPT];
             int cnt = 0;
             const bool all = g.c_in - base > NTH * PV;  // (a shorter round: one unit per thread)
@@ -283,7 +285,7 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
 #pragma unroll
                     for (int e = 0; e < PV; ++e)
                         if (mask[k] & (1u << e)) {
-                            list[pos] = entry((tid + k * NTH) * PV + e, CSC ? dv[CSC ? e : 0] : value(a[k], s[k], e));
+                            list[pos] = entry((tid + k * NTH) * PV + e, VALUES ? dv[VALUES ? e : 0] : value(a[k], s[k], e));
                             ++pos;
                         }
                 }
@@ -461,7 +463,7 @@ __global__ __launch_bounds__(NTH + FCD_BOOKS) void fc_delta_kernel(const unsigne
                 load_unit(e0, a, s);
                 const unsigned int nt0 = ntrunc;
                 const float tq0 = tsq;
-                val_t dv[CSC ? PV : 1];
+                val_t dv[VALUES ? PV : 1];
                 diff_unit(a, s, dv, mask, nw);
                 ntrunc = nt0;  // (already counted)
                 tsq = tq0;
@@ -637,7 +639,10 @@ hipError_t launch_fc_delta(int dtype, const void* x_t, void* x_snap, const void*
     const bool few = (long long)ranges * g.n * nks <= NUM_CU;  // a compute unit for every workgroup
     auto form = [&]<bool CSC>() {
         if (dtype == RRM_I8_I32) {
-            if (g.vec_ok) return fc_delta_kernel<RRM_I8_I32, CSC, true, 512, !CSC>;
+            // (where two workgroups share a compute unit two units a thread only for rows that are one round so: 5760 -> 3296, 7 streams, 9.65 us and
+            // 9.5 with one)
+            if (g.vec_ok)
+                return few || g.c_in > fcd_round(dtype, 512, false) ? fc_delta_kernel<RRM_I8_I32, CSC, true, 512, !CSC> : fc_delta_kernel<RRM_I8_I32, CSC, true, 512, false>;
             // (a form of two ragged units a thread has no registers for a second workgroup on its compute unit: 22 streams of 599 -> 990,
             // 352 workgroups, 10.8 us and 8.6 with one)
             return !CSC && few ? fc_delta_kernel<RRM_I8_I32, CSC, false, 512, !CSC> : fc_delta_kernel<RRM_I8_I32, CSC, false, 512, false>;

@@ -150,10 +150,11 @@ def test_fc_step_compare_rounds(ci, co, n, dt):
 
 # Rounds of two units per thread (int8 up to 12288 entries, bf16 of the larger form up to 11264) and their neighbours: the second
 # unit's first and last thread, a second round of one unit, two full rounds, ragged rows.  One workgroup per
-# compute unit (the wavefront that announces it) and more (many channels and streams: thread 0 does).
+# compute unit (the wavefront that announces it) and more (many channels and streams: thread 0 does; int8 up to 8192 entries in a form of
+# one unit).
 @pytest.mark.parametrize("ci,co,n", [
     (8192, 64, 1), (8208, 48, 1), (12288, 64, 2), (12304, 32, 1), (24576, 32, 1), (4096, 64, 1), (4104, 32, 2), (5632, 32, 1), (5640, 64, 1),
-    (11264, 32, 1), (11272, 32, 1), (9217, 32, 1), (12289, 16, 2), (9216, 8256, 3),
+    (11264, 32, 1), (11272, 32, 1), (9217, 32, 1), (12289, 16, 2), (9216, 8256, 3), (4112, 208, 70), (8192, 208, 70), (8208, 208, 70),
 ])
 @pytest.mark.parametrize("dt", [S.I8, S.BF16])
 def test_fc_step_rounds_of_two_units(ci, co, n, dt):
