@@ -184,7 +184,8 @@ __global__ __launch_bounds__(256) void bin_conv_kernel(const unsigned int* __res
 // holds far fewer).  v_mfma_f32_32x32x64_f8f6f4 multiplies 32 output channels x 32 listed positions x 64 input
 // channels of one tap in 32 cycles, where the popcount form takes 256 vector cycles.
 // Measured (28 x 28, 256 -> 256 channels, 64 streams, 5 % of the values flipping): 36.8 us a step with popcounts, 23.0 with weights
-// fetched as nibbles (16 bytes a lane, K step and 32 channels: what the vector cache delivers per clock was the bound), 21.0 so;
+// fetched as nibbles (16 bytes a lane, K step and 32 channels: what the vector cache delivers per clock was the bound), 21.0 so, 19.3 with
+// the steps' table;
 // one stream of 14 x 14, 512 -> 512 channels, 10 %: 16.8, 10.3 and 7.4 (6.3 with shorter lists and the steps' table).
 //
 // 32 values of a word are 4 registers of E2M1 nibbles; nibble j of register i is value 4 j + (1, 0, 3, 2)[i].  Of a difference
@@ -288,7 +289,7 @@ __global__ __launch_bounds__(BAND_THREADS, 4) void bin_band_kernel(const unsigne
     };
     // Where the wavefront's K steps lie in a window, from a table, a lane each (up to 64 of them).  Worked out, it was a chain of some
     // twenty scalar instructions a step that every pass waited for (a dependent instruction takes 8 cycles): with the table, 14 x 14, 512 ->
-    // 512, 10 %, 64 streams, 26.0 -> 24.0 us a step, one stream 7.5 -> 6.9; 28 x 28, 448 -> 256 dense, 8 streams, 16.6 -> 14.5.
+    // 512, 10 %, 64 streams, 24.6 -> 21.7 us a step, one stream 7.5 -> 6.9; 28 x 28, 448 -> 256 dense, 8 streams, 16.6 -> 14.5.
     int at0 = 0;
     auto first_frags = [&]() __attribute__((always_inline)) {
 #pragma unroll
